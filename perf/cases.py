@@ -155,6 +155,38 @@ def _segments(gen, case):
     return _normal(gen, shape), _normal(gen, shape)
 
 
+def _decode_inputs(case, seed):
+    """Compressed segments, their lengths (None: full), tail rows (keys rotated), the new tokens' q, k, v."""
+    B, S, kt, tail, T, hq, hkv, d = (case[k] for k in ("batch", "segs", "keep_tokens", "tail", "tokens", "hq", "hkv", "d"))
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    kc, vc = _segments(gen, case)
+    seg_len = None
+    if case["ragged"]:
+        seg_len = torch.randint(kt // 2, kt + 1, (B, S), generator=gen, device="cuda", dtype=torch.int32)
+    k_tail, v_tail = _normal(gen, (B, tail, hkv, d)), _normal(gen, (B, tail, hkv, d))
+    return (kc, vc, seg_len, k_tail, v_tail, _normal(gen, (T, B, 1, hq, d), 2.0), _normal(gen, (T, B, 1, hkv, d)),
+            _normal(gen, (T, B, 1, hkv, d)))
+
+
+def _cache8_inputs(case, seed):
+    """Source rows of K and V, the kept chunks and tokens, the query block's q, k, v."""
+    B, C, rows, S, kt, nq, hq, hkv, d = (case[k] for k in ("batch", "chunks", "rows", "segs", "keep_tokens", "nq", "hq", "hkv", "d"))
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    src, i32 = (B, C, rows, hkv, d), torch.int32
+    chunk_idx = torch.rand((B, C), generator=gen, device="cuda").argsort(dim=1)[:, :S].to(i32).contiguous()
+    tok_idx = torch.rand((B, S, hkv, rows), generator=gen, device="cuda").argsort(dim=-1)[..., :kt]
+    tok_idx = tok_idx.sort(dim=-1).values.to(i32).contiguous()
+    return (_normal(gen, src), _normal(gen, src), chunk_idx, tok_idx, _normal(gen, (B, nq, hq, d), 2.0),
+            _normal(gen, (B, nq, hkv, d)), _normal(gen, (B, nq, hkv, d)))
+
+
+def _selfinfo_inputs(case, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    C, T, V = case["chunks"], case["tokens"], case["vocab"]
+    return (_normal(gen, (C, T, V), 2.0),
+            torch.randint(0, V, (T,), generator=gen, device="cuda", dtype=torch.int32))
+
+
 def prepare(case, seed):
     kind = case["kind"]
     if kind in ("layer", "prefill", "stream"):
@@ -170,51 +202,39 @@ def prepare(case, seed):
         if case["ragged"]:
             s["dev_lens"] = torch.tensor(lens, dtype=torch.int32, device="cuda")
         return s
-    gen = torch.Generator(device="cuda").manual_seed(seed)
     if kind in ("decode", "decode8"):
         B, S, kt, tail, T, hq, hkv, d = (case[k] for k in ("batch", "segs", "keep_tokens", "tail", "tokens", "hq", "hkv", "d"))
-        kc, vc = _segments(gen, case)
-        seg_len = None
-        if case["ragged"]:
-            seg_len = torch.randint(kt // 2, kt + 1, (B, S), generator=gen, device="cuda", dtype=torch.int32)
-        k_tail, v_tail = _normal(gen, (B, tail, hkv, d)), _normal(gen, (B, tail, hkv, d))
+        kc, vc, seg_len, k_tail, v_tail, q, k, v = _decode_inputs(case, seed)
         if kind == "decode":
             cache = DecodeCache(B, S, kt, hq, hkv, d, case["base"])
         else:
             cache = DecodeCacheFp8(B, S, kt, tail + T, hq, hkv, d, case["base"])
         cache.load(kc, vc, seg_len, k_tail, v_tail)
-        return {"case": case, "cache": cache,
-                "q": _normal(gen, (T, B, 1, hq, d), 2.0), "k": _normal(gen, (T, B, 1, hkv, d)),
-                "v": _normal(gen, (T, B, 1, hkv, d)),
+        return {"case": case, "cache": cache, "q": q, "k": k, "v": v,
                 "outs": torch.empty((T, B, 1, hq, d), dtype=BF16, device="cuda")}
+    f32 = torch.float32
     if kind == "cache8":
         B, C, rows, S, kt, nq, hq, hkv, d = (case[k] for k in ("batch", "chunks", "rows", "segs", "keep_tokens", "nq", "hq", "hkv", "d"))
-        src = (B, C, rows, hkv, d)
-        f32, i32 = torch.float32, torch.int32
-        chunk_idx = torch.rand((B, C), generator=gen, device="cuda").argsort(dim=1)[:, :S].to(i32).contiguous()
-        tok_idx = torch.rand((B, S, hkv, rows), generator=gen, device="cuda").argsort(dim=-1)[..., :kt]
+        k_src, v_src, chunk_idx, tok_idx, q, k_self, v_self = _cache8_inputs(case, seed)
         kc = torch.empty((B, S, hkv, kt, d), dtype=BF16, device="cuda")
-        return {"case": case, "k_src": _normal(gen, src), "v_src": _normal(gen, src), "chunk_idx": chunk_idx,
-                "tok_idx": tok_idx.sort(dim=-1).values.to(i32).contiguous(),
+        return {"case": case, "k_src": k_src, "v_src": v_src, "chunk_idx": chunk_idx, "tok_idx": tok_idx,
                 "kc": kc, "vc": torch.empty_like(kc),
                 "k_amax": torch.empty((B, S, hkv), dtype=f32, device="cuda"),
                 "v_amax": torch.empty((B, S, hkv), dtype=f32, device="cuda"),
                 "k8": fp8_alloc(B, S, hkv, kt, d), "v8": fp8_alloc(B, S, hkv, kt, d),
                 "k_scale": torch.empty((B, S, hkv), dtype=f32, device="cuda"),
                 "v_scale": torch.empty((B, S, hkv), dtype=f32, device="cuda"),
-                "q": _normal(gen, (B, nq, hq, d), 2.0), "k_self": _normal(gen, (B, nq, hkv, d)),
-                "v_self": _normal(gen, (B, nq, hkv, d)),
+                "q": q, "k_self": k_self, "v_self": v_self,
                 "out": torch.empty((B, nq, hq, d), dtype=BF16, device="cuda"),
                 "lse": torch.empty((B, hq, nq), dtype=f32, device="cuda"),
                 "ws": pc.alloc_workspace(pc.pc_parallel_attn_fp8_workspace_bytes(B, nq, S, kt, 0, hq, hkv, d, True))}
-    C, T, V, keep = (case[k] for k in ("chunks", "tokens", "vocab", "keep_chunks"))
-    logits = _normal(gen, (C, T, V), 2.0)
-    targets = torch.randint(0, V, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    C, T, keep = (case[k] for k in ("chunks", "tokens", "keep_chunks"))
+    logits, targets = _selfinfo_inputs(case, seed)
     return {"case": case, "logits": logits, "targets": targets,
-            "nll": torch.empty((C, T), dtype=torch.float32, device="cuda"),
-            "info": torch.empty((C,), dtype=torch.float32, device="cuda"),
+            "nll": torch.empty((C, T), dtype=f32, device="cuda"),
+            "info": torch.empty((C,), dtype=f32, device="cuda"),
             "idx": torch.empty((keep,), dtype=torch.int32, device="cuda"),
-            "top": torch.empty((keep,), dtype=torch.float32, device="cuda")}
+            "top": torch.empty((keep,), dtype=f32, device="cuda")}
 
 
 # ------------------------------------------------------------------------------------------ one pass
@@ -319,3 +339,157 @@ def tolerance(case):
     # Scores are good to a few 1e-6, so of two tokens that close at the k-th place
     # either may be kept: the kept list of one (chunk, head) then shifts between their places.
     return {"rel": 1e-2, "differ": 0.01}
+
+
+# ------------------------------------------------------------------------------------------ in 64 bits
+def _rope64(x, pos, base):
+    """Rotation of the pairs (i, i + d / 2) of x [..., rows, d] at the positions pos [rows]."""
+    d = x.shape[-1]
+    theta = base ** (-2.0 * torch.arange(d // 2, dtype=torch.float64, device=x.device) / d)
+    ang = pos.to(torch.float64)[:, None] * theta
+    c, s, a, b = ang.cos(), ang.sin(), x[..., :d // 2], x[..., d // 2:]
+    return torch.cat([a * c - b * s, b * c + a * s], dim=-1)
+
+
+def _attend64(q, k, v, offset=None, votes=0):
+    """softmax(q k^T / sqrt(d)) v for q [rows, d] and its logsumexp, rows in blocks; row r sees the keys up to
+    r + offset (None: all); votes: also the sum over the last `votes` rows of the probability of every key."""
+    n, d = q.shape
+    out, lse = torch.empty_like(q), torch.empty(n, dtype=torch.float64, device=q.device)
+    score = torch.zeros(k.shape[0], dtype=torch.float64, device=q.device) if votes else None
+    kt = k.t().contiguous()
+    for r0 in range(0, n, 2048):
+        r1 = min(r0 + 2048, n)
+        m = k.shape[0] if offset is None else min(k.shape[0], r1 + offset)
+        s = (q[r0:r1] @ kt[:, :m].contiguous()) / math.sqrt(d)
+        if offset is not None:
+            rows = torch.arange(r0, r1, device=q.device)[:, None]
+            s.masked_fill_(torch.arange(m, device=q.device)[None] > rows + offset, float("-inf"))
+        lse[r0:r1] = torch.logsumexp(s, dim=1)
+        p = s.sub_(lse[r0:r1, None]).exp_()
+        out[r0:r1] = p @ v[:m]
+        if r1 > n - votes:
+            score[:m] += p[max(0, n - votes - r0):].sum(dim=0)
+    return out, lse, score
+
+
+def _exact_layer(case, seed):
+    C, w, wq, hq, hkv, d, obs = (case[k] for k in ("chunks", "w", "wq", "hq", "hkv", "d", "obs"))
+    kc, kt, stream = case["keep_chunks"], case["keep_tokens"], case["kind"] == "stream"
+    q, k, v, lens = _layer_inputs(case, seed)
+    G, L, dev, f64 = hq // hkv, w + wq, "cuda", torch.float64
+    tok = torch.zeros((C, hkv, w), dtype=f64, device=dev)
+    o, lse, kr, q0, k_kept = [], [], [], None, []
+    for c, n in enumerate(lens):
+        pos = torch.arange(n + wq, device=dev)
+        qc = _rope64(q[c, :n + wq].transpose(0, 1).to(f64), pos, case["base"])
+        kcx = _rope64(k[c, :n + wq].transpose(0, 1).to(f64), pos, case["base"])
+        vcx = v[c, :n + wq].transpose(0, 1).to(f64)
+        oc, lc = [], []
+        for h in range(hq):
+            x, y, z = _attend64(qc[h], kcx[h // G], vcx[h // G], 0, obs)
+            oc.append(x.float()); lc.append(y); tok[c, h // G, :n] += z[:n]
+        o.append(torch.stack(oc, dim=1)); lse.append(torch.stack(lc)); kr.append(kcx.transpose(0, 1).float())
+        if c == 0 and kc:
+            q0, k_self, v_self = qc[:, n:], kcx[:, n:], vcx[:, n:]
+    chunk = tok.sum(dim=(1, 2))
+    out = {"chunk_score": chunk}
+    if case["ragged"]:
+        out.update(tok_score=tok, o=o, lse=lse, k_rope=kr, tok_cnt=None)
+    elif stream:                     # the batch buffers hold the last batch, behind it rows of the one before
+        b = min(case["batch"], C)
+        last = [max(c for c in range(C) if c % b == i) for i in range(b)]
+        out.update(o=torch.stack([o[c] for c in last]), lse=torch.stack([lse[c] for c in last]),
+                   k_rope=torch.stack([kr[c] for c in last]))
+    else:
+        out.update(tok_score=tok, o=torch.stack(o), lse=torch.stack(lse), k_rope=torch.stack(kr))
+    if kc:
+        go = torch.empty((1, wq, hq, d), dtype=f64, device=dev)
+        gl = torch.empty((1, hq, wq), dtype=f64, device=dev)
+        kept = chunk.argsort(descending=True, stable=True)[:kc].tolist()
+        for g in range(hkv):
+            ks, vs = [], []
+            for c in kept:
+                t = tok[c, g, :lens[c]].clone()
+                if case["cls"]:
+                    head = t[:case["cls"]]
+                    head[head > case["lam"]] = -1.0
+                idx = t.argsort(descending=True, stable=True)[:kt]
+                idx = idx[t[idx] >= 0]
+                ks.append(kr[c][idx, g].to(f64)); vs.append(v[c, idx, g].to(f64))
+            ks, vs = torch.cat(ks + [k_self[g]]), torch.cat(vs + [v_self[g]])
+            for h in range(g * G, (g + 1) * G):
+                go[0, :, h], gl[0, h], _ = _attend64(q0[h], ks, vs, ks.shape[0] - wq)
+        out.update(global_o=go, global_lse=gl, tok_idx=None)
+        out.update({"queue_id": None, "queue_score": None, "queue_slot": None} if stream else {"chunk_idx": None})
+    return out
+
+
+def _exact_decode(case, seed):
+    B, tail, T, hq, hkv, d = (case[k] for k in ("batch", "tail", "tokens", "hq", "hkv", "d"))
+    kc, vc, seg_len, k_tail, v_tail, q, k, v = _decode_inputs(case, seed)
+    if case["kind"] == "decode8":
+        kc, vc = ((c * s[..., None, None]).to(torch.float64) for c, s in (_e4m3(x, seg_len) for x in (kc, vc)))
+    G, f64 = hq // hkv, torch.float64
+    pos = 7680 + tail + torch.arange(T, device="cuda")
+    outs = torch.empty((T, B, 1, hq, d), dtype=f64, device="cuda")
+    lse = torch.empty((B, hq, 1), dtype=f64, device="cuda")
+    for b in range(B):
+        n = [case["keep_tokens"]] * case["segs"] if seg_len is None else seg_len[b].tolist()
+        for g in range(hkv):
+            new = _rope64(k[:, b, 0, g].to(f64), pos, case["base"])
+            ks = torch.cat([kc[b, s, g, :m].to(f64) for s, m in enumerate(n)] + [k_tail[b, :, g].to(f64), new])
+            vs = torch.cat([vc[b, s, g, :m].to(f64) for s, m in enumerate(n)] + [v_tail[b, :, g].to(f64), v[:, b, 0, g].to(f64)])
+            for h in range(g * G, (g + 1) * G):
+                x, y, _ = _attend64(_rope64(q[:, b, 0, h].to(f64), pos, case["base"]), ks, vs, ks.shape[0] - T)
+                outs[:, b, 0, h], lse[b, h, 0] = x, y[-1]
+    return {"outs": outs, "lse": lse, "tail_len": None, "k_tail": None, "v_tail": None}
+
+
+def _e4m3(x, seg_len=None):
+    """The 8-bit cache's values: E4M3 codes (as numbers) of the valid rows of x [B, S, hkv, rows, d] over a scale."""
+    x = x.float()
+    if seg_len is not None:
+        x = x * (torch.arange(x.shape[3], device=x.device) < seg_len[:, :, None, None])[..., None]
+    scale = x.abs().amax(dim=(3, 4)) / 448.0
+    scale = torch.where(scale > 0, scale, torch.ones_like(scale))
+    return (x / scale[..., None, None]).to(torch.float8_e4m3fn).float(), scale
+
+
+def _exact_cache8(case, seed):
+    B, C, S, kt, nq, hq, hkv, d = (case[k] for k in ("batch", "chunks", "segs", "keep_tokens", "nq", "hq", "hkv", "d"))
+    k_src, v_src, chunk_idx, tok_idx, q, k_self, v_self = _cache8_inputs(case, seed)
+    G, f64 = hq // hkv, torch.float64
+    b_, g_ = torch.arange(B, device="cuda").view(B, 1, 1, 1), torch.arange(hkv, device="cuda").view(1, 1, hkv, 1)
+    where = (b_, chunk_idx.long()[:, :, None, None], tok_idx.long(), g_)
+    kc, vc = k_src[where], v_src[where]
+    (k8, k_scale), (v8, v_scale) = _e4m3(kc), _e4m3(vc)
+    out = torch.empty((B, nq, hq, d), dtype=f64, device="cuda")
+    lse = torch.empty((B, hq, nq), dtype=f64, device="cuda")
+    pos = case["rows"] + torch.arange(nq, device="cuda")
+    for b in range(B):
+        for g in range(hkv):
+            ks = torch.cat([(k8[b, :, g].to(f64) * k_scale[b, :, g, None, None]).flatten(0, 1), k_self[b, :, g].to(f64)])
+            vs = torch.cat([(v8[b, :, g].to(f64) * v_scale[b, :, g, None, None]).flatten(0, 1), v_self[b, :, g].to(f64)])
+            for h in range(g * G, (g + 1) * G):
+                out[b, :, h], lse[b, h], _ = _attend64(_rope64(q[b, :, h].to(f64), pos, case["base"]), ks, vs, ks.shape[0] - nq)
+    return {"kc": None, "vc": None, "k_amax": None, "v_amax": None, "k8": None, "v8": None,
+            "k_scale": k_scale, "v_scale": v_scale, "out": out, "lse": lse}
+
+
+def _exact_selfinfo(case, seed):
+    logits, targets = _selfinfo_inputs(case, seed)
+    nll = []
+    for c in range(case["chunks"]):
+        x = logits[c].to(torch.float64)
+        nll.append(torch.logsumexp(x, dim=1) - x.gather(1, targets.long()[:, None])[:, 0])
+    nll = torch.stack(nll)
+    return {"nll": nll, "info": -nll.sum(dim=1), "idx": None, "top": None}
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits (codes, copies and lists of places: None)."""
+    kind = case["kind"]
+    if kind in ("layer", "prefill", "stream"):
+        return _exact_layer(case, seed)
+    return {"decode": _exact_decode, "decode8": _exact_decode, "cache8": _exact_cache8, "selfinfo": _exact_selfinfo}[kind](case, seed)
