@@ -352,10 +352,66 @@ __global__ __launch_bounds__(D) void merge_kernel(PcMergeArgs a) {
     a.lse_out[((long long)b * a.n_q_heads + h) * a.n_q + t] = den > 0.f ? M + logf(den) : -INFINITY;
 }
 
+// Merge for a block of query rows: bound by reading the fp32 partials once.  A thread owns 4
+// values of one output row (D / 4 threads a row, 16-byte loads, whole rows per wavefront) and
+// computes the row's weights for itself: the partials' logsumexps are the same address for all
+// threads of a row.
+template <int D>
+__global__ __launch_bounds__(256) void merge_rows_kernel(const float* __restrict__ part_o,
+                                                         const float* __restrict__ part_lse,
+                                                         uint16_t* __restrict__ out,
+                                                         float* __restrict__ lse_out, long long n_rows,
+                                                         int n_q, int n_q_heads, int n_parts) {
+  constexpr int TPR = D / 4;
+  const long long row = ((long long)blockIdx.x * 256 + threadIdx.x) / TPR;      // (b, t, h)
+  const int d4 = (threadIdx.x % TPR) * 4;
+  if (row >= n_rows) return;
+  const long long th = (long long)n_q * n_q_heads, b = row / th, in_b = row % th;
+  const float* lse = part_lse + b * n_parts * th + in_b;
+  const float* po = part_o + (b * n_parts * th + in_b) * D + d4;
+  float M = -INFINITY;
+  for (int p = 0; p < n_parts; ++p) M = fmaxf(M, lse[p * th]);
+  floatx4 num = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
+  if (M > -INFINITY) {
+#pragma unroll 4
+    for (int p = 0; p < n_parts; ++p) {
+      const float w = expf(lse[p * th] - M);
+      const floatx4 x = __builtin_nontemporal_load((const floatx4*)(po + p * th * D));
+      den += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] += w * x[e];
+    }
+  }
+  float y[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = den > 0.f ? num[e] / den : 0.f;
+  *(uint2*)(out + row * D + d4) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+  if (lse_out && d4 == 0)
+    lse_out[(b * n_q_heads + in_b % n_q_heads) * n_q + in_b / n_q_heads] = den > 0.f ? M + logf(den) : -INFINITY;
+}
+
+int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, float* lse_out, int batch,
+                         int n_q, int n_q_heads, int head_dim, int n_parts, hipStream_t st) {
+  const long long n_rows = (long long)batch * n_q * n_q_heads;
+  const long long blocks = (n_rows * (head_dim / 4) + 255) / 256;
+  if (blocks == 0) return PC_OK;
+  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_MERGE, st);
+  const dim3 grid((unsigned)blocks), block(256);
+  if (head_dim == 128)
+    hipLaunchKernelGGL(merge_rows_kernel<128>, grid, block, 0, st, part_o, part_lse, (uint16_t*)out, lse_out,
+                       n_rows, n_q, n_q_heads, n_parts);
+  else
+    hipLaunchKernelGGL(merge_rows_kernel<64>, grid, block, 0, st, part_o, part_lse, (uint16_t*)out, lse_out,
+                       n_rows, n_q, n_q_heads, n_parts);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+
 // ------------------------------------------------------------------------------------------
-// Rotate the query rows of the global attention at positions pos0 + t (fp64 angles; pos0 < 0:
-// the rows are already rotated) and multiply them by `mul` before the one rounding to bf16 (the
-// tile kernel wants its query operand scaled by softmax scale x log2(e); 1 for the split-KV kernel).
+// Rotate the query rows of the split-KV kernel at positions pos0 + t (fp64 angles; pos0 < 0:
+// the rows are already rotated) and multiply them by `mul` before the one rounding to bf16.
 __global__ void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
                               long long n_pairs, int n_q, int n_heads, int D, int pos0,
                               double log_base, double mul) {

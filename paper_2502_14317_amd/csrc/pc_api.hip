@@ -167,7 +167,7 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
   void* kr = k_rope;                                       // nullable: then only the images are written
   const int L = s->chunk_len + s->query_len, D = s->head_dim;
 
-  rc = pc_launch_rope_table(table, L, D, s->rope_base, st);
+  rc = pc_launch_rope_table(table, 0, L, D, s->rope_base, st);
   if (rc != PC_OK) return rc;
   if (tok_score) {
     // the first score pass reads and rotates every key anyway: it also writes the rotated keys
@@ -181,13 +181,10 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
 
   PcFlashArgs a = {};
   a.q = q; a.k_img = k_img; a.v_img = v_img; a.table = table; a.o = o; a.lse = lse;
-  a.part_o = nullptr; a.part_lse = nullptr; a.part_len = nullptr;
-  a.img_seq_stride = (long long)s->n_kv_heads * (w.Lp / 64); a.img_part_stride = 0;
+  a.img_seq_stride = (long long)s->n_kv_heads * (w.Lp / 64);
   a.img_head_stride = w.Lp / 64;
-  a.n_seq = s->n_chunks; a.n_rows = L; a.n_keys = L;
+  a.n_seq = s->n_chunks; a.n_rows = L;
   a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads; a.head_dim = D;
-  a.n_parts_grid = 1; a.n_parts_total = 1; a.part0 = 0;
-  a.causal_offset = 0; a.q_pos0 = 0;
   a.seq_ctx = chunk_lens; a.seq_add = s->query_len;
   a.scale = eff_scale(s->softmax_scale, D);
   return pc_launch_flash(a, st);
@@ -208,7 +205,7 @@ extern "C" int pc_chunk_query_scores(const pc_shape* s, const void* q, const voi
   const int L = s->chunk_len + s->query_len;
   float2* table = (float2*)ws;
   void* ml = (char*)ws + pc_align_up((size_t)L * (s->head_dim / 2) * sizeof(float2), kAlign);
-  rc = pc_launch_rope_table(table, L, s->head_dim, s->rope_base, st);
+  rc = pc_launch_rope_table(table, 0, L, s->head_dim, s->rope_base, st);
   if (rc != PC_OK) return rc;
   return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, st);
 }
@@ -265,45 +262,55 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
                                    k_amax, v_amax, k8, v8, k_scale, v_scale, (hipStream_t)stream);
 }
 
+// 64-key tiles of n segments of k_t keys
+static long long key_tiles(int n, int k_t) { return (long long)n * ((k_t + 63) / 64); }
+
+// The query's place in the workspace: rotated rows for the split-KV kernels, the (cos, sin) table
+// of the rows' positions for the tile kernel (which rotates as it loads).
+static size_t q_ws_bytes(bool small, size_t rows, int n_q, int D) {
+  return small ? rows * D * 2 : (size_t)n_q * (D / 2) * sizeof(float2);
+}
+
+// Parts of the tile path's keys and the partials the workspace has room for: what the segments
+// alone would be cut into and one more for a self segment, so that the workspace grows with
+// every group of keys.
+static int tile_parts(int batch, int n_q, long long seg_tiles, int n_q_heads, int n_kv_heads, int D, int has_self,
+                      int& room) {
+  room = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles) + (has_self ? 1 : 0);
+  const int parts = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles + key_tiles(has_self, n_q));
+  return parts < room ? parts : room;
+}
+
 struct Par8Ws {
-  size_t q_rot, part_o, part_lse, rows_k, rows_v, k_seg, v_seg, k_tail, v_tail, k_self, v_self, total;
-  int n_parts, parts8, ktp, tcp, nqp;
+  size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rope table of the rows on the tile path
+  int n_parts, parts8;
   bool small;
 };
 
 static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_cap, int n_q_heads,
                              int n_kv_heads, int D, int has_self) {
   Par8Ws w;
+  int parts_room = 0;
   w.small = (long long)n_q * (n_q_heads / n_kv_heads) <= 16;
-  w.ktp = (k_t + 63) / 64 * 64; w.tcp = (tail_cap + 63) / 64 * 64; w.nqp = (n_q + 63) / 64 * 64;
   if (w.small) {
     w.parts8 = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
     w.n_parts = w.parts8;
     if (tail_cap > 0) w.n_parts += pc_decode_split(tail_cap, 1, (long long)batch * n_kv_heads).n_parts;
-  } else {           // tile path: one partial per segment, one for the tail, one for the self segment
-    w.parts8 = n_seg;
-    w.n_parts = n_seg + (tail_cap > 0 ? 1 : 0) + (has_self ? 1 : 0);
+  } else {
+    w.parts8 = 0;
+    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t) + key_tiles(1, tail_cap), n_q_heads, n_kv_heads, D, has_self, parts_room);
   }
   size_t off = 0;
   const size_t rows = (size_t)batch * n_q * n_q_heads;
-  w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  w.part_o = off;   off = pc_align_up(off + rows * (size_t)w.n_parts * D * sizeof(float), kAlign);
-  w.part_lse = off; off = pc_align_up(off + rows * (size_t)w.n_parts * sizeof(float), kAlign);
-  w.rows_k = w.rows_v = w.k_seg = w.v_seg = w.k_tail = w.v_tail = w.k_self = w.v_self = off;
-  if (!w.small) {
-    // dequantised segments as bf16 rows, then the tile images of segments, tail and self segment
+  w.q_rot = off;    off = pc_align_up(off + q_ws_bytes(w.small, rows, n_q, D), kAlign);
+  if (w.small) parts_room = w.n_parts;
+  w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
+  w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
+  w.rows_k = w.rows_v = off;
+  if (!w.small) {       // dequantised segments as bf16 rows
     const size_t seg_rows = (size_t)batch * n_seg * n_kv_heads * k_t * D * 2;
-    const size_t seg_img = (size_t)batch * n_seg * n_kv_heads * D * w.ktp * 2;
-    const size_t tail_img = (size_t)batch * n_kv_heads * D * w.tcp * 2;
-    const size_t self_img = has_self ? (size_t)batch * n_kv_heads * D * w.nqp * 2 : 0;
     w.rows_k = off; off = pc_align_up(off + seg_rows, kAlign);
     w.rows_v = off; off = pc_align_up(off + seg_rows, kAlign);
-    w.k_seg = off;  off = pc_align_up(off + seg_img, kAlign);
-    w.v_seg = off;  off = pc_align_up(off + seg_img, kAlign);
-    w.k_tail = off; off = pc_align_up(off + tail_img, kAlign);
-    w.v_tail = off; off = pc_align_up(off + tail_img, kAlign);
-    w.k_self = off; off = pc_align_up(off + self_img, kAlign);
-    w.v_self = off; off = pc_align_up(off + self_img, kAlign);
   }
   w.total = off;
   return w;
@@ -484,37 +491,28 @@ extern "C" int pc_gather_kv_amax(const void* k_src, const void* v_src, const int
 
 // ---------------------------------------------------------------------------- parallel attention
 struct ParWs {
-  size_t q_rot, part_o, part_lse, v_seg, k_seg, v_self, k_self, total;
-  int n_parts, ktp, nqp;
+  size_t q_rot, part_o, part_lse, total;       // q_rot: the rope table of the rows on the tile path
+  int n_parts;
   bool small;
 };
 
 static ParWs par_ws_layout(int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                            int D, int has_self) {
   ParWs w;
+  int parts_room = 0;
   const int G = n_q_heads / n_kv_heads;
   w.small = (long long)n_q * G <= 16;
-  w.ktp = (k_t + 63) / 64 * 64;
-  w.nqp = (n_q + 63) / 64 * 64;
   if (w.small) {
     w.n_parts = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
   } else {
-    w.n_parts = n_seg + (has_self ? 1 : 0);
+    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t), n_q_heads, n_kv_heads, D, has_self, parts_room);
   }
   size_t off = 0;
   const size_t rows = (size_t)batch * n_q * n_q_heads;
-  w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  w.part_o = off;   off = pc_align_up(off + rows * (size_t)w.n_parts * D * sizeof(float), kAlign);
-  w.part_lse = off; off = pc_align_up(off + rows * (size_t)w.n_parts * sizeof(float), kAlign);
-  w.v_seg = w.k_seg = w.v_self = w.k_self = off;
-  if (!w.small) {   // tile images of the segments and of the self segment (K and V^T)
-    const size_t seg_bytes = (size_t)batch * n_seg * n_kv_heads * D * w.ktp * 2;
-    const size_t self_bytes = has_self ? (size_t)batch * n_kv_heads * D * w.nqp * 2 : 0;
-    w.v_seg = off;  off = pc_align_up(off + seg_bytes, kAlign);
-    w.k_seg = off;  off = pc_align_up(off + seg_bytes, kAlign);
-    w.v_self = off; off = pc_align_up(off + self_bytes, kAlign);
-    w.k_self = off; off = pc_align_up(off + self_bytes, kAlign);
-  }
+  w.q_rot = off;    off = pc_align_up(off + q_ws_bytes(w.small, rows, n_q, D), kAlign);
+  if (w.small) parts_room = w.n_parts;
+  w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
+  w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
   w.total = off;
   return w;
 }
@@ -562,6 +560,37 @@ static int check_par_args(const void* q, const void* kc, const void* vc, int32_t
   return PC_OK;
 }
 
+// ---- the tile kernel's key groups: segments [batch, n, H_kv, cap, D], the self segment [batch, n_q, H_kv, D]
+static PcKvGroup segment_group(const void* k, const void* v, const int32_t* len, int per_head, int n, int cap,
+                               int n_kv_heads, int D) {
+  PcKvGroup kg = {};
+  kg.k = k; kg.v = v; kg.len = len; kg.len_per_head = per_head; kg.n = n; kg.cap = cap;
+  kg.row_stride = D; kg.head_stride = (long long)cap * D;
+  kg.seg_stride = n_kv_heads * kg.head_stride; kg.seq_stride = n * kg.seg_stride;
+  return kg;
+}
+static PcKvGroup self_group(const void* k, const void* v, int n_q, int n_kv_heads, int D) {
+  PcKvGroup kg = {};
+  kg.k = k; kg.v = v; kg.n = 1; kg.cap = n_q; kg.causal = 1;
+  kg.row_stride = n_kv_heads * D; kg.head_stride = D; kg.seq_stride = (long long)n_q * kg.row_stride;
+  return kg;
+}
+
+// Tile path of Eq. 9-11: the (cos, sin) table of the query rows (identity for rows that arrive
+// rotated, q_pos0 < 0), one launch over all key groups, the merge if it was cut into parts.
+static int tile_attn_run(PcFlashArgs& a, const void* q, int batch, int n_q, int n_q_heads, int n_kv_heads,
+                         int D, int q_pos0, float rope_base, float scale, float2* table, float* part_o,
+                         float* part_lse, int n_parts, void* out, float* lse_out, hipStream_t st) {
+  int rc = pc_launch_rope_table(table, q_pos0, n_q, D, rope_base, st);
+  if (rc != PC_OK) return rc;
+  a.global = 1; a.q = q; a.table = table; a.o = out; a.lse = lse_out; a.part_o = part_o; a.part_lse = part_lse;
+  a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = D;
+  a.scale = scale; a.n_parts = n_parts;
+  rc = pc_launch_flash(a, st);
+  if (rc != PC_OK || n_parts == 1) return rc;
+  return pc_launch_merge_rows(part_o, part_lse, out, lse_out, batch, n_q, n_q_heads, D, n_parts, st);
+}
+
 // Enqueues the kernels of Eq. 9-11 on a validated request; ws holds at least w.total bytes.
 static int parallel_attn_run(const void* q, const void* kc, const void* vc, const int32_t* seg_len,
                              int32_t seg_len_per_head, const void* k_self, const void* v_self,
@@ -576,21 +605,18 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
   char* base = (char*)ws;
   const float scale = eff_scale(softmax_scale, D);
 
-  // Query operand.  Split-KV path: the rotated rows (the scale is applied to the fp32 logits).
-  // Tile path: rotated and multiplied by scale * log2(e) before the one rounding to bf16, so the
-  // matrix cores deliver logits in log2 units (rows that arrive already rotated, q_pos0 < 0, are
-  // only scaled: their bf16 values are rounded a second time).
-  const void* q_rot = q;
-  if (q_pos0 >= 0 || !w.small) {
-    rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                          q_pos0, rope_base, w.small ? 1.0f : scale * 1.4426950408889634f, st);
-    if (rc != PC_OK) return rc;
-    q_rot = base + w.q_rot;
-  }
   float* part_o = (float*)(base + w.part_o);
   float* part_lse = (float*)(base + w.part_lse);
 
   if (w.small) {
+    // split-KV path: the rotated rows (the scale is applied to the fp32 logits)
+    const void* q_rot = q;
+    if (q_pos0 >= 0) {
+      rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
+                            q_pos0, rope_base, 1.0f, st);
+      if (rc != PC_OK) return rc;
+      q_rot = base + w.q_rot;
+    }
     if (n_seg > 0) {
       rc = pc_launch_decode(q_rot, kc, vc, seg_len, seg_len_per_head, batch, n_q, n_seg, k_t, n_q_heads, n_kv_heads,
                             D, scale, part_o, part_lse, w.n_parts, 0, st);
@@ -600,46 +626,17 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
                            n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
   }
 
-  // ---- many query rows: MFMA tile kernel per (segment), partials merged afterwards
+  // ---- many query rows: MFMA tile kernel over [segments ; causal self segment]
   PcFlashArgs a = {};
-  a.q = q_rot; a.table = nullptr; a.o = nullptr; a.lse = nullptr;
-  a.part_o = part_o; a.part_lse = part_lse;
-  a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.head_dim = D; a.n_parts_total = w.n_parts; a.q_pos0 = 0; a.scale = scale;
-  if (n_seg > 0) {
-    // compacted K is already rotated: copy it into tile images next to those of V^T
-    rc = pc_launch_kv_prepass(kc, vc, nullptr, nullptr, base + w.k_seg, base + w.v_seg,
-                              batch * n_seg * n_kv_heads, k_t, w.ktp, 1, D, st);
-    if (rc != PC_OK) return rc;
-    a.k_img = base + w.k_seg; a.v_img = base + w.v_seg; a.part_len = seg_len;
-    a.part_len_per_head = seg_len_per_head;
-    a.img_seq_stride = (long long)n_seg * n_kv_heads * (w.ktp / 64);
-    a.img_part_stride = (long long)n_kv_heads * (w.ktp / 64);
-    a.img_head_stride = w.ktp / 64;
-    a.n_keys = k_t; a.n_parts_grid = n_seg; a.part0 = 0; a.causal_offset = PC_NO_CAUSAL;
-    rc = pc_launch_flash(a, st);
-    if (rc != PC_OK) return rc;
-  }
-  if (has_self) {
-    rc = pc_launch_kv_prepass(k_self, v_self, nullptr, nullptr, base + w.k_self, base + w.v_self,
-                              batch, n_q, w.nqp, n_kv_heads, D, st);
-    if (rc != PC_OK) return rc;
-    a.k_img = base + w.k_self; a.v_img = base + w.v_self; a.part_len = nullptr;
-    a.part_len_per_head = 0;
-    a.img_seq_stride = (long long)n_kv_heads * (w.nqp / 64); a.img_part_stride = 0;
-    a.img_head_stride = w.nqp / 64;
-    a.n_keys = n_q; a.n_parts_grid = 1; a.part0 = n_seg; a.causal_offset = 0;
-    rc = pc_launch_flash(a, st);
-    if (rc != PC_OK) return rc;
-  }
-  return pc_launch_merge(part_o, part_lse, q_rot, nullptr, nullptr, out, lse_out, batch, n_q,
-                         n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
+  if (n_seg > 0) a.grp[0] = segment_group(kc, vc, seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
+  if (has_self) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
+  return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
+                       (float2*)(base + w.q_rot), part_o, part_lse, w.n_parts, out, lse_out, st);
 }
 
 // Eq. 9-11 for a block of query rows over the 8-bit cache: the segments are widened to bf16 rows
 // (code * scale, rounded to bf16) in the workspace, then everything runs through the tile kernel
-// as for a 16-bit cache: one partial per segment, one for the 16-bit tail (all its rows
-// visible), one for the causal self segment, merged by logsumexp.
+// as for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].
 static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8, const float* k_scale,
                                    const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
                                    const void* k_tail, const void* v_tail, const int32_t* tail_len,
@@ -647,54 +644,18 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
                                    int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads, int D,
                                    int q_pos0, float rope_base, float scale, void* out, float* lse_out,
                                    const Par8Ws& w, char* base, hipStream_t st) {
-  int rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                            q_pos0, rope_base, scale * 1.4426950408889634f, st);
-  if (rc != PC_OK) return rc;
   PcFlashArgs a = {};
-  a.q = base + w.q_rot; a.table = nullptr; a.o = nullptr; a.lse = nullptr;
-  a.part_o = (float*)(base + w.part_o); a.part_lse = (float*)(base + w.part_lse);
-  a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.head_dim = D; a.n_parts_total = w.n_parts; a.q_pos0 = 0; a.scale = scale;
-  int part0 = 0;
-  // groups of segments [batch, n, H_kv, cap, D] (bf16 rows): images, then one partial each
-  auto segment_group = [&](const void* kc, const void* vc, const int32_t* len, int per_head, int n,
-                           int cap, int capp, void* k_img, void* v_img) -> int {
-    int r = pc_launch_kv_prepass(kc, vc, nullptr, nullptr, k_img, v_img, batch * n * n_kv_heads, cap, capp,
-                                 1, D, st);
-    if (r != PC_OK) return r;
-    a.k_img = k_img; a.v_img = v_img; a.part_len = len; a.part_len_per_head = per_head;
-    a.img_seq_stride = (long long)n * n_kv_heads * (capp / 64);
-    a.img_part_stride = (long long)n_kv_heads * (capp / 64);
-    a.img_head_stride = capp / 64;
-    a.n_keys = cap; a.n_parts_grid = n; a.part0 = part0; a.causal_offset = PC_NO_CAUSAL;
-    part0 += n;
-    return pc_launch_flash(a, st);
-  };
   if (n_seg > 0) {
-    rc = pc_launch_fp8_to_rows(k8, v8, k_scale, v_scale, (long long)batch * n_seg * n_kv_heads, k_t, D,
-                               base + w.rows_k, base + w.rows_v, st);
+    const int rc = pc_launch_fp8_to_rows(k8, v8, k_scale, v_scale, (long long)batch * n_seg * n_kv_heads, k_t, D,
+                                         base + w.rows_k, base + w.rows_v, st);
     if (rc != PC_OK) return rc;
-    rc = segment_group(base + w.rows_k, base + w.rows_v, seg_len, seg_len_per_head, n_seg, k_t, w.ktp,
-                       base + w.k_seg, base + w.v_seg);
-    if (rc != PC_OK) return rc;
+    a.grp[0] = segment_group(base + w.rows_k, base + w.rows_v, seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
   }
-  if (tail_cap > 0) {
-    rc = segment_group(k_tail, v_tail, tail_len, 0, 1, tail_cap, w.tcp, base + w.k_tail, base + w.v_tail);
-    if (rc != PC_OK) return rc;
-  }
-  if (k_self != nullptr) {
-    rc = pc_launch_kv_prepass(k_self, v_self, nullptr, nullptr, base + w.k_self, base + w.v_self, batch, n_q,
-                              w.nqp, n_kv_heads, D, st);
-    if (rc != PC_OK) return rc;
-    a.k_img = base + w.k_self; a.v_img = base + w.v_self; a.part_len = nullptr; a.part_len_per_head = 0;
-    a.img_seq_stride = (long long)n_kv_heads * (w.nqp / 64); a.img_part_stride = 0;
-    a.img_head_stride = w.nqp / 64;
-    a.n_keys = n_q; a.n_parts_grid = 1; a.part0 = part0; a.causal_offset = 0;
-    rc = pc_launch_flash(a, st);
-    if (rc != PC_OK) return rc;
-  }
-  return pc_launch_merge(a.part_o, a.part_lse, a.q, nullptr, nullptr, out, lse_out, batch, n_q, n_q_heads,
-                         n_kv_heads, D, w.n_parts, scale, st);
+  if (tail_cap > 0) a.grp[1] = segment_group(k_tail, v_tail, tail_len, 0, 1, tail_cap, n_kv_heads, D);
+  if (k_self != nullptr) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
+  return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
+                       (float2*)(base + w.q_rot), (float*)(base + w.part_o), (float*)(base + w.part_lse),
+                       w.n_parts, out, lse_out, st);
 }
 
 extern "C" int pc_parallel_attn(const void* q, const void* kc, const void* vc, const int32_t* seg_len,

@@ -123,7 +123,7 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
                           int32_t* queue_id, float* queue_score, int32_t* queue_slot,
                           int32_t* slot_src, hipStream_t st);
 
-int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st);
+int pc_launch_rope_table(float2* table, int pos0, int n_pos, int head_dim, float base, hipStream_t st);
 
 // K/V pre-pass: K (rotated when a table is given; skipped when k == nullptr) -> k_rope (row-major,
 // optional) and K tile images (optional); V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
@@ -131,30 +131,43 @@ int pc_launch_kv_prepass(const void* k, const void* v, const float2* table, void
                          void* k_img, void* v_img, int n_seq, int L, int Lp, int n_kv_heads,
                          int head_dim, hipStream_t st);
 
-// Flash-style tile kernel.  A workgroup handles (sequence, query head, 128-row Q tile, part);
-// a "part" is an independent key set (a compressed segment) with its own softmax.
+// Flash-style tile kernel.  Local (global == 0): causal attention inside n_seq sequences of n_rows
+// rows.  Global: n_rows query rows per sequence over groups of key segments under one softmax.
+// A group: segments [n] of up to cap keys each, bf16 rows of D; key j of (sequence, segment, KV
+// head) at element seq * seq_stride + segment * seg_stride + head * head_stride + j * row_stride.
+struct PcKvGroup {
+  const void* k;            // rotated keys
+  const void* v;
+  const int32_t* len;       // [n_seq, n] (x [n_kv_heads] if len_per_head) valid keys, or nullptr (= cap)
+  int len_per_head, n, cap; // n = 0: no such group
+  int causal;               // key j visible to query row t iff j <= t (cap = n_rows)
+  int row_stride;
+  long long seq_stride, seg_stride, head_stride;
+};
+#define PC_KV_GROUPS 3
 struct PcFlashArgs {
-  const void* q;            // [n_seq, n_rows, H_q, D] bf16
-  const void* k_img;        // K tile images (rotated keys), image index = seq * img_seq_stride +
-  const void* v_img;        //   part * img_part_stride + head * img_head_stride + tile; V^T likewise
-  const float2* table;      // rope table (rotate q at q_pos0 + row, then scale), or nullptr: q is
-                            //   already rotated AND already multiplied by scale * log2(e)
-  void* o;                  // [n_seq, n_rows, H_q, D] bf16 (final output mode)
+  int global;
+  const void* q;            // [n_seq, n_rows, H_q, D] bf16, rotated here by `table` and scaled
+  const float2* table;      // rope table, row t for query row t
+  void* o;                  // [n_seq, n_rows, H_q, D] bf16
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
-  float* part_o;            // partial mode: [n_seq, n_parts_total, n_rows, H_q, D] fp32, else nullptr
-  float* part_lse;          // [n_seq, n_parts_total, n_rows, H_q]
-  const int32_t* part_len;  // [n_seq, n_parts_grid] (x [n_kv_heads] if part_len_per_head) valid keys per part, or nullptr (= n_keys)
-  int part_len_per_head;
+  int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;
+  float scale;
+  // local
+  const void* k_img;        // K tile images (rotated keys), image index = seq * img_seq_stride +
+  const void* v_img;        //   head * img_head_stride + tile; V^T likewise
+  long long img_seq_stride, img_head_stride;                               // in tile images
   const int32_t* seq_ctx;   // [n_seq] context rows per sequence or nullptr: sequence s has
   int seq_add;              //   min(seq_ctx[s], n_rows - seq_add) + seq_add rows (and keys)
-  long long img_seq_stride, img_part_stride, img_head_stride;              // in tile images
-  int n_seq, n_rows, n_keys, n_q_heads, n_kv_heads, head_dim;
-  int n_parts_grid, n_parts_total, part0;
-  int causal_offset;        // key j visible to row r iff j <= r + causal_offset; >= 2^29: no mask
-  int q_pos0;
-  float scale;
+  // global
+  PcKvGroup grp[PC_KV_GROUPS];
+  int n_parts;              // workgroups a Q tile's keys are cut into; 1: o and lse are written
+  float* part_o;            // n_parts > 1: [n_seq, n_parts, n_rows, H_q, D] fp32
+  float* part_lse;          // [n_seq, n_parts, n_rows, H_q]
 };
-#define PC_NO_CAUSAL (1 << 29)
+// How many parts the global attention's keys are cut into (n_tiles: 64-key tiles of a KV head at
+// full lengths)
+int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles);
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
 
 int pc_launch_self_info(const void* logits, const int32_t* targets, int n_chunks, int n_tokens,
@@ -280,6 +293,9 @@ int pc_launch_decode_fp8(const void* q_rot, const void* k8, const void* v8, cons
                          int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                          int head_dim, float scale, float* part_o, float* part_lse, int n_parts,
                          hipStream_t st);
+// Merge of the tile kernel's partials [batch, n_parts, n_q, H_q, D] (no self segment)
+int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, float* lse_out, int batch,
+                         int n_q, int n_q_heads, int head_dim, int n_parts, hipStream_t st);
 int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_rot,
                     const void* k_self, const void* v_self, void* out, float* lse_out, int batch,
                     int n_q, int n_q_heads, int n_kv_heads, int head_dim, int n_parts, float scale,

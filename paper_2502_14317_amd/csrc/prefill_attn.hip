@@ -43,22 +43,23 @@
 #define PC_LN2 0.6931471805599453f
 
 // ------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(float2* __restrict__ table, int n_pos, int D, double log_base) {
+// cos/sin of the positions pos0 .. pos0 + n_pos - 1; pos0 < 0: the identity (rows already rotated)
+__global__ void rope_table_kernel(float2* __restrict__ table, int pos0, int n_pos, int D, double log_base) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int half = D / 2;
   if (idx >= n_pos * half) return;
   const int p = idx / half, i = idx % half;
   const double theta = exp(-2.0 * (double)i / (double)D * log_base);
-  double sn, cs;
-  sincos((double)p * theta, &sn, &cs);
+  double sn = 0.0, cs = 1.0;
+  if (pos0 >= 0) sincos((double)(pos0 + p) * theta, &sn, &cs);
   table[idx] = make_float2((float)cs, (float)sn);
 }
 
-int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st) {
+int pc_launch_rope_table(float2* table, int pos0, int n_pos, int head_dim, float base, hipStream_t st) {
   const int n = n_pos * (head_dim / 2);
   PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, n_pos,
-                     head_dim, log((double)base));
+  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, pos0,
+                     n_pos, head_dim, log((double)(pos0 >= 0 ? base : 2.0f)));
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
@@ -183,58 +184,211 @@ __device__ __forceinline__ int pc_key_of_row(int m) {
   return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1);
 }
 
-template <int D, bool ROPE_Q, bool PARTIAL>
+// The global attention's keys as tiles of 64: the tiles that every row of the workgroup sees whole
+// come first (no mask), then those that need one (a segment's ragged last tile, the causal
+// diagonal), so that the main loop holds no mask.  `full` tiles of a segment of `len` keys:
+__device__ __forceinline__ int pc_seg_len(const PcKvGroup& kg, int b, int g, int n_kv_heads, int s) {
+  if (!kg.len) return kg.cap;
+  return min(max(kg.len[kg.len_per_head ? (b * kg.n + s) * n_kv_heads + g : b * kg.n + s], 0), kg.cap);
+}
+// t0, t1: first and last query row of the workgroup (a causal segment's keys end at t1)
+__device__ __forceinline__ int pc_full_tiles(const PcKvGroup& kg, int len, int t0) {
+  return (kg.causal ? min(t0 + 1, len) : len) / 64;
+}
+__device__ __forceinline__ int pc_seg_tiles(const PcKvGroup& kg, int len, int t0, int t1, bool masked) {
+  const int end = kg.causal ? min(t1 + 1, len) : len, full = pc_full_tiles(kg, len, t0);
+  return masked ? (end + 63) / 64 - full : full;
+}
+// Sum over a group's segments, and the segment that holds tile `rel` of it (0 <= rel < sum; all
+// wavefront-uniform).  With lengths on the device the lanes take a segment each, 64 per round.
+__device__ __forceinline__ int pc_kv_tiles(const PcKvGroup& kg, int b, int g, int n_kv_heads, int t0, int t1,
+                                           bool masked, int lane) {
+  if (!kg.len) return kg.n * pc_seg_tiles(kg, kg.cap, t0, t1, masked);
+  int total = 0;
+  for (int s0 = 0; s0 < kg.n; s0 += PC_WAVE) {
+    int nt = s0 + lane < kg.n ? pc_seg_tiles(kg, pc_seg_len(kg, b, g, n_kv_heads, s0 + lane), t0, t1, masked) : 0;
+#pragma unroll
+    for (int off = PC_WAVE / 2; off > 0; off >>= 1) nt += __shfl_xor(nt, off);
+    total += __builtin_amdgcn_readfirstlane(nt);
+  }
+  return total;
+}
+__device__ __forceinline__ void pc_kv_find(const PcKvGroup& kg, int b, int g, int n_kv_heads, int t0, int t1,
+                                           bool masked, int lane, int rel, int& seg, int& tile, int& len) {
+  if (!kg.len) {
+    const int nt = pc_seg_tiles(kg, kg.cap, t0, t1, masked);
+    seg = rel / nt; tile = rel % nt; len = kg.cap;
+    return;
+  }
+  for (int s0 = 0; s0 < kg.n; s0 += PC_WAVE) {
+    const int l = s0 + lane < kg.n ? pc_seg_len(kg, b, g, n_kv_heads, s0 + lane) : 0;
+    const int nt = pc_seg_tiles(kg, l, t0, t1, masked);
+    int incl = nt;                                           // inclusive prefix sum over the lanes
+#pragma unroll
+    for (int off = 1; off < PC_WAVE; off <<= 1) {
+      const int up = __shfl_up(incl, off);
+      if (lane >= off) incl += up;
+    }
+    const unsigned long long hit = __ballot(incl - nt <= rel && rel < incl);
+    if (hit) {
+      const int src = __ffsll((long long)hit) - 1;
+      seg = s0 + src;
+      tile = rel - __builtin_amdgcn_readfirstlane(__shfl(incl - nt, src));
+      len = __builtin_amdgcn_readfirstlane(__shfl(l, src));
+      return;
+    }
+    rel -= __builtin_amdgcn_readfirstlane(__shfl(incl, PC_WAVE - 1));
+  }
+}
+
+// GLOBAL = false: causal local attention of whole sequences over tile images of K and V^T.
+// GLOBAL = true: a block of query rows over groups of row-major segments (compressed segments, a
+//   16-bit tail, the causal self segment) under one softmax.  The rows of a KV head's G query
+//   heads are packed into one run of n_rows * G rows (row r = query r / G, head r % G of the
+//   group), so a short query block fills its 128-row tiles; all segments' tiles laid end to end
+//   are cut into n_parts equal runs, one workgroup each.  With one part the workgroup writes the
+//   final output, otherwise a partial result for the merge.
+template <int D, bool GLOBAL>
 __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs a) {
   using SM = FlashSmem<D>;
   constexpr int KS = D / 16;        // k-steps of the first product (over head_dim)
   constexpr int DB = D / 32;        // 32-row blocks of O^T (over head_dim)
   constexpr int HALF = D / 2;
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-  auto k_lds = [&](int t) __attribute__((always_inline)) { return smem + (t % SM::KBUF) * SM::K_ELEMS; };
+  auto k_at = [&](int t) __attribute__((always_inline)) { return (t % SM::KBUF) * SM::K_ELEMS; };
+  auto k_lds = [&](int t) __attribute__((always_inline)) { return smem + k_at(t); };
   auto v_lds = [&](int t) __attribute__((always_inline)) {
     return smem + SM::KBUF * SM::K_ELEMS + (t % SM::VBUF) * SM::V_ELEMS;
   };
 
   // ---- which (sequence, head, Q tile): one XCD (blockIdx % 8) works through whole
-  //      (sequence, KV head) groups, heavy Q tiles first, the group's query heads adjacent
+  //      (sequence, KV head) groups, heavy Q tiles first, the group's query heads adjacent; the
+  //      last groups, when their number is no multiple of 8, are dealt out to all XCDs
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int n_qt = (a.n_rows + PC_FA_BM - 1) / PC_FA_BM;
-  const int per_group = G * n_qt * a.n_parts_grid;
-  const int xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
-  const int cg = (jb / per_group) * 8 + xcd;
-  if (cg >= a.n_seq * a.n_kv_heads) return;
-  int within = jb % per_group;
-  const int part = within % a.n_parts_grid; within /= a.n_parts_grid;
-  const int qt = n_qt - 1 - within / G;
-  const int hg = within % G;
+  const int rows_wg = GLOBAL ? a.n_rows * G : a.n_rows;      // rows that the Q tiles of a head (of a group) cover
+  const int n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
+  const int per_group = GLOBAL ? n_qt * a.n_parts : G * n_qt;
+  const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
+  int cg, within;
+  if ((int)blockIdx.x < full_blocks) {
+    const int xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
+    cg = (jb / per_group) * 8 + xcd;
+    within = jb % per_group;
+  } else {
+    const int rest = blockIdx.x - full_blocks;
+    cg = n_groups / 8 * 8 + rest / per_group;
+    within = rest % per_group;
+  }
   const int seq = cg / a.n_kv_heads, g = cg % a.n_kv_heads;
-  const int h = g * G + hg;
+  const int part = GLOBAL ? within / n_qt : 0;
+  const int qt = GLOBAL ? within % n_qt : n_qt - 1 - within / G;
+  const int h = GLOBAL ? g * G : g * G + within % G;         // (GLOBAL: the group's first head)
 
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
   const int row0_wg = qt * PC_FA_BM;
   // rows (= keys) of this sequence: a short chunk is [its context rows ; the query rows]
-  const int seq_rows = a.seq_ctx ? min(max(a.seq_ctx[seq], 0), a.n_rows - a.seq_add) + a.seq_add : a.n_rows;
+  const int seq_rows = GLOBAL ? rows_wg
+                       : (a.seq_ctx ? min(max(a.seq_ctx[seq], 0), a.n_rows - a.seq_add) + a.seq_add : a.n_rows);
   if (row0_wg >= seq_rows) return;                 // a Q tile of padding rows (uniform over the workgroup)
   constexpr int NB = PC_FA_NB;
   const int row0 = row0_wg + 32 * NB * wave;      // first query row of this wavefront
-  int my_row[NB], max_key[NB];
+  // query row -> index in [row, head] of its q and output rows, its position
+  auto row_at = [&](int r) __attribute__((always_inline)) {
+    return GLOBAL ? ((long long)seq * a.n_rows + r / G) * a.n_q_heads + h + r % G
+                  : ((long long)seq * a.n_rows + r) * a.n_q_heads + h;
+  };
+  auto pos_of = [&](int r) __attribute__((always_inline)) { return GLOBAL ? r / G : r; };
+  int my_row[NB], my_t[NB], max_key[NB];
 
-  // ---- keys of this workgroup: [0, key_end) of the part
-  const int len_idx = a.part_len_per_head ? (seq * a.n_parts_grid + part) * a.n_kv_heads + g
-                                          : seq * a.n_parts_grid + part;
-  const int n_valid = a.part_len ? min(max(a.part_len[len_idx], 0), a.n_keys)
-                                 : (a.seq_ctx ? min(a.n_keys, seq_rows) : a.n_keys);
-  int key_end = n_valid;
-  if (a.causal_offset < PC_NO_CAUSAL) key_end = min(key_end, row0_wg + PC_FA_BM + a.causal_offset);
-  const int T = (key_end + PC_FA_BN - 1) / PC_FA_BN;          // 64-key tiles
-  // steps of 32 keys: steps [0, J0) are visible to every row of the workgroup (no mask)
-  const int J0 = (min(row0_wg + a.causal_offset, n_valid - 1) + 1) / 32;
-
-  // tile images of this (sequence, part, KV head): consecutive 64-key tiles of 64 * D elements
-  const long long img0 = (seq * a.img_seq_stride + part * a.img_part_stride + g * a.img_head_stride) * (64LL * D);
+  // ---- local: keys [0, key_end) in T 64-key tiles; steps of 32 keys [0, J0) are visible to every
+  //      row of the workgroup (no mask)
+  const int n_valid = seq_rows;
+  int T = (min(n_valid, row0_wg + PC_FA_BM) + 63) / 64;
+  const int J0 = (min(row0_wg, n_valid - 1) + 1) / 32;
+  const long long img0 = (seq * a.img_seq_stride + g * a.img_head_stride) * (64LL * D);
   const uint16_t* kbase = (const uint16_t*)a.k_img + img0;
   const uint16_t* vbase = (const uint16_t*)a.v_img + img0;
+
+  // ---- global: a cursor over the run's tiles, the unmasked ones of all segments first.  Inside a
+  //      segment it moves by scalar additions; the groups' descriptions are read only where a
+  //      segment begins.  `cut` is how many keys from the tile's first on are valid, c0 the first
+  //      key's position if the segment is causal, else far below every row.
+  struct Cursor {
+    const uint16_t* k; const uint16_t* v;
+    int row_bytes, cut, c0, c0_step;
+    int in_seg, in_phase, left;                    // tiles left in the segment, among the unmasked / masked ones, in the run
+    int grp, seg;
+    bool masked, seg_start;
+  };
+  Cursor cur = {};
+  const int wg_t0 = row0_wg / G, wg_t1 = (min(row0_wg + PC_FA_BM, rows_wg) - 1) / G;
+  int run_full = 0, masked_lo = 0;                           // unmasked tiles of the run; its first masked tile
+  auto cur_place = [&](int tile, int len) __attribute__((always_inline)) {   // tile: among the segment's of this phase
+    const PcKvGroup& kg = a.grp[cur.grp];
+    const int idx = tile + (cur.masked ? pc_full_tiles(kg, len, wg_t0) : 0);
+    const long long at = seq * kg.seq_stride + cur.seg * kg.seg_stride + g * kg.head_stride + 64LL * idx * kg.row_stride;
+    cur.k = (const uint16_t*)kg.k + at; cur.v = (const uint16_t*)kg.v + at;
+    cur.row_bytes = 2 * kg.row_stride;
+    cur.cut = len - 64 * idx;
+    cur.c0 = kg.causal ? 64 * idx : -(1 << 28);
+    cur.c0_step = kg.causal ? 64 : 0;
+    cur.in_seg = pc_seg_tiles(kg, len, wg_t0, wg_t1, cur.masked) - tile;
+    cur.seg_start = idx == 0;
+  };
+  auto cur_seek = [&](int rel) __attribute__((always_inline)) {              // to tile `rel` of the phase
+    int tile = 0, len = 0;
+    cur.grp = 0;
+    for (; cur.grp < PC_KV_GROUPS; ++cur.grp) {
+      const PcKvGroup& kg = a.grp[cur.grp];
+      const int nt = kg.n > 0 ? pc_kv_tiles(kg, seq, g, a.n_kv_heads, wg_t0, wg_t1, cur.masked, lane) : 0;
+      if (rel < nt) break;
+      rel -= nt;
+    }
+    pc_kv_find(a.grp[cur.grp], seq, g, a.n_kv_heads, wg_t0, wg_t1, cur.masked, lane, rel, cur.seg, tile, len);
+    cur_place(tile, len);
+  };
+  auto cur_next = [&]() __attribute__((always_inline)) {     // stays on the run's last tile
+    if (cur.left <= 1) return;
+    --cur.left;
+    if (cur.in_phase > 1 && cur.in_seg > 1) {
+      --cur.in_phase; --cur.in_seg;
+      cur.k += 32 * cur.row_bytes; cur.v += 32 * cur.row_bytes;      // 64 rows
+      cur.cut -= 64; cur.c0 += cur.c0_step; cur.seg_start = false;
+    } else if (cur.in_phase > 1) {
+      --cur.in_phase;
+      int len;
+      do {                                                   // the next segment that has tiles of this kind
+        if (++cur.seg >= a.grp[cur.grp].n) { cur.seg = 0; ++cur.grp; }
+        len = a.grp[cur.grp].n > 0 ? pc_seg_len(a.grp[cur.grp], seq, g, a.n_kv_heads, cur.seg) : 0;
+        len = __builtin_amdgcn_readfirstlane(len);
+      } while (len == 0 || pc_seg_tiles(a.grp[cur.grp], len, wg_t0, wg_t1, cur.masked) == 0);
+      cur_place(0, len);
+    } else {
+      cur.masked = true;
+      cur.in_phase = cur.left;
+      cur_seek(masked_lo);
+    }
+  };
+  if (GLOBAL) {
+    int n_full = 0, n_masked = 0;
+    for (int i = 0; i < PC_KV_GROUPS; ++i)
+      if (a.grp[i].n > 0) {
+        n_full += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, false, lane);
+        n_masked += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, true, lane);
+      }
+    // every part takes an equal run of all tiles, [lo, hi) of [full ; masked]
+    const int lo = (int)((long long)(n_full + n_masked) * part / a.n_parts);
+    const int hi = (int)((long long)(n_full + n_masked) * (part + 1) / a.n_parts);
+    T = cur.left = hi - lo;
+    run_full = max(0, min(hi, n_full) - lo);
+    masked_lo = max(0, lo - n_full);
+    if (T > 0) {
+      cur.masked = run_full == 0;
+      cur.in_phase = cur.masked ? T : run_full;
+      cur_seek(cur.masked ? masked_lo : lo);
+    }
+  }
 
   // ---- Q^T as B operand, NB 32-row blocks: lane holds query n of each, d = 16*ks + 8*hf .. +7.
   //      The softmax scale and log2(e) are folded into Q before its rounding to bf16, so the
@@ -244,10 +398,9 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     my_row[nb] = row0 + 32 * nb + n;
-    max_key[nb] = min(my_row[nb] + a.causal_offset, n_valid - 1);
-    const int ld_row = min(my_row[nb], seq_rows - 1);
-    const uint16_t* qrow = (const uint16_t*)a.q + (((long long)seq * a.n_rows + ld_row) * a.n_q_heads + h) * D;
-    if (ROPE_Q) {
+    my_t[nb] = pos_of(my_row[nb]);
+    max_key[nb] = min(my_row[nb], n_valid - 1);
+    {
       // The wavefront's 32 query rows and their (cos, sin) table rows are fetched with
       // coalesced loads (a load instruction covers whole rows, 1 KiB contiguous where the rows
       // are adjacent) and handed to the lanes that own them through a private, XOR-swizzled
@@ -267,8 +420,8 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
       for (int i = 0; i < NLD; ++i) {
         const int r = RPL * i + l_row;
         const int grow = min(row0 + 32 * nb + r, seq_rows - 1);
-        rq[i] = pc_load_once((const u32x4*)((const uint16_t*)a.q + (((long long)seq * a.n_rows + grow) * a.n_q_heads + h) * D + 8 * l_piece));
-        const char* trow = (const char*)(a.table + (long long)(a.q_pos0 + grow) * HALF);
+        rq[i] = pc_load_once((const u32x4*)((const uint16_t*)a.q + row_at(grow) * D + 8 * l_piece));
+        const char* trow = (const char*)(a.table + (long long)pos_of(grow) * HALF);
         rt[0][i] = *(const u32x4*)(trow + 16 * l_piece);
         rt[1][i] = *(const u32x4*)(trow + 2 * D + 16 * l_piece);
       }
@@ -308,44 +461,73 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
         }
         PC_FA_WAVE_LDS_SYNC();                                // the table area is rewritten / the tiles move in
       }
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        // already rotated and scaled by the caller (rounded to bf16 once, there)
-        const u32x4 x = *(const u32x4*)(qrow + 16 * ks + 8 * hf);
-        bq[nb][ks] = *(bf16x8*)&x;
-      }
     }
   }
 
-  // ---- cooperative tile loads, straight from global memory into LDS: a tile image is copied
-  //      as it is, wavefront w issuing instruction i for its 1 KiB block WAVES i + w.  Loads go
-  //      through buffer descriptors (descriptor base + scalar offset + one constant per-lane
-  //      offset, no 64-bit vector arithmetic per load).
+  // ---- cooperative tile loads, straight from global memory into LDS, through buffer descriptors.
+  //      Local: a tile image is copied as it is, wavefront w issuing instruction i for its 1 KiB
+  //      block WAVES i + w (descriptor base + scalar offset + one constant per-lane offset).
+  //      Global: row-major rows; wavefront w takes rows 16 w .. + 15, an instruction 64 bytes of
+  //      each (the four lanes of a row adjacent), in LDS [16-row group][64-byte column block][row].
+  //      Of a K row's four 16-byte granules in a block, granule c lies at place c ^ (row % 16 / 4), so
+  //      that the 16 lanes an operand read serves together (one granule column, 16 rows) touch 256
+  //      different bytes; V is kept straight: half a wavefront's transposing read takes 4 rows =
+  //      256 consecutive bytes.  A tile's descriptor ends behind its last valid row: the rows after
+  //      it arrive as zeros.
   constexpr int WAVES = PC_FA_WAVES;
   constexpr int T_LD = D / 8 / WAVES;              // load instructions per wavefront per tile
   constexpr int IMG_BYTES = 64 * D * 2;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   typedef __attribute__((address_space(3))) void* lptr_t;
-  const int n_img = (a.n_keys + 63) / 64;
+  const int n_img = (a.n_rows + 63) / 64;
   const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, n_img * IMG_BYTES, 0x00020000);
   const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)vbase, 0, n_img * IMG_BYTES, 0x00020000);
   const int ld_goff = 1024 * wave_s + 16 * lane;
-  auto load_k_i = [&](int t, int i) __attribute__((always_inline)) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(k_lds(t) + 512 * (WAVES * i + wave_s)), 16,
-                                             ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
+  // what the (global) loads of the cursor's tile need
+  struct TileLoad { const uint16_t* k; const uint16_t* v; int bytes, k_off, v_off; };
+  auto tile_load = [&]() __attribute__((always_inline)) {
+    TileLoad x;
+    x.k = cur.k; x.v = cur.v;
+    x.bytes = (min(cur.cut, 64) - 1) * cur.row_bytes + 2 * D;
+    int id = tid;                                  // recomputed per tile: the loop has no registers to spare
+    asm volatile("" : "+v"(id));
+    x.v_off = (id / 4) * cur.row_bytes + 16 * (id % 4);            // row 16 wave + lane / 4
+    x.k_off = x.v_off ^ (id & 48);                                 // ^ 16 (lane / 16); rows start at multiples of 64 bytes
+    return x;
   };
-  auto load_v_i = [&](int t, int i) __attribute__((always_inline)) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_lds(t) + 512 * (WAVES * i + wave_s)), 16,
-                                             ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
+  auto load_rows_i = [&](const uint16_t* base, int bytes, int off, uint16_t* dst, int i) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)(dst + 512 * (T_LD * wave_s + i)), 16, off, 64 * i, 0, 0);
   };
-  auto load_k = [&](int t) __attribute__((always_inline)) {
+  auto load_k_i = [&](const TileLoad& x, int t, int i) __attribute__((always_inline)) {
+    if (GLOBAL)
+      load_rows_i(x.k, x.bytes, x.k_off, k_lds(t), i);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(k_lds(t) + 512 * (WAVES * i + wave_s)), 16,
+                                               ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
+  };
+  auto load_v_i = [&](const TileLoad& x, int t, int i) __attribute__((always_inline)) {
+    if (GLOBAL)
+      load_rows_i(x.v, x.bytes, x.v_off, v_lds(t), i);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_lds(t) + 512 * (WAVES * i + wave_s)), 16,
+                                               ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
+  };
+  auto load_tile = [&](const TileLoad& x, int t) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < T_LD; ++i) load_k_i(t, i);
-  };
-  auto load_v = [&](int t) __attribute__((always_inline)) {
+    for (int i = 0; i < T_LD; ++i) load_k_i(x, t, i);
 #pragma unroll
-    for (int i = 0; i < T_LD; ++i) load_v_i(t, i);
+    for (int i = 0; i < T_LD; ++i) load_v_i(x, t, i);
+  };
+  // A operand of the second product from row-major V, V^T(d = n, 8 keys): two transposing reads of
+  // 4 keys each.  16 lanes point at 4 rows x 16 columns (8 bytes a lane) and receive a column's 4 rows.
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  auto read_v_rows = [&](const uint16_t* p) __attribute__((always_inline)) {
+    union { s16x4 h[2]; bf16x8 v; } x;
+    typedef __attribute__((address_space(3))) s16x4* rptr_t;
+    x.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rptr_t)p);
+    x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rptr_t)(p + 4 * 32));
+    return x.v;
   };
   // s_waitcnt vmcnt(N): N newest loads of this wavefront may still be in flight
 #define PC_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
@@ -375,11 +557,27 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   floatx16 s_buf[2][NB];                           // [step parity][row block]
   u32x4 p_buf[2][NB][2];                            // [step parity][row block][16-key k-step], bf16 pairs
 
-  // Per-lane element offsets of the MFMA A operands inside a tile image: K granule
-  // (2 ks + hf, 32 (j & 1) + krow), V^T granule (4 (j & 1) + 2 ts + hf, 32 db + n).  Everything
-  // but the lane's own part is a compile-time offset of the LDS read.
-  int k_base = (hf * 64 + krow) * 8;
-  int v_base = (hf * D + n) * 8;
+  // Per-lane element offsets of the MFMA A operands inside a tile.  Image: K granule
+  // (2 ks + hf, 32 (j & 1) + krow), V^T granule (4 (j & 1) + 2 ts + hf, 32 db + n).  Rows: K
+  // granule 2 ks + hf of row 32 (j & 1) + krow, whose place in its block changes by one bit between
+  // even and odd ks; V keys 8 hf .. + 3 of the column group (lane / 16) % 2.  Everything but the
+  // lane's own part is a compile-time offset of the LDS read.
+  int k_base, v_base;
+  if (GLOBAL) {
+    k_base = (krow / 16) * (16 * D) + (krow % 16) * 32 + ((hf ^ (krow % 16 / 4)) * 8);
+    v_base = (8 * hf + (lane % 16) / 4) * 32 + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  } else {
+    k_base = (hf * 64 + krow) * 8;
+    v_base = (hf * D + n) * 8;
+  }
+  auto read_k = [&](int tile, int half, int ks) __attribute__((always_inline)) {
+    return GLOBAL ? *(const bf16x8*)(smem + ((tile + 32 * D * half + k_base) ^ (16 * (ks % 2))) + 512 * (ks / 2))
+                  : *(const bf16x8*)(smem + tile + 32 * 8 * half + k_base + 2 * ks * 64 * 8);
+  };
+  auto read_v = [&](const uint16_t* tile, int half, int ts, int db) __attribute__((always_inline)) {
+    return GLOBAL ? read_v_rows(tile + 32 * D * half + v_base + 16 * D * ts + 512 * db)
+                  : *(const bf16x8*)(tile + 4 * half * D * 8 + v_base + 2 * ts * D * 8 + 32 * db * 8);
+  };
 
   // MFMA A operands, read from LDS one region ahead of their use
   bf16x8 ka[KS], va[2][DB];                        // K rows of a step; V^T [16-key k-step][d block]
@@ -399,7 +597,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   //              VALU  rest of P^T(j) = exp2(S^T(j) - m)
   // Register r of a row block at lane half hf is key 32 j + 16 (r / 8) + 8 hf + (r % 8).
   // Lazy rescale: the reference m_run of a row only moves when the step maximum exceeds it by
-  // more than 2^8; until then p = exp2(s - m_run) <= 256 and O, l keep their scale.  The P V
+  // more than `window` (log2 units), 8 as a rule; until then p = exp2(s - m_run) <= 256 and O, l keep their scale.  The P V
   // products of step j - 1 (old reference) are all issued in region 1, so O is rescaled after it.
   // has_pv / has_qk are compile-time: the first step has no previous P V, the last no next K Q^T.
   // Steps that lie wholly above a wavefront's rows on the diagonal: those inside the loop are
@@ -411,13 +609,18 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   constexpr int NG = 16 * NB + 1;                  // probability groups per step
   // groups placed in region 1: the share of its free slices among all slices that take groups
   constexpr int G1 = NG * (NM - MAX_SL - 1) / (2 * NM - MAX_SL - 1);
-  auto step = [&](auto mask_tag, auto has_pv, auto has_qk, auto has_ld, int j, int t_ld, floatx16(&s_cur)[NB],
+  // A mask hides the keys behind the row's last visible one; the step's first key counts as key
+  // `k0`.  A (global) tile's limits: its valid keys, and its first key's position where the segment
+  // is causal.
+  struct Limit { int cut, c0; };
+  auto step = [&](auto mask_tag, auto has_pv, auto has_qk, auto has_ld, const Limit& lim, float window, int j, int k0,
+                  int t_ld, const TileLoad& ld, floatx16(&s_cur)[NB],
                   floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2],
                   const u32x4(&p_prev)[NB][2]) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
     constexpr bool PV = decltype(has_pv)::value, QK = decltype(has_qk)::value, LD = decltype(has_ld)::value;
-    const uint16_t* kp = k_lds((j + 1) >> 1) + 32 * 8 * ((j + 1) & 1) + k_base;   // this lane's granule of column hf
-    const uint16_t* vp = v_lds(j >> 1) + 4 * (j & 1) * D * 8 + v_base;
+    const int kt = k_at((j + 1) >> 1);
+    const uint16_t* vt = v_lds(j >> 1);
     float t[NB], alpha[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) { t[nb] = 0.f; alpha[nb] = 1.f; }
@@ -453,19 +656,19 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
         o_acc[nb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
             va[ts][db], *(const bf16x8*)&p_prev[nb][ts], o_acc[nb][db], 0, 0, 0);
       }
-      if (QK && i < KS) ka[i] = *(const bf16x8*)(kp + 2 * i * 64 * 8);
+      if (QK && i < KS) ka[i] = read_k(kt, (j + 1) & 1, i);
       if (LD && i >= NM - 2 * T_LD) {               // one tile-load instruction per slice
         const int li = i - (NM - 2 * T_LD);
-        if (li < T_LD) load_k_i(t_ld, li);
-        else load_v_i(t_ld, li - T_LD);
+        if (li < T_LD) load_k_i(ld, t_ld, li);
+        else load_v_i(ld, t_ld, li - T_LD);
       }
       if (MASK && i == 0) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int key = 32 * j + 16 * (r / 8) + 8 * hf + (r % 8);
-            if (key > max_key[nb]) s_cur[nb][r] = -INFINITY;
+            const int key = k0 + 16 * (r / 8) + 8 * hf + (r % 8);
+            if (key > (GLOBAL ? min(lim.cut - 1, my_t[nb] - lim.c0) : max_key[nb])) s_cur[nb][r] = -INFINITY;
           }
       }
       if (i < MAX_SL) {
@@ -486,13 +689,13 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
         // to the reference, so the test is a compare with a constant; everything else is rare.
         bool grow = !PV;                            // the first step sets the reference exactly
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) grow |= t[nb] > 8.0f;
+        for (int nb = 0; nb < NB; ++nb) grow |= t[nb] > window;
         grow_any = __any(grow);
         if (grow_any) {
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) {
             const float tm = pc_xhalf_max(t[nb]);   // both lane halves hold keys of the same row
-            const bool gr = PV ? tm > 8.0f : tm != -INFINITY;
+            const bool gr = PV ? tm > window : tm != -INFINITY;
             const float delta = gr ? tm : 0.f;
             alpha[nb] = PV ? __builtin_amdgcn_exp2f(-delta) : 1.0f;   // nothing accumulated before the first step
             m_run[nb] += delta;
@@ -531,7 +734,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
       }
       if (i < KS) {
         const int ts = i / DB, db = i % DB;
-        va[ts][db] = *(const bf16x8*)(vp + 2 * ts * D * 8 + 32 * db * 8);
+        va[ts][db] = read_v(vt, j & 1, ts, db);
       }
 #pragma unroll
       for (int g = G1; g < NG; ++g)
@@ -541,9 +744,8 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   };
   // first S^T of a workgroup: operands of step 0, then the product
   auto first_qk = [&](floatx16(&s)[NB]) __attribute__((always_inline)) {
-    const uint16_t* kp = k_lds(0) + k_base;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ka[ks] = *(const bf16x8*)(kp + 2 * ks * 64 * 8);
+    for (int ks = 0; ks < KS; ++ks) ka[ks] = read_k(k_at(0), 0, ks);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -565,43 +767,41 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
           o_acc[nb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ts][db], *(const bf16x8*)&p[nb][ts], o_acc[nb][db], 0, 0, 0);
   };
 
-  if (T > 0) {
-    // ---- prologue: tiles 0 and 1 must have landed before the first step; tiles 2, 3 stay in flight
-    if (ROPE_Q) __syncthreads();                   // every wavefront has left its staging area
-    load_k(0);
-    load_v(0);
-    load_k(min(1, T - 1));
-    load_v(min(1, T - 1));
+  // Keeps k_base / v_base opaque in a loop: it stops the compiler from hoisting a dozen
+  // loop-invariant per-lane addresses out of the loop into registers the loop cannot spare;
+  // recomputing them costs a few vector-ALU instructions per period.
+  auto opaque_bases = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(k_base), "+v"(v_base)); };
+  // One period = two steps.  Period p runs steps 2p+1 and 2p+2: it reads K tile p + 1 and the
+  // V^T tiles p and p + 1 (the latter only its first half, for the next period's first step).
+  // After its barrier it issues the loads of K(p + 2) and V(p + 2), one instruction per slice
+  // of its first step, into the buffers that held K(p) and V(p - 1), both last read before
+  // that barrier; the next period's barrier waits for them.  Past the last tile the loads repeat
+  // tile T - 1 into buffers nobody reads again, which keeps the loop free of branches.
+  const TileLoad no_ld = {};
+  const Limit no_lim = {};
+  if (!GLOBAL) {
+    // ---- prologue: tiles 0 and 1 must have landed before the first step
+    __syncthreads();                               // every wavefront has left its staging area
+    const TileLoad ld = {};                        // (images: addressed by tile number)
+    load_tile(ld, 0);
+    load_tile(ld, min(1, T - 1));
     PC_WAIT_VMCNT(0);
     __syncthreads();
     first_qk(s_buf[0]);
-    step(with_mask{}, no{}, yes{}, no{}, 0, 0, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
-
-    // One period = two steps.  Period p runs steps 2p+1 and 2p+2: it reads K tile p + 1 and the
-    // V^T tiles p and p + 1 (the latter only its first half, for the next period's first step).
-    // After its barrier it issues the loads of K(p + 4) and V(p + 4), one instruction per slice
-    // of its first step, into the buffers that held K(p) and V(p - 1), both last read before
-    // that barrier.  Tiles are first read three periods after their loads were issued, so before
-    // a barrier a wavefront only waits for the loads it issued two periods earlier (the two
-    // newest batches may stay in flight).  Past the last tile the loads repeat tile T - 1 into
-    // buffers nobody reads again, which keeps the loop free of branches.
+    step(with_mask{}, no{}, yes{}, no{}, no_lim, 8.0f, 0, 0, 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
     auto period = [&](auto mask_tag, int p) __attribute__((always_inline)) {
-      // Opaque no-ops on the address seeds: they stop the compiler from hoisting a dozen
-      // loop-invariant per-lane addresses out of the loop into registers the loop cannot spare;
-      // recomputing them costs a few vector-ALU instructions per period.
-      asm volatile("" : "+v"(k_base), "+v"(v_base));
+      opaque_bases();
       PC_WAIT_VMCNT(0);
       __syncthreads();
       const int t_ld = min(p + 2, T - 1);
-      step(mask_tag, yes{}, yes{}, yes{}, 2 * p + 1, t_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
-      step(mask_tag, yes{}, yes{}, no{}, 2 * p + 2, 0, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+      step(mask_tag, yes{}, yes{}, yes{}, no_lim, 8.0f, 2 * p + 1, 32 * (2 * p + 1), t_ld, ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      step(mask_tag, yes{}, yes{}, no{}, no_lim, 8.0f, 2 * p + 2, 32 * (2 * p + 2), 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
     };
     const int n_plain = min(T - 1, max(0, (J0 - 1) / 2));   // periods whose steps need no mask
     // Last step with a key visible to any row of this wavefront.  On the diagonal the steps
     // behind it hold only masked keys: the wavefront keeps the workgroup's barrier count but
     // leaves their arithmetic out (the tile loads of the last period only repeat tile T - 1).
-    const int j_need = __builtin_amdgcn_readfirstlane(
-        min(row0 + 32 * NB - 1 + a.causal_offset, n_valid - 1) >> 5);
+    const int j_need = __builtin_amdgcn_readfirstlane(min(row0 + 32 * NB - 1, n_valid - 1) >> 5);
     const bool skip_last_period = T >= 2 && j_need < 2 * T - 3;
     const int n_periods = skip_last_period ? T - 2 : T - 1;
     int p = 0;
@@ -615,11 +815,55 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
     PC_WAIT_VMCNT(0);
     __syncthreads();
     if (j_need >= 2 * T - 1) {
-      step(with_mask{}, yes{}, no{}, no{}, 2 * T - 1, 0, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      step(with_mask{}, yes{}, no{}, no{}, no_lim, 8.0f, 2 * T - 1, 32 * (2 * T - 1), 0, no_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
       last_pv(p_buf[1]);
     } else {
       last_pv(p_buf[0]);                                     // P V of the last step that ran (an even one)
     }
+  } else if (T > 0) {
+    // The same pipeline over the cursor's tiles; a tile carries its own limits (tile p + 2 is the
+    // cursor's, lim0 / lim1 belong to tiles p and p + 1).  Every row that sees a key of the run sees
+    // its first one, so the first step sets the row's reference as in the local kernel.
+    __syncthreads();
+    load_tile(tile_load(), 0);
+    Limit lim0 = {cur.cut, cur.c0};
+    cur_next();
+    load_tile(tile_load(), min(1, T - 1));
+    PC_WAIT_VMCNT(0);
+    __syncthreads();
+    first_qk(s_buf[0]);
+    step(with_mask{}, no{}, yes{}, no{}, lim0, 8.0f, 0, 0, 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+    auto period = [&](auto mask_tag, int p) __attribute__((always_inline)) {
+      // the cursor is on tile p + 1 here
+      const Limit lim1 = {cur.cut, cur.c0};
+      // at the start of a segment the reference moves up to the step's maximum, however little it
+      // grew, as it does at the start of a run: probability 1 is exact in bf16, so a short
+      // segment's heaviest key carries no rounding error
+      const float window = cur.seg_start ? 0.0f : 8.0f;
+      cur_next();                                            // tile p + 2 (or the last one again)
+      const TileLoad ld = tile_load();
+      const int t_ld = min(p + 2, T - 1);
+      opaque_bases();
+      PC_WAIT_VMCNT(0);
+      __syncthreads();
+      step(mask_tag, yes{}, yes{}, yes{}, lim0, 8.0f, 2 * p + 1, 32, t_ld, ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      step(mask_tag, yes{}, yes{}, no{}, lim1, window, 2 * p + 2, 0, 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+      lim0 = lim1;
+    };
+    int p = 0;
+    for (; p < run_full - 1; ++p) period(no_mask{}, p);      // tiles p and p + 1 are both unmasked
+    for (; p < T - 1; ++p) period(with_mask{}, p);
+    PC_WAIT_VMCNT(0);
+    __syncthreads();
+    // does the last tile's second half hold a key that some row of the wavefront sees?
+    if (__builtin_amdgcn_readfirstlane(min(lim0.cut - 1, min(row0 + 31, rows_wg - 1) / G - lim0.c0)) >= 32) {
+      step(with_mask{}, yes{}, no{}, no{}, lim0, 8.0f, 2 * T - 1, 32, 0, no_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      last_pv(p_buf[1]);
+    } else {
+      last_pv(p_buf[0]);
+    }
+  } else {
+    __syncthreads();                               // every wavefront has left its staging area
   }
 
   // ---- epilogue: lane halves hold disjoint key subsets of the same query
@@ -628,9 +872,9 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
     const float l = pc_xhalf_sum(l_run[nb]);
     const float inv_l = l > 0.f ? 1.f / l : 0.f;
     const float lse = l > 0.f ? m_run[nb] * PC_LN2 + logf(l) : -INFINITY;
-    if (PARTIAL) {
+    if (GLOBAL && a.n_parts > 1) {
       if (my_row[nb] < seq_rows) {
-        const long long prow = ((((long long)seq * a.n_parts_total + a.part0 + part) * a.n_rows) + my_row[nb]) * a.n_q_heads + h;
+        const long long prow = (((long long)seq * a.n_parts + part) * a.n_rows + my_row[nb] / G) * a.n_q_heads + h + my_row[nb] % G;
         float* po = a.part_o + prow * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -668,30 +912,29 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
         const u32x4 x = *(const u32x4*)(st_o + (r * PPR + (l_piece ^ (r % PPR))) * 8);
         const int grow = row0 + 32 * nb + r;
         if (grow < seq_rows)
-          pc_store_once((u32x4*)((uint16_t*)a.o + (((long long)seq * a.n_rows + grow) * a.n_q_heads + h) * D + 8 * l_piece), x);
+          pc_store_once((u32x4*)((uint16_t*)a.o + row_at(grow) * D + 8 * l_piece), x);
       }
       if (my_row[nb] < seq_rows && hf == 0 && a.lse)
-        a.lse[((long long)seq * a.n_q_heads + h) * a.n_rows + my_row[nb]] = lse;
+        a.lse[((long long)seq * a.n_q_heads + h + (GLOBAL ? my_row[nb] % G : 0)) * a.n_rows + pos_of(my_row[nb])] = lse;
     }
   }
 }
 
-template <int D, bool ROPE_Q, bool PARTIAL>
+template <int D, bool GLOBAL>
 static int launch_flash_t(const PcFlashArgs& a, hipStream_t st) {
   using SM = FlashSmem<D>;
-  auto kern = flash_fwd_kernel<D, ROPE_Q, PARTIAL>;
+  auto kern = flash_fwd_kernel<D, GLOBAL>;
   static std::atomic<uint64_t> raised{0};          // one per instantiation of this launcher
   const int lds_rc = pc_raise_dynamic_lds((const void*)kern, SM::BYTES, raised);
   if (lds_rc != PC_OK) return lds_rc;
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int n_qt = (a.n_rows + PC_FA_BM - 1) / PC_FA_BM;
-  const long long per_group = (long long)G * n_qt * a.n_parts_grid;
-  const long long groups = (long long)a.n_seq * a.n_kv_heads;
-  const long long blocks = (groups + 7) / 8 * per_group * 8;
+  const long long rows_wg = GLOBAL ? (long long)a.n_rows * G : a.n_rows;
+  const long long n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
+  const long long blocks = (long long)a.n_seq * a.n_kv_heads * n_qt * (GLOBAL ? a.n_parts : G);
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
-  // tile loads address one (sequence, part, head) region with 32-bit byte offsets
-  if (((long long)a.n_keys + 63) / 64 * 64 * D * 2 >= 0x7fffffffLL) return PC_ERR_SHAPE;
+  // image loads address one (sequence, head) region with 32-bit byte offsets
+  if (!GLOBAL && ((long long)a.n_rows + 63) / 64 * 64 * D * 2 >= 0x7fffffffLL) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_FLASH, st);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PC_FA_THREADS), SM::BYTES, st, a);
   PC_LAUNCH_CHECK();
@@ -699,11 +942,28 @@ static int launch_flash_t(const PcFlashArgs& a, hipStream_t st) {
 }
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
-  const bool rope = a.table != nullptr, partial = a.part_o != nullptr;
-  if (a.head_dim == 128) {
-    if (rope) return partial ? launch_flash_t<128, true, true>(a, st) : launch_flash_t<128, true, false>(a, st);
-    return partial ? launch_flash_t<128, false, true>(a, st) : launch_flash_t<128, false, false>(a, st);
+  if (a.head_dim == 128) return a.global ? launch_flash_t<128, true>(a, st) : launch_flash_t<128, false>(a, st);
+  return a.global ? launch_flash_t<64, true>(a, st) : launch_flash_t<64, false>(a, st);
+}
+
+int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles) {
+  // The parts that minimise the estimated time of the tile kernel and the merge together.  A
+  // workgroup costs a fixed 10 us (query rows, first tiles, output) and a time per tile that
+  // depends on whether it shares its CU; 512 of them run at a time (two per CU).  The partials of
+  // P > 1 parts are written and read once more as fp32, next to a launch.
+  const long long G = n_q_heads / n_kv_heads;
+  const long long wgs = (long long)n_seq * n_kv_heads * ((n_rows * G + PC_FA_BM - 1) / PC_FA_BM);
+  const double tile_us = head_dim == 128 ? 1.5 : 0.9;
+  const double merge_us = 2.0 * n_seq * n_rows * n_q_heads * head_dim * 4 / 4e6;
+  const int p_max = (int)(n_tiles < 1 ? 1 : (n_tiles > 64 ? 64 : n_tiles));
+  int best_p = 1;
+  double best = 0.0;
+  for (int p = 1; p <= p_max; ++p) {
+    const long long n = wgs * p;
+    const double tiles = (double)((n_tiles + p - 1) / p);
+    const double run = n <= 256 ? tiles * (0.6 * tile_us) + 10.0 : (double)((n + 511) / 512) * (tiles * tile_us + 10.0);
+    const double cost = run + (p > 1 ? 4.0 + merge_us * p : 0.0);
+    if (p == 1 || cost < best) { best = cost; best_p = p; }
   }
-  if (rope) return partial ? launch_flash_t<64, true, true>(a, st) : launch_flash_t<64, true, false>(a, st);
-  return partial ? launch_flash_t<64, false, true>(a, st) : launch_flash_t<64, false, false>(a, st);
+  return best_p;
 }
