@@ -411,10 +411,10 @@ int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, 
 
 // ------------------------------------------------------------------------------------------
 // Rotate the query rows of the split-KV kernel at positions pos0 + t (fp64 angles; pos0 < 0:
-// the rows are already rotated) and multiply them by `mul` before the one rounding to bf16.
+// the rows are already rotated).
 __global__ void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
                               long long n_pairs, int n_q, int n_heads, int D, int pos0,
-                              double log_base, double mul) {
+                              double log_base) {
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= n_pairs) return;
   const int half = D / 2;
@@ -427,18 +427,18 @@ __global__ void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restri
     sincos((double)(pos0 + t) * theta, &sn, &cs);
   }
   const double x1 = bf16_bits_to_f32(q[row * D + i]), x2 = bf16_bits_to_f32(q[row * D + i + half]);
-  q_rot[row * D + i] = (uint16_t)f32_to_bf16_bits((float)((x1 * cs - x2 * sn) * mul));
-  q_rot[row * D + i + half] = (uint16_t)f32_to_bf16_bits((float)((x2 * cs + x1 * sn) * mul));
+  q_rot[row * D + i] = (uint16_t)f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
+  q_rot[row * D + i + half] = (uint16_t)f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
 }
 
 int pc_launch_rope_q(const void* q, void* q_rot, long long n_rows, int n_q, int n_heads, int D,
-                     int pos0, float base, float mul, hipStream_t st) {
+                     int pos0, float base, hipStream_t st) {
   const long long n_pairs = n_rows * (D / 2);
   if (n_pairs == 0) return PC_OK;
   PcProfScope prof(PC_KERNEL_ROPE_Q, st);
   hipLaunchKernelGGL(rope_q_kernel, dim3((unsigned)((n_pairs + 255) / 256)), dim3(256), 0, st,
                      (const uint16_t*)q, (uint16_t*)q_rot, n_pairs, n_q, n_heads, D, pos0,
-                     log((double)(pos0 >= 0 ? base : 2.0f)), (double)mul);
+                     log((double)(pos0 >= 0 ? base : 2.0f)));
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

@@ -384,7 +384,7 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
   const void* q_rot = q;
   if (q_pos0 >= 0) {
     rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                          q_pos0, rope_base, 1.0f, st);
+                          q_pos0, rope_base, st);
     if (rc != PC_OK) return rc;
     q_rot = base + w.q_rot;
   }
@@ -613,7 +613,7 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
     const void* q_rot = q;
     if (q_pos0 >= 0) {
       rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                            q_pos0, rope_base, 1.0f, st);
+                            q_pos0, rope_base, st);
       if (rc != PC_OK) return rc;
       q_rot = base + w.q_rot;
     }

@@ -125,8 +125,8 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 
 int pc_launch_rope_table(float2* table, int pos0, int n_pos, int head_dim, float base, hipStream_t st);
 
-// K/V pre-pass: K (rotated when a table is given; skipped when k == nullptr) -> k_rope (row-major,
-// optional) and K tile images (optional); V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
+// K/V pre-pass of the local attention: K rotated -> k_rope (row-major, optional) and K tile images;
+// V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
 int pc_launch_kv_prepass(const void* k, const void* v, const float2* table, void* k_rope,
                          void* k_img, void* v_img, int n_seq, int L, int Lp, int n_kv_heads,
                          int head_dim, hipStream_t st);
@@ -183,7 +183,7 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
                      hipStream_t st);
 
 int pc_launch_rope_q(const void* q, void* q_rot, long long n_rows, int n_q, int n_heads, int D,
-                     int pos0, float base, float mul, hipStream_t st);
+                     int pos0, float base, hipStream_t st);
 // How the split-KV decode kernels cut the keys into workgroups (n_bg = batch * H_kv): the keys of
 // a (sequence, KV head) group, all its segments laid end to end in blocks of 32 keys, are cut
 // into n_parts equal runs of blocks, one workgroup (and one partial result) each.

@@ -88,9 +88,9 @@ __global__ __launch_bounds__(256) void kv_prepass_kernel(
   const long long seq_base = (long long)seq * L;
   const long long img = (((long long)seq * n_kv_heads + g) * (Lp / 64) + tile) * (64 * D);
 
-  // ---- K: rotate pairs (i, i + D/2) when a table is given; a thread handles 8 consecutive i of one row
+  // ---- K: rotate pairs (i, i + D/2); a thread handles 8 consecutive i of one row
   constexpr int K_ITEMS = 64 * (HALF / 8);
-  for (int it = threadIdx.x; k != nullptr && it < K_ITEMS; it += 256) {
+  for (int it = threadIdx.x; it < K_ITEMS; it += 256) {
     const int r = it / (HALF / 8), i0 = (it % (HALF / 8)) * 8;
     const int row = row0 + r;
     uint4 oa = make_uint4(0, 0, 0, 0), ob = make_uint4(0, 0, 0, 0);
@@ -98,32 +98,26 @@ __global__ __launch_bounds__(256) void kv_prepass_kernel(
       const long long off = ((seq_base + row) * n_kv_heads + g) * D;
       const uint4 a = pc_load_once((const uint4*)(k + off + i0));
       const uint4 b = pc_load_once((const uint4*)(k + off + HALF + i0));
-      if (table != nullptr) {
-        const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-        uint32_t ra[4], rb[4];
-        const float2* cs = table + (long long)row * HALF + i0;
+      const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+      uint32_t ra[4], rb[4];
+      const float2* cs = table + (long long)row * HALF + i0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float2 c0 = cs[2 * e], c1 = cs[2 * e + 1];
-          const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
-          const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
-          ra[e] = pack_bf16x2(x1l * c0.x - x2l * c0.y, x1h * c1.x - x2h * c1.y);
-          rb[e] = pack_bf16x2(x2l * c0.x + x1l * c0.y, x2h * c1.x + x1h * c1.y);
-        }
-        oa = make_uint4(ra[0], ra[1], ra[2], ra[3]);
-        ob = make_uint4(rb[0], rb[1], rb[2], rb[3]);
-      } else {
-        oa = a; ob = b;
+      for (int e = 0; e < 4; ++e) {
+        const float2 c0 = cs[2 * e], c1 = cs[2 * e + 1];
+        const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
+        const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
+        ra[e] = pack_bf16x2(x1l * c0.x - x2l * c0.y, x1h * c1.x - x2h * c1.y);
+        rb[e] = pack_bf16x2(x2l * c0.x + x1l * c0.y, x2h * c1.x + x1h * c1.y);
       }
+      oa = make_uint4(ra[0], ra[1], ra[2], ra[3]);
+      ob = make_uint4(rb[0], rb[1], rb[2], rb[3]);
       if (k_rope != nullptr) {
         pc_store_once((uint4*)(k_rope + off + i0), oa);
         pc_store_once((uint4*)(k_rope + off + HALF + i0), ob);
       }
     }
-    if (k_img != nullptr) {
-      pc_store_once((uint4*)(k_img + img + ((i0 / 8) * 64 + r) * 8), oa);
-      pc_store_once((uint4*)(k_img + img + (((HALF + i0) / 8) * 64 + r) * 8), ob);
-    }
+    pc_store_once((uint4*)(k_img + img + ((i0 / 8) * 64 + r) * 8), oa);
+    pc_store_once((uint4*)(k_img + img + (((HALF + i0) / 8) * 64 + r) * 8), ob);
   }
 
   // ---- V: 64 x D tile -> LDS -> V^T image (zero beyond row L)
@@ -947,22 +941,24 @@ int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
 }
 
 int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles) {
-  // The parts that minimise the estimated time of the tile kernel and the merge together.  A
-  // workgroup costs a fixed 10 us (query rows, first tiles, output) and a time per tile that
-  // depends on whether it shares its CU; 512 of them run at a time (two per CU).  The partials of
-  // P > 1 parts are written and read once more as fp32, next to a launch.
+  // The parts that minimise the estimated time of the tile kernel and the merge together.
+  // Measured (parts swept from 1 to 32 over eight shapes; head_dim 128): a workgroup costs about
+  // 10 us (query rows, first tiles, output) and 1.27 us a tile alone on its CU, 2.1 us next to
+  // another (512 fit at a time); the merge 5 us, and 0.4 us and 7 TB/s for every part.  E.g. 512
+  // rows, 32 / 8 heads, 8 x 2048 keys (128 workgroups a part): 342 us with 1 part, 205 with 2, 163
+  // with 4, 176 with 8, 208 with 16; four such sequences: 575 with 1 part, 625 with 2.
   const long long G = n_q_heads / n_kv_heads;
   const long long wgs = (long long)n_seq * n_kv_heads * ((n_rows * G + PC_FA_BM - 1) / PC_FA_BM);
-  const double tile_us = head_dim == 128 ? 1.5 : 0.9;
-  const double merge_us = 2.0 * n_seq * n_rows * n_q_heads * head_dim * 4 / 4e6;
+  const double pair_us = head_dim == 128 ? 2.1 : 1.4, alone_us = head_dim == 128 ? 1.27 : 0.95;
+  const double merge_us = 0.4 + (double)n_seq * n_rows * n_q_heads * head_dim * 4 / 7e6;
   const int p_max = (int)(n_tiles < 1 ? 1 : (n_tiles > 64 ? 64 : n_tiles));
   int best_p = 1;
   double best = 0.0;
   for (int p = 1; p <= p_max; ++p) {
     const long long n = wgs * p;
     const double tiles = (double)((n_tiles + p - 1) / p);
-    const double run = n <= 256 ? tiles * (0.6 * tile_us) + 10.0 : (double)((n + 511) / 512) * (tiles * tile_us + 10.0);
-    const double cost = run + (p > 1 ? 4.0 + merge_us * p : 0.0);
+    const double run = n <= 256 ? tiles * alone_us + 10.0 : (double)((n + 511) / 512) * (tiles * pair_us + 10.0);
+    const double cost = run + (p > 1 ? 5.0 + merge_us * p : 0.0);
     if (p == 1 || cost < best) { best = cost; best_p = p; }
   }
   return best_p;
