@@ -119,7 +119,7 @@ static PrefillWs prefill_ws_layout(const pc_shape* s) {
   const size_t img_bytes = (size_t)s->n_chunks * s->n_kv_heads * s->head_dim * w.Lp * 2;   // tile images
   w.v_img = off; off = pc_align_up(off + img_bytes, kAlign);
   w.k_img = off; off = pc_align_up(off + img_bytes, kAlign);
-  w.ml = off;    off = pc_align_up(off + pc_scores_ml_bytes(s), kAlign);
+  w.ml = off;    off = pc_align_up(off + pc_scores_ws_bytes(s), kAlign);
   w.total = off;
   return w;
 }
@@ -137,7 +137,7 @@ extern "C" size_t pc_chunk_query_scores_workspace_bytes(const pc_shape* s) {
   if (check_shape(s) != PC_OK || check_obs(s, false) != PC_OK) return 0;
   const size_t L = (size_t)s->chunk_len + s->query_len;
   return pc_align_up(L * (s->head_dim / 2) * sizeof(float2), kAlign) +
-         pc_align_up(pc_scores_ml_bytes(s), kAlign);
+         pc_align_up(pc_scores_ws_bytes(s), kAlign);
 }
 
 extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const void* k, const void* v,

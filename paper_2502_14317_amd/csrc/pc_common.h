@@ -173,7 +173,7 @@ int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
 int pc_launch_self_info(const void* logits, const int32_t* targets, int n_chunks, int n_tokens,
                         int vocab, int negate, float* token_nll, float* info, hipStream_t st);
 
-size_t pc_scores_ml_bytes(const pc_shape* s);
+size_t pc_scores_ws_bytes(const pc_shape* s);
 // Pre-pass duties the first score pass can take over (it reads and rotates every key anyway):
 // the rotated keys (k_rope, nullable), the K tile images and the V^T tile images of
 // pc_launch_kv_prepass, Lp = L rounded up to 64.

@@ -28,8 +28,9 @@
 // and moves V through LDS into the V^T tile images.  The keys are then read from HBM once for
 // both jobs, and rotated once.
 //
-// Any number of voting rows: the (row, head) columns of a KV group are handled in rounds of 128
-// (4 blocks of 32), the key tiles being re-read (from the caches) in every round.
+// Any number of voting rows: up to 128 (row, head) columns of a KV group (4 blocks of 32) are kept in
+// registers while the keys stream by (scores_kernel).  More columns turn the loops round
+// (scores_many_kernel): 128 keys are staged once and stay in LDS, the columns stream by.
 #include "pc_common.h"
 #include <math.h>
 
@@ -40,6 +41,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #define PC_SC_KB 256        // keys per workgroup: the smallest block (sizes the workspace)
 #define PC_SC_KB_MAX 1024   // the largest
 #define PC_SC_TILE 64       // keys staged in LDS at a time
+#define PC_SC_KB_MANY 128   // keys per workgroup with more than 4 column blocks; half where that leaves CUs idle
 #define PC_SC_LOG2E 1.4426950408889634f
 
 struct PcScoreArgs {
@@ -48,9 +50,11 @@ struct PcScoreArgs {
   const int32_t* chunk_lens; // [C] context rows per chunk or nullptr (= w)
   const float2* table;     // [L, D/2] (cos, sin)
   float2* ml;              // workspace [C, H_kv, n_kb, n_cols] (max in log2 units, sum)
-  float* lse2;             // workspace [C, H_kv, n_cols] row logsumexp in log2 units
+  float* lse2;             // workspace [C, H_kv, 32 n_cb] row logsumexp in log2 units (+inf behind n_cols)
+  const uint16_t* q_split; // workspace [C, H_kv, n_cb][hi, lo][D / 16][64 lanes][8]: rotated, scaled, split query
+                           //   columns as MFMA operands (only with more than 4 column blocks)
   float* tok_score;        // [C, H_kv, w]
-  int L, w, w_obs, n_q_heads, n_kv_heads, n_kb, n_cols;
+  int L, w, w_obs, n_q_heads, n_kv_heads, n_kb, n_cols, n_cb;
   int kb_keys;             // keys per workgroup: 256, 512 or 1024 (at most 512 when WPC == 4)
   float scale_log2;        // softmax scale x log2(e), folded into the query operand
   float* blk_sum;          // workspace [C, H_kv, n_kb]: sum of each pass-2 block's tok_score
@@ -69,6 +73,172 @@ __device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, u
   lo = pack_bf16x2(x0 - bf16_lo_to_f32(hi), x1 - bf16_hi_to_f32(hi));
 }
 
+// Column `col` of a KV group's (voting row, head) columns as an MFMA operand, the lane half's part:
+// the query row rotated at its position, scaled to log2 units, split hi / lo.
+template <int D>
+__device__ __forceinline__ void load_query_column(const PcScoreArgs& a, int c, int g, int G, int first_obs, int col,
+                                                  int hf, bf16x8 (&qhi)[D / 16], bf16x8 (&qlo)[D / 16]) {
+  constexpr int KS = D / 16, HALF = D / 2;
+  const int row = first_obs + col % a.w_obs;
+  const uint16_t* qrow = a.q + (((long long)c * a.L + row) * a.n_q_heads + g * G + col / a.w_obs) * D;
+  const float2* cs = a.table + (long long)row * HALF;
+#pragma unroll
+  for (int ks = 0; ks < KS / 2; ++ks) {
+    const int i0 = 16 * ks + 8 * hf;
+    const uint4 x1 = *(const uint4*)(qrow + i0);
+    const uint4 x2 = *(const uint4*)(qrow + HALF + i0);
+    const uint32_t aw[4] = {x1.x, x1.y, x1.z, x1.w}, bw[4] = {x2.x, x2.y, x2.z, x2.w};
+    uint32_t h1[4], l1[4], h2[4], l2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float2 c0 = cs[i0 + 2 * e], c1 = cs[i0 + 2 * e + 1];
+      const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
+      const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
+      // logits come out of the matrix cores in log2 units: the scale rides on q
+      split_bf16x2((x1l * c0.x - x2l * c0.y) * a.scale_log2, (x1h * c1.x - x2h * c1.y) * a.scale_log2, h1[e], l1[e]);
+      split_bf16x2((x2l * c0.x + x1l * c0.y) * a.scale_log2, (x2h * c1.x + x1h * c1.y) * a.scale_log2, h2[e], l2[e]);
+    }
+    uint4 t;
+    t = make_uint4(h1[0], h1[1], h1[2], h1[3]); qhi[ks] = *(bf16x8*)&t;
+    t = make_uint4(l1[0], l1[1], l1[2], l1[3]); qlo[ks] = *(bf16x8*)&t;
+    t = make_uint4(h2[0], h2[1], h2[2], h2[3]); qhi[ks + KS / 2] = *(bf16x8*)&t;
+    t = make_uint4(l2[0], l2[1], l2[2], l2[3]); qlo[ks + KS / 2] = *(bf16x8*)&t;
+  }
+}
+
+// K tile staging, split in two so that the loads of the next tile are in flight while the matrix
+// cores work on this one: fetch (global -> registers), stage (rotate in fp32, split hi / lo,
+// registers -> LDS).  A thread always handles the same 8 rotation pairs, of rows RP apart, so it
+// reads (cos, sin) from the table once, for its first row, and turns them by the constant angle of
+// RP rows from item to item (one complex multiplication per pair in fp32, at most kb_keys / RP - 1
+// <= 31 in a chain: ~1e-7 relative per link).
+// PRE: pass 1, which also carries the pre-pass duties where they are wanted (`pre`).
+template <int D, int TILE, bool PRE>
+struct PcKeyStage {
+  static constexpr int HALF = D / 2, KSTRIDE = D + 8;
+  static constexpr int ITEMS = TILE * (HALF / 8) / PC_SC_THREADS;      // per thread and tile
+  static constexpr int RP = PC_SC_THREADS / (HALF / 8);                // rows between a thread's items
+  static_assert(ITEMS >= 1 && TILE * (HALF / 8) % PC_SC_THREADS == 0, "tile / thread mismatch");
+  // V: a thread takes 8 consecutive keys x 4 values (eight 8-byte loads), transposes them in
+  // registers and stores four 16-byte granules of the V^T image, (8 keys, d) each
+  static constexpr int V_ALL = (TILE / 8) * (D / 4);                   // such items per tile
+  static constexpr int V_ITEMS = (V_ALL + PC_SC_THREADS - 1) / PC_SC_THREADS;
+  int tid, st_r0, st_i0;
+  bool pre;
+  uint4 pf_x1[ITEMS], pf_x2[ITEMS];
+  float2 cs_cur[8], cs_step[8];
+  u32x2 pf_v[PRE ? V_ITEMS : 1][8];
+
+  __device__ __forceinline__ void begin(const PcScoreArgs& a, int thread, int first_key, bool with_pre) {
+    tid = thread; pre = with_pre;
+    st_r0 = tid / (HALF / 8); st_i0 = (tid % (HALF / 8)) * 8;
+    const float4* c4 = (const float4*)(a.table + (long long)min(first_key + st_r0, a.L - 1) * HALF + st_i0);
+    const float4* s4 = (const float4*)(a.table + (long long)min(RP, a.L - 1) * HALF + st_i0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float4 cv = c4[e], sv4 = s4[e];
+      cs_cur[2 * e] = make_float2(cv.x, cv.y); cs_cur[2 * e + 1] = make_float2(cv.z, cv.w);
+      cs_step[2 * e] = make_float2(sv4.x, sv4.y); cs_step[2 * e + 1] = make_float2(sv4.z, sv4.w);
+    }
+  }
+  __device__ __forceinline__ void fetch(const PcScoreArgs& a, int c, int g, int key0) {
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u) {
+      const int row = min(key0 + st_r0 + u * RP, a.L - 1);
+      const uint16_t* krow = a.k + (((long long)c * a.L + row) * a.n_kv_heads + g) * D;
+      pf_x1[u] = pc_load_once((const uint4*)(krow + st_i0));
+      pf_x2[u] = pc_load_once((const uint4*)(krow + HALF + st_i0));
+    }
+    if (pre) {
+#pragma unroll
+      for (int u = 0; u < V_ITEMS; ++u) {
+        const int it = tid + u * PC_SC_THREADS;
+        const int row0 = key0 + 8 * (it / (D / 4)), d4 = (it % (D / 4)) * 4;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          pf_v[u][j] = u32x2{0u, 0u};                                // rows past the sequence: zeros in the image
+          if (it < V_ALL && row0 + j < a.L)
+            pf_v[u][j] = __builtin_nontemporal_load(
+                (const u32x2*)(a.v + (((long long)c * a.L + row0 + j) * a.n_kv_heads + g) * D + d4));
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void stage(const PcScoreArgs& a, int c, int g, int key0, uint16_t* k_hi, uint16_t* k_lo) {
+    const long long img_cg = ((long long)c * a.n_kv_heads + g) * (a.Lp / 64);   // first tile image of (c, g)
+    if (pre) {
+      // V^T tile images: granule (c8, d) = V[keys 8 c8 .. 8 c8 + 7][d]; word e of a granule pairs
+      // the values of keys 2 e and 2 e + 1 (one byte permute per word)
+#pragma unroll
+      for (int u = 0; u < V_ITEMS; ++u) {
+        const int it = tid + u * PC_SC_THREADS;
+        const int row0 = key0 + 8 * (it / (D / 4)), d4 = (it % (D / 4)) * 4;
+        if (it < V_ALL && row0 < a.Lp) {
+          uint16_t* img = a.v_img + (img_cg + row0 / 64) * (64LL * D) + (((row0 % 64) / 8) * D + d4) * 8;
+          uint4 gr[4];
+          uint32_t* gw = (uint32_t*)gr;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const u32x2 r0 = pf_v[u][2 * e], r1 = pf_v[u][2 * e + 1];
+            gw[0 * 4 + e] = __builtin_amdgcn_perm(r1.x, r0.x, 0x05040100u);   // d4 + 0: low halves
+            gw[1 * 4 + e] = __builtin_amdgcn_perm(r1.x, r0.x, 0x07060302u);   // d4 + 1: high halves
+            gw[2 * 4 + e] = __builtin_amdgcn_perm(r1.y, r0.y, 0x05040100u);   // d4 + 2
+            gw[3 * 4 + e] = __builtin_amdgcn_perm(r1.y, r0.y, 0x07060302u);   // d4 + 3
+          }
+          // ordinary stores: an instruction writes 16 bytes of every 64 a lane owns, and the
+          // last-level cache merges the four pieces of a line (with the streaming hint they
+          // reached memory as partial lines: 2.4 times slower)
+#pragma unroll
+          for (int dd = 0; dd < 4; ++dd) *(uint4*)(img + dd * 8) = gr[dd];
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u) {
+      const int r = st_r0 + u * RP, i0 = st_i0;
+      const uint32_t aw[4] = {pf_x1[u].x, pf_x1[u].y, pf_x1[u].z, pf_x1[u].w};
+      const uint32_t bw[4] = {pf_x2[u].x, pf_x2[u].y, pf_x2[u].z, pf_x2[u].w};
+      uint32_t h1[4], l1[4], h2[4], l2[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float2 c0 = cs_cur[2 * e], c1 = cs_cur[2 * e + 1];
+        const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
+        const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
+        split_bf16x2(x1l * c0.x - x2l * c0.y, x1h * c1.x - x2h * c1.y, h1[e], l1[e]);
+        split_bf16x2(x2l * c0.x + x1l * c0.y, x2h * c1.x + x1h * c1.y, h2[e], l2[e]);
+      }
+      *(uint4*)(k_hi + r * KSTRIDE + i0) = make_uint4(h1[0], h1[1], h1[2], h1[3]);
+      *(uint4*)(k_lo + r * KSTRIDE + i0) = make_uint4(l1[0], l1[1], l1[2], l1[3]);
+      *(uint4*)(k_hi + r * KSTRIDE + HALF + i0) = make_uint4(h2[0], h2[1], h2[2], h2[3]);
+      *(uint4*)(k_lo + r * KSTRIDE + HALF + i0) = make_uint4(l2[0], l2[1], l2[2], l2[3]);
+      if (pre) {
+        // the hi halves are the rotated key rounded to bf16: the cache row and its K image granules
+        const int row = key0 + r;
+        const bool in_seq = row < a.L;
+        const uint4 oa = in_seq ? make_uint4(h1[0], h1[1], h1[2], h1[3]) : make_uint4(0, 0, 0, 0);
+        const uint4 ob = in_seq ? make_uint4(h2[0], h2[1], h2[2], h2[3]) : make_uint4(0, 0, 0, 0);
+        if (in_seq && a.k_rope != nullptr) {
+          uint16_t* dst = a.k_rope + (((long long)c * a.L + row) * a.n_kv_heads + g) * D;
+          pc_store_once((uint4*)(dst + i0), oa);
+          pc_store_once((uint4*)(dst + HALF + i0), ob);
+        }
+        if (row < a.Lp) {
+          uint16_t* img = a.k_img + (img_cg + row / 64) * (64LL * D);
+          pc_store_once((uint4*)(img + ((i0 / 8) * 64 + row % 64) * 8), oa);
+          pc_store_once((uint4*)(img + (((HALF + i0) / 8) * 64 + row % 64) * 8), ob);
+        }
+      }
+      // (cos, sin) of the thread's next row: angle + RP theta
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float cn = cs_cur[e].x * cs_step[e].x - cs_cur[e].y * cs_step[e].y;
+        const float sn = cs_cur[e].y * cs_step[e].x + cs_cur[e].x * cs_step[e].y;
+        cs_cur[e] = make_float2(cn, sn);
+      }
+    }
+  }
+};
+
 // WPC = wavefronts per block of 32 columns.  With 4 or more column blocks (a GQA group of 4
 // heads x 32 voting rows) a wavefront owns a column block and takes both 32-key halves of every
 // 64-key tile (WPC = 1).  With fewer column blocks the wavefronts of a block share its keys
@@ -78,11 +248,9 @@ template <int D, int PASS, int WPC>
 __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a) {
   // The pre-pass duties ride on pass 1 and are switched at run time (a.v_img != nullptr), so the
   // standalone score call and the fused one execute the same code and give the same bits.
-  constexpr bool PRE = PASS == 1;
-  constexpr int KS = D / 16, HALF = D / 2, KSTRIDE = D + 8;
+  constexpr int KS = D / 16, KSTRIDE = D + 8;
   constexpr int TILE = WPC == 4 ? 2 * PC_SC_TILE : PC_SC_TILE;   // keys staged in LDS at a time
   constexpr int NSUB = TILE / 32;                                // 32-key sub-blocks per tile
-  constexpr int CB_PER_ROUND = PC_SC_WAVES / WPC;
   __shared__ __attribute__((aligned(16))) uint16_t k_hi[TILE * KSTRIDE];
   __shared__ __attribute__((aligned(16))) uint16_t k_lo[TILE * KSTRIDE];
   constexpr int KB_CAP = WPC == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;   // LDS: two workgroups per CU
@@ -93,301 +261,151 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   const int G = a.n_q_heads / a.n_kv_heads;
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
-  const int n_cb = (a.n_cols + 31) / 32;
   // a short chunk is [len context rows ; the query rows]: its voting rows end at len + w_q
   const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
   const int first_obs = ctx_len + (a.L - a.w) - a.w_obs;
   const long long ml_base = (((long long)c * a.n_kv_heads + g) * a.n_kb) * a.n_cols;
 
-  const float* lse2 = a.lse2 + ((long long)c * a.n_kv_heads + g) * a.n_cols;
+  const float* lse2 = a.lse2 + ((long long)c * a.n_kv_heads + g) * (32 * a.n_cb);
 
   // pass 2: every wavefront accumulates its columns' share of the keys' sums in its own LDS row
   if (PASS == 2)
     for (int i = lane; i < a.kb_keys; i += PC_WAVE) tok_part[wave][i] = 0.f;
 
-  const int n_rounds = (n_cb + CB_PER_ROUND - 1) / CB_PER_ROUND;
   const int kb0 = wave % WPC;                      // this wavefront's first sub-block of a tile
-  for (int round = 0; round < n_rounds; ++round) {
-    const int cb = round * CB_PER_ROUND + wave / WPC;
-    const bool active = cb < n_cb;
-    // ---- this lane's column as an MFMA operand: rotate at the row's position, split hi/lo
-    const int col = min(32 * cb + n, a.n_cols - 1);
-    const int hg = col / a.w_obs, qrow_idx = first_obs + col % a.w_obs;
-    bf16x8 qhi[KS], qlo[KS];
-    if (active) {
-      const uint16_t* qrow = a.q + (((long long)c * a.L + qrow_idx) * a.n_q_heads + g * G + hg) * D;
-      const float2* cs = a.table + (long long)qrow_idx * HALF;
+  const int cb = wave / WPC;                       // its column block
+  const bool active = cb < a.n_cb;
+  // ---- this lane's column as an MFMA operand
+  const int col = min(32 * cb + n, a.n_cols - 1);
+  bf16x8 qhi[KS], qlo[KS];
+  if (active) load_query_column<D>(a, c, g, G, first_obs, col, hf, qhi, qlo);
+  // pass 1: this lane's voting row (column) and its running statistics
+  const int my_qrow = first_obs + col % a.w_obs;
+  float m_run = -INFINITY, l_run = 0.f;
+  // pass 2: the voting rows / logsumexp of the 16 result registers (rows of S)
+  float lse_r[16];
+  int qrow_r[16];
+  if (PASS == 2) {
 #pragma unroll
-      for (int ks = 0; ks < KS / 2; ++ks) {
-        const int i0 = 16 * ks + 8 * hf;
-        const uint4 x1 = *(const uint4*)(qrow + i0);
-        const uint4 x2 = *(const uint4*)(qrow + HALF + i0);
-        const uint32_t aw[4] = {x1.x, x1.y, x1.z, x1.w}, bw[4] = {x2.x, x2.y, x2.z, x2.w};
-        uint32_t h1[4], l1[4], h2[4], l2[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float2 c0 = cs[i0 + 2 * e], c1 = cs[i0 + 2 * e + 1];
-          const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
-          const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
-          // logits come out of the matrix cores in log2 units: the scale rides on q
-          split_bf16x2((x1l * c0.x - x2l * c0.y) * a.scale_log2, (x1h * c1.x - x2h * c1.y) * a.scale_log2, h1[e], l1[e]);
-          split_bf16x2((x2l * c0.x + x1l * c0.y) * a.scale_log2, (x2h * c1.x + x1h * c1.y) * a.scale_log2, h2[e], l2[e]);
-        }
-        uint4 t;
-        t = make_uint4(h1[0], h1[1], h1[2], h1[3]); qhi[ks] = *(bf16x8*)&t;
-        t = make_uint4(l1[0], l1[1], l1[2], l1[3]); qlo[ks] = *(bf16x8*)&t;
-        t = make_uint4(h2[0], h2[1], h2[2], h2[3]); qhi[ks + KS / 2] = *(bf16x8*)&t;
-        t = make_uint4(l2[0], l2[1], l2[2], l2[3]); qlo[ks + KS / 2] = *(bf16x8*)&t;
-      }
+    for (int r = 0; r < 16; ++r) {
+      const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
+      const bool ok = active && cc < a.n_cols;
+      lse_r[r] = ok ? lse2[cc] : INFINITY;                // exp2(-inf) = 0 for padding columns
+      qrow_r[r] = ok ? first_obs + cc % a.w_obs : -1;
     }
-    // pass 1: this lane's voting row (column) and its running statistics
-    const int my_qrow = qrow_idx;
-    float m_run = -INFINITY, l_run = 0.f;
-    // pass 2: the voting rows / logsumexp of the 16 result registers (rows of S)
-    float lse_r[16];
-    int qrow_r[16];
-    if (PASS == 2) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
-        const bool ok = active && cc < a.n_cols;
-        lse_r[r] = ok ? lse2[cc] : INFINITY;                // exp2(-inf) = 0 for padding columns
-        qrow_r[r] = ok ? first_obs + cc % a.w_obs : -1;
-      }
-    }
+  }
 
-    // K tile staging, split in two so that the loads of tile t + 1 are in flight while the
-    // matrix cores work on tile t: fetch (global -> registers), stage (rotate in fp32, split
-    // hi / lo, registers -> LDS).  A thread always handles the same 8 rotation pairs, of rows
-    // RP apart, so it reads (cos, sin) from the table once, for its first row, and turns them by
-    // the constant angle of RP rows from item to item (one complex multiplication per pair in
-    // fp32, at most kb_keys / RP - 1 <= 31 in a chain: ~1e-7 relative per link).
-    constexpr int ITEMS = TILE * (HALF / 8) / PC_SC_THREADS;           // per thread and tile
-    constexpr int RP = PC_SC_THREADS / (HALF / 8);                     // rows between a thread's items
-    static_assert(ITEMS >= 1 && TILE * (HALF / 8) % PC_SC_THREADS == 0, "tile / thread mismatch");
-    const int st_r0 = tid / (HALF / 8), st_i0 = (tid % (HALF / 8)) * 8;
-    uint4 pf_x1[ITEMS], pf_x2[ITEMS];
-    float2 cs_cur[8], cs_step[8];
-    {
-      const float4* c4 = (const float4*)(a.table + (long long)min(kblock * a.kb_keys + st_r0, a.L - 1) * HALF + st_i0);
-      const float4* s4 = (const float4*)(a.table + (long long)min(RP, a.L - 1) * HALF + st_i0);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float4 cv = c4[e], sv4 = s4[e];
-        cs_cur[2 * e] = make_float2(cv.x, cv.y); cs_cur[2 * e + 1] = make_float2(cv.z, cv.w);
-        cs_step[2 * e] = make_float2(sv4.x, sv4.y); cs_step[2 * e + 1] = make_float2(sv4.z, sv4.w);
-      }
-    }
-    // pre-pass duties run in the first round only (every round stages the same keys)
-    const bool pre = PRE && round == 0 && a.v_img != nullptr;
-    // V: a thread takes 8 consecutive keys x 4 values (eight 8-byte loads), transposes them in
-    // registers and stores four 16-byte granules of the V^T image, (8 keys, d) each
-    constexpr int V_ALL = (TILE / 8) * (D / 4);                        // such items per tile
-    constexpr int V_ITEMS = (V_ALL + PC_SC_THREADS - 1) / PC_SC_THREADS;
-    u32x2 pf_v[PRE ? V_ITEMS : 1][8];
-    const long long img_cg = ((long long)c * a.n_kv_heads + g) * (a.Lp / 64);   // first tile image of (c, g)
-    auto fetch = [&](int key0) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < ITEMS; ++u) {
-        const int row = min(key0 + st_r0 + u * RP, a.L - 1);
-        const uint16_t* krow = a.k + (((long long)c * a.L + row) * a.n_kv_heads + g) * D;
-        pf_x1[u] = pc_load_once((const uint4*)(krow + st_i0));
-        pf_x2[u] = pc_load_once((const uint4*)(krow + HALF + st_i0));
-      }
-      if (pre) {
-#pragma unroll
-        for (int u = 0; u < V_ITEMS; ++u) {
-          const int it = tid + u * PC_SC_THREADS;
-          const int row0 = key0 + 8 * (it / (D / 4)), d4 = (it % (D / 4)) * 4;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            pf_v[u][j] = u32x2{0u, 0u};                                // rows past the sequence: zeros in the image
-            if (it < V_ALL && row0 + j < a.L)
-              pf_v[u][j] = __builtin_nontemporal_load(
-                  (const u32x2*)(a.v + (((long long)c * a.L + row0 + j) * a.n_kv_heads + g) * D + d4));
-          }
-        }
-      }
-    };
-    auto stage = [&](int key0) __attribute__((always_inline)) {
-      if (pre) {
-        // V^T tile images: granule (c8, d) = V[keys 8 c8 .. 8 c8 + 7][d]; word e of a granule pairs
-        // the values of keys 2 e and 2 e + 1 (one byte permute per word)
-#pragma unroll
-        for (int u = 0; u < V_ITEMS; ++u) {
-          const int it = tid + u * PC_SC_THREADS;
-          const int row0 = key0 + 8 * (it / (D / 4)), d4 = (it % (D / 4)) * 4;
-          if (it < V_ALL && row0 < a.Lp) {
-            uint16_t* img = a.v_img + (img_cg + row0 / 64) * (64LL * D) + (((row0 % 64) / 8) * D + d4) * 8;
-            uint4 gr[4];
-            uint32_t* gw = (uint32_t*)gr;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const u32x2 r0 = pf_v[u][2 * e], r1 = pf_v[u][2 * e + 1];
-              gw[0 * 4 + e] = __builtin_amdgcn_perm(r1.x, r0.x, 0x05040100u);   // d4 + 0: low halves
-              gw[1 * 4 + e] = __builtin_amdgcn_perm(r1.x, r0.x, 0x07060302u);   // d4 + 1: high halves
-              gw[2 * 4 + e] = __builtin_amdgcn_perm(r1.y, r0.y, 0x05040100u);   // d4 + 2
-              gw[3 * 4 + e] = __builtin_amdgcn_perm(r1.y, r0.y, 0x07060302u);   // d4 + 3
-            }
-            // ordinary stores: an instruction writes 16 bytes of every 64 a lane owns, and the
-            // last-level cache merges the four pieces of a line (with the streaming hint they
-            // reached memory as partial lines: 2.4 times slower)
-#pragma unroll
-            for (int dd = 0; dd < 4; ++dd) *(uint4*)(img + dd * 8) = gr[dd];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < ITEMS; ++u) {
-        const int r = st_r0 + u * RP, i0 = st_i0;
-        const uint32_t aw[4] = {pf_x1[u].x, pf_x1[u].y, pf_x1[u].z, pf_x1[u].w};
-        const uint32_t bw[4] = {pf_x2[u].x, pf_x2[u].y, pf_x2[u].z, pf_x2[u].w};
-        uint32_t h1[4], l1[4], h2[4], l2[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float2 c0 = cs_cur[2 * e], c1 = cs_cur[2 * e + 1];
-          const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
-          const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
-          split_bf16x2(x1l * c0.x - x2l * c0.y, x1h * c1.x - x2h * c1.y, h1[e], l1[e]);
-          split_bf16x2(x2l * c0.x + x1l * c0.y, x2h * c1.x + x1h * c1.y, h2[e], l2[e]);
-        }
-        *(uint4*)(k_hi + r * KSTRIDE + i0) = make_uint4(h1[0], h1[1], h1[2], h1[3]);
-        *(uint4*)(k_lo + r * KSTRIDE + i0) = make_uint4(l1[0], l1[1], l1[2], l1[3]);
-        *(uint4*)(k_hi + r * KSTRIDE + HALF + i0) = make_uint4(h2[0], h2[1], h2[2], h2[3]);
-        *(uint4*)(k_lo + r * KSTRIDE + HALF + i0) = make_uint4(l2[0], l2[1], l2[2], l2[3]);
-        if (pre) {
-          // the hi halves are the rotated key rounded to bf16: the cache row and its K image granules
-          const int row = key0 + r;
-          const bool in_seq = row < a.L;
-          const uint4 oa = in_seq ? make_uint4(h1[0], h1[1], h1[2], h1[3]) : make_uint4(0, 0, 0, 0);
-          const uint4 ob = in_seq ? make_uint4(h2[0], h2[1], h2[2], h2[3]) : make_uint4(0, 0, 0, 0);
-          if (in_seq && a.k_rope != nullptr) {
-            uint16_t* dst = a.k_rope + (((long long)c * a.L + row) * a.n_kv_heads + g) * D;
-            pc_store_once((uint4*)(dst + i0), oa);
-            pc_store_once((uint4*)(dst + HALF + i0), ob);
-          }
-          if (row < a.Lp) {
-            uint16_t* img = a.k_img + (img_cg + row / 64) * (64LL * D);
-            pc_store_once((uint4*)(img + ((i0 / 8) * 64 + row % 64) * 8), oa);
-            pc_store_once((uint4*)(img + (((HALF + i0) / 8) * 64 + row % 64) * 8), ob);
-          }
-        }
-        // (cos, sin) of the thread's next row: angle + RP theta
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float cn = cs_cur[e].x * cs_step[e].x - cs_cur[e].y * cs_step[e].y;
-          const float sn = cs_cur[e].y * cs_step[e].x + cs_cur[e].x * cs_step[e].y;
-          cs_cur[e] = make_float2(cn, sn);
-        }
-      }
-    };
-    if (kblock * a.kb_keys < a.L) fetch(kblock * a.kb_keys);
+  // keys that count: pass 1 the sequence's, pass 2 its context rows; the pre-pass wants all rows
+  const bool pre = PASS == 1 && a.v_img != nullptr;
+  const int key_end = PASS == 1 ? ctx_len + (a.L - a.w) : ctx_len;
+  const int stage_end = pre ? a.L : key_end;
+  PcKeyStage<D, TILE, PASS == 1> keys;
+  keys.begin(a, tid, kblock * a.kb_keys, pre);
+  if (kblock * a.kb_keys < stage_end) keys.fetch(a, c, g, kblock * a.kb_keys);
 
-    // one loop body (not unrolled): leaves room for the prefetch registers
-    const int n_tiles = a.kb_keys / TILE;
+  // one loop body (not unrolled): leaves room for the prefetch registers
+  const int n_tiles = a.kb_keys / TILE;
 #pragma unroll 1
-    for (int t = 0; t < n_tiles; ++t) {
-      const int key0 = kblock * a.kb_keys + t * TILE;
-      if (key0 >= a.L) break;                               // uniform over the workgroup
-      __syncthreads();                                      // previous tile fully consumed
-      stage(key0);
-      __syncthreads();
-      if (t + 1 < n_tiles && key0 + TILE < a.L) fetch(key0 + TILE);
-      if (!active) continue;
-      // every key of the tile is visible to every voting row: no causal mask (all but the last
-      // tiles of a sequence; the voting rows sit at its end)
-      const bool unmasked = key0 + TILE - 1 <= first_obs;
+  for (int t = 0; t < n_tiles; ++t) {
+    const int key0 = kblock * a.kb_keys + t * TILE;
+    if (key0 >= stage_end) break;                         // uniform over the workgroup
+    __syncthreads();                                      // previous tile fully consumed
+    keys.stage(a, c, g, key0, k_hi, k_lo);
+    __syncthreads();
+    if (t + 1 < n_tiles && key0 + TILE < stage_end) keys.fetch(a, c, g, key0 + TILE);
+    if (!active || key0 >= key_end) continue;
+    // every key of the tile is visible to every voting row: no causal mask (all but the last
+    // tiles of a sequence; the voting rows sit at its end)
+    const bool unmasked = key0 + TILE - 1 <= first_obs;
 
 #pragma unroll
-      for (int kq = 0; kq < NSUB / WPC; ++kq) {
-        const int kb = kb0 + kq * WPC;
-        floatx16 s;
+    for (int kq = 0; kq < NSUB / WPC; ++kq) {
+      const int kb = kb0 + kq * WPC;
+      floatx16 s;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = 0.f;
-        const uint16_t* ph = k_hi + (32 * kb + n) * KSTRIDE + 8 * hf;
-        const uint16_t* pl = k_lo + (32 * kb + n) * KSTRIDE + 8 * hf;
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      const uint16_t* ph = k_hi + (32 * kb + n) * KSTRIDE + 8 * hf;
+      const uint16_t* pl = k_lo + (32 * kb + n) * KSTRIDE + 8 * hf;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8 kh = *(const bf16x8*)(ph + 16 * ks);
-          const bf16x8 kl = *(const bf16x8*)(pl + 16 * ks);
-          if (PASS == 1) {     // rows = keys, columns = voting rows
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qhi[ks], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qlo[ks], s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qhi[ks], s, 0, 0, 0);
-          } else {             // rows = voting rows, columns = keys
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qhi[ks], kl, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qlo[ks], kh, s, 0, 0, 0);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qhi[ks], kh, s, 0, 0, 0);
-          }
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 kh = *(const bf16x8*)(ph + 16 * ks);
+        const bf16x8 kl = *(const bf16x8*)(pl + 16 * ks);
+        if (PASS == 1) {     // rows = keys, columns = voting rows
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qhi[ks], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qlo[ks], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qhi[ks], s, 0, 0, 0);
+        } else {             // rows = voting rows, columns = keys
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qhi[ks], kl, s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qlo[ks], kh, s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qhi[ks], kh, s, 0, 0, 0);
         }
-        if (PASS == 1) {
-          float sv[16], tmax = -INFINITY;
-          if (unmasked) {
+      }
+      if (PASS == 1) {
+        float sv[16], tmax = -INFINITY;
+        if (unmasked) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) { sv[r] = s[r]; tmax = fmaxf(tmax, sv[r]); }
-          } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int key = key0 + 32 * kb + 8 * (r / 4) + 4 * hf + (r % 4);
-              sv[r] = (key <= my_qrow) ? s[r] : -INFINITY;
-              tmax = fmaxf(tmax, sv[r]);
-            }
-          }
-          const float m_new = fmaxf(m_run, tmax);
-          if (m_new > -INFINITY) {
-            float sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(sv[r] - m_new);
-            l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + sum;
-            m_run = m_new;
-          }
+          for (int r = 0; r < 16; ++r) { sv[r] = s[r]; tmax = fmaxf(tmax, sv[r]); }
         } else {
-          const int key = key0 + 32 * kb + n;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int key = key0 + 32 * kb + 8 * (r / 4) + 4 * hf + (r % 4);
+            sv[r] = (key <= my_qrow) ? s[r] : -INFINITY;
+            tmax = fmaxf(tmax, sv[r]);
+          }
+        }
+        const float m_new = fmaxf(m_run, tmax);
+        if (m_new > -INFINITY) {
           float sum = 0.f;
-          if (unmasked) {       // padding columns carry lse = +inf: their p is 0 without a mask
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-          } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-              sum += (key <= qrow_r[r]) ? p : 0.f;
-            }
-          }
-          sum += __shfl_xor(sum, 32);
-          if (hf == 0) tok_part[wave][t * TILE + 32 * kb + n] += sum;
+          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(sv[r] - m_new);
+          l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + sum;
+          m_run = m_new;
         }
+      } else {
+        const int key = key0 + 32 * kb + n;
+        float sum = 0.f;
+        if (unmasked) {       // padding columns carry lse = +inf: their p is 0 without a mask
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
+            sum += (key <= qrow_r[r]) ? p : 0.f;
+          }
+        }
+        sum += __shfl_xor(sum, 32);
+        if (hf == 0) tok_part[wave][t * TILE + 32 * kb + n] += sum;
       }
     }
+  }
 
-    if (PASS == 1) {
-      // the lane halves hold disjoint keys of the same column; then the WPC wavefronts of the
-      // column block (disjoint keys again) are combined in wavefront order
-      const float m_o = __shfl_xor(m_run, 32), l_o = __shfl_xor(l_run, 32);
-      float M = fmaxf(m_run, m_o);
-      float l = 0.f;
-      if (l_run > 0.f) l += l_run * exp2f(m_run - M);
-      if (l_o > 0.f) l += l_o * exp2f(m_o - M);
-      if (WPC > 1) {
-        if (hf == 0) ml_part[wave][n] = make_float2(M, l);
-        __syncthreads();
-        if (kb0 == 0) {
-          M = -INFINITY;
+  if (PASS == 1) {
+    // the lane halves hold disjoint keys of the same column; then the WPC wavefronts of the
+    // column block (disjoint keys again) are combined in wavefront order
+    const float m_o = __shfl_xor(m_run, 32), l_o = __shfl_xor(l_run, 32);
+    float M = fmaxf(m_run, m_o);
+    float l = 0.f;
+    if (l_run > 0.f) l += l_run * exp2f(m_run - M);
+    if (l_o > 0.f) l += l_o * exp2f(m_o - M);
+    if (WPC > 1) {
+      if (hf == 0) ml_part[wave][n] = make_float2(M, l);
+      __syncthreads();
+      if (kb0 == 0) {
+        M = -INFINITY;
 #pragma unroll
-          for (int i = 0; i < WPC; ++i) M = fmaxf(M, ml_part[wave + i][n].x);
-          l = 0.f;
+        for (int i = 0; i < WPC; ++i) M = fmaxf(M, ml_part[wave + i][n].x);
+        l = 0.f;
 #pragma unroll
-          for (int i = 0; i < WPC; ++i) {
-            const float2 v = ml_part[wave + i][n];
-            if (v.y > 0.f) l += v.y * exp2f(v.x - M);
-          }
+        for (int i = 0; i < WPC; ++i) {
+          const float2 v = ml_part[wave + i][n];
+          if (v.y > 0.f) l += v.y * exp2f(v.x - M);
         }
-        __syncthreads();                               // ml_part free for the next round
       }
-      const int cc = 32 * cb + n;
-      if (active && kb0 == 0 && hf == 0 && cc < a.n_cols)
-        a.ml[ml_base + (long long)kblock * a.n_cols + cc] = make_float2(M, l);
     }
+    const int cc = 32 * cb + n;
+    if (active && kb0 == 0 && hf == 0 && cc < a.n_cols)
+      a.ml[ml_base + (long long)kblock * a.n_cols + cc] = make_float2(M, l);
   }
 
   if (PASS == 2) {
@@ -414,38 +432,218 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
       float tot = 0.f;
 #pragma unroll
       for (int wv = 0; wv < PC_SC_WAVES; ++wv) tot += tok_part[0][wv];
-      a.blk_sum[((long long)c * a.n_kv_heads + g) * a.n_kb + kblock] = tot;
+      a.blk_sum[((long long)c * a.n_kv_heads + g) * gridDim.z + kblock] = tot;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// More than 4 column blocks (many voting rows, e.g. every query row as Eq. 6 prints it).  Keeping
+// columns in registers and streaming the keys would rotate, split and stage every key once per
+// 128 columns.  Here a workgroup stages its 128 keys (hi and lo, 68 KiB) once and the columns
+// stream by: a wavefront takes every fourth column block and reads it as ready MFMA operands
+// (split once, by score_queries_kernel) while the block before is multiplied.  No barrier and no
+// conversion in the loop: bound by the matrix cores (96 MFMAs a block) and 64 exponentials a lane.
+// Measured, every query row voting, pass 1 with the pre-pass + pass 2, before (rounds of 128
+// columns over re-staged keys) and now: 12 ragged chunks of 2011 rows, 203 rows voting, 32 / 8 heads
+// 324 + 305 -> 215 + 154 us; 16 x 7680, 512 voting 2052 + 2081 -> 1487 + 1281; 36 x 3584, 32 / 32
+// heads 2805 + 2369 -> 3019 + 1834 (the pre-pass, 1.25 ms of memory traffic, no longer overlaps).
+template <int D>
+__global__ __launch_bounds__(PC_WAVE) void score_queries_kernel(PcScoreArgs a, uint16_t* __restrict__ q_split) {
+  constexpr int KS = D / 16;
+  const int c = blockIdx.x / a.n_cb, cb = blockIdx.x % a.n_cb, g = blockIdx.y, lane = threadIdx.x;
+  const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
+  bf16x8 q[2][KS];
+  load_query_column<D>(a, c, g, a.n_q_heads / a.n_kv_heads, ctx_len + (a.L - a.w) - a.w_obs,
+                       min(32 * cb + lane % 32, a.n_cols - 1), lane / 32, q[0], q[1]);
+  uint16_t* dst = q_split + ((((long long)c * a.n_kv_heads + g) * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane) * 8;
+#pragma unroll
+  for (int i = 0; i < 2 * KS; ++i) *(bf16x8*)(dst + i * PC_WAVE * 8) = q[i / KS][i % KS];
+}
+
+template <int D, int PASS, int TILE>
+__global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreArgs a) {
+  constexpr int KS = D / 16, KSTRIDE = D + 8, NSUB = TILE / 32;
+  __shared__ __attribute__((aligned(16))) uint16_t k_hi[TILE * KSTRIDE];
+  __shared__ __attribute__((aligned(16))) uint16_t k_lo[TILE * KSTRIDE];
+  __shared__ float tok_part[PC_SC_WAVES][PASS == 2 ? TILE : 1];
+
+  const int c = blockIdx.x, g = blockIdx.y, kblock = blockIdx.z, key0 = kblock * TILE;
+  const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
+  const int hf = lane / 32, n = lane % 32;
+  const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
+  const int first_obs = ctx_len + (a.L - a.w) - a.w_obs;
+  const int key_end = PASS == 1 ? ctx_len + (a.L - a.w) : ctx_len;
+  const bool pre = PASS == 1 && a.v_img != nullptr;
+  const long long cg = (long long)c * a.n_kv_heads + g;
+  const bool unmasked = key0 + TILE - 1 <= first_obs;      // every key is visible to every voting row
+  const int n_sub = min(NSUB, (key_end - key0 + 31) / 32); // (<= 0: nobody looks at these keys)
+  float tok[NSUB];
+#pragma unroll
+  for (int kq = 0; kq < NSUB; ++kq) tok[kq] = 0.f;
+
+  bf16x8 q[2][2 * KS];                                     // this column block and the next: hi, lo
+  auto load_q = [&](bf16x8(&x)[2 * KS], int cb) __attribute__((always_inline)) {
+    const uint16_t* src = a.q_split + ((cg * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane) * 8;
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) x[i] = *(const bf16x8*)(src + i * PC_WAVE * 8);
+  };
+  if (wave < a.n_cb) load_q(q[0], wave);                   // in flight while the keys are staged
+  if (key0 < (pre ? a.L : key_end)) {
+    PcKeyStage<D, TILE, PASS == 1> keys;
+    keys.begin(a, tid, key0, pre);
+    keys.fetch(a, c, g, key0);
+    keys.stage(a, c, g, key0, k_hi, k_lo);
+  }
+  __syncthreads();
+
+  auto block = [&](const bf16x8(&x)[2 * KS], int cb) __attribute__((always_inline)) {
+    float m_run = -INFINITY, l_run = 0.f;
+    const int col = min(32 * cb + n, a.n_cols - 1), my_qrow = first_obs + col % a.w_obs;
+    float lse_r[16];
+    if (PASS == 2) {
+      const float* lse2 = a.lse2 + cg * (32 * a.n_cb) + 32 * cb + 4 * hf;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = *(const float4*)(lse2 + 8 * i);
+        lse_r[4 * i] = v.x; lse_r[4 * i + 1] = v.y; lse_r[4 * i + 2] = v.z; lse_r[4 * i + 3] = v.w;
+      }
+    }
+#pragma unroll
+    for (int kq = 0; kq < NSUB; ++kq) {
+      if (kq >= n_sub) break;
+      floatx16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+      const uint16_t* ph = k_hi + (32 * kq + n) * KSTRIDE + 8 * hf;
+      const uint16_t* pl = k_lo + (32 * kq + n) * KSTRIDE + 8 * hf;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 kh = *(const bf16x8*)(ph + 16 * ks);
+        const bf16x8 kl = *(const bf16x8*)(pl + 16 * ks);
+        if (PASS == 1) {
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, x[ks], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, x[KS + ks], s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, x[ks], s, 0, 0, 0);
+        } else {
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks], kl, s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[KS + ks], kh, s, 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks], kh, s, 0, 0, 0);
+        }
+      }
+      if (PASS == 1) {
+        if (!unmasked) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (key0 + 32 * kq + 8 * (r / 4) + 4 * hf + (r % 4) > my_qrow) s[r] = -INFINITY;
+        }
+        float m_new = m_run;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) m_new = fmaxf(m_new, s[r]);
+        if (m_new > -INFINITY) {
+          float sum = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - m_new);
+          l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + sum;
+          m_run = m_new;
+        }
+      } else {
+        float sum = 0.f;
+        if (unmasked) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
+            const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
+            sum += (key0 + 32 * kq + n <= first_obs + cc % a.w_obs) ? p : 0.f;
+          }
+        }
+        tok[kq] += sum;
+      }
+    }
+    if (PASS == 1) {
+      // the lane halves hold disjoint keys of the same column
+      const float m_o = __shfl_xor(m_run, 32), l_o = __shfl_xor(l_run, 32);
+      const float M = fmaxf(m_run, m_o);
+      float l = 0.f;
+      if (l_run > 0.f) l += l_run * exp2f(m_run - M);
+      if (l_o > 0.f) l += l_o * exp2f(m_o - M);
+      if (hf == 0 && 32 * cb + n < a.n_cols)
+        a.ml[(cg * a.n_kb + kblock) * a.n_cols + 32 * cb + n] = make_float2(M, l);
+    }
+  };
+  if (PASS == 1 || n_sub > 0) {
+#pragma unroll 1
+    for (int cb = wave; cb < a.n_cb; cb += 2 * PC_SC_WAVES) {
+      if (cb + PC_SC_WAVES < a.n_cb) load_q(q[1], cb + PC_SC_WAVES);
+      block(q[0], cb);
+      if (cb + PC_SC_WAVES >= a.n_cb) break;
+      if (cb + 2 * PC_SC_WAVES < a.n_cb) load_q(q[0], cb + 2 * PC_SC_WAVES);
+      block(q[1], cb + PC_SC_WAVES);
+    }
+  }
+
+  if (PASS == 2) {
+#pragma unroll
+    for (int kq = 0; kq < NSUB; ++kq) {
+      const float x = tok[kq] + __shfl_xor(tok[kq], 32);
+      if (hf == 0) tok_part[wave][32 * kq + n] = x;
+    }
+    __syncthreads();
+    float blk = 0.f;
+    if (tid < TILE && key0 + tid < a.w) {
+      float x = 0.f;
+#pragma unroll
+      for (int wv = 0; wv < PC_SC_WAVES; ++wv) x += tok_part[wv][tid];
+      x = key0 + tid < ctx_len ? x : 0.f;
+      a.tok_score[cg * a.w + key0 + tid] = x;
+      blk = x;
+    }
+    // block sum in a fixed order: lanes (xor tree), then the wavefronts in order
+#pragma unroll
+    for (int off = PC_WAVE / 2; off > 0; off >>= 1) blk += __shfl_xor(blk, off);
+    __syncthreads();
+    if (lane == 0) tok_part[0][wave] = blk;
+    __syncthreads();
+    if (tid == 0) {
+      float tot = 0.f;
+#pragma unroll
+      for (int wv = 0; wv < PC_SC_WAVES; ++wv) tot += tok_part[0][wv];
+      a.blk_sum[cg * gridDim.z + kblock] = tot;
     }
   }
 }
 
 // Row logsumexp (log2 units) of every voting row from the per-key-block (max, sum) of pass 1,
-// combined in block order.  One thread per column; the loads of a batch of blocks are
-// independent, so a thread waits for memory n_kb / 8 times, not n_kb times.
+// combined in block order.  One thread per column, the blocks read once, in batches of 8
+// independent loads.
 __global__ __launch_bounds__(128) void scores_lse_kernel(const float2* __restrict__ ml,
                                                          float* __restrict__ lse2, int n_kb,
-                                                         int n_cols) {
+                                                         int n_cols, int n_pad) {
   const int col = blockIdx.y * 128 + threadIdx.x;
-  if (col >= n_cols) return;
-  const float2* src = ml + (long long)blockIdx.x * n_kb * n_cols + col;
-  float M = -INFINITY;
-  for (int kb0 = 0; kb0 < n_kb; kb0 += 8) {
-    float2 v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = src[(long long)min(kb0 + i, n_kb - 1) * n_cols];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) M = fmaxf(M, v[i].x);
+  if (col >= n_pad) return;
+  if (col >= n_cols) {                                       // padding of the last column block: p = 0
+    lse2[(long long)blockIdx.x * n_pad + col] = INFINITY;
+    return;
   }
-  float sum = 0.f;
+  const float2* src = ml + (long long)blockIdx.x * n_kb * n_cols + col;
+  float M = -INFINITY, sum = 0.f;
   for (int kb0 = 0; kb0 < n_kb; kb0 += 8) {
     float2 v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = src[(long long)min(kb0 + i, n_kb - 1) * n_cols];
+    float m_new = M;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m_new = fmaxf(m_new, v[i].x);
+    if (sum > 0.f) sum *= exp2f(M - m_new);
+    M = m_new;
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (kb0 + i < n_kb && v[i].y > 0.f) sum += v[i].y * exp2f(v[i].x - M);
   }
-  lse2[(long long)blockIdx.x * n_cols + col] = M + log2f(sum);
+  lse2[(long long)blockIdx.x * n_pad + col] = M + log2f(sum);
 }
 
 // chunk_score[c] = sum of tok_score[c, :, :] = sum of the chunk's pass-2 block sums, added in a
@@ -466,80 +664,104 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
   if (threadIdx.x == 0) chunk_score[blockIdx.x] = red[0];
 }
 
-template <int PASS>
-static void launch_scores_pass(int head_dim, int wpc, dim3 grid, dim3 block, hipStream_t st,
-                               const PcScoreArgs& a) {
-  if (head_dim == 128) {
-    if (wpc == 4) hipLaunchKernelGGL((scores_kernel<128, PASS, 4>), grid, block, 0, st, a);
-    else if (wpc == 2) hipLaunchKernelGGL((scores_kernel<128, PASS, 2>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((scores_kernel<128, PASS, 1>), grid, block, 0, st, a);
-  } else {
-    if (wpc == 4) hipLaunchKernelGGL((scores_kernel<64, PASS, 4>), grid, block, 0, st, a);
-    else if (wpc == 2) hipLaunchKernelGGL((scores_kernel<64, PASS, 2>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((scores_kernel<64, PASS, 1>), grid, block, 0, st, a);
-  }
+template <int D, int PASS>
+static void launch_scores_pass(int wpc, dim3 grid, dim3 block, hipStream_t st, const PcScoreArgs& a) {
+  if (wpc == 0 && a.kb_keys == PC_SC_KB_MANY)
+    hipLaunchKernelGGL((scores_many_kernel<D, PASS, PC_SC_KB_MANY>), grid, block, 0, st, a);
+  else if (wpc == 0) hipLaunchKernelGGL((scores_many_kernel<D, PASS, PC_SC_KB_MANY / 2>), grid, block, 0, st, a);
+  else if (wpc == 4) hipLaunchKernelGGL((scores_kernel<D, PASS, 4>), grid, block, 0, st, a);
+  else if (wpc == 2) hipLaunchKernelGGL((scores_kernel<D, PASS, 2>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((scores_kernel<D, PASS, 1>), grid, block, 0, st, a);
 }
 
-size_t pc_scores_ml_bytes(const pc_shape* s) {
-  const size_t L = (size_t)s->chunk_len + s->query_len;
-  const size_t n_kb = (L + PC_SC_KB - 1) / PC_SC_KB;
-  const size_t n_cols = (size_t)(s->n_q_heads / s->n_kv_heads) * s->obs_window;
-  const size_t cg = (size_t)s->n_chunks * s->n_kv_heads;
-  // per-block (max, sum) of pass 1, the combined row logsumexp, the block sums of pass 2
-  return cg * n_kb * n_cols * sizeof(float2) + cg * n_cols * sizeof(float) + cg * n_kb * sizeof(float);
+// Keys per workgroup of scores_many_kernel: 128, or 64 where that is less than one workgroup per CU
+static int many_kb_keys(const pc_shape* s) {
+  const long long L = (long long)s->chunk_len + s->query_len;
+  const long long wgs = (long long)s->n_chunks * s->n_kv_heads * ((L + PC_SC_KB_MANY - 1) / PC_SC_KB_MANY);
+  return wgs < 256 ? PC_SC_KB_MANY / 2 : PC_SC_KB_MANY;
 }
+
+// Workspace of the score passes: per-block (max, sum) of pass 1, the combined row logsumexp, the
+// block sums of pass 2 and, with more than 4 column blocks, the split query columns.
+struct PcScoreWs { size_t ml, lse2, blk_sum, q_split, total; };
+static PcScoreWs scores_ws_layout(const pc_shape* s) {
+  const size_t L = (size_t)s->chunk_len + s->query_len;
+  const size_t n_cols = (size_t)(s->n_q_heads / s->n_kv_heads) * s->obs_window;
+  const size_t n_cb = (n_cols + 31) / 32, cg = (size_t)s->n_chunks * s->n_kv_heads;
+  const size_t kb = n_cb > PC_SC_WAVES ? many_kb_keys(s) : PC_SC_KB, n_kb = (L + kb - 1) / kb;
+  PcScoreWs w;
+  size_t off = 0;
+  w.ml = off;      off = pc_align_up(off + cg * n_kb * n_cols * sizeof(float2), 256);
+  w.lse2 = off;    off = pc_align_up(off + cg * n_cb * 32 * sizeof(float), 256);
+  w.blk_sum = off; off = pc_align_up(off + cg * n_kb * sizeof(float), 256);
+  w.q_split = off; off += n_cb > PC_SC_WAVES ? cg * n_cb * 32 * (size_t)s->head_dim * 2 * 2 : 0;
+  w.total = off;
+  return w;
+}
+
+size_t pc_scores_ws_bytes(const pc_shape* s) { return scores_ws_layout(s).total; }
 
 int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int32_t* chunk_lens, const float2* table,
-                     void* ml_ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
+                     void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
                      hipStream_t st) {
+  const PcScoreWs w = scores_ws_layout(s);
   PcScoreArgs a = {};
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.table = table; a.chunk_lens = chunk_lens;
-  a.ml = (float2*)ml_ws; a.tok_score = tok_score;
+  a.ml = (float2*)((char*)ws + w.ml); a.lse2 = (float*)((char*)ws + w.lse2);
+  a.blk_sum = (float*)((char*)ws + w.blk_sum);
+  a.tok_score = tok_score;
   a.L = s->chunk_len + s->query_len; a.w = s->chunk_len; a.w_obs = s->obs_window;
   a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads;
   a.n_cols = (s->n_q_heads / s->n_kv_heads) * s->obs_window;
-  const int n_cb = (a.n_cols + 31) / 32;
-  const int wpc = n_cb == 1 ? 4 : (n_cb == 2 ? 2 : 1);
+  a.n_cb = (a.n_cols + 31) / 32;
+  const bool many = a.n_cb > PC_SC_WAVES;
+  const int wpc = many ? 0 : (a.n_cb == 1 ? 4 : (a.n_cb == 2 ? 2 : 1));
   // keys per workgroup: double while at least 512 workgroups (one full round of two per CU)
   // remain: fewer, longer workgroups spread their start-up over more keys (measured: 4 and 8
   // chunks of 8192 rows 10 % faster than with twice as many workgroups of half the keys)
-  a.kb_keys = PC_SC_KB;
+  a.kb_keys = many ? many_kb_keys(s) : PC_SC_KB;
   const int kb_cap = wpc == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;
-  while (a.kb_keys < kb_cap &&
+  while (!many && a.kb_keys < kb_cap &&
          (long long)s->n_chunks * s->n_kv_heads * ((a.L + 2 * a.kb_keys - 1) / (2 * a.kb_keys)) >= 512)
     a.kb_keys *= 2;
   a.n_kb = (a.L + a.kb_keys - 1) / a.kb_keys;
+  const int n_kb2 = (a.w + a.kb_keys - 1) / a.kb_keys;       // pass 2 looks at context keys only
   const float scale = s->softmax_scale > 0.f ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   a.scale_log2 = scale * PC_SC_LOG2E;
-  const size_t cg = (size_t)s->n_chunks * s->n_kv_heads;
-  a.lse2 = (float*)(a.ml + cg * a.n_kb * a.n_cols);
-  a.blk_sum = a.lse2 + cg * a.n_cols;
-  if ((long long)a.n_kb > 65535 || (long long)s->n_kv_heads > 65535) return PC_ERR_SHAPE;   // grid limits
-  dim3 grid(s->n_chunks, s->n_kv_heads, a.n_kb), block(PC_SC_THREADS);
+  if (a.n_kb > 65535 || s->n_kv_heads > 65535) return PC_ERR_SHAPE;   // grid limits
+  const dim3 grid(s->n_chunks, s->n_kv_heads, a.n_kb), grid2(s->n_chunks, s->n_kv_heads, n_kb2), block(PC_SC_THREADS);
   if (pre) {
     a.v = (const uint16_t*)pre->v; a.k_rope = (uint16_t*)pre->k_rope; a.k_img = (uint16_t*)pre->k_img;
     a.v_img = (uint16_t*)pre->v_img; a.Lp = pre->Lp;
-    PcProfScope prof(PC_KERNEL_PREPASS_SCORES, st);
-    launch_scores_pass<1>(s->head_dim, wpc, grid, block, st, a);
-  } else {
-    PcProfScope prof(PC_KERNEL_SCORES_P1, st);
-    launch_scores_pass<1>(s->head_dim, wpc, grid, block, st, a);
+  }
+  {
+    PcProfScope prof(pre ? PC_KERNEL_PREPASS_SCORES : PC_KERNEL_SCORES_P1, st);
+    if (many) {
+      uint16_t* q_split = (uint16_t*)((char*)ws + w.q_split);
+      const dim3 q_grid(s->n_chunks * a.n_cb, s->n_kv_heads);
+      if (s->head_dim == 128) hipLaunchKernelGGL(score_queries_kernel<128>, q_grid, dim3(PC_WAVE), 0, st, a, q_split);
+      else hipLaunchKernelGGL(score_queries_kernel<64>, q_grid, dim3(PC_WAVE), 0, st, a, q_split);
+      a.q_split = q_split;
+    }
+    if (s->head_dim == 128) launch_scores_pass<128, 1>(wpc, grid, block, st, a);
+    else launch_scores_pass<64, 1>(wpc, grid, block, st, a);
   }
   PC_LAUNCH_CHECK();
   {
     PcProfScope prof(PC_KERNEL_SCORES_LSE, st);
-    hipLaunchKernelGGL(scores_lse_kernel, dim3(s->n_chunks * s->n_kv_heads, (a.n_cols + 127) / 128),
-                       dim3(128), 0, st, a.ml, a.lse2, a.n_kb, a.n_cols);
+    hipLaunchKernelGGL(scores_lse_kernel, dim3(s->n_chunks * s->n_kv_heads, (32 * a.n_cb + 127) / 128),
+                       dim3(128), 0, st, a.ml, a.lse2, a.n_kb, a.n_cols, 32 * a.n_cb);
   }
   {
     PcProfScope prof(PC_KERNEL_SCORES_P2, st);
-    launch_scores_pass<2>(s->head_dim, wpc, grid, block, st, a);
+    if (s->head_dim == 128) launch_scores_pass<128, 2>(wpc, grid2, block, st, a);
+    else launch_scores_pass<64, 2>(wpc, grid2, block, st, a);
   }
   PC_LAUNCH_CHECK();
   if (chunk_score) {
     PcProfScope prof(PC_KERNEL_CHUNK_SCORE, st);
     hipLaunchKernelGGL(chunk_score_kernel, dim3(s->n_chunks), dim3(256), 0, st, a.blk_sum,
-                       chunk_score, s->n_kv_heads * a.n_kb);
+                       chunk_score, s->n_kv_heads * n_kb2);
     PC_LAUNCH_CHECK();
   }
   return PC_OK;
