@@ -33,8 +33,7 @@
 // 16 + 4 g + (j - 4) (j >= 4).  A piece is one fully coalesced 16-byte-per-lane load and gives
 // two A operands.  A segment holds ceil(k_t / 32) blocks of K and of V; keys behind k_t or behind
 // the segment's length carry code 0.
-#include "pc_common.h"
-#include <math.h>
+#include "decode_core.h"
 
 #define PC_D8_WAVES 4
 #define PC_D8_ITER_KEYS 32
@@ -167,7 +166,7 @@ int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg
 
 // ------------------------------------------------------------------------------------------
 struct PcDecode8Args {
-  const uint16_t* q;      // rotated queries [B, n_q, H_q, D] bf16
+  PcDecodeQuery query;
   const uint8_t* k8;      // [B, S, H_kv, ceil(k_t / 32) * 32 * D] E4M3 codes in 32-key blocks
   const uint8_t* v8;      // the same size, transposed blocks
   const float* k_scale;   // [B, S, H_kv]
@@ -259,8 +258,11 @@ int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, 
   return PC_OK;
 }
 
+// One launch: the workgroups of the 8-bit segments first (one per CU where the shapes allow), those of
+// the 16-bit tail behind them, next to which they find room: the tail, a few per cent of the bytes,
+// costs no launch, ramp and drain of its own.
 template <int D, int NQ>
-__global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(PcDecode8Args a) {
+__device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid) {
   constexpr int KSTEPS = D / 32;            // MFMA k-steps; a lane owns 8 KSTEPS = D / 4 bytes of each of its K rows
   constexpr int KQ = D / 64;                // 16-byte loads per lane and 16-key block
   constexpr int VLOADS = D / 32;            // 1 KiB pieces of a V block: one 16-byte load per lane each
@@ -270,13 +272,13 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
 
   __shared__ float red_o[PC_D8_WAVES][NQ][D];
   __shared__ float red_m[PC_D8_WAVES][NQ], red_l[PC_D8_WAVES][NQ];
+  __shared__ __attribute__((aligned(16))) uint16_t q_lds[NQ][D];
 
   const int G = a.n_q_heads / a.n_kv_heads;
   const int n_cols = a.n_q * G;             // valid query columns (<= NQ)
   const int lane = threadIdx.x % PC_WAVE, wave = threadIdx.x / PC_WAVE;
   const int kk = lane / 16, c16 = lane % 16;
 
-  int bid = blockIdx.x;
   const int part = bid % a.parts_grid; bid /= a.parts_grid;
   const int g = bid % a.n_kv_heads;    bid /= a.n_kv_heads;
   const int b = bid;
@@ -295,8 +297,11 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
     if (at.valid) {
       const long long seg_id = ((long long)b * a.n_seg + at.s) * a.n_kv_heads + g;
       c.k = a.k8 + seg_id * seg_bytes; c.v = a.v8 + seg_id * seg_bytes;
-      c.k_sc = a.k_scale[seg_id] * a.scale_log2;           // logits in log2 units
-      c.v_sc = a.v_scale[seg_id];
+      // read-only here, and asked for through the scalar cache: a vector load would have to be waited
+      // for behind the keys in flight
+      typedef const __attribute__((address_space(4))) float* scalar_t;
+      c.k_sc = ((scalar_t)(uintptr_t)a.k_scale)[seg_id] * a.scale_log2;    // logits in log2 units
+      c.v_sc = ((scalar_t)(uintptr_t)a.v_scale)[seg_id];
     }
     return c;
   };
@@ -307,12 +312,22 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
   bf16x8 bq[KSTEPS];
   {
     const bool valid = c16 < n_cols;
-    const int t = valid ? c16 / G : 0, hg = valid ? c16 % G : 0;
-    const uint16_t* qrow = a.q + (((long long)b * a.n_q + t) * a.n_q_heads + g * G + hg) * D;
+    const int n = valid ? c16 : 0;
+    if (a.query.pos0 >= 0) {
+      pc_rotate_columns<D>(a.query, b, g, G, n_cols, q_lds);
+      __syncthreads();
 #pragma unroll
-    for (int j = 0; j < KSTEPS; ++j) {
-      uint4 raw = valid ? *(const uint4*)(qrow + 64 * (j / 2) + 16 * kk + 8 * (j % 2)) : make_uint4(0, 0, 0, 0);
-      bq[j] = *(bf16x8*)&raw;
+      for (int j = 0; j < KSTEPS; ++j) {
+        uint4 raw = valid ? *(const uint4*)(q_lds[n] + 64 * (j / 2) + 16 * kk + 8 * (j % 2)) : make_uint4(0, 0, 0, 0);
+        bq[j] = *(bf16x8*)&raw;
+      }
+    } else {
+      const uint16_t* qrow = a.query.q + (((long long)b * a.n_q + n / G) * a.n_q_heads + g * G + n % G) * D;
+#pragma unroll
+      for (int j = 0; j < KSTEPS; ++j) {
+        uint4 raw = valid ? *(const uint4*)(qrow + 64 * (j / 2) + 16 * kk + 8 * (j % 2)) : make_uint4(0, 0, 0, 0);
+        bq[j] = *(bf16x8*)&raw;
+      }
     }
   }
 
@@ -322,7 +337,6 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) o_acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // three register buffers: the loads of two iterations (2 x 8 KiB per wavefront) stay in flight
   uint4 kbuf[3][KBLK][KQ], vbuf[3][VLOADS];
   auto issue_loads = [&](int buf, const Cursor& c) {
     // the block's pieces: key0 is a multiple of 32, and whole blocks exist up to ceil(k_t / 32)
@@ -417,7 +431,7 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
     if (c1.valid) issue_loads(1, c1);
     auto iter = [&](int cur_buf, int fill_buf) __attribute__((always_inline)) {
       // c0 = block to consume (in cur_buf), c1 = the block after it (already in flight)
-      Cursor c2 = c1.valid ? next(c1) : c1;
+      const Cursor c2 = next(c1);                            // (behind the run's end: not valid)
       if (c2.valid) issue_loads(fill_buf, c2);
       consume(cur_buf, c0);
       c0 = c1; c1 = c2;
@@ -463,36 +477,50 @@ __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(
   }
 }
 
+template <int D, int NQ>
+__global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(PcDecode8Args a, PcDecodeArgs tail,
+                                                                                int n_wg8) {
+  static_assert(PC_D8_WAVES == PC_DEC_WAVES, "one workgroup size");
+  if ((int)blockIdx.x < n_wg8) decode8_workgroup<D, NQ>(a, blockIdx.x);
+  else pc_decode_workgroup<D, NQ>(tail, blockIdx.x - n_wg8);
+}
+
 template <int D>
-static int launch_decode8_d(const PcDecode8Args& a, int batch, int nq_pad, hipStream_t st) {
-  const long long blocks = (long long)batch * a.n_kv_heads * a.parts_grid;
+static int launch_decode8_d(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, int nq_pad, hipStream_t st) {
+  const long long groups = (long long)batch * a.n_kv_heads;
+  const long long n_wg8 = groups * a.parts_grid, blocks = n_wg8 + groups * tail.parts_grid;
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   dim3 grid((unsigned)blocks), block(PC_D8_WAVES * PC_WAVE);
   PcProfScope prof(PC_KERNEL_DECODE_FP8, st);
-  if (nq_pad == 4) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 4>), grid, block, 0, st, a);
-  else if (nq_pad == 8) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 8>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 16>), grid, block, 0, st, a);
+  if (nq_pad == 4) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 4>), grid, block, 0, st, a, tail, (int)n_wg8);
+  else if (nq_pad == 8) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 8>), grid, block, 0, st, a, tail, (int)n_wg8);
+  else hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 16>), grid, block, 0, st, a, tail, (int)n_wg8);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
 
-int pc_launch_decode_fp8(const void* q_rot, const void* k8, const void* v8, const float* k_scale,
-                         const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
-                         int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
-                         int head_dim, float scale, float* part_o, float* part_lse, int n_parts,
-                         hipStream_t st) {
+int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
+                         const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                         int seg_len_per_head, const void* k_tail, const void* v_tail,
+                         const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
+                         int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
+                         float* part_lse, int n_parts, hipStream_t st) {
+  const int cols = n_q * (n_q_heads / n_kv_heads);
+  if (cols > 16) return PC_ERR_UNSUPPORTED;               // the columns of one 16x16x32 MFMA
   PcDecode8Args a;
-  a.q = (const uint16_t*)q_rot; a.k8 = (const uint8_t*)k8; a.v8 = (const uint8_t*)v8;
+  a.query = pc_decode_query(q, pos0, base, n_q, n_q_heads);
+  a.k8 = (const uint8_t*)k8; a.v8 = (const uint8_t*)v8;
   a.k_scale = k_scale; a.v_scale = v_scale;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
   a.parts_grid = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
   a.n_parts = n_parts;
   a.scale_log2 = scale * PC_D8_LOG2E;
-  const int cols = n_q * (n_q_heads / n_kv_heads);
-  if (cols > 16) return PC_ERR_UNSUPPORTED;               // the columns of one 16x16x32 MFMA
+  const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_cap > 0 ? 1 : 0,
+                                           tail_cap > 0 ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
+                                           n_parts, a.parts_grid);
   const int nq_pad = cols <= 4 ? 4 : (cols <= 8 ? 8 : 16);
-  return head_dim == 128 ? launch_decode8_d<128>(a, batch, nq_pad, st)
-                         : launch_decode8_d<64>(a, batch, nq_pad, st);
+  return head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, nq_pad, st)
+                         : launch_decode8_d<64>(a, tail, batch, nq_pad, st);
 }

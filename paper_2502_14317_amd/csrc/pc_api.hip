@@ -381,28 +381,25 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
     return parallel_attn_fp8_tiles(q, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, k_tail, v_tail,
                                    tail_len, tail_cap, k_self, v_self, batch, n_q, n_seg, k_t, n_q_heads,
                                    n_kv_heads, D, q_pos0, rope_base, scale, out, lse_out, w, base, st);
-  const void* q_rot = q;
-  if (q_pos0 >= 0) {
+  // the kernels rotate the query rows themselves, unless the merge needs them too (self segment)
+  const void* q_in = q;
+  int pos0 = q_pos0;
+  if (q_pos0 >= 0 && has_self) {
     rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
                           q_pos0, rope_base, st);
     if (rc != PC_OK) return rc;
-    q_rot = base + w.q_rot;
+    q_in = base + w.q_rot; pos0 = -1;
   }
   float* part_o = (float*)(base + w.part_o);
   float* part_lse = (float*)(base + w.part_lse);
-  if (n_seg > 0) {
-    rc = pc_launch_decode_fp8(q_rot, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, batch, n_q,
-                              n_seg, k_t, n_q_heads, n_kv_heads, D, scale, part_o, part_lse,
-                              w.n_parts, st);
-    if (rc != PC_OK) return rc;
-  }
-  if (tail_cap > 0) {     // the 16-bit tail: one more segment of the split-KV kernel
-    rc = pc_launch_decode(q_rot, k_tail, v_tail, tail_len, 0, batch, n_q, 1, tail_cap, n_q_heads,
-                          n_kv_heads, D, scale, part_o, part_lse, w.n_parts, w.parts8, st);
+  if (n_seg > 0 || tail_cap > 0) {
+    rc = pc_launch_decode_fp8(q_in, pos0, rope_base, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head,
+                              k_tail, v_tail, tail_len, tail_cap, batch, n_q, n_seg, k_t, n_q_heads,
+                              n_kv_heads, D, scale, part_o, part_lse, w.n_parts, st);
     if (rc != PC_OK) return rc;
   }
   // the few-row causal self segment (if any) is evaluated inside the merge
-  return pc_launch_merge(part_o, part_lse, q_rot, k_self, v_self, out, lse_out, batch, n_q,
+  return pc_launch_merge(part_o, part_lse, q_in, k_self, v_self, out, lse_out, batch, n_q,
                          n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
 }
 
@@ -609,20 +606,22 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
   float* part_lse = (float*)(base + w.part_lse);
 
   if (w.small) {
-    // split-KV path: the rotated rows (the scale is applied to the fp32 logits)
-    const void* q_rot = q;
-    if (q_pos0 >= 0) {
+    // split-KV path: the kernel rotates the query rows itself (the scale is applied to the fp32
+    // logits), unless the merge needs them too (self segment)
+    const void* q_in = q;
+    int pos0 = q_pos0;
+    if (q_pos0 >= 0 && has_self) {
       rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
                             q_pos0, rope_base, st);
       if (rc != PC_OK) return rc;
-      q_rot = base + w.q_rot;
+      q_in = base + w.q_rot; pos0 = -1;
     }
     if (n_seg > 0) {
-      rc = pc_launch_decode(q_rot, kc, vc, seg_len, seg_len_per_head, batch, n_q, n_seg, k_t, n_q_heads, n_kv_heads,
-                            D, scale, part_o, part_lse, w.n_parts, 0, st);
+      rc = pc_launch_decode(q_in, pos0, rope_base, kc, vc, seg_len, seg_len_per_head, batch, n_q, n_seg, k_t,
+                            n_q_heads, n_kv_heads, D, scale, part_o, part_lse, w.n_parts, 0, st);
       if (rc != PC_OK) return rc;
     }
-    return pc_launch_merge(part_o, part_lse, q_rot, k_self, v_self, out, lse_out, batch, n_q,
+    return pc_launch_merge(part_o, part_lse, q_in, k_self, v_self, out, lse_out, batch, n_q,
                            n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
   }
 

@@ -200,7 +200,10 @@ struct PcSegLens {
   __device__ __forceinline__ int len(int s) const {
     if (!seg_len) return k_t;
     const int idx = per_head ? (b * n_seg + s) * n_kv_heads + g : b * n_seg + s;
-    return min(max(seg_len[idx], 0), k_t);
+    // read-only while a kernel runs: where the index is uniform this is a scalar load, which does not
+    // queue behind the keys in flight
+    typedef const __attribute__((address_space(4))) int32_t* scalar_t;
+    return min(max(((scalar_t)(uintptr_t)seg_len)[idx], 0), k_t);
   }
 };
 struct PcBlockCursor {
@@ -273,8 +276,9 @@ int pc_launch_kv_append(const void* k_new, const void* v_new, int batch, int n_n
                         int seg, int k_t, int n_kv_heads, int head_dim, int pos0, float base,
                         void* kc, void* vc, int32_t* seg_len, int seg_len_per_head,
                         hipStream_t st);
-int pc_launch_decode(const void* q_rot, const void* kc, const void* vc, const int32_t* seg_len,
-                     int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
+// q: rotated by the kernel at positions pos0 + t (pos0 < 0: it arrives rotated)
+int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const void* vc,
+                     const int32_t* seg_len, int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                      int head_dim, float scale, float* part_o, float* part_lse, int n_parts, int part0,
                      hipStream_t st);
 // k_amax, v_amax [n_segs] (both or neither): the largest |value| of every segment's valid rows,
@@ -288,11 +292,13 @@ int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg
 int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
                           long long n_segs, int k_t, int head_dim, void* k_rows, void* v_rows,
                           hipStream_t st);
-int pc_launch_decode_fp8(const void* q_rot, const void* k8, const void* v8, const float* k_scale,
-                         const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
-                         int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
-                         int head_dim, float scale, float* part_o, float* part_lse, int n_parts,
-                         hipStream_t st);
+// Partials of the 8-bit segments, then those of the 16-bit tail (tail_cap > 0), in one launch
+int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
+                         const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                         int seg_len_per_head, const void* k_tail, const void* v_tail,
+                         const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
+                         int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
+                         float* part_lse, int n_parts, hipStream_t st);
 // Merge of the tile kernel's partials [batch, n_parts, n_q, H_q, D] (no self segment)
 int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, float* lse_out, int batch,
                          int n_q, int n_q_heads, int head_dim, int n_parts, hipStream_t st);
