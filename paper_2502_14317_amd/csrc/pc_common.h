@@ -152,6 +152,7 @@ struct PcFlashArgs {
   void* o;                  // [n_seq, n_rows, H_q, D] bf16
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
   int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;
+  int group_batch;          // (sequence, KV head) groups an XCD interleaves, >= 1 (set by the launcher)
   float scale;
   // local
   const void* k_img;        // K tile images (rotated keys), image index = seq * img_seq_stride +

@@ -77,3 +77,29 @@ def test_tile_attention_edges(case):
                 v_self=bf16_bits_to_f64(vs[b])[:, g:g + 1] if with_self else None)
             assert_close(dev_bf16_to_f64(out[b, :, heads]), ro, O_ATOL, O_RTOL, f"out[b={b}, g={g}]")
             assert_close(lse[b, heads].cpu().numpy().T, rl, LSE_ATOL, 1e-3, f"lse[b={b}, g={g}]")
+
+
+# chunks, H_kv, H_q, D, w, w_q: (chunk, KV head) groups per XCD, batches of them and the rest
+@pytest.mark.parametrize("C,Hkv,Hq,D,w,wq", [
+    (57, 1, 16, 64, 150, 50),       # 7 groups per XCD in batches of 4 and 3, one group dealt to all
+    (3, 3, 3, 128, 130, 40),        # one group per XCD, one dealt to all
+    (2, 2, 8, 64, 300, 20),         # fewer groups than XCDs
+    (24, 1, 1, 128, 129, 1),        # three groups of two Q tiles, one batch
+])
+def test_local_attention_group_order(C, Hkv, Hq, D, w, wq):
+    print("group order", C, Hkv, Hq, D, w, wq, flush=True)
+    r = np.random.default_rng([64, C, Hkv, Hq, D, w])
+    mk = lambda h: f32_to_bf16_bits(r.standard_normal((C, w + wq, h, D)).astype(np.float32))
+    q, k, v = mk(Hq), mk(Hkv), mk(Hkv)
+    shape = pc.make_shape(C, w, wq, Hq, Hkv, D, 1, 1.0e4)
+    o = torch.full((C, w + wq, Hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((C, Hq, w + wq), float("nan"), dtype=torch.float32, device="cuda")
+    ws = pc.alloc_workspace(pc.pc_chunk_prefill_workspace_bytes(shape))
+    pc.pc_chunk_prefill_attn(shape, bits_to_dev(q), bits_to_dev(k), bits_to_dev(v), o, lse, None, None, None, ws)
+    torch.cuda.synchronize()
+    pos = np.arange(w + wq)
+    for c in range(C):
+        ro, rl = oracle.local_attention(oracle.rope(bf16_bits_to_f64(q[c]), pos, 1.0e4),
+                                        oracle.rope(bf16_bits_to_f64(k[c]), pos, 1.0e4), bf16_bits_to_f64(v[c]))[:2]
+        assert_close(dev_bf16_to_f64(o[c]), ro, O_ATOL, O_RTOL, f"o[c={c}]")
+        assert_close(lse[c].cpu().numpy().T, rl, LSE_ATOL, 1e-3, f"lse[c={c}]")
