@@ -3,7 +3,6 @@
 // the lower index wins.  Scores are mapped to unsigned keys whose integer order is the float
 // order, so every comparison is exact integer work.
 #include "pc_common.h"
-#include <atomic>
 
 // ------------------------------------------------------------------------------------------
 // Chunks: n <= 4096.  One workgroup; rank by counting.  rank(i) = #{j : key_j > key_i or
@@ -110,29 +109,34 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 }
 
 // ------------------------------------------------------------------------------------------
-// Tokens: one workgroup per (selected chunk, KV head).  The n keys sit in LDS.
-//  1. Radix select, 4 passes of 8 bits from the top: after the passes T is the k-th largest
-//     key and `need_eq` the number of keys equal to T that still fit (1 <= need_eq).
-//  2. Ordered compaction: each wavefront owns a contiguous index range; it counts its keys
-//     above T and equal to T, the counts are prefix-summed over wavefronts, and a second sweep
-//     emits index i iff key_i > T, or key_i == T and fewer than need_eq equal keys precede it.
-//     Output is ascending by construction and ties go to the lower index.
+// Tokens: one workgroup per (selected chunk, KV head), the n keys in registers: wavefront w owns a
+// contiguous index range, KPT slots of 64 consecutive indices.
+//  1. The k-th largest key T by counting keys into 2048 equal bins between the smallest and the
+//     largest key left, finding the bin that holds it and going on inside that bin (at most three
+//     rounds, 11 bits each; as a rule two).  The bins cover the range that the keys really have, so
+//     neighbouring scores fall into different bins and the LDS counters do not collide.
+//  2. Ordered compaction: every wavefront counts its keys above T and equal to T, the counts are
+//     prefix-summed over wavefronts, and a second sweep emits index i iff key_i > T, or key_i == T
+//     and fewer than need_eq equal keys precede it.  Output is ascending by construction and ties
+//     go to the lower index.
 // Attention calibration (Eq. 8) is a predicate on the keys: a token of the position class
 // [cls_lo, cls_hi) whose score is above lambda gets key 0, below every candidate (a NaN score
 // is a candidate with key 1), and k shrinks to the number of candidates when fewer are left;
 // the unused tail of the output is filled with -1 and the kept count is reported.
-#define PC_SEL_THREADS 512
-#define PC_SEL_WAVES (PC_SEL_THREADS / PC_WAVE)
+// Measured, before (keys in LDS, four 8-bit radix passes) and now: 512 tokens x
+// 16 workgroups 7.0 -> 5.8 us, 3584 x 32 13.8 -> 9.2, 7680 x 64 27 -> 15.  (Two bits a round counted with
+// ballots, no histogram: 8.5, 14.6 and 23.8.)
+#define PC_SEL_BINS 2048
 
-__global__ __launch_bounds__(PC_SEL_THREADS) void select_tokens_kernel(
+template <int KPT, int THREADS>
+__global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     const float* __restrict__ tok_score, const int32_t* __restrict__ chunk_idx, int n_kv_heads,
     int n, int k, float lambda, int cls_lo, int cls_hi, const int32_t* __restrict__ chunk_lens,
     int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt) {
-  extern __shared__ uint32_t keys[];   // n
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t sh_bin, sh_need, sh_evicted;
-  __shared__ uint32_t wave_tot[256 / PC_WAVE];
-  __shared__ uint32_t wave_gt[PC_SEL_WAVES], wave_eq[PC_SEL_WAVES];
+  constexpr int WAVES = THREADS / PC_WAVE, BPT = PC_SEL_BINS / THREADS;      // bins per thread
+  __shared__ uint32_t hist[PC_SEL_BINS];
+  __shared__ uint32_t sh_cand, sh_min, sh_max, sh_bin, sh_need, sh_in_bin;
+  __shared__ uint32_t wave_tot[WAVES], wave_gt[WAVES], wave_eq[WAVES];
 
   const int s = blockIdx.x / n_kv_heads;
   const int g = blockIdx.x % n_kv_heads;
@@ -140,106 +144,108 @@ __global__ __launch_bounds__(PC_SEL_THREADS) void select_tokens_kernel(
   if (c < 0) return;                               // no chunk for this entry: its outputs stay as they are
   const float* src = tok_score + ((long long)c * n_kv_heads + g) * n;
   int32_t* dst = out_idx + (long long)blockIdx.x * k;
+  const int wave = threadIdx.x / PC_WAVE, lane = threadIdx.x % PC_WAVE;
+  const int first = wave * (KPT * PC_WAVE) + lane; // index of the thread's slot 0; slot j: + 64 j
 
   const int n_valid = chunk_lens ? min(max(chunk_lens[c], 0), n) : n;   // a short chunk has fewer tokens
-  if (threadIdx.x == 0) sh_evicted = 0;
-  __syncthreads();
-  uint32_t my_evicted = 0;
-  for (int i = threadIdx.x; i < n; i += PC_SEL_THREADS) {
-    const float x = src[i];
-    uint32_t key = pc_order_key(x);
-    key = key == 0u ? 1u : key;
-    if ((i >= cls_lo && i < cls_hi && x > lambda) || i >= n_valid) { key = 0u; ++my_evicted; }
-    keys[i] = key;
+  if (threadIdx.x == 0) { sh_cand = 0u; sh_min = 0xffffffffu; sh_max = 0u; }
+  uint32_t key[KPT];
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const int i = first + PC_WAVE * j;
+    const float x = i < n ? src[i] : 0.f;
+    key[j] = max(pc_order_key(x), 1u);
+    if (i >= n_valid || (i >= cls_lo && i < cls_hi && x > lambda)) key[j] = 0u;
   }
-  if (my_evicted) atomicAdd(&sh_evicted, my_evicted);
   __syncthreads();
-  const int k_eff = min(k, n - (int)sh_evicted);
-  for (int i = k_eff + threadIdx.x; i < k; i += PC_SEL_THREADS) dst[i] = -1;
+  // number of candidates, their smallest and largest key
+  uint32_t cand = 0, lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    cand += (uint32_t)__popcll(__ballot(key[j] != 0u));
+    if (key[j] != 0u) { lo = min(lo, key[j]); hi = max(hi, key[j]); }
+  }
+#pragma unroll
+  for (int off = PC_WAVE / 2; off > 0; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+  }
+  if (lane == 0 && cand) { atomicAdd(&sh_cand, cand); atomicMin(&sh_min, lo); atomicMax(&sh_max, hi); }
+  __syncthreads();
+  const int k_eff = min(k, (int)sh_cand);
+  for (int i = k_eff + threadIdx.x; i < k; i += THREADS) dst[i] = -1;
   if (threadIdx.x == 0 && out_cnt) out_cnt[blockIdx.x] = k_eff;
   if (k_eff == 0) return;                          // uniform over the workgroup
 
-  uint32_t prefix = 0, mask = 0, need = (uint32_t)k_eff;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-    __syncthreads();
-    // Histogram of the next 8 bits over the keys that still match the prefix.  Scores of one
-    // chunk are close to each other, so in the upper passes nearly all keys of a wavefront fall
-    // into one bin: the lanes that share the first active lane's bin are counted with a ballot
-    // and added once, the others add one each.
-    for (int i0 = 0; i0 < n; i0 += PC_SEL_THREADS) {
-      const int i = i0 + threadIdx.x;
-      const uint32_t key = i < n ? keys[i] : 0u;
-      const bool live = i < n && (key & mask) == prefix;
-      const uint32_t bin = (key >> shift) & 255u;
-      const unsigned long long todo = __ballot(live);
-      if (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const uint32_t lead_bin = (uint32_t)__shfl((int)bin, leader);
-        const bool with_leader = live && bin == lead_bin;
-        const unsigned long long same = __ballot(with_leader);
-        if ((int)(threadIdx.x % PC_WAVE) == leader) atomicAdd(&hist[lead_bin], (uint32_t)__popcll(same));
-        if (live && !with_leader) atomicAdd(&hist[bin], 1u);
-      }
-    }
-    __syncthreads();
-    // The bin that holds the need-th largest key: every bin's count of keys above it by a
-    // suffix sum over the 256 bins (4 wavefronts x 64 bins), instead of one thread walking them.
-    {
-      const int t = threadIdx.x, ln = t % PC_WAVE;
-      const uint32_t h = t < 256 ? hist[t] : 0u;
-      uint32_t suf = h;                              // inclusive suffix sum inside the wavefront
+  // The need-th largest of the keys in [lo, hi].  T ends as the k-th largest key, or one below the
+  // smallest admitted key where a bin is taken whole (then no key equal to T is admitted).
+  lo = sh_min; hi = sh_max;
+  uint32_t need = (uint32_t)k_eff, T = lo;
+  while (lo != hi) {
+    const int shift = max(0, 32 - __clz((int)(hi - lo)) - 11);
 #pragma unroll
-      for (int off = 1; off < PC_WAVE; off <<= 1) {
-        const uint32_t up = (uint32_t)__shfl_down((int)suf, off);
-        if (ln + off < PC_WAVE) suf += up;
+    for (int u = 0; u < BPT; ++u) hist[threadIdx.x + THREADS * u] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KPT; ++j)
+      if (key[j] >= lo && key[j] <= hi) atomicAdd(&hist[(key[j] - lo) >> shift], 1u);
+    __syncthreads();
+    // keys in higher bins, by a suffix sum: a thread's BPT bins, the wavefront, the wavefronts above
+    uint32_t h[BPT], sum = 0;
+#pragma unroll
+    for (int u = 0; u < BPT; ++u) { h[u] = hist[BPT * threadIdx.x + u]; sum += h[u]; }
+    uint32_t suf = sum;
+#pragma unroll
+    for (int off = 1; off < PC_WAVE; off <<= 1) {
+      const uint32_t up = (uint32_t)__shfl_down((int)suf, off);
+      if (lane + off < PC_WAVE) suf += up;
+    }
+    if (lane == 0) wave_tot[wave] = suf;
+    __syncthreads();
+    uint32_t above = suf - sum;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) above += w > wave ? wave_tot[w] : 0u;
+#pragma unroll
+    for (int u = BPT - 1; u >= 0; --u) {
+      if (h[u] > 0 && above < need && above + h[u] >= need) {
+        sh_bin = (uint32_t)(BPT * threadIdx.x + u); sh_need = need - above; sh_in_bin = h[u];
       }
-      if (t < 256 && ln == 0) wave_tot[t / PC_WAVE] = suf;
-      __syncthreads();
-      if (t < 256) {
-        uint32_t above = suf - h;                    // keys in higher bins
-        for (int w = t / PC_WAVE + 1; w < 256 / PC_WAVE; ++w) above += wave_tot[w];
-        if (h > 0 && above < need && above + h >= need) { sh_bin = (uint32_t)t; sh_need = need - above; }
-      }
+      above += h[u];
     }
     __syncthreads();
-    prefix |= sh_bin << shift;
-    mask |= 255u << shift;
     need = sh_need;
+    lo += sh_bin << shift;
+    T = lo;
+    if (need == sh_in_bin) { T = lo - 1u; break; }             // every key of the bin is admitted
+    if (shift == 0) break;                                     // the bin is one key value
+    hi = min(hi, lo + ((1u << shift) - 1u));
   }
-  const uint32_t T = prefix;       // k-th largest key
-  const uint32_t need_eq = need;   // how many keys equal to T are admitted
-
-  const int wave = threadIdx.x / PC_WAVE, lane = threadIdx.x % PC_WAVE;
-  const int per_wave = ((n + PC_SEL_WAVES - 1) / PC_SEL_WAVES + PC_WAVE - 1) / PC_WAVE * PC_WAVE;
-  const int begin = wave * per_wave;
-  const int end = min(n, begin + per_wave);
 
   uint32_t cnt_gt = 0, cnt_eq = 0;
-  for (int i0 = begin; i0 < end; i0 += PC_WAVE) {
-    const int i = i0 + lane;
-    const uint32_t key = (i < end) ? keys[i] : 0u;
-    const bool gt = (i < end) && key > T, eq = (i < end) && key == T;
-    cnt_gt += (uint32_t)__popcll(__ballot(gt));
-    cnt_eq += (uint32_t)__popcll(__ballot(eq));
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    cnt_gt += (uint32_t)__popcll(__ballot(key[j] > T));
+    cnt_eq += (uint32_t)__popcll(__ballot(key[j] == T));
   }
   if (lane == 0) { wave_gt[wave] = cnt_gt; wave_eq[wave] = cnt_eq; }
   __syncthreads();
-  uint32_t base_gt = 0, base_eq = 0;
-  for (int w = 0; w < wave; ++w) { base_gt += wave_gt[w]; base_eq += wave_eq[w]; }
+  uint32_t base_gt = 0, base_eq = 0, total_gt = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    const uint32_t x = wave_gt[w];
+    total_gt += x;
+    if (w < wave) { base_gt += x; base_eq += wave_eq[w]; }
+  }
+  const uint32_t need_eq = (uint32_t)k_eff - total_gt;      // how many keys equal to T are admitted
 
-  for (int i0 = begin; i0 < end; i0 += PC_WAVE) {
-    const int i = i0 + lane;
-    const uint32_t key = (i < end) ? keys[i] : 0u;
-    const bool gt = (i < end) && key > T, eq = (i < end) && key == T;
+  const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const bool gt = key[j] > T, eq = key[j] == T;
     const unsigned long long bg = __ballot(gt), be = __ballot(eq);
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const uint32_t gt_before = base_gt + (uint32_t)__popcll(bg & below);
     const uint32_t eq_before = base_eq + (uint32_t)__popcll(be & below);
-    if (gt || (eq && eq_before < need_eq)) {
-      const uint32_t pos = gt_before + min(eq_before, need_eq);
-      dst[pos] = i;
-    }
+    if (gt || (eq && eq_before < need_eq)) dst[gt_before + min(eq_before, need_eq)] = first + PC_WAVE * j;
     base_gt += (uint32_t)__popcll(bg);
     base_eq += (uint32_t)__popcll(be);
   }
@@ -249,16 +255,21 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
                             int n_kv_heads, int chunk_len, int k, float lambda, int cls_lo,
                             int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
                             int32_t* out_cnt, hipStream_t st) {
-  const size_t lds = (size_t)chunk_len * sizeof(uint32_t);
-  if (lds > 48 * 1024) {      // raised once per device, to the largest chunk the entry point accepts
-    static std::atomic<uint64_t> raised{0};
-    const int rc = pc_raise_dynamic_lds((const void*)select_tokens_kernel, 32768 * (int)sizeof(uint32_t), raised);
-    if (rc != PC_OK) return rc;
-  }
   PcProfScope prof(PC_KERNEL_SELECT_TOKENS, st);
-  hipLaunchKernelGGL(select_tokens_kernel, dim3(n_sel * n_kv_heads), dim3(PC_SEL_THREADS), lds, st,
-                     tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,
-                     chunk_lens, out_idx, out_cnt);
+  // key slots per thread: the smallest power of two that holds the chunk (at most 32768 tokens), up
+  // to 8 with 512 threads, whose barriers are cheaper
+#define PC_SEL_LAUNCH(KPT, THREADS)                                                                   \
+  hipLaunchKernelGGL((select_tokens_kernel<KPT, THREADS>), dim3(n_sel * n_kv_heads), dim3(THREADS), 0, \
+                     st, tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,      \
+                     chunk_lens, out_idx, out_cnt)
+  if (chunk_len <= 512) PC_SEL_LAUNCH(1, 512);
+  else if (chunk_len <= 1024) PC_SEL_LAUNCH(2, 512);
+  else if (chunk_len <= 2048) PC_SEL_LAUNCH(4, 512);
+  else if (chunk_len <= 4096) PC_SEL_LAUNCH(8, 512);
+  else if (chunk_len <= 8192) PC_SEL_LAUNCH(8, 1024);
+  else if (chunk_len <= 16384) PC_SEL_LAUNCH(16, 1024);
+  else PC_SEL_LAUNCH(32, 1024);
+#undef PC_SEL_LAUNCH
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
