@@ -169,11 +169,12 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
 
   rc = pc_launch_rope_table(table, 0, L, D, s->rope_base, st);
   if (rc != PC_OK) return rc;
+  PcChunkSum sum = {};
   if (tok_score) {
     // the first score pass reads and rotates every key anyway: it also writes the rotated keys
     // and the tile images (the keys are read from memory once for both jobs)
     const PcPrepassOut pre = {v, kr, k_img, v_img, w.Lp};
-    rc = pc_launch_scores(s, q, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, st);
+    rc = pc_launch_scores(s, q, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
   } else {
     rc = pc_launch_kv_prepass(k, v, table, kr, k_img, v_img, s->n_chunks, L, w.Lp, s->n_kv_heads, D, st);
   }
@@ -185,7 +186,7 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
   a.img_head_stride = w.Lp / 64;
   a.n_seq = s->n_chunks; a.n_rows = L;
   a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads; a.head_dim = D;
-  a.seq_ctx = chunk_lens; a.seq_add = s->query_len;
+  a.seq_ctx = chunk_lens; a.seq_add = s->query_len; a.sum = sum;
   a.scale = eff_scale(s->softmax_scale, D);
   return pc_launch_flash(a, st);
 }
@@ -207,7 +208,7 @@ extern "C" int pc_chunk_query_scores(const pc_shape* s, const void* q, const voi
   void* ml = (char*)ws + pc_align_up((size_t)L * (s->head_dim / 2) * sizeof(float2), kAlign);
   rc = pc_launch_rope_table(table, 0, L, s->head_dim, s->rope_base, st);
   if (rc != PC_OK) return rc;
-  return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, st);
+  return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, nullptr, st);
 }
 
 extern "C" int pc_kv_append(const void* k_new, const void* v_new, int32_t batch, int32_t n_new,

@@ -145,6 +145,22 @@ struct PcKvGroup {
   long long seq_stride, seg_stride, head_stride;
 };
 #define PC_KV_GROUPS 3
+// chunk_score[c] = sum of per_chunk block sums; chunk_score == nullptr: nothing to do
+struct PcChunkSum { const float* blk_sum; float* chunk_score; int per_chunk; };
+// By 256 threads, in a fixed order (thread-strided partial sums, then a tree), so that the result does
+// not depend on timing; red: 256 floats of LDS.
+__device__ __forceinline__ void pc_chunk_sum(const float* blk_sum, float* chunk_score, int per_chunk, int c, float* red) {
+  const float* src = blk_sum + (long long)c * per_chunk;
+  float x = 0.f;
+  for (int i = threadIdx.x; i < per_chunk; i += 256) x += src[i];
+  red[threadIdx.x] = x;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) chunk_score[c] = red[0];
+}
 struct PcFlashArgs {
   int global;
   const void* q;            // [n_seq, n_rows, H_q, D] bf16, rotated here by `table` and scaled
@@ -160,6 +176,8 @@ struct PcFlashArgs {
   long long img_seq_stride, img_head_stride;                               // in tile images
   const int32_t* seq_ctx;   // [n_seq] context rows per sequence or nullptr: sequence s has
   int seq_add;              //   min(seq_ctx[s], n_rows - seq_add) + seq_add rows (and keys)
+  PcChunkSum sum;           // done by sum_blocks workgroups in front of the attention's (a multiple of
+  int sum_blocks;           //   8, so that those keep their XCDs; set by the launcher)
   // global
   PcKvGroup grp[PC_KV_GROUPS];
   int n_parts;              // workgroups a Q tile's keys are cut into; 1: o and lse are written
@@ -179,9 +197,10 @@ size_t pc_scores_ws_bytes(const pc_shape* s);
 // the rotated keys (k_rope, nullable), the K tile images and the V^T tile images of
 // pc_launch_kv_prepass, Lp = L rounded up to 64.
 struct PcPrepassOut { const void* v; void* k_rope; void* k_img; void* v_img; int Lp; };
+// later: the chunk scores' last addition is left to the caller, who passes it to pc_launch_flash
 int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int32_t* chunk_lens, const float2* table,
-                     void* ml_ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
-                     hipStream_t st);
+                     void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
+                     PcChunkSum* later, hipStream_t st);
 
 int pc_launch_rope_q(const void* q, void* q_rot, long long n_rows, int n_q, int n_heads, int D,
                      int pos0, float base, hipStream_t st);

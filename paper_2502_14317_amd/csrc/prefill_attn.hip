@@ -263,15 +263,23 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   const int n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
   const int per_group = GLOBAL ? n_qt * a.n_parts : G * n_qt;
   const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
-  int cg, within;
-  if ((int)blockIdx.x < full_blocks) {
-    const int xcd = blockIdx.x % 8, jb = blockIdx.x / 8;
+  int cg, within, bid = blockIdx.x;
+  if (!GLOBAL) {
+    static_assert(PC_FA_THREADS == 256, "pc_chunk_sum");
+    if (bid < a.sum_blocks) {
+      if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
+      return;
+    }
+    bid -= a.sum_blocks;
+  }
+  if (bid < full_blocks) {
+    const int xcd = bid % 8, jb = bid / 8;
     const int batch = jb / (a.group_batch * per_group), in_batch = jb % (a.group_batch * per_group);
     const int n_batch = min(a.group_batch, n_groups / 8 - batch * a.group_batch);
     cg = (batch * a.group_batch + in_batch % n_batch) * 8 + xcd;
     within = in_batch / n_batch;
   } else {
-    const int rest = blockIdx.x - full_blocks;
+    const int rest = bid - full_blocks;
     cg = n_groups / 8 * 8 + rest / per_group;
     within = rest % per_group;
   }
@@ -927,7 +935,8 @@ static int launch_flash_t(const PcFlashArgs& args, hipStream_t st) {
   const int G = a.n_q_heads / a.n_kv_heads;
   const long long rows_wg = GLOBAL ? (long long)a.n_rows * G : a.n_rows;
   const long long n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
-  const long long blocks = (long long)a.n_seq * a.n_kv_heads * n_qt * (GLOBAL ? a.n_parts : G);
+  a.sum_blocks = !GLOBAL && a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
+  const long long blocks = (long long)a.n_seq * a.n_kv_heads * n_qt * (GLOBAL ? a.n_parts : G) + a.sum_blocks;
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   // Local: a group that cannot fill an XCD's 64 workgroup slots by itself is interleaved with

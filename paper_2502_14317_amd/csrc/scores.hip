@@ -14,7 +14,8 @@
 // splitting its query columns, is then spread over more keys):
 //   pass 1  (S^T = K Q^T, a lane owns a voting row)  per-block running max / sum of every
 //           voting row -> workspace [c, g, key block, column] (m, l)
-//   between the passes a small kernel combines the blocks' (m, l) into the row logsumexp
+//   the blocks' (m, l) are combined into the row logsumexp by pass 2 itself while they are few, by a
+//   small kernel in between otherwise
 //   pass 2  (S = Q K^T, a lane owns a key)           recompute the logits, p = exp2(s - lse)
 //           and sum p over the columns (voting rows x heads of the group) for each key
 //           -> tok_score
@@ -42,6 +43,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #define PC_SC_KB_MAX 1024   // the largest
 #define PC_SC_TILE 64       // keys staged in LDS at a time
 #define PC_SC_KB_MANY 128   // keys per workgroup with more than 4 column blocks; half where that leaves CUs idle
+#define PC_SC_LSE_BLOCKS 64 // up to this many blocks of pass 1, pass 2 combines their (max, sum) itself
 #define PC_SC_LOG2E 1.4426950408889634f
 
 struct PcScoreArgs {
@@ -282,19 +284,6 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   // pass 1: this lane's voting row (column) and its running statistics
   const int my_qrow = first_obs + col % a.w_obs;
   float m_run = -INFINITY, l_run = 0.f;
-  // pass 2: the voting rows / logsumexp of the 16 result registers (rows of S)
-  float lse_r[16];
-  int qrow_r[16];
-  if (PASS == 2) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
-      const bool ok = active && cc < a.n_cols;
-      lse_r[r] = ok ? lse2[cc] : INFINITY;                // exp2(-inf) = 0 for padding columns
-      qrow_r[r] = ok ? first_obs + cc % a.w_obs : -1;
-    }
-  }
-
   // keys that count: pass 1 the sequence's, pass 2 its context rows; the pre-pass wants all rows
   const bool pre = PASS == 1 && a.v_img != nullptr;
   const int key_end = PASS == 1 ? ctx_len + (a.L - a.w) : ctx_len;
@@ -302,6 +291,49 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   PcKeyStage<D, TILE, PASS == 1> keys;
   keys.begin(a, tid, kblock * a.kb_keys, pre);
   if (kblock * a.kb_keys < stage_end) keys.fetch(a, c, g, kblock * a.kb_keys);
+
+  // pass 2: the voting rows / logsumexp of the 16 result registers (rows of S).  Where pass 1 left few
+  // blocks, every wavefront combines its columns' (max, sum) itself, while its first keys are on
+  // their way: a lane half takes every other block.
+  float lse_r[16];
+  int qrow_r[16];
+  if (PASS == 2) {
+    float lse = INFINITY;                                  // column 32 cb + n; exp2(-inf) = 0 for padding columns
+    const int my_col = 32 * cb + n;
+    if (active && my_col < a.n_cols && a.n_kb <= PC_SC_LSE_BLOCKS) {
+      const float2* src = a.ml + ml_base + my_col;
+      float M = -INFINITY, sum = 0.f;
+      for (int kb = hf; kb < a.n_kb; kb += 8) {
+        float2 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = src[(long long)min(kb + 2 * i, a.n_kb - 1) * a.n_cols];
+        float m_new = M;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m_new = fmaxf(m_new, v[i].x);
+        if (sum > 0.f) sum *= exp2f(M - m_new);
+        M = m_new;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (kb + 2 * i < a.n_kb && v[i].y > 0.f) sum += v[i].y * exp2f(v[i].x - M);
+      }
+      const float m_o = __shfl_xor(M, 32), s_o = __shfl_xor(sum, 32);
+      const float top = fmaxf(M, m_o);
+      float tot = 0.f;
+      // the lower half's share first, on both sides: both halves hold the same bits
+      const float m0 = hf ? m_o : M, s0 = hf ? s_o : sum, m1 = hf ? M : m_o, s1 = hf ? sum : s_o;
+      if (s0 > 0.f) tot += s0 * exp2f(m0 - top);
+      if (s1 > 0.f) tot += s1 * exp2f(m1 - top);
+      lse = top + log2f(tot);
+    } else if (active && my_col < a.n_cols) {
+      lse = lse2[my_col];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int in_cb = 8 * (r / 4) + 4 * hf + (r % 4), cc = 32 * cb + in_cb;
+      lse_r[r] = __shfl(lse, in_cb);
+      qrow_r[r] = active && cc < a.n_cols ? first_obs + cc % a.w_obs : -1;
+    }
+  }
 
   // one loop body (not unrolled): leaves room for the prefetch registers
   const int n_tiles = a.kb_keys / TILE;
@@ -646,22 +678,13 @@ __global__ __launch_bounds__(128) void scores_lse_kernel(const float2* __restric
   lse2[(long long)blockIdx.x * n_pad + col] = M + log2f(sum);
 }
 
-// chunk_score[c] = sum of tok_score[c, :, :] = sum of the chunk's pass-2 block sums, added in a
-// fixed order (thread-strided partial sums, then a tree), so the result does not depend on timing.
+// chunk_score[c] = sum of tok_score[c, :, :] = sum of the chunk's pass-2 block sums (the standalone
+// score call; inside the prefill call the attention launch that follows does it).
 __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restrict__ blk_sum,
                                                           float* __restrict__ chunk_score,
                                                           int per_chunk) {
   __shared__ float red[256];
-  const float* src = blk_sum + (long long)blockIdx.x * per_chunk;
-  float x = 0.f;
-  for (int i = threadIdx.x; i < per_chunk; i += 256) x += src[i];
-  red[threadIdx.x] = x;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) chunk_score[blockIdx.x] = red[0];
+  pc_chunk_sum(blk_sum, chunk_score, per_chunk, blockIdx.x, red);
 }
 
 template <int D, int PASS>
@@ -703,7 +726,7 @@ size_t pc_scores_ws_bytes(const pc_shape* s) { return scores_ws_layout(s).total;
 
 int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int32_t* chunk_lens, const float2* table,
                      void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
-                     hipStream_t st) {
+                     PcChunkSum* later, hipStream_t st) {
   const PcScoreWs w = scores_ws_layout(s);
   PcScoreArgs a = {};
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.table = table; a.chunk_lens = chunk_lens;
@@ -747,7 +770,7 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
     else launch_scores_pass<64, 1>(wpc, grid, block, st, a);
   }
   PC_LAUNCH_CHECK();
-  {
+  if (many || a.n_kb > PC_SC_LSE_BLOCKS) {
     PcProfScope prof(PC_KERNEL_SCORES_LSE, st);
     hipLaunchKernelGGL(scores_lse_kernel, dim3(s->n_chunks * s->n_kv_heads, (32 * a.n_cb + 127) / 128),
                        dim3(128), 0, st, a.ml, a.lse2, a.n_kb, a.n_cols, 32 * a.n_cb);
@@ -758,7 +781,9 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
     else launch_scores_pass<64, 2>(wpc, grid2, block, st, a);
   }
   PC_LAUNCH_CHECK();
-  if (chunk_score) {
+  if (later) {
+    *later = PcChunkSum{a.blk_sum, chunk_score, s->n_kv_heads * n_kb2};
+  } else if (chunk_score) {
     PcProfScope prof(PC_KERNEL_CHUNK_SCORE, st);
     hipLaunchKernelGGL(chunk_score_kernel, dim3(s->n_chunks), dim3(256), 0, st, a.blk_sum,
                        chunk_score, s->n_kv_heads * n_kb2);
