@@ -272,14 +272,15 @@ static size_t q_ws_bytes(bool small, size_t rows, int n_q, int D) {
   return small ? rows * D * 2 : (size_t)n_q * (D / 2) * sizeof(float2);
 }
 
-// Parts of the tile path's keys and the partials the workspace has room for: what the segments
-// alone would be cut into and one more for a self segment, so that the workspace grows with
-// every group of keys.
+// Parts of the tile path's keys and the partials the workspace has room for: with a self segment at
+// least one more than the segments alone are cut into, so that the workspace grows with every group
+// of keys.
 static int tile_parts(int batch, int n_q, long long seg_tiles, int n_q_heads, int n_kv_heads, int D, int has_self,
                       int& room) {
-  room = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles) + (has_self ? 1 : 0);
+  const int alone = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles) + (has_self ? 1 : 0);
   const int parts = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles + key_tiles(has_self, n_q));
-  return parts < room ? parts : room;
+  room = parts > alone ? parts : alone;
+  return parts;
 }
 
 struct Par8Ws {

@@ -185,7 +185,7 @@ struct PcFlashArgs {
   float* part_lse;          // [n_seq, n_parts, n_rows, H_q]
 };
 // How many parts the global attention's keys are cut into (n_tiles: 64-key tiles of a KV head at
-// full lengths)
+// full lengths), 1 to 64
 int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles);
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
 
