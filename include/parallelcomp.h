@@ -308,7 +308,7 @@ size_t pc_parallel_attn_fp8_workspace_bytes(int32_t batch, int32_t n_q, int32_t 
  * library instead of a caller workspace.  Calls no hipMalloc / hipFree / allocating routine.
  * Same arguments, arithmetic and results as pc_parallel_attn (the same kernels run), except:
  *   - no ws / ws_bytes;
- *   - PC_ERR_UNSUPPORTED when n_q * H_q / H_kv > 16 (the tile path's K/V images do not fit);
+ *   - PC_ERR_UNSUPPORTED when n_q * H_q / H_kv > 16 (the tile path is not served here);
  *   - PC_ERR_WORKSPACE when the request needs more than PC_STATIC_SCRATCH_BYTES, i.e. when
  *     pc_parallel_attn_workspace_bytes(...) of the same shape exceeds it
  *     (the decode config, 16 sequences x 32 heads x 128, 2 partials per group, needs 0.63 MiB).

@@ -717,7 +717,7 @@ extern "C" int pc_parallel_attn_static(const void* q, const void* kc, const void
   if (rc != PC_OK) return rc;
   const ParWs w = par_ws_layout(batch, n_q, n_seg, k_t, n_q_heads, n_kv_heads, head_dim,
                                 k_self != nullptr);
-  if (!w.small) return PC_ERR_UNSUPPORTED;                  // the tile path needs K/V images: too large
+  if (!w.small) return PC_ERR_UNSUPPORTED;                  // the tile path is not served here
   if (w.total > PC_STATIC_SCRATCH_BYTES) return PC_ERR_WORKSPACE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
