@@ -121,11 +121,13 @@ def _ptr(t):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("tensors must be contiguous GPU tensors")
-    return c_void_p(t.data_ptr())
+    return t.data_ptr()          # a plain integer: the argument types make it a pointer
 
 
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of torch.cuda.current_stream() without the stream object around it: a decoding step of
+    # a short cache is bound by its two calls
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ws(ws):
