@@ -181,35 +181,50 @@ int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, 
 }
 
 // ------------------------------------------------------------------------------------------
-// Rotate the query rows of the split-KV kernel at positions pos0 + t (fp64 angles; pos0 < 0:
-// the rows are already rotated).
-__global__ void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
-                              long long n_pairs, int n_q, int n_heads, int D, int pos0,
-                              double log_base) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_pairs) return;
-  const int half = D / 2;
-  const int i = (int)(idx % half);
-  const long long row = idx / half;                       // (b, t, h)
-  const int t = (int)((row / n_heads) % n_q);
-  double sn = 0.0, cs = 1.0;
+// Query rows rotated at positions pos0 + t (pos0 < 0: they arrive rotated), times mul, all in fp64 and
+// rounded to bf16 once: the tile kernel's operand (mul = softmax scale x log2(e)) and the few-row
+// path's where the merge needs it too (mul = 1).  One workgroup per query row; a thread keeps its two
+// rotation pairs and goes through the heads, so the fp64 exp and sincos are paid once per row and
+// not once per head.
+__global__ __launch_bounds__(256) void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
+                                                     int n_q, int n_heads, int D, int pos0, double log_base,
+                                                     double mul) {
+  const int half = D / 2, tpr = half / 2, i = 2 * (threadIdx.x % tpr);
+  double sn[2] = {0.0, 0.0}, cs[2] = {1.0, 1.0};
   if (pos0 >= 0) {
-    const double theta = exp(-2.0 * (double)i / (double)D * log_base);
-    sincos((double)(pos0 + t) * theta, &sn, &cs);
+    const int t = pos0 + (int)(blockIdx.x % (unsigned)n_q);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const double theta = exp(-2.0 * (double)(i + e) / (double)D * log_base);
+      sincos((double)t * theta, &sn[e], &cs[e]);
+    }
   }
-  const double x1 = bf16_bits_to_f32(q[row * D + i]), x2 = bf16_bits_to_f32(q[row * D + i + half]);
-  q_rot[row * D + i] = (uint16_t)f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
-  q_rot[row * D + i + half] = (uint16_t)f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
+  const long long row0 = (long long)blockIdx.x * n_heads;          // (b, t, head 0)
+#pragma unroll 4
+  for (int h = threadIdx.x / tpr; h < n_heads; h += 256 / tpr) {
+    const long long at = (row0 + h) * D + i;
+    const uint32_t a = *(const uint32_t*)(q + at), b = *(const uint32_t*)(q + at + half);
+    const double x1[2] = {bf16_lo_to_f32(a), bf16_hi_to_f32(a)}, x2[2] = {bf16_lo_to_f32(b), bf16_hi_to_f32(b)};
+    uint32_t y1[2], y2[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      y1[e] = f32_to_bf16_bits((float)((x1[e] * cs[e] - x2[e] * sn[e]) * mul));
+      y2[e] = f32_to_bf16_bits((float)((x2[e] * cs[e] + x1[e] * sn[e]) * mul));
+    }
+    *(uint32_t*)(q_rot + at) = y1[0] | (y1[1] << 16);
+    *(uint32_t*)(q_rot + at + half) = y2[0] | (y2[1] << 16);
+  }
 }
 
-int pc_launch_rope_q(const void* q, void* q_rot, long long n_rows, int n_q, int n_heads, int D,
-                     int pos0, float base, hipStream_t st) {
-  const long long n_pairs = n_rows * (D / 2);
-  if (n_pairs == 0) return PC_OK;
+int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads, int D, int pos0,
+                     float base, float mul, hipStream_t st) {
+  const long long blocks = (long long)batch * n_q;
+  if (blocks == 0) return PC_OK;
+  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_ROPE_Q, st);
-  hipLaunchKernelGGL(rope_q_kernel, dim3((unsigned)((n_pairs + 255) / 256)), dim3(256), 0, st,
-                     (const uint16_t*)q, (uint16_t*)q_rot, n_pairs, n_q, n_heads, D, pos0,
-                     log((double)(pos0 >= 0 ? base : 2.0f)));
+  hipLaunchKernelGGL(rope_q_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)q,
+                     (uint16_t*)q_rot, n_q, n_heads, D, pos0, log((double)(pos0 >= 0 ? base : 2.0f)),
+                     (double)mul);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

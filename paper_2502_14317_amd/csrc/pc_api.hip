@@ -167,7 +167,7 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
   void* kr = k_rope;                                       // nullable: then only the images are written
   const int L = s->chunk_len + s->query_len, D = s->head_dim;
 
-  rc = pc_launch_rope_table(table, 0, L, D, s->rope_base, st);
+  rc = pc_launch_rope_table(table, L, D, s->rope_base, st);
   if (rc != PC_OK) return rc;
   PcChunkSum sum = {};
   if (tok_score) {
@@ -206,7 +206,7 @@ extern "C" int pc_chunk_query_scores(const pc_shape* s, const void* q, const voi
   const int L = s->chunk_len + s->query_len;
   float2* table = (float2*)ws;
   void* ml = (char*)ws + pc_align_up((size_t)L * (s->head_dim / 2) * sizeof(float2), kAlign);
-  rc = pc_launch_rope_table(table, 0, L, s->head_dim, s->rope_base, st);
+  rc = pc_launch_rope_table(table, L, s->head_dim, s->rope_base, st);
   if (rc != PC_OK) return rc;
   return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, nullptr, st);
 }
@@ -266,12 +266,6 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
 // 64-key tiles of n segments of k_t keys
 static long long key_tiles(int n, int k_t) { return (long long)n * ((k_t + 63) / 64); }
 
-// The query's place in the workspace: rotated rows for the split-KV kernels, the (cos, sin) table
-// of the rows' positions for the tile kernel (which rotates as it loads).
-static size_t q_ws_bytes(bool small, size_t rows, int n_q, int D) {
-  return small ? rows * D * 2 : (size_t)n_q * (D / 2) * sizeof(float2);
-}
-
 // Parts of the tile path's keys and the partials the workspace has room for: with a self segment at
 // least one more than the segments alone are cut into, so that the workspace grows with every group
 // of keys.
@@ -284,7 +278,7 @@ static int tile_parts(int batch, int n_q, long long seg_tiles, int n_q_heads, in
 }
 
 struct Par8Ws {
-  size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rope table of the rows on the tile path
+  size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rotated query rows
   int n_parts, parts8;
   bool small;
 };
@@ -304,7 +298,7 @@ static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_ca
   }
   size_t off = 0;
   const size_t rows = (size_t)batch * n_q * n_q_heads;
-  w.q_rot = off;    off = pc_align_up(off + q_ws_bytes(w.small, rows, n_q, D), kAlign);
+  w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
   if (w.small) parts_room = w.n_parts;
   w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
   w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
@@ -387,8 +381,7 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
   const void* q_in = q;
   int pos0 = q_pos0;
   if (q_pos0 >= 0 && has_self) {
-    rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                          q_pos0, rope_base, st);
+    rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
     if (rc != PC_OK) return rc;
     q_in = base + w.q_rot; pos0 = -1;
   }
@@ -490,7 +483,7 @@ extern "C" int pc_gather_kv_amax(const void* k_src, const void* v_src, const int
 
 // ---------------------------------------------------------------------------- parallel attention
 struct ParWs {
-  size_t q_rot, part_o, part_lse, total;       // q_rot: the rope table of the rows on the tile path
+  size_t q_rot, part_o, part_lse, total;       // q_rot: the rotated query rows
   int n_parts;
   bool small;
 };
@@ -508,7 +501,7 @@ static ParWs par_ws_layout(int batch, int n_q, int n_seg, int k_t, int n_q_heads
   }
   size_t off = 0;
   const size_t rows = (size_t)batch * n_q * n_q_heads;
-  w.q_rot = off;    off = pc_align_up(off + q_ws_bytes(w.small, rows, n_q, D), kAlign);
+  w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
   if (w.small) parts_room = w.n_parts;
   w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
   w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
@@ -575,14 +568,16 @@ static PcKvGroup self_group(const void* k, const void* v, int n_q, int n_kv_head
   return kg;
 }
 
-// Tile path of Eq. 9-11: the (cos, sin) table of the query rows (identity for rows that arrive
-// rotated, q_pos0 < 0), one launch over all key groups, the merge if it was cut into parts.
+// Tile path of Eq. 9-11: the query operand (rotated and multiplied by scale x log2(e) before the one
+// rounding to bf16, so that the matrix cores deliver logits in log2 units; rows that arrive rotated,
+// q_pos0 < 0, are only scaled: their bf16 values are rounded a second time), one launch over all key
+// groups, the merge if it was cut into parts.
 static int tile_attn_run(PcFlashArgs& a, const void* q, int batch, int n_q, int n_q_heads, int n_kv_heads,
-                         int D, int q_pos0, float rope_base, float scale, float2* table, float* part_o,
+                         int D, int q_pos0, float rope_base, float scale, void* q_rot, float* part_o,
                          float* part_lse, int n_parts, void* out, float* lse_out, hipStream_t st) {
-  int rc = pc_launch_rope_table(table, q_pos0, n_q, D, rope_base, st);
+  int rc = pc_launch_rope_q(q, q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, scale * 1.4426950408889634f, st);
   if (rc != PC_OK) return rc;
-  a.global = 1; a.q = q; a.table = table; a.o = out; a.lse = lse_out; a.part_o = part_o; a.part_lse = part_lse;
+  a.global = 1; a.q = q_rot; a.o = out; a.lse = lse_out; a.part_o = part_o; a.part_lse = part_lse;
   a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = D;
   a.scale = scale; a.n_parts = n_parts;
   rc = pc_launch_flash(a, st);
@@ -613,8 +608,7 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
     const void* q_in = q;
     int pos0 = q_pos0;
     if (q_pos0 >= 0 && has_self) {
-      rc = pc_launch_rope_q(q, base + w.q_rot, (long long)batch * n_q * n_q_heads, n_q, n_q_heads, D,
-                            q_pos0, rope_base, st);
+      rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
       if (rc != PC_OK) return rc;
       q_in = base + w.q_rot; pos0 = -1;
     }
@@ -632,7 +626,7 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
   if (n_seg > 0) a.grp[0] = segment_group(kc, vc, seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
   if (has_self) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
   return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
-                       (float2*)(base + w.q_rot), part_o, part_lse, w.n_parts, out, lse_out, st);
+                       base + w.q_rot, part_o, part_lse, w.n_parts, out, lse_out, st);
 }
 
 // Eq. 9-11 for a block of query rows over the 8-bit cache: the segments are widened to bf16 rows
@@ -655,7 +649,7 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
   if (tail_cap > 0) a.grp[1] = segment_group(k_tail, v_tail, tail_len, 0, 1, tail_cap, n_kv_heads, D);
   if (k_self != nullptr) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
   return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
-                       (float2*)(base + w.q_rot), (float*)(base + w.part_o), (float*)(base + w.part_lse),
+                       base + w.q_rot, (float*)(base + w.part_o), (float*)(base + w.part_lse),
                        w.n_parts, out, lse_out, st);
 }
 

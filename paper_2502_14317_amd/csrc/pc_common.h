@@ -123,7 +123,7 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
                           int32_t* queue_id, float* queue_score, int32_t* queue_slot,
                           int32_t* slot_src, hipStream_t st);
 
-int pc_launch_rope_table(float2* table, int pos0, int n_pos, int head_dim, float base, hipStream_t st);
+int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st);
 
 // K/V pre-pass of the local attention: K rotated -> k_rope (row-major, optional) and K tile images;
 // V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
@@ -163,8 +163,9 @@ __device__ __forceinline__ void pc_chunk_sum(const float* blk_sum, float* chunk_
 }
 struct PcFlashArgs {
   int global;
-  const void* q;            // [n_seq, n_rows, H_q, D] bf16, rotated here by `table` and scaled
-  const float2* table;      // rope table, row t for query row t
+  const void* q;            // [n_seq, n_rows, H_q, D] bf16.  Local: rotated here by `table` and scaled; global:
+                            //   rotated, multiplied by scale * log2(e) and rounded beforehand
+  const float2* table;      // local: rope table, row t for query row t
   void* o;                  // [n_seq, n_rows, H_q, D] bf16
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
   int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;
@@ -202,8 +203,10 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
                      void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
                      PcChunkSum* later, hipStream_t st);
 
-int pc_launch_rope_q(const void* q, void* q_rot, long long n_rows, int n_q, int n_heads, int D,
-                     int pos0, float base, hipStream_t st);
+// q [batch, n_q, n_heads, D] -> rotated at positions pos0 + t (pos0 < 0: it arrives rotated) and
+// multiplied by mul in fp64, rounded to bf16 once
+int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads, int D, int pos0,
+                     float base, float mul, hipStream_t st);
 // How the split-KV decode kernels cut the keys into workgroups (n_bg = batch * H_kv): the keys of
 // a (sequence, KV head) group, all its segments laid end to end in blocks of 32 keys, are cut
 // into n_parts equal runs of blocks, one workgroup (and one partial result) each.

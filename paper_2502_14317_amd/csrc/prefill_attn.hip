@@ -43,23 +43,22 @@
 #define PC_LN2 0.6931471805599453f
 
 // ------------------------------------------------------------------------------------------
-// cos/sin of the positions pos0 .. pos0 + n_pos - 1; pos0 < 0: the identity (rows already rotated)
-__global__ void rope_table_kernel(float2* __restrict__ table, int pos0, int n_pos, int D, double log_base) {
+__global__ void rope_table_kernel(float2* __restrict__ table, int n_pos, int D, double log_base) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int half = D / 2;
   if (idx >= n_pos * half) return;
   const int p = idx / half, i = idx % half;
   const double theta = exp(-2.0 * (double)i / (double)D * log_base);
-  double sn = 0.0, cs = 1.0;
-  if (pos0 >= 0) sincos((double)(pos0 + p) * theta, &sn, &cs);
+  double sn, cs;
+  sincos((double)p * theta, &sn, &cs);
   table[idx] = make_float2((float)cs, (float)sn);
 }
 
-int pc_launch_rope_table(float2* table, int pos0, int n_pos, int head_dim, float base, hipStream_t st) {
+int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st) {
   const int n = n_pos * (head_dim / 2);
   PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, pos0,
-                     n_pos, head_dim, log((double)(pos0 >= 0 ? base : 2.0f)));
+  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, n_pos,
+                     head_dim, log((double)base));
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
@@ -396,7 +395,8 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
 
   // ---- Q^T as B operand, NB 32-row blocks: lane holds query n of each, d = 16*ks + 8*hf .. +7.
   //      The softmax scale and log2(e) are folded into Q before its rounding to bf16, so the
-  //      first product yields logits in log2 units and the exponent needs no multiply.
+  //      first product yields logits in log2 units and the exponent needs no multiply.  (Global: the
+  //      rows arrive rotated, scaled and rounded, see rope_q_kernel.)
   const float c_log2 = a.scale * PC_LOG2E;
   bf16x8 bq[NB][KS];
 #pragma unroll
@@ -418,13 +418,18 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
       static_assert(NB == 1, "staging area is sized for one row block per wavefront");
       uint16_t* st_q = smem + wave * (2 * 32 * D);            // 32 rows x D bf16
       uint16_t* st_t = st_q + 32 * D;                         // 32 half rows of the table (D bytes x 2)
-      const int l_row = lane / PPR, l_piece = lane % PPR;
+      // (global: addresses from an opaque copy of the lane index, so that the epilogue's, which are alike, are
+      // not kept in registers across the loop, which has none to spare: 4 spills instead of 24)
+      int l = lane;
+      if (GLOBAL) asm volatile("" : "+v"(l));
+      const int l_row = l / PPR, l_piece = l % PPR, n = l % 32, hf = l / 32;
       u32x4 rq[NLD], rt[2][NLD];
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         const int r = RPL * i + l_row;
         const int grow = min(row0 + 32 * nb + r, seq_rows - 1);
         rq[i] = pc_load_once((const u32x4*)((const uint16_t*)a.q + row_at(grow) * D + 8 * l_piece));
+        if (GLOBAL) continue;
         const char* trow = (const char*)(a.table + (long long)pos_of(grow) * HALF);
         rt[0][i] = *(const u32x4*)(trow + 16 * l_piece);
         rt[1][i] = *(const u32x4*)(trow + 2 * D + 16 * l_piece);
@@ -434,8 +439,14 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
         const int r = RPL * i + l_row;
         *(u32x4*)(st_q + (r * PPR + (l_piece ^ (r % PPR))) * 8) = rq[i];
       }
+      if (GLOBAL) {
+        PC_FA_WAVE_LDS_SYNC();
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
+        for (int ks = 0; ks < KS; ++ks)
+          bq[nb][ks] = *(const bf16x8*)(st_q + (n * PPR + ((2 * ks + hf) ^ (n % PPR))) * 8);
+      }
+#pragma unroll
+      for (int half = 0; half < (GLOBAL ? 0 : 2); ++half) {
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
           const int r = RPL * i + l_row;
