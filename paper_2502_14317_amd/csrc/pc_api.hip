@@ -277,6 +277,17 @@ static int tile_parts(int batch, int n_q, long long seg_tiles, int n_q_heads, in
   return parts;
 }
 
+// Limits of the tile path beyond those of the shape checks.  The tile kernel steps through the self
+// segment by 64 rows of all KV heads and addresses a tile with 32-bit byte offsets: up to 65535 heads
+// (63 x 65535 x 256 bytes) keep both in range.  65535 is also the most 64-key tiles of a segment or
+// tail it takes.
+static int check_tile_limits(int n_seg, int k_t, int tail_cap, int n_kv_heads, int has_self) {
+  if (has_self && n_kv_heads > 65535) return PC_ERR_SHAPE;
+  if (n_seg > 0 && key_tiles(1, k_t) > 65535) return PC_ERR_SHAPE;
+  if (key_tiles(1, tail_cap) > 65535) return PC_ERR_SHAPE;
+  return PC_OK;
+}
+
 struct Par8Ws {
   size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rotated query rows
   int n_parts, parts8;
@@ -373,10 +384,13 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
   hipStream_t st = (hipStream_t)stream;
   char* base = (char*)ws;
   const float scale = eff_scale(softmax_scale, D);
-  if (!w.small)
+  if (!w.small) {
+    rc = check_tile_limits(n_seg, k_t, tail_cap, n_kv_heads, has_self);
+    if (rc != PC_OK) return rc;
     return parallel_attn_fp8_tiles(q, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, k_tail, v_tail,
                                    tail_len, tail_cap, k_self, v_self, batch, n_q, n_seg, k_t, n_q_heads,
                                    n_kv_heads, D, q_pos0, rope_base, scale, out, lse_out, w, base, st);
+  }
   // the kernels rotate the query rows themselves, unless the merge needs them too (self segment)
   const void* q_in = q;
   int pos0 = q_pos0;
@@ -622,6 +636,8 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
   }
 
   // ---- many query rows: MFMA tile kernel over [segments ; causal self segment]
+  rc = check_tile_limits(n_seg, k_t, 0, n_kv_heads, has_self);
+  if (rc != PC_OK) return rc;
   PcFlashArgs a = {};
   if (n_seg > 0) a.grp[0] = segment_group(kc, vc, seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
   if (has_self) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
