@@ -698,25 +698,36 @@ static void launch_scores_pass(int wpc, dim3 grid, dim3 block, hipStream_t st, c
 }
 
 // Keys per workgroup of scores_many_kernel: 128, or 64 where that is less than one workgroup per CU
+#define PC_SC_MANY_WGS 256
+static size_t key_blocks(const pc_shape* s, int kb) {
+  const size_t L = (size_t)s->chunk_len + s->query_len;
+  return (size_t)s->n_chunks * s->n_kv_heads * ((L + kb - 1) / kb);
+}
 static int many_kb_keys(const pc_shape* s) {
-  const long long L = (long long)s->chunk_len + s->query_len;
-  const long long wgs = (long long)s->n_chunks * s->n_kv_heads * ((L + PC_SC_KB_MANY - 1) / PC_SC_KB_MANY);
-  return wgs < 256 ? PC_SC_KB_MANY / 2 : PC_SC_KB_MANY;
+  return key_blocks(s, PC_SC_KB_MANY) < PC_SC_MANY_WGS ? PC_SC_KB_MANY / 2 : PC_SC_KB_MANY;
+}
+// Key blocks of all chunks and KV heads that the workspace has room for.  A workspace serves every call
+// with no more chunks or rows than the one it was sized for (a short last batch is an example), so
+// this must not fall where many_kb_keys rises to the larger block: blocks of half the keys, of
+// which there are never as many as 2 x PC_SC_MANY_WGS, have room behind that point too.
+static size_t key_blocks_room(const pc_shape* s, size_t n_cb) {
+  if (n_cb <= PC_SC_WAVES) return key_blocks(s, PC_SC_KB);
+  const size_t large = key_blocks(s, PC_SC_KB_MANY), small = key_blocks(s, PC_SC_KB_MANY / 2);
+  const size_t small_max = small < 2 * PC_SC_MANY_WGS ? small : 2 * PC_SC_MANY_WGS;
+  return large > small_max ? large : small_max;
 }
 
 // Workspace of the score passes: per-block (max, sum) of pass 1, the combined row logsumexp, the
 // block sums of pass 2 and, with more than 4 column blocks, the split query columns.
 struct PcScoreWs { size_t ml, lse2, blk_sum, q_split, total; };
 static PcScoreWs scores_ws_layout(const pc_shape* s) {
-  const size_t L = (size_t)s->chunk_len + s->query_len;
   const size_t n_cols = (size_t)(s->n_q_heads / s->n_kv_heads) * s->obs_window;
-  const size_t n_cb = (n_cols + 31) / 32, cg = (size_t)s->n_chunks * s->n_kv_heads;
-  const size_t kb = n_cb > PC_SC_WAVES ? many_kb_keys(s) : PC_SC_KB, n_kb = (L + kb - 1) / kb;
+  const size_t n_cb = (n_cols + 31) / 32, cg = (size_t)s->n_chunks * s->n_kv_heads, blocks = key_blocks_room(s, n_cb);
   PcScoreWs w;
   size_t off = 0;
-  w.ml = off;      off = pc_align_up(off + cg * n_kb * n_cols * sizeof(float2), 256);
+  w.ml = off;      off = pc_align_up(off + blocks * n_cols * sizeof(float2), 256);
   w.lse2 = off;    off = pc_align_up(off + cg * n_cb * 32 * sizeof(float), 256);
-  w.blk_sum = off; off = pc_align_up(off + cg * n_kb * sizeof(float), 256);
+  w.blk_sum = off; off = pc_align_up(off + blocks * sizeof(float), 256);
   w.q_split = off; off += n_cb > PC_SC_WAVES ? cg * n_cb * 32 * (size_t)s->head_dim * 2 * 2 : 0;
   w.total = off;
   return w;
