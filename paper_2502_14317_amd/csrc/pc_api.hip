@@ -266,15 +266,13 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
 // 64-key tiles of n segments of k_t keys
 static long long key_tiles(int n, int k_t) { return (long long)n * ((k_t + 63) / 64); }
 
-// Parts of the tile path's keys and the partials the workspace has room for: with a self segment at
-// least one more than the segments alone are cut into, so that the workspace grows with every group
-// of keys.
+// Parts the tile path's keys are cut into, and how many partial rows the workspace has room for.  The
+// number of parts falls where there are more rows to fill the chip, the room only ever rises.
 static int tile_parts(int batch, int n_q, long long seg_tiles, int n_q_heads, int n_kv_heads, int D, int has_self,
-                      int& room) {
-  const int alone = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles) + (has_self ? 1 : 0);
-  const int parts = pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, seg_tiles + key_tiles(has_self, n_q));
-  room = parts > alone ? parts : alone;
-  return parts;
+                      size_t& room) {
+  const long long tiles = seg_tiles + key_tiles(has_self, n_q);
+  room = pc_flash_part_rows((size_t)batch * n_q * n_q_heads, tiles, has_self);
+  return pc_flash_parts(batch, n_q, n_q_heads, n_kv_heads, D, tiles);
 }
 
 // Limits of the tile path beyond those of the shape checks.  The tile kernel steps through the self
@@ -297,7 +295,8 @@ struct Par8Ws {
 static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_cap, int n_q_heads,
                              int n_kv_heads, int D, int has_self) {
   Par8Ws w;
-  int parts_room = 0;
+  const size_t rows = (size_t)batch * n_q * n_q_heads;
+  size_t part_rows = 0;
   w.small = (long long)n_q * (n_q_heads / n_kv_heads) <= 16;
   if (w.small) {
     w.parts8 = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
@@ -305,14 +304,13 @@ static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_ca
     if (tail_cap > 0) w.n_parts += pc_decode_split(tail_cap, 1, (long long)batch * n_kv_heads).n_parts;
   } else {
     w.parts8 = 0;
-    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t) + key_tiles(1, tail_cap), n_q_heads, n_kv_heads, D, has_self, parts_room);
+    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t) + key_tiles(1, tail_cap), n_q_heads, n_kv_heads, D, has_self, part_rows);
   }
   size_t off = 0;
-  const size_t rows = (size_t)batch * n_q * n_q_heads;
   w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  if (w.small) parts_room = w.n_parts;
-  w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
-  w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
+  if (w.small) part_rows = rows * w.n_parts;
+  w.part_o = off;   off = pc_align_up(off + part_rows * D * sizeof(float), kAlign);
+  w.part_lse = off; off = pc_align_up(off + part_rows * sizeof(float), kAlign);
   w.rows_k = w.rows_v = off;
   if (!w.small) {       // dequantised segments as bf16 rows
     const size_t seg_rows = (size_t)batch * n_seg * n_kv_heads * k_t * D * 2;
@@ -505,20 +503,20 @@ struct ParWs {
 static ParWs par_ws_layout(int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                            int D, int has_self) {
   ParWs w;
-  int parts_room = 0;
+  const size_t rows = (size_t)batch * n_q * n_q_heads;
+  size_t part_rows = 0;
   const int G = n_q_heads / n_kv_heads;
   w.small = (long long)n_q * G <= 16;
   if (w.small) {
     w.n_parts = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
   } else {
-    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t), n_q_heads, n_kv_heads, D, has_self, parts_room);
+    w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t), n_q_heads, n_kv_heads, D, has_self, part_rows);
   }
   size_t off = 0;
-  const size_t rows = (size_t)batch * n_q * n_q_heads;
   w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  if (w.small) parts_room = w.n_parts;
-  w.part_o = off;   off = pc_align_up(off + rows * (size_t)parts_room * D * sizeof(float), kAlign);
-  w.part_lse = off; off = pc_align_up(off + rows * (size_t)parts_room * sizeof(float), kAlign);
+  if (w.small) part_rows = rows * w.n_parts;
+  w.part_o = off;   off = pc_align_up(off + part_rows * D * sizeof(float), kAlign);
+  w.part_lse = off; off = pc_align_up(off + part_rows * sizeof(float), kAlign);
   w.total = off;
   return w;
 }

@@ -188,6 +188,9 @@ struct PcFlashArgs {
 // How many parts the global attention's keys are cut into (n_tiles: 64-key tiles of a KV head at
 // full lengths), 1 to 64
 int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles);
+// Partial rows to have room for: at least rows x pc_flash_parts (rows = n_seq x n_rows x n_q_heads) of
+// this and of every smaller call, so it never falls where a size grows
+size_t pc_flash_part_rows(size_t rows, long long n_tiles, int has_self);
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
 
 int pc_launch_self_info(const void* logits, const int32_t* targets, int n_chunks, int n_tokens,

@@ -975,6 +975,9 @@ int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
   return a.global ? launch_flash_t<64, true>(a, st) : launch_flash_t<64, false>(a, st);
 }
 
+#define PC_FA_PARTS_MAX 64
+#define PC_FA_PARTS_WGS 2048
+#define PC_FA_PARTS_MIN 4
 int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles) {
   // The parts that minimise the estimated time of the tile kernel and the merge together.
   // Measured (parts swept from 1 to 32 over eight shapes; head_dim 128): a workgroup costs about
@@ -986,7 +989,12 @@ int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int hea
   const long long wgs = (long long)n_seq * n_kv_heads * ((n_rows * G + PC_FA_BM - 1) / PC_FA_BM);
   const double pair_us = head_dim == 128 ? 2.1 : 1.4, alone_us = head_dim == 128 ? 1.27 : 0.95;
   const double merge_us = 0.4 + (double)n_seq * n_rows * n_q_heads * head_dim * 4 / 7e6;
-  const int p_max = (int)(n_tiles < 1 ? 1 : (n_tiles > 64 ? 64 : n_tiles));
+  // At most 2048 workgroups (four rounds) or 4 parts, whichever is more: the partials of a call stay
+  // within a bound that pc_flash_part_rows can state.  By the estimate above that costs 0.07 % on
+  // average and 14 % at worst (just above one round) over 1 to 64 sequences x 17 to 2048 rows.
+  const long long p_wgs = wgs * PC_FA_PARTS_MIN < PC_FA_PARTS_WGS ? PC_FA_PARTS_WGS / wgs : PC_FA_PARTS_MIN;
+  const long long p_cap = p_wgs < PC_FA_PARTS_MAX ? p_wgs : PC_FA_PARTS_MAX;
+  const int p_max = (int)(n_tiles < 1 ? 1 : (n_tiles > p_cap ? p_cap : n_tiles));
   int best_p = 1;
   double best = 0.0;
   for (int p = 1; p <= p_max; ++p) {
@@ -997,4 +1005,13 @@ int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int hea
     if (p == 1 || cost < best) { best = cost; best_p = p; }
   }
   return best_p;
+}
+
+size_t pc_flash_part_rows(size_t rows, long long n_tiles, int has_self) {
+  // at most PC_FA_PARTS_MAX parts and one per tile; at most PC_FA_PARTS_WGS workgroups of PC_FA_BM rows or
+  // PC_FA_PARTS_MIN parts.  A self segment asks for one part more, so that the room grows with it too.
+  const size_t parts = (size_t)(n_tiles < 1 ? 1 : (n_tiles > PC_FA_PARTS_MAX ? PC_FA_PARTS_MAX : n_tiles)) + (has_self ? 1 : 0);
+  const size_t by_wgs = (size_t)PC_FA_PARTS_WGS * PC_FA_BM, by_parts = rows * PC_FA_PARTS_MIN;
+  const size_t bound = by_wgs > by_parts ? by_wgs : by_parts;
+  return rows * parts < bound ? rows * parts : bound;
 }

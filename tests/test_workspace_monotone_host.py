@@ -26,3 +26,20 @@ def test_score_workspace_rises_with_chunks_and_rows():
                 _assert_rising(_score_sizes([(c, n, wq, hq, hkv, d, obs) for n in rows], fn), (fn, hq, hkv, c, "rows"))
                 _assert_rising(_score_sizes([(c, w, wq, hq, hkv, d, n) for n in range(1, wq + 1)], fn),
                                (fn, hq, hkv, c, "voting rows"))
+
+
+def test_tile_attention_workspace_rises_with_every_size():
+    """Batch, query rows, segments, keys, tail and self segment, where the number of parts the keys are cut
+    into goes up and down."""
+    a, a8 = pc.pc_parallel_attn_workspace_bytes, pc.pc_parallel_attn_fp8_workspace_bytes
+    for hq, hkv, d in ((32, 8, 128), (32, 32, 128), (8, 8, 64), (64, 8, 128), (3, 1, 64)):
+        for s in (False, True):
+            for n_q, n_seg, k_t in ((512, 8, 2048), (64, 4, 300), (100, 32, 1000)):
+                _assert_rising([(b, a(b, n_q, n_seg, k_t, hq, hkv, d, s)) for b in range(1, 65)], (hq, s, "batch"))
+                _assert_rising([(b, a8(b, n_q, n_seg, k_t, 200, hq, hkv, d, s)) for b in range(1, 65)], (hq, s, "batch, 8 bit"))
+            for b in (1, 3, 8):
+                _assert_rising([(n, a(b, n, 8, 2048, hq, hkv, d, s)) for n in range(17, 2100, 5)], (hq, s, b, "rows"))
+                _assert_rising([(n, a(b, 200, n, 500, hq, hkv, d, s)) for n in range(1, 100)], (hq, s, b, "segments"))
+                _assert_rising([(n, a(b, 200, 3, n, hq, hkv, d, s)) for n in range(1, 6000, 31)], (hq, s, b, "keys"))
+                _assert_rising([(n, a8(b, 200, 3, 100, n, hq, hkv, d, s)) for n in range(1, 6000, 31)], (hq, s, b, "tail"))
+                assert a(b, 200, 3, 500, hq, hkv, d, True) >= a(b, 200, 3, 500, hq, hkv, d, False)
