@@ -265,9 +265,17 @@ int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, 
   return PC_OK;
 }
 
-// One launch: the workgroups of the 8-bit segments first (one per CU where the shapes allow), those of
-// the 16-bit tail behind them, next to which they find room: the tail, a few per cent of the bytes,
-// costs no launch, ramp and drain of its own.
+// The 16-bit tail can ride in the launch of the 8-bit segments, its workgroups behind theirs: the tail, a
+// few per cent of the bytes, then costs no launch, ramp and drain of its own.  A kernel takes the larger
+// register count of the two functions and the sum of their LDS, and beyond 4 columns the 16-bit function
+// (P V on the vector ALUs, 8 accumulators per column and lane) needs so many that the 8-bit workgroups
+// lose the second one on their CU (head_dim 128: 308 and 439 registers against 204 and 206, 83 KB of
+// LDS against 37).  So with more columns the tail rides only where no CU has a second 8-bit workgroup to
+// lose.  Measured, 8 x 2048 or 8 x 1024 keys and a tail of 512 or 256, one launch / two (us): 64 / 8
+// heads, 4 sequences (256 workgroups) 60 / 62, 16 (256) 183 / 186; 33 sequences (264 groups) 373 / 278,
+// 65 541 / 344, 100 417 / 376; 16 / 1 heads, 200 sequences 275 / 183; head_dim 64, 64 / 4 heads, 130
+// sequences 486 / 227.
+#define PC_D8_TAIL_WGS 256
 template <int D, int NQ>
 __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid) {
   constexpr int KSTEPS = D / 32;            // MFMA k-steps; a lane owns 8 KSTEPS = D / 4 bytes of each of its K rows
@@ -485,26 +493,38 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
 }
 
 template <int D, int NQ>
-__global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(PcDecode8Args a, PcDecodeArgs tail,
-                                                                                int n_wg8) {
+__global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(PcDecode8Args a) {
+  decode8_workgroup<D, NQ>(a, blockIdx.x);
+}
+template <int D, int NQ>
+__global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_tail_kernel(PcDecode8Args a, PcDecodeArgs tail,
+                                                                                     int n_wg8) {
   static_assert(PC_D8_WAVES == PC_DEC_WAVES, "one workgroup size");
   if ((int)blockIdx.x < n_wg8) decode8_workgroup<D, NQ>(a, blockIdx.x);
   else pc_decode_workgroup<D, NQ>(tail, blockIdx.x - n_wg8);
 }
 
-template <int D>
-static int launch_decode8_d(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, int nq_pad, hipStream_t st) {
+// tail: rides in the launch, unless its parts_grid is 0
+template <int D, int NQ>
+static int launch_decode8_t(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, hipStream_t st) {
   const long long groups = (long long)batch * a.n_kv_heads;
   const long long n_wg8 = groups * a.parts_grid, blocks = n_wg8 + groups * tail.parts_grid;
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   dim3 grid((unsigned)blocks), block(PC_D8_WAVES * PC_WAVE);
   PcProfScope prof(PC_KERNEL_DECODE_FP8, st);
-  if (nq_pad == 4) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 4>), grid, block, 0, st, a, tail, (int)n_wg8);
-  else if (nq_pad == 8) hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 8>), grid, block, 0, st, a, tail, (int)n_wg8);
-  else hipLaunchKernelGGL((decode_attn_fp8_kernel<D, 16>), grid, block, 0, st, a, tail, (int)n_wg8);
+  if (tail.parts_grid > 0)
+    hipLaunchKernelGGL((decode_attn_fp8_tail_kernel<D, NQ>), grid, block, 0, st, a, tail, (int)n_wg8);
+  else
+    hipLaunchKernelGGL((decode_attn_fp8_kernel<D, NQ>), grid, block, 0, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
+}
+template <int D>
+static int launch_decode8_d(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, int nq_pad, hipStream_t st) {
+  if (nq_pad == 4) return launch_decode8_t<D, 4>(a, tail, batch, st);
+  if (nq_pad == 8) return launch_decode8_t<D, 8>(a, tail, batch, st);
+  return launch_decode8_t<D, 16>(a, tail, batch, st);
 }
 
 int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
@@ -524,10 +544,15 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
   a.parts_grid = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
   a.n_parts = n_parts;
   a.scale_log2 = scale * PC_D8_LOG2E;
-  const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_cap > 0 ? 1 : 0,
-                                           tail_cap > 0 ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
-                                           n_parts, a.parts_grid);
   const int nq_pad = cols <= 4 ? 4 : (cols <= 8 ? 8 : 16);
-  return head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, nq_pad, st)
-                         : launch_decode8_d<64>(a, tail, batch, nq_pad, st);
+  const long long n_wg8 = (long long)batch * n_kv_heads * a.parts_grid;
+  const bool tail_here = tail_cap > 0 && (nq_pad == 4 || n_wg8 <= PC_D8_TAIL_WGS);
+  const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_here ? 1 : 0,
+                                           tail_here ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
+                                           n_parts, a.parts_grid);
+  const int rc = head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, nq_pad, st)
+                                 : launch_decode8_d<64>(a, tail, batch, nq_pad, st);
+  if (rc != PC_OK || tail_cap == 0 || tail_here) return rc;
+  return pc_launch_decode(q, pos0, base, k_tail, v_tail, tail_len, 0, batch, n_q, 1, tail_cap, n_q_heads, n_kv_heads,
+                          head_dim, scale, part_o, part_lse, n_parts, a.parts_grid, st);
 }

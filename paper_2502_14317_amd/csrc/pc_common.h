@@ -318,7 +318,7 @@ int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg
 int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
                           long long n_segs, int k_t, int head_dim, void* k_rows, void* v_rows,
                           hipStream_t st);
-// Partials of the 8-bit segments, then those of the 16-bit tail (tail_cap > 0), in one launch
+// Partials of the 8-bit segments, then those of the 16-bit tail (tail_cap > 0)
 int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
                          const float* k_scale, const float* v_scale, const int32_t* seg_len,
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
