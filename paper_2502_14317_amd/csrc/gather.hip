@@ -2,11 +2,16 @@
 //
 // HBM-bound byte copy.  One head row is D bf16 = 128 or 256 bytes; a lane moves one 16-byte
 // piece of a K row and the matching piece of the V row, so D/8 adjacent lanes read one
-// contiguous row and a wavefront writes 1 KiB of contiguous destination per store.  A workgroup
+// contiguous row and a wavefront writes 1 KiB of contiguous destination per store.  A wavefront
 // stays inside one destination segment (b, s, g), so that everything but the token index is a
 // scalar; a thread handles UNROLL rows, so that several independent loads are in flight (4, or 1
 // where that leaves CUs without a workgroup).  Both sides are touched once, so loads and stores
 // carry the non-temporal hint (64 -> 70 % of peak).
+// Measured with 64 x 16 x 8 segments of k rows, segments packed row by row / a workgroup (64 rows of 128
+// values) inside one segment / a wavefront inside one (us): k = 1 7.6 / 9.7 / 6.3, 65 98 / 130 / 96, 100
+// 147 / 172 / 147, 128 201 / 198 / 195; rows of 64 values, k = 129 99 / 147 / 98, 200 148 / 189 / 147; with
+// the maxima k = 65 2197 / 136 / 99 (packed, a row updates its segment by itself).  A workgroup whose rows
+// end just behind a segment's multiple is all but idle, and packed rows cost four divisions each.
 #include "pc_common.h"
 
 // largest bf16 magnitude (15-bit pattern) among the 8 values of a 16-byte piece
@@ -28,12 +33,14 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(
     const uint4* __restrict__ k_src, const uint4* __restrict__ v_src,
     const int32_t* __restrict__ chunk_idx, const int32_t* __restrict__ tok_idx,
     uint4* __restrict__ k_dst, uint4* __restrict__ v_dst,
-    int n_chunks, int rows, int n_sel, int n_kv_heads, int k, unsigned blocks_per_seg,
+    int n_chunks, int rows, int n_sel, int n_kv_heads, int k, unsigned units_per_seg, unsigned n_units,
     uint32_t* __restrict__ k_amax, uint32_t* __restrict__ v_amax) {
-  constexpr int ROWS = 256 / LANES_PER_ROW;                     // rows of a workgroup per step
+  constexpr int ROWS = PC_WAVE / LANES_PER_ROW;                 // rows of a wavefront per step
   const int piece = threadIdx.x % LANES_PER_ROW;
-  const unsigned bsg = blockIdx.x / blocks_per_seg;             // ((b * n_sel + s) * H_kv + g)
-  const int first = (int)(blockIdx.x % blocks_per_seg) * (ROWS * UNROLL) + (int)threadIdx.x / LANES_PER_ROW;
+  const unsigned unit = blockIdx.x * 4 + (unsigned)__builtin_amdgcn_readfirstlane((int)threadIdx.x / PC_WAVE);
+  if (unit >= n_units) return;
+  const unsigned bsg = unit / units_per_seg;                    // ((b * n_sel + s) * H_kv + g)
+  const int first = (int)(unit % units_per_seg) * (ROWS * UNROLL) + (int)(threadIdx.x % PC_WAVE) / LANES_PER_ROW;
   const int g = (int)(bsg % (unsigned)n_kv_heads);
   const unsigned bs = bsg / (unsigned)n_kv_heads;
   const int s = (int)(bs % (unsigned)n_sel), b = (int)(bs / (unsigned)n_sel);
@@ -105,17 +112,17 @@ int pc_launch_gather(const void* k_src, const void* v_src, const int32_t* chunk_
   }
   const int lanes = head_dim / 8;
   const long long n_segs = (long long)batch * n_sel * n_kv_heads;
-  const int step = 256 / lanes;                                 // rows of a workgroup per step
-  const int unroll = n_segs * ((k + 4 * step - 1) / (4 * step)) < 512 ? 1 : 4;
-  const long long blocks_per_seg = (k + (long long)unroll * step - 1) / (unroll * step);
-  const long long blocks = n_segs * blocks_per_seg;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
-  dim3 grid((unsigned)blocks), block(256);
+  const int step = PC_WAVE / lanes;                             // rows of a wavefront per step
+  const int unroll = n_segs * ((k + 4 * step - 1) / (4 * step)) < 4 * 512 ? 1 : 4;
+  const long long units_per_seg = (k + (long long)unroll * step - 1) / (unroll * step);
+  const long long units = n_segs * units_per_seg;               // wavefronts
+  if (units > 0xffffffffLL) return PC_ERR_SHAPE;
+  dim3 grid((unsigned)((units + 3) / 4)), block(256);
   PcProfScope prof(PC_KERNEL_GATHER, st);
 #define PC_GATHER_LAUNCH(LANES, AMAX, UNROLL)                                                        \
   hipLaunchKernelGGL((gather_kv_kernel<LANES, AMAX, UNROLL>), grid, block, 0, st, (const uint4*)k_src, \
                      (const uint4*)v_src, chunk_idx, tok_idx, (uint4*)k_dst, (uint4*)v_dst, n_chunks, \
-                     rows, n_sel, n_kv_heads, k, (unsigned)blocks_per_seg, (uint32_t*)k_amax, (uint32_t*)v_amax)
+                     rows, n_sel, n_kv_heads, k, (unsigned)units_per_seg, (unsigned)units, (uint32_t*)k_amax, (uint32_t*)v_amax)
 #define PC_GATHER_PICK(LANES)                                                                        \
   if (amax) { if (unroll == 4) PC_GATHER_LAUNCH(LANES, true, 4); else PC_GATHER_LAUNCH(LANES, true, 1); } \
   else { if (unroll == 4) PC_GATHER_LAUNCH(LANES, false, 4); else PC_GATHER_LAUNCH(LANES, false, 1); }
