@@ -263,6 +263,16 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
                                    k_amax, v_amax, k8, v8, k_scale, v_scale, (hipStream_t)stream);
 }
 
+// Few query rows: rotated by the split-KV kernel itself, which saves a launch but puts the fp64 exp and
+// sincos (some 5 us) in front of every workgroup, or by rope_q_kernel first.  First where the merge needs
+// the rows too (self segment), and beyond 512 workgroups, of which two share a CU: those of later rounds
+// pay it again.  Measured, 16-bit / 8-bit cache, 8 x 1024 keys, kernel itself -> first (us): 32 / 8 heads, 1
+// sequence 16.0 -> 17.5 / 16.4 -> 17.4, 64 (512 workgroups) 338 -> 340 / 180 -> 180, 33 (264 groups in many
+// parts) 230 -> 214 / 150 -> 136, 65 446 -> 414 / 279 -> 253; 24 / 8 heads of 64, 65 sequences 238 -> 209 /
+// 158 -> 125; 16 / 1 heads, 300 sequences 1065 -> 914 / 424 -> 334.
+#define PC_DEC_ROT_WGS 512
+static bool rotate_first(int has_self, long long workgroups) { return has_self || workgroups > PC_DEC_ROT_WGS; }
+
 // 64-key tiles of n segments of k_t keys
 static long long key_tiles(int n, int k_t) { return (long long)n * ((k_t + 63) / 64); }
 
@@ -389,10 +399,9 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
                                    tail_len, tail_cap, k_self, v_self, batch, n_q, n_seg, k_t, n_q_heads,
                                    n_kv_heads, D, q_pos0, rope_base, scale, out, lse_out, w, base, st);
   }
-  // the kernels rotate the query rows themselves, unless the merge needs them too (self segment)
   const void* q_in = q;
   int pos0 = q_pos0;
-  if (q_pos0 >= 0 && has_self) {
+  if (q_pos0 >= 0 && rotate_first(has_self, (long long)batch * n_kv_heads * w.parts8)) {
     rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
     if (rc != PC_OK) return rc;
     q_in = base + w.q_rot; pos0 = -1;
@@ -615,11 +624,10 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
   float* part_lse = (float*)(base + w.part_lse);
 
   if (w.small) {
-    // split-KV path: the kernel rotates the query rows itself (the scale is applied to the fp32
-    // logits), unless the merge needs them too (self segment)
+    // split-KV path (the scale is applied to the fp32 logits)
     const void* q_in = q;
     int pos0 = q_pos0;
-    if (q_pos0 >= 0 && has_self) {
+    if (q_pos0 >= 0 && rotate_first(has_self, (long long)batch * n_kv_heads * w.n_parts)) {
       rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
       if (rc != PC_OK) return rc;
       q_in = base + w.q_rot; pos0 = -1;
