@@ -4,14 +4,16 @@
 // piece of a K row and the matching piece of the V row, so D/8 adjacent lanes read one
 // contiguous row and a wavefront writes 1 KiB of contiguous destination per store.  A wavefront
 // stays inside one destination segment (b, s, g), so that everything but the token index is a
-// scalar; a thread handles UNROLL rows, so that several independent loads are in flight (4, or 1
-// where that leaves CUs without a workgroup).  Both sides are touched once, so loads and stores
+// scalar; a thread handles UNROLL rows, so that several independent loads are in flight (4; 2 where
+// the last of a segment's wavefronts would idle for more than an eighth of its rows; 1 where 4 leave
+// CUs without a workgroup).  Both sides are touched once, so loads and stores
 // carry the non-temporal hint (64 -> 70 % of peak).
 // Measured with 64 x 16 x 8 segments of k rows, segments packed row by row / a workgroup (64 rows of 128
-// values) inside one segment / a wavefront inside one (us): k = 1 7.6 / 9.7 / 6.3, 65 98 / 130 / 96, 100
-// 147 / 172 / 147, 128 201 / 198 / 195; rows of 64 values, k = 129 99 / 147 / 98, 200 148 / 189 / 147; with
-// the maxima k = 65 2197 / 136 / 99 (packed, a row updates its segment by itself).  A workgroup whose rows
-// end just behind a segment's multiple is all but idle, and packed rows cost four divisions each.
+// values) inside one segment / a wavefront inside one (us): k = 1 7.6 / 9.7 / 6.3, 65 99 / 130 / 94, 100
+// 147 / 172 / 147, 128 201 / 198 / 195; rows of 64 values, k = 100 78 / 84 / 73, 129 99 / 147 / 93, 200 148 /
+// 189 / 147; with the maxima k = 65 2197 / 136 / 99 (packed, a row updates its segment by itself).  A
+// workgroup whose rows end just behind a segment's multiple is all but idle, and packed rows cost four
+// divisions each.
 #include "pc_common.h"
 
 // largest bf16 magnitude (15-bit pattern) among the 8 values of a 16-byte piece
@@ -113,7 +115,8 @@ int pc_launch_gather(const void* k_src, const void* v_src, const int32_t* chunk_
   const int lanes = head_dim / 8;
   const long long n_segs = (long long)batch * n_sel * n_kv_heads;
   const int step = PC_WAVE / lanes;                             // rows of a wavefront per step
-  const int unroll = n_segs * ((k + 4 * step - 1) / (4 * step)) < 4 * 512 ? 1 : 4;
+  int unroll = n_segs * ((k + 4 * step - 1) / (4 * step)) < 4 * 512 ? 1 : 4;
+  if (unroll == 4 && (k + 4LL * step - 1) / (4 * step) * (4 * step) * 8 > k * 9LL) unroll = 2;
   const long long units_per_seg = (k + (long long)unroll * step - 1) / (unroll * step);
   const long long units = n_segs * units_per_seg;               // wavefronts
   if (units > 0xffffffffLL) return PC_ERR_SHAPE;
@@ -124,8 +127,8 @@ int pc_launch_gather(const void* k_src, const void* v_src, const int32_t* chunk_
                      (const uint4*)v_src, chunk_idx, tok_idx, (uint4*)k_dst, (uint4*)v_dst, n_chunks, \
                      rows, n_sel, n_kv_heads, k, (unsigned)units_per_seg, (unsigned)units, (uint32_t*)k_amax, (uint32_t*)v_amax)
 #define PC_GATHER_PICK(LANES)                                                                        \
-  if (amax) { if (unroll == 4) PC_GATHER_LAUNCH(LANES, true, 4); else PC_GATHER_LAUNCH(LANES, true, 1); } \
-  else { if (unroll == 4) PC_GATHER_LAUNCH(LANES, false, 4); else PC_GATHER_LAUNCH(LANES, false, 1); }
+  if (amax) { if (unroll == 4) PC_GATHER_LAUNCH(LANES, true, 4); else if (unroll == 2) PC_GATHER_LAUNCH(LANES, true, 2); else PC_GATHER_LAUNCH(LANES, true, 1); } \
+  else { if (unroll == 4) PC_GATHER_LAUNCH(LANES, false, 4); else if (unroll == 2) PC_GATHER_LAUNCH(LANES, false, 2); else PC_GATHER_LAUNCH(LANES, false, 1); }
   if (lanes == 16) { PC_GATHER_PICK(16) } else { PC_GATHER_PICK(8) }
 #undef PC_GATHER_PICK
 #undef PC_GATHER_LAUNCH

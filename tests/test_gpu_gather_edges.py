@@ -1,5 +1,5 @@
-"""The gather at the edges of its units (a wavefront takes 4 or 16 rows of 128 values, 8 or 32 of 64, of
-one segment): bit for bit against the rule written out in numpy, maxima included, with skipped segments, token indices
+"""The gather at the edges of its units (a wavefront takes 4, 8 or 16 rows of 128 values, 8, 16 or 32 of 64,
+of one segment): bit for bit against the rule written out in numpy, maxima included, with skipped segments, token indices
 outside the source and buffers pre-filled to show stray writes."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ from helpers import bits_to_dev, dev_to_bits
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,S,Hkv", [(1, 3, 1), (40, 15, 4)], ids=["few segments", "many segments"])   # 1 and 4 rows a thread
+@pytest.mark.parametrize("B,S,Hkv", [(1, 3, 1), (40, 15, 4)], ids=["few segments", "many segments"])   # 1, and 2 or 4, rows a thread
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("k", [1, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33, 65])
 def test_gather_unit_edges(B, S, Hkv, D, k):
