@@ -656,8 +656,8 @@ def main():
         step()
     torch.cuda.synchronize()
     # Timed region: only the roofline kernel's launches are bracketed by HIP events (on the
-    # launch stream, inside the library); bracketing all fourteen kernels of a step costs the
-    # step 0.19 ms of event records.  The per-kernel breakdown comes from a second, untimed pass.
+    # launch stream, inside the library); bracketing all ten kernels of a step costs the step
+    # more than 0.1 ms of event records.  The per-kernel breakdown comes from a second, untimed pass.
     pc.pc_profile_begin("flash_fwd_kernel")
     t0 = time.perf_counter()
     for _ in range(args.steps):
@@ -675,7 +675,7 @@ def main():
     for name, ms in pc.pc_profile_records():
         per_kernel.setdefault(name, []).append(ms)
     per_kernel["flash_fwd_kernel"] = flash_all
-    # flash_fwd_kernel runs once per step for the local attention and (full path) twice more in
+    # flash_fwd_kernel runs once per step for the local attention and (full path) once more for
     # the global attention; the local-attention launch is the first one of every step
     n_flash = len(per_kernel["flash_fwd_kernel"]) // args.steps
     flash_ms = per_kernel["flash_fwd_kernel"][0::n_flash]

@@ -74,6 +74,7 @@ typedef struct pc_shape {
  *          follow the context directly, at positions chunk_lens[c] + t.  Rows behind a short
  *          sequence are padding: o and lse there are not written, tok_score of the missing
  *          tokens is 0, k_rope there is unspecified.  NULL => every chunk has w rows.
+ * A workspace also serves calls with fewer chunks, rows or voting rows of the same heads.
  * Arithmetic: bf16 MFMA products, fp32 softmax and accumulation.  The operands are the rotated
  * k rounded to bf16 (the cache's precision) and the rotated q multiplied by scale * log2(e) in
  * fp32 and then rounded to bf16, once; probabilities are rounded to bf16 for the second product.
@@ -188,7 +189,8 @@ int pc_gather_kv(const void* k_src, const void* v_src, const int32_t* chunk_idx,
  * segments and, optionally, the causal self segment of the query's own keys:
  *   out[b, t, h, :] = softmax over { kc[b, s, g, 0:seg_len[b,s]] for all s } U
  *                                  { k_self[b, 0..t, g] } of q . k * scale, times the values.
- * Computed as independent per-segment (and per-split) softmaxes merged exactly by logsumexp:
+ * One softmax over all of them.  The keys may be cut into parts, whatever the segments' borders,
+ * whose softmaxes are merged exactly by logsumexp:
  *   LSE = log sum_p exp(lse_p),  out = sum_p exp(lse_p - LSE) o_p.
  *   q [B, n_q, H_q, D] bf16; if q_pos0 >= 0 it is rotated here at positions q_pos0 + t,
  *     if q_pos0 < 0 it is taken as already rotated.
@@ -200,9 +202,11 @@ int pc_gather_kv(const void* k_src, const void* v_src, const int32_t* chunk_idx,
  *   out [B, n_q, H_q, D] bf16;  lse_out [B, H_q, n_q] fp32, nullable.
  * n_q * (H_q / H_kv) <= 16 runs the HBM-bound split-KV kernel (bf16 operands as given, scale
  * applied to the fp32 logits); larger n_q the MFMA tile kernel, whose query operand is the rotated
- * q times scale * log2(e), rounded to bf16 once when q_pos0 >= 0 (a q that arrives rotated,
- * q_pos0 < 0, is scaled and rounded a second time).
- * Workspace: pc_parallel_attn_workspace_bytes(...). */
+ * q times scale * log2(e) (rotation and product in 64 bits), rounded to bf16 once when q_pos0 >= 0
+ * (a q that arrives rotated, q_pos0 < 0, is scaled and rounded a second time).  The tile kernel
+ * takes up to 65535 KV heads with a self segment and 65535 64-key tiles a segment (PC_ERR_SHAPE).
+ * Workspace: pc_parallel_attn_workspace_bytes(...).  With n_q * (H_q / H_kv) > 16 a workspace also
+ * serves every such call with the same heads and no larger batch, n_q, n_seg and k_t. */
 int pc_parallel_attn(const void* q, const void* kc, const void* vc, const int32_t* seg_len,
                      int32_t seg_len_per_head, const void* k_self, const void* v_self, int32_t batch, int32_t n_q,
                      int32_t n_seg, int32_t k_t, int32_t n_q_heads, int32_t n_kv_heads,

@@ -19,8 +19,9 @@
 //   pass 2  (S = Q K^T, a lane owns a key)           recompute the logits, p = exp2(s - lse)
 //           and sum p over the columns (voting rows x heads of the group) for each key
 //           -> tok_score
-// Pass 2 also leaves the sum of its tok_score block; a last kernel adds those per chunk in a
-// fixed order (deterministic) -> chunk_score.
+// Pass 2 also leaves the sum of its tok_score block; those are added per chunk in a fixed order
+// (deterministic) -> chunk_score, by a last kernel in the standalone call and by workgroups of the
+// attention launch that follows in the prefill call.
 //
 // Fused K/V pre-pass.  Inside pc_chunk_prefill_attn pass 1 takes over the work of
 // kv_prepass_kernel (switched on by its output pointers): it already reads every key row once and rotates it in
