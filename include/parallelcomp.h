@@ -74,7 +74,8 @@ typedef struct pc_shape {
  *          follow the context directly, at positions chunk_lens[c] + t.  Rows behind a short
  *          sequence are padding: o and lse there are not written, tok_score of the missing
  *          tokens is 0, k_rope there is unspecified.  NULL => every chunk has w rows.
- * A workspace also serves calls with fewer chunks, rows or voting rows of the same heads.
+ * A workspace also serves calls with fewer chunks, rows or voting rows of the same heads (so does
+ * that of pc_chunk_query_scores).
  * Arithmetic: bf16 MFMA products, fp32 softmax and accumulation.  The operands are the rotated
  * k rounded to bf16 (the cache's precision) and the rotated q multiplied by scale * log2(e) in
  * fp32 and then rounded to bf16, once; probabilities are rounded to bf16 for the second product.
@@ -206,7 +207,7 @@ int pc_gather_kv(const void* k_src, const void* v_src, const int32_t* chunk_idx,
  * (a q that arrives rotated, q_pos0 < 0, is scaled and rounded a second time).  The tile kernel
  * takes up to 65535 KV heads with a self segment and 65535 64-key tiles a segment (PC_ERR_SHAPE).
  * Workspace: pc_parallel_attn_workspace_bytes(...).  With n_q * (H_q / H_kv) > 16 a workspace also
- * serves every such call with the same heads and no larger batch, n_q, n_seg and k_t. */
+ * serves every such call with the same heads and no larger batch, n_q, n_seg, k_t and has_self. */
 int pc_parallel_attn(const void* q, const void* kc, const void* vc, const int32_t* seg_len,
                      int32_t seg_len_per_head, const void* k_self, const void* v_self, int32_t batch, int32_t n_q,
                      int32_t n_seg, int32_t k_t, int32_t n_q_heads, int32_t n_kv_heads,
