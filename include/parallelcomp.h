@@ -236,6 +236,34 @@ int pc_kv_append(const void* k_new, const void* v_new, int32_t batch, int32_t n_
                  float rope_base, void* kc, void* vc, int32_t* seg_len, int32_t seg_len_per_head,
                  void* stream);
 
+/* One decoding step: pc_kv_append of one token to the last segment (seg = n_seg - 1), then
+ * pc_parallel_attn of its query row over all n_seg segments, the new token included, in two launches:
+ * the attention kernel stores the new row and the merge takes it as one more key (its logit in fp32)
+ * and counts it in seg_len.  Arguments, layouts, effects on kc, vc and seg_len and errors are those of
+ * the two calls (every check before any launch):
+ *   q [B, 1, H_q, D], k_new, v_new [B, 1, H_kv, D] before RoPE, rotated at `pos` (pos < 0: they arrive
+ *   rotated); seg_len as there, required.  A token that does not fit is dropped and not attended.
+ * More than 16 query heads per KV head run pc_kv_append and the tile kernel.
+ * Workspace: pc_decode_step_workspace_bytes(...). */
+int pc_decode_step(const void* q, const void* k_new, const void* v_new, int32_t batch, int32_t n_seg,
+                   int32_t k_t, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t pos,
+                   float rope_base, float softmax_scale, void* kc, void* vc, int32_t* seg_len,
+                   int32_t seg_len_per_head, void* out, float* lse_out, void* ws, size_t ws_bytes,
+                   void* stream);
+size_t pc_decode_step_workspace_bytes(int32_t batch, int32_t n_seg, int32_t k_t, int32_t n_q_heads,
+                                      int32_t n_kv_heads, int32_t head_dim);
+/* The same over the 8-bit cache: pc_kv_append to the 16-bit tail (a cache of one segment of tail_cap
+ * >= 1 rows), then pc_parallel_attn_fp8 of one query row over [8-bit segments ; tail]. */
+int pc_decode_step_fp8(const void* q, const void* k_new, const void* v_new, const void* k8, const void* v8,
+                       const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                       int32_t seg_len_per_head, void* k_tail, void* v_tail, int32_t* tail_len,
+                       int32_t tail_cap, int32_t batch, int32_t n_seg, int32_t k_t, int32_t n_q_heads,
+                       int32_t n_kv_heads, int32_t head_dim, int32_t pos, float rope_base,
+                       float softmax_scale, void* out, float* lse_out, void* ws, size_t ws_bytes,
+                       void* stream);
+size_t pc_decode_step_fp8_workspace_bytes(int32_t batch, int32_t n_seg, int32_t k_t, int32_t tail_cap,
+                                          int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim);
+
 /* ---- 8-bit compressed cache for the decoding stage (extension) -------------------------------
  * The paper leaves the precision of the cache open (its decoding stage, Eq. 9-11 with one query
  * row, reads the whole compressed cache per token: the ms/token column of its throughput table).

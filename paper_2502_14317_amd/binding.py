@@ -25,7 +25,8 @@ SYMBOLS = [
     "pc_kv_quantize_fp8", "pc_parallel_attn_fp8", "pc_parallel_attn_fp8_workspace_bytes",
     "pc_profile_begin_kernel", "pc_parallel_attn_static", "pc_parallel_attn_static_max_bytes",
     "pc_chunk_queue_update", "pc_gather_kv_amax", "pc_kv_quantize_fp8_amax",
-    "pc_copy_ceiling",
+    "pc_copy_ceiling", "pc_decode_step", "pc_decode_step_workspace_bytes", "pc_decode_step_fp8",
+    "pc_decode_step_fp8_workspace_bytes",
 ]
 
 
@@ -112,6 +113,15 @@ def lib():
     L.pc_parallel_attn_fp8.restype = c_int
     L.pc_parallel_attn_fp8_workspace_bytes.argtypes = [c_int32] * 9
     L.pc_parallel_attn_fp8_workspace_bytes.restype = c_size_t
+    L.pc_decode_step.argtypes = [P] * 3 + [c_int32] * 7 + [c_float, c_float, P, P, P, c_int32, P, P, P, c_size_t, P]
+    L.pc_decode_step.restype = c_int
+    L.pc_decode_step_workspace_bytes.argtypes = [c_int32] * 6
+    L.pc_decode_step_workspace_bytes.restype = c_size_t
+    L.pc_decode_step_fp8.argtypes = ([P] * 8 + [c_int32] + [P] * 3 + [c_int32] * 8 +
+                                     [c_float, c_float, P, P, P, c_size_t, P])
+    L.pc_decode_step_fp8.restype = c_int
+    L.pc_decode_step_fp8_workspace_bytes.argtypes = [c_int32] * 7
+    L.pc_decode_step_fp8_workspace_bytes.restype = c_size_t
     _lib = L
     return L
 
@@ -126,7 +136,7 @@ def _ptr(t):
 
 def _stream():
     # the handle of torch.cuda.current_stream() without the stream object around it: a decoding step of
-    # a short cache is bound by its two calls
+    # a short cache is bound by its call
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
@@ -264,6 +274,33 @@ def pc_kv_append(k_new, v_new, batch, n_new, n_seg, seg, k_t, n_kv_heads, head_d
     _check(lib().pc_kv_append(_ptr(k_new), _ptr(v_new), batch, n_new, n_seg, seg, k_t, n_kv_heads,
                               head_dim, pos0, rope_base, _ptr(kc), _ptr(vc), _ptr(seg_len),
                               seg_len_per_head, _stream()), "pc_kv_append")
+
+
+def pc_decode_step_workspace_bytes(batch, n_seg, k_t, n_q_heads, n_kv_heads, head_dim):
+    return int(lib().pc_decode_step_workspace_bytes(batch, n_seg, k_t, n_q_heads, n_kv_heads, head_dim))
+
+
+def pc_decode_step(q, k_new, v_new, batch, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, pos, rope_base,
+                   softmax_scale, kc, vc, seg_len, out, lse_out, ws, seg_len_per_head=0):
+    p, n = _ws(ws)
+    _check(lib().pc_decode_step(_ptr(q), _ptr(k_new), _ptr(v_new), batch, n_seg, k_t, n_q_heads, n_kv_heads,
+                                head_dim, pos, rope_base, softmax_scale, _ptr(kc), _ptr(vc), _ptr(seg_len),
+                                seg_len_per_head, _ptr(out), _ptr(lse_out), p, n, _stream()), "pc_decode_step")
+
+
+def pc_decode_step_fp8_workspace_bytes(batch, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, head_dim):
+    return int(lib().pc_decode_step_fp8_workspace_bytes(batch, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, head_dim))
+
+
+def pc_decode_step_fp8(q, k_new, v_new, k8, v8, k_scale, v_scale, seg_len, k_tail, v_tail, tail_len, tail_cap,
+                       batch, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, pos, rope_base, softmax_scale, out,
+                       lse_out, ws, seg_len_per_head=0):
+    p, n = _ws(ws)
+    _check(lib().pc_decode_step_fp8(_ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k8), _ptr(v8), _ptr(k_scale),
+                                    _ptr(v_scale), _ptr(seg_len), seg_len_per_head, _ptr(k_tail), _ptr(v_tail),
+                                    _ptr(tail_len), tail_cap, batch, n_seg, k_t, n_q_heads, n_kv_heads, head_dim,
+                                    pos, rope_base, softmax_scale, _ptr(out), _ptr(lse_out), p, n, _stream()),
+           "pc_decode_step_fp8")
 
 
 def pc_kv_quantize_fp8(kc, vc, seg_len, batch, n_seg, k_t, n_kv_heads, head_dim, k8, v8, k_scale,

@@ -21,106 +21,131 @@ __global__ __launch_bounds__(PC_DEC_WAVES * PC_WAVE) void decode_attn_kernel(PcD
 }
 
 // ------------------------------------------------------------------------------------------
-// Merge of partials (+ the causal self segment for the few-row path).  One workgroup of D
-// threads per (b, t, h).  lse values are natural logarithms.
+// Merge of partials (+ the causal self segment of the few-row path, or a decoding step's new token).  One
+// workgroup of 256 threads per (b, t, h): D / 4 threads take a partial, 4 values each, 8 (16) partials at a
+// time, under a running maximum of their own, and are put together at the end in a fixed order, so that
+// nothing waits for the logsumexps of all partials first.  lse values are natural logarithms.
+// Latency: decode_one's 32 partials 4.8 us with D threads a row and the weights in a pass of their own.
 struct PcMergeArgs {
   const float* part_o;     // [B, P, n_q, H_q, D]
   const float* part_lse;   // [B, P, n_q, H_q]
-  const uint16_t* q;       // rotated q, used only with the self segment
-  const uint16_t* k_self;  // [B, n_q, H_kv, D] or nullptr
+  const uint16_t* q;       // rotated q, used only with a self segment or a step
+  const uint16_t* k_self;  // [B, n_q, H_kv, D] or nullptr: row t sees keys 0 .. t
   const uint16_t* v_self;
+  PcMergeStep step;
   uint16_t* out;           // [B, n_q, H_q, D]
   float* lse_out;          // [B, H_q, n_q] or nullptr
   int n_q, n_q_heads, n_kv_heads, n_parts;
   float scale;
 };
 
-#define PC_MERGE_MAX_LDS_PARTS 1024      // weights of up to this many partials are kept in LDS
-
 template <int D>
-__global__ __launch_bounds__(D) void merge_kernel(PcMergeArgs a) {
-  __shared__ float red[D / PC_WAVE + 1];
-  __shared__ float self_s[16];
-  __shared__ float wgt_lds[PC_MERGE_MAX_LDS_PARTS];
-  const int d = threadIdx.x;
+__global__ __launch_bounds__(256) void merge_kernel(PcMergeArgs a) {
+  constexpr int TPR = D / 4, GROUPS = 256 / TPR, U = 4;
+  __shared__ floatx4 num_lds[GROUPS][TPR];
+  __shared__ float2 ml_lds[GROUPS];
+  const int grp = threadIdx.x / TPR, d4 = threadIdx.x % TPR * 4;
   int bid = blockIdx.x;
   const int h = bid % a.n_q_heads; bid /= a.n_q_heads;
   const int t = bid % a.n_q;       bid /= a.n_q;
   const int b = bid;
-  const int G = a.n_q_heads / a.n_kv_heads, g = h / G;
+  const int g = h / (a.n_q_heads / a.n_kv_heads);
   // partial p of this (b, t, h): row = row0 + p * row_stride
   const long long row0 = ((long long)b * a.n_parts * a.n_q + t) * a.n_q_heads + h;
   const long long row_stride = (long long)a.n_q * a.n_q_heads;
-  const bool in_lds = a.n_parts <= PC_MERGE_MAX_LDS_PARTS;
+  const long long orow = ((long long)b * a.n_q + t) * a.n_q_heads + h;
 
-  // the partials' logsumexps, one per thread and round (independent loads), and their maximum
-  float M = -INFINITY;
-  for (int p = d; p < a.n_parts; p += D) {
-    const float l = a.part_lse[row0 + p * row_stride];
-    if (in_lds) wgt_lds[p] = l;
-    M = fmaxf(M, l);
+  // keys of the launch's own: the self segment's first t + 1, or a step's one
+  const uint16_t* k_self = a.k_self;
+  const uint16_t* v_self = a.v_self;
+  long long self0 = ((long long)b * a.n_q * a.n_kv_heads + g) * D;
+  int n_self = k_self ? t + 1 : 0;
+  if (a.step.self_row) {
+    const int row = a.step.self_row[b * a.n_kv_heads + g];
+    k_self = a.step.k; v_self = a.step.v;
+    n_self = row >= 0;
+    self0 = ((((long long)b * a.step.n_seg + a.step.n_seg - 1) * a.n_kv_heads + g) * a.step.cap + max(row, 0)) * D;
   }
-#pragma unroll
-  for (int off = PC_WAVE / 2; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-  if (d % PC_WAVE == 0) red[d / PC_WAVE] = M;
-  __syncthreads();
-  M = red[0];
-#pragma unroll
-  for (int w = 1; w < D / PC_WAVE; ++w) M = fmaxf(M, red[w]);
-  __syncthreads();                                           // red is reused below
 
-  // self segment (only launched with n_q <= 16): logits of keys 0..t
-  const bool has_self = a.k_self != nullptr;
-  if (has_self) {
-    const float qd = bf16_bits_to_f32(a.q[(((long long)b * a.n_q + t) * a.n_q_heads + h) * D + d]);
-    for (int j = 0; j <= t; ++j) {
-      float x = qd * bf16_bits_to_f32(a.k_self[(((long long)b * a.n_q + j) * a.n_kv_heads + g) * D + d]);
+  float m = -INFINITY, den = 0.f;
+  floatx4 num = {0.f, 0.f, 0.f, 0.f};
+  for (int p0 = grp; p0 < a.n_parts; p0 += GROUPS * U) {
+    float l[U], top = m;
+    floatx4 x[U];
 #pragma unroll
-      for (int off = PC_WAVE / 2; off > 0; off >>= 1) x += __shfl_xor(x, off);
-      if (d % PC_WAVE == 0) red[d / PC_WAVE] = x;
-      __syncthreads();
-      if (d == 0) {
-        float tot = 0.f;
-        for (int w = 0; w < D / PC_WAVE; ++w) tot += red[w];
-        self_s[j] = tot * a.scale;
-      }
-      __syncthreads();
+    for (int u = 0; u < U; ++u) {
+      const long long row = row0 + min(p0 + u * GROUPS, a.n_parts - 1) * row_stride;
+      l[u] = a.part_lse[row];
+      x[u] = *(const floatx4*)(a.part_o + row * D + d4);
     }
-    for (int j = 0; j <= t; ++j) M = fmaxf(M, self_s[j]);
-  }
-  float num = 0.f, den = 0.f;
-  if (M > -INFINITY) {
-    // weights exp(lse_p - M): computed once per partial and kept in LDS; every thread then sums
-    // them in the same (partial) order, so all threads hold the same denominator
-    if (in_lds) {
-      for (int p = d; p < a.n_parts; p += D) wgt_lds[p] = expf(wgt_lds[p] - M);
-      __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (p0 + u * GROUPS >= a.n_parts) l[u] = -INFINITY;
+      top = fmaxf(top, l[u]);
     }
-    constexpr int U = 8;                                     // independent loads in flight per thread
-    for (int p0 = 0; p0 < a.n_parts; p0 += U) {
-      float w[U], x[U];
+    if (top > -INFINITY) {
+      const float w0 = expf(m - top);
+      m = top; den *= w0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) num[e] *= w0;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int p = min(p0 + u, a.n_parts - 1);
-        w[u] = in_lds ? wgt_lds[p] : expf(a.part_lse[row0 + p * row_stride] - M);
-        x[u] = a.part_o[(row0 + p * row_stride) * D + d];
-      }
+        const float w = expf(l[u] - top);
+        den += w;
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (p0 + u < a.n_parts) { num += w[u] * x[u]; den += w[u]; }
-    }
-    if (has_self) {
-      for (int j = 0; j <= t; ++j) {
-        const float wgt = expf(self_s[j] - M);
-        num += wgt * bf16_bits_to_f32(a.v_self[(((long long)b * a.n_q + j) * a.n_kv_heads + g) * D + d]);
-        den += wgt;
+        for (int e = 0; e < 4; ++e) num[e] += w * x[u][e];
       }
     }
   }
-  const long long orow = ((long long)b * a.n_q + t) * a.n_q_heads + h;
-  a.out[orow * D + d] = (uint16_t)f32_to_bf16_bits(den > 0.f ? num / den : 0.f);
-  if (a.lse_out && d == 0)
-    a.lse_out[((long long)b * a.n_q_heads + h) * a.n_q + t] = den > 0.f ? M + logf(den) : -INFINITY;
+  // from the last group on: it has the fewest partials
+  for (int j = GROUPS - 1 - grp; j < n_self; j += GROUPS) {
+    const long long at = self0 + (long long)j * a.n_kv_heads * D + d4;
+    const uint2 kw = *(const uint2*)(k_self + at), vw = *(const uint2*)(v_self + at), qw = *(const uint2*)(a.q + orow * D + d4);
+    float l = bf16_lo_to_f32(kw.x) * bf16_lo_to_f32(qw.x) + bf16_hi_to_f32(kw.x) * bf16_hi_to_f32(qw.x) +
+              bf16_lo_to_f32(kw.y) * bf16_lo_to_f32(qw.y) + bf16_hi_to_f32(kw.y) * bf16_hi_to_f32(qw.y);
+#pragma unroll
+    for (int off = TPR / 2; off > 0; off >>= 1) l += __shfl_xor(l, off);
+    l *= a.scale;
+    const float top = fmaxf(m, l);
+    const float w0 = m > -INFINITY ? expf(m - top) : 0.f, w = expf(l - top);
+    m = top;
+    den = den * w0 + w;
+    num[0] = num[0] * w0 + w * bf16_lo_to_f32(vw.x); num[1] = num[1] * w0 + w * bf16_hi_to_f32(vw.x);
+    num[2] = num[2] * w0 + w * bf16_lo_to_f32(vw.y); num[3] = num[3] * w0 + w * bf16_hi_to_f32(vw.y);
+  }
+  num_lds[grp][d4 / 4] = num;
+  if (d4 == 0) ml_lds[grp] = make_float2(m, den);
+  __syncthreads();
+  if (threadIdx.x < TPR) {
+    float M = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < GROUPS; ++i) M = fmaxf(M, ml_lds[i].x);
+    float tot = 0.f;
+    floatx4 y = {0.f, 0.f, 0.f, 0.f};
+    if (M > -INFINITY) {
+#pragma unroll
+      for (int i = 0; i < GROUPS; ++i) {
+        const float w = expf(ml_lds[i].x - M);
+        const floatx4 x = num_lds[i][d4 / 4];
+        tot += w * ml_lds[i].y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] += w * x[e];
+      }
+    }
+    const float inv = tot > 0.f ? 1.f / tot : 0.f;
+    *(uint2*)(a.out + orow * D + d4) = make_uint2(pack_bf16x2(y[0] * inv, y[1] * inv), pack_bf16x2(y[2] * inv, y[3] * inv));
+    if (a.lse_out && d4 == 0)
+      a.lse_out[((long long)b * a.n_q_heads + h) * a.n_q + t] = tot > 0.f ? M + logf(tot) : -INFINITY;
+  }
+  // count the step's row (nothing else in this launch looks at the lengths)
+  if (a.step.seg_len && h == 0) {
+    const int n_len = a.step.len_per_head ? a.n_kv_heads : 1;
+    int32_t* len_at = a.step.seg_len + ((long long)b * a.step.n_seg + a.step.n_seg - 1) * n_len;
+    for (int i = threadIdx.x; i < n_len; i += 256) {
+      const int len = min(max(len_at[i], 0), a.step.cap);
+      len_at[i] = min(len + 1, a.step.cap);
+    }
+  }
 }
 
 // Merge for a block of query rows: bound by reading the fp32 partials once.  A thread owns 4
@@ -189,7 +214,7 @@ int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, 
 // 9.6 us, 15.4 with every thread computing its own angles.
 template <int D>
 __global__ __launch_bounds__(256) void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
-                                                     int n_q, int n_heads, int pos0, double log_base, double mul) {
+                                                     int n_q, int n_heads, int pos0, PcRope rope, double mul) {
   constexpr int HALF = D / 2, TPR = HALF / 8;                       // threads per head row
   __shared__ double2 angle[HALF];                                   // (cos, sin)
   const int i0 = (threadIdx.x % TPR) * 8;
@@ -202,10 +227,8 @@ __global__ __launch_bounds__(256) void rope_q_kernel(const uint16_t* __restrict_
   }
   if (threadIdx.x < HALF) {
     double sn = 0.0, cs = 1.0;
-    if (pos0 >= 0) {
-      const double theta = exp(-2.0 * (double)(int)threadIdx.x / (double)D * log_base);
-      sincos((double)(pos0 + (int)(blockIdx.x % (unsigned)n_q)) * theta, &sn, &cs);
-    }
+    if (pos0 >= 0)
+      pc_sincos((double)(pos0 + (int)(blockIdx.x % (unsigned)n_q)) * pc_rope_theta(rope, (int)threadIdx.x), sn, cs);
     angle[threadIdx.x] = make_double2(cs, sn);
   }
   __syncthreads();
@@ -238,13 +261,13 @@ int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_ROPE_Q, st);
   const dim3 grid((unsigned)blocks), block(256);
-  const double log_base = log((double)(pos0 >= 0 ? base : 2.0f));
+  const PcRope rope = pc_rope_factors(pos0 >= 0 ? base : 2.0f, D);
   if (D == 128)
     hipLaunchKernelGGL(rope_q_kernel<128>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, n_q, n_heads,
-                       pos0, log_base, (double)mul);
+                       pos0, rope, (double)mul);
   else
     hipLaunchKernelGGL(rope_q_kernel<64>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, n_q, n_heads,
-                       pos0, log_base, (double)mul);
+                       pos0, rope, (double)mul);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
@@ -260,14 +283,14 @@ int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads
 #define PC_APPEND_THREADS 1024
 __global__ __launch_bounds__(PC_APPEND_THREADS) void kv_append_kernel(
     const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int n_new, int n_seg,
-    int seg, int k_t, int n_kv_heads, int D, int pos0, double log_base, uint16_t* __restrict__ kc,
+    int seg, int k_t, int n_kv_heads, int D, int pos0, PcRope rope, uint16_t* __restrict__ kc,
     uint16_t* __restrict__ vc, int32_t* __restrict__ seg_len, int per_head) {
   const int b = blockIdx.x;
   const int half = D / 2;
   const long long len_base = per_head ? ((long long)b * n_seg + seg) * n_kv_heads
                                       : (long long)b * n_seg + seg;
   const int i = threadIdx.x % half;
-  const double theta = pos0 >= 0 ? exp(-2.0 * (double)i / (double)D * log_base) : 0.0;
+  const double theta = pc_rope_theta(rope, i);
   int at = -1;
   double sn = 0.0, cs = 1.0;
   const long long rows = (long long)n_new * n_kv_heads;
@@ -279,7 +302,7 @@ __global__ __launch_bounds__(PC_APPEND_THREADS) void kv_append_kernel(
     const long long dst = ((((long long)b * n_seg + seg) * n_kv_heads + g) * k_t + len + t) * D;
     const uint16_t a1 = k_new[src + i], a2 = k_new[src + i + half];
     if (pos0 >= 0) {
-      if (t != at) { sincos((double)(pos0 + t) * theta, &sn, &cs); at = t; }
+      if (t != at) { pc_sincos((double)(pos0 + t) * theta, sn, cs); at = t; }
       const float x1 = bf16_bits_to_f32(a1), x2 = bf16_bits_to_f32(a2);
       kc[dst + i] = (uint16_t)f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
       kc[dst + i + half] = (uint16_t)f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
@@ -302,7 +325,7 @@ int pc_launch_kv_append(const void* k_new, const void* v_new, int batch, int n_n
   PcProfScope prof(PC_KERNEL_KV_APPEND, st);
   hipLaunchKernelGGL(kv_append_kernel, dim3(batch), dim3(PC_APPEND_THREADS), 0, st, (const uint16_t*)k_new,
                      (const uint16_t*)v_new, n_new, n_seg, seg, k_t, n_kv_heads, head_dim, pos0,
-                     log((double)(pos0 >= 0 ? base : 2.0f)), (uint16_t*)kc, (uint16_t*)vc, seg_len,
+                     pc_rope_factors(pos0 >= 0 ? base : 2.0f, head_dim), (uint16_t*)kc, (uint16_t*)vc, seg_len,
                      seg_len_per_head);
   PC_LAUNCH_CHECK();
   return PC_OK;
@@ -351,10 +374,10 @@ PcDecodeSplit pc_decode_split(int k_t, int n_seg, long long n_bg) {
 int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const void* vc,
                      const int32_t* seg_len, int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                      int head_dim, float scale, float* part_o, float* part_lse, int n_parts,
-                     int part0, hipStream_t st) {
-  const PcDecodeArgs a = pc_decode_args(pc_decode_query(q, pos0, base, n_q, n_q_heads), kc, vc, seg_len,
+                     int part0, const PcDecodeAppend& app, hipStream_t st) {
+  const PcDecodeArgs a = pc_decode_args(pc_decode_query(q, pos0, base, n_q, n_q_heads, head_dim), kc, vc, seg_len,
                                         seg_len_per_head, batch, n_seg, k_t, n_kv_heads, scale, part_o,
-                                        part_lse, n_parts, part0);
+                                        part_lse, n_parts, part0, app);
   const int cols = n_q * (n_q_heads / n_kv_heads);
   const int nq_pad = cols <= 4 ? 4 : (cols <= 8 ? 8 : 16);
   return head_dim == 128 ? launch_decode_d<128>(a, batch, nq_pad, st)
@@ -362,12 +385,12 @@ int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const 
 }
 
 int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_rot,
-                    const void* k_self, const void* v_self, void* out, float* lse_out, int batch,
-                    int n_q, int n_q_heads, int n_kv_heads, int head_dim, int n_parts, float scale,
+                    const void* k_self, const void* v_self, const PcMergeStep& step, void* out, float* lse_out,
+                    int batch, int n_q, int n_q_heads, int n_kv_heads, int head_dim, int n_parts, float scale,
                     hipStream_t st) {
   PcMergeArgs a;
   a.part_o = part_o; a.part_lse = part_lse; a.q = (const uint16_t*)q_rot;
-  a.k_self = (const uint16_t*)k_self; a.v_self = (const uint16_t*)v_self;
+  a.k_self = (const uint16_t*)k_self; a.v_self = (const uint16_t*)v_self; a.step = step;
   a.out = (uint16_t*)out; a.lse_out = lse_out;
   a.n_q = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.n_parts = n_parts;
   a.scale = scale;
@@ -375,8 +398,8 @@ int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_ro
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_MERGE, st);
-  if (head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3((unsigned)blocks), dim3(128), 0, st, a);
-  else hipLaunchKernelGGL(merge_kernel<64>, dim3((unsigned)blocks), dim3(64), 0, st, a);
+  if (head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(merge_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

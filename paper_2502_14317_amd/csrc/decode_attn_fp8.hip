@@ -302,49 +302,33 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   // softmax (one partial per workgroup).  A cursor names the next block: where it is, the
   // segment's base pointers and its scales (K: folded into the logit scale; V: applied to the
   // probabilities that multiply the codes, not to the row sum).
-  struct Cursor { PcBlockCursor at; const uint8_t* k; const uint8_t* v; float k_sc, v_sc; bool valid; };
+  struct Cursor { PcBlockCursor at; const uint8_t* k; const uint8_t* v; float k_sc, v_sc; int bytes; };
   const long long seg_bytes = (long long)((a.k_t + 31) / 32) * 32 * D;
   PcSegLens lens;
   lens.seg_len = a.seg_len; lens.per_head = a.seg_len_per_head; lens.n_seg = a.n_seg;
   lens.n_kv_heads = a.n_kv_heads; lens.k_t = a.k_t; lens.b = b; lens.g = g;
   auto place = [&](const PcBlockCursor& at) {
-    Cursor c; c.at = at; c.valid = at.valid; c.k = nullptr; c.v = nullptr; c.k_sc = 0.f; c.v_sc = 0.f;
-    if (at.valid) {
+    Cursor c; c.at = at; c.k = a.k8; c.v = a.v8; c.k_sc = 0.f; c.v_sc = 0.f;
+    c.bytes = 0;                                                        // behind the run's end: nothing is read
+    if (at.left > 0) {
       const long long seg_id = ((long long)b * a.n_seg + at.s) * a.n_kv_heads + g;
-      c.k = a.k8 + seg_id * seg_bytes; c.v = a.v8 + seg_id * seg_bytes;
+      const long long first = seg_id * seg_bytes + (long long)at.blk * 32 * D;
+      c.k = a.k8 + first; c.v = a.v8 + first; c.bytes = 32 * D;         // whole blocks exist up to ceil(k_t / 32)
       // read-only here, and asked for through the scalar cache: a vector load would have to be waited
       // for behind the keys in flight
       typedef const __attribute__((address_space(4))) float* scalar_t;
-      c.k_sc = ((scalar_t)(uintptr_t)a.k_scale)[seg_id] * a.scale_log2;    // logits in log2 units
+      c.k_sc = ((scalar_t)(uintptr_t)a.k_scale)[seg_id];
       c.v_sc = ((scalar_t)(uintptr_t)a.v_scale)[seg_id];
     }
     return c;
   };
   auto next = [&](const Cursor& c) { return place(pc_blocks_next(lens, c.at)); };
 
+  PcColumnRotation<D> rot;
+  rot.begin(a.query, b, g, G, n_cols);
   // B operand: column c16 = (t, head-in-group); k-step j of lane group kk covers
   // d = 64 (j / 2) + 16 kk + 8 (j % 2) .. + 7, the d order of the K block layout
   bf16x8 bq[KSTEPS];
-  {
-    const bool valid = c16 < n_cols;
-    const int n = valid ? c16 : 0;
-    if (a.query.pos0 >= 0) {
-      pc_rotate_columns<D>(a.query, b, g, G, n_cols, q_lds);
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < KSTEPS; ++j) {
-        uint4 raw = valid ? *(const uint4*)(q_lds[n] + 64 * (j / 2) + 16 * kk + 8 * (j % 2)) : make_uint4(0, 0, 0, 0);
-        bq[j] = *(bf16x8*)&raw;
-      }
-    } else {
-      const uint16_t* qrow = a.query.q + (((long long)b * a.n_q + n / G) * a.n_q_heads + g * G + n % G) * D;
-#pragma unroll
-      for (int j = 0; j < KSTEPS; ++j) {
-        uint4 raw = valid ? *(const uint4*)(qrow + 64 * (j / 2) + 16 * kk + 8 * (j % 2)) : make_uint4(0, 0, 0, 0);
-        bq[j] = *(bf16x8*)&raw;
-      }
-    }
-  }
 
   float m_run = -INFINITY, l_run = 0.f;     // of column c16 (this lane's share of the sum)
   // O^T: row block mb, register r = value d = 16 mb + 4 kk + r of column c16
@@ -352,25 +336,27 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) o_acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  uint4 kbuf[3][KBLK][KQ], vbuf[3][VLOADS];
-  auto issue_loads = [&](int buf, const Cursor& c) {
-    // the block's pieces: key0 is a multiple of 32, and whole blocks exist up to ceil(k_t / 32)
-    const long long blk_off = (long long)c.at.blk * 32 * D + 16 * lane;
-    const uint8_t* kblk = c.k + blk_off;
-    const uint8_t* vblk = c.v + blk_off;
+  // unconditional loads (see pc_decode_workgroup)
+  u32x4 kbuf[3][KBLK][KQ], vbuf[3][VLOADS];
+  auto issue_loads = [&](int buf, const Cursor& c) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)c.k, 0, c.bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)c.v, 0, c.bytes, 0x00020000);
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
       for (int i = 0; i < KQ; ++i)
-        kbuf[buf][bi][i] = pc_load_once((const uint4*)(kblk + bi * 16 * D + 1024 * i));
+        kbuf[buf][bi][i] = __builtin_amdgcn_raw_buffer_load_b128(kr, 16 * lane, bi * 16 * D + 1024 * i, PC_BUF_NT);
 #pragma unroll
     for (int i = 0; i < VLOADS; ++i)
-      vbuf[buf][i] = pc_load_once((const uint4*)(vblk + 1024 * i));
+      vbuf[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(vr, 16 * lane, 1024 * i, PC_BUF_NT);
+    __builtin_amdgcn_sched_barrier(0);                       // not behind the arithmetic that follows
   };
 
   auto consume = [&](int buf, const Cursor& cur) {
     const int key0 = 32 * cur.at.blk, w_end = cur.at.len;
-    const float k_sc = cur.k_sc, v_sc = cur.v_sc;
+    // (the product here, not in the cursor: a vector register written between a block's loads and its
+    // arithmetic can be one that a load behind the run's end has yet to fill, and costs a wait for all)
+    const float k_sc = cur.k_sc * a.scale_log2, v_sc = cur.v_sc;           // logits in log2 units
     floatx4 acc[KBLK];
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi) {
@@ -378,8 +364,7 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
 #pragma unroll
       for (int j = 0; j < KSTEPS; ++j) {
         // k-step j: words 2 (j % 2), 2 (j % 2) + 1 of the lane's load j / 2
-        const uint4 raw = kbuf[buf][bi][j / 2];
-        const uint32_t w0 = (j % 2) ? raw.z : raw.x, w1 = (j % 2) ? raw.w : raw.y;
+        const uint32_t w0 = kbuf[buf][bi][j / 2][2 * (j % 2)], w1 = kbuf[buf][bi][j / 2][2 * (j % 2) + 1];
         u32x4 kb16;
         uint32_t lo, hi;
         pc_e4m3x4_to_bf16(w0, lo, hi); kb16[0] = lo; kb16[1] = hi;
@@ -392,13 +377,19 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int key = key0 + 16 * bi + 4 * kk + j;
-        sv[bi][j] = (key < w_end) ? acc[bi][j] * k_sc : -INFINITY;
-        bmax = fmaxf(bmax, sv[bi][j]);
-      }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+      for (int j = 0; j < 4; ++j) sv[bi][j] = acc[bi][j] * k_sc;
+    if (key0 + 32 > w_end) {                         // a segment's last block
+#pragma unroll
+      for (int bi = 0; bi < KBLK; ++bi)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (key0 + 16 * bi + 4 * kk + j >= w_end) sv[bi][j] = -INFINITY;
+    }
+#pragma unroll
+    for (int bi = 0; bi < KBLK; ++bi)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bmax = fmaxf(bmax, sv[bi][j]);
+    bmax = pc_rows_max(bmax);
     const float m_new = fmaxf(m_run, bmax);          // finite: every block holds a valid key
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // arguments <= 0: the bare instruction
     m_run = m_new;
@@ -424,10 +415,9 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
     }
 #pragma unroll
     for (int i = 0; i < VLOADS; ++i) {
-      const uint4 raw = vbuf[buf][i];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const uint32_t w0 = h ? raw.z : raw.x, w1 = h ? raw.w : raw.y;
+        const uint32_t w0 = vbuf[buf][i][2 * h], w1 = vbuf[buf][i][2 * h + 1];
         u32x4 va;
         uint32_t lo, hi;
         pc_e4m3x4_to_bf16(w0, lo, hi); va[0] = lo; va[1] = hi;
@@ -438,29 +428,35 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   };
 
   // three register buffers: the loads of two blocks (2 x 8 KiB per wavefront) stay in flight
-  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave),
-                                    PC_D8_WAVES, lane));
-  if (c0.valid) {
-    Cursor c1 = next(c0);
-    issue_loads(0, c0);
-    if (c1.valid) issue_loads(1, c1);
-    auto iter = [&](int cur_buf, int fill_buf) __attribute__((always_inline)) {
-      // c0 = block to consume (in cur_buf), c1 = the block after it (already in flight)
-      const Cursor c2 = next(c1);                            // (behind the run's end: not valid)
-      if (c2.valid) issue_loads(fill_buf, c2);
-      consume(cur_buf, c0);
-      c0 = c1; c1 = c2;
-    };
-    while (true) {
-      iter(0, 2); if (!c0.valid) break;
-      iter(1, 0); if (!c0.valid) break;
-      iter(2, 1); if (!c0.valid) break;
-    }
+  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane));
+  Cursor c1 = next(c0);
+  issue_loads(0, c0);
+  issue_loads(1, c1);
+  rot.finish(a.query, b, g, G, n_cols, q_lds);
+  PC_LDS_BARRIER();
+#pragma unroll
+  for (int j = 0; j < KSTEPS; ++j) {
+    u32x4 raw = *(const u32x4*)(q_lds[min(c16, n_cols - 1)] + 64 * (j / 2) + 16 * kk + 8 * (j % 2));
+    if (c16 >= n_cols) raw = u32x4{0, 0, 0, 0};
+    bq[j] = *(bf16x8*)&raw;
+  }
+  auto iter = [&](int cur_buf, int fill_buf) __attribute__((always_inline)) {
+    // c0 = block to consume (in cur_buf), c1 = the block after it (already in flight)
+    const Cursor c2 = next(c1);                              // (behind the run's end: not valid)
+    issue_loads(fill_buf, c2);
+    if (c0.at.left > 0) consume(cur_buf, c0);
+    c0 = c1; c1 = c2;
+  };
+  // (no way out in the middle: it would join the loop's end, where the compiler would then have to take
+  // either buffer for the one asked for last)
+  while (c0.at.left > 0) {
+    iter(0, 2);
+    iter(1, 0);
+    iter(2, 1);
   }
 
   // ---- wavefront totals: sum the per-lane shares
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_run = pc_rows_sum(l_run);
   if (kk == 0 && c16 < NQ) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
   if (c16 < NQ) {
 #pragma unroll
@@ -532,11 +528,11 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
                          const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
                          int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
-                         float* part_lse, int n_parts, hipStream_t st) {
+                         float* part_lse, int n_parts, const PcDecodeAppend& app, hipStream_t st) {
   const int cols = n_q * (n_q_heads / n_kv_heads);
   if (cols > 16) return PC_ERR_UNSUPPORTED;               // the columns of one 16x16x32 MFMA
   PcDecode8Args a;
-  a.query = pc_decode_query(q, pos0, base, n_q, n_q_heads);
+  a.query = pc_decode_query(q, pos0, base, n_q, n_q_heads, head_dim);
   a.k8 = (const uint8_t*)k8; a.v8 = (const uint8_t*)v8;
   a.k_scale = k_scale; a.v_scale = v_scale;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
@@ -549,10 +545,10 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
   const bool tail_here = tail_cap > 0 && (nq_pad == 4 || n_wg8 <= PC_D8_TAIL_WGS);
   const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_here ? 1 : 0,
                                            tail_here ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
-                                           n_parts, a.parts_grid);
+                                           n_parts, a.parts_grid, app);
   const int rc = head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, nq_pad, st)
                                  : launch_decode8_d<64>(a, tail, batch, nq_pad, st);
   if (rc != PC_OK || tail_cap == 0 || tail_here) return rc;
   return pc_launch_decode(q, pos0, base, k_tail, v_tail, tail_len, 0, batch, n_q, 1, tail_cap, n_q_heads, n_kv_heads,
-                          head_dim, scale, part_o, part_lse, n_parts, a.parts_grid, st);
+                          head_dim, scale, part_o, part_lse, n_parts, a.parts_grid, app, st);
 }

@@ -20,30 +20,94 @@
 struct PcDecodeQuery {
   const uint16_t* q;
   int pos0, n_q, n_q_heads;
-  double log_base;
+  PcRope rope;
 };
 
-// The columns (query t, head) of KV head g, rotated, into LDS: column n = t * G + head in group.
+// The columns (query t, head) of KV head g, rotated, into LDS: column n = t * G + head in group.  In two
+// steps, so that the first keys can be asked for in between: `begin` asks for the query values (they are
+// the older loads, so waiting for them leaves the keys in flight), `finish` rotates and writes.
 template <int D>
-__device__ __forceinline__ void pc_rotate_columns(const PcDecodeQuery& x, int b, int g, int G, int n_cols,
-                                                  uint16_t (*cols)[D]) {
-  constexpr int HALF = D / 2;
-  const int i = threadIdx.x % HALF;                         // a thread keeps its rotation pair
-  const double theta = exp(-2.0 * (double)i / (double)D * x.log_base);
-  int at = -1;
-  double sn = 0.0, cs = 1.0;
-  for (int n = threadIdx.x / HALF; n < n_cols; n += blockDim.x / HALF) {
-    const int t = n / G;
-    if (t != at) { sincos((double)(x.pos0 + t) * theta, &sn, &cs); at = t; }
-    const uint16_t* row = x.q + (((long long)b * x.n_q + t) * x.n_q_heads + g * G + n % G) * D;
-    const double x1 = bf16_bits_to_f32(row[i]), x2 = bf16_bits_to_f32(row[i + HALF]);
-    cols[n][i] = (uint16_t)f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
-    cols[n][i + HALF] = (uint16_t)f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
+struct PcColumnRotation {
+  static constexpr int HALF = D / 2;
+  int i, n0;                                                // the thread's rotation pair, its first column
+  uint32_t a, b;
+  __device__ __forceinline__ const uint16_t* row(const PcDecodeQuery& x, int seq, int g, int G, int n) const {
+    return x.q + (((long long)seq * x.n_q + n / G) * x.n_q_heads + g * G + n % G) * D;
   }
-}
+  __device__ __forceinline__ void begin(const PcDecodeQuery& x, int seq, int g, int G, int n_cols) {
+    i = threadIdx.x % HALF; n0 = threadIdx.x / HALF;
+    const uint16_t* r = row(x, seq, g, G, min(n0, n_cols - 1));
+    a = r[i]; b = r[i + HALF];
+  }
+  __device__ __forceinline__ void finish(const PcDecodeQuery& x, int seq, int g, int G, int n_cols, uint16_t (*cols)[D]) {
+    const double theta = pc_rope_theta(x.rope, i);
+    int at = -1;
+    double sn = 0.0, cs = 1.0;
+    for (int n = n0; n < n_cols; n += blockDim.x / HALF) {
+      if (n != n0) { const uint16_t* r = row(x, seq, g, G, n); a = r[i]; b = r[i + HALF]; }
+      uint32_t ra = a, rb = b;                              // pos0 < 0: as they are
+      if (x.pos0 >= 0) {
+        if (n / G != at) { at = n / G; pc_sincos((double)(x.pos0 + at) * theta, sn, cs); }
+        const double x1 = bf16_bits_to_f32((uint16_t)a), x2 = bf16_bits_to_f32((uint16_t)b);
+        ra = f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
+        rb = f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
+      }
+      cols[n][i] = (uint16_t)ra;
+      cols[n][i + HALF] = (uint16_t)rb;
+    }
+  }
+};
+// A decoding step's new token (one query row): its key, rotated at `pos` (pos < 0: it arrives rotated), and
+// value are stored behind the rows of the last segment, unless that is full; the merge takes the token as
+// one more key and counts the row.  In two steps like the columns.
+struct PcDecodeAppend {
+  const uint16_t* k_new;   // [B, H_kv, D] or nullptr: no step
+  const uint16_t* v_new;
+  int pos;
+  uint16_t* q_rot;         // [B, H_q, D] out: the rotated query for the merge; nullptr: the merge has it already
+  int32_t* self_row;       // [B, H_kv] out: the row written, -1 if there was no room
+};
+template <int D>
+struct PcRowAppend {
+  uint32_t a, b, v;
+  __device__ __forceinline__ void begin(const PcDecodeAppend& x, int bg) {
+    const int i = threadIdx.x % (D / 2);
+    const uint16_t* k = x.k_new + (long long)bg * D;
+    a = k[i]; b = k[i + D / 2];
+    v = x.v_new[(long long)bg * D + threadIdx.x % D];
+  }
+  __device__ __forceinline__ void finish(const PcDecodeAppend& x, const PcRope& rope, int bg, int len, int cap,
+                                         uint16_t* k_seg, uint16_t* v_seg) {
+    const int tid = threadIdx.x;
+    if (tid == 0) x.self_row[bg] = len < cap ? len : -1;
+    if (len >= cap) return;
+    const long long at = (long long)len * D;
+    if (tid < D / 2) {
+      uint32_t ra = a, rb = b;
+      if (x.pos >= 0) {
+        double sn, cs;
+        pc_sincos((double)x.pos * pc_rope_theta(rope, tid), sn, cs);
+        const double x1 = bf16_bits_to_f32((uint16_t)a), x2 = bf16_bits_to_f32((uint16_t)b);
+        ra = f32_to_bf16_bits((float)(x1 * cs - x2 * sn));
+        rb = f32_to_bf16_bits((float)(x2 * cs + x1 * sn));
+      }
+      k_seg[at + tid] = (uint16_t)ra;
+      k_seg[at + tid + D / 2] = (uint16_t)rb;
+    }
+    if (tid < D) v_seg[at + tid] = (uint16_t)v;
+  }
+};
+// Barrier over what the wavefronts wrote to LDS; loads from memory stay in flight
+#define PC_LDS_BARRIER()                                     \
+  do {                                                       \
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  \
+    __builtin_amdgcn_s_barrier();                            \
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");  \
+  } while (0)
 
 struct PcDecodeArgs {
   PcDecodeQuery query;
+  PcDecodeAppend app;
   const uint16_t* kc;     // [B, S, H_kv, k_t, D]
   const uint16_t* vc;
   const int32_t* seg_len; // [B, S] ([B, S, H_kv] if seg_len_per_head) or nullptr
@@ -84,42 +148,29 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   // A wavefront streams its run of 32-key blocks, through segment boundaries; the running
   // softmax carries over (same query columns, same KV head), so a workgroup leaves one partial.
   // A cursor names the next block: where it is, plus the segment's base pointers.
-  struct Cursor { PcBlockCursor at; int key0; const uint16_t* k; const uint16_t* v; bool valid; };
+  struct Cursor { PcBlockCursor at; const uint16_t* k; const uint16_t* v; int bytes; };
   PcSegLens lens;
   lens.seg_len = a.seg_len; lens.per_head = a.seg_len_per_head; lens.n_seg = a.n_seg;
   lens.n_kv_heads = a.n_kv_heads; lens.k_t = a.k_t; lens.b = b; lens.g = g;
   auto place = [&](const PcBlockCursor& at) {
-    Cursor c; c.at = at; c.valid = at.valid; c.key0 = 32 * at.blk; c.k = nullptr; c.v = nullptr;
-    if (at.valid) {
-      const long long seg_base = ((((long long)b * a.n_seg + at.s) * a.n_kv_heads + g) * a.k_t) * D;
-      c.k = a.kc + seg_base; c.v = a.vc + seg_base;
+    Cursor c; c.at = at; c.k = a.kc; c.v = a.vc; c.bytes = 0;       // behind the run's end: nothing is read
+    if (at.left > 0) {
+      const long long first = ((((long long)b * a.n_seg + at.s) * a.n_kv_heads + g) * a.k_t + 32LL * at.blk) * D;
+      c.k = a.kc + first; c.v = a.vc + first;
+      c.bytes = min(32, at.len - 32 * at.blk) * (2 * D);
     }
     return c;
   };
   auto next = [&](const Cursor& c) { return place(pc_blocks_next(lens, c.at)); };
 
-  // B operand: column c16 = (t, head-in-group); lane holds d = 32*ks + 8*kk .. +7
-  bf16x8 bq[KSTEPS];
-  {
-    const bool valid = c16 < n_cols;
-    const int n = valid ? c16 : 0;
-    if (a.query.pos0 >= 0) {
-      pc_rotate_columns<D>(a.query, b, g, G, n_cols, q_lds);
-      __syncthreads();
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        uint4 raw = valid ? *(const uint4*)(q_lds[n] + 32 * ks + 8 * kk) : make_uint4(0, 0, 0, 0);
-        bq[ks] = *(bf16x8*)&raw;
-      }
-    } else {
-      const uint16_t* qrow = a.query.q + (((long long)b * a.n_q + n / G) * a.n_q_heads + g * G + n % G) * D;
-#pragma unroll
-      for (int ks = 0; ks < KSTEPS; ++ks) {
-        uint4 raw = valid ? *(const uint4*)(qrow + 32 * ks + 8 * kk) : make_uint4(0, 0, 0, 0);
-        bq[ks] = *(bf16x8*)&raw;
-      }
-    }
-  }
+  PcColumnRotation<D> rot;
+  rot.begin(a.query, b, g, G, n_cols);
+  // the group's last workgroup also stores the new token: nobody reads its row in this launch (the
+  // lengths still exclude it)
+  const bool append = a.app.k_new != nullptr && part == a.parts_grid - 1;
+  PcRowAppend<D> row;
+  if (append) row.begin(a.app, b * a.n_kv_heads + g);
+  bf16x8 bq[KSTEPS];                        // B operand: column c16 = (t, head-in-group); lane holds d = 32*ks + 8*kk .. +7
 
   float m_run = -INFINITY, l_run = 0.f;     // of column c16 (this lane's share of the sum)
   float o_acc[NQ][8];
@@ -130,24 +181,28 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
 
   const int v_row = lane / LPR, v_piece = lane % LPR;
 
-  uint4 kbuf[2][KBLK][KSTEPS], vbuf[2][VLOADS];
-  auto issue_loads = [&](int buf, const Cursor& c) {
+  // A block's rows through buffer descriptors that end behind its last valid row: the rows after it arrive
+  // as zeros, and behind the run's end nothing is read.  So the loads are unconditional, and the waits in
+  // front of a block's arithmetic count the next block's loads as what they are, in flight (with loads
+  // under a condition the compiler must assume that they were not issued and waits for all).
+  u32x4 kbuf[2][KBLK][KSTEPS], vbuf[2][VLOADS];
+  const int k_off = 2 * (c16 * D + 8 * kk), v_off = 2 * (v_row * D + 8 * v_piece);
+  auto issue_loads = [&](int buf, const Cursor& c) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)c.k, 0, c.bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)c.v, 0, c.bytes, 0x00020000);
 #pragma unroll
-    for (int bi = 0; bi < KBLK; ++bi) {
-      const int row = min(c.key0 + 16 * bi + c16, c.at.len - 1);
+    for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks)
-        kbuf[buf][bi][ks] = pc_load_once((const uint4*)(c.k + (long long)row * D + 32 * ks + 8 * kk));
-    }
+        kbuf[buf][bi][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, k_off, 2 * (16 * bi * D + 32 * ks), PC_BUF_NT);
 #pragma unroll
-    for (int i = 0; i < VLOADS; ++i) {
-      const int row = min(c.key0 + RPI * i + v_row, c.at.len - 1);
-      vbuf[buf][i] = pc_load_once((const uint4*)(c.v + (long long)row * D + 8 * v_piece));
-    }
+    for (int i = 0; i < VLOADS; ++i)
+      vbuf[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(vr, v_off, 2 * RPI * i * D, PC_BUF_NT);
+    __builtin_amdgcn_sched_barrier(0);                       // not behind the arithmetic that follows
   };
 
   auto consume = [&](int buf, const Cursor& cur) {
-    const int key0 = cur.key0, w_end = cur.at.len;
+    const int key0 = 32 * cur.at.blk, w_end = cur.at.len;
     // S^T block: keys x columns
     floatx4 acc[KBLK];
 #pragma unroll
@@ -163,13 +218,19 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int key = key0 + 16 * bi + 4 * kk + j;
-        sv[bi][j] = (key < w_end) ? acc[bi][j] * a.scale_log2 : -INFINITY;
-        bmax = fmaxf(bmax, sv[bi][j]);
-      }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+      for (int j = 0; j < 4; ++j) sv[bi][j] = acc[bi][j] * a.scale_log2;
+    if (key0 + 32 > w_end) {                         // a segment's last block
+#pragma unroll
+      for (int bi = 0; bi < KBLK; ++bi)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (key0 + 16 * bi + 4 * kk + j >= w_end) sv[bi][j] = -INFINITY;
+    }
+#pragma unroll
+    for (int bi = 0; bi < KBLK; ++bi)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bmax = fmaxf(bmax, sv[bi][j]);
+    bmax = pc_rows_max(bmax);
     const float m_new = fmaxf(m_run, bmax);          // finite: every block holds a valid key
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // arguments <= 0: the bare instruction
     m_run = m_new;
@@ -198,12 +259,11 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
 #pragma unroll
     for (int i = 0; i < VLOADS; ++i) {
       const int key_local = RPI * i + v_row;
-      const uint4 raw = vbuf[buf][i];
       float vf[8];
-      vf[0] = bf16_lo_to_f32(raw.x); vf[1] = bf16_hi_to_f32(raw.x);
-      vf[2] = bf16_lo_to_f32(raw.y); vf[3] = bf16_hi_to_f32(raw.y);
-      vf[4] = bf16_lo_to_f32(raw.z); vf[5] = bf16_hi_to_f32(raw.z);
-      vf[6] = bf16_lo_to_f32(raw.w); vf[7] = bf16_hi_to_f32(raw.w);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        vf[2 * e] = bf16_lo_to_f32(vbuf[buf][i][e]); vf[2 * e + 1] = bf16_hi_to_f32(vbuf[buf][i][e]);
+      }
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
         const float p = p_lds[wave][key_local][n];    // 0 for masked keys
@@ -214,27 +274,38 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
     PC_WAVE_LDS_SYNC();
   };
 
-  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave),
-                                     PC_DEC_WAVES, lane));
-  if (cur.valid) {
+  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane));
+  issue_loads(0, cur);
+
+  rot.finish(a.query, b, g, G, n_cols, q_lds);
+  PC_LDS_BARRIER();
+  if (append) {
+    const long long seg0 = (((long long)b * a.n_seg + a.n_seg - 1) * a.n_kv_heads + g) * a.k_t * D;
+    row.finish(a.app, a.query.rope, b * a.n_kv_heads + g, lens.len(a.n_seg - 1), a.k_t, const_cast<uint16_t*>(a.kc) + seg0,
+               const_cast<uint16_t*>(a.vc) + seg0);
+    if (a.app.q_rot)
+      for (int x = threadIdx.x; x < n_cols * D; x += blockDim.x)     // one query row: heads g G .. are adjacent
+        a.app.q_rot[((long long)b * a.n_q_heads + g * G) * D + x] = q_lds[x / D][x % D];
+  }
+#pragma unroll
+  for (int ks = 0; ks < KSTEPS; ++ks) {
+    u32x4 raw = *(const u32x4*)(q_lds[min(c16, n_cols - 1)] + 32 * ks + 8 * kk);
+    if (c16 >= n_cols) raw = u32x4{0, 0, 0, 0};
+    bq[ks] = *(bf16x8*)&raw;
+  }
+
+  while (cur.at.left > 0) {
+    Cursor nx = next(cur);
+    issue_loads(1, nx);
+    consume(0, cur);
+    if (nx.at.left == 0) break;
+    cur = next(nx);
     issue_loads(0, cur);
-    while (true) {
-      Cursor nx = next(cur);
-      if (nx.valid) issue_loads(1, nx);
-      consume(0, cur);
-      if (!nx.valid) break;
-      cur = nx;
-      nx = next(cur);
-      if (nx.valid) issue_loads(0, nx);
-      consume(1, cur);
-      if (!nx.valid) break;
-      cur = nx;
-    }
+    consume(1, nx);
   }
 
   // ---- wavefront totals: sum the per-lane shares
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_run = pc_rows_sum(l_run);
 #pragma unroll
   for (int n = 0; n < NQ; ++n)
 #pragma unroll
@@ -276,18 +347,18 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   }
 }
 
-static inline PcDecodeQuery pc_decode_query(const void* q, int pos0, float base, int n_q, int n_q_heads) {
+static inline PcDecodeQuery pc_decode_query(const void* q, int pos0, float base, int n_q, int n_q_heads, int head_dim) {
   PcDecodeQuery x;
   x.q = (const uint16_t*)q; x.pos0 = pos0; x.n_q = n_q; x.n_q_heads = n_q_heads;
-  x.log_base = log((double)(pos0 >= 0 ? base : 2.0f));
+  x.rope = pc_rope_factors(base > 1.0f ? base : 2.0f, head_dim);        // (not looked at where nothing is rotated)
   return x;
 }
 static inline PcDecodeArgs pc_decode_args(const PcDecodeQuery& query, const void* kc, const void* vc,
                                           const int32_t* seg_len, int seg_len_per_head, int batch, int n_seg,
                                           int k_t, int n_kv_heads, float scale, float* part_o, float* part_lse,
-                                          int n_parts, int part0) {
+                                          int n_parts, int part0, const PcDecodeAppend& app) {
   PcDecodeArgs a;
-  a.query = query; a.part0 = part0;
+  a.query = query; a.part0 = part0; a.app = app;
   a.kc = (const uint16_t*)kc; a.vc = (const uint16_t*)vc;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = query.n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = query.n_q_heads; a.n_kv_heads = n_kv_heads;

@@ -1,6 +1,6 @@
 // C ABI of the ParallelComp library: argument validation, workspace carving, kernel dispatch.
 // Every host-visible argument is checked before any GPU work is enqueued.
-#include "pc_common.h"
+#include "decode_core.h"
 #include <math.h>
 #include <mutex>
 
@@ -211,10 +211,9 @@ extern "C" int pc_chunk_query_scores(const pc_shape* s, const void* q, const voi
   return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, nullptr, st);
 }
 
-extern "C" int pc_kv_append(const void* k_new, const void* v_new, int32_t batch, int32_t n_new,
-                            int32_t n_seg, int32_t seg, int32_t k_t, int32_t n_kv_heads,
-                            int32_t head_dim, int32_t pos0, float rope_base, void* kc, void* vc,
-                            int32_t* seg_len, int32_t seg_len_per_head, void* stream) {
+static int check_append(const void* k_new, const void* v_new, int batch, int n_new, int n_seg, int seg, int k_t,
+                        int n_kv_heads, int head_dim, int pos0, float rope_base, const void* kc, const void* vc,
+                        const int32_t* seg_len) {
   if (!k_new || !v_new || !kc || !vc || !seg_len) return PC_ERR_NULL;
   if (batch < 0 || n_new < 0 || n_seg < 1 || seg < 0 || seg >= n_seg || k_t < 1 || n_kv_heads < 1)
     return PC_ERR_SHAPE;
@@ -223,6 +222,16 @@ extern "C" int pc_kv_append(const void* k_new, const void* v_new, int32_t batch,
   if (!pc_aligned(k_new, 2) || !pc_aligned(v_new, 2) || !pc_aligned(kc, 2) || !pc_aligned(vc, 2) ||
       !pc_aligned(seg_len, 4))
     return PC_ERR_SHAPE;
+  return PC_OK;
+}
+
+extern "C" int pc_kv_append(const void* k_new, const void* v_new, int32_t batch, int32_t n_new,
+                            int32_t n_seg, int32_t seg, int32_t k_t, int32_t n_kv_heads,
+                            int32_t head_dim, int32_t pos0, float rope_base, void* kc, void* vc,
+                            int32_t* seg_len, int32_t seg_len_per_head, void* stream) {
+  const int rc = check_append(k_new, v_new, batch, n_new, n_seg, seg, k_t, n_kv_heads, head_dim, pos0, rope_base,
+                              kc, vc, seg_len);
+  if (rc != PC_OK) return rc;
   if (batch == 0 || n_new == 0) return PC_OK;
   return pc_launch_kv_append(k_new, v_new, batch, n_new, n_seg, seg, k_t, n_kv_heads, head_dim,
                              pos0, rope_base, kc, vc, seg_len, seg_len_per_head != 0,
@@ -272,6 +281,16 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
 // 158 -> 125; 16 / 1 heads, 300 sequences 1065 -> 914 / 424 -> 334.
 #define PC_DEC_ROT_WGS 512
 static bool rotate_first(int has_self, long long workgroups) { return has_self || workgroups > PC_DEC_ROT_WGS; }
+
+// A decoding step's part in the split-KV launch (k_new == nullptr: none).  kernel_pos < 0 at pos >= 0: the query
+// was rotated in front and the merge has it; otherwise the launch leaves the rotated row.
+static PcDecodeAppend step_append(const void* k_new, const void* v_new, int pos, int kernel_pos, void* q_rot, int32_t* self_row) {
+  PcDecodeAppend a = {};
+  if (!k_new) return a;
+  a.k_new = (const uint16_t*)k_new; a.v_new = (const uint16_t*)v_new; a.pos = pos; a.self_row = self_row;
+  if (kernel_pos >= 0) a.q_rot = (uint16_t*)q_rot;
+  return a;
+}
 
 // 64-key tiles of n segments of k_t keys
 static long long key_tiles(int n, int k_t) { return (long long)n * ((k_t + 63) / 64); }
@@ -353,6 +372,60 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
                                    int q_pos0, float rope_base, float scale, void* out, float* lse_out,
                                    const Par8Ws& w, char* base, hipStream_t st);
 
+static int check_par8_args(const void* q, const void* k8, const void* v8, const float* k_scale, const float* v_scale,
+                           int seg_len_per_head, const void* k_tail, const void* v_tail, const int32_t* tail_len,
+                           int tail_cap, const void* k_self, const void* v_self, int batch, int n_q, int n_seg, int k_t,
+                           int n_q_heads, int n_kv_heads, int head_dim, int q_pos0, float rope_base,
+                           float softmax_scale, const void* out) {
+  const int rc = check_par8(batch, n_q, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, head_dim);
+  if (rc != PC_OK) return rc;
+  if (!q || !out) return PC_ERR_NULL;
+  if (n_seg > 0 && (!k8 || !v8 || !k_scale || !v_scale)) return PC_ERR_NULL;
+  if (tail_cap > 0 && (!k_tail || !v_tail || !tail_len)) return PC_ERR_NULL;
+  if ((k_self == nullptr) != (v_self == nullptr)) return PC_ERR_NULL;
+  const int has_self = k_self != nullptr;
+  if (n_seg == 0 && tail_cap == 0 && !has_self) return PC_ERR_SHAPE;
+  if (seg_len_per_head != 0 && seg_len_per_head != 1) return PC_ERR_SHAPE;
+  if (q_pos0 >= 0 && (!(rope_base > 1.0f) || !isfinite(rope_base))) return PC_ERR_SHAPE;
+  if (!(softmax_scale >= 0.0f) || !isfinite(softmax_scale)) return PC_ERR_SHAPE;
+  if (n_seg > 0 && (!pc_aligned(k8, 16) || !pc_aligned(v8, 16))) return PC_ERR_SHAPE;
+  if (!pc_aligned(q, 16) || !pc_aligned(out, 16) || !pc_aligned(k_tail, 16) || !pc_aligned(v_tail, 16) ||
+      !pc_aligned(k_self, 16) || !pc_aligned(v_self, 16))
+    return PC_ERR_SHAPE;
+  return PC_OK;
+}
+
+// The few-row path over the 8-bit segments and the tail.  k_new, v_new: a decoding step, the tail's next row
+// (self_row: [batch, H_kv] scratch); tail_len then counts it.
+static int par8_small_run(const void* q, const void* k8, const void* v8, const float* k_scale, const float* v_scale,
+                          const int32_t* seg_len, int seg_len_per_head, const void* k_tail, const void* v_tail,
+                          const int32_t* tail_len, int tail_cap, const void* k_self, const void* v_self, int batch,
+                          int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads, int D, int q_pos0,
+                          float rope_base, float scale, void* out, float* lse_out, const Par8Ws& w, char* base,
+                          const void* k_new, const void* v_new, int32_t* self_row, hipStream_t st) {
+  const void* q_in = q;
+  int pos0 = q_pos0, rc;
+  if (q_pos0 >= 0 && rotate_first(k_self != nullptr, (long long)batch * n_kv_heads * w.parts8)) {
+    rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
+    if (rc != PC_OK) return rc;
+    q_in = base + w.q_rot; pos0 = -1;
+  }
+  float* part_o = (float*)(base + w.part_o);
+  float* part_lse = (float*)(base + w.part_lse);
+  const PcDecodeAppend app = step_append(k_new, v_new, q_pos0, pos0, base + w.q_rot, self_row);
+  if (n_seg > 0 || tail_cap > 0) {
+    rc = pc_launch_decode_fp8(q_in, pos0, rope_base, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head,
+                              k_tail, v_tail, tail_len, tail_cap, batch, n_q, n_seg, k_t, n_q_heads,
+                              n_kv_heads, D, scale, part_o, part_lse, w.n_parts, app, st);
+    if (rc != PC_OK) return rc;
+  }
+  PcMergeStep step = {};
+  if (k_new) step = PcMergeStep{self_row, (const uint16_t*)k_tail, (const uint16_t*)v_tail, (int32_t*)tail_len, 1, tail_cap, 0};
+  // the few-row causal self segment (if any) is evaluated inside the merge
+  return pc_launch_merge(part_o, part_lse, app.q_rot ? app.q_rot : q_in, k_self, v_self, step, out, lse_out, batch,
+                         n_q, n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
+}
+
 extern "C" size_t pc_parallel_attn_fp8_workspace_bytes(int32_t batch, int32_t n_q, int32_t n_seg,
                                                        int32_t k_t, int32_t tail_cap,
                                                        int32_t n_q_heads, int32_t n_kv_heads,
@@ -371,21 +444,11 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
                                     int32_t head_dim, int32_t q_pos0, float rope_base,
                                     float softmax_scale, void* out, float* lse_out, void* ws,
                                     size_t ws_bytes, void* stream) {
-  int rc = check_par8(batch, n_q, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, head_dim);
+  int rc = check_par8_args(q, k8, v8, k_scale, v_scale, seg_len_per_head, k_tail, v_tail, tail_len, tail_cap, k_self,
+                           v_self, batch, n_q, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, q_pos0, rope_base,
+                           softmax_scale, out);
   if (rc != PC_OK) return rc;
-  if (!q || !out) return PC_ERR_NULL;
-  if (n_seg > 0 && (!k8 || !v8 || !k_scale || !v_scale)) return PC_ERR_NULL;
-  if (tail_cap > 0 && (!k_tail || !v_tail || !tail_len)) return PC_ERR_NULL;
-  if ((k_self == nullptr) != (v_self == nullptr)) return PC_ERR_NULL;
   const int has_self = k_self != nullptr;
-  if (n_seg == 0 && tail_cap == 0 && !has_self) return PC_ERR_SHAPE;
-  if (seg_len_per_head != 0 && seg_len_per_head != 1) return PC_ERR_SHAPE;
-  if (q_pos0 >= 0 && (!(rope_base > 1.0f) || !isfinite(rope_base))) return PC_ERR_SHAPE;
-  if (!(softmax_scale >= 0.0f) || !isfinite(softmax_scale)) return PC_ERR_SHAPE;
-  if (n_seg > 0 && (!pc_aligned(k8, 16) || !pc_aligned(v8, 16))) return PC_ERR_SHAPE;
-  if (!pc_aligned(q, 16) || !pc_aligned(out, 16) || !pc_aligned(k_tail, 16) || !pc_aligned(v_tail, 16) ||
-      !pc_aligned(k_self, 16) || !pc_aligned(v_self, 16))
-    return PC_ERR_SHAPE;
   const int D = head_dim;
   const Par8Ws w = par8_ws_layout(batch, n_q, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, D, has_self);
   if (!ws || !pc_aligned(ws, kAlign) || ws_bytes < w.total) return PC_ERR_WORKSPACE;
@@ -399,24 +462,9 @@ extern "C" int pc_parallel_attn_fp8(const void* q, const void* k8, const void* v
                                    tail_len, tail_cap, k_self, v_self, batch, n_q, n_seg, k_t, n_q_heads,
                                    n_kv_heads, D, q_pos0, rope_base, scale, out, lse_out, w, base, st);
   }
-  const void* q_in = q;
-  int pos0 = q_pos0;
-  if (q_pos0 >= 0 && rotate_first(has_self, (long long)batch * n_kv_heads * w.parts8)) {
-    rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
-    if (rc != PC_OK) return rc;
-    q_in = base + w.q_rot; pos0 = -1;
-  }
-  float* part_o = (float*)(base + w.part_o);
-  float* part_lse = (float*)(base + w.part_lse);
-  if (n_seg > 0 || tail_cap > 0) {
-    rc = pc_launch_decode_fp8(q_in, pos0, rope_base, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head,
-                              k_tail, v_tail, tail_len, tail_cap, batch, n_q, n_seg, k_t, n_q_heads,
-                              n_kv_heads, D, scale, part_o, part_lse, w.n_parts, st);
-    if (rc != PC_OK) return rc;
-  }
-  // the few-row causal self segment (if any) is evaluated inside the merge
-  return pc_launch_merge(part_o, part_lse, q_in, k_self, v_self, out, lse_out, batch, n_q,
-                         n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
+  return par8_small_run(q, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, k_tail, v_tail, tail_len, tail_cap,
+                        k_self, v_self, batch, n_q, n_seg, k_t, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
+                        out, lse_out, w, base, nullptr, nullptr, nullptr, st);
 }
 
 extern "C" int pc_chunk_self_information(const void* logits, const int32_t* targets, int32_t n_chunks,
@@ -606,13 +654,15 @@ static int tile_attn_run(PcFlashArgs& a, const void* q, int batch, int n_q, int 
   return pc_launch_merge_rows(part_o, part_lse, out, lse_out, batch, n_q, n_q_heads, D, n_parts, st);
 }
 
-// Enqueues the kernels of Eq. 9-11 on a validated request; ws holds at least w.total bytes.
+// Enqueues the kernels of Eq. 9-11 on a validated request; ws holds at least w.total bytes.  k_new, v_new (few
+// rows only): a decoding step, the last segment's next row (self_row: [batch, H_kv] scratch); seg_len counts it.
 static int parallel_attn_run(const void* q, const void* kc, const void* vc, const int32_t* seg_len,
                              int32_t seg_len_per_head, const void* k_self, const void* v_self,
                              int32_t batch, int32_t n_q, int32_t n_seg, int32_t k_t,
                              int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                              int32_t q_pos0, float rope_base, float softmax_scale, void* out,
-                             float* lse_out, const ParWs& w, void* ws, void* stream) {
+                             float* lse_out, const ParWs& w, void* ws, const void* k_new, const void* v_new,
+                             int32_t* self_row, void* stream) {
   int rc;
   const int has_self = k_self != nullptr;
   const int D = head_dim;
@@ -632,13 +682,16 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
       if (rc != PC_OK) return rc;
       q_in = base + w.q_rot; pos0 = -1;
     }
+    const PcDecodeAppend app = step_append(k_new, v_new, q_pos0, pos0, base + w.q_rot, self_row);
     if (n_seg > 0) {
       rc = pc_launch_decode(q_in, pos0, rope_base, kc, vc, seg_len, seg_len_per_head, batch, n_q, n_seg, k_t,
-                            n_q_heads, n_kv_heads, D, scale, part_o, part_lse, w.n_parts, 0, st);
+                            n_q_heads, n_kv_heads, D, scale, part_o, part_lse, w.n_parts, 0, app, st);
       if (rc != PC_OK) return rc;
     }
-    return pc_launch_merge(part_o, part_lse, q_in, k_self, v_self, out, lse_out, batch, n_q,
-                           n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
+    PcMergeStep step = {};
+    if (k_new) step = PcMergeStep{self_row, (const uint16_t*)kc, (const uint16_t*)vc, (int32_t*)seg_len, n_seg, k_t, seg_len_per_head};
+    return pc_launch_merge(part_o, part_lse, app.q_rot ? app.q_rot : q_in, k_self, v_self, step, out, lse_out, batch,
+                           n_q, n_q_heads, n_kv_heads, D, w.n_parts, scale, st);
   }
 
   // ---- many query rows: MFMA tile kernel over [segments ; causal self segment]
@@ -689,7 +742,81 @@ extern "C" int pc_parallel_attn(const void* q, const void* kc, const void* vc, c
   if (!ws || !pc_aligned(ws, kAlign) || ws_bytes < w.total) return PC_ERR_WORKSPACE;
   return parallel_attn_run(q, kc, vc, seg_len, seg_len_per_head, k_self, v_self, batch, n_q, n_seg,
                            k_t, n_q_heads, n_kv_heads, head_dim, q_pos0, rope_base, softmax_scale,
-                           out, lse_out, w, ws, stream);
+                           out, lse_out, w, ws, nullptr, nullptr, nullptr, stream);
+}
+
+// ---------------------------------------------------------------------------- decoding step
+// pc_kv_append of one row + the attention of one row, as two launches: the split-KV kernel stores the new row
+// (its lengths still exclude it) and the merge takes it as one more key and counts it.
+// [batch, H_kv] int32 behind the attention's workspace
+static size_t self_row_bytes(int batch, int n_kv_heads) { return pc_align_up((size_t)batch * n_kv_heads * 4, kAlign); }
+
+extern "C" size_t pc_decode_step_workspace_bytes(int32_t batch, int32_t n_seg, int32_t k_t, int32_t n_q_heads,
+                                                 int32_t n_kv_heads, int32_t head_dim) {
+  const size_t attn = pc_parallel_attn_workspace_bytes(batch, 1, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, 0);
+  return attn ? attn + self_row_bytes(batch, n_kv_heads) : 0;
+}
+
+extern "C" int pc_decode_step(const void* q, const void* k_new, const void* v_new, int32_t batch, int32_t n_seg,
+                              int32_t k_t, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t pos,
+                              float rope_base, float softmax_scale, void* kc, void* vc, int32_t* seg_len,
+                              int32_t seg_len_per_head, void* out, float* lse_out, void* ws, size_t ws_bytes,
+                              void* stream) {
+  int rc = check_append(k_new, v_new, batch, 1, n_seg, n_seg - 1, k_t, n_kv_heads, head_dim, pos, rope_base, kc, vc, seg_len);
+  if (rc != PC_OK) return rc;
+  rc = check_par_args(q, kc, vc, seg_len_per_head, nullptr, nullptr, batch, 1, n_seg, k_t, n_q_heads, n_kv_heads,
+                      head_dim, pos, rope_base, softmax_scale, out);
+  if (rc != PC_OK) return rc;
+  const ParWs w = par_ws_layout(batch, 1, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, 0);
+  if (!ws || !pc_aligned(ws, kAlign) || ws_bytes < w.total + self_row_bytes(batch, n_kv_heads)) return PC_ERR_WORKSPACE;
+  if (!w.small) {                                            // more than 16 heads a group: the tile path
+    rc = check_tile_limits(n_seg, k_t, 0, n_kv_heads, 0);
+    if (rc == PC_OK)
+      rc = pc_launch_kv_append(k_new, v_new, batch, 1, n_seg, n_seg - 1, k_t, n_kv_heads, head_dim, pos, rope_base,
+                               kc, vc, seg_len, seg_len_per_head, (hipStream_t)stream);
+    if (rc != PC_OK) return rc;
+    k_new = v_new = nullptr;
+  }
+  return parallel_attn_run(q, kc, vc, seg_len, seg_len_per_head, nullptr, nullptr, batch, 1, n_seg, k_t, n_q_heads,
+                           n_kv_heads, head_dim, pos, rope_base, softmax_scale, out, lse_out, w, ws, k_new, v_new,
+                           (int32_t*)((char*)ws + w.total), stream);
+}
+
+extern "C" size_t pc_decode_step_fp8_workspace_bytes(int32_t batch, int32_t n_seg, int32_t k_t, int32_t tail_cap,
+                                                     int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim) {
+  const size_t attn = pc_parallel_attn_fp8_workspace_bytes(batch, 1, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, head_dim, 0);
+  return attn ? attn + self_row_bytes(batch, n_kv_heads) : 0;
+}
+
+extern "C" int pc_decode_step_fp8(const void* q, const void* k_new, const void* v_new, const void* k8, const void* v8,
+                                  const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                                  int32_t seg_len_per_head, void* k_tail, void* v_tail, int32_t* tail_len,
+                                  int32_t tail_cap, int32_t batch, int32_t n_seg, int32_t k_t, int32_t n_q_heads,
+                                  int32_t n_kv_heads, int32_t head_dim, int32_t pos, float rope_base,
+                                  float softmax_scale, void* out, float* lse_out, void* ws, size_t ws_bytes,
+                                  void* stream) {
+  int rc = check_append(k_new, v_new, batch, 1, 1, 0, tail_cap, n_kv_heads, head_dim, pos, rope_base, k_tail, v_tail, tail_len);
+  if (rc != PC_OK) return rc;
+  rc = check_par8_args(q, k8, v8, k_scale, v_scale, seg_len_per_head, k_tail, v_tail, tail_len, tail_cap, nullptr,
+                       nullptr, batch, 1, n_seg, k_t, n_q_heads, n_kv_heads, head_dim, pos, rope_base, softmax_scale, out);
+  if (rc != PC_OK) return rc;
+  const int D = head_dim;
+  const Par8Ws w = par8_ws_layout(batch, 1, n_seg, k_t, tail_cap, n_q_heads, n_kv_heads, D, 0);
+  if (!ws || !pc_aligned(ws, kAlign) || ws_bytes < w.total + self_row_bytes(batch, n_kv_heads)) return PC_ERR_WORKSPACE;
+  const float scale = eff_scale(softmax_scale, D);
+  hipStream_t st = (hipStream_t)stream;
+  if (w.small)
+    return par8_small_run(q, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, k_tail, v_tail, tail_len, tail_cap,
+                          nullptr, nullptr, batch, 1, n_seg, k_t, n_q_heads, n_kv_heads, D, pos, rope_base, scale, out,
+                          lse_out, w, (char*)ws, k_new, v_new, (int32_t*)((char*)ws + w.total), st);
+  rc = check_tile_limits(n_seg, k_t, tail_cap, n_kv_heads, 0);
+  if (rc == PC_OK)
+    rc = pc_launch_kv_append(k_new, v_new, batch, 1, 1, 0, tail_cap, n_kv_heads, D, pos, rope_base, k_tail, v_tail,
+                             tail_len, 0, st);
+  if (rc != PC_OK) return rc;
+  return parallel_attn_fp8_tiles(q, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, k_tail, v_tail, tail_len,
+                                 tail_cap, nullptr, nullptr, batch, 1, n_seg, k_t, n_q_heads, n_kv_heads, D, pos,
+                                 rope_base, scale, out, lse_out, w, (char*)ws, st);
 }
 
 // ---------------------------------------------------------------------------- no-allocation variant
@@ -742,5 +869,5 @@ extern "C" int pc_parallel_attn_static(const void* q, const void* kc, const void
   // (rotated q, one partial per workgroup), so nothing has to be cleared
   return parallel_attn_run(q, kc, vc, seg_len, seg_len_per_head, k_self, v_self, batch, n_q, n_seg,
                            k_t, n_q_heads, n_kv_heads, head_dim, q_pos0, rope_base, softmax_scale,
-                           out, lse_out, w, ws, stream);
+                           out, lse_out, w, ws, nullptr, nullptr, nullptr, stream);
 }

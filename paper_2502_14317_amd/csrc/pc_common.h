@@ -1,6 +1,7 @@
 // Internal helpers shared by the HIP translation units of the ParallelComp library (gfx950).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include "parallelcomp.h"
 #include "parallelcomp_bench.h"
@@ -70,6 +71,55 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return *(uint32_t*)&r;
 }
 
+// ---------------------------------------------------------------- rotation angles
+// RoPE angles in 64 bits: theta_i = base^(-2 i / D) for i < D / 2 as the product of the factors of i's
+// set bits, f[b] = base^(-2 2^b / D) from the host; angle = position * theta_i.  Written out here because
+// the math library's exp and sincos (2 KB of code each, with the branch for huge arguments) were most of
+// the time of the small launches and of every decode workgroup's start.  Relative error of theta below 1e-15
+// (exp of a rounded product: up to 3e-15), of the reduced sine and cosine below 2e-16 absolute.
+struct PcRope { double f[6]; };
+static inline PcRope pc_rope_factors(float base, int head_dim) {
+  PcRope r;
+  for (int b = 0; b < 6; ++b) r.f[b] = pow((double)base, -2.0 * (double)(1 << b) / (double)head_dim);
+  return r;
+}
+__host__ __device__ __forceinline__ double pc_rope_theta(const PcRope& r, int i) {
+  double t = 1.0;
+#pragma unroll
+  for (int b = 0; b < 6; ++b) t *= (i >> b) & 1 ? r.f[b] : 1.0;
+  return t;
+}
+// sine and cosine of x, 0 <= x < 2^31: reduction by multiples of pi / 2 (Cody and Waite: two parts of pi / 2,
+// each product exact in the fused multiply-add), then the Taylor polynomials on [-pi / 4, pi / 4]
+__host__ __device__ __forceinline__ void pc_sincos(double x, double& sn, double& cs) {
+  const double n = rint(x * 0.63661977236758134308);               // 2 / pi
+  const double r = fma(-n, 6.123233995736766e-17, fma(-n, 1.5707963267948966, x));
+  const int quadrant = (int)(unsigned)n;
+  const double z = r * r;
+  double s = -1.0 / 1307674368000.0;                               // 1 / 15!
+  s = fma(s, z, 1.0 / 6227020800.0);
+  s = fma(s, z, -1.0 / 39916800.0);
+  s = fma(s, z, 1.0 / 362880.0);
+  s = fma(s, z, -1.0 / 5040.0);
+  s = fma(s, z, 1.0 / 120.0);
+  s = fma(s, z, -1.0 / 6.0);
+  s = fma(s * z, r, r);
+  double c = 1.0 / 20922789888000.0;                               // 1 / 16!
+  c = fma(c, z, -1.0 / 87178291200.0);
+  c = fma(c, z, 1.0 / 479001600.0);
+  c = fma(c, z, -1.0 / 3628800.0);
+  c = fma(c, z, 1.0 / 40320.0);
+  c = fma(c, z, -1.0 / 720.0);
+  c = fma(c, z, 1.0 / 24.0);
+  c = fma(c, z, -0.5);
+  c = fma(c, z, 1.0);
+  const double a = quadrant & 1 ? c : s, b = quadrant & 1 ? s : c;
+  sn = quadrant & 2 ? -a : a;
+  cs = (quadrant + 1) & 2 ? -b : b;
+}
+
+#define PC_BUF_NT 2        // the same hint on a buffer load
+
 // 16-byte global load / store of data that is touched once (streamed): the non-temporal hint
 // keeps it from displacing reusable lines in the caches
 __device__ __forceinline__ uint4 pc_load_once(const uint4* p) {
@@ -94,6 +144,19 @@ __device__ __forceinline__ float pc_xhalf_sum(float x) {
   const unsigned u = __float_as_uint(x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The same between lane l and lane l ^ 16 (v_permlane16_swap exchanges neighbouring rows of 16 lanes): max and sum
+// over the four lanes l % 16 + 16 i, left in all of them.
+__device__ __forceinline__ float pc_rows_max(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return pc_xhalf_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float pc_rows_sum(float x) {
+  const unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return pc_xhalf_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 // fp32 score -> uint32 key whose unsigned order is the float order; NaN -> 0 (below everything),
@@ -233,61 +296,70 @@ struct PcSegLens {
   }
 };
 struct PcBlockCursor {
-  int s, blk, n_blk, len, left;   // segment, block within it, its block count and length, blocks left in the run
-  bool valid;
+  int s, blk, n_blk, len, left;   // segment, block within it, its block count and length, blocks left in the run (0: behind its end)
 };
-__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts,
-                                                         int wave, int n_waves, int lane) {
-  PcBlockCursor c; c.s = 0; c.blk = 0; c.n_blk = 0; c.len = 0; c.left = 0; c.valid = false;
+// inclusive prefix sum over the wavefront's lanes (row shifts, then the rows' totals broadcast onwards)
+__device__ __forceinline__ int pc_wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);    // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);    // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);    // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);    // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);    // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);    // row_bcast:31
+  return x;
+}
+// Runs as equal as possible: the first total % n of n runs hold a block more.  32 bits are enough for
+// what fits in memory (a block of a group is at least 2 KiB of keys).
+__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, int wave, int lane) {
+  constexpr int WAVES = 4;
+  PcBlockCursor c; c.s = 0; c.blk = 0; c.n_blk = 0; c.len = 0; c.left = 0;
   const int nb_full = (L.k_t + 31) / 32;
-  long long total = 0;
+  // lanes take a segment each, 64 segments per round; up to 64 segments the one round is kept
+  int total = 0, len = 0, nb = 0, incl = 0;
   if (!L.seg_len) {
-    total = (long long)L.n_seg * nb_full;
+    total = L.n_seg * nb_full;
   } else {
-    // lanes take a segment each, 64 segments per round
     for (int s0 = 0; s0 < L.n_seg; s0 += PC_WAVE) {
-      int nb = s0 + lane < L.n_seg ? (L.len(s0 + lane) + 31) / 32 : 0;
-#pragma unroll
-      for (int off = PC_WAVE / 2; off > 0; off >>= 1) nb += __shfl_xor(nb, off);
-      total += __builtin_amdgcn_readfirstlane(nb);
+      len = s0 + lane < L.n_seg ? L.len(s0 + lane) : 0;
+      nb = (len + 31) / 32;
+      incl = pc_wave_scan(nb);
+      total += __builtin_amdgcn_readlane(incl, PC_WAVE - 1);
     }
   }
-  const long long lo = total * part / n_parts, hi = total * (part + 1) / n_parts;
-  const long long w_lo = lo + (hi - lo) * wave / n_waves, w_hi = lo + (hi - lo) * (wave + 1) / n_waves;
+  const int per = total / n_parts, extra = total % n_parts;
+  const int lo = part * per + min(part, extra), n = per + (part < extra);
+  const int w_lo = lo + n * wave / WAVES, w_hi = lo + n * (wave + 1) / WAVES;
   if (w_lo >= w_hi) return c;
-  c.left = (int)(w_hi - w_lo);
+  c.left = w_hi - w_lo;
   if (!L.seg_len) {
-    c.s = (int)(w_lo / nb_full); c.blk = (int)(w_lo % nb_full); c.n_blk = nb_full; c.len = L.k_t;
-    c.valid = true;
+    c.s = w_lo / nb_full; c.blk = w_lo % nb_full; c.n_blk = nb_full; c.len = L.k_t;
     return c;
   }
-  long long base = 0;
+  int base = 0;
   for (int s0 = 0; s0 < L.n_seg; s0 += PC_WAVE) {
-    const int len = s0 + lane < L.n_seg ? L.len(s0 + lane) : 0;
-    const int nb = (len + 31) / 32;
-    int incl = nb;                                            // inclusive prefix sum over the lanes
-#pragma unroll
-    for (int off = 1; off < PC_WAVE; off <<= 1) {
-      const int up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
+    if (L.n_seg > PC_WAVE) {
+      len = s0 + lane < L.n_seg ? L.len(s0 + lane) : 0;
+      nb = (len + 31) / 32;
+      incl = pc_wave_scan(nb);
     }
-    const long long rel = w_lo - base;                        // the run's first block, counted from this round's first segment
+    const int rel = w_lo - base;                              // the run's first block, counted from this round's first segment
     const unsigned long long hit = __ballot(nb > 0 && incl - nb <= rel && rel < incl);
     if (hit) {
       const int src = __ffsll((long long)hit) - 1;
       c.s = s0 + src;
-      c.blk = __builtin_amdgcn_readfirstlane((int)rel - __shfl(incl - nb, src));
-      c.n_blk = __builtin_amdgcn_readfirstlane(__shfl(nb, src));
-      c.len = __builtin_amdgcn_readfirstlane(__shfl(len, src));
-      c.valid = true;
+      c.n_blk = __builtin_amdgcn_readlane(nb, src);
+      c.blk = rel - (__builtin_amdgcn_readlane(incl, src) - c.n_blk);
+      c.len = __builtin_amdgcn_readlane(len, src);
       return c;
     }
-    base += __builtin_amdgcn_readfirstlane(__shfl(incl, PC_WAVE - 1));
+    base += __builtin_amdgcn_readlane(incl, PC_WAVE - 1);
   }
+  c.left = 0;
   return c;                                                   // not reached: w_lo < total
 }
 __device__ __forceinline__ PcBlockCursor pc_blocks_next(const PcSegLens& L, PcBlockCursor c) {
-  if (--c.left <= 0) { c.valid = false; return c; }
+  if (c.left <= 1) { c.left = 0; return c; }
+  --c.left;
   if (++c.blk < c.n_blk) return c;
   c.blk = 0;
   for (++c.s; c.s < L.n_seg; ++c.s) {                         // the next segment that has keys
@@ -295,18 +367,28 @@ __device__ __forceinline__ PcBlockCursor pc_blocks_next(const PcSegLens& L, PcBl
     c.n_blk = (c.len + 31) / 32;
     if (c.n_blk > 0) return c;
   }
-  c.valid = false;                                            // not reached: left counted real blocks
+  c.left = 0;                                                 // not reached: left counted real blocks
   return c;
 }
 int pc_launch_kv_append(const void* k_new, const void* v_new, int batch, int n_new, int n_seg,
                         int seg, int k_t, int n_kv_heads, int head_dim, int pos0, float base,
                         void* kc, void* vc, int32_t* seg_len, int seg_len_per_head,
                         hipStream_t st);
+struct PcDecodeAppend;     // decode_core.h; default: no step
+// A decoding step in the merge: the new token's row of the last of n_seg segments [.., H_kv, cap, D] (one more
+// key, where self_row >= 0), and the lengths [B, n_seg] ([B, n_seg, H_kv] if len_per_head) that count it
+struct PcMergeStep {
+  const int32_t* self_row; // [B, H_kv] or nullptr: no step
+  const uint16_t* k;
+  const uint16_t* v;
+  int32_t* seg_len;
+  int n_seg, cap, len_per_head;
+};
 // q: rotated by the kernel at positions pos0 + t (pos0 < 0: it arrives rotated)
 int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const void* vc,
                      const int32_t* seg_len, int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                      int head_dim, float scale, float* part_o, float* part_lse, int n_parts, int part0,
-                     hipStream_t st);
+                     const PcDecodeAppend& app, hipStream_t st);
 // k_amax, v_amax [n_segs] (both or neither): the largest |value| of every segment's valid rows,
 // known beforehand (the gather leaves it): the kernel then reads the segment once
 int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg_len,
@@ -324,11 +406,11 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
                          const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
                          int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
-                         float* part_lse, int n_parts, hipStream_t st);
+                         float* part_lse, int n_parts, const PcDecodeAppend& app, hipStream_t st);
 // Merge of the tile kernel's partials [batch, n_parts, n_q, H_q, D] (no self segment)
 int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, float* lse_out, int batch,
                          int n_q, int n_q_heads, int head_dim, int n_parts, hipStream_t st);
 int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_rot,
-                    const void* k_self, const void* v_self, void* out, float* lse_out, int batch,
-                    int n_q, int n_q_heads, int n_kv_heads, int head_dim, int n_parts, float scale,
+                    const void* k_self, const void* v_self, const PcMergeStep& step, void* out, float* lse_out,
+                    int batch, int n_q, int n_q_heads, int n_kv_heads, int head_dim, int n_parts, float scale,
                     hipStream_t st);

@@ -43,14 +43,13 @@
 #define PC_LN2 0.6931471805599453f
 
 // ------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(float2* __restrict__ table, int n_pos, int D, double log_base) {
+__global__ void rope_table_kernel(float2* __restrict__ table, int n_pos, int D, PcRope rope) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   const int half = D / 2;
   if (idx >= n_pos * half) return;
   const int p = idx / half, i = idx % half;
-  const double theta = exp(-2.0 * (double)i / (double)D * log_base);
   double sn, cs;
-  sincos((double)p * theta, &sn, &cs);
+  pc_sincos((double)p * pc_rope_theta(rope, i), sn, cs);
   table[idx] = make_float2((float)cs, (float)sn);
 }
 
@@ -58,7 +57,7 @@ int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hip
   const int n = n_pos * (head_dim / 2);
   PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
   hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, n_pos,
-                     head_dim, log((double)base));
+                     head_dim, pc_rope_factors(base, head_dim));
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

@@ -165,9 +165,9 @@ class DecodeCache:
     """The decoding stage (sec. 3.1, Eq. 9-11 token by token): the compressed segments of B
     sequences plus one tail segment that starts as the query block's keys / values and grows by
     one row per generated token.  Segment lengths live on the device and are advanced by
-    pc_kv_append, so a run of decode steps is a run of library calls with no host round trip.
-    A step = pc_kv_append (rotate and store the new token's K, V) + pc_parallel_attn (the new
-    token's query over [segments ; tail], itself included)."""
+    the steps, so a run of decode steps is a run of library calls with no host round trip.
+    A step = pc_decode_step: rotate and store the new token's K, V, then its query over
+    [segments ; tail], itself included."""
 
     def __init__(self, batch, n_seg, keep_tokens, n_q_heads, n_kv_heads, head_dim, rope_base,
                  softmax_scale=0.0, device="cuda"):
@@ -180,8 +180,8 @@ class DecodeCache:
         self.seg_len = torch.zeros((batch, self.S), dtype=i32, device=device)
         self.out = torch.empty((batch, 1, n_q_heads, head_dim), dtype=bf, device=device)
         self.lse = torch.empty((batch, n_q_heads, 1), dtype=torch.float32, device=device)
-        self.ws = B.alloc_workspace(B.pc_parallel_attn_workspace_bytes(
-            batch, 1, self.S, keep_tokens, n_q_heads, n_kv_heads, head_dim, False), device)
+        self.ws = B.alloc_workspace(B.pc_decode_step_workspace_bytes(
+            batch, self.S, keep_tokens, n_q_heads, n_kv_heads, head_dim), device)
 
     def load(self, kc, vc, seg_len, k_tail, v_tail):
         """kc, vc [B, n_seg, H_kv, k_t, D] compacted segments (plain copies into the cache),
@@ -200,11 +200,8 @@ class DecodeCache:
     def step(self, q_new, k_new, v_new, pos):
         """q_new [B, 1, H_q, D], k_new, v_new [B, 1, H_kv, D] before RoPE; pos = the token's
         position (continues behind the query block).  Returns out [B, 1, H_q, D]."""
-        B.pc_kv_append(k_new, v_new, self.B, 1, self.S, self.S - 1, self.kt, self.Hkv, self.D, pos,
-                       self.rope_base, self.kc, self.vc, self.seg_len)
-        B.pc_parallel_attn(q_new, self.kc, self.vc, self.seg_len, None, None, self.B, 1, self.S,
-                           self.kt, self.Hq, self.Hkv, self.D, pos, self.rope_base, self.scale,
-                           self.out, self.lse, self.ws)
+        B.pc_decode_step(q_new, k_new, v_new, self.B, self.S, self.kt, self.Hq, self.Hkv, self.D, pos,
+                         self.rope_base, self.scale, self.kc, self.vc, self.seg_len, self.out, self.lse, self.ws)
         return self.out
 
 
@@ -223,7 +220,7 @@ class DecodeCacheFp8:
     """DecodeCache with the compressed segments stored in 8 bits (E4M3 codes + one scale per
     sequence, segment and KV head, written once by pc_kv_quantize_fp8 when the cache is loaded)
     and the growing tail kept in bf16 as a one-segment cache of its own.  A step =
-    pc_kv_append on the tail + pc_parallel_attn_fp8 over [8-bit segments ; tail]."""
+    pc_decode_step_fp8: append to the tail, attend over [8-bit segments ; tail]."""
 
     def __init__(self, batch, n_seg, keep_tokens, tail_cap, n_q_heads, n_kv_heads, head_dim, rope_base,
                  softmax_scale=0.0, device="cuda"):
@@ -241,8 +238,8 @@ class DecodeCacheFp8:
         self.tail_len = torch.zeros((batch, 1), dtype=i32, device=device)
         self.out = torch.empty((batch, 1, n_q_heads, head_dim), dtype=bf, device=device)
         self.lse = torch.empty((batch, n_q_heads, 1), dtype=f32, device=device)
-        self.ws = B.alloc_workspace(B.pc_parallel_attn_fp8_workspace_bytes(
-            batch, 1, n_seg, keep_tokens, tail_cap, n_q_heads, n_kv_heads, head_dim), device)
+        self.ws = B.alloc_workspace(B.pc_decode_step_fp8_workspace_bytes(
+            batch, n_seg, keep_tokens, tail_cap, n_q_heads, n_kv_heads, head_dim), device)
 
     def load(self, kc, vc, seg_len, k_tail, v_tail):
         """kc, vc [B, n_seg, H_kv, k_t, D] bf16 compacted segments (quantised here), seg_len
@@ -258,10 +255,7 @@ class DecodeCacheFp8:
                        self.rope_base, self.k_tail, self.v_tail, self.tail_len)
 
     def step(self, q_new, k_new, v_new, pos):
-        B.pc_kv_append(k_new, v_new, self.B, 1, 1, 0, self.cap, self.Hkv, self.D, pos, self.rope_base,
-                       self.k_tail, self.v_tail, self.tail_len)
-        B.pc_parallel_attn_fp8(q_new, self.k8, self.v8, self.k_scale, self.v_scale, self.seg_len,
-                               self.k_tail, self.v_tail, self.tail_len, self.cap, self.B, 1, self.S,
-                               self.kt, self.Hq, self.Hkv, self.D, pos, self.rope_base, self.scale,
-                               self.out, self.lse, self.ws)
+        B.pc_decode_step_fp8(q_new, k_new, v_new, self.k8, self.v8, self.k_scale, self.v_scale, self.seg_len,
+                             self.k_tail, self.v_tail, self.tail_len, self.cap, self.B, self.S, self.kt, self.Hq,
+                             self.Hkv, self.D, pos, self.rope_base, self.scale, self.out, self.lse, self.ws)
         return self.out
