@@ -10,14 +10,14 @@
 //     16-byte loads, the next 32 keys already in flight while the current ones are used;
 //   * the query columns of one KV group (n_q * G <= 16) form the N side of a 16x16x32 bf16
 //     MFMA: S^T = K Q^T, so the lane that owns a column owns its running max and sum;
-//   * P V runs on the vector ALUs in the layout the V loads arrive in (D across lanes), with
-//     the probabilities broadcast through a small per-wavefront LDS tile;
+//   * P V runs on the same MFMA, V transposed in registers, P as two bf16 halves (hi + lo);
 //   * partial (o, lse) per workgroup go to the workspace; a second kernel merges them.
 #include "decode_core.h"
 
-template <int D, int NQ>
+template <int D>
 __global__ __launch_bounds__(PC_DEC_WAVES * PC_WAVE) void decode_attn_kernel(PcDecodeArgs a) {
-  pc_decode_workgroup<D, NQ>(a, blockIdx.x);
+  __shared__ PcDecodeLds<D> sm;
+  pc_decode_workgroup<D>(a, blockIdx.x, sm);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -332,15 +332,13 @@ int pc_launch_kv_append(const void* k_new, const void* v_new, int batch, int n_n
 }
 
 template <int D>
-static int launch_decode_d(const PcDecodeArgs& a, int batch, int nq_pad, hipStream_t st) {
+static int launch_decode_d(const PcDecodeArgs& a, int batch, hipStream_t st) {
   const long long blocks = (long long)batch * a.n_kv_heads * a.parts_grid;
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   dim3 grid((unsigned)blocks), block(PC_DEC_WAVES * PC_WAVE);
   PcProfScope prof(PC_KERNEL_DECODE, st);
-  if (nq_pad == 4) hipLaunchKernelGGL((decode_attn_kernel<D, 4>), grid, block, 0, st, a);
-  else if (nq_pad == 8) hipLaunchKernelGGL((decode_attn_kernel<D, 8>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((decode_attn_kernel<D, 16>), grid, block, 0, st, a);
+  hipLaunchKernelGGL(decode_attn_kernel<D>, grid, block, 0, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
@@ -378,10 +376,7 @@ int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const 
   const PcDecodeArgs a = pc_decode_args(pc_decode_query(q, pos0, base, n_q, n_q_heads, head_dim), kc, vc, seg_len,
                                         seg_len_per_head, batch, n_seg, k_t, n_kv_heads, scale, part_o,
                                         part_lse, n_parts, part0, app);
-  const int cols = n_q * (n_q_heads / n_kv_heads);
-  const int nq_pad = cols <= 4 ? 4 : (cols <= 8 ? 8 : 16);
-  return head_dim == 128 ? launch_decode_d<128>(a, batch, nq_pad, st)
-                         : launch_decode_d<64>(a, batch, nq_pad, st);
+  return head_dim == 128 ? launch_decode_d<128>(a, batch, st) : launch_decode_d<64>(a, batch, st);
 }
 
 int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_rot,

@@ -276,8 +276,8 @@ int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, 
 // 65 541 / 344, 100 417 / 376; 16 / 1 heads, 200 sequences 275 / 183; head_dim 64, 64 / 4 heads, 130
 // sequences 486 / 227.
 #define PC_D8_TAIL_WGS 256
-template <int D, int NQ>
-__device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid) {
+template <int D>
+__device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid, PcDecodeLds<D>& sm) {
   constexpr int KSTEPS = D / 32;            // MFMA k-steps; a lane owns 8 KSTEPS = D / 4 bytes of each of its K rows
   constexpr int KQ = D / 64;                // 16-byte loads per lane and 16-key block
   constexpr int VLOADS = D / 32;            // 1 KiB pieces of a V block: one 16-byte load per lane each
@@ -285,12 +285,8 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   constexpr int KBLK = PC_D8_ITER_KEYS / 16;
   static_assert(KBLK == 2, "the V block layout assumes two 16-key logit tiles per block");
 
-  __shared__ float red_o[PC_D8_WAVES][NQ][D];
-  __shared__ float red_m[PC_D8_WAVES][NQ], red_l[PC_D8_WAVES][NQ];
-  __shared__ __attribute__((aligned(16))) uint16_t q_lds[NQ][D];
-
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int n_cols = a.n_q * G;             // valid query columns (<= NQ)
+  const int n_cols = a.n_q * G;             // valid query columns (<= 16)
   const int lane = threadIdx.x % PC_WAVE, wave = threadIdx.x / PC_WAVE;
   const int kk = lane / 16, c16 = lane % 16;
 
@@ -353,7 +349,6 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   };
 
   auto consume = [&](int buf, const Cursor& cur) {
-    const int key0 = 32 * cur.at.blk, w_end = cur.at.len;
     // (the product here, not in the cursor: a vector register written between a block's loads and its
     // arithmetic can be one that a load behind the run's end has yet to fill, and costs a wait for all)
     const float k_sc = cur.k_sc * a.scale_log2, v_sc = cur.v_sc;           // logits in log2 units
@@ -372,41 +367,15 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
         acc[bi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&kb16, bq[j], acc[bi], 0, 0, 0);
       }
     }
-    float sv[KBLK][4];
-    float bmax = -INFINITY;
-#pragma unroll
-    for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sv[bi][j] = acc[bi][j] * k_sc;
-    if (key0 + 32 > w_end) {                         // a segment's last block
-#pragma unroll
-      for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (key0 + 16 * bi + 4 * kk + j >= w_end) sv[bi][j] = -INFINITY;
-    }
-#pragma unroll
-    for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bmax = fmaxf(bmax, sv[bi][j]);
-    bmax = pc_rows_max(bmax);
-    const float m_new = fmaxf(m_run, bmax);          // finite: every block holds a valid key
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // arguments <= 0: the bare instruction
-    m_run = m_new;
-    float psum = 0.f;
+    float pr[KBLK][4], alpha;
+    pc_decode_softmax(acc, k_sc, min(32, cur.at.len - 32 * cur.at.blk), kk, m_run, l_run, alpha, pr);
     // P^T as the B operand: this lane's 8 probabilities are k-slice kk of column c16, in the
     // key order of the V block layout; the V scale rides on them (not on the row sum)
     u32x4 pb;
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(sv[bi][j] - m_new);
-        const float p1 = __builtin_amdgcn_exp2f(sv[bi][j + 1] - m_new);
-        psum += p0 + p1;
-        pb[2 * bi + j / 2] = pack_bf16x2(p0 * v_sc, p1 * v_sc);
-      }
-    l_run = l_run * alpha + psum;
+      for (int j = 0; j < 4; j += 2) pb[2 * bi + j / 2] = pack_bf16x2(pr[bi][j] * v_sc, pr[bi][j + 1] * v_sc);
     if (__any(alpha != 1.0f)) {                      // some column's maximum grew (rare after the first keys)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
@@ -432,11 +401,11 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   Cursor c1 = next(c0);
   issue_loads(0, c0);
   issue_loads(1, c1);
-  rot.finish(a.query, b, g, G, n_cols, q_lds);
+  rot.finish(a.query, b, g, G, n_cols, sm.q);
   PC_LDS_BARRIER();
 #pragma unroll
   for (int j = 0; j < KSTEPS; ++j) {
-    u32x4 raw = *(const u32x4*)(q_lds[min(c16, n_cols - 1)] + 64 * (j / 2) + 16 * kk + 8 * (j % 2));
+    u32x4 raw = *(const u32x4*)(sm.q[min(c16, n_cols - 1)] + 64 * (j / 2) + 16 * kk + 8 * (j % 2));
     if (c16 >= n_cols) raw = u32x4{0, 0, 0, 0};
     bq[j] = *(bf16x8*)&raw;
   }
@@ -455,54 +424,33 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
     iter(2, 1);
   }
 
-  // ---- wavefront totals: sum the per-lane shares
+  // ---- wavefront totals, then one partial per workgroup
   l_run = pc_rows_sum(l_run);
-  if (kk == 0 && c16 < NQ) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
-  if (c16 < NQ) {
+  if (kk == 0) { sm.m[wave][c16] = m_run; sm.l[wave][c16] = l_run; }
+  if (c16 < n_cols) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red_o[wave][c16][16 * mb + 4 * kk + r] = o_acc[mb][r];
+    for (int mb = 0; mb < MB; ++mb) *(floatx4*)&sm.o[wave][c16][16 * mb + 4 * kk] = o_acc[mb];
   }
-  __syncthreads();
-
-  // ---- merge the 4 wavefronts, write one partial per workgroup (values scaled back)
-  for (int idx = threadIdx.x; idx < n_cols * D; idx += blockDim.x) {
-    const int n = idx / D, d = idx % D;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < PC_D8_WAVES; ++w) M = fmaxf(M, red_m[w][n]);
-    float num = 0.f, den = 0.f;
-    if (M > -INFINITY) {
-#pragma unroll
-      for (int w = 0; w < PC_D8_WAVES; ++w) {
-        const float sc = exp2f(red_m[w][n] - M);
-        num += sc * red_o[w][n][d];
-        den += sc * red_l[w][n];
-      }
-    }
-    const int t = n / G, hg = n % G;
-    const long long row = (((long long)b * a.n_parts + part) * a.n_q + t) * a.n_q_heads + g * G + hg;
-    a.part_o[row * D + d] = (den > 0.f) ? num / den : 0.f;
-    if (d == 0) a.part_lse[row] = (den > 0.f) ? (M + log2f(den)) * 0.6931471805599453f : -INFINITY;
-  }
+  pc_write_partial<D>(sm, G, n_cols, a.n_q, a.n_q_heads, (long long)b * a.n_parts + part, g, a.part_o, a.part_lse);
 }
 
-template <int D, int NQ>
+template <int D>
 __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_kernel(PcDecode8Args a) {
-  decode8_workgroup<D, NQ>(a, blockIdx.x);
+  __shared__ PcDecodeLds<D> sm;
+  decode8_workgroup<D>(a, blockIdx.x, sm);
 }
-template <int D, int NQ>
+template <int D>
 __global__ __launch_bounds__(PC_D8_WAVES * PC_WAVE) void decode_attn_fp8_tail_kernel(PcDecode8Args a, PcDecodeArgs tail,
                                                                                      int n_wg8) {
   static_assert(PC_D8_WAVES == PC_DEC_WAVES, "one workgroup size");
-  if ((int)blockIdx.x < n_wg8) decode8_workgroup<D, NQ>(a, blockIdx.x);
-  else pc_decode_workgroup<D, NQ>(tail, blockIdx.x - n_wg8);
+  __shared__ PcDecodeLds<D> sm;
+  if ((int)blockIdx.x < n_wg8) decode8_workgroup<D>(a, blockIdx.x, sm);
+  else pc_decode_workgroup<D>(tail, blockIdx.x - n_wg8, sm);
 }
 
 // tail: rides in the launch, unless its parts_grid is 0
-template <int D, int NQ>
-static int launch_decode8_t(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, hipStream_t st) {
+template <int D>
+static int launch_decode8_d(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, hipStream_t st) {
   const long long groups = (long long)batch * a.n_kv_heads;
   const long long n_wg8 = groups * a.parts_grid, blocks = n_wg8 + groups * tail.parts_grid;
   if (blocks == 0) return PC_OK;
@@ -510,19 +458,12 @@ static int launch_decode8_t(const PcDecode8Args& a, const PcDecodeArgs& tail, in
   dim3 grid((unsigned)blocks), block(PC_D8_WAVES * PC_WAVE);
   PcProfScope prof(PC_KERNEL_DECODE_FP8, st);
   if (tail.parts_grid > 0)
-    hipLaunchKernelGGL((decode_attn_fp8_tail_kernel<D, NQ>), grid, block, 0, st, a, tail, (int)n_wg8);
+    hipLaunchKernelGGL(decode_attn_fp8_tail_kernel<D>, grid, block, 0, st, a, tail, (int)n_wg8);
   else
-    hipLaunchKernelGGL((decode_attn_fp8_kernel<D, NQ>), grid, block, 0, st, a);
+    hipLaunchKernelGGL(decode_attn_fp8_kernel<D>, grid, block, 0, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
-template <int D>
-static int launch_decode8_d(const PcDecode8Args& a, const PcDecodeArgs& tail, int batch, int nq_pad, hipStream_t st) {
-  if (nq_pad == 4) return launch_decode8_t<D, 4>(a, tail, batch, st);
-  if (nq_pad == 8) return launch_decode8_t<D, 8>(a, tail, batch, st);
-  return launch_decode8_t<D, 16>(a, tail, batch, st);
-}
-
 int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
                          const float* k_scale, const float* v_scale, const int32_t* seg_len,
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
@@ -540,14 +481,13 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
   a.parts_grid = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
   a.n_parts = n_parts;
   a.scale_log2 = scale * PC_D8_LOG2E;
-  const int nq_pad = cols <= 4 ? 4 : (cols <= 8 ? 8 : 16);
   const long long n_wg8 = (long long)batch * n_kv_heads * a.parts_grid;
-  const bool tail_here = tail_cap > 0 && (nq_pad == 4 || n_wg8 <= PC_D8_TAIL_WGS);
+  const bool tail_here = tail_cap > 0 && (cols <= 4 || n_wg8 <= PC_D8_TAIL_WGS);
   const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_here ? 1 : 0,
                                            tail_here ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
                                            n_parts, a.parts_grid, app);
-  const int rc = head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, nq_pad, st)
-                                 : launch_decode8_d<64>(a, tail, batch, nq_pad, st);
+  const int rc = head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, st)
+                                 : launch_decode8_d<64>(a, tail, batch, st);
   if (rc != PC_OK || tail_cap == 0 || tail_here) return rc;
   return pc_launch_decode(q, pos0, base, k_tail, v_tail, tail_len, 0, batch, n_q, 1, tail_cap, n_q_heads, n_kv_heads,
                           head_dim, scale, part_o, part_lse, n_parts, a.parts_grid, app, st);

@@ -8,13 +8,6 @@
 #define PC_DEC_ITER_KEYS 32
 #define PC_DEC_LOG2E 1.4426950408889634f
 
-#define PC_WAVE_LDS_SYNC()                                   \
-  do {                                                       \
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   \
-    __builtin_amdgcn_wave_barrier();                         \
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   \
-  } while (0)
-
 // The query rows of the few-row kernels: bf16 [B, n_q, H_q, D], rotated by the kernel at positions
 // pos0 + t (fp64 angles, rounded to bf16 once); pos0 < 0: they arrive rotated.
 struct PcDecodeQuery {
@@ -120,24 +113,94 @@ struct PcDecodeArgs {
   float scale_log2;       // softmax scale * log2(e)
 };
 
+// LDS of a split-KV workgroup (the 16-bit and the 8-bit function of one launch use the same)
+template <int D>
+struct PcDecodeLds {
+  float o[PC_DEC_WAVES][16][D];
+  float m[PC_DEC_WAVES][16], l[PC_DEC_WAVES][16];
+  __attribute__((aligned(16))) uint16_t q[16][D];
+};
+// The 4 wavefronts' (o, max in log2 units, sum) in LDS -> the workgroup's partial
+template <int D>
+__device__ __forceinline__ void pc_write_partial(const PcDecodeLds<D>& sm, int G, int n_cols, int n_q, int n_q_heads,
+                                                 long long part_row, int g, float* part_o, float* part_lse) {
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < n_cols * (D / 4); idx += PC_DEC_WAVES * PC_WAVE) {
+    const int n = idx / (D / 4), d4 = idx % (D / 4) * 4;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < PC_DEC_WAVES; ++w) M = fmaxf(M, sm.m[w][n]);
+    floatx4 num = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+    if (M > -INFINITY) {
+#pragma unroll
+      for (int w = 0; w < PC_DEC_WAVES; ++w) {
+        const float sc = exp2f(sm.m[w][n] - M);
+        const floatx4 x = *(const floatx4*)&sm.o[w][n][d4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) num[e] += sc * x[e];
+        den += sc * sm.l[w][n];
+      }
+    }
+    const long long row = (part_row * n_q + n / G) * n_q_heads + g * G + n % G;
+    floatx4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = den > 0.f ? num[e] / den : 0.f;
+    *(floatx4*)(part_o + row * D + d4) = y;
+    if (d4 == 0) part_lse[row] = (den > 0.f) ? (M + log2f(den)) * 0.6931471805599453f : -INFINITY;
+  }
+}
+// A block's logits (lane: column lane % 16, keys 16 bi + 4 (lane / 16) + j) -> probabilities relative to the
+// running maximum of the column, which moves (alpha: what everything before is worth now); keys behind
+// the segment's end are masked in its last block.
+__device__ __forceinline__ void pc_decode_softmax(const floatx4 (&acc)[2], float scale, int keys, int kk, float& m_run,
+                                                  float& l_run, float& alpha, float (&pr)[2][4]) {
+  float top = -INFINITY;
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) pr[bi][j] = acc[bi][j] * scale;
+  if (keys < 32) {
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (16 * bi + 4 * kk + j >= keys) pr[bi][j] = -INFINITY;
+  }
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) top = fmaxf(top, pr[bi][j]);
+  const float m_new = fmaxf(m_run, pc_rows_max(top));          // finite: every block holds a valid key
+  alpha = __builtin_amdgcn_exp2f(m_run - m_new);               // arguments <= 0: the bare instruction
+  m_run = m_new;
+  float sum = 0.f;
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      pr[bi][j] = __builtin_amdgcn_exp2f(pr[bi][j] - m_new);
+      sum += pr[bi][j];
+    }
+  l_run = l_run * alpha + sum;
+}
+
 // One workgroup (PC_DEC_WAVES wavefronts) of the split-KV attention, number `bid` of batch * H_kv *
-// parts_grid.
-template <int D, int NQ>
-__device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int bid) {
+// parts_grid.  Both products on the 16x16x32 MFMA, S^T = K Q^T and O^T += V^T P^T, with the query columns on
+// the N side, so that a lane owns one column throughout.  V arrives row-major, 8 bytes a lane (4 values of
+// a key): eight keys of a lane, transposed by byte permutes, are four operands, of the values 64 c + 4 m + e.
+// The lane's keys are those whose probabilities it holds, so P goes from the logit registers into the
+// operand.  P keeps fp32 accuracy as two bf16 halves (hi + lo: 2^-17 relative), two MFMAs a block of V.
+// P V on the vector ALUs (32 multiply-adds per loaded piece and column, P through LDS, a kernel each for 4, 8
+// and 16 columns) took 21.3 us a step of 8 x 2048 keys, 4 columns, this 20.1; error against 64 bits the same.
+template <int D>
+__device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int bid, PcDecodeLds<D>& sm) {
   constexpr int KSTEPS = D / 32;            // MFMA k-steps over the head dimension
-  constexpr int LPR = D / 8;                // lanes per V row (16-byte pieces)
-  constexpr int RPI = PC_WAVE / LPR;        // V rows per load instruction
-  constexpr int VLOADS = PC_DEC_ITER_KEYS / RPI;
+  constexpr int NC = D / 64;                // 8-byte pieces a lane takes of a V row
   constexpr int KBLK = PC_DEC_ITER_KEYS / 16;
 
-  __shared__ float p_lds[PC_DEC_WAVES][PC_DEC_ITER_KEYS][NQ];
-  __shared__ float alpha_lds[PC_DEC_WAVES][NQ];
-  __shared__ float red_o[PC_DEC_WAVES][NQ][D];
-  __shared__ float red_m[PC_DEC_WAVES][NQ], red_l[PC_DEC_WAVES][NQ];
-  __shared__ __attribute__((aligned(16))) uint16_t q_lds[NQ][D];
-
   const int G = a.n_q_heads / a.n_kv_heads;
-  const int n_cols = a.n_q * G;             // valid query columns (<= NQ)
+  const int n_cols = a.n_q * G;             // valid query columns (<= 16)
   const int lane = threadIdx.x % PC_WAVE, wave = threadIdx.x / PC_WAVE;
   const int kk = lane / 16, c16 = lane % 16;
 
@@ -147,17 +210,17 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
 
   // A wavefront streams its run of 32-key blocks, through segment boundaries; the running
   // softmax carries over (same query columns, same KV head), so a workgroup leaves one partial.
-  // A cursor names the next block: where it is, plus the segment's base pointers.
-  struct Cursor { PcBlockCursor at; const uint16_t* k; const uint16_t* v; int bytes; };
+  // A cursor names the next block: where it is, plus its rows.
+  struct Cursor { PcBlockCursor at; const uint16_t* k; const uint16_t* v; int keys; };
   PcSegLens lens;
   lens.seg_len = a.seg_len; lens.per_head = a.seg_len_per_head; lens.n_seg = a.n_seg;
   lens.n_kv_heads = a.n_kv_heads; lens.k_t = a.k_t; lens.b = b; lens.g = g;
   auto place = [&](const PcBlockCursor& at) {
-    Cursor c; c.at = at; c.k = a.kc; c.v = a.vc; c.bytes = 0;       // behind the run's end: nothing is read
+    Cursor c; c.at = at; c.k = a.kc; c.v = a.vc; c.keys = 0;        // behind the run's end: nothing is read
     if (at.left > 0) {
       const long long first = ((((long long)b * a.n_seg + at.s) * a.n_kv_heads + g) * a.k_t + 32LL * at.blk) * D;
       c.k = a.kc + first; c.v = a.vc + first;
-      c.bytes = min(32, at.len - 32 * at.blk) * (2 * D);
+      c.keys = min(32, at.len - 32 * at.blk);
     }
     return c;
   };
@@ -170,114 +233,85 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   const bool append = a.app.k_new != nullptr && part == a.parts_grid - 1;
   PcRowAppend<D> row;
   if (append) row.begin(a.app, b * a.n_kv_heads + g);
-  bf16x8 bq[KSTEPS];                        // B operand: column c16 = (t, head-in-group); lane holds d = 32*ks + 8*kk .. +7
-
-  float m_run = -INFINITY, l_run = 0.f;     // of column c16 (this lane's share of the sum)
-  float o_acc[NQ][8];
-#pragma unroll
-  for (int n = 0; n < NQ; ++n)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o_acc[n][e] = 0.f;
-
-  const int v_row = lane / LPR, v_piece = lane % LPR;
 
   // A block's rows through buffer descriptors that end behind its last valid row: the rows after it arrive
   // as zeros, and behind the run's end nothing is read.  So the loads are unconditional, and the waits in
   // front of a block's arithmetic count the next block's loads as what they are, in flight (with loads
   // under a condition the compiler must assume that they were not issued and waits for all).
-  u32x4 kbuf[2][KBLK][KSTEPS], vbuf[2][VLOADS];
-  const int k_off = 2 * (c16 * D + 8 * kk), v_off = 2 * (v_row * D + 8 * v_piece);
+  // V: key i of the lane is 4 kk + i (i < 4) or 16 + 4 kk + i - 4, piece c its values 64 c + 4 c16 .. + 3.
+  u32x4 kbuf[2][KBLK][KSTEPS];
+  u32x2 vbuf[2][8][NC];
+  const int k_off = 2 * (c16 * D + 8 * kk), v_off = 2 * (4 * kk * D + 4 * c16);
   auto issue_loads = [&](int buf, const Cursor& c) __attribute__((always_inline)) {
-    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)c.k, 0, c.bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)c.v, 0, c.bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)c.k, 0, c.keys * (2 * D), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)c.v, 0, c.keys * (2 * D), 0x00020000);
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks)
         kbuf[buf][bi][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, k_off, 2 * (16 * bi * D + 32 * ks), PC_BUF_NT);
 #pragma unroll
-    for (int i = 0; i < VLOADS; ++i)
-      vbuf[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(vr, v_off, 2 * RPI * i * D, PC_BUF_NT);
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int c4 = 0; c4 < NC; ++c4)
+        vbuf[buf][i][c4] = __builtin_amdgcn_raw_buffer_load_b64(vr, v_off, 2 * ((i < 4 ? i : i + 12) * D + 64 * c4), PC_BUF_NT);
     __builtin_amdgcn_sched_barrier(0);                       // not behind the arithmetic that follows
   };
 
-  auto consume = [&](int buf, const Cursor& cur) {
-    const int key0 = 32 * cur.at.blk, w_end = cur.at.len;
-    // S^T block: keys x columns
+  bf16x8 bq[KSTEPS];                        // B operand: column c16 = (t, head-in-group); lane holds d = 32*ks + 8*kk .. +7
+  float m_run = -INFINITY, l_run = 0.f;     // of column c16 (this lane's share of the sum)
+  // O^T: o_acc[c][e], register i = value d = 64 c + 16 kk + 4 i + e of column c16
+  floatx4 o_acc[NC][4];
+#pragma unroll
+  for (int c4 = 0; c4 < NC; ++c4)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o_acc[c4][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  auto consume = [&](int buf, const Cursor& cur) __attribute__((always_inline)) {
     floatx4 acc[KBLK];
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi) {
       acc[bi] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks)
-        acc[bi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&kbuf[buf][bi][ks], bq[ks],
-                                                          acc[bi], 0, 0, 0);
+        acc[bi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&kbuf[buf][bi][ks], bq[ks], acc[bi], 0, 0, 0);
     }
-    float sv[KBLK][4];
-    float bmax = -INFINITY;
+    float pr[KBLK][4], alpha;
+    pc_decode_softmax(acc, a.scale_log2, cur.keys, kk, m_run, l_run, alpha, pr);
+    u32x4 p_hi, p_lo;
 #pragma unroll
     for (int bi = 0; bi < KBLK; ++bi)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) sv[bi][j] = acc[bi][j] * a.scale_log2;
-    if (key0 + 32 > w_end) {                         // a segment's last block
-#pragma unroll
-      for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (key0 + 16 * bi + 4 * kk + j >= w_end) sv[bi][j] = -INFINITY;
-    }
-#pragma unroll
-    for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bmax = fmaxf(bmax, sv[bi][j]);
-    bmax = pc_rows_max(bmax);
-    const float m_new = fmaxf(m_run, bmax);          // finite: every block holds a valid key
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // arguments <= 0: the bare instruction
-    m_run = m_new;
-    float psum = 0.f;
-#pragma unroll
-    for (int bi = 0; bi < KBLK; ++bi)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float p = __builtin_amdgcn_exp2f(sv[bi][j] - m_new);
-        psum += p;
-        if (c16 < NQ) p_lds[wave][16 * bi + 4 * kk + j][c16] = p;
+      for (int j = 0; j < 4; j += 2) {
+        const uint32_t h = pack_bf16x2(pr[bi][j], pr[bi][j + 1]);
+        p_hi[2 * bi + j / 2] = h;
+        p_lo[2 * bi + j / 2] = pack_bf16x2(pr[bi][j] - bf16_lo_to_f32(h), pr[bi][j + 1] - bf16_hi_to_f32(h));
       }
-    l_run = l_run * alpha + psum;
-    const bool moved = __any(alpha != 1.0f);         // some column's maximum grew (rare after the first keys)
-    if (moved && kk == 0 && c16 < NQ) alpha_lds[wave][c16] = alpha;
-    PC_WAVE_LDS_SYNC();
-    // rescale (only when a maximum moved), then o[n][:] += p[key][n] * v[key][:]
-    if (moved) {
+    if (__any(alpha != 1.0f)) {                      // some column's maximum grew (rare after the first keys)
 #pragma unroll
-      for (int n = 0; n < NQ; ++n) {
-        const float al = alpha_lds[wave][n];
+      for (int c4 = 0; c4 < NC; ++c4)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o_acc[n][e] *= al;
-      }
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o_acc[c4][e][i] *= alpha;
     }
 #pragma unroll
-    for (int i = 0; i < VLOADS; ++i) {
-      const int key_local = RPI * i + v_row;
-      float vf[8];
+    for (int c4 = 0; c4 < NC; ++c4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        vf[2 * e] = bf16_lo_to_f32(vbuf[buf][i][e]); vf[2 * e + 1] = bf16_hi_to_f32(vbuf[buf][i][e]);
-      }
+        u32x4 va;                                    // value 64 c4 + 4 c16 + e of the lane's 8 keys
 #pragma unroll
-      for (int n = 0; n < NQ; ++n) {
-        const float p = p_lds[wave][key_local][n];    // 0 for masked keys
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o_acc[n][e] = fmaf(p, vf[e], o_acc[n][e]);
+        for (int i = 0; i < 4; ++i)
+          va[i] = __builtin_amdgcn_perm(vbuf[buf][2 * i + 1][c4][e / 2], vbuf[buf][2 * i][c4][e / 2], e % 2 ? 0x07060302u : 0x05040100u);
+        o_acc[c4][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_lo, o_acc[c4][e], 0, 0, 0);
+        o_acc[c4][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_hi, o_acc[c4][e], 0, 0, 0);
       }
-    }
-    PC_WAVE_LDS_SYNC();
   };
 
   Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane));
   issue_loads(0, cur);
 
-  rot.finish(a.query, b, g, G, n_cols, q_lds);
+  rot.finish(a.query, b, g, G, n_cols, sm.q);
   PC_LDS_BARRIER();
   if (append) {
     const long long seg0 = (((long long)b * a.n_seg + a.n_seg - 1) * a.n_kv_heads + g) * a.k_t * D;
@@ -285,66 +319,38 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
                const_cast<uint16_t*>(a.vc) + seg0);
     if (a.app.q_rot)
       for (int x = threadIdx.x; x < n_cols * D; x += blockDim.x)     // one query row: heads g G .. are adjacent
-        a.app.q_rot[((long long)b * a.n_q_heads + g * G) * D + x] = q_lds[x / D][x % D];
+        a.app.q_rot[((long long)b * a.n_q_heads + g * G) * D + x] = sm.q[x / D][x % D];
   }
 #pragma unroll
   for (int ks = 0; ks < KSTEPS; ++ks) {
-    u32x4 raw = *(const u32x4*)(q_lds[min(c16, n_cols - 1)] + 32 * ks + 8 * kk);
+    u32x4 raw = *(const u32x4*)(sm.q[min(c16, n_cols - 1)] + 32 * ks + 8 * kk);
     if (c16 >= n_cols) raw = u32x4{0, 0, 0, 0};
     bq[ks] = *(bf16x8*)&raw;
   }
 
+  // (no way out in the middle: it would join the loop's end, where the compiler would then have to take
+  // either buffer for the one asked for last)
   while (cur.at.left > 0) {
-    Cursor nx = next(cur);
+    const Cursor nx = next(cur);
     issue_loads(1, nx);
     consume(0, cur);
-    if (nx.at.left == 0) break;
     cur = next(nx);
     issue_loads(0, cur);
-    consume(1, nx);
+    if (nx.at.left > 0) consume(1, nx);
   }
 
-  // ---- wavefront totals: sum the per-lane shares
+  // ---- wavefront totals, then one partial per workgroup
   l_run = pc_rows_sum(l_run);
+  if (kk == 0) { sm.m[wave][c16] = m_run; sm.l[wave][c16] = l_run; }
+  if (c16 < n_cols) {
 #pragma unroll
-  for (int n = 0; n < NQ; ++n)
+    for (int c4 = 0; c4 < NC; ++c4)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float x = o_acc[n][e];
-#pragma unroll
-      for (int off = LPR; off < PC_WAVE; off <<= 1) x += __shfl_xor(x, off);
-      o_acc[n][e] = x;
-    }
-  if (kk == 0 && c16 < NQ) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
-  if (v_row == 0) {
-#pragma unroll
-    for (int n = 0; n < NQ; ++n)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) red_o[wave][n][8 * v_piece + e] = o_acc[n][e];
+      for (int i = 0; i < 4; ++i)
+        *(floatx4*)&sm.o[wave][c16][64 * c4 + 16 * kk + 4 * i] =
+            floatx4{o_acc[c4][0][i], o_acc[c4][1][i], o_acc[c4][2][i], o_acc[c4][3][i]};
   }
-  __syncthreads();
-
-  // ---- merge the 4 wavefronts, write one partial per workgroup
-  const int part_out = a.part0 + part;
-  for (int idx = threadIdx.x; idx < n_cols * D; idx += blockDim.x) {
-    const int n = idx / D, d = idx % D;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < PC_DEC_WAVES; ++w) M = fmaxf(M, red_m[w][n]);
-    float num = 0.f, den = 0.f;
-    if (M > -INFINITY) {
-#pragma unroll
-      for (int w = 0; w < PC_DEC_WAVES; ++w) {
-        const float sc = exp2f(red_m[w][n] - M);
-        num += sc * red_o[w][n][d];
-        den += sc * red_l[w][n];
-      }
-    }
-    const int t = n / G, hg = n % G;
-    const long long row = (((long long)b * a.n_parts + part_out) * a.n_q + t) * a.n_q_heads + g * G + hg;
-    a.part_o[row * D + d] = (den > 0.f) ? num / den : 0.f;
-    if (d == 0) a.part_lse[row] = (den > 0.f) ? (M + log2f(den)) * 0.6931471805599453f : -INFINITY;
-  }
+  pc_write_partial<D>(sm, G, n_cols, a.n_q, a.n_q_heads, (long long)b * a.n_parts + a.part0 + part, g, a.part_o, a.part_lse);
 }
 
 static inline PcDecodeQuery pc_decode_query(const void* q, int pos0, float base, int n_q, int n_q_heads, int head_dim) {

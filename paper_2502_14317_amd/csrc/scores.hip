@@ -36,8 +36,6 @@
 #include "pc_common.h"
 #include <math.h>
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 #define PC_SC_THREADS 256
 #define PC_SC_WAVES 4
 #define PC_SC_KB 256        // keys per workgroup: the smallest block (sizes the workspace)
