@@ -343,28 +343,56 @@ static int launch_decode_d(const PcDecodeArgs& a, int batch, hipStream_t st) {
   return PC_OK;
 }
 
-PcDecodeSplit pc_decode_split(int k_t, int n_seg, long long n_bg) {
-  // Workgroups (partials) per (sequence, KV head) group.  Measured at the decode config (128
-  // groups of 32 x 2048 keys, bf16): 256 workgroups, one per CU, each streaming half of a
-  // group's keys, reach 89 % of the HBM peak; 512 and 1024
-  // workgroups (the same bytes in shorter runs, two workgroups per CU at a time) 81 %.  Fewer
-  // concurrent streams with longer runs are kinder to the memory system than more occupancy, and
-  // a launch of exactly one round has no ragged end.  So: the number of parts that minimises
-  // rounds / parts (the time of the slowest CU in units of one group's work), each round count
-  // weighted by the bandwidth fraction measured for it; every wavefront keeps at least one
-  // 32-key block at full lengths; at most 64 parts (the merge reads them all).
+// Partials of a group that the workspace has room for: the parts that minimise rounds / parts, rounds of
+// one workgroup a CU, at least one block a wavefront at full lengths, at most 64.
+static int split_room(int k_t, int n_seg, long long n_bg) {
   const int n_cu = 256;                                    // MI355X
   const long long blocks_full = (long long)n_seg * ((k_t + 31) / 32);
   const long long p_cap = blocks_full / PC_DEC_WAVES;
   const int p_max = (int)(p_cap < 1 ? 1 : (p_cap > 64 ? 64 : p_cap));
-  PcDecodeSplit d;
-  d.n_parts = n_seg > 0 ? 1 : 0;                           // no segments: no launch, no partial
-  if (n_seg <= 0) return d;
+  if (n_seg <= 0) return 0;                                // no segments: no launch, no partial
+  int room = 1;
   double best = 0.0;
   for (int p = 1; p <= p_max; ++p) {
     const long long rounds = (n_bg * p + n_cu - 1) / n_cu;
     const double cost = (double)rounds / p / (rounds == 1 ? 0.89 : 0.81);
-    if (p == 1 || cost < best * (1.0 - 1e-9)) { best = cost; d.n_parts = p; }
+    if (p == 1 || cost < best * (1.0 - 1e-9)) { best = cost; room = p; }
+  }
+  return room;
+}
+
+PcDecodeSplit pc_decode_split(int k_t, int n_seg, int elem_bytes, int tail_cap, int head_dim, long long n_bg) {
+  // The parts, within the room, of the least estimated time.  Measured over 17 shapes x 10 numbers of parts a
+  // cache precision (1 to 65 sequences, 4 to 256 KV heads in all, 3 MB to 2.2 GB, data out of the caches): a
+  // launch and its merge cost some 10.5 us; a workgroup alone on its CU reads 38 GB/s (8-bit, in whole KiB
+  // and with two blocks ahead, 57), less as the others load the memory; 256 CUs together 6.9 (6.6) TB/s; a
+  // further round of workgroups on a CU costs 3.5 us.  E.g. 16-bit, 33 sequences of 8 x 1024 keys, 8 KV heads:
+  // 1 part 291 us, 4 218, 8 222, 31 (whole rounds) 268; 65: 4 parts 391, 63 499; 8-bit, one sequence of 8 x 2048:
+  // 16 parts + 4 of the tail 15.5 us, 32 + 4 (a second round for 32 CUs) 19.9; 65 sequences 2 parts 192, 63 274.
+  PcDecodeSplit d = {};
+  d.room = split_room(k_t, n_seg, n_bg);
+  d.tail_room = tail_cap > 0 ? split_room(tail_cap, 1, n_bg) : 0;
+  const double seg_bytes = (double)n_seg * k_t * head_dim * 2 * elem_bytes, tail_bytes = (double)tail_cap * head_dim * 4;
+  const double mem = elem_bytes == 1 ? 6.6e6 : 6.9e6, alone = elem_bytes == 1 ? 57e3 : 38e3, slower = elem_bytes == 1 ? 110.0 : 33.0;
+  const int p_max = d.room > 0 ? d.room : d.tail_room;
+  double best = 0.0;
+  for (int p = 1; p <= p_max; ++p) {
+    int parts = d.room > 0 ? p : 0, tail = d.room > 0 ? d.tail_room : p;
+    if (parts > 0 && tail > 0) {                           // tail workgroups of about the others' size
+      const int even = (int)(p * tail_bytes / seg_bytes + 0.5);
+      tail = even < 1 ? 1 : (even < tail ? even : tail);
+    }
+    const long long wgs = n_bg * (parts + tail), rounds = (wgs + 255) / 256;
+    double us = 10.5 + 3.5 * (double)(rounds - 1);
+    if (rounds == 1) {                                     // the longest workgroup
+      const double rate = alone - slower * (double)wgs, fair = mem / (double)wgs;
+      const double most = (parts > 0 ? seg_bytes / parts : 0.0) > (tail > 0 ? tail_bytes / tail : 0.0) ? seg_bytes / parts : tail_bytes / tail;
+      us += most / (rate < fair ? rate : fair);
+    } else {
+      us += (double)rounds * (seg_bytes + tail_bytes) / (parts + tail) / (mem / 256.0);
+    }
+    // on a par within one round: more of the CUs
+    if (p == 1 || us < best * (rounds == 1 ? 1.005 : 1.0)) { best = us; d.parts = parts; d.tail_parts = tail; }
   }
   return d;
 }
@@ -372,10 +400,10 @@ PcDecodeSplit pc_decode_split(int k_t, int n_seg, long long n_bg) {
 int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const void* vc,
                      const int32_t* seg_len, int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                      int head_dim, float scale, float* part_o, float* part_lse, int n_parts,
-                     int part0, const PcDecodeAppend& app, hipStream_t st) {
+                     int part0, int parts_grid, const PcDecodeAppend& app, hipStream_t st) {
   const PcDecodeArgs a = pc_decode_args(pc_decode_query(q, pos0, base, n_q, n_q_heads, head_dim), kc, vc, seg_len,
-                                        seg_len_per_head, batch, n_seg, k_t, n_kv_heads, scale, part_o,
-                                        part_lse, n_parts, part0, app);
+                                        seg_len_per_head, n_seg, k_t, n_kv_heads, scale, part_o,
+                                        part_lse, n_parts, part0, parts_grid, app);
   return head_dim == 128 ? launch_decode_d<128>(a, batch, st) : launch_decode_d<64>(a, batch, st);
 }
 

@@ -266,15 +266,9 @@ int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, 
 }
 
 // The 16-bit tail can ride in the launch of the 8-bit segments, its workgroups behind theirs: the tail, a
-// few per cent of the bytes, then costs no launch, ramp and drain of its own.  A kernel takes the larger
-// register count of the two functions and the sum of their LDS, and beyond 4 columns the 16-bit function
-// (P V on the vector ALUs, 8 accumulators per column and lane) needs so many that the 8-bit workgroups
-// lose the second one on their CU (head_dim 128: 308 and 439 registers against 204 and 206, 83 KB of
-// LDS against 37).  So with more columns the tail rides only where no CU has a second 8-bit workgroup to
-// lose.  Measured, 8 x 2048 or 8 x 1024 keys and a tail of 512 or 256, one launch / two (us): 64 / 8
-// heads, 4 sequences (256 workgroups) 60 / 62, 16 (256) 183 / 186; 33 sequences (264 groups) 373 / 278,
-// 65 541 / 344, 100 417 / 376; 16 / 1 heads, 200 sequences 275 / 183; head_dim 64, 64 / 4 heads, 130
-// sequences 486 / 227.
+// few per cent of the bytes, then costs no launch, ramp and drain of its own: 2.5 us of a step of one
+// sequence.  Beyond 4 columns it rides up to 256 8-bit workgroups only; with more of them a launch is lost
+// among the rounds, and the 8-bit kernel alone is the smaller one.
 #define PC_D8_TAIL_WGS 256
 template <int D>
 __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid, PcDecodeLds<D>& sm) {
@@ -469,7 +463,7 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
                          const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
                          int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
-                         float* part_lse, int n_parts, const PcDecodeAppend& app, hipStream_t st) {
+                         float* part_lse, const PcDecodeSplit& split, const PcDecodeAppend& app, hipStream_t st) {
   const int cols = n_q * (n_q_heads / n_kv_heads);
   if (cols > 16) return PC_ERR_UNSUPPORTED;               // the columns of one 16x16x32 MFMA
   PcDecode8Args a;
@@ -478,17 +472,17 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
   a.k_scale = k_scale; a.v_scale = v_scale;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.parts_grid = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
-  a.n_parts = n_parts;
+  a.parts_grid = split.parts;
+  a.n_parts = split.parts + split.tail_parts;
   a.scale_log2 = scale * PC_D8_LOG2E;
   const long long n_wg8 = (long long)batch * n_kv_heads * a.parts_grid;
   const bool tail_here = tail_cap > 0 && (cols <= 4 || n_wg8 <= PC_D8_TAIL_WGS);
-  const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, batch, tail_here ? 1 : 0,
+  const PcDecodeArgs tail = pc_decode_args(a.query, k_tail, v_tail, tail_len, 0, tail_here ? 1 : 0,
                                            tail_here ? tail_cap : 1, n_kv_heads, scale, part_o, part_lse,
-                                           n_parts, a.parts_grid, app);
+                                           a.n_parts, split.parts, tail_here ? split.tail_parts : 0, app);
   const int rc = head_dim == 128 ? launch_decode8_d<128>(a, tail, batch, st)
                                  : launch_decode8_d<64>(a, tail, batch, st);
   if (rc != PC_OK || tail_cap == 0 || tail_here) return rc;
   return pc_launch_decode(q, pos0, base, k_tail, v_tail, tail_len, 0, batch, n_q, 1, tail_cap, n_q_heads, n_kv_heads,
-                          head_dim, scale, part_o, part_lse, n_parts, a.parts_grid, app, st);
+                          head_dim, scale, part_o, part_lse, a.n_parts, split.parts, split.tail_parts, app, st);
 }

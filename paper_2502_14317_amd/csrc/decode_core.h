@@ -360,15 +360,15 @@ static inline PcDecodeQuery pc_decode_query(const void* q, int pos0, float base,
   return x;
 }
 static inline PcDecodeArgs pc_decode_args(const PcDecodeQuery& query, const void* kc, const void* vc,
-                                          const int32_t* seg_len, int seg_len_per_head, int batch, int n_seg,
+                                          const int32_t* seg_len, int seg_len_per_head, int n_seg,
                                           int k_t, int n_kv_heads, float scale, float* part_o, float* part_lse,
-                                          int n_parts, int part0, const PcDecodeAppend& app) {
+                                          int n_parts, int part0, int parts_grid, const PcDecodeAppend& app) {
   PcDecodeArgs a;
   a.query = query; a.part0 = part0; a.app = app;
   a.kc = (const uint16_t*)kc; a.vc = (const uint16_t*)vc;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = query.n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = query.n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.parts_grid = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
+  a.parts_grid = parts_grid;
   a.n_parts = n_parts;
   a.scale_log2 = scale * PC_DEC_LOG2E;
   return a;

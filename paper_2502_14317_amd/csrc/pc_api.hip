@@ -272,13 +272,10 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
                                    k_amax, v_amax, k8, v8, k_scale, v_scale, (hipStream_t)stream);
 }
 
-// Few query rows: rotated by the split-KV kernel itself, which saves a launch but puts the fp64 exp and
-// sincos (some 5 us) in front of every workgroup, or by rope_q_kernel first.  First where the merge needs
-// the rows too (self segment), and beyond 512 workgroups, of which two share a CU: those of later rounds
-// pay it again.  Measured, 16-bit / 8-bit cache, 8 x 1024 keys, kernel itself -> first (us): 32 / 8 heads, 1
-// sequence 16.0 -> 17.5 / 16.4 -> 17.4, 64 (512 workgroups) 338 -> 340 / 180 -> 180, 33 (264 groups in many
-// parts) 230 -> 214 / 150 -> 136, 65 446 -> 414 / 279 -> 253; 24 / 8 heads of 64, 65 sequences 238 -> 209 /
-// 158 -> 125; 16 / 1 heads, 300 sequences 1065 -> 914 / 424 -> 334.
+// Few query rows: rotated by the split-KV kernel itself, behind its first key loads, which saves a launch (one
+// sequence of 8 x 2048 keys 19.4 against 21.5 us a step), or by rope_q_kernel first: where the merge needs the
+// rows too (self segment), and beyond 512 workgroups, of which two share a CU: those of later rounds would
+// rotate again (33 sequences of 64 / 8 heads 275 against 276 us, 65 of 32 / 8 503 against 504: no difference).
 #define PC_DEC_ROT_WGS 512
 static bool rotate_first(int has_self, long long workgroups) { return has_self || workgroups > PC_DEC_ROT_WGS; }
 
@@ -317,7 +314,8 @@ static int check_tile_limits(int n_seg, int k_t, int tail_cap, int n_kv_heads, i
 
 struct Par8Ws {
   size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rotated query rows
-  int n_parts, parts8;
+  int n_parts;
+  PcDecodeSplit split;                                     // small
   bool small;
 };
 
@@ -328,16 +326,15 @@ static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_ca
   size_t part_rows = 0;
   w.small = (long long)n_q * (n_q_heads / n_kv_heads) <= 16;
   if (w.small) {
-    w.parts8 = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
-    w.n_parts = w.parts8;
-    if (tail_cap > 0) w.n_parts += pc_decode_split(tail_cap, 1, (long long)batch * n_kv_heads).n_parts;
+    w.split = pc_decode_split(k_t, n_seg, 1, tail_cap, D, (long long)batch * n_kv_heads);
+    w.n_parts = w.split.parts + w.split.tail_parts;
   } else {
-    w.parts8 = 0;
+    w.split = PcDecodeSplit{};
     w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t) + key_tiles(1, tail_cap), n_q_heads, n_kv_heads, D, has_self, part_rows);
   }
   size_t off = 0;
   w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  if (w.small) part_rows = rows * w.n_parts;
+  if (w.small) part_rows = rows * (w.split.room + w.split.tail_room);
   w.part_o = off;   off = pc_align_up(off + part_rows * D * sizeof(float), kAlign);
   w.part_lse = off; off = pc_align_up(off + part_rows * sizeof(float), kAlign);
   w.rows_k = w.rows_v = off;
@@ -405,7 +402,7 @@ static int par8_small_run(const void* q, const void* k8, const void* v8, const f
                           const void* k_new, const void* v_new, int32_t* self_row, hipStream_t st) {
   const void* q_in = q;
   int pos0 = q_pos0, rc;
-  if (q_pos0 >= 0 && rotate_first(k_self != nullptr, (long long)batch * n_kv_heads * w.parts8)) {
+  if (q_pos0 >= 0 && rotate_first(k_self != nullptr, (long long)batch * n_kv_heads * w.split.parts)) {
     rc = pc_launch_rope_q(q, base + w.q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, 1.0f, st);
     if (rc != PC_OK) return rc;
     q_in = base + w.q_rot; pos0 = -1;
@@ -416,7 +413,7 @@ static int par8_small_run(const void* q, const void* k8, const void* v8, const f
   if (n_seg > 0 || tail_cap > 0) {
     rc = pc_launch_decode_fp8(q_in, pos0, rope_base, k8, v8, k_scale, v_scale, seg_len, seg_len_per_head,
                               k_tail, v_tail, tail_len, tail_cap, batch, n_q, n_seg, k_t, n_q_heads,
-                              n_kv_heads, D, scale, part_o, part_lse, w.n_parts, app, st);
+                              n_kv_heads, D, scale, part_o, part_lse, w.split, app, st);
     if (rc != PC_OK) return rc;
   }
   PcMergeStep step = {};
@@ -565,13 +562,14 @@ static ParWs par_ws_layout(int batch, int n_q, int n_seg, int k_t, int n_q_heads
   const int G = n_q_heads / n_kv_heads;
   w.small = (long long)n_q * G <= 16;
   if (w.small) {
-    w.n_parts = pc_decode_split(k_t, n_seg, (long long)batch * n_kv_heads).n_parts;
+    const PcDecodeSplit split = pc_decode_split(k_t, n_seg, 2, 0, D, (long long)batch * n_kv_heads);
+    w.n_parts = split.parts;
+    part_rows = rows * split.room;
   } else {
     w.n_parts = tile_parts(batch, n_q, key_tiles(n_seg, k_t), n_q_heads, n_kv_heads, D, has_self, part_rows);
   }
   size_t off = 0;
   w.q_rot = off;    off = pc_align_up(off + rows * D * 2, kAlign);
-  if (w.small) part_rows = rows * w.n_parts;
   w.part_o = off;   off = pc_align_up(off + part_rows * D * sizeof(float), kAlign);
   w.part_lse = off; off = pc_align_up(off + part_rows * sizeof(float), kAlign);
   w.total = off;
@@ -685,7 +683,7 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
     const PcDecodeAppend app = step_append(k_new, v_new, q_pos0, pos0, base + w.q_rot, self_row);
     if (n_seg > 0) {
       rc = pc_launch_decode(q_in, pos0, rope_base, kc, vc, seg_len, seg_len_per_head, batch, n_q, n_seg, k_t,
-                            n_q_heads, n_kv_heads, D, scale, part_o, part_lse, w.n_parts, 0, app, st);
+                            n_q_heads, n_kv_heads, D, scale, part_o, part_lse, w.n_parts, 0, w.n_parts, app, st);
       if (rc != PC_OK) return rc;
     }
     PcMergeStep step = {};

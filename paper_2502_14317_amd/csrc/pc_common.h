@@ -274,11 +274,13 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
 // multiplied by mul in fp64, rounded to bf16 once
 int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads, int D, int pos0,
                      float base, float mul, hipStream_t st);
-// How the split-KV decode kernels cut the keys into workgroups (n_bg = batch * H_kv): the keys of
-// a (sequence, KV head) group, all its segments laid end to end in blocks of 32 keys, are cut
-// into n_parts equal runs of blocks, one workgroup (and one partial result) each.
-struct PcDecodeSplit { int n_parts; };
-PcDecodeSplit pc_decode_split(int k_t, int n_seg, long long n_bg);
+// How the split-KV decode kernels cut the keys into workgroups (n_bg = batch * H_kv): the keys of a
+// (sequence, KV head) group, all its segments laid end to end in blocks of 32 keys, are cut into `parts`
+// equal runs of blocks, one workgroup (and one partial result) each; those of the 16-bit tail of an
+// 8-bit cache (elem_bytes 1) into tail_parts.  room, tail_room: partials the workspace has room for, never
+// fewer than parts and tail_parts.
+struct PcDecodeSplit { int parts, tail_parts, room, tail_room; };
+PcDecodeSplit pc_decode_split(int k_t, int n_seg, int elem_bytes, int tail_cap, int head_dim, long long n_bg);
 
 // A wavefront's walk over its run of 32-key blocks.  The group's blocks are numbered through all
 // segments (segment s has ceil(len_s / 32) of them); part `part` of n_parts takes blocks
@@ -389,7 +391,7 @@ struct PcMergeStep {
 int pc_launch_decode(const void* q, int pos0, float base, const void* kc, const void* vc,
                      const int32_t* seg_len, int seg_len_per_head, int batch, int n_q, int n_seg, int k_t, int n_q_heads, int n_kv_heads,
                      int head_dim, float scale, float* part_o, float* part_lse, int n_parts, int part0,
-                     const PcDecodeAppend& app, hipStream_t st);
+                     int parts_grid, const PcDecodeAppend& app, hipStream_t st);
 // k_amax, v_amax [n_segs] (both or neither): the largest |value| of every segment's valid rows,
 // known beforehand (the gather leaves it): the kernel then reads the segment once
 int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg_len,
@@ -407,7 +409,7 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
                          int seg_len_per_head, const void* k_tail, const void* v_tail,
                          const int32_t* tail_len, int tail_cap, int batch, int n_q, int n_seg, int k_t,
                          int n_q_heads, int n_kv_heads, int head_dim, float scale, float* part_o,
-                         float* part_lse, int n_parts, const PcDecodeAppend& app, hipStream_t st);
+                         float* part_lse, const PcDecodeSplit& split, const PcDecodeAppend& app, hipStream_t st);
 // Merge of the tile kernel's partials [batch, n_parts, n_q, H_q, D] (no self segment)
 int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, float* lse_out, int batch,
                          int n_q, int n_q_heads, int head_dim, int n_parts, hipStream_t st);

@@ -76,3 +76,41 @@ def test_step_is_append_then_attention(case, eight_bit):
     assert torch.equal(k0, k1) and torch.equal(v0, v1) and torch.equal(s0, s1)
     assert_close(o1.double().cpu().numpy(), o0.double().cpu().numpy(), O_ATOL, O_RTOL, "out")
     assert_close(l1.double().cpu().numpy(), l0.double().cpu().numpy(), LSE_ATOL, 1e-3, "lse")
+
+
+@pytest.mark.parametrize("B,S,kt,cap", [(33, 4, 256, 96), (72, 2, 700, 40), (2, 8, 2048, 512), (1, 1, 33, 31)])
+def test_parts_of_either_rule_attend_to_the_same_keys(B, S, kt, cap):
+    """Shapes where the split cuts into fewer parts than the workspace has room for: the 8-bit segments and
+    their tail, and both precisions of the same cache, against one softmax in fp32."""
+    Hq, Hkv, D, pos = 8, 4, 64, 12
+    print("parts", B, S, kt, cap, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(B + kt)
+    mk = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    q, kc, vc = mk(B, 1, Hq, D), mk(B, S, Hkv, kt, D), mk(B, S, Hkv, kt, D)
+    k_tail, v_tail = mk(B, 1, Hkv, cap, D), mk(B, 1, Hkv, cap, D)
+    n_tail = torch.full((B, 1), cap, dtype=torch.int32, device="cuda")
+
+    def reference(keys, vals):                             # [B, Hkv, n, D] fp32; q arrives rotated
+        s = (q.float().view(B, Hkv, Hq // Hkv, 1, D) * keys[:, :, None]).sum(-1) / D ** 0.5
+        return (torch.softmax(s, -1)[..., None] * vals[:, :, None]).sum(-2).reshape(B, 1, Hq, D), torch.logsumexp(s, -1).reshape(B, Hq, 1)
+
+    flat = lambda x: x.float().transpose(1, 2).reshape(B, Hkv, -1, D)
+    out = torch.full((B, 1, Hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, Hq, 1), float("nan"), dtype=torch.float32, device="cuda")
+    ws = pc.alloc_workspace(pc.pc_parallel_attn_workspace_bytes(B, 1, S, kt, Hq, Hkv, D, False))
+    pc.pc_parallel_attn(q, kc, vc, None, None, None, B, 1, S, kt, Hq, Hkv, D, -1, 1.0e4, 0.0, out, lse, ws)
+    ro, rl = reference(flat(kc), flat(vc))
+    assert_close(out.float().cpu().numpy(), ro.cpu().numpy(), O_ATOL, O_RTOL, "out")
+    assert_close(lse.cpu().numpy(), rl.cpu().numpy(), LSE_ATOL, 1e-3, "lse")
+    k8, v8 = fp8_alloc(B, S, Hkv, kt, D), fp8_alloc(B, S, Hkv, kt, D)
+    ks = torch.empty((B, S, Hkv), dtype=torch.float32, device="cuda")
+    vs = torch.empty_like(ks)
+    pc.pc_kv_quantize_fp8(kc, vc, None, B, S, kt, Hkv, D, k8, v8, ks, vs)
+    ws = pc.alloc_workspace(pc.pc_parallel_attn_fp8_workspace_bytes(B, 1, S, kt, cap, Hq, Hkv, D))
+    pc.pc_parallel_attn_fp8(q, k8, v8, ks, vs, None, k_tail, v_tail, n_tail, cap, B, 1, S, kt, Hq, Hkv, D, -1, 1.0e4,
+                            0.0, out, lse, ws)
+    deq = lambda x, sc: ((x.float() / sc[..., None, None]).to(torch.float8_e4m3fn).float() * sc[..., None, None])
+    cat = lambda x, sc, t: torch.cat([flat(deq(x, sc)), t[:, 0].float()], dim=2)
+    ro, rl = reference(cat(kc, ks, k_tail), cat(vc, vs, v_tail))
+    assert_close(out.float().cpu().numpy(), ro.cpu().numpy(), O_ATOL, O_RTOL, "out, 8 bit")
+    assert_close(lse.cpu().numpy(), rl.cpu().numpy(), LSE_ATOL, 1e-3, "lse, 8 bit")
