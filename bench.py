@@ -49,6 +49,15 @@ def flash_flops(cfg):
     return 4.0 * cfg.head_dim * (L * (L + 1) / 2.0) * cfg.n_q_heads * cfg.n_chunks
 
 
+def step_flash_flops(cfg):
+    """Those of the attention launch of a whole step, which holds the query block's global attention too."""
+    if cfg.keep_chunks == 0:
+        return flash_flops(cfg)
+    wq = cfg.query_len
+    pairs = wq * cfg.keep_chunks * cfg.keep_tokens + wq * (wq + 1) / 2.0
+    return flash_flops(cfg) + 4.0 * cfg.head_dim * cfg.n_q_heads * pairs
+
+
 def bench_calibration(pc, torch, cfg, layer, qd, vd, steps):
     """Attention calibration (Eq. 8 before Eq. 7) on the scores of the timed workload: the
     first-100-token class with a threshold at the 99.9th percentile of its scores.  Reports the
@@ -488,7 +497,6 @@ def bench_other_config(pc, torch, name, steps=3, warmup=1):
     dt = (time.perf_counter() - t0) / steps
     pc.pc_profile_end()
     fl = [ms for n, ms in pc.pc_profile_records() if n == "flash_fwd_kernel"]
-    fl = fl[0::len(fl) // steps]
     flash_avg = sum(fl) / len(fl) * 1e-3
     # without the per-kernel event records, eager and as a HIP graph replay (no per-launch host work)
     step(); torch.cuda.synchronize()
@@ -512,7 +520,7 @@ def bench_other_config(pc, torch, name, steps=3, warmup=1):
     return {"step": "chunk prefill + scores" if prefill_only else "whole path", "ms_per_step": dt * 1e3,
             "graph_replay_ms_per_step": dt_graph * 1e3,
             "tokens_per_s_per_layer": cfg.context_tokens / dt, "flash_kernel_ms": flash_avg * 1e3,
-            "flash_frac_of_bf16_mfma_peak": flash_flops(cfg) / flash_avg / PEAK_BF16_FLOPS}
+            "flash_frac_of_bf16_mfma_peak": step_flash_flops(cfg) / flash_avg / PEAK_BF16_FLOPS}
 
 
 def bench_secondary(pc, torch, steps, warmup):
@@ -675,12 +683,10 @@ def main():
     for name, ms in pc.pc_profile_records():
         per_kernel.setdefault(name, []).append(ms)
     per_kernel["flash_fwd_kernel"] = flash_all
-    # flash_fwd_kernel runs once per step for the local attention and (full path) once more for
-    # the global attention; the local-attention launch is the first one of every step
-    n_flash = len(per_kernel["flash_fwd_kernel"]) // args.steps
-    flash_ms = per_kernel["flash_fwd_kernel"][0::n_flash]
+    # one launch a step: the local attention and (full path) the query block's global attention
+    flash_ms = per_kernel["flash_fwd_kernel"]
     flash_avg = sum(flash_ms) / len(flash_ms) * 1e-3
-    flops = flash_flops(cfg)
+    flops = step_flash_flops(cfg)
     ms_per_step = elapsed / args.steps * 1e3
     breakdown = {}
     for name, lst in per_kernel.items():

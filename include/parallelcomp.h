@@ -217,6 +217,26 @@ size_t pc_parallel_attn_workspace_bytes(int32_t batch, int32_t n_q, int32_t n_se
                                         int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
                                         int32_t has_self);
 
+/* ---- one layer in one call -------------------------------------------------------------------
+ * pc_chunk_prefill_attn with scores, pc_select_chunks_topk, pc_select_tokens_topk (calibrated = 0) or
+ * pc_select_tokens_calibrated (calibrated = 1: lambda, class_lo, class_hi, chunk_lens, counts in tok_cnt),
+ * pc_gather_kv and pc_parallel_attn of the query block, in that order: the same arguments, results and
+ * errors (all of them before any launch), batch 1.  The query block is rows first_len .. first_len + w_q
+ * of chunk 0 (first_len = its context rows, chunk_lens[0] or w; 0 <= first_len <= w), its keys and values
+ * the causal self segment; with calibrated = 1 tok_cnt are the segments' lengths per head.
+ * Nothing of the path reads the local attention's output, so the selections and the compaction come
+ * before it and the global attention runs in its launch.
+ *   chunk_idx [keep_chunks], chunk_top [keep_chunks] (nullable), tok_idx [keep_chunks, H_kv, keep_tokens],
+ *   tok_cnt [keep_chunks, H_kv] (calibrated), kc, vc [1, keep_chunks, H_kv, keep_tokens, D],
+ *   global_o [1, w_q, H_q, D], global_lse [1, H_q, w_q] (nullable); k_rope, tok_score, chunk_score required.
+ * Workspace: pc_layer_workspace_bytes(...). */
+int pc_layer_forward(const pc_shape* shape, const void* q, const void* k, const void* v, const int32_t* chunk_lens,
+                     int32_t first_len, int32_t keep_chunks, int32_t keep_tokens, int32_t calibrated, float lambda,
+                     int32_t class_lo, int32_t class_hi, void* o, float* lse, void* k_rope, float* tok_score,
+                     float* chunk_score, int32_t* chunk_idx, float* chunk_top, int32_t* tok_idx, int32_t* tok_cnt,
+                     void* kc, void* vc, void* global_o, float* global_lse, void* ws, size_t ws_bytes, void* stream);
+size_t pc_layer_workspace_bytes(const pc_shape* shape, int32_t keep_chunks, int32_t keep_tokens);
+
 /* ---- decoding stage (Eq. 9-11 token by token) ------------------------------------------------
  * Append the keys / values of n_new newly generated tokens to segment `seg` of the compacted
  * cache, behind the seg_len[b, seg] rows it holds (the growing tail: query block + generated

@@ -26,7 +26,7 @@ SYMBOLS = [
     "pc_profile_begin_kernel", "pc_parallel_attn_static", "pc_parallel_attn_static_max_bytes",
     "pc_chunk_queue_update", "pc_gather_kv_amax", "pc_kv_quantize_fp8_amax",
     "pc_copy_ceiling", "pc_decode_step", "pc_decode_step_workspace_bytes", "pc_decode_step_fp8",
-    "pc_decode_step_fp8_workspace_bytes",
+    "pc_decode_step_fp8_workspace_bytes", "pc_layer_forward", "pc_layer_workspace_bytes",
 ]
 
 
@@ -122,6 +122,11 @@ def lib():
     L.pc_decode_step_fp8.restype = c_int
     L.pc_decode_step_fp8_workspace_bytes.argtypes = [c_int32] * 7
     L.pc_decode_step_fp8_workspace_bytes.restype = c_size_t
+    L.pc_layer_forward.argtypes = ([POINTER(pc_shape)] + [P] * 4 + [c_int32] * 4 + [c_float, c_int32, c_int32] + [P] * 14 +
+                                   [c_size_t, P])
+    L.pc_layer_forward.restype = c_int
+    L.pc_layer_workspace_bytes.argtypes = [POINTER(pc_shape), c_int32, c_int32]
+    L.pc_layer_workspace_bytes.restype = c_size_t
     _lib = L
     return L
 
@@ -179,6 +184,23 @@ def pc_chunk_prefill_attn(shape, q, k, v, o, lse, k_rope, tok_score, chunk_score
     _check(lib().pc_chunk_prefill_attn(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v),
                                        _ptr(chunk_lens), _ptr(o), _ptr(lse), _ptr(k_rope), _ptr(tok_score), _ptr(chunk_score),
                                        p, n, _stream()), "pc_chunk_prefill_attn")
+
+
+def pc_layer_workspace_bytes(shape, keep_chunks, keep_tokens):
+    return int(lib().pc_layer_workspace_bytes(ctypes.byref(shape), keep_chunks, keep_tokens))
+
+
+def pc_layer_forward(shape, q, k, v, first_len, keep_chunks, keep_tokens, o, lse, k_rope, tok_score, chunk_score,
+                     chunk_idx, chunk_top, tok_idx, tok_cnt, kc, vc, global_o, global_lse, ws, chunk_lens=None,
+                     calibration=None):
+    """calibration: None (Eq. 7) or (lambda, class_lo, class_hi) of Eq. 8, with counts in tok_cnt."""
+    p, n = _ws(ws)
+    lam, lo, hi = calibration if calibration is not None else (0.0, 0, 0)
+    _check(lib().pc_layer_forward(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(chunk_lens), first_len,
+                                  keep_chunks, keep_tokens, int(calibration is not None), lam, lo, hi, _ptr(o),
+                                  _ptr(lse), _ptr(k_rope), _ptr(tok_score), _ptr(chunk_score), _ptr(chunk_idx),
+                                  _ptr(chunk_top), _ptr(tok_idx), _ptr(tok_cnt), _ptr(kc), _ptr(vc), _ptr(global_o),
+                                  _ptr(global_lse), p, n, _stream()), "pc_layer_forward")
 
 
 def pc_chunk_query_scores(shape, q, k, tok_score, chunk_score, ws, chunk_lens=None):

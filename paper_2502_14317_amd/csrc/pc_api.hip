@@ -140,17 +140,39 @@ extern "C" size_t pc_chunk_query_scores_workspace_bytes(const pc_shape* s) {
          pc_align_up(pc_scores_ws_bytes(s), kAlign);
 }
 
-extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const void* k, const void* v,
-                                     const int32_t* chunk_lens, void* o, float* lse, void* k_rope, float* tok_score,
-                                     float* chunk_score, void* ws, size_t ws_bytes, void* stream) {
-  int rc = check_shape(s);
-  if (rc != PC_OK) return rc;
+// The local attention over the tile images in the workspace
+static PcFlashArgs local_flash_args(const pc_shape* s, const void* q, const int32_t* chunk_lens, void* o, float* lse,
+                                    char* base, const PrefillWs& w) {
+  PcFlashArgs a = {};
+  a.q = q; a.k_img = base + w.k_img; a.v_img = base + w.v_img; a.table = (const float2*)(base + w.table); a.o = o; a.lse = lse;
+  a.img_seq_stride = (long long)s->n_kv_heads * (w.Lp / 64);
+  a.img_head_stride = w.Lp / 64;
+  a.n_seq = s->n_chunks; a.n_rows = s->chunk_len + s->query_len;
+  a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads; a.head_dim = s->head_dim;
+  a.seq_ctx = chunk_lens; a.seq_add = s->query_len;
+  a.scale = eff_scale(s->softmax_scale, s->head_dim);
+  return a;
+}
+
+// What pc_chunk_prefill_attn asks of its tensors
+static int check_prefill_args(const void* q, const void* k, const void* v, const void* o, const float* lse,
+                              const void* k_rope, const float* tok_score, const float* chunk_score) {
   if (!q || !k || !v || !o || !lse) return PC_ERR_NULL;
   if (chunk_score && !tok_score) return PC_ERR_NULL;
   // every kernel moves these tensors with 16-byte loads and stores
   if (!pc_aligned(q, 16) || !pc_aligned(k, 16) || !pc_aligned(v, 16) || !pc_aligned(o, 16) ||
       !pc_aligned(k_rope, 16))
     return PC_ERR_SHAPE;
+  return PC_OK;
+}
+
+extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const void* k, const void* v,
+                                     const int32_t* chunk_lens, void* o, float* lse, void* k_rope, float* tok_score,
+                                     float* chunk_score, void* ws, size_t ws_bytes, void* stream) {
+  int rc = check_shape(s);
+  if (rc != PC_OK) return rc;
+  rc = check_prefill_args(q, k, v, o, lse, k_rope, tok_score, chunk_score);
+  if (rc != PC_OK) return rc;
   if (tok_score) {
     rc = check_obs(s, chunk_lens != nullptr);
     if (rc != PC_OK) return rc;
@@ -179,15 +201,8 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
     rc = pc_launch_kv_prepass(k, v, table, kr, k_img, v_img, s->n_chunks, L, w.Lp, s->n_kv_heads, D, st);
   }
   if (rc != PC_OK) return rc;
-
-  PcFlashArgs a = {};
-  a.q = q; a.k_img = k_img; a.v_img = v_img; a.table = table; a.o = o; a.lse = lse;
-  a.img_seq_stride = (long long)s->n_kv_heads * (w.Lp / 64);
-  a.img_head_stride = w.Lp / 64;
-  a.n_seq = s->n_chunks; a.n_rows = L;
-  a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads; a.head_dim = D;
-  a.seq_ctx = chunk_lens; a.seq_add = s->query_len; a.sum = sum;
-  a.scale = eff_scale(s->softmax_scale, D);
+  PcFlashArgs a = local_flash_args(s, q, chunk_lens, o, lse, base, w);
+  a.sum = sum;
   return pc_launch_flash(a, st);
 }
 
@@ -646,7 +661,7 @@ static int tile_attn_run(PcFlashArgs& a, const void* q, int batch, int n_q, int 
   if (rc != PC_OK) return rc;
   a.global = 1; a.q = q_rot; a.o = out; a.lse = lse_out; a.part_o = part_o; a.part_lse = part_lse;
   a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = D;
-  a.scale = scale; a.n_parts = n_parts;
+  a.scale = scale; a.n_parts = n_parts; a.window = 8.0f;
   rc = pc_launch_flash(a, st);
   if (rc != PC_OK || n_parts == 1) return rc;
   return pc_launch_merge_rows(part_o, part_lse, out, lse_out, batch, n_q, n_q_heads, D, n_parts, st);
@@ -741,6 +756,106 @@ extern "C" int pc_parallel_attn(const void* q, const void* kc, const void* vc, c
   return parallel_attn_run(q, kc, vc, seg_len, seg_len_per_head, k_self, v_self, batch, n_q, n_seg,
                            k_t, n_q_heads, n_kv_heads, head_dim, q_pos0, rope_base, softmax_scale,
                            out, lse_out, w, ws, nullptr, nullptr, nullptr, stream);
+}
+
+// ---------------------------------------------------------------------------- a whole layer
+static int check_select_tokens(int n_sel, int n_kv_heads, int chunk_len, int k) {
+  if (n_sel < 0 || n_kv_heads < 1 || chunk_len < 1 || chunk_len > 32768 || k < 1 || k > chunk_len) return PC_ERR_SHAPE;
+  if ((long long)n_sel * n_kv_heads > 0x7fffffffLL) return PC_ERR_SHAPE;
+  return PC_OK;
+}
+
+extern "C" size_t pc_layer_workspace_bytes(const pc_shape* s, int32_t keep_chunks, int32_t keep_tokens) {
+  const size_t prefill = pc_chunk_prefill_workspace_bytes(s);
+  if (prefill == 0) return 0;
+  const size_t attn = pc_parallel_attn_workspace_bytes(1, s->query_len, keep_chunks, keep_tokens, s->n_q_heads,
+                                                       s->n_kv_heads, s->head_dim, 1);
+  return attn ? pc_align_up(prefill, kAlign) + attn : 0;
+}
+
+extern "C" int pc_layer_forward(const pc_shape* s, const void* q, const void* k, const void* v, const int32_t* chunk_lens,
+                                int32_t first_len, int32_t keep_chunks, int32_t keep_tokens, int32_t calibrated, float lambda,
+                                int32_t class_lo, int32_t class_hi, void* o, float* lse, void* k_rope, float* tok_score,
+                                float* chunk_score, int32_t* chunk_idx, float* chunk_top, int32_t* tok_idx, int32_t* tok_cnt,
+                                void* kc, void* vc, void* global_o, float* global_lse, void* ws, size_t ws_bytes, void* stream) {
+  int rc = check_shape(s);
+  if (rc != PC_OK) return rc;
+  rc = check_prefill_args(q, k, v, o, lse, k_rope, tok_score, chunk_score);
+  if (rc != PC_OK) return rc;
+  if (!tok_score || !chunk_score || !k_rope || !chunk_idx || !tok_idx || (calibrated && !tok_cnt)) return PC_ERR_NULL;
+  rc = check_obs(s, chunk_lens != nullptr);
+  if (rc != PC_OK) return rc;
+  const int C = s->n_chunks, w_ctx = s->chunk_len, n_q = s->query_len, Hq = s->n_q_heads, Hkv = s->n_kv_heads, D = s->head_dim;
+  if (C > 4096 || keep_chunks < 1 || keep_chunks > C || first_len < 0 || first_len > w_ctx) return PC_ERR_SHAPE;
+  rc = check_select_tokens(keep_chunks, Hkv, w_ctx, keep_tokens);
+  if (rc != PC_OK) return rc;
+  if (calibrated && (class_lo < 0 || class_hi < class_lo || class_hi > w_ctx || lambda != lambda)) return PC_ERR_SHAPE;
+  if (!kc || !vc) return PC_ERR_NULL;
+  // the query block: the rows behind chunk 0's context
+  const uint16_t* q_blk = (const uint16_t*)q + (size_t)first_len * Hq * D;
+  const uint16_t* k_self = (const uint16_t*)k_rope + (size_t)first_len * Hkv * D;
+  const uint16_t* v_self = (const uint16_t*)v + (size_t)first_len * Hkv * D;
+  rc = check_par_args(q_blk, kc, vc, calibrated != 0, k_self, v_self, 1, n_q, keep_chunks, keep_tokens, Hq, Hkv, D, first_len,
+                      s->rope_base, s->softmax_scale, global_o);
+  if (rc != PC_OK) return rc;
+  const PrefillWs w = prefill_ws_layout(s);
+  const size_t attn0 = pc_align_up(pc_chunk_prefill_workspace_bytes(s), kAlign);
+  const ParWs pw = par_ws_layout(1, n_q, keep_chunks, keep_tokens, Hq, Hkv, D, 1);
+  if (!ws || !pc_aligned(ws, kAlign) || ws_bytes < attn0 + pw.total) return PC_ERR_WORKSPACE;
+  if (!pw.small) {
+    rc = check_tile_limits(keep_chunks, keep_tokens, 0, Hkv, 1);
+    if (rc != PC_OK) return rc;
+  }
+  hipStream_t st = (hipStream_t)stream;
+  char* base = (char*)ws;
+  char* attn = base + attn0;
+  float2* table = (float2*)(base + w.table);
+  const float scale = eff_scale(s->softmax_scale, D);
+  const int L = w_ctx + n_q;
+
+  if (pw.small) rc = pc_launch_rope_table(table, L, D, s->rope_base, st);
+  else rc = pc_launch_rope_table_queries(table, L, D, s->rope_base, q_blk, attn + pw.q_rot, n_q, Hq, first_len,
+                                         scale * 1.4426950408889634f, st);
+  if (rc != PC_OK) return rc;
+  PcChunkSum sum = {};
+  const PcPrepassOut pre = {v, k_rope, base + w.k_img, base + w.v_img, w.Lp};
+  rc = pc_launch_scores(s, q, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
+  if (rc != PC_OK) return rc;
+  // the selections need the scores, not the attention: they and the gather come first, and the global
+  // attention rides in the local one's launch
+  const int lo = calibrated ? class_lo : 0, hi = calibrated ? class_hi : 0;
+  const int32_t* lens = calibrated ? chunk_lens : nullptr;
+  int32_t* cnt = calibrated ? tok_cnt : nullptr;
+  if (pc_select_layer_fits(C, sum.per_chunk)) {
+    rc = pc_launch_select_layer(sum, C, keep_chunks, tok_score, Hkv, w_ctx, keep_tokens, lambda, lo, hi, lens, chunk_idx,
+                                chunk_top, tok_idx, cnt, st);
+  } else {
+    rc = pc_launch_chunk_sums(sum, C, st);
+    if (rc == PC_OK) rc = pc_launch_select_chunks(chunk_score, C, keep_chunks, chunk_idx, chunk_top, st);
+    if (rc == PC_OK)
+      rc = pc_launch_select_tokens(tok_score, chunk_idx, keep_chunks, Hkv, w_ctx, keep_tokens, lambda, lo, hi, lens, tok_idx, cnt, st);
+  }
+  if (rc != PC_OK) return rc;
+  rc = pc_launch_gather(k_rope, v, chunk_idx, tok_idx, 1, C, L, keep_chunks, Hkv, keep_tokens, D, kc, vc, nullptr, nullptr, st);
+  if (rc != PC_OK) return rc;
+  const PcFlashArgs local = local_flash_args(s, q, chunk_lens, o, lse, base, w);
+  if (pw.small) {
+    rc = pc_launch_flash(local, st);
+    if (rc != PC_OK) return rc;
+    return parallel_attn_run(q_blk, kc, vc, cnt, calibrated != 0, k_self, v_self, 1, n_q, keep_chunks, keep_tokens, Hq, Hkv, D,
+                             first_len, s->rope_base, s->softmax_scale, global_o, global_lse, pw, attn, nullptr, nullptr,
+                             nullptr, stream);
+  }
+  PcFlashArgs g = {};
+  g.grp[0] = segment_group(kc, vc, cnt, calibrated != 0, keep_chunks, keep_tokens, Hkv, D);
+  g.grp[2] = self_group(k_self, v_self, n_q, Hkv, D);
+  g.global = 1; g.q = attn + pw.q_rot; g.o = global_o; g.lse = global_lse;
+  g.part_o = (float*)(attn + pw.part_o); g.part_lse = (float*)(attn + pw.part_lse);
+  g.n_seq = 1; g.n_rows = n_q; g.n_q_heads = Hq; g.n_kv_heads = Hkv; g.head_dim = D; g.scale = scale; g.window = 0.0f;
+  g.n_parts = pc_flash_both_parts(C, L, n_q, Hq, Hkv, D, key_tiles(keep_chunks, keep_tokens) + key_tiles(1, n_q), pw.n_parts);
+  rc = pc_launch_flash_both(local, g, st);
+  if (rc != PC_OK || g.n_parts == 1) return rc;
+  return pc_launch_merge_rows(g.part_o, g.part_lse, global_o, global_lse, 1, n_q, Hq, D, g.n_parts, st);
 }
 
 // ---------------------------------------------------------------------------- decoding step

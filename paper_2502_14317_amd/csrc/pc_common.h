@@ -169,6 +169,24 @@ __device__ __forceinline__ uint32_t pc_order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// chunk_score[c] = sum of per_chunk block sums; chunk_score == nullptr: nothing to do
+struct PcChunkSum { const float* blk_sum; float* chunk_score; int per_chunk; };
+// The sum of chunk c in a fixed order, so that it does not depend on timing or on who computes it: 256
+// strided partial sums, added pairwise 128 apart, 64, .. 1.
+// By 256 threads; red: 256 floats of LDS.
+__device__ __forceinline__ void pc_chunk_sum(const float* blk_sum, float* chunk_score, int per_chunk, int c, float* red) {
+  const float* src = blk_sum + (long long)c * per_chunk;
+  float x = 0.f;
+  for (int i = threadIdx.x; i < per_chunk; i += 256) x += src[i];
+  red[threadIdx.x] = x;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) chunk_score[c] = red[0];
+}
+
 // ---------------------------------------------------------------- kernels' host launchers
 // (each defined in its own translation unit; all arguments already validated)
 int pc_launch_gather(const void* k_src, const void* v_src, const int32_t* chunk_idx,
@@ -183,11 +201,22 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
                             int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
                             int32_t* out_cnt, hipStream_t st);
 
+// Chunks and tokens in one launch: every workgroup adds up and ranks the chunk scores for itself.  sum: the
+// pass-2 block sums; also written: sum.chunk_score, chunk_idx, chunk_top (nullable).
+bool pc_select_layer_fits(int n_chunks, int per_chunk);
+int pc_launch_select_layer(const PcChunkSum& sum, int n_chunks, int n_sel, const float* tok_score, int n_kv_heads, int chunk_len,
+                           int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* chunk_idx,
+                           float* chunk_top, int32_t* out_idx, int32_t* out_cnt, hipStream_t st);
+int pc_launch_chunk_sums(const PcChunkSum& sum, int n_chunks, hipStream_t st);
+
 int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, int cap,
                           int32_t* queue_id, float* queue_score, int32_t* queue_slot,
                           int32_t* slot_src, hipStream_t st);
 
 int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st);
+// The table and, as pc_launch_rope_q leaves them, n_q query rows
+int pc_launch_rope_table_queries(float2* table, int n_pos, int head_dim, float base, const void* q, void* q_rot, int n_q,
+                                 int n_heads, int pos0, float mul, hipStream_t st);
 
 // K/V pre-pass of the local attention: K rotated -> k_rope (row-major, optional) and K tile images;
 // V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
@@ -209,22 +238,6 @@ struct PcKvGroup {
   long long seq_stride, seg_stride, head_stride;
 };
 #define PC_KV_GROUPS 3
-// chunk_score[c] = sum of per_chunk block sums; chunk_score == nullptr: nothing to do
-struct PcChunkSum { const float* blk_sum; float* chunk_score; int per_chunk; };
-// By 256 threads, in a fixed order (thread-strided partial sums, then a tree), so that the result does
-// not depend on timing; red: 256 floats of LDS.
-__device__ __forceinline__ void pc_chunk_sum(const float* blk_sum, float* chunk_score, int per_chunk, int c, float* red) {
-  const float* src = blk_sum + (long long)c * per_chunk;
-  float x = 0.f;
-  for (int i = threadIdx.x; i < per_chunk; i += 256) x += src[i];
-  red[threadIdx.x] = x;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) chunk_score[c] = red[0];
-}
 struct PcFlashArgs {
   int global;
   const void* q;            // [n_seq, n_rows, H_q, D] bf16.  Local: rotated here by `table` and scaled; global:
@@ -245,6 +258,7 @@ struct PcFlashArgs {
   int sum_blocks;           //   8, so that those keep their XCDs; set by the launcher)
   // global
   PcKvGroup grp[PC_KV_GROUPS];
+  float window;             // log2 units a row's maximum may exceed its reference at a tile's first keys
   int n_parts;              // workgroups a Q tile's keys are cut into; 1: o and lse are written
   float* part_o;            // n_parts > 1: [n_seq, n_parts, n_rows, H_q, D] fp32
   float* part_lse;          // [n_seq, n_parts, n_rows, H_q]
@@ -256,6 +270,9 @@ int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int hea
 // this and of every smaller call, so it never falls where a size grows
 size_t pc_flash_part_rows(size_t rows, long long n_tiles, int has_self);
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
+// One launch of both (the chunk sums are not its business), and the parts of the global one in it
+int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st);
+int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most);
 
 int pc_launch_self_info(const void* logits, const int32_t* targets, int n_chunks, int n_tokens,
                         int vocab, int negate, float* token_nll, float* info, hipStream_t st);

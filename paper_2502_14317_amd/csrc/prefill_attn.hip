@@ -23,8 +23,9 @@
 // visits key tiles up to its diagonal and the mask is applied on diagonal tiles only.
 // Workgroups are ordered so that one XCD works on one (sequence, KV head) at a time (its K/V
 // stay in that XCD's L2) and takes the long (late) Q tiles first.
-#include "pc_common.h"
+#include "rope.h"
 #include <math.h>
+#include <algorithm>
 #include <type_traits>
 
 #define PC_FA_NB 1                   // 32-row blocks per wavefront
@@ -58,6 +59,40 @@ int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hip
   PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
   hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, n_pos,
                      head_dim, pc_rope_factors(base, head_dim));
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+
+// The table, and behind its workgroups the query block's rows for the global attention (pc_launch_rope_q's
+// result): neither depends on anything, and a launch of their own each costs 3 to 6 us.
+template <int D>
+__global__ __launch_bounds__(256) void rope_table_queries_kernel(float2* __restrict__ table, int n_pos, PcRope rope,
+                                                                 int table_blocks, const uint16_t* __restrict__ q,
+                                                                 uint16_t* __restrict__ q_rot, int n_q, int n_heads,
+                                                                 int pos0, double mul) {
+  if ((int)blockIdx.x >= table_blocks) {
+    pc_rope_q_workgroup<D>(q, q_rot, blockIdx.x - table_blocks, n_q, n_heads, pos0, rope, mul);
+    return;
+  }
+  const int idx = blockIdx.x * 256 + threadIdx.x, p = idx / (D / 2), i = idx % (D / 2);
+  if (p >= n_pos) return;
+  double sn, cs;
+  pc_sincos((double)p * pc_rope_theta(rope, i), sn, cs);
+  table[idx] = make_float2((float)cs, (float)sn);
+}
+
+int pc_launch_rope_table_queries(float2* table, int n_pos, int head_dim, float base, const void* q, void* q_rot, int n_q,
+                                 int n_heads, int pos0, float mul, hipStream_t st) {
+  const int table_blocks = (int)(((long long)n_pos * (head_dim / 2) + 255) / 256);
+  const dim3 grid(table_blocks + n_q), block(256);
+  const PcRope rope = pc_rope_factors(base, head_dim);
+  PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
+  if (head_dim == 128)
+    hipLaunchKernelGGL(rope_table_queries_kernel<128>, grid, block, 0, st, table, n_pos, rope, table_blocks, (const uint16_t*)q,
+                       (uint16_t*)q_rot, n_q, n_heads, pos0, (double)mul);
+  else
+    hipLaunchKernelGGL(rope_table_queries_kernel<64>, grid, block, 0, st, table, n_pos, rope, table_blocks, (const uint16_t*)q,
+                       (uint16_t*)q_rot, n_q, n_heads, pos0, (double)mul);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
@@ -241,12 +276,11 @@ __device__ __forceinline__ void pc_kv_find(const PcKvGroup& kg, int b, int g, in
 //   are cut into n_parts equal runs, one workgroup each.  With one part the workgroup writes the
 //   final output, otherwise a partial result for the merge.
 template <int D, bool GLOBAL>
-__global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs a) {
+__device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, uint16_t* smem) {
   using SM = FlashSmem<D>;
   constexpr int KS = D / 16;        // k-steps of the first product (over head_dim)
   constexpr int DB = D / 32;        // 32-row blocks of O^T (over head_dim)
   constexpr int HALF = D / 2;
-  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   auto k_at = [&](int t) __attribute__((always_inline)) { return (t % SM::KBUF) * SM::K_ELEMS; };
   auto k_lds = [&](int t) __attribute__((always_inline)) { return smem + k_at(t); };
   auto v_lds = [&](int t) __attribute__((always_inline)) {
@@ -261,15 +295,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
   const int n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
   const int per_group = GLOBAL ? n_qt * a.n_parts : G * n_qt;
   const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
-  int cg, within, bid = blockIdx.x;
-  if (!GLOBAL) {
-    static_assert(PC_FA_THREADS == 256, "pc_chunk_sum");
-    if (bid < a.sum_blocks) {
-      if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
-      return;
-    }
-    bid -= a.sum_blocks;
-  }
+  int cg, within;
   if (bid < full_blocks) {
     const int xcd = bid % 8, jb = bid / 8;
     const int batch = jb / (a.group_batch * per_group), in_batch = jb % (a.group_batch * per_group);
@@ -853,7 +879,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
       // at the start of a segment the reference moves up to the step's maximum, however little it
       // grew, as it does at the start of a run: probability 1 is exact in bf16, so a short
       // segment's heaviest key carries no rounding error
-      const float window = cur.seg_start ? 0.0f : 8.0f;
+      const float window = cur.seg_start ? 0.0f : a.window;
       cur_next();                                            // tile p + 2 (or the last one again)
       const TileLoad ld = tile_load();
       const int t_ld = min(p + 2, T - 1);
@@ -935,20 +961,44 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
 }
 
 template <int D, bool GLOBAL>
-static int launch_flash_t(const PcFlashArgs& args, hipStream_t st) {
-  PcFlashArgs a = args;
-  using SM = FlashSmem<D>;
-  auto kern = flash_fwd_kernel<D, GLOBAL>;
-  static std::atomic<uint64_t> raised{0};          // one per instantiation of this launcher
-  const int lds_rc = pc_raise_dynamic_lds((const void*)kern, SM::BYTES, raised);
-  if (lds_rc != PC_OK) return lds_rc;
+__global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  int bid = blockIdx.x;
+  if (!GLOBAL) {
+    static_assert(PC_FA_THREADS == 256, "pc_chunk_sum");
+    if (bid < a.sum_blocks) {
+      if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
+      return;
+    }
+    bid -= a.sum_blocks;
+  }
+  flash_workgroup<D, GLOBAL>(a, bid, smem);
+}
+
+// Local and global attention in one launch, for a layer whose selections are done before the local
+// attention (which nothing of the path reads): the global workgroups stand in front, so that they and their
+// latencies hide behind the local ones.  glob_blocks of them, padded to `front`, a multiple of 8, so that
+// the local ones keep their XCDs.
+template <int D>
+__global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_both_kernel(PcFlashArgs local, PcFlashArgs global, int glob_blocks,
+                                                                      int front) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int bid = blockIdx.x;
+  if (bid >= front) flash_workgroup<D, false>(local, bid - front, smem);
+  else if (bid < glob_blocks) flash_workgroup<D, true>(global, bid, smem);
+}
+
+// The global part's reference follows the maximum at every tile there (window 0), as it starts anew in every part of
+// a run that is cut: one long run is then at least as exact as the parts it replaces (512 rows over 8 x 2048
+// keys, from 64 bits: 4 parts 5.52e-3, one part 5.46e-3, with the lazy window 5.54e-3).  It costs 2 % of a launch
+// that holds global workgroups only, and does not show here.
+
+// Workgroups of a call without those of the chunk sums; fills in what the launcher decides
+template <bool GLOBAL>
+static long long flash_blocks(PcFlashArgs& a) {
   const int G = a.n_q_heads / a.n_kv_heads;
   const long long rows_wg = GLOBAL ? (long long)a.n_rows * G : a.n_rows;
   const long long n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
-  a.sum_blocks = !GLOBAL && a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
-  const long long blocks = (long long)a.n_seq * a.n_kv_heads * n_qt * (GLOBAL ? a.n_parts : G) + a.sum_blocks;
-  if (blocks == 0) return PC_OK;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
   // Local: a group that cannot fill an XCD's 64 workgroup slots by itself is interleaved with
   // others, up to three rounds of slots, so that the long Q tiles of all of them start first.  A
   // group that can keeps its XCD to itself: its short tiles then overlap the start of the next
@@ -961,12 +1011,72 @@ static int launch_flash_t(const PcFlashArgs& args, hipStream_t st) {
     const long long m = (192 + per_group - 1) / per_group, batches = (groups_xcd + m - 1) / m;
     a.group_batch = (int)((groups_xcd + batches - 1) / batches);           // batches of equal size
   }
-  // image loads address one (sequence, head) region with 32-bit byte offsets
-  if (!GLOBAL && ((long long)a.n_rows + 63) / 64 * 64 * D * 2 >= 0x7fffffffLL) return PC_ERR_SHAPE;
+  return (long long)a.n_seq * a.n_kv_heads * per_group;
+}
+
+// image loads address one (sequence, head) region with 32-bit byte offsets
+static bool images_too_long(const PcFlashArgs& a) {
+  return ((long long)a.n_rows + 63) / 64 * 64 * a.head_dim * 2 >= 0x7fffffffLL;
+}
+
+template <int D, bool GLOBAL>
+static int launch_flash_t(const PcFlashArgs& args, hipStream_t st) {
+  PcFlashArgs a = args;
+  using SM = FlashSmem<D>;
+  auto kern = flash_fwd_kernel<D, GLOBAL>;
+  static std::atomic<uint64_t> raised{0};          // one per instantiation of this launcher
+  const int lds_rc = pc_raise_dynamic_lds((const void*)kern, SM::BYTES, raised);
+  if (lds_rc != PC_OK) return lds_rc;
+  a.sum_blocks = !GLOBAL && a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
+  const long long blocks = flash_blocks<GLOBAL>(a) + a.sum_blocks;
+  if (blocks == 0) return PC_OK;
+  if (blocks > 0x7fffffffLL || (!GLOBAL && images_too_long(a))) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_FLASH, st);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(PC_FA_THREADS), SM::BYTES, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
+}
+
+template <int D>
+static int launch_flash_both_t(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
+  PcFlashArgs l = local, g = global;
+  using SM = FlashSmem<D>;
+  static std::atomic<uint64_t> raised{0};
+  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_both_kernel<D>, SM::BYTES, raised);
+  if (lds_rc != PC_OK) return lds_rc;
+  const long long glob_blocks = flash_blocks<true>(g), front = (glob_blocks + 7) / 8 * 8, blocks = front + flash_blocks<false>(l);
+  if (blocks > 0x7fffffffLL || images_too_long(l)) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_FLASH, st);
+  hipLaunchKernelGGL(flash_both_kernel<D>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), SM::BYTES, st, l, g, (int)glob_blocks, (int)front);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
+  return local.head_dim == 128 ? launch_flash_both_t<128>(local, global, st) : launch_flash_both_t<64>(local, global, st);
+}
+
+// Parts of the global attention's keys next to a local attention of n_seq sequences of n_rows rows, 1 to
+// `most`: the least estimated time of both, which share 512 slots.  A slot holds a workgroup for some 10 us +
+// 1.54 us a 64-key tile (local; 2.1 global; head_dim 64 1.0 and 1.4), and the launch does not end before the
+// longest; cutting costs the merge, 5 us + what it reads.
+int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most) {
+  const double loc_us = head_dim == 128 ? 1.54 : 1.0, glob_us = head_dim == 128 ? 2.1 : 1.4;
+  double work = 0.0, longest = 0.0;
+  for (int r0 = 0; r0 < n_rows; r0 += PC_FA_BM) {
+    const double us = 10.0 + loc_us * ((std::min(n_rows, r0 + PC_FA_BM) + 63) / 64);
+    work += us * n_seq * n_q_heads;
+    longest = us;
+  }
+  const long long wgs = (long long)n_kv_heads * (((long long)n_q * (n_q_heads / n_kv_heads) + PC_FA_BM - 1) / PC_FA_BM);
+  const double merge_us = 0.4 + (double)n_q * n_q_heads * head_dim * 4 / 7e6;
+  int best_p = 1;
+  double best = 0.0;
+  for (int p = 1; p <= most && p <= n_tiles; ++p) {
+    const double each = 10.0 + glob_us * (double)((n_tiles + p - 1) / p);
+    const double us = std::max((work + each * (double)(wgs * p)) / 512.0, std::max(longest, each)) + (p > 1 ? 5.0 + merge_us * p : 0.0);
+    if (p == 1 || us < best) { best = us; best_p = p; }
+  }
+  return best_p;
 }
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {

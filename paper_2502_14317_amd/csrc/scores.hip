@@ -686,6 +686,13 @@ __global__ __launch_bounds__(256) void chunk_score_kernel(const float* __restric
   pc_chunk_sum(blk_sum, chunk_score, per_chunk, blockIdx.x, red);
 }
 
+int pc_launch_chunk_sums(const PcChunkSum& sum, int n_chunks, hipStream_t st) {
+  PcProfScope prof(PC_KERNEL_CHUNK_SCORE, st);
+  hipLaunchKernelGGL(chunk_score_kernel, dim3(n_chunks), dim3(256), 0, st, sum.blk_sum, sum.chunk_score, sum.per_chunk);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+
 template <int D, int PASS>
 static void launch_scores_pass(int wpc, dim3 grid, dim3 block, hipStream_t st, const PcScoreArgs& a) {
   if (wpc == 0 && a.kb_keys == PC_SC_KB_MANY)
@@ -794,10 +801,7 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
   if (later) {
     *later = PcChunkSum{a.blk_sum, chunk_score, s->n_kv_heads * n_kb2};
   } else if (chunk_score) {
-    PcProfScope prof(PC_KERNEL_CHUNK_SCORE, st);
-    hipLaunchKernelGGL(chunk_score_kernel, dim3(s->n_chunks), dim3(256), 0, st, a.blk_sum,
-                       chunk_score, s->n_kv_heads * n_kb2);
-    PC_LAUNCH_CHECK();
+    return pc_launch_chunk_sums(PcChunkSum{a.blk_sum, chunk_score, s->n_kv_heads * n_kb2}, s->n_chunks, st);
   }
   return PC_OK;
 }

@@ -128,11 +128,66 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 // ballots, no histogram: 8.5, 14.6 and 23.8.)
 #define PC_SEL_BINS 2048
 
-template <int KPT, int THREADS>
+// A layer's chunk selection in the same launch: every workgroup adds up the chunks' block sums (the order
+// of pc_chunk_sum, a wavefront a chunk, its 4 x 64 strided sums asked for at once), ranks them as
+// select_chunks_kernel does and takes the chunk of its rank; the first workgroup writes scores and ranks.
+// 2 us in front of the tokens instead of a launch of 5 us, for at most 64 chunks of 2048 block sums.
+#define PC_SEL_CHUNKS 64
+#define PC_SEL_BLOCKS 2048
+struct PcSelectChunks {
+  PcChunkSum sum;
+  int n_chunks;
+  int32_t* idx;            // [n_sel] out
+  float* top;              // [n_sel] out, nullable
+};
+template <int THREADS>
+__device__ __forceinline__ int select_own_chunk(const PcSelectChunks& x, int n_sel, int s, bool writer) {
+  __shared__ float score[PC_SEL_CHUNKS];
+  __shared__ int own;
+  const int wave = threadIdx.x / PC_WAVE, lane = threadIdx.x % PC_WAVE;
+  for (int c = wave; c < x.n_chunks; c += THREADS / PC_WAVE) {
+    const float* src = x.sum.blk_sum + (long long)c * x.sum.per_chunk;
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < x.sum.per_chunk; i0 += 256) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = i0 + 64 * j + lane;
+        if (i < x.sum.per_chunk) part[j] += src[i];
+      }
+    }
+    float v = (part[0] + part[2]) + (part[1] + part[3]);
+#pragma unroll
+    for (int off = PC_WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (lane == 0) score[c] = v;
+  }
+  __syncthreads();
+  const int i = threadIdx.x;
+  if (i < x.n_chunks) {
+    const uint32_t ki = pc_order_key(score[i]);
+    int rank = 0;
+    for (int j = 0; j < x.n_chunks; ++j) {
+      const uint32_t kj = pc_order_key(score[j]);
+      rank += (kj > ki) || (kj == ki && j < i);
+    }
+    if (rank == s) own = i;
+    if (writer) {
+      x.sum.chunk_score[i] = score[i];
+      if (rank < n_sel) {
+        x.idx[rank] = i;
+        if (x.top) x.top[rank] = score[i];
+      }
+    }
+  }
+  __syncthreads();
+  return own;
+}
+
+// CHUNKS: the chunk is found here (chunk_idx is not read), otherwise it is chunk_idx[s]
+template <int KPT, int THREADS, bool CHUNKS>
 __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     const float* __restrict__ tok_score, const int32_t* __restrict__ chunk_idx, int n_kv_heads,
     int n, int k, float lambda, int cls_lo, int cls_hi, const int32_t* __restrict__ chunk_lens,
-    int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt) {
+    int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt, PcSelectChunks chunks) {
   constexpr int WAVES = THREADS / PC_WAVE, BPT = PC_SEL_BINS / THREADS;      // bins per thread
   __shared__ uint32_t hist[PC_SEL_BINS];
   __shared__ uint32_t sh_cand, sh_min, sh_max, sh_bin, sh_need, sh_in_bin;
@@ -140,7 +195,9 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
 
   const int s = blockIdx.x / n_kv_heads;
   const int g = blockIdx.x % n_kv_heads;
-  const int c = chunk_idx ? chunk_idx[s] : s;
+  int c;
+  if (CHUNKS) c = select_own_chunk<THREADS>(chunks, (int)gridDim.x / n_kv_heads, s, blockIdx.x == 0);
+  else c = chunk_idx ? chunk_idx[s] : s;
   if (c < 0) return;                               // no chunk for this entry: its outputs stay as they are
   const float* src = tok_score + ((long long)c * n_kv_heads + g) * n;
   int32_t* dst = out_idx + (long long)blockIdx.x * k;
@@ -251,17 +308,17 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   }
 }
 
-int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, int n_sel,
-                            int n_kv_heads, int chunk_len, int k, float lambda, int cls_lo,
-                            int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
-                            int32_t* out_cnt, hipStream_t st) {
+template <bool CHUNKS>
+static int launch_tokens(const float* tok_score, const int32_t* chunk_idx, int n_sel, int n_kv_heads, int chunk_len,
+                         int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
+                         int32_t* out_cnt, const PcSelectChunks& chunks, hipStream_t st) {
   PcProfScope prof(PC_KERNEL_SELECT_TOKENS, st);
   // key slots per thread: the smallest power of two that holds the chunk (at most 32768 tokens), up
   // to 8 with 512 threads, whose barriers are cheaper
-#define PC_SEL_LAUNCH(KPT, THREADS)                                                                   \
-  hipLaunchKernelGGL((select_tokens_kernel<KPT, THREADS>), dim3(n_sel * n_kv_heads), dim3(THREADS), 0, \
-                     st, tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,      \
-                     chunk_lens, out_idx, out_cnt)
+#define PC_SEL_LAUNCH(KPT, THREADS)                                                                             \
+  hipLaunchKernelGGL((select_tokens_kernel<KPT, THREADS, CHUNKS>), dim3(n_sel * n_kv_heads), dim3(THREADS), 0,   \
+                     st, tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,                \
+                     chunk_lens, out_idx, out_cnt, chunks)
   if (chunk_len <= 512) PC_SEL_LAUNCH(1, 512);
   else if (chunk_len <= 1024) PC_SEL_LAUNCH(2, 512);
   else if (chunk_len <= 2048) PC_SEL_LAUNCH(4, 512);
@@ -272,4 +329,20 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
 #undef PC_SEL_LAUNCH
   PC_LAUNCH_CHECK();
   return PC_OK;
+}
+
+int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, int n_sel,
+                            int n_kv_heads, int chunk_len, int k, float lambda, int cls_lo,
+                            int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
+                            int32_t* out_cnt, hipStream_t st) {
+  return launch_tokens<false>(tok_score, chunk_idx, n_sel, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi, chunk_lens,
+                              out_idx, out_cnt, PcSelectChunks{}, st);
+}
+
+bool pc_select_layer_fits(int n_chunks, int per_chunk) { return n_chunks <= PC_SEL_CHUNKS && per_chunk <= PC_SEL_BLOCKS; }
+int pc_launch_select_layer(const PcChunkSum& sum, int n_chunks, int n_sel, const float* tok_score, int n_kv_heads, int chunk_len,
+                           int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* chunk_idx,
+                           float* chunk_top, int32_t* out_idx, int32_t* out_cnt, hipStream_t st) {
+  return launch_tokens<true>(tok_score, nullptr, n_sel, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi, chunk_lens, out_idx,
+                             out_cnt, PcSelectChunks{sum, n_chunks, chunk_idx, chunk_top}, st);
 }

@@ -38,8 +38,8 @@ class ParallelCompLayer:
             self.vc = torch.empty_like(self.kc)
             self.global_o = torch.empty((1, query_len, Hq, D), dtype=bf, device=dev)
             self.global_lse = torch.empty((1, Hq, query_len), dtype=f32, device=dev)
-            ws = max(ws, B.pc_parallel_attn_workspace_bytes(1, query_len, keep_chunks, keep_tokens,
-                                                            Hq, Hkv, D, True))
+            # room for the attention call's workspace behind the prefill's
+            ws = max(ws, B.pc_layer_workspace_bytes(self.shape, keep_chunks, keep_tokens))
         self.ws = B.alloc_workspace(ws, dev)
 
     def chunk_prefill(self, q, k, v, with_scores=True, chunk_lens=None, first_len=None):
@@ -78,10 +78,20 @@ class ParallelCompLayer:
                            seg_len_per_head=per_head)
 
     def forward(self, q, k, v, chunk_lens=None, first_len=None):
-        self.chunk_prefill(q, k, v, with_scores=True, chunk_lens=chunk_lens, first_len=first_len)
-        if self.kc_n > 0:
-            self.evict_and_attend(q, v)
-        return self.global_o if self.kc_n > 0 else self.o
+        """chunk_prefill and evict_and_attend as one call."""
+        if self.kc_n == 0:
+            self.chunk_prefill(q, k, v, with_scores=True, chunk_lens=chunk_lens, first_len=first_len)
+            return self.o
+        self.chunk_lens = chunk_lens
+        self.first_len = self.w if first_len is None else int(first_len)
+        calibration = self.calibration
+        if calibration is None and chunk_lens is not None:          # short chunks: counts per head, nothing evicted
+            calibration = (float("inf"), 0, 0)
+        B.pc_layer_forward(self.shape, q, k, v, self.first_len, self.kc_n, self.kt_n, self.o, self.lse, self.k_rope,
+                           self.tok_score, self.chunk_score, self.chunk_idx, self.chunk_top, self.tok_idx, self.tok_cnt,
+                           self.kc, self.vc, self.global_o, self.global_lse, self.ws, chunk_lens=chunk_lens,
+                           calibration=calibration)
+        return self.global_o
 
 
 class StreamingParallelComp:
