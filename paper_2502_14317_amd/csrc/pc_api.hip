@@ -189,14 +189,17 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
   void* kr = k_rope;                                       // nullable: then only the images are written
   const int L = s->chunk_len + s->query_len, D = s->head_dim;
 
-  rc = pc_launch_rope_table(table, L, D, s->rope_base, st);
+  PcPrepArgs prep = {};
+  prep.table = table; prep.n_pos = L; prep.rope = pc_rope_factors(s->rope_base, D);
+  if (tok_score) prep.scores = pc_scores_queries(s, q, chunk_lens, base + w.ml);
+  rc = pc_launch_prep(prep, D, st);
   if (rc != PC_OK) return rc;
   PcChunkSum sum = {};
   if (tok_score) {
     // the first score pass reads and rotates every key anyway: it also writes the rotated keys
     // and the tile images (the keys are read from memory once for both jobs)
     const PcPrepassOut pre = {v, kr, k_img, v_img, w.Lp};
-    rc = pc_launch_scores(s, q, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
+    rc = pc_launch_scores(s, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
   } else {
     rc = pc_launch_kv_prepass(k, v, table, kr, k_img, v_img, s->n_chunks, L, w.Lp, s->n_kv_heads, D, st);
   }
@@ -221,9 +224,12 @@ extern "C" int pc_chunk_query_scores(const pc_shape* s, const void* q, const voi
   const int L = s->chunk_len + s->query_len;
   float2* table = (float2*)ws;
   void* ml = (char*)ws + pc_align_up((size_t)L * (s->head_dim / 2) * sizeof(float2), kAlign);
-  rc = pc_launch_rope_table(table, L, s->head_dim, s->rope_base, st);
+  PcPrepArgs prep = {};
+  prep.table = table; prep.n_pos = L; prep.rope = pc_rope_factors(s->rope_base, s->head_dim);
+  prep.scores = pc_scores_queries(s, q, chunk_lens, ml);
+  rc = pc_launch_prep(prep, s->head_dim, st);
   if (rc != PC_OK) return rc;
-  return pc_launch_scores(s, q, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, nullptr, st);
+  return pc_launch_scores(s, k, chunk_lens, table, ml, tok_score, chunk_score, nullptr, nullptr, st);
 }
 
 static int check_append(const void* k_new, const void* v_new, int batch, int n_new, int n_seg, int seg, int k_t,
@@ -813,13 +819,18 @@ extern "C" int pc_layer_forward(const pc_shape* s, const void* q, const void* k,
   const float scale = eff_scale(s->softmax_scale, D);
   const int L = w_ctx + n_q;
 
-  if (pw.small) rc = pc_launch_rope_table(table, L, D, s->rope_base, st);
-  else rc = pc_launch_rope_table_queries(table, L, D, s->rope_base, q_blk, attn + pw.q_rot, n_q, Hq, first_len,
-                                         scale * 1.4426950408889634f, st);
+  PcPrepArgs prep = {};
+  prep.table = table; prep.n_pos = L; prep.rope = pc_rope_factors(s->rope_base, D);
+  if (!pw.small) {
+    prep.q_blk = q_blk; prep.q_rot = (uint16_t*)(attn + pw.q_rot); prep.n_q = n_q; prep.n_heads = Hq; prep.pos0 = first_len;
+    prep.mul = (double)(scale * 1.4426950408889634f);
+  }
+  prep.scores = pc_scores_queries(s, q, chunk_lens, base + w.ml);
+  rc = pc_launch_prep(prep, D, st);
   if (rc != PC_OK) return rc;
   PcChunkSum sum = {};
   const PcPrepassOut pre = {v, k_rope, base + w.k_img, base + w.v_img, w.Lp};
-  rc = pc_launch_scores(s, q, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
+  rc = pc_launch_scores(s, k, chunk_lens, table, base + w.ml, tok_score, chunk_score, &pre, &sum, st);
   if (rc != PC_OK) return rc;
   // the selections need the scores, not the attention: they and the gather come first, and the global
   // attention rides in the local one's launch

@@ -121,6 +121,13 @@ __host__ __device__ __forceinline__ void pc_sincos(double x, double& sn, double&
 
 #define PC_BUF_NT 2        // the same hint on a buffer load
 
+// (x0, x1) -> packed bf16 pair of the values and packed bf16 pair of the rounding remainders
+// (both roundings to nearest-even, in hardware; inputs are finite by contract)
+__device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  hi = pack_bf16x2(x0, x1);
+  lo = pack_bf16x2(x0 - bf16_lo_to_f32(hi), x1 - bf16_hi_to_f32(hi));
+}
+
 // 16-byte global load / store of data that is touched once (streamed): the non-temporal hint
 // keeps it from displacing reusable lines in the caches
 __device__ __forceinline__ uint4 pc_load_once(const uint4* p) {
@@ -213,10 +220,26 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
                           int32_t* queue_id, float* queue_score, int32_t* queue_slot,
                           int32_t* slot_src, hipStream_t st);
 
-int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st);
-// The table and, as pc_launch_rope_q leaves them, n_q query rows
-int pc_launch_rope_table_queries(float2* table, int n_pos, int head_dim, float base, const void* q, void* q_rot, int n_q,
-                                 int n_heads, int pos0, float mul, hipStream_t st);
+// prep.hip: the rotation table [n_pos, D / 2], n_q query rows as pc_launch_rope_q leaves them (0: none), and the
+// score passes' query columns (q_split nullptr: none; filled in by pc_scores_queries)
+struct PcScoreQueries {
+  const uint16_t* q;       // [C, L, H_q, D] before RoPE
+  const int32_t* chunk_lens;
+  uint16_t* q_split;       // [C, H_kv, n_cb][hi, lo][D / 16][64 lanes][8]: rotated, scaled, split query columns as MFMA operands
+  int n_chunks, L, w, w_obs, n_kv_heads, G, n_cols, n_cb;
+  float scale_log2;        // softmax scale x log2(e)
+};
+struct PcPrepArgs {
+  float2* table;
+  int n_pos;
+  PcRope rope;
+  const uint16_t* q_blk;
+  uint16_t* q_rot;
+  int n_q, n_heads, pos0;
+  double mul;
+  PcScoreQueries scores;
+};
+int pc_launch_prep(const PcPrepArgs& a, int head_dim, hipStream_t st);
 
 // K/V pre-pass of the local attention: K rotated -> k_rope (row-major, optional) and K tile images;
 // V -> V^T tile images.  Images: [n_seq][n_kv_heads][Lp / 64][64 * D].
@@ -278,12 +301,14 @@ int pc_launch_self_info(const void* logits, const int32_t* targets, int n_chunks
                         int vocab, int negate, float* token_nll, float* info, hipStream_t st);
 
 size_t pc_scores_ws_bytes(const pc_shape* s);
+PcScoreQueries pc_scores_queries(const pc_shape* s, const void* q, const int32_t* chunk_lens, void* ws);
 // Pre-pass duties the first score pass can take over (it reads and rotates every key anyway):
 // the rotated keys (k_rope, nullable), the K tile images and the V^T tile images of
 // pc_launch_kv_prepass, Lp = L rounded up to 64.
 struct PcPrepassOut { const void* v; void* k_rope; void* k_img; void* v_img; int Lp; };
 // later: the chunk scores' last addition is left to the caller, who passes it to pc_launch_flash
-int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int32_t* chunk_lens, const float2* table,
+// (the query columns of pc_scores_queries come first)
+int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens, const float2* table,
                      void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
                      PcChunkSum* later, hipStream_t st);
 

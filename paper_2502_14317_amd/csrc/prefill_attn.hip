@@ -1,7 +1,6 @@
 // Chunk-batched causal local attention (Eq. 1-2) with chunk-local RoPE, for gfx950.
 //
-// Three kernels:
-//   rope_table_kernel   cos/sin of position * theta_i, computed in fp64, stored fp32
+// Two kernels (and the two modes of the second in one launch):
 //   kv_prepass_kernel   K -> rotated K (bf16, the KV cache later steps gather from) and K tile
 //                       images; V -> V^T tile images (the layouts the tile kernel copies to LDS)
 //   flash_fwd_kernel    online-softmax attention on 32x32x16 bf16 MFMA
@@ -23,7 +22,7 @@
 // visits key tiles up to its diagonal and the mask is applied on diagonal tiles only.
 // Workgroups are ordered so that one XCD works on one (sequence, KV head) at a time (its K/V
 // stay in that XCD's L2) and takes the long (late) Q tiles first.
-#include "rope.h"
+#include "pc_common.h"
 #include <math.h>
 #include <algorithm>
 #include <type_traits>
@@ -42,60 +41,6 @@
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   \
   } while (0)
 #define PC_LN2 0.6931471805599453f
-
-// ------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(float2* __restrict__ table, int n_pos, int D, PcRope rope) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int half = D / 2;
-  if (idx >= n_pos * half) return;
-  const int p = idx / half, i = idx % half;
-  double sn, cs;
-  pc_sincos((double)p * pc_rope_theta(rope, i), sn, cs);
-  table[idx] = make_float2((float)cs, (float)sn);
-}
-
-int pc_launch_rope_table(float2* table, int n_pos, int head_dim, float base, hipStream_t st) {
-  const int n = n_pos * (head_dim / 2);
-  PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, table, n_pos,
-                     head_dim, pc_rope_factors(base, head_dim));
-  PC_LAUNCH_CHECK();
-  return PC_OK;
-}
-
-// The table, and behind its workgroups the query block's rows for the global attention (pc_launch_rope_q's
-// result): neither depends on anything, and a launch of their own each costs 3 to 6 us.
-template <int D>
-__global__ __launch_bounds__(256) void rope_table_queries_kernel(float2* __restrict__ table, int n_pos, PcRope rope,
-                                                                 int table_blocks, const uint16_t* __restrict__ q,
-                                                                 uint16_t* __restrict__ q_rot, int n_q, int n_heads,
-                                                                 int pos0, double mul) {
-  if ((int)blockIdx.x >= table_blocks) {
-    pc_rope_q_workgroup<D>(q, q_rot, blockIdx.x - table_blocks, n_q, n_heads, pos0, rope, mul);
-    return;
-  }
-  const int idx = blockIdx.x * 256 + threadIdx.x, p = idx / (D / 2), i = idx % (D / 2);
-  if (p >= n_pos) return;
-  double sn, cs;
-  pc_sincos((double)p * pc_rope_theta(rope, i), sn, cs);
-  table[idx] = make_float2((float)cs, (float)sn);
-}
-
-int pc_launch_rope_table_queries(float2* table, int n_pos, int head_dim, float base, const void* q, void* q_rot, int n_q,
-                                 int n_heads, int pos0, float mul, hipStream_t st) {
-  const int table_blocks = (int)(((long long)n_pos * (head_dim / 2) + 255) / 256);
-  const dim3 grid(table_blocks + n_q), block(256);
-  const PcRope rope = pc_rope_factors(base, head_dim);
-  PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(rope_table_queries_kernel<128>, grid, block, 0, st, table, n_pos, rope, table_blocks, (const uint16_t*)q,
-                       (uint16_t*)q_rot, n_q, n_heads, pos0, (double)mul);
-  else
-    hipLaunchKernelGGL(rope_table_queries_kernel<64>, grid, block, 0, st, table, n_pos, rope, table_blocks, (const uint16_t*)q,
-                       (uint16_t*)q_rot, n_q, n_heads, pos0, (double)mul);
-  PC_LAUNCH_CHECK();
-  return PC_OK;
-}
 
 // ------------------------------------------------------------------------------------------
 // Tile images.  flash_fwd_kernel copies whole 64-key tiles of K and V^T into LDS with contiguous

@@ -9,9 +9,9 @@
 // into bf16 hi + lo parts, and q.k = hi.hi + hi.lo + lo.hi (three MFMAs; the lo.lo term is
 // below 2^-16 relative).
 //
-// Two passes over the keys, both fully parallel over key blocks of 256 to 1024 keys (the largest
-// block that still leaves every CU several workgroups: a workgroup's start-up, rotating and
-// splitting its query columns, is then spread over more keys):
+// Two passes over the keys, both fully parallel over key blocks of 128 to 1024 keys (the largest
+// block that still leaves every CU several workgroups: a workgroup's start-up is then spread over
+// more keys); the query columns come rotated, scaled and split as MFMA operands (prep.hip):
 //   pass 1  (S^T = K Q^T, a lane owns a voting row)  per-block running max / sum of every
 //           voting row -> workspace [c, g, key block, column] (m, l)
 //   the blocks' (m, l) are combined into the row logsumexp by pass 2 itself while they are few, by a
@@ -38,7 +38,9 @@
 
 #define PC_SC_THREADS 256
 #define PC_SC_WAVES 4
-#define PC_SC_KB 256        // keys per workgroup: the smallest block (sizes the workspace)
+#define PC_SC_KB 256        // keys per workgroup
+#define PC_SC_KB_SMALL 128  // where 256 leave CUs idle
+#define PC_SC_SMALL_WGS 350
 #define PC_SC_KB_MAX 1024   // the largest
 #define PC_SC_TILE 64       // keys staged in LDS at a time
 #define PC_SC_KB_MANY 128   // keys per workgroup with more than 4 column blocks; half where that leaves CUs idle
@@ -46,18 +48,15 @@
 #define PC_SC_LOG2E 1.4426950408889634f
 
 struct PcScoreArgs {
-  const uint16_t* q;       // [C, L, H_q, D] before RoPE
   const uint16_t* k;       // [C, L, H_kv, D] before RoPE
   const int32_t* chunk_lens; // [C] context rows per chunk or nullptr (= w)
   const float2* table;     // [L, D/2] (cos, sin)
   float2* ml;              // workspace [C, H_kv, n_kb, n_cols] (max in log2 units, sum)
   float* lse2;             // workspace [C, H_kv, 32 n_cb] row logsumexp in log2 units (+inf behind n_cols)
-  const uint16_t* q_split; // workspace [C, H_kv, n_cb][hi, lo][D / 16][64 lanes][8]: rotated, scaled, split query
-                           //   columns as MFMA operands (only with more than 4 column blocks)
+  const uint16_t* q_split; // workspace: the query columns as MFMA operands (PcScoreQueries)
   float* tok_score;        // [C, H_kv, w]
   int L, w, w_obs, n_q_heads, n_kv_heads, n_kb, n_cols, n_cb;
-  int kb_keys;             // keys per workgroup: 256, 512 or 1024 (at most 512 when WPC == 4)
-  float scale_log2;        // softmax scale x log2(e), folded into the query operand
+  int kb_keys;             // keys per workgroup: 128, 256, 512 or 1024 (at most 512 when WPC == 4)
   float* blk_sum;          // workspace [C, H_kv, n_kb]: sum of each pass-2 block's tok_score
   // pre-pass duties of pass 1 (all nullptr: off): V rows in, rotated keys / K images / V^T images out
   const uint16_t* v;       // [C, L, H_kv, D]
@@ -66,46 +65,6 @@ struct PcScoreArgs {
   uint16_t* v_img;
   int Lp;                  // L rounded up to 64
 };
-
-// (x0, x1) -> packed bf16 pair of the values and packed bf16 pair of the rounding remainders
-// (both roundings to nearest-even, in hardware; inputs are finite by contract)
-__device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-  hi = pack_bf16x2(x0, x1);
-  lo = pack_bf16x2(x0 - bf16_lo_to_f32(hi), x1 - bf16_hi_to_f32(hi));
-}
-
-// Column `col` of a KV group's (voting row, head) columns as an MFMA operand, the lane half's part:
-// the query row rotated at its position, scaled to log2 units, split hi / lo.
-template <int D>
-__device__ __forceinline__ void load_query_column(const PcScoreArgs& a, int c, int g, int G, int first_obs, int col,
-                                                  int hf, bf16x8 (&qhi)[D / 16], bf16x8 (&qlo)[D / 16]) {
-  constexpr int KS = D / 16, HALF = D / 2;
-  const int row = first_obs + col % a.w_obs;
-  const uint16_t* qrow = a.q + (((long long)c * a.L + row) * a.n_q_heads + g * G + col / a.w_obs) * D;
-  const float2* cs = a.table + (long long)row * HALF;
-#pragma unroll
-  for (int ks = 0; ks < KS / 2; ++ks) {
-    const int i0 = 16 * ks + 8 * hf;
-    const uint4 x1 = *(const uint4*)(qrow + i0);
-    const uint4 x2 = *(const uint4*)(qrow + HALF + i0);
-    const uint32_t aw[4] = {x1.x, x1.y, x1.z, x1.w}, bw[4] = {x2.x, x2.y, x2.z, x2.w};
-    uint32_t h1[4], l1[4], h2[4], l2[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float2 c0 = cs[i0 + 2 * e], c1 = cs[i0 + 2 * e + 1];
-      const float x1l = bf16_lo_to_f32(aw[e]), x1h = bf16_hi_to_f32(aw[e]);
-      const float x2l = bf16_lo_to_f32(bw[e]), x2h = bf16_hi_to_f32(bw[e]);
-      // logits come out of the matrix cores in log2 units: the scale rides on q
-      split_bf16x2((x1l * c0.x - x2l * c0.y) * a.scale_log2, (x1h * c1.x - x2h * c1.y) * a.scale_log2, h1[e], l1[e]);
-      split_bf16x2((x2l * c0.x + x1l * c0.y) * a.scale_log2, (x2h * c1.x + x1h * c1.y) * a.scale_log2, h2[e], l2[e]);
-    }
-    uint4 t;
-    t = make_uint4(h1[0], h1[1], h1[2], h1[3]); qhi[ks] = *(bf16x8*)&t;
-    t = make_uint4(l1[0], l1[1], l1[2], l1[3]); qlo[ks] = *(bf16x8*)&t;
-    t = make_uint4(h2[0], h2[1], h2[2], h2[3]); qhi[ks + KS / 2] = *(bf16x8*)&t;
-    t = make_uint4(l2[0], l2[1], l2[2], l2[3]); qlo[ks + KS / 2] = *(bf16x8*)&t;
-  }
-}
 
 // K tile staging, split in two so that the loads of the next tile are in flight while the matrix
 // cores work on this one: fetch (global -> registers), stage (rotate in fp32, split hi / lo,
@@ -259,7 +218,6 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   __shared__ float2 ml_part[PC_SC_WAVES][32];
 
   const int c = blockIdx.x, g = blockIdx.y, kblock = blockIdx.z;
-  const int G = a.n_q_heads / a.n_kv_heads;
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
   // a short chunk is [len context rows ; the query rows]: its voting rows end at len + w_q
@@ -279,7 +237,14 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   // ---- this lane's column as an MFMA operand
   const int col = min(32 * cb + n, a.n_cols - 1);
   bf16x8 qhi[KS], qlo[KS];
-  if (active) load_query_column<D>(a, c, g, G, first_obs, col, hf, qhi, qlo);
+  {
+    const uint16_t* src = a.q_split + ((((long long)c * a.n_kv_heads + g) * a.n_cb + min(cb, a.n_cb - 1)) * (2 * KS) * PC_WAVE + lane) * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      qhi[ks] = *(const bf16x8*)(src + ks * PC_WAVE * 8);
+      qlo[ks] = *(const bf16x8*)(src + (KS + ks) * PC_WAVE * 8);
+    }
+  }
   // pass 1: this lane's voting row (column) and its running statistics
   const int my_qrow = first_obs + col % a.w_obs;
   float m_run = -INFINITY, l_run = 0.f;
@@ -473,25 +438,12 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
 // columns in registers and streaming the keys would rotate, split and stage every key once per
 // 128 columns.  Here a workgroup stages its 128 keys (hi and lo, 68 KiB) once and the columns
 // stream by: a wavefront takes every fourth column block and reads it as ready MFMA operands
-// (split once, by score_queries_kernel) while the block before is multiplied.  No barrier and no
+// (split once, in prep.hip) while the block before is multiplied.  No barrier and no
 // conversion in the loop: bound by the matrix cores (96 MFMAs a block) and 64 exponentials a lane.
 // Measured, every query row voting, pass 1 with the pre-pass + pass 2, before (rounds of 128
 // columns over re-staged keys) and now: 12 ragged chunks of 2011 rows, 203 rows voting, 32 / 8 heads
 // 324 + 305 -> 215 + 154 us; 16 x 7680, 512 voting 2052 + 2081 -> 1487 + 1281; 36 x 3584, 32 / 32
 // heads 2805 + 2369 -> 3019 + 1834 (the pre-pass, 1.25 ms of memory traffic, no longer overlaps).
-template <int D>
-__global__ __launch_bounds__(PC_WAVE) void score_queries_kernel(PcScoreArgs a, uint16_t* __restrict__ q_split) {
-  constexpr int KS = D / 16;
-  const int c = blockIdx.x / a.n_cb, cb = blockIdx.x % a.n_cb, g = blockIdx.y, lane = threadIdx.x;
-  const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
-  bf16x8 q[2][KS];
-  load_query_column<D>(a, c, g, a.n_q_heads / a.n_kv_heads, ctx_len + (a.L - a.w) - a.w_obs,
-                       min(32 * cb + lane % 32, a.n_cols - 1), lane / 32, q[0], q[1]);
-  uint16_t* dst = q_split + ((((long long)c * a.n_kv_heads + g) * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane) * 8;
-#pragma unroll
-  for (int i = 0; i < 2 * KS; ++i) *(bf16x8*)(dst + i * PC_WAVE * 8) = q[i / KS][i % KS];
-}
-
 template <int D, int PASS, int TILE>
 __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreArgs a) {
   constexpr int KS = D / 16, KSTRIDE = D + 8, NSUB = TILE / 32;
@@ -714,17 +666,17 @@ static int many_kb_keys(const pc_shape* s) {
 }
 // Key blocks of all chunks and KV heads that the workspace has room for.  A workspace serves every call
 // with no more chunks or rows than the one it was sized for (a short last batch is an example), so
-// this must not fall where many_kb_keys rises to the larger block: blocks of half the keys, of
-// which there are never as many as 2 x PC_SC_MANY_WGS, have room behind that point too.
+// this must not fall where the larger block takes over: blocks of half the keys, of which there are
+// never as many as 2 x PC_SC_MANY_WGS (PC_SC_SMALL_WGS), have room behind that point too.
 static size_t key_blocks_room(const pc_shape* s, size_t n_cb) {
-  if (n_cb <= PC_SC_WAVES) return key_blocks(s, PC_SC_KB);
-  const size_t large = key_blocks(s, PC_SC_KB_MANY), small = key_blocks(s, PC_SC_KB_MANY / 2);
-  const size_t small_max = small < 2 * PC_SC_MANY_WGS ? small : 2 * PC_SC_MANY_WGS;
+  const bool many = n_cb > PC_SC_WAVES;
+  const size_t large = key_blocks(s, many ? PC_SC_KB_MANY : PC_SC_KB), small = key_blocks(s, many ? PC_SC_KB_MANY / 2 : PC_SC_KB_SMALL);
+  const size_t most = 2 * (many ? PC_SC_MANY_WGS : PC_SC_SMALL_WGS), small_max = small < most ? small : most;
   return large > small_max ? large : small_max;
 }
 
 // Workspace of the score passes: per-block (max, sum) of pass 1, the combined row logsumexp, the
-// block sums of pass 2 and, with more than 4 column blocks, the split query columns.
+// block sums of pass 2 and the split query columns.
 struct PcScoreWs { size_t ml, lse2, blk_sum, q_split, total; };
 static PcScoreWs scores_ws_layout(const pc_shape* s) {
   const size_t n_cols = (size_t)(s->n_q_heads / s->n_kv_heads) * s->obs_window;
@@ -734,19 +686,31 @@ static PcScoreWs scores_ws_layout(const pc_shape* s) {
   w.ml = off;      off = pc_align_up(off + blocks * n_cols * sizeof(float2), 256);
   w.lse2 = off;    off = pc_align_up(off + cg * n_cb * 32 * sizeof(float), 256);
   w.blk_sum = off; off = pc_align_up(off + blocks * sizeof(float), 256);
-  w.q_split = off; off += n_cb > PC_SC_WAVES ? cg * n_cb * 32 * (size_t)s->head_dim * 2 * 2 : 0;
+  w.q_split = off; off += cg * n_cb * 32 * (size_t)s->head_dim * 2 * 2;
   w.total = off;
   return w;
 }
 
 size_t pc_scores_ws_bytes(const pc_shape* s) { return scores_ws_layout(s).total; }
 
-int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int32_t* chunk_lens, const float2* table,
+PcScoreQueries pc_scores_queries(const pc_shape* s, const void* q, const int32_t* chunk_lens, void* ws) {
+  PcScoreQueries a = {};
+  a.q = (const uint16_t*)q; a.chunk_lens = chunk_lens;
+  a.q_split = (uint16_t*)((char*)ws + scores_ws_layout(s).q_split);
+  a.n_chunks = s->n_chunks; a.L = s->chunk_len + s->query_len; a.w = s->chunk_len; a.w_obs = s->obs_window;
+  a.n_kv_heads = s->n_kv_heads; a.G = s->n_q_heads / s->n_kv_heads;
+  a.n_cols = a.G * s->obs_window; a.n_cb = (a.n_cols + 31) / 32;
+  const float scale = s->softmax_scale > 0.f ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
+  a.scale_log2 = scale * PC_SC_LOG2E;
+  return a;
+}
+
+int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens, const float2* table,
                      void* ws, float* tok_score, float* chunk_score, const PcPrepassOut* pre,
                      PcChunkSum* later, hipStream_t st) {
   const PcScoreWs w = scores_ws_layout(s);
   PcScoreArgs a = {};
-  a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.table = table; a.chunk_lens = chunk_lens;
+  a.q_split = (const uint16_t*)((char*)ws + w.q_split); a.k = (const uint16_t*)k; a.table = table; a.chunk_lens = chunk_lens;
   a.ml = (float2*)((char*)ws + w.ml); a.lse2 = (float*)((char*)ws + w.lse2);
   a.blk_sum = (float*)((char*)ws + w.blk_sum);
   a.tok_score = tok_score;
@@ -758,16 +722,16 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
   const int wpc = many ? 0 : (a.n_cb == 1 ? 4 : (a.n_cb == 2 ? 2 : 1));
   // keys per workgroup: double while at least 512 workgroups (one full round of two per CU)
   // remain: fewer, longer workgroups spread their start-up over more keys (measured: 4 and 8
-  // chunks of 8192 rows 10 % faster than with twice as many workgroups of half the keys)
+  // chunks of 8192 rows 10 % faster than with twice as many workgroups of half the keys); half where 256
+  // leave CUs idle (and pass 2 still combines the blocks itself).  Both passes, 256 / 128 keys (us): 1 x 1174 rows,
+  // 8 KV heads (40 workgroups of 256) 26.8 / 20.7, 2 x 2800, 4 (88) 37.8 / 28.5, 20 x 500, 8 (320) 55.0 / 52.1, 12 x 900 of
+  // 64 values, 8 (384) 37.6 / 35.7, 3 x 860, 32 (384) 50.7 / 51.5, 1 x 4096, 32 (512) 55.7 / 67.5.
   a.kb_keys = many ? many_kb_keys(s) : PC_SC_KB;
+  if (!many && key_blocks(s, PC_SC_KB) < PC_SC_SMALL_WGS && a.L <= PC_SC_LSE_BLOCKS * PC_SC_KB_SMALL) a.kb_keys = PC_SC_KB_SMALL;
   const int kb_cap = wpc == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;
-  while (!many && a.kb_keys < kb_cap &&
-         (long long)s->n_chunks * s->n_kv_heads * ((a.L + 2 * a.kb_keys - 1) / (2 * a.kb_keys)) >= 512)
-    a.kb_keys *= 2;
+  while (!many && a.kb_keys >= PC_SC_KB && a.kb_keys < kb_cap && key_blocks(s, 2 * a.kb_keys) >= 512) a.kb_keys *= 2;
   a.n_kb = (a.L + a.kb_keys - 1) / a.kb_keys;
   const int n_kb2 = (a.w + a.kb_keys - 1) / a.kb_keys;       // pass 2 looks at context keys only
-  const float scale = s->softmax_scale > 0.f ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
-  a.scale_log2 = scale * PC_SC_LOG2E;
   if (a.n_kb > 65535 || s->n_kv_heads > 65535) return PC_ERR_SHAPE;   // grid limits
   const dim3 grid(s->n_chunks, s->n_kv_heads, a.n_kb), grid2(s->n_chunks, s->n_kv_heads, n_kb2), block(PC_SC_THREADS);
   if (pre) {
@@ -776,13 +740,6 @@ int pc_launch_scores(const pc_shape* s, const void* q, const void* k, const int3
   }
   {
     PcProfScope prof(pre ? PC_KERNEL_PREPASS_SCORES : PC_KERNEL_SCORES_P1, st);
-    if (many) {
-      uint16_t* q_split = (uint16_t*)((char*)ws + w.q_split);
-      const dim3 q_grid(s->n_chunks * a.n_cb, s->n_kv_heads);
-      if (s->head_dim == 128) hipLaunchKernelGGL(score_queries_kernel<128>, q_grid, dim3(PC_WAVE), 0, st, a, q_split);
-      else hipLaunchKernelGGL(score_queries_kernel<64>, q_grid, dim3(PC_WAVE), 0, st, a, q_split);
-      a.q_split = q_split;
-    }
     if (s->head_dim == 128) launch_scores_pass<128, 1>(wpc, grid, block, st, a);
     else launch_scores_pass<64, 1>(wpc, grid, block, st, a);
   }
