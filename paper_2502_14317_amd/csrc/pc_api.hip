@@ -106,7 +106,7 @@ static float eff_scale(float scale, int head_dim) {
 }
 
 struct PrefillWs {
-  size_t table, v_img, k_img, ml, total;
+  size_t table, q_table, v_img, k_img, ml, total;
   int Lp;
 };
 
@@ -116,6 +116,7 @@ static PrefillWs prefill_ws_layout(const pc_shape* s) {
   w.Lp = (int)((L + 63) / 64 * 64);
   size_t off = 0;
   w.table = off; off = pc_align_up(off + L * (s->head_dim / 2) * sizeof(float2), kAlign);
+  w.q_table = off; off = pc_align_up(off + (L + 127) / 128 * 128 * (s->head_dim / 2) * sizeof(float2), kAlign);
   const size_t img_bytes = (size_t)s->n_chunks * s->n_kv_heads * s->head_dim * w.Lp * 2;   // tile images
   w.v_img = off; off = pc_align_up(off + img_bytes, kAlign);
   w.k_img = off; off = pc_align_up(off + img_bytes, kAlign);
@@ -144,10 +145,10 @@ extern "C" size_t pc_chunk_query_scores_workspace_bytes(const pc_shape* s) {
 static PcFlashArgs local_flash_args(const pc_shape* s, const void* q, const int32_t* chunk_lens, void* o, float* lse,
                                     char* base, const PrefillWs& w) {
   PcFlashArgs a = {};
-  a.q = q; a.k_img = base + w.k_img; a.v_img = base + w.v_img; a.table = (const float2*)(base + w.table); a.o = o; a.lse = lse;
+  a.q = q; a.k_img = base + w.k_img; a.v_img = base + w.v_img; a.table = (const float2*)(base + w.q_table); a.o = o; a.lse = lse;
   a.img_seq_stride = (long long)s->n_kv_heads * (w.Lp / 64);
   a.img_head_stride = w.Lp / 64;
-  a.n_seq = s->n_chunks; a.n_rows = s->chunk_len + s->query_len;
+  a.n_seq = s->n_chunks; a.n_rows = s->chunk_len + s->query_len; a.table_rows = (a.n_rows + 127) / 128 * 128;
   a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads; a.head_dim = s->head_dim;
   a.seq_ctx = chunk_lens; a.seq_add = s->query_len;
   a.scale = eff_scale(s->softmax_scale, s->head_dim);
@@ -191,6 +192,7 @@ extern "C" int pc_chunk_prefill_attn(const pc_shape* s, const void* q, const voi
 
   PcPrepArgs prep = {};
   prep.table = table; prep.n_pos = L; prep.rope = pc_rope_factors(s->rope_base, D);
+  prep.q_table = (float2*)(base + w.q_table); prep.q_scale = (double)(eff_scale(s->softmax_scale, D) * 1.4426950408889634f);
   if (tok_score) prep.scores = pc_scores_queries(s, q, chunk_lens, base + w.ml);
   rc = pc_launch_prep(prep, D, st);
   if (rc != PC_OK) return rc;
@@ -821,6 +823,7 @@ extern "C" int pc_layer_forward(const pc_shape* s, const void* q, const void* k,
 
   PcPrepArgs prep = {};
   prep.table = table; prep.n_pos = L; prep.rope = pc_rope_factors(s->rope_base, D);
+  prep.q_table = (float2*)(base + w.q_table); prep.q_scale = (double)(scale * 1.4426950408889634f);
   if (!pw.small) {
     prep.q_blk = q_blk; prep.q_rot = (uint16_t*)(attn + pw.q_rot); prep.n_q = n_q; prep.n_heads = Hq; prep.pos0 = first_len;
     prep.mul = (double)(scale * 1.4426950408889634f);

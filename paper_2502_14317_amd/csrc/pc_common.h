@@ -232,6 +232,8 @@ struct PcScoreQueries {
 struct PcPrepArgs {
   float2* table;
   int n_pos;
+  float2* q_table;         // the local attention's queries: [D / 4][n_pos rounded up to 128][2 pairs], times q_scale; nullptr: none
+  double q_scale;
   PcRope rope;
   const uint16_t* q_blk;
   uint16_t* q_rot;
@@ -263,9 +265,10 @@ struct PcKvGroup {
 #define PC_KV_GROUPS 3
 struct PcFlashArgs {
   int global;
-  const void* q;            // [n_seq, n_rows, H_q, D] bf16.  Local: rotated here by `table` and scaled; global:
+  const void* q;            // [n_seq, n_rows, H_q, D] bf16.  Local: rotated and scaled here by `table`; global:
                             //   rotated, multiplied by scale * log2(e) and rounded beforehand
-  const float2* table;      // local: rope table, row t for query row t
+  const float2* table;      // local: the queries' table [D / 4][table_rows][2 pairs], (cos, sin) x scale x log2(e)
+  int table_rows;           //   (n_rows rounded up to 128)
   void* o;                  // [n_seq, n_rows, H_q, D] bf16
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
   int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;

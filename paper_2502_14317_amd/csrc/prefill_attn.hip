@@ -273,6 +273,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   };
   auto pos_of = [&](int r) __attribute__((always_inline)) { return GLOBAL ? r / G : r; };
   int my_row[NB], my_t[NB], max_key[NB];
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
   // ---- local: keys [0, key_end) in T 64-key tiles; steps of 32 keys [0, J0) are visible to every
   //      row of the workgroup (no mask)
@@ -283,6 +284,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   const uint16_t* kbase = (const uint16_t*)a.k_img + img0;
   const uint16_t* vbase = (const uint16_t*)a.v_img + img0;
 
+  struct Limit { int cut, c0; };                   // a (global) tile's valid keys, its first key's position if causal
   // ---- global: a cursor over the run's tiles, the unmasked ones of all segments first.  Inside a
   //      segment it moves by scalar additions; the groups' descriptions are read only where a
   //      segment begins.  `cut` is how many keys from the tile's first on are valid, c0 the first
@@ -363,92 +365,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     }
   }
 
-  // ---- Q^T as B operand, NB 32-row blocks: lane holds query n of each, d = 16*ks + 8*hf .. +7.
-  //      The softmax scale and log2(e) are folded into Q before its rounding to bf16, so the
-  //      first product yields logits in log2 units and the exponent needs no multiply.  (Global: the
-  //      rows arrive rotated, scaled and rounded, see rope_q_kernel.)
-  const float c_log2 = a.scale * PC_LOG2E;
-  bf16x8 bq[NB][KS];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    my_row[nb] = row0 + 32 * nb + n;
-    my_t[nb] = pos_of(my_row[nb]);
-    max_key[nb] = min(my_row[nb], n_valid - 1);
-    {
-      // The wavefront's 32 query rows and their (cos, sin) table rows are fetched with
-      // coalesced loads (a load instruction covers whole rows, 1 KiB contiguous where the rows
-      // are adjacent) and handed to the lanes that own them through a private, XOR-swizzled
-      // LDS area in the tile buffers, which are still unused at this point.  A gather straight
-      // into the operand layout (every lane its own row) would touch 32 to 64 cache lines per
-      // instruction and costs several microseconds per workgroup.
-      constexpr int PPR = D / 8;                  // 16-byte pieces per query row (and per table half row)
-      constexpr int RPL = PC_WAVE / PPR;          // rows per load instruction
-      constexpr int NLD = 32 / RPL;               // load instructions per 32 rows
-      constexpr int KS_HALF = D / 64;             // ks iterations served by one half of a table row
-      static_assert(NB == 1, "staging area is sized for one row block per wavefront");
-      uint16_t* st_q = smem + wave * (2 * 32 * D);            // 32 rows x D bf16
-      uint16_t* st_t = st_q + 32 * D;                         // 32 half rows of the table (D bytes x 2)
-      // (global: addresses from an opaque copy of the lane index, so that the epilogue's, which are alike, are
-      // not kept in registers across the loop, which has none to spare: 4 spills instead of 24)
-      int l = lane;
-      if (GLOBAL) asm volatile("" : "+v"(l));
-      const int l_row = l / PPR, l_piece = l % PPR, n = l % 32, hf = l / 32;
-      u32x4 rq[NLD], rt[2][NLD];
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int r = RPL * i + l_row;
-        const int grow = min(row0 + 32 * nb + r, seq_rows - 1);
-        rq[i] = pc_load_once((const u32x4*)((const uint16_t*)a.q + row_at(grow) * D + 8 * l_piece));
-        if (GLOBAL) continue;
-        const char* trow = (const char*)(a.table + (long long)pos_of(grow) * HALF);
-        rt[0][i] = *(const u32x4*)(trow + 16 * l_piece);
-        rt[1][i] = *(const u32x4*)(trow + 2 * D + 16 * l_piece);
-      }
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int r = RPL * i + l_row;
-        *(u32x4*)(st_q + (r * PPR + (l_piece ^ (r % PPR))) * 8) = rq[i];
-      }
-      if (GLOBAL) {
-        PC_FA_WAVE_LDS_SYNC();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          bq[nb][ks] = *(const bf16x8*)(st_q + (n * PPR + ((2 * ks + hf) ^ (n % PPR))) * 8);
-      }
-#pragma unroll
-      for (int half = 0; half < (GLOBAL ? 0 : 2); ++half) {
-#pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-          const int r = RPL * i + l_row;
-          *(u32x4*)(st_t + (r * PPR + (l_piece ^ (r % PPR))) * 8) = rt[half][i];
-        }
-        PC_FA_WAVE_LDS_SYNC();
-#pragma unroll
-        for (int kh = 0; kh < KS_HALF; ++kh) {
-          const int ks = half * KS_HALF + kh;
-          const int pq = 2 * ks + hf;                         // piece of the row's first half; + PPR / 2: second half
-          const u32x4 x1 = *(const u32x4*)(st_q + (n * PPR + (pq ^ (n % PPR))) * 8);
-          const u32x4 x2 = *(const u32x4*)(st_q + (n * PPR + ((pq + PPR / 2) ^ (n % PPR))) * 8);
-          u32x4 ra, rbv;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int pt = 8 * kh + 4 * hf + e;               // piece e of the lane's 64 bytes of (cos, sin)
-            const u32x4 cw = *(const u32x4*)(st_t + (n * PPR + (pt ^ (n % PPR))) * 8);
-            const float2 c0 = make_float2(__uint_as_float(cw[0]), __uint_as_float(cw[1]));
-            const float2 c1 = make_float2(__uint_as_float(cw[2]), __uint_as_float(cw[3]));
-            const float x1l = bf16_lo_to_f32(x1[e]), x1h = bf16_hi_to_f32(x1[e]);
-            const float x2l = bf16_lo_to_f32(x2[e]), x2h = bf16_hi_to_f32(x2[e]);
-            ra[e] = pack_bf16x2((x1l * c0.x - x2l * c0.y) * c_log2, (x1h * c1.x - x2h * c1.y) * c_log2);
-            rbv[e] = pack_bf16x2((x2l * c0.x + x1l * c0.y) * c_log2, (x2h * c1.x + x1h * c1.y) * c_log2);
-          }
-          bq[nb][ks] = *(bf16x8*)&ra;
-          bq[nb][ks + KS / 2] = *(bf16x8*)&rbv;
-        }
-        PC_FA_WAVE_LDS_SYNC();                                // the table area is rewritten / the tiles move in
-      }
-    }
-  }
-
   // ---- cooperative tile loads, straight from global memory into LDS, through buffer descriptors.
   //      Local: a tile image is copied as it is, wavefront w issuing instruction i for its 1 KiB
   //      block WAVES i + w (descriptor base + scalar offset + one constant per-lane offset).
@@ -462,7 +378,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   constexpr int WAVES = PC_FA_WAVES;
   constexpr int T_LD = D / 8 / WAVES;              // load instructions per wavefront per tile
   constexpr int IMG_BYTES = 64 * D * 2;
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   typedef __attribute__((address_space(3))) void* lptr_t;
   const int n_img = (a.n_rows + 63) / 64;
   const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kbase, 0, n_img * IMG_BYTES, 0x00020000);
@@ -484,26 +399,118 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)(dst + 512 * (T_LD * wave_s + i)), 16, off, 64 * i, 0, 0);
   };
-  auto load_k_i = [&](const TileLoad& x, int t, int i) __attribute__((always_inline)) {
+  // (tile t into the buffers of tile `to`)
+  auto load_k_i = [&](const TileLoad& x, int t, int to, int i) __attribute__((always_inline)) {
     if (GLOBAL)
-      load_rows_i(x.k, x.bytes, x.k_off, k_lds(t), i);
+      load_rows_i(x.k, x.bytes, x.k_off, k_lds(to), i);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(k_lds(t) + 512 * (WAVES * i + wave_s)), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(k_lds(to) + 512 * (WAVES * i + wave_s)), 16,
                                                ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
   };
-  auto load_v_i = [&](const TileLoad& x, int t, int i) __attribute__((always_inline)) {
+  auto load_v_i = [&](const TileLoad& x, int t, int to, int i) __attribute__((always_inline)) {
     if (GLOBAL)
-      load_rows_i(x.v, x.bytes, x.v_off, v_lds(t), i);
+      load_rows_i(x.v, x.bytes, x.v_off, v_lds(to), i);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_lds(t) + 512 * (WAVES * i + wave_s)), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_lds(to) + 512 * (WAVES * i + wave_s)), 16,
                                                ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
   };
-  auto load_tile = [&](const TileLoad& x, int t) __attribute__((always_inline)) {
+  // s_waitcnt vmcnt(N): N newest loads of this wavefront may still be in flight
+#define PC_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
+
+  // ---- Q^T as B operand, NB 32-row blocks: lane holds query n of each, d = 16*ks + 8*hf .. +7.
+  //      The softmax scale and log2(e) are folded into Q before its rounding to bf16 (local: they ride on
+  //      the rotation table), so the first product yields logits in log2 units and the exponent needs
+  //      no multiply.  (Global: the rows arrive rotated, scaled and rounded, see rope_q_kernel.)
+  //
+  // The wavefront's 32 query rows are fetched with coalesced loads (a load instruction covers whole rows,
+  // 1 KiB contiguous where the rows are adjacent) and handed to the lanes that own them through a
+  // private, XOR-swizzled LDS area in the V buffers of tiles 1 and 2; a gather straight into the operand
+  // layout (every lane its own row) would touch 32 to 64 cache lines per instruction.  The table holds two
+  // pairs' (cos, sin) of consecutive rows side by side, so the lanes of 32 rows read it straight into
+  // registers, 16 bytes each (one pair, 8 bytes: twice the instructions, 2000 cycles more).  The first tiles (K 0, V 0, K 1) are asked for behind the queries: one memory latency in
+  // front of the first product instead of two.  Cycles of a workgroup in front of its loop and behind it,
+  // 12 x 1550 rows, 32 / 8 heads, with the table through LDS, 64-bit addresses a row, tiles after the rotation ->
+  // now: queries 4470 -> 5600, rotation 4300 -> 2690, tiles 1840 -> 510, output 2310 -> 1840 (a tile takes 2400);
+  // the launch 331 -> 318 us, 20 x 500 85.8 -> 82, 36 x 4096 of 32 / 32 heads 4434 -> 4367, 8 x 8192 3637 -> 3613.
+  bf16x8 bq[NB][KS];
+  static_assert(NB == 1, "the staging areas are sized for one row block per wavefront");
+  constexpr int PPR = D / 8;                      // 16-byte pieces per row
+  constexpr int RPL = PC_WAVE / PPR;              // rows per load instruction
+  constexpr int NLD = 32 / RPL;                   // load instructions per 32 rows
+  my_row[0] = row0 + n;
+  my_t[0] = pos_of(my_row[0]);
+  max_key[0] = min(my_row[0], n_valid - 1);
+  // local: the wavefront's rows of q and o through descriptors that end behind the sequence's last row
+  const int row0_s = row0_wg + 32 * wave_s, rows_left = min(seq_rows - row0_s, 32);
+  const int qo_stride = a.n_q_heads * (2 * D);
+  const int qo_bytes = rows_left > 0 ? (rows_left - 1) * qo_stride + 2 * D : 0;
+  const long long qo_at = (((long long)seq * a.n_rows + (rows_left > 0 ? row0_s : 0)) * a.n_q_heads + h) * D;
+  Limit lim0 = {};
+  {
+    // (global: addresses from an opaque copy of the lane index, so that the epilogue's, which are alike, are
+    // not kept in registers across the loop, which has none to spare: 4 spills instead of 24)
+    int l = lane;
+    if (GLOBAL) asm volatile("" : "+v"(l));
+    const int l_row = l / PPR, l_piece = l % PPR, n = l % 32, hf = l / 32;
+    uint16_t* st_q = smem + SM::KBUF * SM::K_ELEMS + SM::V_ELEMS + wave * (32 * D);
+    u32x4 rq[NLD];
+    u32x4 cs[GLOBAL ? 1 : KS / 2][4];              // (cos, sin) x scale of the lane's row, pairs 16 ks + 8 hf + 2 e, + 1
+    if (GLOBAL) {
 #pragma unroll
-    for (int i = 0; i < T_LD; ++i) load_k_i(x, t, i);
+      for (int i = 0; i < NLD; ++i)
+        rq[i] = pc_load_once((const u32x4*)((const uint16_t*)a.q + row_at(min(row0 + RPL * i + l_row, seq_rows - 1)) * D + 8 * l_piece));
+    } else {
+      const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint16_t*)a.q + qo_at), 0, qo_bytes, 0x00020000);
+      const int q_off = l_row * qo_stride + 16 * l_piece;
 #pragma unroll
-    for (int i = 0; i < T_LD; ++i) load_v_i(x, t, i);
-  };
+      for (int i = 0; i < NLD; ++i) rq[i] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, q_off, RPL * i * qo_stride, PC_BUF_NT);
+      const __amdgpu_buffer_rsrc_t t_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.table, 0, HALF * a.table_rows * 8, 0x00020000);
+      const int t_off = 16 * (4 * hf * a.table_rows + row0 + n);
+#pragma unroll
+      for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[ks][e] = __builtin_amdgcn_raw_buffer_load_b128(t_rsrc, t_off, 16 * (8 * ks + e) * a.table_rows, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (!GLOBAL || T > 0) {
+      const TileLoad ld = GLOBAL ? tile_load() : TileLoad{};
+#pragma unroll
+      for (int i = 0; i < T_LD; ++i) load_k_i(ld, 0, 0, i);
+#pragma unroll
+      for (int i = 0; i < T_LD; ++i) load_v_i(ld, 0, 0, i);
+      if (GLOBAL) { lim0 = {cur.cut, cur.c0}; cur_next(); }
+      const TileLoad ld1 = GLOBAL ? tile_load() : TileLoad{};
+#pragma unroll
+      for (int i = 0; i < T_LD; ++i) load_k_i(ld1, min(1, T - 1), 1, i);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int r = RPL * i + l_row;
+      *(u32x4*)(st_q + (r * PPR + (l_piece ^ (r % PPR))) * 8) = rq[i];
+    }
+    PC_FA_WAVE_LDS_SYNC();
+    auto piece = [&](int p) __attribute__((always_inline)) { return *(const u32x4*)(st_q + (n * PPR + (p ^ (n % PPR))) * 8); };
+#pragma unroll
+    for (int ks = 0; ks < (GLOBAL ? KS : KS / 2); ++ks) {
+      const u32x4 x1 = piece(2 * ks + hf);
+      if (GLOBAL) { bq[0][ks] = *(const bf16x8*)&x1; continue; }
+      const u32x4 x2 = piece(2 * ks + hf + PPR / 2);         // the row's second half
+      u32x4 ra, rbv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const u32x4 cw = cs[GLOBAL ? 0 : ks][e];
+        const float c0x = __uint_as_float(cw[0]), c0y = __uint_as_float(cw[1]), c1x = __uint_as_float(cw[2]), c1y = __uint_as_float(cw[3]);
+        const float x1l = bf16_lo_to_f32(x1[e]), x1h = bf16_hi_to_f32(x1[e]);
+        const float x2l = bf16_lo_to_f32(x2[e]), x2h = bf16_hi_to_f32(x2[e]);
+        ra[e] = pack_bf16x2(x1l * c0x - x2l * c0y, x1h * c1x - x2h * c1y);
+        rbv[e] = pack_bf16x2(x2l * c0x + x1l * c0y, x2h * c1x + x1h * c1y);
+      }
+      bq[0][ks] = *(bf16x8*)&ra;
+      bq[0][ks + KS / 2] = *(bf16x8*)&rbv;
+    }
+  }
+
   // A operand of the second product from row-major V, V^T(d = n, 8 keys): two transposing reads of
   // 4 keys each.  16 lanes point at 4 rows x 16 columns (8 bytes a lane) and receive a column's 4 rows.
   typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -514,9 +521,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((rptr_t)(p + 4 * 32));
     return x.v;
   };
-  // s_waitcnt vmcnt(N): N newest loads of this wavefront may still be in flight
-#define PC_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(0x0F70 | ((N) & 15) | (((N) >> 4) << 14))
-
   floatx16 o_acc[NB][DB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
@@ -597,7 +601,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   // A mask hides the keys behind the row's last visible one; the step's first key counts as key
   // `k0`.  A (global) tile's limits: its valid keys, and its first key's position where the segment
   // is causal.
-  struct Limit { int cut, c0; };
   auto step = [&](auto mask_tag, auto has_pv, auto has_qk, auto has_ld, const Limit& lim, float window, int j, int k0,
                   int t_ld, const TileLoad& ld, floatx16(&s_cur)[NB],
                   floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2],
@@ -644,8 +647,8 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
       if (QK && i < KS) ka[i] = read_k(kt, (j + 1) & 1, i);
       if (LD && i >= NM - 2 * T_LD) {               // one tile-load instruction per slice
         const int li = i - (NM - 2 * T_LD);
-        if (li < T_LD) load_k_i(ld, t_ld, li);
-        else load_v_i(ld, t_ld, li - T_LD);
+        if (li < T_LD) load_k_i(ld, t_ld, t_ld, li);
+        else load_v_i(ld, t_ld, t_ld, li - T_LD);
       }
       if (MASK && i == 0) {
 #pragma unroll
@@ -764,14 +767,16 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   // tile T - 1 into buffers nobody reads again, which keeps the loop free of branches.
   const TileLoad no_ld = {};
   const Limit no_lim = {};
-  if (!GLOBAL) {
-    // ---- prologue: tiles 0 and 1 must have landed before the first step
-    __syncthreads();                               // every wavefront has left its staging area
-    const TileLoad ld = {};                        // (images: addressed by tile number)
-    load_tile(ld, 0);
-    load_tile(ld, min(1, T - 1));
+  // K 0, V 0 and K 1 have landed, and every wavefront has left its staging area: V 1 may move in
+  if (!GLOBAL || T > 0) {
     PC_WAIT_VMCNT(0);
     __syncthreads();
+    const TileLoad ld = GLOBAL ? tile_load() : TileLoad{};   // the cursor is on tile 1
+#pragma unroll
+    for (int i = 0; i < T_LD; ++i) load_v_i(ld, min(1, T - 1), 1, i);
+  }
+  if (!GLOBAL) {
+    const TileLoad ld = {};                        // (images: addressed by tile number)
     first_qk(s_buf[0]);
     step(with_mask{}, no{}, yes{}, no{}, no_lim, 8.0f, 0, 0, 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
     auto period = [&](auto mask_tag, int p) __attribute__((always_inline)) {
@@ -809,13 +814,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     // The same pipeline over the cursor's tiles; a tile carries its own limits (tile p + 2 is the
     // cursor's, lim0 / lim1 belong to tiles p and p + 1).  Every row that sees a key of the run sees
     // its first one, so the first step sets the row's reference as in the local kernel.
-    __syncthreads();
-    load_tile(tile_load(), 0);
-    Limit lim0 = {cur.cut, cur.c0};
-    cur_next();
-    load_tile(tile_load(), min(1, T - 1));
-    PC_WAIT_VMCNT(0);
-    __syncthreads();
     first_qk(s_buf[0]);
     step(with_mask{}, no{}, yes{}, no{}, lim0, 8.0f, 0, 0, 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
     auto period = [&](auto mask_tag, int p) __attribute__((always_inline)) {
@@ -876,7 +874,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
       // an instruction would touch 32 rows.  The rows go through a swizzled staging area in the
       // K buffers (nobody reads K after the last barrier: the last step has no next S^T) and
       // leave as whole 16-byte-per-lane rows, 1 KiB per instruction where rows are adjacent.
-      constexpr int PPR = D / 8, RPL = PC_WAVE / PPR, NLD = 32 / RPL;
       static_assert(NB == 1 && PC_FA_WAVES * 32 * D <= SM::KBUF * SM::K_ELEMS, "staging area is the K buffers");
       uint16_t* st_o = smem + wave * (32 * D);
 #pragma unroll
@@ -891,10 +888,15 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
         }
       PC_FA_WAVE_LDS_SYNC();
       const int l_row = lane / PPR, l_piece = lane % PPR;
+      const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((uint16_t*)a.o + qo_at), 0, qo_bytes, 0x00020000);
 #pragma unroll
       for (int k = 0; k < NLD; ++k) {
         const int r = RPL * k + l_row;
         const u32x4 x = *(const u32x4*)(st_o + (r * PPR + (l_piece ^ (r % PPR))) * 8);
+        if (!GLOBAL) {                                         // (rows behind the sequence: dropped)
+          __builtin_amdgcn_raw_buffer_store_b128(x, o_rsrc, l_row * qo_stride + 16 * l_piece, RPL * k * qo_stride, PC_BUF_NT);
+          continue;
+        }
         const int grow = row0 + 32 * nb + r;
         if (grow < seq_rows)
           pc_store_once((u32x4*)((uint16_t*)a.o + row_at(grow) * D + 8 * l_piece), x);

@@ -1,6 +1,8 @@
 // What a layer's other launches read and nothing of which depends on the keys, in one launch (a launch of
 // its own each costs 3 to 6 us):
-//   the rotation table        cos / sin of position * theta_i, computed in fp64, stored fp32
+//   the rotation table        cos / sin of position * theta_i, computed in fp64, stored fp32; for the local
+//                             attention's queries a second one, turned (two pairs' positions side by side) and
+//                             times scale * log2(e)
 //   the query block           rotated for the global attention (pc_rope_q_workgroup)
 //   the score passes' queries the voting rows as ready MFMA operands: rotated in fp32, scaled to log2 units,
 //                             split into bf16 hi + lo, so that a workgroup of the passes starts with
@@ -52,13 +54,29 @@ __device__ __forceinline__ void split_query_columns(const PcScoreQueries& a, con
 
 template <int D>
 __global__ __launch_bounds__(256) void layer_prep_kernel(PcPrepArgs a, int table_blocks, long long split_units) {
+  // the tables, 16 positions a workgroup; the queries' one with the positions side by side goes through LDS
+  constexpr int HALF = D / 2, PER = 16 * HALF / 256;
+  __shared__ float2 turned[HALF][17];                               // [pair][position]
   int bid = blockIdx.x;
   if (bid < table_blocks) {
-    const int idx = bid * 256 + threadIdx.x, p = idx / (D / 2), i = idx % (D / 2);
-    if (p >= a.n_pos) return;
-    double sn, cs;
-    pc_sincos((double)p * pc_rope_theta(a.rope, i), sn, cs);
-    a.table[idx] = make_float2((float)cs, (float)sn);
+    const int p0 = 16 * bid, i = threadIdx.x % HALF, rows = (a.n_pos + 127) / 128 * 128;
+    const double theta = pc_rope_theta(a.rope, i);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int p = threadIdx.x / HALF + (256 / HALF) * u;
+      double sn, cs;
+      pc_sincos((double)(p0 + p) * theta, sn, cs);
+      if (p0 + p < a.n_pos) a.table[(long long)(p0 + p) * HALF + i] = make_float2((float)cs, (float)sn);
+      turned[i][p] = make_float2((float)(cs * a.q_scale), (float)(sn * a.q_scale));
+    }
+    if (a.q_table == nullptr) return;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int x = threadIdx.x + 256 * u;
+      const int pair = x / 32 * 2 + x % 2, p = x % 32 / 2;
+      a.q_table[((long long)(pair / 2) * rows + p0 + p) * 2 + pair % 2] = turned[pair][p];
+    }
     return;
   }
   bid -= table_blocks;
@@ -71,7 +89,7 @@ __global__ __launch_bounds__(256) void layer_prep_kernel(PcPrepArgs a, int table
 }
 
 int pc_launch_prep(const PcPrepArgs& a, int head_dim, hipStream_t st) {
-  const long long table_blocks = ((long long)a.n_pos * (head_dim / 2) + 255) / 256;
+  const long long table_blocks = a.q_table ? (a.n_pos + 127LL) / 128 * 8 : (a.n_pos + 15LL) / 16;
   const long long units = a.scores.q_split ? (long long)a.scores.n_chunks * a.scores.n_kv_heads * a.scores.n_cb * (head_dim / 32) : 0;
   const long long blocks = table_blocks + a.n_q + (units + 3) / 4;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
