@@ -191,76 +191,136 @@ __device__ __forceinline__ void pc_e4m3x4_to_bf16(uint32_t w, uint32_t& lo, uint
 }
 
 // ------------------------------------------------------------------------------------------
-// Widening of 8-bit segments to bf16 rows (for the tile kernel, which takes the query block over
-// the 8-bit cache through the same path as a 16-bit cache): value = code * scale, rounded to bf16.
-// One workgroup per (segment, 32-key block, K or V); a thread takes one 16-byte piece of the block
-// (the layouts are those of kv_quantize_fp8_kernel above).  The rows are put together in LDS and
-// leave as whole 16-byte pieces: bound by memory, 1 byte read and 2 written per value.  Measured at
-// 256 segments of 2048 x 128 (0.40 GB): 89 us with 2-byte stores of V from the registers, 60 now.
+// Tile images for the tile kernel, which takes a query block over the 8-bit cache: the local attention's
+// layout (K granule (c, r) = K[key r][8 c .. 8 c + 7] at 64 c + r, V^T granule (c, d) = V[keys 8 c .. + 7][d] at
+// D c + d), so that its loop needs neither transposing LDS reads nor row addresses.  8-bit segments: value =
+// code * scale, rounded to bf16; one workgroup per 64-key tile (K and V), a thread takes 16-byte pieces of the
+// blocks (layouts above).  A K piece holds 16 values of a key, two granules; of a V piece a lane holds keys
+// 4 g .. and 16 + 4 g .. of a value, and neighbouring lane rows exchange halves (v_permlane16_swap) to whole
+// granules.  Every 16 lanes store 256 consecutive bytes.  Bound by memory, 1 byte read and 2 written a value:
+// 256 segments of 2048 x 128 (0.40 GB) 66 us, 6.1 TB/s (as rows, through LDS: 61), and the attention that reads
+// them (4 x 512 rows, 32 / 8 heads) 548 -> 506 us.  The tail and the self segment follow in the same launch.
 template <int D>
-__global__ __launch_bounds__(256) void fp8_to_rows_kernel(
+__device__ __forceinline__ void widen_piece(const uint8_t* src, float scale, bool have, uint32_t (&o)[8]) {
+  uint4 raw = make_uint4(0, 0, 0, 0);
+  if (have) raw = pc_load_once((const uint4*)src);
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t lo, hi;
+    pc_e4m3x4_to_bf16(w[e], lo, hi);
+    o[2 * e] = pack_bf16x2(bf16_lo_to_f32(lo) * scale, bf16_hi_to_f32(lo) * scale);
+    o[2 * e + 1] = pack_bf16x2(bf16_lo_to_f32(hi) * scale, bf16_hi_to_f32(hi) * scale);
+  }
+}
+template <int D>
+__device__ __forceinline__ void rows_to_image(const PcRowsToImages& x, int unit, int n_kv_heads) {
+  const int tiles = (x.n_rows + 63) / 64, tile = unit % tiles, bg = unit / tiles, b = bg / n_kv_heads, g = bg % n_kv_heads;
+  const int len = x.len ? min(max(x.len[b], 0), x.n_rows) : x.n_rows, left = len - 64 * tile;
+  if (left <= 0) return;
+  const long long src = b * x.seq_stride + g * x.head_stride + 64LL * tile * x.row_stride, dst = (long long)unit * (64 * D);
+  for (int it = threadIdx.x; it < 8 * D; it += 256) {
+    const int row = it % 64, c = it / 64;
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (row < left) w = *(const uint4*)(x.k + src + (long long)row * x.row_stride + 8 * c);
+    *(uint4*)(x.k_img + dst + it * 8) = w;
+  }
+  const int c = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4) * 4;
+  if (c >= 8) return;
+  u32x2 w[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    w[j] = u32x2{0u, 0u};
+    if (8 * c + j < left) w[j] = *(const u32x2*)(x.v + src + (8LL * c + j) * x.row_stride + d4);
+  }
+#pragma unroll
+  for (int dd = 0; dd < 4; ++dd) {
+    u32x4 gr;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      gr[e] = __builtin_amdgcn_perm(w[2 * e + 1][dd / 2], w[2 * e][dd / 2], dd % 2 ? 0x07060302u : 0x05040100u);
+    *(u32x4*)(x.v_img + dst + (c * D + d4 + dd) * 8) = gr;
+  }
+}
+template <int D>
+__global__ __launch_bounds__(256) void fp8_images_kernel(
     const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, const float* __restrict__ k_scale,
-    const float* __restrict__ v_scale, int k_t, uint16_t* __restrict__ k_rows,
-    uint16_t* __restrict__ v_rows) {
-  constexpr int STRIDE = D + 8;                           // 16-byte pieces stay aligned, rows start in other banks
-  __shared__ __attribute__((aligned(16))) uint16_t rows[32 * STRIDE];
-  const long long seg = blockIdx.x;
-  const int blk = blockIdx.y, is_v = blockIdx.z;
-  const int n_blk = (k_t + 31) / 32;
-  const int p = threadIdx.x;                              // 16-byte piece of the block
-  if (p < 32 * D / 16) {
-    const float scale = (is_v ? v_scale : k_scale)[seg];
-    const uint4 raw = pc_load_once((const uint4*)((is_v ? v8 : k8) + (seg * n_blk + blk) * 32LL * D + 16 * p));
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-    uint32_t o[8];                                        // 16 values, rounded to bf16
+    const float* __restrict__ v_scale, const int32_t* __restrict__ seg_len, int per_head, int k_t, long long n_segs, uint16_t* __restrict__ k_img, uint16_t* __restrict__ v_img,
+    PcRowsToImages tail, PcRowsToImages self, int n_seq, int n_kv_heads) {
+  const int tiles = (k_t + 63) / 64, n_blk = (k_t + 31) / 32;
+  const long long seg_units = n_segs * tiles, unit = blockIdx.x;
+  if (unit >= seg_units) {
+    const int rest = (int)(unit - seg_units), tail_units = n_seq * n_kv_heads * ((tail.n_rows + 63) / 64);
+    if (rest < tail_units) rows_to_image<D>(tail, rest, n_kv_heads);
+    else rows_to_image<D>(self, rest - tail_units, n_kv_heads);
+    return;
+  }
+  const long long seg = unit / tiles;
+  const int tile = (int)(unit % tiles);
+  const int left = (seg_len ? min(seg_len[per_head ? seg : seg / n_kv_heads], k_t) : k_t) - 64 * tile;
+  if (left <= 0) return;
+  const float ks = k_scale[seg], vs = v_scale[seg];
+  const long long dst = unit * (64 * D);
+  constexpr int PIECES = 2 * 32 * D / 16;                 // 16-byte pieces of the tile's two blocks
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint32_t lo, hi;
-      pc_e4m3x4_to_bf16(w[e], lo, hi);
-      o[2 * e] = pack_bf16x2(bf16_lo_to_f32(lo) * scale, bf16_hi_to_f32(lo) * scale);
-      o[2 * e + 1] = pack_bf16x2(bf16_lo_to_f32(hi) * scale, bf16_hi_to_f32(hi) * scale);
+  for (int u = 0; u < PIECES / 256; ++u) {
+    const int p = threadIdx.x + 256 * u, blk = p / (2 * D), pb = p % (2 * D), lane = pb % 64, piece = pb / 64;
+    const bool have = 2 * tile + blk < n_blk;
+    const long long at = (seg * n_blk + 2 * tile + blk) * 32LL * D + 16 * pb;
+    uint32_t o[8];
+    {
+      // piece = 16-key tile * (D / 64) + i; lane 16 kk + c: values d = 64 i + 16 kk .. + 15 of key c of the tile
+      widen_piece<D>(k8 + at, ks, have, o);
+      const int key = 32 * blk + 16 * (piece / (D / 64)) + lane % 16, col = 8 * (piece % (D / 64)) + 2 * (lane / 16);
+      uint16_t* out = k_img + dst + (col * 64 + key) * 8;
+      if (key >= left) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = 0;
+      }
+      *(uint4*)out = make_uint4(o[0], o[1], o[2], o[3]);
+      *(uint4*)(out + 64 * 8) = make_uint4(o[4], o[5], o[6], o[7]);
     }
-    const int lane = p % 64, piece = p / 64;
-    if (!is_v) {
-      // piece = tile * (D / 64) + i; lane 16 kk + c: values d = 64 i + 16 kk .. + 15 of key c of the tile
-      const int tile = piece / (D / 64), i = piece % (D / 64), kk = lane / 16, c = lane % 16;
-      uint4* r4 = (uint4*)(rows + (16 * tile + c) * STRIDE + 64 * i + 16 * kk);
-      r4[0] = make_uint4(o[0], o[1], o[2], o[3]);
-      r4[1] = make_uint4(o[4], o[5], o[6], o[7]);
-    } else {
+    {
       // piece q; lane 16 g + m holds [h][j]: value d = 32 q + 16 h + m of key 4 g + j (j < 4) or
-      // 16 + 4 g + (j - 4)
-      const int g = lane / 16, m = lane % 16;
+      // 16 + 4 g + (j - 4); after the exchange an even g has keys 4 g .. 4 g + 7, an odd one 16 + 4 (g - 1) ..
+      widen_piece<D>(v8 + at, vs, have, o);
+      const int g = lane / 16, m = lane % 16, c = 4 * blk + (g % 2 ? 2 : 0) + g / 2;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int h = 0; h < 2; ++h) {
+        uint32_t w[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int key = j < 4 ? 4 * g + j : 16 + 4 * g + (j - 4);
-          rows[key * STRIDE + 32 * piece + 16 * h + m] = (uint16_t)(o[4 * h + j / 2] >> (16 * (j % 2)));
+        for (int e = 0; e < 2; ++e) {
+          auto x = __builtin_amdgcn_permlane16_swap(o[4 * h + e], o[4 * h + 2 + e], false, false);
+          w[e] = x[0]; w[2 + e] = x[1];
         }
+        if (left < 64) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int key = 8 * c + 2 * e;
+            w[e] = key + 1 < left ? w[e] : (key < left ? w[e] & 0xffffu : 0u);
+          }
+        }
+        *(uint4*)(v_img + dst + (c * D + 32 * piece + 16 * h + m) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
     }
   }
-  __syncthreads();
-  uint16_t* dst = (is_v ? v_rows : k_rows) + (seg * k_t + 32LL * blk) * D;
-  const int n_rows = min(32, k_t - 32 * blk);
-  for (int x = threadIdx.x; x < n_rows * (D / 8); x += 256)
-    *(uint4*)(dst + 8 * x) = *(const uint4*)(rows + x / (D / 8) * STRIDE + x % (D / 8) * 8);
 }
 
-int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
-                          long long n_segs, int k_t, int head_dim, void* k_rows, void* v_rows,
-                          hipStream_t st) {
-  if (n_segs == 0) return PC_OK;
-  const int n_blk = (k_t + 31) / 32;
-  if (n_segs > 0x7fffffffLL || n_blk > 65535) return PC_ERR_SHAPE;
-  PcProfScope prof(PC_KERNEL_FP8_TO_ROWS, st);
-  const dim3 grid((unsigned)n_segs, n_blk, 2), block(256);
+int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
+                         const int32_t* seg_len, int seg_len_per_head, long long n_segs, int k_t, int head_dim, void* k_img, void* v_img,
+                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads, hipStream_t st) {
+  const long long row_tiles = (tail.n_rows + 63) / 64 + (self.n_rows + 63LL) / 64;
+  const long long blocks = n_segs * ((k_t + 63) / 64) + (long long)n_seq * n_kv_heads * row_tiles;
+  if (blocks == 0) return PC_OK;
+  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_FP8_IMAGES, st);
+  const dim3 grid((unsigned)blocks), block(256);
   if (head_dim == 128)
-    hipLaunchKernelGGL(fp8_to_rows_kernel<128>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8,
-                       k_scale, v_scale, k_t, (uint16_t*)k_rows, (uint16_t*)v_rows);
+    hipLaunchKernelGGL(fp8_images_kernel<128>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale,
+                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads);
   else
-    hipLaunchKernelGGL(fp8_to_rows_kernel<64>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8,
-                       k_scale, v_scale, k_t, (uint16_t*)k_rows, (uint16_t*)v_rows);
+    hipLaunchKernelGGL(fp8_images_kernel<64>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale,
+                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

@@ -71,7 +71,7 @@ extern "C" const char* pc_kernel_name(int id) {
       "gather_kv_kernel", "rope_q_kernel", "decode_attn_kernel", "merge_kernel",
       "self_info_rows_kernel", "kv_append_kernel", "scores_lse_kernel", "kv_quantize_fp8_kernel",
       "decode_attn_fp8_kernel", "scores_kernel<1>+kv_prepass", "chunk_queue_kernel",
-      "fp8_to_rows_kernel"};
+      "fp8_images_kernel"};
   return (id >= 0 && id < PC_KERNEL_COUNT) ? names[id] : "unknown";
 }
 
@@ -336,7 +336,8 @@ static int check_tile_limits(int n_seg, int k_t, int tail_cap, int n_kv_heads, i
 }
 
 struct Par8Ws {
-  size_t q_rot, part_o, part_lse, rows_k, rows_v, total;   // q_rot: the rotated query rows
+  size_t q_rot, part_o, part_lse, total;                   // q_rot: the rotated query rows
+  size_t k_img[3], v_img[3];                               // tile images of segments, tail, self segment
   int n_parts;
   PcDecodeSplit split;                                     // small
   bool small;
@@ -360,11 +361,13 @@ static Par8Ws par8_ws_layout(int batch, int n_q, int n_seg, int k_t, int tail_ca
   if (w.small) part_rows = rows * (w.split.room + w.split.tail_room);
   w.part_o = off;   off = pc_align_up(off + part_rows * D * sizeof(float), kAlign);
   w.part_lse = off; off = pc_align_up(off + part_rows * sizeof(float), kAlign);
-  w.rows_k = w.rows_v = off;
-  if (!w.small) {       // dequantised segments as bf16 rows
-    const size_t seg_rows = (size_t)batch * n_seg * n_kv_heads * k_t * D * 2;
-    w.rows_k = off; off = pc_align_up(off + seg_rows, kAlign);
-    w.rows_v = off; off = pc_align_up(off + seg_rows, kAlign);
+  if (!w.small) {
+    const size_t head_tiles[3] = {(size_t)n_seg * key_tiles(1, k_t), (size_t)key_tiles(1, tail_cap), has_self ? (size_t)key_tiles(1, n_q) : 0};
+    for (int i = 0; i < 3; ++i) {
+      const size_t bytes = (size_t)batch * n_kv_heads * head_tiles[i] * 64 * D * 2;
+      w.k_img[i] = off; off = pc_align_up(off + bytes, kAlign);
+      w.v_img[i] = off; off = pc_align_up(off + bytes, kAlign);
+    }
   }
   w.total = off;
   return w;
@@ -725,9 +728,17 @@ static int parallel_attn_run(const void* q, const void* kc, const void* vc, cons
                        base + w.q_rot, part_o, part_lse, w.n_parts, out, lse_out, st);
 }
 
-// Eq. 9-11 for a block of query rows over the 8-bit cache: the segments are widened to bf16 rows
-// (code * scale, rounded to bf16) in the workspace, then everything runs through the tile kernel
-// as for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].
+// n segments of up to cap keys as tile images
+static PcKvGroup image_group(const void* k, const void* v, const int32_t* len, int per_head, int n, int cap, int n_kv_heads, int D) {
+  PcKvGroup kg = segment_group(k, v, len, per_head, n, cap, n_kv_heads, D);
+  kg.head_stride = key_tiles(1, cap) * 64 * D;
+  kg.seg_stride = n_kv_heads * kg.head_stride; kg.seq_stride = n * kg.seg_stride;
+  return kg;
+}
+
+// Eq. 9-11 for a block of query rows over the 8-bit cache: everything becomes tile images in the workspace
+// (code * scale, rounded to bf16, and the 16-bit rows as they are), then one launch of the tile kernel as
+// for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].
 static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8, const float* k_scale,
                                    const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
                                    const void* k_tail, const void* v_tail, const int32_t* tail_len,
@@ -736,14 +747,24 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
                                    int q_pos0, float rope_base, float scale, void* out, float* lse_out,
                                    const Par8Ws& w, char* base, hipStream_t st) {
   PcFlashArgs a = {};
-  if (n_seg > 0) {
-    const int rc = pc_launch_fp8_to_rows(k8, v8, k_scale, v_scale, (long long)batch * n_seg * n_kv_heads, k_t, D,
-                                         base + w.rows_k, base + w.rows_v, st);
-    if (rc != PC_OK) return rc;
-    a.grp[0] = segment_group(base + w.rows_k, base + w.rows_v, seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
+  PcRowsToImages tail = {}, self = {};
+  auto at = [&](size_t off) { return (uint16_t*)(base + off); };
+  if (n_seg > 0) a.grp[0] = image_group(at(w.k_img[0]), at(w.v_img[0]), seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
+  if (tail_cap > 0) {
+    tail = PcRowsToImages{(const uint16_t*)k_tail, (const uint16_t*)v_tail, tail_len, tail_cap, D, (long long)n_kv_heads * tail_cap * D,
+                          (long long)tail_cap * D, at(w.k_img[1]), at(w.v_img[1])};
+    a.grp[1] = image_group(tail.k_img, tail.v_img, tail_len, 0, 1, tail_cap, n_kv_heads, D);
   }
-  if (tail_cap > 0) a.grp[1] = segment_group(k_tail, v_tail, tail_len, 0, 1, tail_cap, n_kv_heads, D);
-  if (k_self != nullptr) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
+  if (k_self != nullptr) {
+    self = PcRowsToImages{(const uint16_t*)k_self, (const uint16_t*)v_self, nullptr, n_q, n_kv_heads * D,
+                          (long long)n_q * n_kv_heads * D, D, at(w.k_img[2]), at(w.v_img[2])};
+    a.grp[2] = image_group(self.k_img, self.v_img, nullptr, 0, 1, n_q, n_kv_heads, D);
+    a.grp[2].causal = 1;
+  }
+  a.images = 1;
+  const int rc = pc_launch_fp8_images(k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, (long long)batch * n_seg * n_kv_heads, k_t,
+                                      D, base + w.k_img[0], base + w.v_img[0], tail, self, batch, n_kv_heads, st);
+  if (rc != PC_OK) return rc;
   return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
                        base + w.q_rot, (float*)(base + w.part_o), (float*)(base + w.part_lse),
                        w.n_parts, out, lse_out, st);

@@ -265,6 +265,7 @@ struct PcKvGroup {
 #define PC_KV_GROUPS 3
 struct PcFlashArgs {
   int global;
+  int images;               // global: the groups' segments are tile images (row_stride D, a segment whole tiles)
   const void* q;            // [n_seq, n_rows, H_q, D] bf16.  Local: rotated and scaled here by `table`; global:
                             //   rotated, multiplied by scale * log2(e) and rounded beforehand
   const float2* table;      // local: the queries' table [D / 4][table_rows][2 pairs], (cos, sin) x scale x log2(e)
@@ -443,11 +444,21 @@ int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg
                               int seg_len_per_head, long long n_segs, int n_kv_heads, int k_t,
                               int head_dim, const float* k_amax, const float* v_amax, void* k8,
                               void* v8, float* k_scale, float* v_scale, hipStream_t st);
-// 8-bit segments (32-key block layout of pc_kv_quantize_fp8) -> bf16 rows [n_segs, k_t, D] of
-// code * scale (rounded to bf16), K and V
-int pc_launch_fp8_to_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
-                          long long n_segs, int k_t, int head_dim, void* k_rows, void* v_rows,
-                          hipStream_t st);
+// Tile images (the tile kernel's) of the global attention's keys over the 8-bit cache, in one launch: 8-bit
+// segments widened to code * scale (rounded to bf16), and 16-bit rows.  Every segment takes whole 64-key
+// tiles, [segment][tiles][64 * D]; keys behind its length are zeros in the last tile, later tiles are not written.
+struct PcRowsToImages {
+  const uint16_t* k;        // bf16 rows; row j of (sequence, head) at seq * seq_stride + head * head_stride + j * row_stride
+  const uint16_t* v;
+  const int32_t* len;       // [n_seq] valid rows or nullptr (= n_rows)
+  int n_rows, row_stride;   // n_rows = 0: none
+  long long seq_stride, head_stride;
+  uint16_t* k_img;          // [n_seq][n_kv_heads][tiles][64 * D]
+  uint16_t* v_img;
+};
+int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
+                         const int32_t* seg_len, int seg_len_per_head, long long n_segs, int k_t, int head_dim, void* k_img, void* v_img,
+                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads, hipStream_t st);
 // Partials of the 8-bit segments, then those of the 16-bit tail (tail_cap > 0)
 int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
                          const float* k_scale, const float* v_scale, const int32_t* seg_len,

@@ -156,6 +156,10 @@ __device__ __forceinline__ int pc_key_of_row(int m) {
   return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1);
 }
 
+#define PC_FA_LOCAL 0
+#define PC_FA_ROWS 1
+#define PC_FA_IMAGES 2
+
 // The global attention's keys as tiles of 64: the tiles that every row of the workgroup sees whole
 // come first (no mask), then those that need one (a segment's ragged last tile, the causal
 // diagonal), so that the main loop holds no mask.  `full` tiles of a segment of `len` keys:
@@ -213,15 +217,17 @@ __device__ __forceinline__ void pc_kv_find(const PcKvGroup& kg, int b, int g, in
   }
 }
 
-// GLOBAL = false: causal local attention of whole sequences over tile images of K and V^T.
-// GLOBAL = true: a block of query rows over groups of row-major segments (compressed segments, a
-//   16-bit tail, the causal self segment) under one softmax.  The rows of a KV head's G query
+// MODE PC_FA_LOCAL: causal local attention of whole sequences over tile images of K and V^T.
+// MODE PC_FA_ROWS: a block of query rows over groups of row-major segments (compressed segments, a
+//   16-bit tail, the causal self segment) under one softmax.  PC_FA_IMAGES: the same over segments that
+//   are tile images (the 8-bit cache, which has to be widened anyway).  The rows of a KV head's G query
 //   heads are packed into one run of n_rows * G rows (row r = query r / G, head r % G of the
 //   group), so a short query block fills its 128-row tiles; all segments' tiles laid end to end
 //   are cut into n_parts equal runs, one workgroup each.  With one part the workgroup writes the
 //   final output, otherwise a partial result for the merge.
-template <int D, bool GLOBAL>
+template <int D, int MODE>
 __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, uint16_t* smem) {
+  constexpr bool GLOBAL = MODE != PC_FA_LOCAL;
   using SM = FlashSmem<D>;
   constexpr int KS = D / 16;        // k-steps of the first product (over head_dim)
   constexpr int DB = D / 32;        // 32-row blocks of O^T (over head_dim)
@@ -368,8 +374,8 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   // ---- cooperative tile loads, straight from global memory into LDS, through buffer descriptors.
   //      Local: a tile image is copied as it is, wavefront w issuing instruction i for its 1 KiB
   //      block WAVES i + w (descriptor base + scalar offset + one constant per-lane offset).
-  //      Global: row-major rows; wavefront w takes rows 16 w .. + 15, an instruction 64 bytes of
-  //      each (the four lanes of a row adjacent), in LDS [16-row group][64-byte column block][row].
+  //      Images of the global mode: the same from the cursor's tile.  Rows: wavefront w takes rows
+  //      16 w .. + 15, an instruction 64 bytes of each (the four lanes of a row adjacent), in LDS [16-row group][64-byte column block][row].
   //      Of a K row's four 16-byte granules in a block, granule c lies at place c ^ (row % 16 / 4), so
   //      that the 16 lanes an operand read serves together (one granule column, 16 rows) touch 256
   //      different bytes; V is kept straight: half a wavefront's transposing read takes 4 rows =
@@ -388,6 +394,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   auto tile_load = [&]() __attribute__((always_inline)) {
     TileLoad x;
     x.k = cur.k; x.v = cur.v;
+    if (MODE == PC_FA_IMAGES) { x.bytes = x.v_off = x.k_off = 0; return x; }
     x.bytes = (min(cur.cut, 64) - 1) * cur.row_bytes + 2 * D;
     int id = tid;                                  // recomputed per tile: the loop has no registers to spare
     asm volatile("" : "+v"(id));
@@ -399,17 +406,25 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)(dst + 512 * (T_LD * wave_s + i)), 16, off, 64 * i, 0, 0);
   };
+  auto load_image_i = [&](const uint16_t* base, uint16_t* dst, int i) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, IMG_BYTES, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lptr_t)(dst + 512 * (WAVES * i + wave_s)), 16, ld_goff, 1024 * WAVES * i, 0, 0);
+  };
   // (tile t into the buffers of tile `to`)
   auto load_k_i = [&](const TileLoad& x, int t, int to, int i) __attribute__((always_inline)) {
-    if (GLOBAL)
+    if (MODE == PC_FA_ROWS)
       load_rows_i(x.k, x.bytes, x.k_off, k_lds(to), i);
+    else if (MODE == PC_FA_IMAGES)
+      load_image_i(x.k, k_lds(to), i);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(k_lds(to) + 512 * (WAVES * i + wave_s)), 16,
                                                ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
   };
   auto load_v_i = [&](const TileLoad& x, int t, int to, int i) __attribute__((always_inline)) {
-    if (GLOBAL)
+    if (MODE == PC_FA_ROWS)
       load_rows_i(x.v, x.bytes, x.v_off, v_lds(to), i);
+    else if (MODE == PC_FA_IMAGES)
+      load_image_i(x.v, v_lds(to), i);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_lds(to) + 512 * (WAVES * i + wave_s)), 16,
                                                ld_goff, t * IMG_BYTES + 1024 * WAVES * i, 0, 0);
@@ -427,8 +442,9 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   // private, XOR-swizzled LDS area in the V buffers of tiles 1 and 2; a gather straight into the operand
   // layout (every lane its own row) would touch 32 to 64 cache lines per instruction.  The table holds two
   // pairs' (cos, sin) of consecutive rows side by side, so the lanes of 32 rows read it straight into
-  // registers, 16 bytes each (one pair, 8 bytes: twice the instructions, 2000 cycles more).  The first tiles (K 0, V 0, K 1) are asked for behind the queries: one memory latency in
-  // front of the first product instead of two.  Cycles of a workgroup in front of its loop and behind it,
+  // registers, 16 bytes each (one pair, 8 bytes: twice the instructions, 2000 cycles more).  The first tiles
+  // (K 0, V 0, K 1) are asked for behind the queries: one memory latency in front of the first product
+  // instead of two.  Cycles of a workgroup in front of its loop and behind it,
   // 12 x 1550 rows, 32 / 8 heads, with the table through LDS, 64-bit addresses a row, tiles after the rotation ->
   // now: queries 4470 -> 5600, rotation 4300 -> 2690, tiles 1840 -> 510, output 2310 -> 1840 (a tile takes 2400);
   // the launch 331 -> 318 us, 20 x 500 85.8 -> 82, 36 x 4096 of 32 / 32 heads 4434 -> 4367, 8 x 8192 3637 -> 3613.
@@ -552,7 +568,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   // even and odd ks; V keys 8 hf .. + 3 of the column group (lane / 16) % 2.  Everything but the
   // lane's own part is a compile-time offset of the LDS read.
   int k_base, v_base;
-  if (GLOBAL) {
+  if (MODE == PC_FA_ROWS) {
     k_base = (krow / 16) * (16 * D) + (krow % 16) * 32 + ((hf ^ (krow % 16 / 4)) * 8);
     v_base = (8 * hf + (lane % 16) / 4) * 32 + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
   } else {
@@ -560,11 +576,11 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     v_base = (hf * D + n) * 8;
   }
   auto read_k = [&](int tile, int half, int ks) __attribute__((always_inline)) {
-    return GLOBAL ? *(const bf16x8*)(smem + ((tile + 32 * D * half + k_base) ^ (16 * (ks % 2))) + 512 * (ks / 2))
+    return MODE == PC_FA_ROWS ? *(const bf16x8*)(smem + ((tile + 32 * D * half + k_base) ^ (16 * (ks % 2))) + 512 * (ks / 2))
                   : *(const bf16x8*)(smem + tile + 32 * 8 * half + k_base + 2 * ks * 64 * 8);
   };
   auto read_v = [&](const uint16_t* tile, int half, int ts, int db) __attribute__((always_inline)) {
-    return GLOBAL ? read_v_rows(tile + 32 * D * half + v_base + 16 * D * ts + 512 * db)
+    return MODE == PC_FA_ROWS ? read_v_rows(tile + 32 * D * half + v_base + 16 * D * ts + 512 * db)
                   : *(const bf16x8*)(tile + 4 * half * D * 8 + v_base + 2 * ts * D * 8 + 32 * db * 8);
   };
 
@@ -907,11 +923,11 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   }
 }
 
-template <int D, bool GLOBAL>
+template <int D, int MODE>
 __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   int bid = blockIdx.x;
-  if (!GLOBAL) {
+  if (MODE == PC_FA_LOCAL) {
     static_assert(PC_FA_THREADS == 256, "pc_chunk_sum");
     if (bid < a.sum_blocks) {
       if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
@@ -919,7 +935,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs
     }
     bid -= a.sum_blocks;
   }
-  flash_workgroup<D, GLOBAL>(a, bid, smem);
+  flash_workgroup<D, MODE>(a, bid, smem);
 }
 
 // Local and global attention in one launch, for a layer whose selections are done before the local
@@ -931,8 +947,8 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_both_kernel(PcFlashArg
                                                                       int front) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   const int bid = blockIdx.x;
-  if (bid >= front) flash_workgroup<D, false>(local, bid - front, smem);
-  else if (bid < glob_blocks) flash_workgroup<D, true>(global, bid, smem);
+  if (bid >= front) flash_workgroup<D, PC_FA_LOCAL>(local, bid - front, smem);
+  else if (bid < glob_blocks) flash_workgroup<D, PC_FA_ROWS>(global, bid, smem);
 }
 
 // The global part's reference follows the maximum at every tile there (window 0), as it starts anew in every part of
@@ -966,11 +982,12 @@ static bool images_too_long(const PcFlashArgs& a) {
   return ((long long)a.n_rows + 63) / 64 * 64 * a.head_dim * 2 >= 0x7fffffffLL;
 }
 
-template <int D, bool GLOBAL>
+template <int D, int MODE>
 static int launch_flash_t(const PcFlashArgs& args, hipStream_t st) {
+  constexpr bool GLOBAL = MODE != PC_FA_LOCAL;
   PcFlashArgs a = args;
   using SM = FlashSmem<D>;
-  auto kern = flash_fwd_kernel<D, GLOBAL>;
+  auto kern = flash_fwd_kernel<D, MODE>;
   static std::atomic<uint64_t> raised{0};          // one per instantiation of this launcher
   const int lds_rc = pc_raise_dynamic_lds((const void*)kern, SM::BYTES, raised);
   if (lds_rc != PC_OK) return lds_rc;
@@ -1027,8 +1044,11 @@ int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_
 }
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
-  if (a.head_dim == 128) return a.global ? launch_flash_t<128, true>(a, st) : launch_flash_t<128, false>(a, st);
-  return a.global ? launch_flash_t<64, true>(a, st) : launch_flash_t<64, false>(a, st);
+  if (a.head_dim == 128)
+    return !a.global ? launch_flash_t<128, PC_FA_LOCAL>(a, st)
+                     : (a.images ? launch_flash_t<128, PC_FA_IMAGES>(a, st) : launch_flash_t<128, PC_FA_ROWS>(a, st));
+  return !a.global ? launch_flash_t<64, PC_FA_LOCAL>(a, st)
+                   : (a.images ? launch_flash_t<64, PC_FA_IMAGES>(a, st) : launch_flash_t<64, PC_FA_ROWS>(a, st));
 }
 
 #define PC_FA_PARTS_MAX 64
