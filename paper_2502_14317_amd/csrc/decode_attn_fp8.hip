@@ -8,12 +8,11 @@
 //   code  = E4M3(x / scale), round to nearest even, saturating
 // The paper leaves the cache precision open; this format is an extension of this library.
 //
-// kv_quantize_fp8_kernel   one workgroup per (sequence, segment, KV head, K or V): maximum,
-//                          then codes; the second sweep reads the segment again (5 bytes per
-//                          element in all), unless the caller hands in the maxima (the gather
-//                          that fills the cache can leave them: 3 bytes per element).  Codes are
-//                          written in 32-key blocks laid out for the matrix cores (below), V
-//                          transposed.
+// kv_quantize_fp8_kernel   codes from maxima that the caller hands in (the gather that fills the cache can
+//                          leave them: 3 bytes per element), or one workgroup per (sequence, segment, KV
+//                          head, K or V) that finds the maximum first and reads the segment again (5
+//                          bytes).  Codes are written in 32-key blocks laid out for the matrix cores
+//                          (below), V transposed.
 // decode_attn_fp8_kernel   the split-KV kernel of decode_attn.hip on 8-bit operands: codes are
 //                          widened in registers (every E4M3 value is exact in bf16), both
 //                          products run on the 16x16x32 bf16 MFMA, the scales are folded into the
@@ -42,45 +41,165 @@
 
 
 // ------------------------------------------------------------------------------------------
-// Quantisation.  blockIdx.x = (b, s, g), blockIdx.y = 0 (K) or 1 (V).  The segment is read twice
-// (maximum, then codes): 5 bytes of traffic per element.  1024 threads with 4 loads each in
-// flight keep HBM busy (6.0 TB/s of actual traffic at the decode config); bounding the
-// workgroups per CU so that the segments between the two sweeps would fit the last-level cache
-// measured no gain.
+// Quantisation.  A wavefront takes units of 4 KiB of codes (4096 / D keys) by itself: all its loads go out at
+// once, a lane then holds 16 values of a key for each K piece, or 8 keys x 8 values for V, whose codes are
+// packed along the keys; V granules pass through the wavefront's own LDS (swizzled, no bank taken more than twice) so
+// that every store covers 1 KiB.  Bound by memory if the division is not: x / scale by v_div_* is about 11
+// instructions a value; here the correctly rounded quotient from the reciprocal, once rounded itself, and
+// one residual: q = x r, q' = q - (q scale - x) r.  It equals the division for every pair of mantissas (2^23
+// scales x 2^7 values, compared one by one); exponents do not matter while nothing under- or overflows, which
+// holds where the code is not 0 for scales within 2^+-60.  Others divide.  -0 stays -0.
+// 256 segments of 2048 x 128 (0.40 GB) with maxima: one workgroup of 1024 per segment, both directions through
+// LDS between barriers, division 88 us; now 59; 64 segments 48 -> 17; 4096 (6.4 GB) 1192 -> 1084, 5.9 TB/s.
+// Without: 124 -> 97, 55 -> 30, 1570 -> 1520.  The rows carry the non-temporal hint where they are more than
+// the last-level cache holds (256 MiB): smaller ones the gather has just left there, and the second sweep finds
+// the first one's (64 segments without the hint 17 and 30 us, with it 19 and 39; 4096 1118 and 1084).
 #define PC_Q8_THREADS 1024
-#define PC_Q8_UNROLL 4
-__global__ __launch_bounds__(PC_Q8_THREADS) void kv_quantize_fp8_kernel(
-    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
-    const int32_t* __restrict__ seg_len, int per_head, int n_kv_heads, int k_t, int D,
-    const float* __restrict__ k_amax, const float* __restrict__ v_amax,
-    uint8_t* __restrict__ k8, uint8_t* __restrict__ v8, float* __restrict__ k_scale,
-    float* __restrict__ v_scale) {
-  __shared__ uint32_t red[PC_Q8_THREADS / PC_WAVE];
-  __shared__ __attribute__((aligned(16))) uint8_t tile[PC_Q8_THREADS * PC_Q8_UNROLL * 8];   // 32 KiB of codes, block layout
-  const long long seg = blockIdx.x;
-  const uint16_t* src = (blockIdx.y ? vc : kc) + seg * (long long)k_t * D;
-  const int n_blk = (k_t + 31) / 32;
-  uint8_t* dst = (blockIdx.y ? v8 : k8) + seg * (long long)n_blk * 32 * D;
-  float* scale_out = blockIdx.y ? v_scale : k_scale;
-  const int len = seg_len ? min(max(seg_len[per_head ? seg : seg / n_kv_heads], 0), k_t) : k_t;
-  // 8-element groups: of the valid rows, and of all rows to write (whole 32-key blocks)
-  const long long n_valid = (long long)len * D / 8;
-  const long long n_all = (long long)n_blk * 32 * D / 8;
-  const int gpr = D / 8;                                   // groups per row
 
-  // largest magnitude: bf16 magnitudes order like their 15-bit patterns.  When the caller knows
-  // it already (the gather leaves it), the first sweep is skipped and the segment is read once.
-  const float* amax_in = blockIdx.y ? v_amax : k_amax;
-  uint32_t amax = 0;
-  for (long long i0 = 0; amax_in == nullptr && i0 < n_valid; i0 += PC_Q8_THREADS * PC_Q8_UNROLL) {
-    uint4 x[PC_Q8_UNROLL];
+// x = scale's multiple, clamped to the format (a NaN to its lowest, as max and min do)
+struct PcQuantScale {
+  float scale, inv, limit;
+  bool fast;
+};
+__device__ __forceinline__ PcQuantScale pc_quant_scale(float amax) {
+  PcQuantScale q;
+  q.scale = amax > 0.f ? amax / PC_E4M3_MAX : 1.0f;
+  q.fast = q.scale > 0x1p-60f && q.scale < 0x1p60f;
+  q.inv = 1.0f / q.scale;
+  q.limit = PC_E4M3_MAX * q.scale;
+  return q;
+}
+template <bool FAST>
+__device__ __forceinline__ float pc_quotient(float x, const PcQuantScale& s) {
+  if (!FAST) return fminf(fmaxf(x / s.scale, -PC_E4M3_MAX), PC_E4M3_MAX);
+  x = __builtin_amdgcn_fmed3f(x, -s.limit, s.limit);       // (the quotient of the limit is below 464, still code 448)
+  const float q = x * s.inv;
+  return fmaf(-fmaf(q, s.scale, -x), s.inv, q);
+}
+template <bool FAST>
+__device__ __forceinline__ uint32_t pc_e4m3x4(float a, float b, float c, float d, const PcQuantScale& s) {
+  uint32_t w = __builtin_amdgcn_cvt_pk_fp8_f32(pc_quotient<FAST>(a, s), pc_quotient<FAST>(b, s), 0, false);
+  return __builtin_amdgcn_cvt_pk_fp8_f32(pc_quotient<FAST>(c, s), pc_quotient<FAST>(d, s), w, true);
+}
+
+template <int D, bool FAST>
+__device__ __forceinline__ void quantize_values(const u32x4 (&x)[8], bool is_v, uint8_t* dst, int n_blk_left,
+                                                const PcQuantScale& s, uint8_t* stage) {
+  const int lane = threadIdx.x % PC_WAVE;
+  u32x4 out[4];
+  if (!is_v) {
 #pragma unroll
-    for (int u = 0; u < PC_Q8_UNROLL; ++u) {
+    for (int pc = 0; pc < 4; ++pc)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t w0 = x[2 * pc + e / 2][2 * (e % 2)], w1 = x[2 * pc + e / 2][2 * (e % 2) + 1];
+        out[pc][e] = pc_e4m3x4<FAST>(bf16_lo_to_f32(w0), bf16_hi_to_f32(w0), bf16_lo_to_f32(w1), bf16_hi_to_f32(w1), s);
+      }
+  } else {
+    const int dc = lane % (D / 8), g = lane / (D / 8) % 4, blk = lane / (D / 2);
+    const int q = dc / 4, m0 = 8 * (dc % 2), swz = g + 4 * (q % 2);
+    uint8_t* row = stage + blk * 32 * D + q * 1024 + g * 256 + 8 * (dc / 2 % 2);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float f[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f[j] = e % 2 ? bf16_hi_to_f32(x[j][e / 2]) : bf16_lo_to_f32(x[j][e / 2]);
+      const u32x2 code = {pc_e4m3x4<FAST>(f[0], f[1], f[2], f[3], s), pc_e4m3x4<FAST>(f[4], f[5], f[6], f[7], s)};
+      *(u32x2*)(row + ((m0 + e) ^ swz) * 16) = code;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int pc = 0; pc < 4; ++pc)
+      out[pc] = *(const u32x4*)(stage + pc * 1024 + (lane / 16) * 256 + ((lane % 16) ^ (lane / 16 + 4 * (pc % 2))) * 16);
+  }
+#pragma unroll
+  for (int pc = 0; pc < 4; ++pc)
+    if (pc * 1024 < n_blk_left * 32 * D) pc_store_once((u32x4*)(dst + 1024 * pc + 16 * lane), out[pc]);
+}
+
+template <int D, int HINT>
+__device__ __forceinline__ void load_unit(const __amdgpu_buffer_rsrc_t& rsrc, bool is_v, u32x4 (&x)[8]) {
+  const int lane = threadIdx.x % PC_WAVE;
+  if (!is_v) {
+    const int off = 2 * (lane % 16 * D + lane / 16 * 16);
+#pragma unroll
+    for (int pc = 0; pc < 4; ++pc)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+        x[2 * pc + e] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 2 * (pc / (D / 64) * 16 * D + pc % (D / 64) * 64 + 8 * e), HINT);
+  } else {
+    const int dc = lane % (D / 8), g = lane / (D / 8) % 4, blk = lane / (D / 2);
+    const int off = 2 * ((32 * blk + 4 * g) * D + 8 * dc);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 2 * (j < 4 ? j : 12 + j) * D, HINT);
+  }
+}
+
+// unit u of a segment: keys 4096 / D u ..; len valid rows, the codes of others are 0
+template <int D>
+__device__ __forceinline__ void quantize_unit(const uint16_t* src, uint8_t* dst, bool is_v, int u, int len, int n_blk,
+                                              float amax, int keep, uint8_t* stage) {
+  constexpr int KEYS = 4096 / D;
+  const int key0 = u * KEYS;
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(src + (long long)key0 * D), 0,
+                                                                        min(max(len - key0, 0), KEYS) * 2 * D, 0x00020000);
+  u32x4 x[8];
+  if (keep) load_unit<D, 0>(rsrc, is_v, x);
+  else load_unit<D, PC_BUF_NT>(rsrc, is_v, x);
+  const PcQuantScale s = pc_quant_scale(amax);
+  dst += (long long)key0 * D;
+  if (s.fast) quantize_values<D, true>(x, is_v, dst, n_blk - key0 / 32, s, stage);
+  else quantize_values<D, false>(x, is_v, dst, n_blk - key0 / 32, s, stage);
+}
+
+// with maxima: a wavefront per unit, blockIdx.y = 0 (K) or 1 (V)
+template <int D>
+__global__ __launch_bounds__(256) void kv_quantize_fp8_kernel(
+    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, const int32_t* __restrict__ seg_len, int per_head,
+    int n_kv_heads, int k_t, unsigned n_segs, const float* __restrict__ k_amax, const float* __restrict__ v_amax,
+    uint8_t* __restrict__ k8, uint8_t* __restrict__ v8, float* __restrict__ k_scale, float* __restrict__ v_scale, int keep) {
+  __shared__ __attribute__((aligned(16))) uint8_t stage[4][4096];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / PC_WAVE), is_v = blockIdx.y;
+  const int n_blk = (k_t + 31) / 32;
+  const unsigned units = (unsigned)(k_t + 4096 / D - 1) / (4096 / D);
+  const unsigned long long id = blockIdx.x * 4ULL + wave;
+  const unsigned seg = (unsigned)(id / units);
+  const int u = (int)(id % units);
+  if (seg >= n_segs) return;
+  const int len = seg_len ? min(max(seg_len[per_head ? seg : seg / n_kv_heads], 0), k_t) : k_t;
+  const float amax = fabsf((is_v ? v_amax : k_amax)[seg]);
+  quantize_unit<D>((is_v ? vc : kc) + (long long)seg * k_t * D, (is_v ? v8 : k8) + (long long)seg * n_blk * 32 * D, is_v, u,
+                   len, n_blk, amax, keep, stage[wave]);
+  if (u == 0 && threadIdx.x % PC_WAVE == 0) (is_v ? v_scale : k_scale)[seg] = pc_quant_scale(amax).scale;
+}
+
+// without: a workgroup per segment sweeps it for the maximum (bf16 magnitudes order like their 15-bit
+// patterns), then its wavefronts take the units
+template <int D>
+__global__ __launch_bounds__(PC_Q8_THREADS) void kv_amax_quantize_fp8_kernel(
+    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc, const int32_t* __restrict__ seg_len, int per_head,
+    int n_kv_heads, int k_t, uint8_t* __restrict__ k8, uint8_t* __restrict__ v8, float* __restrict__ k_scale,
+    float* __restrict__ v_scale, int keep) {
+  constexpr int WAVES = PC_Q8_THREADS / PC_WAVE, UNROLL = 4;
+  __shared__ uint32_t red[WAVES];
+  __shared__ __attribute__((aligned(16))) uint8_t stage[WAVES][4096];
+  const long long seg = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / PC_WAVE), is_v = blockIdx.y;
+  const uint16_t* src = (is_v ? vc : kc) + seg * (long long)k_t * D;
+  const int n_blk = (k_t + 31) / 32;
+  const int len = seg_len ? min(max(seg_len[per_head ? seg : seg / n_kv_heads], 0), k_t) : k_t;
+  const long long n_valid = (long long)len * D / 8;        // 8-element groups of the valid rows
+  uint32_t amax = 0;
+  for (long long i0 = 0; i0 < n_valid; i0 += PC_Q8_THREADS * UNROLL) {
+    uint4 x[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
       const long long i = i0 + u * PC_Q8_THREADS + threadIdx.x;
       x[u] = i < n_valid ? *(const uint4*)(src + 8 * i) : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int u = 0; u < PC_Q8_UNROLL; ++u) {
+    for (int u = 0; u < UNROLL; ++u) {
       const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) amax = max(amax, max(w[e] & 0x7fffu, (w[e] >> 16) & 0x7fffu));
@@ -88,66 +207,16 @@ __global__ __launch_bounds__(PC_Q8_THREADS) void kv_quantize_fp8_kernel(
   }
 #pragma unroll
   for (int off = PC_WAVE / 2; off > 0; off >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, off));
-  if (threadIdx.x % PC_WAVE == 0) red[threadIdx.x / PC_WAVE] = amax;
+  if (threadIdx.x % PC_WAVE == 0) red[wave] = amax;
   __syncthreads();
   amax = 0;
 #pragma unroll
-  for (int w = 0; w < PC_Q8_THREADS / PC_WAVE; ++w) amax = max(amax, red[w]);
-  const float fmax_ = amax_in ? fabsf(amax_in[seg]) : __uint_as_float(amax << 16);
-  const float scale = fmax_ > 0.f ? fmax_ / PC_E4M3_MAX : 1.0f;
-  if (threadIdx.x == 0) scale_out[seg] = scale;
-
-  for (long long i0 = 0; i0 < n_all; i0 += PC_Q8_THREADS * PC_Q8_UNROLL) {
-    uint4 x[PC_Q8_UNROLL];
-#pragma unroll
-    for (int u = 0; u < PC_Q8_UNROLL; ++u) {
-      const long long i = i0 + u * PC_Q8_THREADS + threadIdx.x;
-      x[u] = i < n_valid ? pc_load_once((const uint4*)(src + 8 * i)) : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < PC_Q8_UNROLL; ++u) {
-      const long long i = i0 + u * PC_Q8_THREADS + threadIdx.x;
-      if (i >= n_all) continue;
-      uint2 code = make_uint2(0u, 0u);              // rows behind the segment's length or behind k_t
-      if (i < n_valid) {
-        const uint32_t w[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-        float f[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          f[2 * e] = fminf(fmaxf(bf16_lo_to_f32(w[e]) / scale, -PC_E4M3_MAX), PC_E4M3_MAX);
-          f[2 * e + 1] = fminf(fmaxf(bf16_hi_to_f32(w[e]) / scale, -PC_E4M3_MAX), PC_E4M3_MAX);
-        }
-        uint32_t c0 = 0, c1 = 0;
-        c0 = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], c0, false);
-        c0 = __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], c0, true);
-        c1 = __builtin_amdgcn_cvt_pk_fp8_f32(f[4], f[5], c1, false);
-        c1 = __builtin_amdgcn_cvt_pk_fp8_f32(f[6], f[7], c1, true);
-        code = make_uint2(c0, c1);
-      }
-      // group i = 8 values d0..d0+7 of one key: to its place in the block layout, in LDS
-      const int il = (int)(i - i0);                         // group within this sweep step
-      const int key_l = il / gpr, d0 = (il % gpr) * 8;      // key within the step's rows
-      const int kib = key_l % 32, blk_l = key_l / 32;
-      if (!blockIdx.y) {
-        uint8_t* t = tile + blk_l * 32 * D + (kib / 16) * 16 * D + (d0 / 64) * 1024 +
-                     (16 * ((d0 % 64) / 16) + kib % 16) * 16 + d0 % 16;
-        *(uint2*)t = code;
-      } else {
-        const int g = (kib % 16) / 4, j = kib % 4 + 4 * (kib / 16);
-        uint8_t* t = tile + blk_l * 32 * D + (d0 / 32) * 1024 + g * 256 + ((d0 % 32) / 16) * 8 + j;
-        const int m0 = d0 % 16;                               // m = m0 .. m0 + 7
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          t[(m0 + e) * 16] = (uint8_t)(((e < 4 ? code.x : code.y) >> (8 * (e % 4))) & 0xffu);
-      }
-    }
-    // a sweep step covers whole blocks (its rows are a multiple of 32): copy them out
-    __syncthreads();
-    const long long step_bytes = min((long long)PC_Q8_THREADS * PC_Q8_UNROLL * 8, (n_all - i0) * 8);
-    for (long long o = 16LL * threadIdx.x; o < step_bytes; o += 16LL * PC_Q8_THREADS)
-      pc_store_once((uint4*)(dst + i0 * 8 + o), *(const uint4*)(tile + o));
-    __syncthreads();
-  }
+  for (int w = 0; w < WAVES; ++w) amax = max(amax, red[w]);
+  const float fmax_ = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)amax) << 16);
+  if (threadIdx.x == 0) (is_v ? v_scale : k_scale)[seg] = pc_quant_scale(fmax_).scale;
+  const int units = (k_t + 4096 / D - 1) / (4096 / D);
+  for (int u = wave; u < units; u += WAVES)
+    quantize_unit<D>(src, (is_v ? v8 : k8) + seg * (long long)n_blk * 32 * D, is_v, u, len, n_blk, fmax_, keep, stage[wave]);
 }
 
 int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg_len,
@@ -156,10 +225,23 @@ int pc_launch_kv_quantize_fp8(const void* kc, const void* vc, const int32_t* seg
                               void* v8, float* k_scale, float* v_scale, hipStream_t st) {
   if (n_segs == 0) return PC_OK;
   if (n_segs > 0x7fffffffLL) return PC_ERR_SHAPE;
+  const long long units = (k_t + 4096 / head_dim - 1) / (4096 / head_dim);
+  const long long blocks = k_amax ? (n_segs * units + 3) / 4 : n_segs;
+  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  const int keep = 4LL * head_dim * k_t * n_segs <= (256LL << 20);
   PcProfScope prof(PC_KERNEL_KV_QUANTIZE, st);
-  hipLaunchKernelGGL(kv_quantize_fp8_kernel, dim3((unsigned)n_segs, 2), dim3(PC_Q8_THREADS), 0, st,
-                     (const uint16_t*)kc, (const uint16_t*)vc, seg_len, seg_len_per_head, n_kv_heads,
-                     k_t, head_dim, k_amax, v_amax, (uint8_t*)k8, (uint8_t*)v8, k_scale, v_scale);
+  const dim3 grid((unsigned)blocks, 2);
+#define PC_Q8_LAUNCH(D)                                                                                                \
+  if (k_amax)                                                                                                          \
+    hipLaunchKernelGGL(kv_quantize_fp8_kernel<D>, grid, dim3(256), 0, st, (const uint16_t*)kc, (const uint16_t*)vc,     \
+                       seg_len, seg_len_per_head, n_kv_heads, k_t, (unsigned)n_segs, k_amax, v_amax, (uint8_t*)k8,     \
+                       (uint8_t*)v8, k_scale, v_scale, keep);                                                          \
+  else                                                                                                                 \
+    hipLaunchKernelGGL(kv_amax_quantize_fp8_kernel<D>, grid, dim3(PC_Q8_THREADS), 0, st, (const uint16_t*)kc,           \
+                       (const uint16_t*)vc, seg_len, seg_len_per_head, n_kv_heads, k_t, (uint8_t*)k8, (uint8_t*)v8,    \
+                       k_scale, v_scale, keep);
+  if (head_dim == 128) { PC_Q8_LAUNCH(128) } else { PC_Q8_LAUNCH(64) }
+#undef PC_Q8_LAUNCH
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
