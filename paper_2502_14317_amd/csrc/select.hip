@@ -125,8 +125,14 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 // the unused tail of the output is filled with -1 and the kept count is reported.
 // Measured, before (keys in LDS, four 8-bit radix passes) and now: 512 tokens x
 // 16 workgroups 7.0 -> 5.8 us, 3584 x 32 13.8 -> 9.2, 7680 x 64 27 -> 15.  (Two bits a round counted with
-// ballots, no histogram: 8.5, 14.6 and 23.8.)
+// ballots, no histogram: 8.5, 14.6 and 23.8.)  A bin of up to PC_SEL_FEW keys is ranked by counting instead of
+// another round: in a layer's launch 2011 tokens x 40 11.6 -> 10.3, 7680 x 64 17.1 -> 14.9, 3584 x 32 12.
+// The layer's gather in the same launch where a segment is small (PC_SEL_GATHER bytes of K and V): the workgroup
+// copies the rows that it has just selected (16 segments of 128 rows of 64 values: 6.7 + 3.7 us -> 7.7).  One CU
+// moves about 50 bytes a nanosecond, so larger segments are left to the gather's own launch.
 #define PC_SEL_BINS 2048
+#define PC_SEL_FEW 256        // so many keys of a bin are ranked by counting: one pass over them instead of a round
+#define PC_SEL_GATHER 65536
 
 // A layer's chunk selection in the same launch: every workgroup adds up the chunks' block sums (the order
 // of pc_chunk_sum, a wavefront a chunk, its 4 x 64 strided sums asked for at once), ranks them as
@@ -140,6 +146,38 @@ struct PcSelectChunks {
   int32_t* idx;            // [n_sel] out
   float* top;              // [n_sel] out, nullable
 };
+struct PcSelectGather {
+  const uint4* k_src;      // [C, rows, H_kv, D], nullptr: no gather
+  const uint4* v_src;
+  uint4* k_dst;            // [n_sel, H_kv, k, D]
+  uint4* v_dst;
+  int rows, pieces;        // pieces = D / 8
+};
+// rows list[0 .. k) (k_eff valid ones, zeros behind) of chunk c, KV head g to segment seg
+template <int THREADS>
+__device__ __forceinline__ void select_gather(const PcSelectGather& x, const uint32_t* list, int k, int k_eff, int c, int g,
+                                              int n_kv_heads, long long seg) {
+  constexpr int UNROLL = 4;
+  const int piece = threadIdx.x % x.pieces, per_step = THREADS / x.pieces;
+  const long long src0 = ((long long)c * x.rows * n_kv_heads + g) * x.pieces + piece, dst0 = seg * k * x.pieces + piece;
+  for (int r0 = threadIdx.x / x.pieces; r0 < k; r0 += UNROLL * per_step) {
+    uint4 kv[UNROLL], vv[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int r = r0 + u * per_step;
+      kv[u] = vv[u] = make_uint4(0, 0, 0, 0);
+      if (r < k_eff) {
+        const long long src = src0 + (long long)list[r] * n_kv_heads * x.pieces;
+        kv[u] = x.k_src[src]; vv[u] = x.v_src[src];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int r = r0 + u * per_step;
+      if (r < k) { x.k_dst[dst0 + (long long)r * x.pieces] = kv[u]; x.v_dst[dst0 + (long long)r * x.pieces] = vv[u]; }
+    }
+  }
+}
 template <int THREADS>
 __device__ __forceinline__ int select_own_chunk(const PcSelectChunks& x, int n_sel, int s, bool writer) {
   __shared__ float score[PC_SEL_CHUNKS];
@@ -187,10 +225,10 @@ template <int KPT, int THREADS, bool CHUNKS>
 __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     const float* __restrict__ tok_score, const int32_t* __restrict__ chunk_idx, int n_kv_heads,
     int n, int k, float lambda, int cls_lo, int cls_hi, const int32_t* __restrict__ chunk_lens,
-    int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt, PcSelectChunks chunks) {
+    int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt, PcSelectChunks chunks, PcSelectGather gather) {
   constexpr int WAVES = THREADS / PC_WAVE, BPT = PC_SEL_BINS / THREADS;      // bins per thread
   __shared__ uint32_t hist[PC_SEL_BINS];
-  __shared__ uint32_t sh_cand, sh_min, sh_max, sh_bin, sh_need, sh_in_bin;
+  __shared__ uint32_t sh_cand, sh_min, sh_max, sh_bin, sh_need, sh_in_bin, sh_few;
   __shared__ uint32_t wave_tot[WAVES], wave_gt[WAVES], wave_eq[WAVES];
 
   const int s = blockIdx.x / n_kv_heads;
@@ -205,7 +243,7 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   const int first = wave * (KPT * PC_WAVE) + lane; // index of the thread's slot 0; slot j: + 64 j
 
   const int n_valid = chunk_lens ? min(max(chunk_lens[c], 0), n) : n;   // a short chunk has fewer tokens
-  if (threadIdx.x == 0) { sh_cand = 0u; sh_min = 0xffffffffu; sh_max = 0u; }
+  if (threadIdx.x == 0) { sh_cand = 0u; sh_min = 0xffffffffu; sh_max = 0u; sh_few = 0u; }
   uint32_t key[KPT];
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
@@ -232,7 +270,10 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   const int k_eff = min(k, (int)sh_cand);
   for (int i = k_eff + threadIdx.x; i < k; i += THREADS) dst[i] = -1;
   if (threadIdx.x == 0 && out_cnt) out_cnt[blockIdx.x] = k_eff;
-  if (k_eff == 0) return;                          // uniform over the workgroup
+  if (k_eff == 0) {                                // uniform over the workgroup
+    if (CHUNKS && gather.k_src) select_gather<THREADS>(gather, hist, k, 0, c, g, n_kv_heads, blockIdx.x);
+    return;
+  }
 
   // The need-th largest of the keys in [lo, hi].  T ends as the k-th largest key, or one below the
   // smallest admitted key where a bin is taken whole (then no key equal to T is admitted).
@@ -276,6 +317,23 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     if (need == sh_in_bin) { T = lo - 1u; break; }             // every key of the bin is admitted
     if (shift == 0) break;                                     // the bin is one key value
     hi = min(hi, lo + ((1u << shift) - 1u));
+    if (sh_in_bin <= PC_SEL_FEW) {                             // the bin's keys by counting (hist is read no more)
+      const uint32_t m = sh_in_bin;
+#pragma unroll
+      for (int j = 0; j < KPT; ++j)
+        if (key[j] >= lo && key[j] <= hi) hist[atomicAdd(&sh_few, 1u)] = key[j];
+      __syncthreads();
+      if (threadIdx.x < m) {
+        const uint32_t mine = hist[threadIdx.x];
+        uint32_t gt = 0, ge = 0;
+#pragma unroll 8
+        for (uint32_t i = 0; i < m; ++i) { gt += hist[i] > mine; ge += hist[i] >= mine; }
+        if (gt < need && ge >= need) sh_bin = mine;            // one key value: every writer has the same
+      }
+      __syncthreads();
+      T = sh_bin;
+      break;
+    }
   }
 
   uint32_t cnt_gt = 0, cnt_eq = 0;
@@ -293,6 +351,7 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     total_gt += x;
     if (w < wave) { base_gt += x; base_eq += wave_eq[w]; }
   }
+  // (behind the barrier above hist is free: the selected indices for the gather)
   const uint32_t need_eq = (uint32_t)k_eff - total_gt;      // how many keys equal to T are admitted
 
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -302,23 +361,31 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
     const unsigned long long bg = __ballot(gt), be = __ballot(eq);
     const uint32_t gt_before = base_gt + (uint32_t)__popcll(bg & below);
     const uint32_t eq_before = base_eq + (uint32_t)__popcll(be & below);
-    if (gt || (eq && eq_before < need_eq)) dst[gt_before + min(eq_before, need_eq)] = first + PC_WAVE * j;
+    if (gt || (eq && eq_before < need_eq)) {
+      const uint32_t at = gt_before + min(eq_before, need_eq);
+      dst[at] = first + PC_WAVE * j;
+      if (CHUNKS && gather.k_src) hist[at] = (uint32_t)(first + PC_WAVE * j);
+    }
     base_gt += (uint32_t)__popcll(bg);
     base_eq += (uint32_t)__popcll(be);
+  }
+  if (CHUNKS && gather.k_src) {
+    __syncthreads();
+    select_gather<THREADS>(gather, hist, k, k_eff, c, g, n_kv_heads, blockIdx.x);
   }
 }
 
 template <bool CHUNKS>
 static int launch_tokens(const float* tok_score, const int32_t* chunk_idx, int n_sel, int n_kv_heads, int chunk_len,
                          int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
-                         int32_t* out_cnt, const PcSelectChunks& chunks, hipStream_t st) {
+                         int32_t* out_cnt, const PcSelectChunks& chunks, const PcSelectGather& gather, hipStream_t st) {
   PcProfScope prof(PC_KERNEL_SELECT_TOKENS, st);
   // key slots per thread: the smallest power of two that holds the chunk (at most 32768 tokens), up
   // to 8 with 512 threads, whose barriers are cheaper
 #define PC_SEL_LAUNCH(KPT, THREADS)                                                                             \
   hipLaunchKernelGGL((select_tokens_kernel<KPT, THREADS, CHUNKS>), dim3(n_sel * n_kv_heads), dim3(THREADS), 0,   \
                      st, tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,                \
-                     chunk_lens, out_idx, out_cnt, chunks)
+                     chunk_lens, out_idx, out_cnt, chunks, gather)
   if (chunk_len <= 512) PC_SEL_LAUNCH(1, 512);
   else if (chunk_len <= 1024) PC_SEL_LAUNCH(2, 512);
   else if (chunk_len <= 2048) PC_SEL_LAUNCH(4, 512);
@@ -336,13 +403,18 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
                             int cls_hi, const int32_t* chunk_lens, int32_t* out_idx,
                             int32_t* out_cnt, hipStream_t st) {
   return launch_tokens<false>(tok_score, chunk_idx, n_sel, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi, chunk_lens,
-                              out_idx, out_cnt, PcSelectChunks{}, st);
+                              out_idx, out_cnt, PcSelectChunks{}, PcSelectGather{}, st);
 }
 
 bool pc_select_layer_fits(int n_chunks, int per_chunk) { return n_chunks <= PC_SEL_CHUNKS && per_chunk <= PC_SEL_BLOCKS; }
+bool pc_select_gather_fits(int k, int head_dim) { return 4LL * head_dim * k <= PC_SEL_GATHER; }
 int pc_launch_select_layer(const PcChunkSum& sum, int n_chunks, int n_sel, const float* tok_score, int n_kv_heads, int chunk_len,
                            int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* chunk_idx,
-                           float* chunk_top, int32_t* out_idx, int32_t* out_cnt, hipStream_t st) {
+                           float* chunk_top, int32_t* out_idx, int32_t* out_cnt, const void* k_src, const void* v_src, int rows,
+                           int head_dim, void* kc, void* vc, hipStream_t st) {
+  PcSelectGather gather = {};
+  if (pc_select_gather_fits(k, head_dim))
+    gather = PcSelectGather{(const uint4*)k_src, (const uint4*)v_src, (uint4*)kc, (uint4*)vc, rows, head_dim / 8};
   return launch_tokens<true>(tok_score, nullptr, n_sel, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi, chunk_lens, out_idx,
-                             out_cnt, PcSelectChunks{sum, n_chunks, chunk_idx, chunk_top}, st);
+                             out_cnt, PcSelectChunks{sum, n_chunks, chunk_idx, chunk_top}, gather, st);
 }

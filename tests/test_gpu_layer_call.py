@@ -2,7 +2,7 @@
 same bits everywhere but in the global attention, whose keys may be cut into other parts, so that its
 probabilities round to bf16 against other references (2^-9 relative each; outputs within the outputs'
 tolerance).  Shapes on either side of the rules: more than 64 chunks or 2048 block sums a chunk (selection in
-launches of its own), few query columns (no tile path), global attention cut into parts, a global workgroup
+launches of its own), segments of 64 KiB and more (gather in a launch of its own), few query columns (no tile path), global attention cut into parts, a global workgroup
 count that is no multiple of 8, ragged chunks, calibration."""
 import numpy as np
 import pytest
@@ -24,6 +24,9 @@ CASES = [
     (2, 4500, 40, 32, 32, 64, 40, 2, 900, False, None),      # 71 x 32 block sums a chunk
     (1, 600, 19, 40, 8, 64, 19, 1, 580, False, None),
     (2, 3000, 300, 4, 4, 128, 20, 2, 2900, False, None),     # cut into parts
+    (3, 300, 20, 4, 2, 64, 20, 2, 256, False, None),         # 64 KiB a segment: gathered by the selection
+    (3, 300, 20, 4, 2, 64, 20, 2, 257, True, None),          # above
+    (3, 1300, 40, 4, 2, 128, 20, 3, 128, True, (0.0, 0, 1290)),   # heads without 128 candidates: zero rows
 ]
 
 
