@@ -318,8 +318,8 @@ size_t pc_decode_step_fp8_workspace_bytes(int32_t batch, int32_t n_seg, int32_t 
  *   pc_parallel_attn computes it on the dequantised values code * scale.
  * n_q * H_q / H_kv <= 16 (the decoding stage) runs the split-KV kernel on the 8-bit codes (each
  * code is exact in bf16; the scales ride on the fp32 logits and probabilities).  More query rows
- * run the MFMA tile kernel: the segments are first widened to bf16 rows of code * scale (rounded
- * to bf16) in the workspace, then handled like a 16-bit cache.
+ * run the MFMA tile kernel: the segments are first widened to code * scale (rounded to bf16) in the
+ * workspace, then handled like a 16-bit cache.
  * Other arguments, errors and the workspace rule as pc_parallel_attn. */
 /* One-read quantisation.  pc_kv_quantize_fp8 reads every segment twice (maximum, then codes).
  * pc_gather_kv_amax is pc_gather_kv that also leaves, per destination segment, the largest

@@ -66,7 +66,7 @@ extern "C" int pc_profile_get(int i, int* kernel_id, float* ms) {
 }
 extern "C" const char* pc_kernel_name(int id) {
   static const char* names[PC_KERNEL_COUNT] = {
-      "rope_table_kernel", "kv_prepass_kernel", "flash_fwd_kernel", "scores_kernel<1>",
+      "layer_prep_kernel", "kv_prepass_kernel", "flash_fwd_kernel", "scores_kernel<1>",
       "scores_kernel<2>", "chunk_score_kernel", "select_chunks_kernel", "select_tokens_kernel",
       "gather_kv_kernel", "rope_q_kernel", "decode_attn_kernel", "merge_kernel",
       "self_info_rows_kernel", "kv_append_kernel", "scores_lse_kernel", "kv_quantize_fp8_kernel",

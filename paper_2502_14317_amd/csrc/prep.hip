@@ -93,7 +93,7 @@ int pc_launch_prep(const PcPrepArgs& a, int head_dim, hipStream_t st) {
   const long long units = a.scores.q_split ? (long long)a.scores.n_chunks * a.scores.n_kv_heads * a.scores.n_cb * (head_dim / 32) : 0;
   const long long blocks = table_blocks + a.n_q + (units + 3) / 4;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
-  PcProfScope prof(PC_KERNEL_ROPE_TABLE, st);
+  PcProfScope prof(PC_KERNEL_LAYER_PREP, st);
   const dim3 grid((unsigned)blocks), block(256);
   if (head_dim == 128) hipLaunchKernelGGL(layer_prep_kernel<128>, grid, block, 0, st, a, (int)table_blocks, units);
   else hipLaunchKernelGGL(layer_prep_kernel<64>, grid, block, 0, st, a, (int)table_blocks, units);
