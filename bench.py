@@ -30,14 +30,14 @@ PEAK_HBM_BYTES = 8.0e12       # MI355X HBM3E
 # kernels taken with the commands in profiles/pmc_hbm_traffic.md (which lists the raw counts), not
 # values measured inside this process.  Keyed by (kernel, workload).
 MEASURED_TRAFFIC = {
-    ("flash_fwd_kernel", "cfg1_llama3_8b_128k"): 1.2484e6 * 2048 + 1.0650e6 * 1024,
-    ("scores_kernel<1>+kv_prepass", "cfg1_llama3_8b_128k"): 2.67e5 * 2048 + 7.87e5 * 1024,
-    ("scores_kernel<2>", "cfg1_llama3_8b_128k"): 1.26e5 * 2048 + 3.8e3 * 1024,
+    ("flash_fwd_kernel", "cfg1_llama3_8b_128k"): 1.298e6 * 2048 + 1.069e6 * 1024,
+    ("scores_kernel<1>+kv_prepass", "cfg1_llama3_8b_128k"): 2.734e5 * 2048 + 7.875e5 * 1024,
+    ("scores_kernel<2>", "cfg1_llama3_8b_128k"): 1.281e5 * 2048 + 3.8e3 * 1024,
     ("decode_attn_kernel", "cfg4_decode_llama3_8b"): 2.10e6 * 2048 + 1.3e2 * 1024,
     ("decode_attn_kernel", "cfg4_decode_llama3_8b + tail"): 2.12e6 * 2048 + 1.3e2 * 1024,
     ("decode_attn_fp8_kernel", "cfg4_decode_llama3_8b"): 1.0490e6 * 2048 + 5.2e2 * 1024,
-    ("kv_quantize_fp8_kernel", "cfg4_decode_llama3_8b"): 4.181e6 * 2048 + 2.0974e6 * 1024,
-    ("kv_quantize_fp8_kernel one read", "cfg4_decode_llama3_8b"): 2.097e6 * 2048 + 2.0974e6 * 1024,
+    ("kv_quantize_fp8_kernel", "cfg4_decode_llama3_8b"): 4.105e6 * 2048 + 2.097e6 * 1024,
+    ("kv_quantize_fp8_kernel one read", "cfg4_decode_llama3_8b"): 2.250e6 * 2048 + 2.097e6 * 1024,
     ("gather_kv_kernel", "cfg4_decode_llama3_8b"): 2.1136e6 * 2048 + 4.1943e6 * 1024,
     ("self_info_rows_kernel", "16x512x128256"): 1.0280e6 * 2048 + 2.6e2 * 1024,
 }
