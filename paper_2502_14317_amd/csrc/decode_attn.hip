@@ -36,6 +36,7 @@ struct PcMergeArgs {
   PcMergeStep step;
   uint16_t* out;           // [B, n_q, H_q, D]
   float* lse_out;          // [B, H_q, n_q] or nullptr
+  int n_rows;              // B n_q H_q
   int n_q, n_q_heads, n_kv_heads, n_parts;
   float scale;
 };
@@ -46,7 +47,8 @@ __global__ __launch_bounds__(256) void merge_kernel(PcMergeArgs a) {
   __shared__ floatx4 num_lds[GROUPS][TPR];
   __shared__ float2 ml_lds[GROUPS];
   const int grp = threadIdx.x / TPR, d4 = threadIdx.x % TPR * 4;
-  int bid = blockIdx.x;
+  int bid = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  if (bid >= a.n_rows) return;
   const int h = bid % a.n_q_heads; bid /= a.n_q_heads;
   const int t = bid % a.n_q;       bid /= a.n_q;
   const int b = bid;
@@ -378,10 +380,12 @@ int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_ro
   a.scale = scale;
   const long long blocks = (long long)batch * n_q * n_q_heads;
   if (blocks == 0) return PC_OK;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  if (blocks > 0x7fffffffLL - PC_GRID_X) return PC_ERR_SHAPE;
+  a.n_rows = (int)blocks;
   PcProfScope prof(PC_KERNEL_MERGE, st);
-  if (head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3((unsigned)blocks), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL(merge_kernel<64>, dim3((unsigned)blocks), dim3(256), 0, st, a);
+  const dim3 grid = pc_grid_2d(blocks);
+  if (head_dim == 128) hipLaunchKernelGGL(merge_kernel<128>, grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(merge_kernel<64>, grid, dim3(256), 0, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

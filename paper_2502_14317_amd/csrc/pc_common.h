@@ -48,6 +48,15 @@ static inline int pc_raise_dynamic_lds(const void* kernel, int bytes, std::atomi
   return PC_OK;
 }
 
+// A grid dimension holds fewer than 2^32 threads, and more are not always refused: some launches then silently
+// run the first few of their workgroups only.  `blocks` workgroups of up to 256 threads as (x, y), number
+// y * gridDim.x + x; the last row may hold more than there are.
+#define PC_GRID_X (1LL << 23)
+static inline dim3 pc_grid_2d(long long blocks) {
+  if (blocks <= PC_GRID_X) return dim3((unsigned)blocks);
+  return dim3((unsigned)PC_GRID_X, (unsigned)((blocks + PC_GRID_X - 1) / PC_GRID_X));
+}
+
 static inline size_t pc_align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static inline bool pc_aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
