@@ -136,7 +136,8 @@ __device__ __forceinline__ void load_unit(const __amdgpu_buffer_rsrc_t& rsrc, bo
   }
 }
 
-// unit u of a segment: keys 4096 / D u ..; len valid rows, the codes of others are 0
+// unit u of a segment: keys 4096 / D u ..; len valid rows, the codes of others are 0.  (A segment's bytes need
+// more than 32 bits from 2^24 keys of 128 values on: blocks are counted, of a unit's at most 4096 bytes.)
 template <int D>
 __device__ __forceinline__ void quantize_unit(const uint16_t* src, uint8_t* dst, bool is_v, int u, int len, int n_blk,
                                               float amax, int keep, uint8_t* stage) {
@@ -149,8 +150,9 @@ __device__ __forceinline__ void quantize_unit(const uint16_t* src, uint8_t* dst,
   else load_unit<D, PC_BUF_NT>(rsrc, is_v, x);
   const PcQuantScale s = pc_quant_scale(amax);
   dst += (long long)key0 * D;
-  if (s.fast) quantize_values<D, true>(x, is_v, dst, n_blk - key0 / 32, s, stage);
-  else quantize_values<D, false>(x, is_v, dst, n_blk - key0 / 32, s, stage);
+  const int n_blk_left = min(n_blk - key0 / 32, KEYS / 32);
+  if (s.fast) quantize_values<D, true>(x, is_v, dst, n_blk_left, s, stage);
+  else quantize_values<D, false>(x, is_v, dst, n_blk_left, s, stage);
 }
 
 // with maxima: a wavefront per unit, blockIdx.y = 0 (K) or 1 (V)
