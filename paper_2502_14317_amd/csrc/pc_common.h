@@ -237,7 +237,7 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 struct PcScoreQueries {
   const uint16_t* q;       // [C, L, H_q, D] before RoPE
   const int32_t* chunk_lens;
-  uint16_t* q_split;       // [C, H_kv, n_cb][hi, lo][D / 16][64 lanes][8]: rotated, scaled, split query columns as MFMA operands
+  uint16_t* q_split;       // [C, H_kv, n_cb][hi, lo][D / 16][2][min(n_cols, 32)][8]: rotated, scaled, split query columns as MFMA operands
   int n_chunks, L, w, w_obs, n_kv_heads, G, n_cols, n_cb;
   float scale_log2;        // softmax scale x log2(e)
 };

@@ -46,10 +46,12 @@ __device__ __forceinline__ void split_query_columns(const PcScoreQueries& a, con
     split_bf16x2((x2l * cs[0].x + x1l * cs[0].y) * a.scale_log2, (x2h * cs[1].x + x1h * cs[1].y) * a.scale_log2, hi, lo);
     h2[e] = hi; l2[e] = lo;
   }
-  // [hi, lo][k-step][lane][8]
-  u32x4* dst = (u32x4*)a.q_split + (cg * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane;
-  dst[ks * PC_WAVE] = h1;        dst[(ks + KS / 2) * PC_WAVE] = h2;
-  dst[(KS + ks) * PC_WAVE] = l1; dst[(KS + ks + KS / 2) * PC_WAVE] = l2;
+  // [hi, lo][k-step][half][column][8]
+  const int cols = min(a.n_cols, 32), n = lane % 32, step = 2 * cols;
+  if (n >= cols) return;                                           // a single block of fewer columns holds no others
+  u32x4* dst = (u32x4*)a.q_split + (cg * a.n_cb + cb) * (2 * KS) * step + (lane / 32) * cols + n;
+  dst[ks * step] = h1;        dst[(ks + KS / 2) * step] = h2;
+  dst[(KS + ks) * step] = l1; dst[(KS + ks + KS / 2) * step] = l2;
 }
 
 template <int D>

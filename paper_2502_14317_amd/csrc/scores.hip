@@ -238,11 +238,12 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   const int col = min(32 * cb + n, a.n_cols - 1);
   bf16x8 qhi[KS], qlo[KS];
   {
-    const uint16_t* src = a.q_split + ((((long long)c * a.n_kv_heads + g) * a.n_cb + min(cb, a.n_cb - 1)) * (2 * KS) * PC_WAVE + lane) * 8;
+    const int cols = min(a.n_cols, 32);            // a single block of fewer columns holds no others
+    const uint16_t* src = a.q_split + ((((long long)c * a.n_kv_heads + g) * a.n_cb + min(cb, a.n_cb - 1)) * (4 * KS * cols) + hf * cols + min(n, cols - 1)) * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      qhi[ks] = *(const bf16x8*)(src + ks * PC_WAVE * 8);
-      qlo[ks] = *(const bf16x8*)(src + (KS + ks) * PC_WAVE * 8);
+      qhi[ks] = *(const bf16x8*)(src + ks * cols * 16);
+      qlo[ks] = *(const bf16x8*)(src + (KS + ks) * cols * 16);
     }
   }
   // pass 1: this lane's voting row (column) and its running statistics
@@ -686,7 +687,7 @@ static PcScoreWs scores_ws_layout(const pc_shape* s) {
   w.ml = off;      off = pc_align_up(off + blocks * n_cols * sizeof(float2), 256);
   w.lse2 = off;    off = pc_align_up(off + cg * n_cb * 32 * sizeof(float), 256);
   w.blk_sum = off; off = pc_align_up(off + blocks * sizeof(float), 256);
-  w.q_split = off; off += cg * n_cb * 32 * (size_t)s->head_dim * 2 * 2;
+  w.q_split = off; off += cg * n_cb * (n_cols < 32 ? n_cols : 32) * (size_t)s->head_dim * 2 * 2;
   w.total = off;
   return w;
 }
