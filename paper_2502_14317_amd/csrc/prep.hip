@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void layer_prep_kernel(PcPrepArgs a, int table
   // the tables, 16 positions a workgroup; the queries' one with the positions side by side goes through LDS
   constexpr int HALF = D / 2, PER = 16 * HALF / 256;
   __shared__ float2 turned[HALF][17];                               // [pair][position]
-  int bid = blockIdx.x;
+  int bid = (int)(blockIdx.y * gridDim.x + blockIdx.x);
   if (bid < table_blocks) {
     const int p0 = 16 * bid, i = threadIdx.x % HALF, rows = (a.n_pos + 127) / 128 * 128;
     const double theta = pc_rope_theta(a.rope, i);
@@ -94,9 +94,9 @@ int pc_launch_prep(const PcPrepArgs& a, int head_dim, hipStream_t st) {
   const long long table_blocks = a.q_table ? (a.n_pos + 127LL) / 128 * 8 : (a.n_pos + 15LL) / 16;
   const long long units = a.scores.q_split ? (long long)a.scores.n_chunks * a.scores.n_kv_heads * a.scores.n_cb * (head_dim / 32) : 0;
   const long long blocks = table_blocks + a.n_q + (units + 3) / 4;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  if (blocks > 0x7fffffffLL - PC_GRID_X) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_LAYER_PREP, st);
-  const dim3 grid((unsigned)blocks), block(256);
+  const dim3 grid = pc_grid_2d(blocks), block(256);
   if (head_dim == 128) hipLaunchKernelGGL(layer_prep_kernel<128>, grid, block, 0, st, a, (int)table_blocks, units);
   else hipLaunchKernelGGL(layer_prep_kernel<64>, grid, block, 0, st, a, (int)table_blocks, units);
   PC_LAUNCH_CHECK();

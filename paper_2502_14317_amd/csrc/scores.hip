@@ -199,6 +199,15 @@ struct PcKeyStage {
   }
 };
 
+// (chunk, KV head) of a workgroup: heads fastest in the grid's first dimension or, where that would pass its
+// 2^32 threads, in the third
+__device__ __forceinline__ int score_chunk(const PcScoreArgs& a) {
+  return gridDim.z > 1 ? blockIdx.x : blockIdx.x / a.n_kv_heads;
+}
+__device__ __forceinline__ int score_head(const PcScoreArgs& a) {
+  return gridDim.z > 1 ? blockIdx.z : blockIdx.x % a.n_kv_heads;
+}
+
 // WPC = wavefronts per block of 32 columns.  With 4 or more column blocks (a GQA group of 4
 // heads x 32 voting rows) a wavefront owns a column block and takes both 32-key halves of every
 // 64-key tile (WPC = 1).  With fewer column blocks the wavefronts of a block share its keys
@@ -217,7 +226,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   __shared__ float tok_part[PC_SC_WAVES][PASS == 2 ? KB_CAP : 1];
   __shared__ float2 ml_part[PC_SC_WAVES][32];
 
-  const int c = blockIdx.x / a.n_kv_heads, g = blockIdx.x % a.n_kv_heads, kblock = blockIdx.y;
+  const int c = score_chunk(a), g = score_head(a), kblock = blockIdx.y;
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
   // a short chunk is [len context rows ; the query rows]: its voting rows end at len + w_q
@@ -452,7 +461,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   __shared__ __attribute__((aligned(16))) uint16_t k_lo[TILE * KSTRIDE];
   __shared__ float tok_part[PC_SC_WAVES][PASS == 2 ? TILE : 1];
 
-  const int c = blockIdx.x / a.n_kv_heads, g = blockIdx.x % a.n_kv_heads, kblock = blockIdx.y, key0 = kblock * TILE;
+  const int c = score_chunk(a), g = score_head(a), kblock = blockIdx.y, key0 = kblock * TILE;
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
   const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
@@ -738,7 +747,9 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
   // eight) gets every chunk, whatever the chunks' lengths.  Chunks fastest -> heads fastest (us): pass 1 of
   // 36 x 4096 rows, 32 KV heads 1292 -> 1200; pass 2 of 12 ragged chunks of 2011 rows, 203 voting 120 -> 107; 8 heads of
   // chunks of one length: 64 x 8704 1165 -> 1184 and 474 -> 478, 16 x 8192 262 -> 263 and 135 -> 139.
-  const dim3 grid(s->n_chunks * s->n_kv_heads, a.n_kb), grid2(s->n_chunks * s->n_kv_heads, n_kb2), block(PC_SC_THREADS);
+  const long long cg = (long long)s->n_chunks * s->n_kv_heads;
+  const unsigned gx = (unsigned)(cg <= PC_GRID_X ? cg : s->n_chunks), gz = (unsigned)(cg <= PC_GRID_X ? 1 : s->n_kv_heads);
+  const dim3 grid(gx, a.n_kb, gz), grid2(gx, n_kb2, gz), block(PC_SC_THREADS);
   if (pre) {
     a.v = (const uint16_t*)pre->v; a.k_rope = (uint16_t*)pre->k_rope; a.k_img = (uint16_t*)pre->k_img;
     a.v_img = (uint16_t*)pre->v_img; a.Lp = pre->Lp;
