@@ -409,6 +409,60 @@ int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, c
   return PC_OK;
 }
 
+// The same segments as bf16 rows [n_segs, k_t, D], next to which the tail and the self segment are read where they
+// lie.  One workgroup per 32-key block, K (blockIdx.y = 0) or V; the rows are put together in LDS and leave as whole
+// 16-byte pieces.  Bound by memory like the images: 256 segments of 2048 x 128 61 us.
+template <int D>
+__global__ __launch_bounds__(256) void fp8_rows_kernel(
+    const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, const float* __restrict__ k_scale, const float* __restrict__ v_scale,
+    const int32_t* __restrict__ seg_len, int per_head, int n_kv_heads, int k_t, uint16_t* __restrict__ k_rows, uint16_t* __restrict__ v_rows) {
+  constexpr int STRIDE = D + 8;                           // 16-byte pieces stay aligned, rows start in other banks
+  __shared__ __attribute__((aligned(16))) uint16_t rows[32 * STRIDE];
+  const int n_blk = (k_t + 31) / 32, blk = (int)(blockIdx.x % n_blk), is_v = blockIdx.y;
+  const long long seg = blockIdx.x / n_blk;
+  const int n_rows = (seg_len ? min(seg_len[per_head ? seg : seg / n_kv_heads], k_t) : k_t) - 32 * blk;
+  if (n_rows <= 0) return;
+  const int p = threadIdx.x;                              // 16-byte piece of the block
+  if (p < 32 * D / 16) {
+    uint32_t o[8];
+    widen_piece<D>((is_v ? v8 : k8) + (seg * n_blk + blk) * 32LL * D + 16 * p, (is_v ? v_scale : k_scale)[seg], true, o);
+    const int lane = p % 64, piece = p / 64;
+    if (!is_v) {
+      uint4* r4 = (uint4*)(rows + (16 * (piece / (D / 64)) + lane % 16) * STRIDE + 64 * (piece % (D / 64)) + 16 * (lane / 16));
+      r4[0] = make_uint4(o[0], o[1], o[2], o[3]);
+      r4[1] = make_uint4(o[4], o[5], o[6], o[7]);
+    } else {
+      const int g = lane / 16, m = lane % 16;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          rows[(j < 4 ? 4 * g + j : 12 + 4 * g + j) * STRIDE + 32 * piece + 16 * h + m] = (uint16_t)(o[4 * h + j / 2] >> (16 * (j % 2)));
+    }
+  }
+  __syncthreads();
+  uint16_t* dst = (is_v ? v_rows : k_rows) + (seg * k_t + 32LL * blk) * D;
+  for (int x = threadIdx.x; x < min(32, n_rows) * (D / 8); x += 256)
+    *(uint4*)(dst + 8 * x) = *(const uint4*)(rows + x / (D / 8) * STRIDE + x % (D / 8) * 8);
+}
+
+int pc_launch_fp8_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                       int seg_len_per_head, long long n_segs, int n_kv_heads, int k_t, int head_dim, void* k_rows, void* v_rows, hipStream_t st) {
+  const long long blocks = n_segs * ((k_t + 31) / 32);
+  if (blocks == 0) return PC_OK;
+  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_FP8_ROWS, st);
+  const dim3 grid((unsigned)blocks, 2), block(256);
+  if (head_dim == 128)
+    hipLaunchKernelGGL(fp8_rows_kernel<128>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale, seg_len,
+                       seg_len_per_head, n_kv_heads, k_t, (uint16_t*)k_rows, (uint16_t*)v_rows);
+  else
+    hipLaunchKernelGGL(fp8_rows_kernel<64>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale, seg_len,
+                       seg_len_per_head, n_kv_heads, k_t, (uint16_t*)k_rows, (uint16_t*)v_rows);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+
 // The 16-bit tail can ride in the launch of the 8-bit segments, its workgroups behind theirs: the tail, a
 // few per cent of the bytes, then costs no launch, ramp and drain of its own: 2.5 us of a step of one
 // sequence.  Beyond 4 columns it rides up to 256 8-bit workgroups only; with more of them a launch is lost

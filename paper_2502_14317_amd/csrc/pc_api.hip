@@ -71,7 +71,7 @@ extern "C" const char* pc_kernel_name(int id) {
       "gather_kv_kernel", "rope_q_kernel", "decode_attn_kernel", "merge_kernel",
       "self_info_rows_kernel", "kv_append_kernel", "scores_lse_kernel", "kv_quantize_fp8_kernel",
       "decode_attn_fp8_kernel", "scores_kernel<1>+kv_prepass", "chunk_queue_kernel",
-      "fp8_images_kernel"};
+      "fp8_images_kernel", "fp8_rows_kernel"};
   return (id >= 0 && id < PC_KERNEL_COUNT) ? names[id] : "unknown";
 }
 
@@ -736,9 +736,24 @@ static PcKvGroup image_group(const void* k, const void* v, const int32_t* len, i
   return kg;
 }
 
-// Eq. 9-11 for a block of query rows over the 8-bit cache: everything becomes tile images in the workspace
-// (code * scale, rounded to bf16, and the 16-bit rows as they are), then one launch of the tile kernel as
-// for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].
+// Whether the keys of a block attention over the 8-bit cache become tile images, which spares the tile kernel the
+// transposing reads of every (row, key) tile but copies the 16-bit tail and the self segment as well, or the segments
+// alone become rows and the rest is read where it lies.  Per KV group, in (row, key) pairs: images gain `rows` a
+// visible key and 330 a widened one (turned to a loss of 520 where the widened keys pass the last-level cache and the
+// extra bytes count), and cost 4000 a copied row and a share of some 12 M pairs of 128 values a launch.  Fitted to 1358
+// calls (1 to 128 groups, 256 to 65536 keys, 17 to 32768 rows a group, tails of 0 to 65536 rows): at most 6 % and on
+// average not slower than rows, 1.5 % faster; images everywhere up to 2.7 times slower.  Rows / images (us), 32 / 8 heads
+// of 128 values, 8 x 2048 keys: 5 rows without a tail 64.6 / 62.2, tail of 8192 rows 69.5 / 78.1, 65536 132 / 250; 4
+// sequences x 512 rows 566 / 510, with a tail of 65536 rows 2601 / 2901.  Without segments nothing is widened: rows.
+static bool widen_to_images(double groups, int D, double rows, double keys, int tail_cap, int n_self) {
+  if (keys == 0.0) return false;
+  const double per_launch = 1.2e7 * 128.0 / (groups * D), share = groups * keys * D / 3.2e8;
+  return per_launch + ((share < 1.0 ? share : 1.0) * 850.0 - 330.0) * keys + 4000.0 * ((double)tail_cap + n_self) <= rows * (keys + tail_cap);
+}
+
+// Eq. 9-11 for a block of query rows over the 8-bit cache: the segments are widened in the workspace (code * scale,
+// rounded to bf16), to rows or, with everything else, to tile images; then one launch of the tile kernel as
+// for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].  The same bits either way.
 static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8, const float* k_scale,
                                    const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
                                    const void* k_tail, const void* v_tail, const int32_t* tail_len,
@@ -747,24 +762,37 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
                                    int q_pos0, float rope_base, float scale, void* out, float* lse_out,
                                    const Par8Ws& w, char* base, hipStream_t st) {
   PcFlashArgs a = {};
-  PcRowsToImages tail = {}, self = {};
   auto at = [&](size_t off) { return (uint16_t*)(base + off); };
-  if (n_seg > 0) a.grp[0] = image_group(at(w.k_img[0]), at(w.v_img[0]), seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
-  if (tail_cap > 0) {
-    tail = PcRowsToImages{(const uint16_t*)k_tail, (const uint16_t*)v_tail, tail_len, tail_cap, D, (long long)n_kv_heads * tail_cap * D,
-                          (long long)tail_cap * D, at(w.k_img[1]), at(w.v_img[1])};
-    a.grp[1] = image_group(tail.k_img, tail.v_img, tail_len, 0, 1, tail_cap, n_kv_heads, D);
+  const long long n_segs = (long long)batch * n_seg * n_kv_heads;
+  a.images = widen_to_images((double)batch * n_kv_heads, D, (double)n_q * (n_q_heads / n_kv_heads), (double)n_seg * k_t, tail_cap,
+                             k_self != nullptr ? n_q : 0);
+  if (!a.images) {
+    if (n_seg > 0) {
+      const int rc = pc_launch_fp8_rows(k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, n_segs, n_kv_heads, k_t, D, at(w.k_img[0]),
+                                        at(w.v_img[0]), st);
+      if (rc != PC_OK) return rc;
+      a.grp[0] = segment_group(at(w.k_img[0]), at(w.v_img[0]), seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
+    }
+    if (tail_cap > 0) a.grp[1] = segment_group(k_tail, v_tail, tail_len, 0, 1, tail_cap, n_kv_heads, D);
+    if (k_self != nullptr) a.grp[2] = self_group(k_self, v_self, n_q, n_kv_heads, D);
+  } else {
+    PcRowsToImages tail = {}, self = {};
+    if (n_seg > 0) a.grp[0] = image_group(at(w.k_img[0]), at(w.v_img[0]), seg_len, seg_len_per_head, n_seg, k_t, n_kv_heads, D);
+    if (tail_cap > 0) {
+      tail = PcRowsToImages{(const uint16_t*)k_tail, (const uint16_t*)v_tail, tail_len, tail_cap, D, (long long)n_kv_heads * tail_cap * D,
+                            (long long)tail_cap * D, at(w.k_img[1]), at(w.v_img[1])};
+      a.grp[1] = image_group(tail.k_img, tail.v_img, tail_len, 0, 1, tail_cap, n_kv_heads, D);
+    }
+    if (k_self != nullptr) {
+      self = PcRowsToImages{(const uint16_t*)k_self, (const uint16_t*)v_self, nullptr, n_q, n_kv_heads * D,
+                            (long long)n_q * n_kv_heads * D, D, at(w.k_img[2]), at(w.v_img[2])};
+      a.grp[2] = image_group(self.k_img, self.v_img, nullptr, 0, 1, n_q, n_kv_heads, D);
+      a.grp[2].causal = 1;
+    }
+    const int rc = pc_launch_fp8_images(k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, n_segs, k_t, D, at(w.k_img[0]),
+                                        at(w.v_img[0]), tail, self, batch, n_kv_heads, st);
+    if (rc != PC_OK) return rc;
   }
-  if (k_self != nullptr) {
-    self = PcRowsToImages{(const uint16_t*)k_self, (const uint16_t*)v_self, nullptr, n_q, n_kv_heads * D,
-                          (long long)n_q * n_kv_heads * D, D, at(w.k_img[2]), at(w.v_img[2])};
-    a.grp[2] = image_group(self.k_img, self.v_img, nullptr, 0, 1, n_q, n_kv_heads, D);
-    a.grp[2].causal = 1;
-  }
-  a.images = 1;
-  const int rc = pc_launch_fp8_images(k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, (long long)batch * n_seg * n_kv_heads, k_t,
-                                      D, base + w.k_img[0], base + w.v_img[0], tail, self, batch, n_kv_heads, st);
-  if (rc != PC_OK) return rc;
   return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
                        base + w.q_rot, (float*)(base + w.part_o), (float*)(base + w.part_lse),
                        w.n_parts, out, lse_out, st);

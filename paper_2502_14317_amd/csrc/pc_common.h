@@ -471,6 +471,9 @@ struct PcRowsToImages {
 int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
                          const int32_t* seg_len, int seg_len_per_head, long long n_segs, int k_t, int head_dim, void* k_img, void* v_img,
                          const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads, hipStream_t st);
+// The segments alone as bf16 rows [n_segs, k_t, D] (those behind a length are not written)
+int pc_launch_fp8_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale, const int32_t* seg_len,
+                       int seg_len_per_head, long long n_segs, int n_kv_heads, int k_t, int head_dim, void* k_rows, void* v_rows, hipStream_t st);
 // Partials of the 8-bit segments, then those of the 16-bit tail (tail_cap > 0)
 int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, const void* v8,
                          const float* k_scale, const float* v_scale, const int32_t* seg_len,
