@@ -33,6 +33,7 @@
 // two A operands.  A segment holds ceil(k_t / 32) blocks of K and of V; keys behind k_t or behind
 // the segment's length carry code 0.
 #include "decode_core.h"
+#include "fp8_quotient.h"
 
 #define PC_D8_WAVES 4
 #define PC_D8_ITER_KEYS 32
@@ -73,8 +74,7 @@ template <bool FAST>
 __device__ __forceinline__ float pc_quotient(float x, const PcQuantScale& s) {
   if (!FAST) return fminf(fmaxf(x / s.scale, -PC_E4M3_MAX), PC_E4M3_MAX);
   x = __builtin_amdgcn_fmed3f(x, -s.limit, s.limit);       // (the quotient of the limit is below 464, still code 448)
-  const float q = x * s.inv;
-  return fmaf(-fmaf(q, s.scale, -x), s.inv, q);
+  return pc_quotient_by_reciprocal(x, s.scale, s.inv);
 }
 template <bool FAST>
 __device__ __forceinline__ uint32_t pc_e4m3x4(float a, float b, float c, float d, const PcQuantScale& s) {
