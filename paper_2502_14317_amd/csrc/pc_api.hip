@@ -889,7 +889,7 @@ extern "C" int pc_layer_forward(const pc_shape* s, const void* q, const void* k,
   const int lo = calibrated ? class_lo : 0, hi = calibrated ? class_hi : 0;
   const int32_t* lens = calibrated ? chunk_lens : nullptr;
   int32_t* cnt = calibrated ? tok_cnt : nullptr;
-  const bool one_select = pc_select_layer_fits(C, sum.per_chunk);
+  const bool small_rows = pc_select_gather_fits(keep_tokens, D), one_select = pc_select_layer_fits(C, sum.per_chunk, small_rows);
   if (one_select) {
     rc = pc_launch_select_layer(sum, C, keep_chunks, tok_score, Hkv, w_ctx, keep_tokens, lambda, lo, hi, lens, chunk_idx,
                                 chunk_top, tok_idx, cnt, k_rope, v, L, D, kc, vc, st);
@@ -899,7 +899,7 @@ extern "C" int pc_layer_forward(const pc_shape* s, const void* q, const void* k,
     if (rc == PC_OK)
       rc = pc_launch_select_tokens(tok_score, chunk_idx, keep_chunks, Hkv, w_ctx, keep_tokens, lambda, lo, hi, lens, tok_idx, cnt, st);
   }
-  if (rc == PC_OK && !(one_select && pc_select_gather_fits(keep_tokens, D)))
+  if (rc == PC_OK && !(one_select && small_rows))
     rc = pc_launch_gather(k_rope, v, chunk_idx, tok_idx, 1, C, L, keep_chunks, Hkv, keep_tokens, D, kc, vc, nullptr, nullptr, st);
   if (rc != PC_OK) return rc;
   const PcFlashArgs local = local_flash_args(s, q, chunk_lens, o, lse, base, w);

@@ -219,9 +219,9 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
 
 // Chunks and tokens in one launch: every workgroup adds up and ranks the chunk scores for itself.  sum: the
 // pass-2 block sums; also written: sum.chunk_score, chunk_idx, chunk_top (nullable).
-bool pc_select_layer_fits(int n_chunks, int per_chunk);
 // (and the gather of [.., rows, H_kv, D] rows where pc_select_gather_fits)
 bool pc_select_gather_fits(int k, int head_dim);
+bool pc_select_layer_fits(int n_chunks, int per_chunk, bool gather);
 int pc_launch_select_layer(const PcChunkSum& sum, int n_chunks, int n_sel, const float* tok_score, int n_kv_heads, int chunk_len,
                            int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* chunk_idx,
                            float* chunk_top, int32_t* out_idx, int32_t* out_cnt, const void* k_src, const void* v_src, int rows,

@@ -137,9 +137,16 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 // A layer's chunk selection in the same launch: every workgroup adds up the chunks' block sums (the order
 // of pc_chunk_sum, a wavefront a chunk, its 4 x 64 strided sums asked for at once), ranks them as
 // select_chunks_kernel does and takes the chunk of its rank; the first workgroup writes scores and ranks.
-// 2 us in front of the tokens instead of a launch of 5 us, for at most 64 chunks of 2048 block sums.
+// Every workgroup reads all the sums, so it pays for few of them only: a chunk costs about 0.1 us, 1000 sums 0.2,
+// against two launches (three with the gather, where the rows of small segments are copied here too).  This / apart
+// (us), chunks x sums, 2048 tokens x 64: 4 x 128 7.1 / 9.7, 16 x 128 8.3 / 10.1, 24 x 320 10.2 / 10.5, 32 x 256 10.8 / 10.5,
+// 64 x 32 13.1 / 11.3, 64 x 2048 39 / 12; with the gather of 128 rows of 64 values 4 x 128 6.7 / 13.3, 32 x 256 10.5 / 12.0,
+// 48 x 256 12.6 / 12.4, 64 x 64 12.8 / 13.0, 64 x 2048 39 / 13.
 #define PC_SEL_CHUNKS 64
 #define PC_SEL_BLOCKS 2048
+#define PC_SEL_CHUNK_COST 400          // a chunk, in sums
+#define PC_SEL_COST 18000              // most that all chunks may cost, in sums
+#define PC_SEL_COST_GATHER 30000       // with the gather
 struct PcSelectChunks {
   PcChunkSum sum;
   int n_chunks;
@@ -406,8 +413,11 @@ int pc_launch_select_tokens(const float* tok_score, const int32_t* chunk_idx, in
                               out_idx, out_cnt, PcSelectChunks{}, PcSelectGather{}, st);
 }
 
-bool pc_select_layer_fits(int n_chunks, int per_chunk) { return n_chunks <= PC_SEL_CHUNKS && per_chunk <= PC_SEL_BLOCKS; }
 bool pc_select_gather_fits(int k, int head_dim) { return 4LL * head_dim * k <= PC_SEL_GATHER; }
+bool pc_select_layer_fits(int n_chunks, int per_chunk, bool gather) {
+  return n_chunks <= PC_SEL_CHUNKS && per_chunk <= PC_SEL_BLOCKS &&
+         n_chunks * (per_chunk + PC_SEL_CHUNK_COST) <= (gather ? PC_SEL_COST_GATHER : PC_SEL_COST);
+}
 int pc_launch_select_layer(const PcChunkSum& sum, int n_chunks, int n_sel, const float* tok_score, int n_kv_heads, int chunk_len,
                            int k, float lambda, int cls_lo, int cls_hi, const int32_t* chunk_lens, int32_t* chunk_idx,
                            float* chunk_top, int32_t* out_idx, int32_t* out_cnt, const void* k_src, const void* v_src, int rows,
