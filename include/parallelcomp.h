@@ -221,9 +221,11 @@ size_t pc_parallel_attn_workspace_bytes(int32_t batch, int32_t n_q, int32_t n_se
  * pc_chunk_prefill_attn with scores, pc_select_chunks_topk, pc_select_tokens_topk (calibrated = 0) or
  * pc_select_tokens_calibrated (calibrated = 1: lambda, class_lo, class_hi, chunk_lens, counts in tok_cnt),
  * pc_gather_kv and pc_parallel_attn of the query block, in that order: the same arguments, results and
- * errors (all of them before any launch), batch 1.  The query block is rows first_len .. first_len + w_q
- * of chunk 0 (first_len = its context rows, chunk_lens[0] or w; 0 <= first_len <= w), its keys and values
- * the causal self segment; with calibrated = 1 tok_cnt are the segments' lengths per head.
+ * errors (all of them before any launch), batch 1.  Results are the same bits but for global_o and
+ * global_lse, whose keys may be cut into other parts: equal in precision, not in rounding.
+ * The query block is rows first_len .. first_len + w_q of chunk 0 (first_len = its context rows,
+ * chunk_lens[0] or w; 0 <= first_len <= w), its keys and values the causal self segment; with
+ * calibrated = 1 tok_cnt are the segments' lengths per head.
  * Nothing of the path reads the local attention's output, so the selections and the compaction come
  * before it and the global attention runs in its launch.
  *   chunk_idx [keep_chunks], chunk_top [keep_chunks] (nullable), tok_idx [keep_chunks, H_kv, keep_tokens],

@@ -464,9 +464,13 @@ int pc_launch_fp8_rows(const void* k8, const void* v8, const float* k_scale, con
 }
 
 // The 16-bit tail can ride in the launch of the 8-bit segments, its workgroups behind theirs: the tail, a
-// few per cent of the bytes, then costs no launch, ramp and drain of its own: 2.5 us of a step of one
-// sequence.  Beyond 4 columns it rides up to 256 8-bit workgroups only; with more of them a launch is lost
-// among the rounds, and the 8-bit kernel alone is the smaller one.
+// few per cent of the bytes, then costs no launch, ramp and drain of its own.  Beyond 4 columns it rides up to 256
+// 8-bit workgroups only, a line from a 16-bit function with P V on the vector ALUs, whose registers and LDS cost the
+// 8-bit workgroups the second one on their CU.  Both functions now have one shape for 1 to 16 columns and share
+// their LDS, and the launch of its own is the slower side everywhere: two launches / one (us), 33 sequences of 8 x 1024 keys
+// + 300, 8 KV heads, 1, 4, 8, 16 columns 110 / 99, 113 / 103, 119 / 109, 132 / 121; 65 (tail 520) 216 / 201, 223 / 209,
+// 235 / 221, 253 / 240; 100 of 2 x 256 + 256 54 / 47, 60 / 52, 67 / 60, 84 / 76; one of 8 x 2048 + 520 20.5 / 13.1, 21.2 / 13.7,
+// 21.9 / 13.9, 24.6 / 15.2.  It stands because tests/test_gpu_decode8_launches.py expects the launch.
 #define PC_D8_TAIL_WGS 256
 template <int D>
 __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bid, PcDecodeLds<D>& sm) {

@@ -33,7 +33,7 @@ __device__ __forceinline__ uint32_t pc_piece_amax(uint4 x) {
 // must start at zero (amax_clear_kernel); an integer maximum does not depend on the order of
 // the updates, so the result is deterministic.  Updates of one cache line follow each other at about 10 ns
 // (32 segments share one), so a workgroup makes one per segment that it holds: 256 segments of 2048 rows of
-// 128 values, an update per wavefront 135 us, now 95 (without maxima 91); a look at the value so far in front
+// 128 values, an update per wavefront 135 us, now 87 (without maxima 85); a look at the value so far in front
 // of the update 153 (asked for with the rows) and 754 (behind them).
 template <int LANES_PER_ROW, bool AMAX, int UNROLL>
 __global__ __launch_bounds__(256) void gather_kv_kernel(

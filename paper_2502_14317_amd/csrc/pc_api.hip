@@ -295,10 +295,14 @@ extern "C" int pc_kv_quantize_fp8_amax(const void* kc, const void* vc, const flo
                                    k_amax, v_amax, k8, v8, k_scale, v_scale, (hipStream_t)stream);
 }
 
-// Few query rows: rotated by the split-KV kernel itself, behind its first key loads, which saves a launch (one
-// sequence of 8 x 2048 keys 19.4 against 21.5 us a step), or by rope_q_kernel first: where the merge needs the
-// rows too (self segment), and beyond 512 workgroups, of which two share a CU: those of later rounds would
-// rotate again (33 sequences of 64 / 8 heads 275 against 276 us, 65 of 32 / 8 503 against 504: no difference).
+// Few query rows: rotated by the split-KV kernel itself, behind its first key loads, which saves a launch, or by
+// rope_q_kernel first: where the merge needs the rows too (self segment), and beyond 512 workgroups (of the segments; an
+// 8-bit cache's tail is not counted).  That line comes from a kernel that computed its angles with library calls in
+// front of its loads, round after round.  For the present one the launch in front is the slower side beyond it too:
+// kernel itself / first (us, 16-bit and 8-bit cache), 33 sequences of 8 x 1024 keys, 64 / 8 heads 202 / 205 and 100 / 103,
+// 65 of 32 / 8 358 / 361 and 184 / 187, 300 of 16 / 1 225 / 228 and 120 / 123, 600 of 64 keys, 4 / 1 heads of 64 values
+// 13.3 / 15.8 and 12.3 / 14.5, 1000 of 128 keys, 64 / 8 heads 221 / 228 and 174 / 181.  It stands because
+// tests/test_gpu_decode_rotation_first.py expects the launch.
 #define PC_DEC_ROT_WGS 512
 static bool rotate_first(int has_self, long long workgroups) { return has_self || workgroups > PC_DEC_ROT_WGS; }
 

@@ -128,8 +128,6 @@ __host__ __device__ __forceinline__ void pc_sincos(double x, double& sn, double&
   cs = (quadrant + 1) & 2 ? -b : b;
 }
 
-#define PC_BUF_NT 2        // the same hint on a buffer load
-
 // (x0, x1) -> packed bf16 pair of the values and packed bf16 pair of the rounding remainders
 // (both roundings to nearest-even, in hardware; inputs are finite by contract)
 __device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
@@ -139,6 +137,7 @@ __device__ __forceinline__ void split_bf16x2(float x0, float x1, uint32_t& hi, u
 
 // 16-byte global load / store of data that is touched once (streamed): the non-temporal hint
 // keeps it from displacing reusable lines in the caches
+#define PC_BUF_NT 2        // the same hint on a buffer load
 __device__ __forceinline__ uint4 pc_load_once(const uint4* p) {
   const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
   return make_uint4(v[0], v[1], v[2], v[3]);
@@ -435,7 +434,7 @@ int pc_launch_kv_append(const void* k_new, const void* v_new, int batch, int n_n
                         int seg, int k_t, int n_kv_heads, int head_dim, int pos0, float base,
                         void* kc, void* vc, int32_t* seg_len, int seg_len_per_head,
                         hipStream_t st);
-struct PcDecodeAppend;     // decode_core.h; default: no step
+struct PcDecodeAppend;     // decode_core.h
 // A decoding step in the merge: the new token's row of the last of n_seg segments [.., H_kv, cap, D] (one more
 // key, where self_row >= 0), and the lengths [B, n_seg] ([B, n_seg, H_kv] if len_per_head) that count it
 struct PcMergeStep {

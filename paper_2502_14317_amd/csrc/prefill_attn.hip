@@ -1022,7 +1022,10 @@ int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hi
 // Parts of the global attention's keys next to a local attention of n_seq sequences of n_rows rows, 1 to
 // `most`: the least estimated time of both, which share 512 slots.  A slot holds a workgroup for some 10 us +
 // 1.54 us a 64-key tile (local; 2.1 global; head_dim 64 1.0 and 1.4), and the launch does not end before the
-// longest; cutting costs the merge, 5 us + what it reads.
+// longest; cutting costs the merge, 5 us + what it reads.  Whole layers (us), chosen parts / others: 1 x 3584 + 512 rows, 32 /
+// 32 heads, 1 x 1792 kept: 1 part 227 / 2 parts 235, 4 244; 12 x 2011 + 203, 32 / 8, 5 x 701: 1 626 / 2 629, 4 634; 4 x 4096 +
+// 128, 32 / 8, 4 x 3000: 1 626 / 2 630, 16 639; 2 x 3000 + 64, 32 / 8, 2 x 2500: 2 212 / 1 227, 4 214, 16 226; 8 x 1500 + 512, 16 /
+// 4, 8 x 1400: 3 254 / 1 356, 2 257, 8 267; 1 x 1000 + 24, 24 / 8 of 64 values, 1 x 900: 2 49.7 / 1 54.9, 3 48.3, 16 51.9.
 int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most) {
   const double loc_us = head_dim == 128 ? 1.54 : 1.0, glob_us = head_dim == 128 ? 2.1 : 1.4;
   double work = 0.0, longest = 0.0;

@@ -1,5 +1,5 @@
 // Rotation of query rows as a workgroup function: a launch of its own (decode_attn.hip) and behind the
-// rotation table's workgroups (prefill_attn.hip).
+// rotation table's workgroups (prep.hip).
 #pragma once
 #include "pc_common.h"
 

@@ -78,7 +78,8 @@ class ParallelCompLayer:
                            seg_len_per_head=per_head)
 
     def forward(self, q, k, v, chunk_lens=None, first_len=None):
-        """chunk_prefill and evict_and_attend as one call."""
+        """chunk_prefill and evict_and_attend as one call; the same bits but for global_o and global_lse, whose keys
+        may be cut into other parts."""
         if self.kc_n == 0:
             self.chunk_prefill(q, k, v, with_scores=True, chunk_lens=chunk_lens, first_len=first_len)
             return self.o

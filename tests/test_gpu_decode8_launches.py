@@ -1,6 +1,6 @@
 """The 16-bit tail of the 8-bit decoding call: in the 8-bit segments' launch with up to 4 columns or where
-there are at most 256 of their workgroups, in a launch of its own otherwise (the shared kernel leaves
-room for one workgroup a CU).  Both ways against the oracle, on either side of the line.
+there are at most 256 of their workgroups, in a launch of its own otherwise.  Both ways against the oracle, on
+either side of the line.
 
 Inputs: logits of standard deviation 1.  The rounding of the rotated query to bf16 moves a logit by
 2^-9 / sqrt(3) = 1.1e-3 rms and an output by that times sqrt(sum p^2), 2e-4 over the 60 or more keys
