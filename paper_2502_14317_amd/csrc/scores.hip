@@ -35,6 +35,7 @@
 // (scores_many_kernel): 128 keys are staged once and stay in LDS, the columns stream by.
 #include "pc_common.h"
 #include <math.h>
+#include <type_traits>
 
 #define PC_SC_THREADS 256
 #define PC_SC_WAVES 4
@@ -449,7 +450,13 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
 // 128 columns.  Here a workgroup stages its 128 keys (hi and lo, 68 KiB) once and the columns
 // stream by: a wavefront takes every fourth column block and reads it as ready MFMA operands
 // (split once, in prep.hip) while the block before is multiplied.  No barrier and no
-// conversion in the loop: bound by the matrix cores (96 MFMAs a block) and 64 exponentials a lane.
+// conversion in the loop: bound by the matrix cores (96 MFMAs a block, 1.25 PFLOP/s where the chip is full) and, next
+// to them, 64 exponentials a lane.  A product (32 keys x 32 columns) is a run of slices that the compiler may not mix:
+// a k-step's three MFMAs, the LDS reads for three k-steps later, a share of the exponentials of the product before.
+// Left to itself it waited for every operand read in front of its MFMA and put the exponentials behind the product.
+// Compiler's order -> slices, the passes alone (us): 4 chunks of 2011 rows, 203 voting, 32 / 8 heads 77 + 57 -> 67 + 46,
+// 12 138 + 125 -> 128 + 110, 16 x 7680, 512 voting 1460 + 1371 -> 1397 + 1293.  Minus the logsumexp as the products'
+// C operand (no subtraction in front of the exponentials) was 7 % faster in pass 2, at 0.2 % more error: not taken.
 // Measured, every query row voting, pass 1 with the pre-pass + pass 2, before (rounds of 128
 // columns over re-staged keys) and now: 12 ragged chunks of 2011 rows, 203 rows voting, 32 / 8 heads
 // 324 + 305 -> 215 + 154 us; 16 x 7680, 512 voting 2052 + 2081 -> 1487 + 1281; 36 x 3584, 32 / 32
@@ -469,19 +476,30 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   const int key_end = PASS == 1 ? ctx_len + (a.L - a.w) : ctx_len;
   const bool pre = PASS == 1 && a.v_img != nullptr;
   const long long cg = (long long)c * a.n_kv_heads + g;
-  const bool unmasked = key0 + TILE - 1 <= first_obs;      // every key is visible to every voting row
+  // every key that counts here is visible to every voting row (pass 2 drops what lies behind the context rows)
+  const bool unmasked = (PASS == 1 ? key0 + TILE : min(key0 + TILE, ctx_len)) - 1 <= first_obs;
   const int n_sub = min(NSUB, (key_end - key0 + 31) / 32); // (<= 0: nobody looks at these keys)
   float tok[NSUB];
 #pragma unroll
   for (int kq = 0; kq < NSUB; ++kq) tok[kq] = 0.f;
 
-  bf16x8 q[2][2 * KS];                                     // this column block and the next: hi, lo
-  auto load_q = [&](bf16x8(&x)[2 * KS], int cb) __attribute__((always_inline)) {
-    const uint16_t* src = a.q_split + ((cg * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane) * 8;
+  bf16x8 q[2 * KS];                                        // a column block: hi, lo
+  auto q_of = [&](int cb) __attribute__((always_inline)) { return a.q_split + ((cg * a.n_cb + cb) * (2 * KS) * PC_WAVE + lane) * 8; };
+  auto load_q = [&](const uint16_t* src) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i) x[i] = *(const bf16x8*)(src + i * PC_WAVE * 8);
+    for (int i = 0; i < 2 * KS; ++i) q[i] = *(const bf16x8*)(src + i * PC_WAVE * 8);
   };
-  if (wave < a.n_cb) load_q(q[0], wave);                   // in flight while the keys are staged
+  // pass 2: the logsumexp of the rows of the column block that the arithmetic is at, and of the next one
+  floatx16 lse, lse_next;
+  auto load_lse = [&](floatx16& x, int cb) __attribute__((always_inline)) {
+    const float* src = a.lse2 + cg * (32 * a.n_cb) + 32 * cb + 4 * hf;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = *(const float4*)(src + 8 * i);
+      x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+    }
+  };
+  if (wave < a.n_cb) load_q(q_of(wave));                   // in flight while the keys are staged
   if (key0 < (pre ? a.L : key_end)) {
     PcKeyStage<D, TILE, PASS == 1> keys;
     keys.begin(a, tid, key0, pre);
@@ -490,92 +508,172 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   }
   __syncthreads();
 
-  auto block = [&](const bf16x8(&x)[2 * KS], int cb) __attribute__((always_inline)) {
-    float m_run = -INFINITY, l_run = 0.f;
-    const int col = min(32 * cb + n, a.n_cols - 1), my_qrow = first_obs + col % a.w_obs;
-    float lse_r[16];
-    if (PASS == 2) {
-      const float* lse2 = a.lse2 + cg * (32 * a.n_cb) + 32 * cb + 4 * hf;
+  // The products of a wavefront, NSUB of them a column block, one after the other; the K operands go round a ring that
+  // is read AHEAD k-steps before its use (behind a product's last ones the next product's)
+  constexpr int RING = 4, AHEAD = 3;
+  static_assert(KS % RING == 0, "k-steps go round the operand ring");
+  bf16x8 ring[RING][2];                                    // hi, lo
+  floatx16 s_buf[2];
+  int k_at = n * KSTRIDE + 8 * hf;                         // opaque in the loops: the reads stay where they are written
+  auto opaque_at = [&]() __attribute__((always_inline)) { asm volatile("" : "+v"(k_at)); };
+  auto read_k = [&](int kq, int ks) __attribute__((always_inline)) {
+    ring[ks % RING][0] = *(const bf16x8*)(k_hi + k_at + 32 * kq * KSTRIDE + 16 * ks);
+    ring[ks % RING][1] = *(const bf16x8*)(k_lo + k_at + 32 * kq * KSTRIDE + 16 * ks);
+  };
+  constexpr int MAX_SL = KS / 4;                           // slices of pass 1 that take the maxima
+  float m_run = -INFINITY, l_run = 0.f;                    // pass 1: of the column block that the arithmetic is at
+  // the last key that the voting row of the lane's column sees, counted as the lane's registers are
+  auto last_key_of = [&](int cb) __attribute__((always_inline)) {
+    return first_obs + min(32 * cb + n, a.n_cols - 1) % a.w_obs - key0 - 4 * hf;
+  };
+  // A product's arithmetic in KS shares: s holds product kq of a column block (MASK: keys behind last_key are hidden,
+  // pass 1 only).
+  auto arith = [&](auto mask_tag, int share, floatx16& s, int kq, int last_key, float& top, float& sum) __attribute__((always_inline)) {
+    constexpr bool MASK = decltype(mask_tag)::value;
+    if (PASS == 1) {
+      if (share < MAX_SL) {
+        if (share == 0) {
+          top = m_run;
+          if (MASK) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 v = *(const float4*)(lse2 + 8 * i);
-        lse_r[4 * i] = v.x; lse_r[4 * i + 1] = v.y; lse_r[4 * i + 2] = v.z; lse_r[4 * i + 3] = v.w;
-      }
-    }
-#pragma unroll
-    for (int kq = 0; kq < NSUB; ++kq) {
-      if (kq >= n_sub) break;
-      floatx16 s;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = 0.f;
-      const uint16_t* ph = k_hi + (32 * kq + n) * KSTRIDE + 8 * hf;
-      const uint16_t* pl = k_lo + (32 * kq + n) * KSTRIDE + 8 * hf;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 kh = *(const bf16x8*)(ph + 16 * ks);
-        const bf16x8 kl = *(const bf16x8*)(pl + 16 * ks);
-        if (PASS == 1) {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, x[ks], s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, x[KS + ks], s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, x[ks], s, 0, 0, 0);
-        } else {
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks], kl, s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[KS + ks], kh, s, 0, 0, 0);
-          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[ks], kh, s, 0, 0, 0);
-        }
-      }
-      if (PASS == 1) {
-        if (!unmasked) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (key0 + 32 * kq + 8 * (r / 4) + 4 * hf + (r % 4) > my_qrow) s[r] = -INFINITY;
-        }
-        float m_new = m_run;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) m_new = fmaxf(m_new, s[r]);
-        if (m_new > -INFINITY) {
-          float sum = 0.f;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - m_new);
-          l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + sum;
-          m_run = m_new;
-        }
-      } else {
-        float sum = 0.f;
-        if (unmasked) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-        } else {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-            const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
-            sum += (key0 + 32 * kq + n <= first_obs + cc % a.w_obs) ? p : 0.f;
+            for (int r = 0; r < 16; ++r)
+              if (32 * kq + 8 * (r / 4) + (r % 4) > last_key) s[r] = -INFINITY;
           }
         }
-        tok[kq] += sum;
+#pragma unroll
+        for (int i = 0; i < 16 / MAX_SL; ++i) top = fmaxf(top, s[share * (16 / MAX_SL) + i]);
+        asm volatile("" : "+v"(top));
+        if (share == MAX_SL - 1) {                         // (no key seen yet: any finite reference does)
+          const float ref = top > -INFINITY ? top : 0.f;
+          l_run *= __builtin_amdgcn_exp2f(m_run - ref);
+          m_run = top; top = ref;
+          asm volatile("" : "+v"(l_run));
+        }
+      } else {
+        constexpr int SL = KS - MAX_SL;
+        const int i = share - MAX_SL;
+        if (i == 0) sum = 0.f;
+#pragma unroll
+        for (int r = 16 * i / SL; r < 16 * (i + 1) / SL; ++r) sum += __builtin_amdgcn_exp2f(s[r] - top);
+        asm volatile("" : "+v"(sum));
+        if (share == KS - 1) l_run += sum;
       }
-    }
-    if (PASS == 1) {
-      // the lane halves hold disjoint keys of the same column
-      const float m_o = __shfl_xor(m_run, 32), l_o = __shfl_xor(l_run, 32);
-      const float M = fmaxf(m_run, m_o);
-      float l = 0.f;
-      if (l_run > 0.f) l += l_run * exp2f(m_run - M);
-      if (l_o > 0.f) l += l_o * exp2f(m_o - M);
-      if (hf == 0 && 32 * cb + n < a.n_cols)
-        a.ml[(cg * a.n_kb + kblock) * a.n_cols + 32 * cb + n] = make_float2(M, l);
+    } else {
+      if (share == 0) sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16 / KS; ++i) sum += __builtin_amdgcn_exp2f(s[share * (16 / KS) + i] - lse[share * (16 / KS) + i]);
+      asm volatile("" : "+v"(sum));
+      if (share == KS - 1) tok[kq] += sum;
     }
   };
-  if (PASS == 1 || n_sub > 0) {
-#pragma unroll 1
-    for (int cb = wave; cb < a.n_cb; cb += 2 * PC_SC_WAVES) {
-      if (cb + PC_SC_WAVES < a.n_cb) load_q(q[1], cb + PC_SC_WAVES);
-      block(q[0], cb);
-      if (cb + PC_SC_WAVES >= a.n_cb) break;
-      if (cb + 2 * PC_SC_WAVES < a.n_cb) load_q(q[0], cb + 2 * PC_SC_WAVES);
-      block(q[1], cb + PC_SC_WAVES);
+  // pass 1: a column block's (max, sum) over this block of keys; the lane halves hold disjoint keys of the same column
+  auto leave = [&](int cb) __attribute__((always_inline)) {
+    const float M = pc_xhalf_max(m_run);
+    const float l = pc_xhalf_sum(l_run != 0.f ? l_run * __builtin_amdgcn_exp2f(m_run - M) : 0.f);
+    if (hf == 0 && 32 * cb + n < a.n_cols)
+      a.ml[(cg * a.n_kb + kblock) * a.n_cols + 32 * cb + n] = make_float2(M, l);
+    m_run = -INFINITY; l_run = 0.f;
+  };
+  auto product = [&](const bf16x8& cols, const bf16x8& keys, const floatx16& c) __attribute__((always_inline)) {
+    return PASS == 1 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(keys, cols, c, 0, 0, 0)     // rows = keys, columns = voting rows
+                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols, keys, c, 0, 0, 0);    // rows = voting rows, columns = keys
+  };
+  // Column block cb, and the last product's arithmetic of the block before it.  Behind its last use in the block an
+  // operand makes room for the next block's: seven k-steps before that needs it.
+  auto block = [&](auto mask_tag, int cb) __attribute__((always_inline)) {
+    constexpr bool MASK = decltype(mask_tag)::value;
+    int last_key = MASK ? last_key_of(max(cb - PC_SC_WAVES, 0)) : 0;
+    const int next = min(cb + PC_SC_WAVES, a.n_cb - 1);
+    const uint16_t* src = q_of(next);
+    opaque_at();
+    static_assert(NSUB % 2 == 0, "products take turns in s_buf");
+#pragma unroll
+    for (int kq = 0; kq < NSUB; ++kq) {
+      floatx16& s = s_buf[kq % 2];
+      float top = 0.f, sum = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 kh = ring[ks % RING][0], kl = ring[ks % RING][1];
+        if (ks == 0) {
+          floatx16 zero;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+          s = product(q[ks], kl, zero);
+        } else {
+          s = product(q[ks], kl, s);
+        }
+        if (PASS == 2 && kq == 0 && ks == 0) load_lse(lse_next, cb);
+        const int to = ks + AHEAD;
+        if (to < KS) read_k(kq, to); else read_k((kq + 1) % NSUB, to - KS);
+        s = product(q[KS + ks], kh, s);
+        if (ks > 0) arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, last_key, top, sum);
+        s = product(q[ks], kh, s);
+        if (ks == 0) {                                     // (the product before is through by then)
+          __builtin_amdgcn_sched_barrier(0);
+          arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, last_key, top, sum);
+        }
+        if (kq == NSUB - 1) {
+          q[ks] = *(const bf16x8*)(src + ks * PC_WAVE * 8);
+          q[KS + ks] = *(const bf16x8*)(src + (KS + ks) * PC_WAVE * 8);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (PASS == 2 && kq == 0) lse = lse_next;
+      if (PASS == 1 && kq == 0) {
+        if (cb >= PC_SC_WAVES) leave(cb - PC_SC_WAVES);
+        m_run = -INFINITY; l_run = 0.f;
+        if (MASK) last_key = last_key_of(cb);
+      }
     }
+  };
+  auto blocks = [&](auto mask_tag) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < AHEAD; ++ks) read_k(0, ks);
+    // nothing before the first block: exponents that add nothing (pass 1: a sum that is dropped)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { s_buf[1][r] = 0.f; lse[r] = INFINITY; }
+    int cb = wave;
+#pragma unroll 1
+    for (; cb < a.n_cb; cb += PC_SC_WAVES) block(mask_tag, cb);
+    float top = 0.f, sum = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) arith(mask_tag, ks, s_buf[1], NSUB - 1, last_key_of(cb - PC_SC_WAVES), top, sum);
+    if (PASS == 1) leave(cb - PC_SC_WAVES);
+  };
+  if (wave < a.n_cb && n_sub > 0) {
+    if (unmasked) {
+      blocks(std::false_type{});
+    } else if (PASS == 1) {
+      blocks(std::true_type{});
+    } else {
+      // voting rows among the context rows (more of them than query rows): product after product
+#pragma unroll 1
+      for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) {
+        load_q(q_of(cb));
+        load_lse(lse, cb);
+#pragma unroll
+        for (int kq = 0; kq < NSUB; ++kq) {
+          floatx16 s;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[r] = 0.f;
+          opaque_at();
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            read_k(kq, ks);
+            s = product(q[ks], ring[ks % RING][1], s);
+            s = product(q[KS + ks], ring[ks % RING][0], s);
+            s = product(q[ks], ring[ks % RING][0], s);
+          }
+#pragma unroll 1
+          for (int r = 0; r < 16; ++r) {
+            const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
+            if (key0 + 32 * kq + n <= first_obs + cc % a.w_obs) tok[kq] += __builtin_amdgcn_exp2f(s[r] - lse[r]);
+          }
+        }
+      }
+    }
+  } else if (PASS == 1) {
+    for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) leave(cb);     // nobody looks at these keys
   }
 
   if (PASS == 2) {
