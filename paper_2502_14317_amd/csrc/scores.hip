@@ -47,6 +47,13 @@
 #define PC_SC_KB_MANY 128   // keys per workgroup with more than 4 column blocks; half where that leaves CUs idle
 #define PC_SC_LSE_BLOCKS 64 // up to this many blocks of pass 1, pass 2 combines their (max, sum) itself
 #define PC_SC_LOG2E 1.4426950408889634f
+// orders a wavefront's own LDS writes and reads (no other wavefront involved)
+#define PC_SC_WAVE_LDS_SYNC()                                \
+  do {                                                       \
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   \
+    __builtin_amdgcn_wave_barrier();                         \
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");   \
+  } while (0)
 
 struct PcScoreArgs {
   const uint16_t* k;       // [C, L, H_kv, D] before RoPE
@@ -74,12 +81,16 @@ struct PcScoreArgs {
 // RP rows from item to item (one complex multiplication per pair in fp32, at most kb_keys / RP - 1
 // <= 31 in a chain: ~1e-7 relative per link).
 // PRE: pass 1, which also carries the pre-pass duties where they are wanted (`pre`).
-template <int D, int TILE, bool PRE>
+// OWN (tiles of 128): a wavefront's 32 rows of the tile lie side by side in LDS, 32 wave .. + 31, where it alone reads them:
+// local row m is row RP (m / RW) + RW wave + m % RW of the tile.  Otherwise a row lies at its place.
+template <int D, int TILE, bool PRE, bool OWN = false>
 struct PcKeyStage {
   static constexpr int HALF = D / 2, KSTRIDE = D + 8;
   static constexpr int ITEMS = TILE * (HALF / 8) / PC_SC_THREADS;      // per thread and tile
   static constexpr int RP = PC_SC_THREADS / (HALF / 8);                // rows between a thread's items
+  static constexpr int RW = PC_WAVE / (HALF / 8);                      // rows of a wavefront's item
   static_assert(ITEMS >= 1 && TILE * (HALF / 8) % PC_SC_THREADS == 0, "tile / thread mismatch");
+  static_assert(!OWN || RW * ITEMS == 32, "32 rows a wavefront");
   // V: a thread takes 8 consecutive keys x 4 values (eight 8-byte loads), transposes them in
   // registers and stores four 16-byte granules of the V^T image, (8 keys, d) each
   static constexpr int V_ALL = (TILE / 8) * (D / 4);                   // such items per tile
@@ -168,10 +179,11 @@ struct PcKeyStage {
         split_bf16x2(x1l * c0.x - x2l * c0.y, x1h * c1.x - x2h * c1.y, h1[e], l1[e]);
         split_bf16x2(x2l * c0.x + x1l * c0.y, x2h * c1.x + x1h * c1.y, h2[e], l2[e]);
       }
-      *(uint4*)(k_hi + r * KSTRIDE + i0) = make_uint4(h1[0], h1[1], h1[2], h1[3]);
-      *(uint4*)(k_lo + r * KSTRIDE + i0) = make_uint4(l1[0], l1[1], l1[2], l1[3]);
-      *(uint4*)(k_hi + r * KSTRIDE + HALF + i0) = make_uint4(h2[0], h2[1], h2[2], h2[3]);
-      *(uint4*)(k_lo + r * KSTRIDE + HALF + i0) = make_uint4(l2[0], l2[1], l2[2], l2[3]);
+      const int at = (OWN ? 32 * (tid / PC_WAVE) + RW * u + tid % PC_WAVE / (HALF / 8) : r) * KSTRIDE + i0;
+      *(uint4*)(k_hi + at) = make_uint4(h1[0], h1[1], h1[2], h1[3]);
+      *(uint4*)(k_lo + at) = make_uint4(l1[0], l1[1], l1[2], l1[3]);
+      *(uint4*)(k_hi + at + HALF) = make_uint4(h2[0], h2[1], h2[2], h2[3]);
+      *(uint4*)(k_lo + at + HALF) = make_uint4(l2[0], l2[1], l2[2], l2[3]);
       if (pre) {
         // the hi halves are the rotated key rounded to bf16: the cache row and its K image granules
         const int row = key0 + r;
@@ -213,7 +225,12 @@ __device__ __forceinline__ int score_head(const PcScoreArgs& a) {
 // heads x 32 voting rows) a wavefront owns a column block and takes both 32-key halves of every
 // 64-key tile (WPC = 1).  With fewer column blocks the wavefronts of a block share its keys
 // instead of idling: WPC = 2 splits the halves of a 64-key tile, WPC = 4 (one column block, e.g.
-// MHA with 32 voting rows) the four 32-key quarters of a 128-key tile.
+// MHA with 32 voting rows) the four 32-key quarters of a 128-key tile.  Pass 2 is bound by its vector instructions at two
+// wavefronts a SIMD (one wavefront issues one about every 5 cycles): without a barrier between staging and products,
+// with the voting rows' positions computed for masked tiles only and twice the keys a workgroup, WPC = 4 takes 330 ->
+// 272 us at 36 x 3584 keys of 32 heads, 19.5 -> 16.7 at 1 x 3584, 6.8 -> 6.0 at 4 x 512 keys of 8 heads of 64 values.
+// (The staging of the next tile between the MFMAs of this one: 283, 17.6 and 5.3.  Pass 1 without the barriers 1189 ->
+// 1203.)
 template <int D, int PASS, int WPC>
 __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a) {
   // The pre-pass duties ride on pass 1 and are switched at run time (a.v_img != nullptr), so the
@@ -223,8 +240,11 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   constexpr int NSUB = TILE / 32;                                // 32-key sub-blocks per tile
   __shared__ __attribute__((aligned(16))) uint16_t k_hi[TILE * KSTRIDE];
   __shared__ __attribute__((aligned(16))) uint16_t k_lo[TILE * KSTRIDE];
-  constexpr int KB_CAP = WPC == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;   // LDS: two workgroups per CU
-  __shared__ float tok_part[PC_SC_WAVES][PASS == 2 ? KB_CAP : 1];
+  // pass 2 with four wavefronts a column block: each stages the 32 keys that it takes itself, so that none waits for
+  // another, and a key's sum has one owner
+  constexpr bool OWN = WPC == 4 && PASS == 2;
+  constexpr int TOK_ROWS = OWN ? 1 : PC_SC_WAVES;
+  __shared__ float tok_part[TOK_ROWS][PASS == 2 ? PC_SC_KB_MAX : 1];
   __shared__ float2 ml_part[PC_SC_WAVES][32];
 
   const int c = score_chunk(a), g = score_head(a), kblock = blockIdx.y;
@@ -238,7 +258,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   const float* lse2 = a.lse2 + ((long long)c * a.n_kv_heads + g) * (32 * a.n_cb);
 
   // pass 2: every wavefront accumulates its columns' share of the keys' sums in its own LDS row
-  if (PASS == 2)
+  if (PASS == 2 && !OWN)
     for (int i = lane; i < a.kb_keys; i += PC_WAVE) tok_part[wave][i] = 0.f;
 
   const int kb0 = wave % WPC;                      // this wavefront's first sub-block of a tile
@@ -263,7 +283,8 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   const bool pre = PASS == 1 && a.v_img != nullptr;
   const int key_end = PASS == 1 ? ctx_len + (a.L - a.w) : ctx_len;
   const int stage_end = pre ? a.L : key_end;
-  PcKeyStage<D, TILE, PASS == 1> keys;
+  typedef PcKeyStage<D, TILE, PASS == 1, OWN> Stage;
+  Stage keys;
   keys.begin(a, tid, kblock * a.kb_keys, pre);
   if (kblock * a.kb_keys < stage_end) keys.fetch(a, c, g, kblock * a.kb_keys);
 
@@ -271,7 +292,6 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   // blocks, every wavefront combines its columns' (max, sum) itself, while its first keys are on
   // their way: a lane half takes every other block.
   float lse_r[16];
-  int qrow_r[16];
   if (PASS == 2) {
     float lse = INFINITY;                                  // column 32 cb + n; exp2(-inf) = 0 for padding columns
     const int my_col = 32 * cb + n;
@@ -304,9 +324,8 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int in_cb = 8 * (r / 4) + 4 * hf + (r % 4), cc = 32 * cb + in_cb;
+      const int in_cb = 8 * (r / 4) + 4 * hf + (r % 4);
       lse_r[r] = __shfl(lse, in_cb);
-      qrow_r[r] = active && cc < a.n_cols ? first_obs + cc % a.w_obs : -1;
     }
   }
 
@@ -316,9 +335,11 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   for (int t = 0; t < n_tiles; ++t) {
     const int key0 = kblock * a.kb_keys + t * TILE;
     if (key0 >= stage_end) break;                         // uniform over the workgroup
-    __syncthreads();                                      // previous tile fully consumed
+    // (a thread's angles go on for 16 tiles' items, 15 links of a chain, then they are read anew)
+    if (OWN && t > 0 && t % (PC_SC_KB_MAX / 2 / TILE) == 0) keys.begin(a, tid, key0, pre);
+    if (OWN) PC_SC_WAVE_LDS_SYNC(); else __syncthreads(); // previous tile fully consumed
     keys.stage(a, c, g, key0, k_hi, k_lo);
-    __syncthreads();
+    if (OWN) PC_SC_WAVE_LDS_SYNC(); else __syncthreads();
     if (t + 1 < n_tiles && key0 + TILE < stage_end) keys.fetch(a, c, g, key0 + TILE);
     if (!active || key0 >= key_end) continue;
     // every key of the tile is visible to every voting row: no causal mask (all but the last
@@ -355,7 +376,8 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
         } else {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int key = key0 + 32 * kb + 8 * (r / 4) + 4 * hf + (r % 4);
+            const int m = 8 * (r / 4) + 4 * hf + (r % 4);
+            const int key = key0 + (OWN ? Stage::RP * (m / Stage::RW) + Stage::RW * wave + m % Stage::RW : 32 * kb + m);
             sv[r] = (key <= my_qrow) ? s[r] : -INFINITY;
             tmax = fmaxf(tmax, sv[r]);
           }
@@ -369,7 +391,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
           m_run = m_new;
         }
       } else {
-        const int key = key0 + 32 * kb + n;
+        const int in_tile = OWN ? Stage::RP * (n / Stage::RW) + Stage::RW * wave + n % Stage::RW : 32 * kb + n, key = key0 + in_tile;
         float sum = 0.f;
         if (unmasked) {       // padding columns carry lse = +inf: their p is 0 without a mask
 #pragma unroll
@@ -377,12 +399,15 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
         } else {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
+            const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
             const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-            sum += (key <= qrow_r[r]) ? p : 0.f;
+            sum += (cc < a.n_cols && key <= first_obs + cc % a.w_obs) ? p : 0.f;
           }
         }
         sum += __shfl_xor(sum, 32);
-        if (hf == 0) tok_part[wave][t * TILE + 32 * kb + n] += sum;
+        if (hf == 0) {
+          if (OWN) tok_part[0][t * TILE + in_tile] = sum; else tok_part[wave][t * TILE + in_tile] += sum;
+        }
       }
     }
   }
@@ -423,7 +448,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
       if (key < a.w) {
         float x = 0.f;
 #pragma unroll
-        for (int wv = 0; wv < PC_SC_WAVES; ++wv) x += tok_part[wv][i];
+        for (int wv = 0; wv < TOK_ROWS; ++wv) x += tok_part[wv][i];
         x = key < ctx_len ? x : 0.f;
         a.tok_score[((long long)c * a.n_kv_heads + g) * a.w + key] = x;
         blk += x;
@@ -839,7 +864,12 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
   const int kb_cap = wpc == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;
   while (!many && a.kb_keys >= PC_SC_KB && a.kb_keys < kb_cap && key_blocks(s, 2 * a.kb_keys) >= 512) a.kb_keys *= 2;
   a.n_kb = (a.L + a.kb_keys - 1) / a.kb_keys;
-  const int n_kb2 = (a.w + a.kb_keys - 1) / a.kb_keys;       // pass 2 looks at context keys only
+  // pass 2 looks at context keys only, in blocks of equal size.  A key's sum has one owner where four wavefronts share a
+  // column block: its blocks have room for twice as many keys (36 x 3584 keys of 32 KV heads, 512 / 1024 keys: 300 / 272 us)
+  int kb2 = a.kb_keys;
+  if (wpc == 4 && kb2 == kb_cap && key_blocks(s, 2 * kb2) >= 512) kb2 *= 2;
+  const int n_kb2 = (a.w + kb2 - 1) / kb2, tile2 = wpc == 4 ? 2 * PC_SC_TILE : PC_SC_TILE;
+  if (!many) kb2 = ((a.w + n_kb2 - 1) / n_kb2 + tile2 - 1) / tile2 * tile2;
   if (a.n_kb > 65535 || s->n_kv_heads > 65535) return PC_ERR_SHAPE;   // grid limits
   // heads fastest: neighbouring workgroups read neighbouring rows of a token, and an XCD (workgroups go round the
   // eight) gets every chunk, whatever the chunks' lengths.  Chunks fastest -> heads fastest (us): pass 1 of
@@ -863,6 +893,7 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
     hipLaunchKernelGGL(scores_lse_kernel, dim3(s->n_chunks * s->n_kv_heads, (32 * a.n_cb + 127) / 128),
                        dim3(128), 0, st, a.ml, a.lse2, a.n_kb, a.n_cols, 32 * a.n_cb);
   }
+  a.kb_keys = kb2;
   {
     PcProfScope prof(PC_KERNEL_SCORES_P2, st);
     if (s->head_dim == 128) launch_scores_pass<128, 2>(wpc, grid2, block, st, a);
