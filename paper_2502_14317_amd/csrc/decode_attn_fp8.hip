@@ -516,6 +516,7 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   };
   auto next = [&](const Cursor& c) { return place(pc_blocks_next(lens, c.at)); };
 
+  const int first_lens = pc_first_lens(lens, lane);
   PcColumnRotation<D> rot;
   rot.begin(a.query, b, g, G, n_cols);
   // B operand: column c16 = (t, head-in-group); k-step j of lane group kk covers
@@ -593,7 +594,7 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   };
 
   // three register buffers: the loads of two blocks (2 x 8 KiB per wavefront) stay in flight
-  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane));
+  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
   Cursor c1 = next(c0);
   issue_loads(0, c0);
   issue_loads(1, c1);

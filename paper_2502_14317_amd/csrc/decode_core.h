@@ -25,6 +25,7 @@ struct PcColumnRotation {
   int i, n0;                                                // the thread's rotation pair, its first column
   uint32_t a, b;
   __device__ __forceinline__ const uint16_t* row(const PcDecodeQuery& x, int seq, int g, int G, int n) const {
+    if (x.n_q == 1) return x.q + ((long long)seq * x.n_q_heads + g * G + n) * D;
     return x.q + (((long long)seq * x.n_q + n / G) * x.n_q_heads + g * G + n % G) * D;
   }
   __device__ __forceinline__ void begin(const PcDecodeQuery& x, int seq, int g, int G, int n_cols) {
@@ -187,8 +188,13 @@ __device__ __forceinline__ void pc_decode_softmax(const floatx4 (&acc)[2], float
 
 // One workgroup (PC_DEC_WAVES wavefronts) of the split-KV attention, number `bid` of batch * H_kv *
 // parts_grid.  Both products on the 16x16x32 MFMA, S^T = K Q^T and O^T += V^T P^T, with the query columns on
-// the N side, so that a lane owns one column throughout.  V arrives row-major, 8 bytes a lane (4 values of
-// a key): eight keys of a lane, transposed by byte permutes, are four operands, of the values 64 c + 4 m + e.
+// the N side, so that a lane owns one column throughout.  V arrives row-major, D / 16 values of a key a lane, 16
+// lanes a row, four whole rows an instruction: eight keys of a lane, transposed by byte permutes, are D / 16 operands,
+// operand e of the values D / 16 m + e.  A workgroup of few blocks spends a sixth of its time issuing its first loads, so
+// there are as few as the bytes allow (16 of V in 8-byte pieces, two half rows each, now 8), and the segments' lengths,
+// which the first key's place needs, are asked for in front of the query: one sequence of 8 x 2048 keys and a tail of
+// 520, 8 KV heads, 15.0 -> 14.2 us; 16 sequences are bound by memory, 603 and 602.  A third and a fourth block in
+// flight 16.5 and 17.0, K in contiguous KiB an instruction 13.6 but 637 for the 16.
 // The lane's keys are those whose probabilities it holds, so P goes from the logit registers into the
 // operand, as two bf16 halves (hi + lo), two MFMAs a block of V: 2^-17 relative where an fp32 operand had 2^-24.  The
 // sum of the row takes P in fp32.  Outputs are rounded to bf16 (2^-9), so theirs is the error that shows: 3.3e-3 to
@@ -199,7 +205,8 @@ __device__ __forceinline__ void pc_decode_softmax(const floatx4 (&acc)[2], float
 template <int D>
 __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int bid, PcDecodeLds<D>& sm) {
   constexpr int KSTEPS = D / 32;            // MFMA k-steps over the head dimension
-  constexpr int NC = D / 64;                // 8-byte pieces a lane takes of a V row
+  constexpr int VE = D / 16;                // values a lane takes of a V row, VE m .. of lane m: 16 (8) bytes
+  typedef uint32_t vpiece __attribute__((ext_vector_type(VE / 2)));
   constexpr int KBLK = PC_DEC_ITER_KEYS / 16;
 
   const int G = a.n_q_heads / a.n_kv_heads;
@@ -229,6 +236,7 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   };
   auto next = [&](const Cursor& c) { return place(pc_blocks_next(lens, c.at)); };
 
+  const int first_lens = pc_first_lens(lens, lane);
   PcColumnRotation<D> rot;
   rot.begin(a.query, b, g, G, n_cols);
   // the group's last workgroup also stores the new token: nobody reads its row in this launch (the
@@ -241,10 +249,10 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   // as zeros, and behind the run's end nothing is read.  So the loads are unconditional, and the waits in
   // front of a block's arithmetic count the next block's loads as what they are, in flight (with loads
   // under a condition the compiler must assume that they were not issued and waits for all).
-  // V: key i of the lane is 4 kk + i (i < 4) or 16 + 4 kk + i - 4, piece c its values 64 c + 4 c16 .. + 3.
+  // V: key i of the lane is 4 kk + i (i < 4) or 16 + 4 kk + i - 4, its values VE c16 .. + VE - 1: whole rows an instruction.
   u32x4 kbuf[2][KBLK][KSTEPS];
-  u32x2 vbuf[2][8][NC];
-  const int k_off = 2 * (c16 * D + 8 * kk), v_off = 2 * (4 * kk * D + 4 * c16);
+  vpiece vbuf[2][8];
+  const int k_off = 2 * (c16 * D + 8 * kk), v_off = 2 * (4 * kk * D + VE * c16);
   auto issue_loads = [&](int buf, const Cursor& c) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)c.k, 0, c.keys * (2 * D), 0x00020000);
     const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)c.v, 0, c.keys * (2 * D), 0x00020000);
@@ -254,21 +262,19 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
       for (int ks = 0; ks < KSTEPS; ++ks)
         kbuf[buf][bi][ks] = __builtin_amdgcn_raw_buffer_load_b128(kr, k_off, 2 * (16 * bi * D + 32 * ks), PC_BUF_NT);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int c4 = 0; c4 < NC; ++c4)
-        vbuf[buf][i][c4] = __builtin_amdgcn_raw_buffer_load_b64(vr, v_off, 2 * ((i < 4 ? i : i + 12) * D + 64 * c4), PC_BUF_NT);
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (VE == 8) vbuf[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(vr, v_off, 2 * (i < 4 ? i : i + 12) * D, PC_BUF_NT);
+      else vbuf[buf][i] = __builtin_amdgcn_raw_buffer_load_b64(vr, v_off, 2 * (i < 4 ? i : i + 12) * D, PC_BUF_NT);
+    }
     __builtin_amdgcn_sched_barrier(0);                       // not behind the arithmetic that follows
   };
 
   bf16x8 bq[KSTEPS];                        // B operand: column c16 = (t, head-in-group); lane holds d = 32*ks + 8*kk .. +7
   float m_run = -INFINITY, l_run = 0.f;     // of column c16 (this lane's share of the sum)
-  // O^T: o_acc[c][e], register i = value d = 64 c + 16 kk + 4 i + e of column c16
-  floatx4 o_acc[NC][4];
+  // O^T: o_acc[e], register i = value d = VE (4 kk + i) + e of column c16
+  floatx4 o_acc[VE];
 #pragma unroll
-  for (int c4 = 0; c4 < NC; ++c4)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) o_acc[c4][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < VE; ++e) o_acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   auto consume = [&](int buf, const Cursor& cur) __attribute__((always_inline)) {
     floatx4 acc[KBLK];
@@ -292,26 +298,22 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
       }
     if (__any(alpha != 1.0f)) {                      // some column's maximum grew (rare after the first keys)
 #pragma unroll
-      for (int c4 = 0; c4 < NC; ++c4)
+      for (int e = 0; e < VE; ++e)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) o_acc[c4][e][i] *= alpha;
+        for (int i = 0; i < 4; ++i) o_acc[e][i] *= alpha;
     }
 #pragma unroll
-    for (int c4 = 0; c4 < NC; ++c4)
+    for (int e = 0; e < VE; ++e) {
+      u32x4 va;                                      // value VE c16 + e of the lane's 8 keys
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        u32x4 va;                                    // value 64 c4 + 4 c16 + e of the lane's 8 keys
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          va[i] = __builtin_amdgcn_perm(vbuf[buf][2 * i + 1][c4][e / 2], vbuf[buf][2 * i][c4][e / 2], e % 2 ? 0x07060302u : 0x05040100u);
-        o_acc[c4][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_lo, o_acc[c4][e], 0, 0, 0);
-        o_acc[c4][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_hi, o_acc[c4][e], 0, 0, 0);
-      }
+      for (int i = 0; i < 4; ++i)
+        va[i] = __builtin_amdgcn_perm(vbuf[buf][2 * i + 1][e / 2], vbuf[buf][2 * i][e / 2], e % 2 ? 0x07060302u : 0x05040100u);
+      o_acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_lo, o_acc[e], 0, 0, 0);
+      o_acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8*)&va, *(bf16x8*)&p_hi, o_acc[e], 0, 0, 0);
+    }
   };
 
-  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane));
+  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
   issue_loads(0, cur);
 
   rot.finish(a.query, b, g, G, n_cols, sm.q);
@@ -347,11 +349,10 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   if (kk == 0) { sm.m[wave][c16] = m_run; sm.l[wave][c16] = l_run; }
   if (c16 < n_cols) {
 #pragma unroll
-    for (int c4 = 0; c4 < NC; ++c4)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        *(floatx4*)&sm.o[wave][c16][64 * c4 + 16 * kk + 4 * i] =
-            floatx4{o_acc[c4][0][i], o_acc[c4][1][i], o_acc[c4][2][i], o_acc[c4][3][i]};
+      for (int e = 0; e < VE; e += 4)
+        *(floatx4*)&sm.o[wave][c16][VE * (4 * kk + i) + e] = floatx4{o_acc[e][i], o_acc[e + 1][i], o_acc[e + 2][i], o_acc[e + 3][i]};
   }
   pc_write_partial<D>(sm, G, n_cols, a.n_q, a.n_q_heads, (long long)b * a.n_parts + a.part0 + part, g, a.part_o, a.part_lse);
 }

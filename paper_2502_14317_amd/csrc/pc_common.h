@@ -370,7 +370,9 @@ __device__ __forceinline__ int pc_wave_scan(int x) {
 }
 // Runs as equal as possible: the first total % n of n runs hold a block more.  32 bits are enough for
 // what fits in memory (a block of a group is at least 2 KiB of keys).
-__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, int wave, int lane) {
+// first: pc_first_lens, asked for in front of whatever else a workgroup starts with, so that the first keys wait for it alone
+__device__ __forceinline__ int pc_first_lens(const PcSegLens& L, int lane) { return L.seg_len && lane < L.n_seg ? L.len(lane) : 0; }
+__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, int wave, int lane, int first) {
   constexpr int WAVES = 4;
   PcBlockCursor c; c.s = 0; c.blk = 0; c.n_blk = 0; c.len = 0; c.left = 0;
   const int nb_full = (L.k_t + 31) / 32;
@@ -380,7 +382,7 @@ __device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int
     total = L.n_seg * nb_full;
   } else {
     for (int s0 = 0; s0 < L.n_seg; s0 += PC_WAVE) {
-      len = s0 + lane < L.n_seg ? L.len(s0 + lane) : 0;
+      len = s0 == 0 ? first : (s0 + lane < L.n_seg ? L.len(s0 + lane) : 0);
       nb = (len + 31) / 32;
       incl = pc_wave_scan(nb);
       total += __builtin_amdgcn_readlane(incl, PC_WAVE - 1);
@@ -398,7 +400,7 @@ __device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int
   int base = 0;
   for (int s0 = 0; s0 < L.n_seg; s0 += PC_WAVE) {
     if (L.n_seg > PC_WAVE) {
-      len = s0 + lane < L.n_seg ? L.len(s0 + lane) : 0;
+      len = s0 == 0 ? first : (s0 + lane < L.n_seg ? L.len(s0 + lane) : 0);
       nb = (len + 31) / 32;
       incl = pc_wave_scan(nb);
     }
