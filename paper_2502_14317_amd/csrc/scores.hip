@@ -64,7 +64,7 @@ struct PcScoreArgs {
   const uint16_t* q_split; // workspace: the query columns as MFMA operands (PcScoreQueries)
   float* tok_score;        // [C, H_kv, w]
   int L, w, w_obs, n_q_heads, n_kv_heads, n_kb, n_cols, n_cb;
-  int kb_keys;             // keys per workgroup: 128, 256, 512 or 1024 (at most 512 when WPC == 4)
+  int kb_keys;             // keys per workgroup: 64 to 1024 (pass 1 at most 512 when WPC == 4)
   float* blk_sum;          // workspace [C, H_kv, n_kb]: sum of each pass-2 block's tok_score
   // pre-pass duties of pass 1 (all nullptr: off): V rows in, rotated keys / K images / V^T images out
   const uint16_t* v;       // [C, L, H_kv, D]
@@ -228,7 +228,7 @@ __device__ __forceinline__ int score_head(const PcScoreArgs& a) {
 // MHA with 32 voting rows) the four 32-key quarters of a 128-key tile.  Pass 2 is bound by its vector instructions at two
 // wavefronts a SIMD (one wavefront issues one about every 5 cycles): without a barrier between staging and products,
 // with the voting rows' positions computed for masked tiles only and twice the keys a workgroup, WPC = 4 takes 330 ->
-// 272 us at 36 x 3584 keys of 32 heads, 19.5 -> 16.7 at 1 x 3584, 6.8 -> 6.0 at 4 x 512 keys of 8 heads of 64 values.
+// 277 us at 36 x 3584 keys of 32 heads, 19.5 -> 16.7 at 1 x 3584, 6.8 -> 6.0 at 4 x 512 keys of 8 heads of 64 values.
 // (The staging of the next tile between the MFMAs of this one: 283, 17.6 and 5.3.  Pass 1 without the barriers 1189 ->
 // 1203.)
 template <int D, int PASS, int WPC>
@@ -864,12 +864,13 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
   const int kb_cap = wpc == 4 ? PC_SC_KB_MAX / 2 : PC_SC_KB_MAX;
   while (!many && a.kb_keys >= PC_SC_KB && a.kb_keys < kb_cap && key_blocks(s, 2 * a.kb_keys) >= 512) a.kb_keys *= 2;
   a.n_kb = (a.L + a.kb_keys - 1) / a.kb_keys;
-  // pass 2 looks at context keys only, in blocks of equal size.  A key's sum has one owner where four wavefronts share a
-  // column block: its blocks have room for twice as many keys (36 x 3584 keys of 32 KV heads, 512 / 1024 keys: 300 / 272 us)
+  // pass 2 looks at context keys only.  A key's sum has one owner where four wavefronts share a column block: its blocks
+  // have room for twice as many keys (36 x 3584 keys of 32 KV heads, 512 / 1024 keys: 300 / 277 us).  Blocks start at
+  // multiples of pass 1's, the angles are read anew there, so a score's bits do not depend on which size was taken (blocks
+  // of equal size move the places where the angles' chains begin, and of two nearly equal scores the other is then kept).
   int kb2 = a.kb_keys;
   if (wpc == 4 && kb2 == kb_cap && key_blocks(s, 2 * kb2) >= 512) kb2 *= 2;
-  const int n_kb2 = (a.w + kb2 - 1) / kb2, tile2 = wpc == 4 ? 2 * PC_SC_TILE : PC_SC_TILE;
-  if (!many) kb2 = ((a.w + n_kb2 - 1) / n_kb2 + tile2 - 1) / tile2 * tile2;
+  const int n_kb2 = (a.w + kb2 - 1) / kb2;
   if (a.n_kb > 65535 || s->n_kv_heads > 65535) return PC_ERR_SHAPE;   // grid limits
   // heads fastest: neighbouring workgroups read neighbouring rows of a token, and an XCD (workgroups go round the
   // eight) gets every chunk, whatever the chunks' lengths.  Chunks fastest -> heads fastest (us): pass 1 of

@@ -1,5 +1,5 @@
-"""Scores with few voting columns where pass 2 takes other key blocks than pass 1: up to 1024 keys, all of one size, against
-the oracle on some of the chunks."""
+"""Scores with few voting columns where pass 2 takes other key blocks than pass 1: up to 1024 keys, against the
+oracle on some of the chunks."""
 import numpy as np
 import pytest
 import torch
@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 
 # C, w, w_q, H_q, H_kv, D, voting rows, ragged
 CASES = [
-    (64, 1300, 40, 4, 4, 64, 32, False),      # one column block: 512 keys in pass 1, 2 x 768 in pass 2
-    (64, 2049, 33, 4, 4, 64, 8, True),        # 8 columns, 3 x 768, ragged and empty chunks
-    (128, 1025, 40, 2, 2, 128, 32, False),    # 2 x 640: angles read anew behind 512 keys
+    (64, 1300, 40, 4, 4, 64, 32, False),      # one column block: 512 keys in pass 1, 1024 in pass 2
+    (64, 2049, 33, 4, 4, 64, 8, True),        # 8 columns, 3 x 1024, one key in the last, ragged and empty chunks
+    (128, 1025, 40, 2, 2, 128, 32, False),    # 1024 + 1: angles read anew behind 512 keys
     (128, 2048, 64, 2, 2, 128, 48, False),    # two column blocks, the voting rows inside the query block: 2 x 1024
-    (32, 1500, 36, 32, 8, 128, 32, True),     # four column blocks, 2 x 768 keys in tiles of 64
+    (32, 1500, 36, 32, 8, 128, 32, True),     # four column blocks, keys in tiles of 64
 ]
 
 
@@ -30,7 +30,7 @@ def test_score_blocks(case):
     lens = np.full(C, w, dtype=np.int32)
     if ragged:
         lens[:] = np.random.default_rng(w).integers(0, w + 1, size=C)
-        lens[:5] = 0, 1, w, 768, 769
+        lens[:5] = 0, 1, w, 1024, 1025
     shape = pc.make_shape(C, w, wq, Hq, Hkv, D, obs, 1.0e4)
     tok = torch.full((C, Hkv, w), float("nan"), dtype=torch.float32, device="cuda")
     chunk = torch.full((C,), float("nan"), dtype=torch.float32, device="cuda")
