@@ -127,12 +127,16 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 // 16 workgroups 7.0 -> 5.8 us, 3584 x 32 13.8 -> 9.2, 7680 x 64 27 -> 15.  (Two bits a round counted with
 // ballots, no histogram: 8.5, 14.6 and 23.8.)  A bin of up to PC_SEL_FEW keys is ranked by counting instead of
 // another round: in a layer's launch 2011 tokens x 40 11.6 -> 10.3, 7680 x 64 17.1 -> 14.9, 3584 x 32 12.
+// The bins are cleared while the scores are on their way, and where a layer has few chunks the scores of all of them
+// are asked for before the chunk is known (one memory latency less): 1 chunk of 3584 tokens x 32 12.0 -> 9.8 us, 4 of
+// 512 x 16 7.1 -> 7.0; 12 chunks of 3584 x 32, their chunks known, 12.0 -> 10.5.
 // The layer's gather in the same launch where a segment is small (PC_SEL_GATHER bytes of K and V): the workgroup
 // copies the rows that it has just selected (16 segments of 128 rows of 64 values: 6.7 + 3.7 us -> 7.7).  One CU
 // moves about 50 bytes a nanosecond, so larger segments are left to the gather's own launch.
 #define PC_SEL_BINS 2048
 #define PC_SEL_FEW 256        // so many keys of a bin are ranked by counting: one pass over them instead of a round
 #define PC_SEL_GATHER 65536
+#define PC_SEL_AHEAD 8        // so many scores a thread are asked for before the chunk is known, where that is all chunks'
 
 // A layer's chunk selection in the same launch: every workgroup adds up the chunks' block sums (the order
 // of pc_chunk_sum, a wavefront a chunk, its 4 x 64 strided sums asked for at once), ranks them as
@@ -240,24 +244,51 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
 
   const int s = blockIdx.x / n_kv_heads;
   const int g = blockIdx.x % n_kv_heads;
-  int c;
-  if (CHUNKS) c = select_own_chunk<THREADS>(chunks, (int)gridDim.x / n_kv_heads, s, blockIdx.x == 0);
-  else c = chunk_idx ? chunk_idx[s] : s;
-  if (c < 0) return;                               // no chunk for this entry: its outputs stay as they are
-  const float* src = tok_score + ((long long)c * n_kv_heads + g) * n;
-  int32_t* dst = out_idx + (long long)blockIdx.x * k;
   const int wave = threadIdx.x / PC_WAVE, lane = threadIdx.x % PC_WAVE;
   const int first = wave * (KPT * PC_WAVE) + lane; // index of the thread's slot 0; slot j: + 64 j
+  // The scores of chunk c0 + AHEAD - 1 at most, slot j of chunk c0 + a in x[a KPT + j]
+  constexpr int AHEAD = KPT <= PC_SEL_AHEAD ? PC_SEL_AHEAD / KPT : 1;
+  float x[AHEAD * KPT];
+  auto load = [&](int c0, int n_chunks) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+      if (a < n_chunks) {
+        const float* src = tok_score + ((long long)(c0 + a) * n_kv_heads + g) * n;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) x[a * KPT + j] = src[min(first + PC_WAVE * j, n - 1)];
+      }
+  };
+  int c;
+  const bool ahead = CHUNKS && chunks.n_chunks <= AHEAD;     // few chunks: all their scores, while the chunk is found
+  if (CHUNKS) {
+    if (ahead) load(0, chunks.n_chunks);
+    c = select_own_chunk<THREADS>(chunks, (int)gridDim.x / n_kv_heads, s, blockIdx.x == 0);
+  } else {
+    c = chunk_idx ? chunk_idx[s] : s;
+  }
+  if (c < 0) return;                               // no chunk for this entry: its outputs stay as they are
+  int32_t* dst = out_idx + (long long)blockIdx.x * k;
+  if (ahead) {
+#pragma unroll
+    for (int a = 1; a < AHEAD; ++a)
+      if (a == c) {
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) x[j] = x[a * KPT + j];
+      }
+  } else {
+    load(c, 1);
+  }
 
   const int n_valid = chunk_lens ? min(max(chunk_lens[c], 0), n) : n;   // a short chunk has fewer tokens
   if (threadIdx.x == 0) { sh_cand = 0u; sh_min = 0xffffffffu; sh_max = 0u; sh_few = 0u; }
+#pragma unroll
+  for (int u = 0; u < BPT; ++u) hist[threadIdx.x + THREADS * u] = 0u;
   uint32_t key[KPT];
 #pragma unroll
   for (int j = 0; j < KPT; ++j) {
     const int i = first + PC_WAVE * j;
-    const float x = i < n ? src[i] : 0.f;
-    key[j] = max(pc_order_key(x), 1u);
-    if (i >= n_valid || (i >= cls_lo && i < cls_hi && x > lambda)) key[j] = 0u;
+    key[j] = max(pc_order_key(x[j]), 1u);
+    if (i >= n_valid || (i >= cls_lo && i < cls_hi && x[j] > lambda)) key[j] = 0u;
   }
   __syncthreads();
   // number of candidates, their smallest and largest key
@@ -286,11 +317,8 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   // smallest admitted key where a bin is taken whole (then no key equal to T is admitted).
   lo = sh_min; hi = sh_max;
   uint32_t need = (uint32_t)k_eff, T = lo;
-  while (lo != hi) {
+  while (lo != hi) {                                 // (the bins are empty here)
     const int shift = max(0, 32 - __clz((int)(hi - lo)) - 11);
-#pragma unroll
-    for (int u = 0; u < BPT; ++u) hist[threadIdx.x + THREADS * u] = 0u;
-    __syncthreads();
 #pragma unroll
     for (int j = 0; j < KPT; ++j)
       if (key[j] >= lo && key[j] <= hi) atomicAdd(&hist[(key[j] - lo) >> shift], 1u);
@@ -341,6 +369,9 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
       T = sh_bin;
       break;
     }
+#pragma unroll
+    for (int u = 0; u < BPT; ++u) hist[threadIdx.x + THREADS * u] = 0u;
+    __syncthreads();
   }
 
   uint32_t cnt_gt = 0, cnt_eq = 0;
