@@ -34,6 +34,8 @@
 // the segment's length carry code 0.
 #include "decode_core.h"
 #include "fp8_quotient.h"
+#include "rope.h"
+#include <algorithm>
 
 #define PC_D8_WAVES 4
 #define PC_D8_ITER_KEYS 32
@@ -284,6 +286,8 @@ __device__ __forceinline__ void pc_e4m3x4_to_bf16(uint32_t w, uint32_t& lo, uint
 // granules.  Every 16 lanes store 256 consecutive bytes.  Bound by memory, 1 byte read and 2 written a value:
 // 256 segments of 2048 x 128 (0.40 GB) 66 us, 6.1 TB/s (as rows, through LDS: 61), and the attention that reads
 // them (4 x 512 rows, 32 / 8 heads) 548 -> 506 us.  The tail and the self segment follow in the same launch.
+// So does the rotation of the query rows, a workgroup each, spread evenly between the others: its fp64 angles cost
+// latency and few bytes, the tiles bytes only (4 x 512 rows: 67 + 10 us in two launches, 72 in one).
 template <int D>
 __device__ __forceinline__ void widen_piece(const uint8_t* src, float scale, bool have, uint32_t (&o)[8]) {
   uint4 raw = make_uint4(0, 0, 0, 0);
@@ -330,9 +334,14 @@ template <int D>
 __global__ __launch_bounds__(256) void fp8_images_kernel(
     const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, const float* __restrict__ k_scale,
     const float* __restrict__ v_scale, const int32_t* __restrict__ seg_len, int per_head, int k_t, long long n_segs, uint16_t* __restrict__ k_img, uint16_t* __restrict__ v_img,
-    PcRowsToImages tail, PcRowsToImages self, int n_seq, int n_kv_heads) {
+    PcRowsToImages tail, PcRowsToImages self, int n_seq, int n_kv_heads, PcRowsToRotate rot) {
+  const uint32_t turn = blockIdx.x / rot.period;
+  if (turn < rot.rows && turn * rot.period == blockIdx.x) {
+    pc_rope_q_workgroup<D>(rot.q, rot.q_rot, (int)turn, rot.n_q, rot.n_heads, rot.pos0, rot.rope, rot.mul);
+    return;
+  }
   const int tiles = (k_t + 63) / 64, n_blk = (k_t + 31) / 32;
-  const long long seg_units = n_segs * tiles, unit = blockIdx.x;
+  const long long seg_units = n_segs * tiles, unit = blockIdx.x - min(rot.rows, turn + 1);
   if (unit >= seg_units) {
     const int rest = (int)(unit - seg_units), tail_units = n_seq * n_kv_heads * ((tail.n_rows + 63) / 64);
     if (rest < tail_units) rows_to_image<D>(tail, rest, n_kv_heads);
@@ -392,19 +401,22 @@ __global__ __launch_bounds__(256) void fp8_images_kernel(
 
 int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
                          const int32_t* seg_len, int seg_len_per_head, long long n_segs, int k_t, int head_dim, void* k_img, void* v_img,
-                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads, hipStream_t st) {
+                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads,
+                         const PcRowsToRotate& rows, hipStream_t st) {
   const long long row_tiles = (tail.n_rows + 63) / 64 + (self.n_rows + 63LL) / 64;
-  const long long blocks = n_segs * ((k_t + 63) / 64) + (long long)n_seq * n_kv_heads * row_tiles;
+  const long long blocks = n_segs * ((k_t + 63) / 64) + (long long)n_seq * n_kv_heads * row_tiles + rows.rows;
   if (blocks == 0) return PC_OK;
   if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  PcRowsToRotate rot = rows;
+  rot.period = (uint32_t)(blocks / std::max(rows.rows, 1u));
   PcProfScope prof(PC_KERNEL_FP8_IMAGES, st);
   const dim3 grid((unsigned)blocks), block(256);
   if (head_dim == 128)
     hipLaunchKernelGGL(fp8_images_kernel<128>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale,
-                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads);
+                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads, rot);
   else
     hipLaunchKernelGGL(fp8_images_kernel<64>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale,
-                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads);
+                       seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads, rot);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }

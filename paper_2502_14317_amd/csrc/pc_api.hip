@@ -672,7 +672,8 @@ static PcKvGroup self_group(const void* k, const void* v, int n_q, int n_kv_head
 static int tile_attn_run(PcFlashArgs& a, const void* q, int batch, int n_q, int n_q_heads, int n_kv_heads,
                          int D, int q_pos0, float rope_base, float scale, void* q_rot, float* part_o,
                          float* part_lse, int n_parts, void* out, float* lse_out, hipStream_t st) {
-  int rc = pc_launch_rope_q(q, q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, scale * 1.4426950408889634f, st);
+  int rc = PC_OK;
+  if (q != nullptr) rc = pc_launch_rope_q(q, q_rot, batch, n_q, n_q_heads, D, q_pos0, rope_base, scale * 1.4426950408889634f, st);
   if (rc != PC_OK) return rc;
   a.global = 1; a.q = q_rot; a.o = out; a.lse = lse_out; a.part_o = part_o; a.part_lse = part_lse;
   a.n_seq = batch; a.n_rows = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.head_dim = D;
@@ -793,9 +794,14 @@ static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8
       a.grp[2] = image_group(self.k_img, self.v_img, nullptr, 0, 1, n_q, n_kv_heads, D);
       a.grp[2].causal = 1;
     }
+    PcRowsToRotate rows = {};
+    rows.q = (const uint16_t*)q; rows.q_rot = at(w.q_rot); rows.rows = (uint32_t)((long long)batch * n_q);
+    rows.n_q = n_q; rows.n_heads = n_q_heads; rows.pos0 = q_pos0;
+    rows.rope = pc_rope_factors(q_pos0 >= 0 ? rope_base : 2.0f, D); rows.mul = (double)(scale * 1.4426950408889634f);
     const int rc = pc_launch_fp8_images(k8, v8, k_scale, v_scale, seg_len, seg_len_per_head, n_segs, k_t, D, at(w.k_img[0]),
-                                        at(w.v_img[0]), tail, self, batch, n_kv_heads, st);
+                                        at(w.v_img[0]), tail, self, batch, n_kv_heads, rows, st);
     if (rc != PC_OK) return rc;
+    q = nullptr;                                             // rotated there
   }
   return tile_attn_run(a, q, batch, n_q, n_q_heads, n_kv_heads, D, q_pos0, rope_base, scale,
                        base + w.q_rot, (float*)(base + w.part_o), (float*)(base + w.part_lse),

@@ -469,9 +469,19 @@ struct PcRowsToImages {
   uint16_t* k_img;          // [n_seq][n_kv_heads][tiles][64 * D]
   uint16_t* v_img;
 };
+// ... and the query rows that the same attention takes, rotated (pos0 + t; pos0 < 0: as they are) and scaled by mul
+struct PcRowsToRotate {
+  const uint16_t* q;        // bf16 [rows = B n_q][n_heads][D]
+  uint16_t* q_rot;
+  uint32_t rows, period;    // every period-th workgroup takes a row (set by the launch)
+  int n_q, n_heads, pos0;
+  PcRope rope;
+  double mul;
+};
 int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, const float* v_scale,
                          const int32_t* seg_len, int seg_len_per_head, long long n_segs, int k_t, int head_dim, void* k_img, void* v_img,
-                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads, hipStream_t st);
+                         const PcRowsToImages& tail, const PcRowsToImages& self, int n_seq, int n_kv_heads,
+                         const PcRowsToRotate& rows, hipStream_t st);
 // The segments alone as bf16 rows [n_segs, k_t, D] (those behind a length are not written)
 int pc_launch_fp8_rows(const void* k8, const void* v8, const float* k_scale, const float* v_scale, const int32_t* seg_len,
                        int seg_len_per_head, long long n_segs, int n_kv_heads, int k_t, int head_dim, void* k_rows, void* v_rows, hipStream_t st);
