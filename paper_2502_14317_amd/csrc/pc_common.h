@@ -346,13 +346,13 @@ PcDecodeSplit pc_decode_split(int k_t, int n_seg, int elem_bytes, int tail_cap, 
 struct PcSegLens {
   const int32_t* seg_len;   // [B, S] ([B, S, H_kv] if per_head) or nullptr (= k_t)
   int per_head, n_seg, n_kv_heads, k_t, b, g;
+  __device__ __forceinline__ int at(int s) const { return per_head ? (b * n_seg + s) * n_kv_heads + g : b * n_seg + s; }
   __device__ __forceinline__ int len(int s) const {
     if (!seg_len) return k_t;
-    const int idx = per_head ? (b * n_seg + s) * n_kv_heads + g : b * n_seg + s;
     // read-only while a kernel runs: where the index is uniform this is a scalar load, which does not
     // queue behind the keys in flight
     typedef const __attribute__((address_space(4))) int32_t* scalar_t;
-    return min(max(((scalar_t)(uintptr_t)seg_len)[idx], 0), k_t);
+    return min(max(((scalar_t)(uintptr_t)seg_len)[at(s)], 0), k_t);
   }
 };
 struct PcBlockCursor {
@@ -370,14 +370,19 @@ __device__ __forceinline__ int pc_wave_scan(int x) {
 }
 // Runs as equal as possible: the first total % n of n runs hold a block more.  32 bits are enough for
 // what fits in memory (a block of a group is at least 2 KiB of keys).
-// first: pc_first_lens, asked for in front of whatever else a workgroup starts with, so that the first keys wait for it alone
-__device__ __forceinline__ int pc_first_lens(const PcSegLens& L, int lane) { return L.seg_len && lane < L.n_seg ? L.len(lane) : 0; }
+// first: pc_first_lens, asked for in front of whatever else a workgroup starts with, so that the first keys wait for it
+// alone: as it lies in memory and by every lane, since the limits or a condition beside the load would be waited for there
+__device__ __forceinline__ int pc_first_lens(const PcSegLens& L, int lane) {
+  return L.seg_len && L.n_seg > 0 ? L.seg_len[L.at(min(lane, L.n_seg - 1))] : 0;
+}
 __device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, int wave, int lane, int first) {
   constexpr int WAVES = 4;
   PcBlockCursor c; c.s = 0; c.blk = 0; c.n_blk = 0; c.len = 0; c.left = 0;
   const int nb_full = (L.k_t + 31) / 32;
   // lanes take a segment each, 64 segments per round; up to 64 segments the one round is kept
   int total = 0, len = 0, nb = 0, incl = 0;
+  asm volatile("" : "+v"(first));                             // not in front of it
+  first = lane < L.n_seg ? min(max(first, 0), L.k_t) : 0;
   if (!L.seg_len) {
     total = L.n_seg * nb_full;
   } else {
