@@ -201,7 +201,8 @@ __device__ __forceinline__ int select_own_chunk(const PcSelectChunks& x, int n_s
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = i0 + 64 * j + lane;
-        if (i < x.sum.per_chunk) part[j] += src[i];
+        const float v = src[min(i, x.sum.per_chunk - 1)];          // (under a condition each would be waited for)
+        part[j] += i < x.sum.per_chunk ? v : 0.f;
       }
     }
     float v = (part[0] + part[2]) + (part[1] + part[3]);
