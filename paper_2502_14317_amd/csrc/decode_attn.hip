@@ -38,7 +38,8 @@ struct PcMergeArgs {
   uint16_t* out;           // [B, n_q, H_q, D]
   float* lse_out;          // [B, H_q, n_q] or nullptr
   int n_rows;              // B n_q H_q
-  int n_q, n_q_heads, n_kv_heads, group, n_parts;    // group = H_q / H_kv
+  int n_q, n_q_heads, n_kv_heads, n_parts;
+  PcDiv q_div, heads_div, group_div;    // by n_q, n_q_heads, H_q / H_kv
   float scale;
 };
 
@@ -52,10 +53,9 @@ __global__ __launch_bounds__(256) void merge_kernel(PcMergeArgs a) {
   // (a workgroup behind the last row goes along and writes nothing: a way out here would part the arguments' loads)
   const uint32_t at = blockIdx.y * gridDim.x + blockIdx.x, bid = min(at, (uint32_t)a.n_rows - 1u);
   const bool own_row = at < (uint32_t)a.n_rows;
-  const uint32_t bt = bid / (uint32_t)a.n_q_heads;
-  const int h = (int)(bid - bt * a.n_q_heads);
-  const int b = (int)(a.n_q == 1 ? bt : bt / (uint32_t)a.n_q), t = (int)bt - b * a.n_q;
-  const int g = h / a.group;
+  const int bt = pc_div((int)bid, a.heads_div), h = (int)bid - bt * a.n_q_heads;
+  const int b = pc_div(bt, a.q_div), t = bt - b * a.n_q;
+  const int g = pc_div(h, a.group_div);
   // partial p of this (b, t, h): row = row0 + p * row_stride
   const long long row0 = ((long long)b * a.n_parts * a.n_q + t) * a.n_q_heads + h;
   const long long row_stride = (long long)a.n_q * a.n_q_heads;
@@ -399,7 +399,7 @@ int pc_launch_merge(const float* part_o, const float* part_lse, const void* q_ro
   a.k_self = (const uint16_t*)k_self; a.v_self = (const uint16_t*)v_self; a.step = step;
   a.out = (uint16_t*)out; a.lse_out = lse_out;
   a.n_q = n_q; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads; a.n_parts = n_parts;
-  a.group = n_q_heads / n_kv_heads;
+  a.q_div = pc_div_by(n_q); a.heads_div = pc_div_by(n_q_heads); a.group_div = pc_div_by(n_q_heads / n_kv_heads);
   a.scale = scale;
   const long long blocks = (long long)batch * n_q * n_q_heads;
   if (blocks == 0) return PC_OK;

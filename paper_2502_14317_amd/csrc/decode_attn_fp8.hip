@@ -262,7 +262,9 @@ struct PcDecode8Args {
   float* part_o;          // [B, P, n_q, H_q, D]
   float* part_lse;        // [B, P, n_q, H_q]
   int n_q, n_seg, k_t, n_q_heads, n_kv_heads, n_parts;
+  int group;              // H_q / H_kv
   int parts_grid;         // workgroups (partials) per (sequence, KV head) in this launch
+  PcDiv parts_div, heads_div;   // by parts_grid, by n_kv_heads
   float scale_log2;       // softmax scale * log2(e)
 };
 
@@ -493,14 +495,13 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   constexpr int KBLK = PC_D8_ITER_KEYS / 16;
   static_assert(KBLK == 2, "the V block layout assumes two 16-key logit tiles per block");
 
-  const int G = a.n_q_heads / a.n_kv_heads;
+  const int G = a.group;
   const int n_cols = a.n_q * G;             // valid query columns (<= 16)
   const int lane = threadIdx.x % PC_WAVE, wave = threadIdx.x / PC_WAVE;
   const int kk = lane / 16, c16 = lane % 16;
 
-  const int part = bid % a.parts_grid; bid /= a.parts_grid;
-  const int g = bid % a.n_kv_heads;    bid /= a.n_kv_heads;
-  const int b = bid;
+  const int bg = pc_div(bid, a.parts_div), part = bid - bg * a.parts_grid;
+  const int b = pc_div(bg, a.heads_div), g = bg - b * a.n_kv_heads;
 
   // A wavefront streams its run of 32-key blocks, through segment boundaries, under one running
   // softmax (one partial per workgroup).  A cursor names the next block: where it is, the
@@ -606,7 +607,7 @@ __device__ __forceinline__ void decode8_workgroup(const PcDecode8Args& a, int bi
   };
 
   // three register buffers: the loads of two blocks (2 x 8 KiB per wavefront) stay in flight
-  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
+  Cursor c0 = place(pc_blocks_begin(lens, part, a.parts_grid, a.parts_div, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
   Cursor c1 = next(c0);
   issue_loads(0, c0);
   issue_loads(1, c1);
@@ -687,7 +688,8 @@ int pc_launch_decode_fp8(const void* q, int pos0, float base, const void* k8, co
   a.k_scale = k_scale; a.v_scale = v_scale;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.parts_grid = split.parts;
+  a.group = n_q_heads / n_kv_heads;
+  a.parts_grid = split.parts; a.parts_div = pc_div_by(split.parts); a.heads_div = pc_div_by(n_kv_heads);
   a.n_parts = split.parts + split.tail_parts;
   a.scale_log2 = scale * PC_D8_LOG2E;
   const long long n_wg8 = (long long)batch * n_kv_heads * a.parts_grid;

@@ -109,7 +109,9 @@ struct PcDecodeArgs {
   float* part_o;          // [B, P, n_q, H_q, D]
   float* part_lse;        // [B, P, n_q, H_q]
   int n_q, n_seg, k_t, n_q_heads, n_kv_heads, n_parts;
+  int group;              // H_q / H_kv
   int parts_grid;         // workgroups (partials) per (sequence, KV head) in this launch
+  PcDiv parts_div, heads_div;   // by parts_grid, by n_kv_heads
   int part0;              // index of this launch's first partial among the n_parts
   float scale_log2;       // softmax scale * log2(e)
 };
@@ -209,14 +211,13 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
   typedef uint32_t vpiece __attribute__((ext_vector_type(VE / 2)));
   constexpr int KBLK = PC_DEC_ITER_KEYS / 16;
 
-  const int G = a.n_q_heads / a.n_kv_heads;
+  const int G = a.group;
   const int n_cols = a.n_q * G;             // valid query columns (<= 16)
   const int lane = threadIdx.x % PC_WAVE, wave = threadIdx.x / PC_WAVE;
   const int kk = lane / 16, c16 = lane % 16;
 
-  const int part = bid % a.parts_grid; bid /= a.parts_grid;
-  const int g = bid % a.n_kv_heads;    bid /= a.n_kv_heads;
-  const int b = bid;
+  const int bg = pc_div(bid, a.parts_div), part = bid - bg * a.parts_grid;
+  const int b = pc_div(bg, a.heads_div), g = bg - b * a.n_kv_heads;
 
   // A wavefront streams its run of 32-key blocks, through segment boundaries; the running
   // softmax carries over (same query columns, same KV head), so a workgroup leaves one partial.
@@ -313,7 +314,7 @@ __device__ __forceinline__ void pc_decode_workgroup(const PcDecodeArgs& a, int b
     }
   };
 
-  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
+  Cursor cur = place(pc_blocks_begin(lens, part, a.parts_grid, a.parts_div, __builtin_amdgcn_readfirstlane(wave), lane, first_lens));
   issue_loads(0, cur);
 
   rot.finish(a.query, b, g, G, n_cols, sm.q);
@@ -372,7 +373,8 @@ static inline PcDecodeArgs pc_decode_args(const PcDecodeQuery& query, const void
   a.kc = (const uint16_t*)kc; a.vc = (const uint16_t*)vc;
   a.seg_len = seg_len; a.seg_len_per_head = seg_len_per_head; a.part_o = part_o; a.part_lse = part_lse;
   a.n_q = query.n_q; a.n_seg = n_seg; a.k_t = k_t; a.n_q_heads = query.n_q_heads; a.n_kv_heads = n_kv_heads;
-  a.parts_grid = parts_grid;
+  a.group = query.n_q_heads / n_kv_heads;
+  a.parts_grid = parts_grid; a.parts_div = pc_div_by(parts_grid); a.heads_div = pc_div_by(n_kv_heads);
   a.n_parts = n_parts;
   a.scale_log2 = scale * PC_DEC_LOG2E;
   return a;

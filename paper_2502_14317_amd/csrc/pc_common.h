@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include "div31.h"
 #include "parallelcomp.h"
 #include "parallelcomp_bench.h"
 
@@ -375,7 +376,7 @@ __device__ __forceinline__ int pc_wave_scan(int x) {
 __device__ __forceinline__ int pc_first_lens(const PcSegLens& L, int lane) {
   return L.seg_len && L.n_seg > 0 ? L.seg_len[L.at(min(lane, L.n_seg - 1))] : 0;
 }
-__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, int wave, int lane, int first) {
+__device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int part, int n_parts, PcDiv parts_div, int wave, int lane, int first) {
   constexpr int WAVES = 4;
   PcBlockCursor c; c.s = 0; c.blk = 0; c.n_blk = 0; c.len = 0; c.left = 0;
   const int nb_full = (L.k_t + 31) / 32;
@@ -393,7 +394,7 @@ __device__ __forceinline__ PcBlockCursor pc_blocks_begin(const PcSegLens& L, int
       total += __builtin_amdgcn_readlane(incl, PC_WAVE - 1);
     }
   }
-  const int per = total / n_parts, extra = total % n_parts;
+  const int per = pc_div(total, parts_div), extra = total - per * n_parts;
   const int lo = part * per + min(part, extra), n = per + (part < extra);
   const int w_lo = lo + n * wave / WAVES, w_hi = lo + n * (wave + 1) / WAVES;
   if (w_lo >= w_hi) return c;
