@@ -239,6 +239,7 @@ struct PcScoreQueries {
   const int32_t* chunk_lens;
   uint16_t* q_split;       // [C, H_kv, n_cb][hi, lo][D / 16][2][min(n_cols, 32)][8]: rotated, scaled, split query columns as MFMA operands
   int n_chunks, L, w, w_obs, n_kv_heads, G, n_cols, n_cb;
+  PcDiv cb_div, heads_div, obs_div;      // by n_cb, n_kv_heads, w_obs
   float scale_log2;        // softmax scale x log2(e)
 };
 struct PcPrepArgs {

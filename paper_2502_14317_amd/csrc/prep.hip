@@ -17,14 +17,16 @@
 template <int D>
 __device__ __forceinline__ void split_query_columns(const PcScoreQueries& a, const PcRope& rope, long long unit, int lane) {
   constexpr int KS = D / 16, HALF = D / 2;
-  const int ks = (int)(unit % (KS / 2)), cb = (int)(unit / (KS / 2) % a.n_cb);
-  const long long cg = unit / (KS / 2) / a.n_cb;
-  const int c = (int)(cg / a.n_kv_heads), g = (int)(cg % a.n_kv_heads), n_heads = a.G * a.n_kv_heads;
+  // (column blocks of all chunks and KV heads are fewer than 2^31: their keys would not fit in memory)
+  const int ks = (int)(unit % (KS / 2)), block = (int)(unit / (KS / 2));
+  const int cg = pc_div(block, a.cb_div), cb = block - cg * a.n_cb;
+  const int c = pc_div(cg, a.heads_div), g = cg - c * a.n_kv_heads, n_heads = a.G * a.n_kv_heads;
   // a short chunk is [len context rows ; the query rows]: its voting rows end at len + w_q
   const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
-  const int col = min(32 * cb + lane % 32, a.n_cols - 1), row = ctx_len + (a.L - a.w) - a.w_obs + col % a.w_obs;
+  const int col = min(32 * cb + lane % 32, a.n_cols - 1), head = pc_div(col, a.obs_div);
+  const int row = ctx_len + (a.L - a.w) - a.w_obs + (col - head * a.w_obs);
   const int i0 = 16 * ks + 8 * (lane / 32);
-  const uint16_t* qrow = a.q + (((long long)c * a.L + row) * n_heads + g * a.G + col / a.w_obs) * D;
+  const uint16_t* qrow = a.q + (((long long)c * a.L + row) * n_heads + g * a.G + head) * D;
   const uint4 x1 = *(const uint4*)(qrow + i0), x2 = *(const uint4*)(qrow + HALF + i0);
   const uint32_t aw[4] = {x1.x, x1.y, x1.z, x1.w}, bw[4] = {x2.x, x2.y, x2.z, x2.w};
   u32x4 h1, l1, h2, l2;
@@ -49,7 +51,7 @@ __device__ __forceinline__ void split_query_columns(const PcScoreQueries& a, con
   // [hi, lo][k-step][half][column][8]
   const int cols = min(a.n_cols, 32), n = lane % 32, step = 2 * cols;
   if (n >= cols) return;                                           // a single block of fewer columns holds no others
-  u32x4* dst = (u32x4*)a.q_split + (cg * a.n_cb + cb) * (2 * KS) * step + (lane / 32) * cols + n;
+  u32x4* dst = (u32x4*)a.q_split + ((long long)cg * a.n_cb + cb) * (2 * KS) * step + (lane / 32) * cols + n;
   dst[ks * step] = h1;        dst[(ks + KS / 2) * step] = h2;
   dst[(KS + ks) * step] = l1; dst[(KS + ks + KS / 2) * step] = l2;
 }
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(256) void layer_prep_kernel(PcPrepArgs a, int table
     pc_rope_q_workgroup<D>(a.q_blk, a.q_rot, bid, a.n_q, a.n_heads, a.pos0, a.rope, a.mul);
     return;
   }
-  const long long unit = (bid - a.n_q) * 4LL + threadIdx.x / PC_WAVE;
+  const long long unit = (bid - a.n_q) * 4LL + __builtin_amdgcn_readfirstlane(threadIdx.x / PC_WAVE);
   if (unit < split_units) split_query_columns<D>(a.scores, a.rope, unit, threadIdx.x % PC_WAVE);
 }
 

@@ -64,6 +64,7 @@ struct PcScoreArgs {
   const uint16_t* q_split; // workspace: the query columns as MFMA operands (PcScoreQueries)
   float* tok_score;        // [C, H_kv, w]
   int L, w, w_obs, n_q_heads, n_kv_heads, n_kb, n_cols, n_cb;
+  PcDiv heads_div, obs_div;  // by n_kv_heads, w_obs
   int kb_keys;             // keys per workgroup: 64 to 1024 (pass 1 at most 512 when WPC == 4)
   float* blk_sum;          // workspace [C, H_kv, n_kb]: sum of each pass-2 block's tok_score
   // pre-pass duties of pass 1 (all nullptr: off): V rows in, rotated keys / K images / V^T images out
@@ -215,10 +216,10 @@ struct PcKeyStage {
 // (chunk, KV head) of a workgroup: heads fastest in the grid's first dimension or, where that would pass its
 // 2^32 threads, in the third
 __device__ __forceinline__ int score_chunk(const PcScoreArgs& a) {
-  return gridDim.z > 1 ? blockIdx.x : blockIdx.x / a.n_kv_heads;
+  return gridDim.z > 1 ? blockIdx.x : pc_div(blockIdx.x, a.heads_div);
 }
 __device__ __forceinline__ int score_head(const PcScoreArgs& a) {
-  return gridDim.z > 1 ? blockIdx.z : blockIdx.x % a.n_kv_heads;
+  return gridDim.z > 1 ? blockIdx.z : blockIdx.x - pc_div(blockIdx.x, a.heads_div) * a.n_kv_heads;
 }
 
 // WPC = wavefronts per block of 32 columns.  With 4 or more column blocks (a GQA group of 4
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
     }
   }
   // pass 1: this lane's voting row (column) and its running statistics
-  const int my_qrow = first_obs + col % a.w_obs;
+  const int my_qrow = first_obs + pc_mod(col, a.w_obs, a.obs_div);
   float m_run = -INFINITY, l_run = 0.f;
   // keys that count: pass 1 the sequence's, pass 2 its context rows; the pre-pass wants all rows
   const bool pre = PASS == 1 && a.v_img != nullptr;
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
           for (int r = 0; r < 16; ++r) {
             const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
             const float p = __builtin_amdgcn_exp2f(s[r] - lse_r[r]);
-            sum += (cc < a.n_cols && key <= first_obs + cc % a.w_obs) ? p : 0.f;
+            sum += (cc < a.n_cols && key <= first_obs + pc_mod(cc, a.w_obs, a.obs_div)) ? p : 0.f;
           }
         }
         sum += __shfl_xor(sum, 32);
@@ -549,7 +550,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   float m_run = -INFINITY, l_run = 0.f;                    // pass 1: of the column block that the arithmetic is at
   // the last key that the voting row of the lane's column sees, counted as the lane's registers are
   auto last_key_of = [&](int cb) __attribute__((always_inline)) {
-    return first_obs + min(32 * cb + n, a.n_cols - 1) % a.w_obs - key0 - 4 * hf;
+    return first_obs + pc_mod(min(32 * cb + n, a.n_cols - 1), a.w_obs, a.obs_div) - key0 - 4 * hf;
   };
   // A product's arithmetic in KS shares: s holds product kq of a column block (MASK: keys behind last_key are hidden,
   // pass 1 only).
@@ -692,7 +693,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
 #pragma unroll 1
           for (int r = 0; r < 16; ++r) {
             const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
-            if (key0 + 32 * kq + n <= first_obs + cc % a.w_obs) tok[kq] += __builtin_amdgcn_exp2f(s[r] - lse[r]);
+            if (key0 + 32 * kq + n <= first_obs + pc_mod(cc, a.w_obs, a.obs_div)) tok[kq] += __builtin_amdgcn_exp2f(s[r] - lse[r]);
           }
         }
       }
@@ -833,6 +834,7 @@ PcScoreQueries pc_scores_queries(const pc_shape* s, const void* q, const int32_t
   a.n_chunks = s->n_chunks; a.L = s->chunk_len + s->query_len; a.w = s->chunk_len; a.w_obs = s->obs_window;
   a.n_kv_heads = s->n_kv_heads; a.G = s->n_q_heads / s->n_kv_heads;
   a.n_cols = a.G * s->obs_window; a.n_cb = (a.n_cols + 31) / 32;
+  a.cb_div = pc_div_by(a.n_cb); a.heads_div = pc_div_by(a.n_kv_heads); a.obs_div = pc_div_by(a.w_obs);
   const float scale = s->softmax_scale > 0.f ? s->softmax_scale : 1.0f / sqrtf((float)s->head_dim);
   a.scale_log2 = scale * PC_SC_LOG2E;
   return a;
@@ -849,6 +851,7 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
   a.tok_score = tok_score;
   a.L = s->chunk_len + s->query_len; a.w = s->chunk_len; a.w_obs = s->obs_window;
   a.n_q_heads = s->n_q_heads; a.n_kv_heads = s->n_kv_heads;
+  a.heads_div = pc_div_by(a.n_kv_heads); a.obs_div = pc_div_by(a.w_obs);
   a.n_cols = (s->n_q_heads / s->n_kv_heads) * s->obs_window;
   a.n_cb = (a.n_cols + 31) / 32;
   const bool many = a.n_cb > PC_SC_WAVES;

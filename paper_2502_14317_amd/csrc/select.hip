@@ -235,7 +235,7 @@ __device__ __forceinline__ int select_own_chunk(const PcSelectChunks& x, int n_s
 // CHUNKS: the chunk is found here (chunk_idx is not read), otherwise it is chunk_idx[s]
 template <int KPT, int THREADS, bool CHUNKS>
 __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
-    const float* __restrict__ tok_score, const int32_t* __restrict__ chunk_idx, int n_kv_heads,
+    const float* __restrict__ tok_score, const int32_t* __restrict__ chunk_idx, int n_kv_heads, PcDiv heads_div,
     int n, int k, float lambda, int cls_lo, int cls_hi, const int32_t* __restrict__ chunk_lens,
     int32_t* __restrict__ out_idx, int32_t* __restrict__ out_cnt, PcSelectChunks chunks, PcSelectGather gather) {
   constexpr int WAVES = THREADS / PC_WAVE, BPT = PC_SEL_BINS / THREADS;      // bins per thread
@@ -243,8 +243,7 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   __shared__ uint32_t sh_cand, sh_min, sh_max, sh_bin, sh_need, sh_in_bin, sh_few;
   __shared__ uint32_t wave_tot[WAVES], wave_gt[WAVES], wave_eq[WAVES];
 
-  const int s = blockIdx.x / n_kv_heads;
-  const int g = blockIdx.x % n_kv_heads;
+  const int s = pc_div(blockIdx.x, heads_div), g = blockIdx.x - s * n_kv_heads;
   const int wave = threadIdx.x / PC_WAVE, lane = threadIdx.x % PC_WAVE;
   const int first = wave * (KPT * PC_WAVE) + lane; // index of the thread's slot 0; slot j: + 64 j
   // The scores of chunk c0 + AHEAD - 1 at most, slot j of chunk c0 + a in x[a KPT + j]
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(THREADS) void select_tokens_kernel(
   const bool ahead = CHUNKS && chunks.n_chunks <= AHEAD;     // few chunks: all their scores, while the chunk is found
   if (CHUNKS) {
     if (ahead) load(0, chunks.n_chunks);
-    c = select_own_chunk<THREADS>(chunks, (int)gridDim.x / n_kv_heads, s, blockIdx.x == 0);
+    c = select_own_chunk<THREADS>(chunks, pc_div(gridDim.x, heads_div), s, blockIdx.x == 0);
   } else {
     c = chunk_idx ? chunk_idx[s] : s;
   }
@@ -423,7 +422,7 @@ static int launch_tokens(const float* tok_score, const int32_t* chunk_idx, int n
   // to 8 with 512 threads, whose barriers are cheaper
 #define PC_SEL_LAUNCH(KPT, THREADS)                                                                             \
   hipLaunchKernelGGL((select_tokens_kernel<KPT, THREADS, CHUNKS>), dim3(n_sel * n_kv_heads), dim3(THREADS), 0,   \
-                     st, tok_score, chunk_idx, n_kv_heads, chunk_len, k, lambda, cls_lo, cls_hi,                \
+                     st, tok_score, chunk_idx, n_kv_heads, pc_div_by(n_kv_heads), chunk_len, k, lambda, cls_lo, cls_hi,                \
                      chunk_lens, out_idx, out_cnt, chunks, gather)
   if (chunk_len <= 512) PC_SEL_LAUNCH(1, 512);
   else if (chunk_len <= 1024) PC_SEL_LAUNCH(2, 512);
