@@ -287,6 +287,10 @@ struct PcFlashArgs {
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
   int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;
   int group_batch;          // (sequence, KV head) groups an XCD interleaves, >= 1 (set by the launcher)
+  // what a workgroup divides its number by (set by the launcher): H_q / H_kv = group, Q tiles, workgroups of a group, of
+  // an XCD's batch of groups, groups of a batch and of the last one, KV heads, parts
+  int group, n_qt;
+  PcDiv group_div, qt_div, per_group_div, per_batch_div, batch_div, last_div, heads_div, parts_div;
   float scale;
   // local
   const void* k_img;        // K tile images (rotated keys), image index = seq * img_seq_stride +

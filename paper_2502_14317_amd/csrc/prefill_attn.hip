@@ -240,28 +240,30 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
 
   // ---- which (sequence, head, Q tile): one XCD (blockIdx % 8) works through whole
   //      (sequence, KV head) groups, heavy Q tiles first, the group's query heads adjacent; the
-  //      last groups, when their number is no multiple of 8, are dealt out to all XCDs
-  const int G = a.n_q_heads / a.n_kv_heads;
+  //      last groups, when their number is no multiple of 8, are dealt out to all XCDs.  By multiplications (PcDiv): a
+  //      run of divisions by arguments stood in front of the first load (36 x 4096 rows, 32 heads 6326 -> 6276 us a layer)
+  const int G = a.group, n_qt = a.n_qt;
   const int rows_wg = GLOBAL ? a.n_rows * G : a.n_rows;      // rows that the Q tiles of a head (of a group) cover
-  const int n_qt = (rows_wg + PC_FA_BM - 1) / PC_FA_BM;
   const int per_group = GLOBAL ? n_qt * a.n_parts : G * n_qt;
   const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
   int cg, within;
   if (bid < full_blocks) {
     const int xcd = bid % 8, jb = bid / 8;
-    const int batch = jb / (a.group_batch * per_group), in_batch = jb % (a.group_batch * per_group);
-    const int n_batch = min(a.group_batch, n_groups / 8 - batch * a.group_batch);
-    cg = (batch * a.group_batch + in_batch % n_batch) * 8 + xcd;
-    within = in_batch / n_batch;
+    const int batch = pc_div(jb, a.per_batch_div), in_batch = jb - batch * (a.group_batch * per_group);
+    const int left = n_groups / 8 - batch * a.group_batch, n_batch = min(a.group_batch, left);
+    within = pc_div(in_batch, left >= a.group_batch ? a.batch_div : a.last_div);
+    cg = (batch * a.group_batch + in_batch - within * n_batch) * 8 + xcd;
   } else {
     const int rest = bid - full_blocks;
-    cg = n_groups / 8 * 8 + rest / per_group;
-    within = rest % per_group;
+    const int at = pc_div(rest, a.per_group_div);
+    cg = n_groups / 8 * 8 + at;
+    within = rest - at * per_group;
   }
-  const int seq = cg / a.n_kv_heads, g = cg % a.n_kv_heads;
-  const int part = GLOBAL ? within / n_qt : 0;
-  const int qt = GLOBAL ? within % n_qt : n_qt - 1 - within / G;
-  const int h = GLOBAL ? g * G : g * G + within % G;         // (GLOBAL: the group's first head)
+  const int seq = pc_div(cg, a.heads_div), g = cg - seq * a.n_kv_heads;
+  const int turn = pc_div(within, GLOBAL ? a.qt_div : a.group_div);
+  const int part = GLOBAL ? turn : 0;
+  const int qt = GLOBAL ? within - turn * n_qt : n_qt - 1 - turn;
+  const int h = GLOBAL ? g * G : g * G + within - turn * G;  // (GLOBAL: the group's first head)
 
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
   const int hf = lane / 32, n = lane % 32;
@@ -274,10 +276,10 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   const int row0 = row0_wg + 32 * NB * wave;      // first query row of this wavefront
   // query row -> index in [row, head] of its q and output rows, its position
   auto row_at = [&](int r) __attribute__((always_inline)) {
-    return GLOBAL ? ((long long)seq * a.n_rows + r / G) * a.n_q_heads + h + r % G
+    return GLOBAL ? ((long long)seq * a.n_rows + pc_div(r, a.group_div)) * a.n_q_heads + h + pc_mod(r, G, a.group_div)
                   : ((long long)seq * a.n_rows + r) * a.n_q_heads + h;
   };
-  auto pos_of = [&](int r) __attribute__((always_inline)) { return GLOBAL ? r / G : r; };
+  auto pos_of = [&](int r) __attribute__((always_inline)) { return GLOBAL ? pc_div(r, a.group_div) : r; };
   int my_row[NB], my_t[NB], max_key[NB];
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
 
@@ -303,7 +305,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     bool masked, seg_start;
   };
   Cursor cur = {};
-  const int wg_t0 = row0_wg / G, wg_t1 = (min(row0_wg + PC_FA_BM, rows_wg) - 1) / G;
+  const int wg_t0 = pc_div(row0_wg, a.group_div), wg_t1 = pc_div(min(row0_wg + PC_FA_BM, rows_wg) - 1, a.group_div);
   int run_full = 0, masked_lo = 0;                           // unmasked tiles of the run; its first masked tile
   auto cur_place = [&](int tile, int len) __attribute__((always_inline)) {   // tile: among the segment's of this phase
     const PcKvGroup& kg = a.grp[cur.grp];
@@ -358,9 +360,10 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
         n_full += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, false, lane);
         n_masked += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, true, lane);
       }
-    // every part takes an equal run of all tiles, [lo, hi) of [full ; masked]
-    const int lo = (int)((long long)(n_full + n_masked) * part / a.n_parts);
-    const int hi = (int)((long long)(n_full + n_masked) * (part + 1) / a.n_parts);
+    // every part (of 64 at most) takes an equal run of all tiles, [lo, hi) of [full ; masked] (2^25 tiles of a KV head
+    // would not fit in memory)
+    const int lo = pc_div((n_full + n_masked) * part, a.parts_div);
+    const int hi = pc_div((n_full + n_masked) * (part + 1), a.parts_div);
     T = cur.left = hi - lo;
     run_full = max(0, min(hi, n_full) - lo);
     masked_lo = max(0, lo - n_full);
@@ -855,7 +858,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     PC_WAIT_VMCNT(0);
     __syncthreads();
     // does the last tile's second half hold a key that some row of the wavefront sees?
-    if (__builtin_amdgcn_readfirstlane(min(lim0.cut - 1, min(row0 + 31, rows_wg - 1) / G - lim0.c0)) >= 32) {
+    if (__builtin_amdgcn_readfirstlane(min(lim0.cut - 1, pc_div(min(row0 + 31, rows_wg - 1), a.group_div) - lim0.c0)) >= 32) {
       step(with_mask{}, yes{}, no{}, no{}, lim0, 8.0f, 2 * T - 1, 32, 0, no_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
       last_pv(p_buf[1]);
     } else {
@@ -873,7 +876,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     const float lse = l > 0.f ? m_run[nb] * PC_LN2 + logf(l) : -INFINITY;
     if (GLOBAL && a.n_parts > 1) {
       if (my_row[nb] < seq_rows) {
-        const long long prow = (((long long)seq * a.n_parts + part) * a.n_rows + my_row[nb] / G) * a.n_q_heads + h + my_row[nb] % G;
+        const long long prow = (((long long)seq * a.n_parts + part) * a.n_rows + pc_div(my_row[nb], a.group_div)) * a.n_q_heads + h + pc_mod(my_row[nb], G, a.group_div);
         float* po = a.part_o + prow * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -918,7 +921,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
           pc_store_once((u32x4*)((uint16_t*)a.o + row_at(grow) * D + 8 * l_piece), x);
       }
       if (my_row[nb] < seq_rows && hf == 0 && a.lse)
-        a.lse[((long long)seq * a.n_q_heads + h + (GLOBAL ? my_row[nb] % G : 0)) * a.n_rows + pos_of(my_row[nb])] = lse;
+        a.lse[((long long)seq * a.n_q_heads + h + (GLOBAL ? pc_mod(my_row[nb], G, a.group_div) : 0)) * a.n_rows + pos_of(my_row[nb])] = lse;
     }
   }
 }
@@ -974,6 +977,12 @@ static long long flash_blocks(PcFlashArgs& a) {
     const long long m = (192 + per_group - 1) / per_group, batches = (groups_xcd + m - 1) / m;
     a.group_batch = (int)((groups_xcd + batches - 1) / batches);           // batches of equal size
   }
+  const int last = (int)(groups_xcd % a.group_batch);
+  a.group = G; a.n_qt = (int)n_qt;
+  a.group_div = pc_div_by(G); a.qt_div = pc_div_by(a.n_qt); a.heads_div = pc_div_by(a.n_kv_heads);
+  a.per_group_div = pc_div_by((int)per_group); a.per_batch_div = pc_div_by((int)(a.group_batch * per_group));
+  a.batch_div = pc_div_by(a.group_batch); a.last_div = pc_div_by(last);
+  a.parts_div = pc_div_by(GLOBAL ? a.n_parts : 1);
   return (long long)a.n_seq * a.n_kv_heads * per_group;
 }
 
