@@ -495,7 +495,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   __shared__ float tok_part[PC_SC_WAVES][PASS == 2 ? TILE : 1];
 
   const int c = score_chunk(a), g = score_head(a), kblock = blockIdx.y, key0 = kblock * TILE;
-  const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = tid / PC_WAVE;
+  const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = __builtin_amdgcn_readfirstlane(tid / PC_WAVE);
   const int hf = lane / 32, n = lane % 32;
   const int ctx_len = a.chunk_lens ? min(max(a.chunk_lens[c], 0), a.w) : a.w;
   const int first_obs = ctx_len + (a.L - a.w) - a.w_obs;
@@ -548,13 +548,27 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   };
   constexpr int MAX_SL = KS / 4;                           // slices of pass 1 that take the maxima
   float m_run = -INFINITY, l_run = 0.f;                    // pass 1: of the column block that the arithmetic is at
-  // the last key that the voting row of the lane's column sees, counted as the lane's registers are
-  auto last_key_of = [&](int cb) __attribute__((always_inline)) {
-    return first_obs + pc_mod(min(32 * cb + n, a.n_cols - 1), a.w_obs, a.obs_div) - key0 - 4 * hf;
+  // What a mask starts from.  Pass 1: the last key that the voting row of the lane's column sees, counted as the lane's
+  // registers are.  Pass 2: the first voting row of the column block (the same one for all lanes).
+  auto limit_of = [&](int cb) __attribute__((always_inline)) {
+    return PASS == 1 ? first_obs + pc_mod(min(32 * cb + n, a.n_cols - 1), a.w_obs, a.obs_div) - key0 - 4 * hf
+                     : pc_mod(32 * cb, a.w_obs, a.obs_div);
   };
-  // A product's arithmetic in KS shares: s holds product kq of a column block (MASK: keys behind last_key are hidden,
-  // pass 1 only).
-  auto arith = [&](auto mask_tag, int share, floatx16& s, int kq, int last_key, float& top, float& sum) __attribute__((always_inline)) {
+  // pass 2: the rows of a column block from voting row row0 on that see the lane's key of product kq, a bit each, moved to
+  // where the lane's registers count from.  The rows of every head of the block are a run that ends at the head's last.
+  // In the slices like everything else: a loop of its own, product after product, had cost more than the slices won.  That
+  // loop -> now (both passes, us): 12 chunks of 2011 + 203 rows, 32 / 8 heads, 512 voting 603 -> 548, all 2214 3114 -> 2529; 1 of
+  // 1000 + 64, 8 heads, 600 voting 40.2 -> 30.5; 16 of 1000 + 64, 24 / 8 heads of 64 values, 300 voting 144 -> 122.
+  auto rows_that_see = [&](int row0, int kq) __attribute__((always_inline)) {
+    const int first = min(max(key0 + 32 * kq + n - first_obs, 0), a.w_obs);
+    auto below = [](int x) __attribute__((always_inline)) { return x <= 0 ? 0u : ~0u >> (32 - min(x, 32)); };
+    uint32_t rows = 0;
+    for (int head = -row0; head < 32; head += a.w_obs) rows |= below(head + a.w_obs) & ~below(head + first);
+    return rows >> (4 * hf);
+  };
+  // A product's arithmetic in KS shares: s holds product kq of a column block (MASK: keys that a row does not see are
+  // left out; pass 2 asks once a product which rows do).
+  auto arith = [&](auto mask_tag, int share, floatx16& s, int kq, int limit, float& top, float& sum, uint32_t& seen) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
     if (PASS == 1) {
       if (share < MAX_SL) {
@@ -563,7 +577,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
           if (MASK) {
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if (32 * kq + 8 * (r / 4) + (r % 4) > last_key) s[r] = -INFINITY;
+              if (32 * kq + 8 * (r / 4) + (r % 4) > limit) s[r] = -INFINITY;
           }
         }
 #pragma unroll
@@ -585,9 +599,15 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
         if (share == KS - 1) l_run += sum;
       }
     } else {
-      if (share == 0) sum = 0.f;
+      if (share == 0) {
+        sum = 0.f;
+        if (MASK) seen = rows_that_see(limit, kq);
+      }
 #pragma unroll
-      for (int i = 0; i < 16 / KS; ++i) sum += __builtin_amdgcn_exp2f(s[share * (16 / KS) + i] - lse[share * (16 / KS) + i]);
+      for (int r = share * (16 / KS); r < (share + 1) * (16 / KS); ++r) {
+        const float p = __builtin_amdgcn_exp2f(s[r] - lse[r]);
+        sum += MASK ? __uint_as_float(__float_as_uint(p) & (uint32_t)__builtin_amdgcn_sbfe((int)seen, 8 * (r / 4) + r % 4, 1)) : p;
+      }
       asm volatile("" : "+v"(sum));
       if (share == KS - 1) tok[kq] += sum;
     }
@@ -608,7 +628,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   // operand makes room for the next block's: seven k-steps before that needs it.
   auto block = [&](auto mask_tag, int cb) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
-    int last_key = MASK ? last_key_of(max(cb - PC_SC_WAVES, 0)) : 0;
+    int limit = MASK ? limit_of(max(cb - PC_SC_WAVES, 0)) : 0;
     const int next = min(cb + PC_SC_WAVES, a.n_cb - 1);
     const uint16_t* src = q_of(next);
     opaque_at();
@@ -617,6 +637,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
     for (int kq = 0; kq < NSUB; ++kq) {
       floatx16& s = s_buf[kq % 2];
       float top = 0.f, sum = 0.f;
+      uint32_t seen = 0;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 kh = ring[ks % RING][0], kl = ring[ks % RING][1];
@@ -632,11 +653,11 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
         const int to = ks + AHEAD;
         if (to < KS) read_k(kq, to); else read_k((kq + 1) % NSUB, to - KS);
         s = product(q[KS + ks], kh, s);
-        if (ks > 0) arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, last_key, top, sum);
+        if (ks > 0) arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, limit, top, sum, seen);
         s = product(q[ks], kh, s);
         if (ks == 0) {                                     // (the product before is through by then)
           __builtin_amdgcn_sched_barrier(0);
-          arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, last_key, top, sum);
+          arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, limit, top, sum, seen);
         }
         if (kq == NSUB - 1) {
           q[ks] = *(const bf16x8*)(src + ks * PC_WAVE * 8);
@@ -648,8 +669,8 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
       if (PASS == 1 && kq == 0) {
         if (cb >= PC_SC_WAVES) leave(cb - PC_SC_WAVES);
         m_run = -INFINITY; l_run = 0.f;
-        if (MASK) last_key = last_key_of(cb);
       }
+      if (MASK && kq == 0) limit = limit_of(cb);
     }
   };
   auto blocks = [&](auto mask_tag) __attribute__((always_inline)) {
@@ -662,41 +683,17 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
 #pragma unroll 1
     for (; cb < a.n_cb; cb += PC_SC_WAVES) block(mask_tag, cb);
     float top = 0.f, sum = 0.f;
+    uint32_t seen = 0;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) arith(mask_tag, ks, s_buf[1], NSUB - 1, last_key_of(cb - PC_SC_WAVES), top, sum);
+    for (int ks = 0; ks < KS; ++ks) arith(mask_tag, ks, s_buf[1], NSUB - 1, limit_of(cb - PC_SC_WAVES), top, sum, seen);
     if (PASS == 1) leave(cb - PC_SC_WAVES);
   };
   if (wave < a.n_cb && n_sub > 0) {
     if (unmasked) {
       blocks(std::false_type{});
-    } else if (PASS == 1) {
-      blocks(std::true_type{});
     } else {
-      // voting rows among the context rows (more of them than query rows): product after product
-#pragma unroll 1
-      for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) {
-        load_q(q_of(cb));
-        load_lse(lse, cb);
-#pragma unroll
-        for (int kq = 0; kq < NSUB; ++kq) {
-          floatx16 s;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[r] = 0.f;
-          opaque_at();
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            read_k(kq, ks);
-            s = product(q[ks], ring[ks % RING][1], s);
-            s = product(q[KS + ks], ring[ks % RING][0], s);
-            s = product(q[ks], ring[ks % RING][0], s);
-          }
-#pragma unroll 1
-          for (int r = 0; r < 16; ++r) {
-            const int cc = 32 * cb + 8 * (r / 4) + 4 * hf + (r % 4);
-            if (key0 + 32 * kq + n <= first_obs + pc_mod(cc, a.w_obs, a.obs_div)) tok[kq] += __builtin_amdgcn_exp2f(s[r] - lse[r]);
-          }
-        }
-      }
+      if (PASS == 2) load_q(q_of(wave));                   // anew: kept for either branch the columns were in registers twice
+      blocks(std::true_type{});
     }
   } else if (PASS == 1) {
     for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) leave(cb);     // nobody looks at these keys
