@@ -504,7 +504,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   const long long cg = (long long)c * a.n_kv_heads + g;
   // every key that counts here is visible to every voting row (pass 2 drops what lies behind the context rows)
   const bool unmasked = (PASS == 1 ? key0 + TILE : min(key0 + TILE, ctx_len)) - 1 <= first_obs;
-  const int n_sub = min(NSUB, (key_end - key0 + 31) / 32); // (<= 0: nobody looks at these keys)
+  const int n_keys = key_end - key0;                       // keys that count (<= 0: nobody looks at this tile)
   float tok[NSUB];
 #pragma unroll
   for (int kq = 0; kq < NSUB; ++kq) tok[kq] = 0.f;
@@ -626,15 +626,16 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   };
   // Column block cb, and the last product's arithmetic of the block before it.  Behind its last use in the block an
   // operand makes room for the next block's: seven k-steps before that needs it.
-  auto block = [&](auto mask_tag, int cb) __attribute__((always_inline)) {
+  auto block = [&](auto mask_tag, auto products_tag, int cb) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
+    constexpr int PRODUCTS = decltype(products_tag)::value;
     int limit = MASK ? limit_of(max(cb - PC_SC_WAVES, 0)) : 0;
     const int next = min(cb + PC_SC_WAVES, a.n_cb - 1);
     const uint16_t* src = q_of(next);
     opaque_at();
-    static_assert(NSUB % 2 == 0, "products take turns in s_buf");
+    static_assert(PRODUCTS % 2 == 0, "products take turns in s_buf");
 #pragma unroll
-    for (int kq = 0; kq < NSUB; ++kq) {
+    for (int kq = 0; kq < PRODUCTS; ++kq) {
       floatx16& s = s_buf[kq % 2];
       float top = 0.f, sum = 0.f;
       uint32_t seen = 0;
@@ -651,15 +652,15 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
         }
         if (PASS == 2 && kq == 0 && ks == 0) load_lse(lse_next, cb);
         const int to = ks + AHEAD;
-        if (to < KS) read_k(kq, to); else read_k((kq + 1) % NSUB, to - KS);
+        if (to < KS) read_k(kq, to); else read_k((kq + 1) % PRODUCTS, to - KS);
         s = product(q[KS + ks], kh, s);
-        if (ks > 0) arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, limit, top, sum, seen);
+        if (ks > 0) arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + PRODUCTS - 1) % PRODUCTS, limit, top, sum, seen);
         s = product(q[ks], kh, s);
         if (ks == 0) {                                     // (the product before is through by then)
           __builtin_amdgcn_sched_barrier(0);
-          arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + NSUB - 1) % NSUB, limit, top, sum, seen);
+          arith(mask_tag, ks, s_buf[1 - kq % 2], (kq + PRODUCTS - 1) % PRODUCTS, limit, top, sum, seen);
         }
-        if (kq == NSUB - 1) {
+        if (kq == PRODUCTS - 1) {
           q[ks] = *(const bf16x8*)(src + ks * PC_WAVE * 8);
           q[KS + ks] = *(const bf16x8*)(src + (KS + ks) * PC_WAVE * 8);
         }
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
       if (MASK && kq == 0) limit = limit_of(cb);
     }
   };
-  auto blocks = [&](auto mask_tag) __attribute__((always_inline)) {
+  auto blocks = [&](auto mask_tag, auto products_tag) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < AHEAD; ++ks) read_k(0, ks);
     // nothing before the first block: exponents that add nothing (pass 1: a sum that is dropped)
@@ -681,20 +682,27 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
     for (int r = 0; r < 16; ++r) { s_buf[1][r] = 0.f; lse[r] = INFINITY; }
     int cb = wave;
 #pragma unroll 1
-    for (; cb < a.n_cb; cb += PC_SC_WAVES) block(mask_tag, cb);
+    for (; cb < a.n_cb; cb += PC_SC_WAVES) block(mask_tag, products_tag, cb);
     float top = 0.f, sum = 0.f;
     uint32_t seen = 0;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) arith(mask_tag, ks, s_buf[1], NSUB - 1, limit_of(cb - PC_SC_WAVES), top, sum, seen);
+    for (int ks = 0; ks < KS; ++ks) arith(mask_tag, ks, s_buf[1], decltype(products_tag)::value - 1, limit_of(cb - PC_SC_WAVES), top, sum, seen);
     if (PASS == 1) leave(cb - PC_SC_WAVES);
   };
-  if (wave < a.n_cb && n_sub > 0) {
-    if (unmasked) {
-      blocks(std::false_type{});
-    } else {
-      if (PASS == 2) load_q(q_of(wave));                   // anew: kept for either branch the columns were in registers twice
-      blocks(std::true_type{});
-    }
+  // A tile with up to 64 keys that count (the last one of the context or of the sequence) takes two products a column
+  // block instead of four, with the same bits.  Four always / two (both passes, us): 300 chunks of 24 + 8 rows, 64 heads on one
+  // KV head, 8 voting 76.1 / 64.9; 200 of 100 + 33, 32 / 8 heads, 33 voting 167.7 / 157.2; 60 ragged of 700 + 60, 60 voting
+  // 154.7 / 147.1; no such tile in 12 of 2011 + 203, 2214 voting 2623 / 2598.
+  if (wave < a.n_cb && n_keys > 0) {
+    auto run = [&](auto products_tag) __attribute__((always_inline)) {
+      if (unmasked && !(PASS == 1 && decltype(products_tag)::value < NSUB)) {    // (pass 1: such a tile ends the sequence)
+        blocks(std::false_type{}, products_tag);
+      } else {
+        if (PASS == 2) load_q(q_of(wave));                 // anew: kept for either branch the columns were in registers twice
+        blocks(std::true_type{}, products_tag);
+      }
+    };
+    if (NSUB == 2 || n_keys > 64) run(std::integral_constant<int, NSUB>{}); else run(std::integral_constant<int, 2>{});
   } else if (PASS == 1) {
     for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) leave(cb);     // nobody looks at these keys
   }

@@ -1,5 +1,6 @@
-"""Scores with many voting columns where the last 128-key tile of a ragged chunk holds 1 to 128 keys that count and the
-rows behind the chunk are NaN: the products run over whole tiles, what lies behind the keys has to drop out."""
+"""Scores with many voting columns where the last tile of a ragged chunk (of 128 keys or, with few workgroups, 64) holds any
+number of keys that count and the rows behind the chunk are NaN: the products run over whole tiles or, with up to 64 keys
+in one of 128, over its first half; what lies behind the keys has to drop out."""
 import numpy as np
 import pytest
 import torch
@@ -12,22 +13,22 @@ from helpers import S_ATOL, S_RTOL, assert_close, bits_to_dev
 
 pytestmark = pytest.mark.gpu
 
-# w, w_q, H_q, D, voting rows: 5 column blocks (a wavefront has two), 8 (two each), 17 (the first has five)
-CASES = [(300, 33, 5, 128, 32), (257, 52, 5, 64, 50), (190, 68, 8, 128, 66)]
+# C, w, w_q, H_q, D, voting rows: 5 column blocks (a wavefront has two), 8 (two each), 17 (the first has five).
+# 86 chunks of up to 384 rows are 258 workgroups of 128 keys, 24 fewer than 256: 64 keys.
+CASES = [(86, 300, 33, 5, 128, 32), (86, 257, 52, 5, 64, 50), (86, 190, 68, 8, 128, 66),
+         (24, 300, 33, 5, 128, 32), (24, 190, 68, 8, 64, 66)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
 def test_many_columns_nan_behind_chunks(case):
-    w, wq, Hq, D, obs = case
-    C, Hkv = 86, 1                                          # 3 (2) tiles a chunk: at least 256 workgroups at 128 keys
-    if C * ((w + wq + 127) // 128) < 256:
-        C = 128
-    print("many columns, padding", case, C, flush=True)
+    C, w, wq, Hq, D, obs = case
+    Hkv = 1
+    print("many columns, padding", case, flush=True)
     r = np.random.default_rng([67, w, wq, Hq, D])
     lens = r.integers(1, w + 1, size=C).astype(np.int32)
-    edge = [0, 1, 31, 32, 33, 64, 95, 96, 127, 128, 129, 160, w]
-    lens[:len(edge)] = [min(e, w) for e in edge]
-    lens[len(edge):len(edge) + 4] = [max(0, 128 - wq), max(1, 129 - wq), 256 - wq, min(w, 257 - wq)]     # the sequence ends at a tile
+    edge = [0, 1, 31, 32, 33, 63, 64, 65, 95, 96, 127, 128, 129, 160, 192, w]          # the context ends there
+    edge += [e - wq for e in (64, 65, 128, 129, 192, 193, 256, 257)]                   # the sequence does
+    lens[:len(edge)] = np.clip(edge, 0, w)
     mk = lambda h: f32_to_bf16_bits(r.standard_normal((C, w + wq, h, D)).astype(np.float32))
     q, k = mk(Hq), mk(Hkv)
     for c in range(C):
@@ -39,7 +40,7 @@ def test_many_columns_nan_behind_chunks(case):
     ws.fill_(0xFF)
     pc.pc_chunk_query_scores(shape, bits_to_dev(q), bits_to_dev(k), tok, chunk, ws, chunk_lens=torch.from_numpy(lens).cuda())
     torch.cuda.synchronize()
-    for c in range(20):
+    for c in range(len(edge)):
         n = int(lens[c])
         pos = np.arange(n + wq)
         qr = oracle.rope(bf16_bits_to_f64(q[c])[:n + wq], pos, 1.0e4)
