@@ -337,17 +337,17 @@ __global__ __launch_bounds__(256) void fp8_images_kernel(
     const uint8_t* __restrict__ k8, const uint8_t* __restrict__ v8, const float* __restrict__ k_scale,
     const float* __restrict__ v_scale, const int32_t* __restrict__ seg_len, int per_head, int k_t, long long n_segs, uint16_t* __restrict__ k_img, uint16_t* __restrict__ v_img,
     PcRowsToImages tail, PcRowsToImages self, int n_seq, int n_kv_heads, PcRowsToRotate rot) {
-  const uint32_t turn = blockIdx.x / rot.period;
-  if (turn < rot.rows && turn * rot.period == blockIdx.x) {
+  const uint32_t bid = blockIdx.y * gridDim.x + blockIdx.x, turn = bid / rot.period;
+  if (turn < rot.rows && turn * rot.period == bid) {
     pc_rope_q_workgroup<D>(rot.q, rot.q_rot, (int)turn, rot.n_q, rot.n_heads, rot.pos0, rot.rope, rot.mul);
     return;
   }
   const int tiles = (k_t + 63) / 64, n_blk = (k_t + 31) / 32;
-  const long long seg_units = n_segs * tiles, unit = blockIdx.x - min(rot.rows, turn + 1);
+  const long long seg_units = n_segs * tiles, unit = bid - min(rot.rows, turn + 1);
   if (unit >= seg_units) {
     const int rest = (int)(unit - seg_units), tail_units = n_seq * n_kv_heads * ((tail.n_rows + 63) / 64);
     if (rest < tail_units) rows_to_image<D>(tail, rest, n_kv_heads);
-    else rows_to_image<D>(self, rest - tail_units, n_kv_heads);
+    else if (rest - tail_units < n_seq * n_kv_heads * ((self.n_rows + 63) / 64)) rows_to_image<D>(self, rest - tail_units, n_kv_heads);
     return;
   }
   const long long seg = unit / tiles;
@@ -408,11 +408,11 @@ int pc_launch_fp8_images(const void* k8, const void* v8, const float* k_scale, c
   const long long row_tiles = (tail.n_rows + 63) / 64 + (self.n_rows + 63LL) / 64;
   const long long blocks = n_segs * ((k_t + 63) / 64) + (long long)n_seq * n_kv_heads * row_tiles + rows.rows;
   if (blocks == 0) return PC_OK;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  if (blocks > 0x7fffffffLL - PC_GRID_X) return PC_ERR_SHAPE;
   PcRowsToRotate rot = rows;
   rot.period = (uint32_t)(blocks / std::max(rows.rows, 1u));
   PcProfScope prof(PC_KERNEL_FP8_IMAGES, st);
-  const dim3 grid((unsigned)blocks), block(256);
+  const dim3 grid = pc_grid_2d(blocks), block(256);
   if (head_dim == 128)
     hipLaunchKernelGGL(fp8_images_kernel<128>, grid, block, 0, st, (const uint8_t*)k8, (const uint8_t*)v8, k_scale, v_scale,
                        seg_len, seg_len_per_head, k_t, n_segs, (uint16_t*)k_img, (uint16_t*)v_img, tail, self, n_seq, n_kv_heads, rot);
