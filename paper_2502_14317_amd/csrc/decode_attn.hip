@@ -233,24 +233,25 @@ int pc_launch_merge_rows(const float* part_o, const float* part_lse, void* out, 
 // ------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void rope_q_kernel(const uint16_t* __restrict__ q, uint16_t* __restrict__ q_rot,
-                                                     int n_q, int n_heads, int pos0, PcRope rope, double mul) {
-  pc_rope_q_workgroup<D>(q, q_rot, blockIdx.x, n_q, n_heads, pos0, rope, mul);
+                                                     int n_rows, int n_q, int n_heads, int pos0, PcRope rope, double mul) {
+  const uint32_t row = blockIdx.y * gridDim.x + blockIdx.x;
+  if (row < (uint32_t)n_rows) pc_rope_q_workgroup<D>(q, q_rot, (int)row, n_q, n_heads, pos0, rope, mul);
 }
 
 int pc_launch_rope_q(const void* q, void* q_rot, int batch, int n_q, int n_heads, int D, int pos0,
                      float base, float mul, hipStream_t st) {
   const long long blocks = (long long)batch * n_q;
   if (blocks == 0) return PC_OK;
-  if (blocks > 0x7fffffffLL) return PC_ERR_SHAPE;
+  if (blocks > 0x7fffffffLL - PC_GRID_X) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_ROPE_Q, st);
-  const dim3 grid((unsigned)blocks), block(256);
+  const dim3 grid = pc_grid_2d(blocks), block(256);
   const PcRope rope = pc_rope_factors(pos0 >= 0 ? base : 2.0f, D);
   if (D == 128)
-    hipLaunchKernelGGL(rope_q_kernel<128>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, n_q, n_heads,
-                       pos0, rope, (double)mul);
+    hipLaunchKernelGGL(rope_q_kernel<128>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, (int)blocks, n_q,
+                       n_heads, pos0, rope, (double)mul);
   else
-    hipLaunchKernelGGL(rope_q_kernel<64>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, n_q, n_heads,
-                       pos0, rope, (double)mul);
+    hipLaunchKernelGGL(rope_q_kernel<64>, grid, block, 0, st, (const uint16_t*)q, (uint16_t*)q_rot, (int)blocks, n_q,
+                       n_heads, pos0, rope, (double)mul);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
