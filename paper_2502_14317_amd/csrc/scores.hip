@@ -874,8 +874,10 @@ int pc_launch_scores(const pc_shape* s, const void* k, const int32_t* chunk_lens
   a.n_kb = (a.L + a.kb_keys - 1) / a.kb_keys;
   // pass 2 looks at context keys only.  A key's sum has one owner where four wavefronts share a column block: its blocks
   // have room for twice as many keys (36 x 3584 keys of 32 KV heads, 512 / 1024 keys: 300 / 277 us).  Blocks start at
-  // multiples of pass 1's, the angles are read anew there, so a score's bits do not depend on which size was taken (blocks
+  // multiples of pass 1's and the angles are read anew there, so blocks of 512 and of 1024 keys give the same bits (blocks
   // of equal size move the places where the angles' chains begin, and of two nearly equal scores the other is then kept).
+  // Smaller blocks, which calls of fewer or shorter chunks take in both passes, begin their chains elsewhere and cut pass 1's
+  // sums elsewhere: there the last bits differ.
   int kb2 = a.kb_keys;
   if (wpc == 4 && kb2 == kb_cap && key_blocks(s, 2 * kb2) >= 512) kb2 *= 2;
   const int n_kb2 = (a.w + kb2 - 1) / kb2;

@@ -50,3 +50,20 @@ def test_score_blocks(case):
             ref[:, :n], total = oracle.query_scores(qr, kr, n, obs, Hkv)
         assert_close(tok[c].cpu().numpy(), ref, S_ATOL, S_RTOL, f"tok_score c={c}")
         assert_close(chunk[c].cpu().numpy(), total, S_ATOL, S_RTOL, f"chunk_score c={c}")
+
+
+# Pass 1 takes 512 keys a workgroup in both calls, pass 2 1024 with all the chunks (512 workgroups of them) and 512 with some
+@pytest.mark.parametrize("C,some,w,wq,H,D", [(64, 48, 1300, 40, 4, 64), (128, 100, 1025, 40, 2, 128)], ids=["d64", "d128"])
+def test_blocks_of_512_and_1024_keys_give_the_same_bits(C, some, w, wq, H, D):
+    print("score blocks, bits", C, some, w, D, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    q, k = (torch.randn((C, w + wq, H, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    toks = []
+    for n in (C, some):
+        shape = pc.make_shape(n, w, wq, H, H, D, 32, 1.0e4)
+        tok = torch.full((n, H, w), float("nan"), dtype=torch.float32, device="cuda")
+        ws = pc.alloc_workspace(pc.pc_chunk_query_scores_workspace_bytes(shape))
+        pc.pc_chunk_query_scores(shape, q[:n], k[:n], tok, None, ws)
+        toks.append(tok)
+    torch.cuda.synchronize()
+    assert torch.equal(toks[0][:some], toks[1])
