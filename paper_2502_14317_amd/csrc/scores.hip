@@ -377,8 +377,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
         } else {
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int m = 8 * (r / 4) + 4 * hf + (r % 4);
-            const int key = key0 + (OWN ? Stage::RP * (m / Stage::RW) + Stage::RW * wave + m % Stage::RW : 32 * kb + m);
+            const int key = key0 + 32 * kb + 8 * (r / 4) + 4 * hf + (r % 4);
             sv[r] = (key <= my_qrow) ? s[r] : -INFINITY;
             tmax = fmaxf(tmax, sv[r]);
           }
