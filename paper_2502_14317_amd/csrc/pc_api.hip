@@ -747,9 +747,12 @@ static PcKvGroup image_group(const void* k, const void* v, const int32_t* len, i
 // visible key and 330 a widened one (turned to a loss of 520 where the widened keys pass the last-level cache and the
 // extra bytes count), and cost 4000 a copied row and a share of some 12 M pairs of 128 values a launch.  Fitted to 1358
 // calls (1 to 128 groups, 256 to 65536 keys, 17 to 32768 rows a group, tails of 0 to 65536 rows): at most 6 % and on
-// average not slower than rows, 1.5 % faster; images everywhere up to 2.7 times slower.  Rows / images (us), 32 / 8 heads
-// of 128 values, 8 x 2048 keys: 5 rows without a tail 64.6 / 62.2, tail of 8192 rows 69.5 / 78.1, 65536 132 / 250; 4
-// sequences x 512 rows 566 / 510, with a tail of 65536 rows 2601 / 2901.  Without segments nothing is widened: rows.
+// average not slower than rows, 1.5 % faster; images everywhere up to 2.7 times slower.  Then both rotated the query rows in a
+// launch in front; images have it in the widening launch now, so the line lies some microseconds on the rows' side: over 1100
+// calls measured since, its choice takes 1.7 % longer than the better of the two (3 % for those near the line).  0.3 M pairs a
+// launch would halve that, with single calls up to 5 % slower.  Rows / images now (us), 32 / 8 heads of 128 values, 8 x 2048
+// keys: 5 rows without a tail 65.1 / 59.7, tail of 8192 rows 69.3 / 74.9, 65536 105 / 209; 4 sequences x 512 rows 564 / 505,
+// with a tail of 65536 rows 2476 / 2729.  Without segments nothing is widened: rows.
 static bool widen_to_images(double groups, int D, double rows, double keys, int tail_cap, int n_self) {
   if (keys == 0.0) return false;
   const double per_launch = 1.2e7 * 128.0 / (groups * D), share = groups * keys * D / 3.2e8;

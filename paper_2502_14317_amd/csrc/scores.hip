@@ -336,7 +336,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
   for (int t = 0; t < n_tiles; ++t) {
     const int key0 = kblock * a.kb_keys + t * TILE;
     if (key0 >= stage_end) break;                         // uniform over the workgroup
-    // (a thread's angles go on for 16 tiles' items, 15 links of a chain, then they are read anew)
+    // (a thread's angles go on for 512 keys, 4 tiles: 16 items at 128 values, 15 links of a chain, 8 at 64; then they are read anew)
     if (OWN && t > 0 && t % (PC_SC_KB_MAX / 2 / TILE) == 0) keys.begin(a, tid, key0, pre);
     if (OWN) PC_SC_WAVE_LDS_SYNC(); else __syncthreads(); // previous tile fully consumed
     keys.stage(a, c, g, key0, k_hi, k_lo);
@@ -482,10 +482,10 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
 // Compiler's order -> slices, the passes alone (us): 4 chunks of 2011 rows, 203 voting, 32 / 8 heads 77 + 57 -> 67 + 46,
 // 12 138 + 125 -> 128 + 110, 16 x 7680, 512 voting 1460 + 1371 -> 1397 + 1293.  Minus the logsumexp as the products'
 // C operand (no subtraction in front of the exponentials) was 7 % faster in pass 2, at 0.2 % more error: not taken.
-// Measured, every query row voting, pass 1 with the pre-pass + pass 2, before (rounds of 128
-// columns over re-staged keys) and now: 12 ragged chunks of 2011 rows, 203 rows voting, 32 / 8 heads
-// 324 + 305 -> 215 + 154 us; 16 x 7680, 512 voting 2052 + 2081 -> 1487 + 1281; 36 x 3584, 32 / 32
-// heads 2805 + 2369 -> 3019 + 1834 (the pre-pass, 1.25 ms of memory traffic, no longer overlaps).
+// Every query row voting, pass 1 with the pre-pass + pass 2 (us), rounds of 128 columns over re-staged keys / the compiler's
+// order / now: 12 ragged chunks of 2011 rows, 203 rows voting, 32 / 8 heads 324 + 305 / 215 + 154 / 135 + 91; 16 x 7680, 512
+// voting 2052 + 2081 / 1487 + 1281 / 1335 + 1163; 36 x 3584, 32 / 32 heads 2805 + 2369 / 3019 + 1834 / 2807 + 1652 (the pre-pass,
+// 1.25 ms of memory traffic, does not overlap the products).
 template <int D, int PASS, int TILE>
 __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreArgs a) {
   constexpr int KS = D / 16, KSTRIDE = D + 8, NSUB = TILE / 32;
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
                      : __builtin_amdgcn_mfma_f32_32x32x16_bf16(cols, keys, c, 0, 0, 0);    // rows = voting rows, columns = keys
   };
   // Column block cb, and the last product's arithmetic of the block before it.  Behind its last use in the block an
-  // operand makes room for the next block's: seven k-steps before that needs it.
+  // operand makes room for the next block's: KS - 1 k-steps before that needs it.
   auto block = [&](auto mask_tag, auto products_tag, int cb) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
     constexpr int PRODUCTS = decltype(products_tag)::value;

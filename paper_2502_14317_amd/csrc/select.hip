@@ -128,7 +128,7 @@ int pc_launch_chunk_queue(const float* batch_score, int n_batch, int chunk_id0, 
 // ballots, no histogram: 8.5, 14.6 and 23.8.)  A bin of up to PC_SEL_FEW keys is ranked by counting instead of
 // another round: in a layer's launch 2011 tokens x 40 11.6 -> 10.3, 7680 x 64 17.1 -> 14.9, 3584 x 32 12.
 // The bins are cleared while the scores are on their way, and where a layer has few chunks the scores of all of them
-// are asked for before the chunk is known (one memory latency less): 1 chunk of 3584 tokens x 32 12.0 -> 9.8 us, 4 of
+// are asked for before the chunk is known (one memory latency less): 1 chunk of 3584 tokens x 32 12.0 -> 9.8 us (8.2 with its block sums asked for at once), 4 of
 // 512 x 16 7.1 -> 7.0; 12 chunks of 3584 x 32, their chunks known, 12.0 -> 10.5.
 // The layer's gather in the same launch where a segment is small (PC_SEL_GATHER bytes of K and V): the workgroup
 // copies the rows that it has just selected (16 segments of 128 rows of 64 values: 6.7 + 3.7 us -> 7.7).  One CU
