@@ -487,7 +487,7 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_kernel(PcScoreArgs a)
 // voting 2052 + 2081 / 1487 + 1281 / 1335 + 1163; 36 x 3584, 32 / 32 heads 2805 + 2369 / 3019 + 1834 / 2807 + 1652 (the pre-pass,
 // 1.25 ms of memory traffic, does not overlap the products).
 template <int D, int PASS, int TILE>
-__global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreArgs a) {
+__global__ __launch_bounds__(PC_SC_THREADS, D == 64 ? 3 : 2) void scores_many_kernel(PcScoreArgs a) {
   constexpr int KS = D / 16, KSTRIDE = D + 8, NSUB = TILE / 32;
   __shared__ __attribute__((aligned(16))) uint16_t k_hi[TILE * KSTRIDE];
   __shared__ __attribute__((aligned(16))) uint16_t k_lo[TILE * KSTRIDE];
@@ -674,6 +674,8 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
     }
   };
   auto blocks = [&](auto mask_tag, auto products_tag) __attribute__((always_inline)) {
+    // (an address of the branch's own: operand reads merged in front of the branches were in registers for all of them)
+    asm volatile("; operands of branch %1" : "+v"(k_at) : "n"(2 * decltype(products_tag)::value + decltype(mask_tag)::value));
 #pragma unroll
     for (int ks = 0; ks < AHEAD; ++ks) read_k(0, ks);
     // nothing before the first block: exponents that add nothing (pass 1: a sum that is dropped)
@@ -693,15 +695,21 @@ __global__ __launch_bounds__(PC_SC_THREADS, 2) void scores_many_kernel(PcScoreAr
   // KV head, 8 voting 76.1 / 64.9; 200 of 100 + 33, 32 / 8 heads, 33 voting 167.7 / 157.2; 60 ragged of 700 + 60, 60 voting
   // 154.7 / 147.1; no such tile in 12 of 2011 + 203, 2214 voting 2623 / 2598.
   if (wave < a.n_cb && n_keys > 0) {
-    auto run = [&](auto products_tag) __attribute__((always_inline)) {
-      if (unmasked && !(PASS == 1 && decltype(products_tag)::value < NSUB)) {    // (pass 1: such a tile ends the sequence)
-        blocks(std::false_type{}, products_tag);
-      } else {
-        if (PASS == 2) load_q(q_of(wave));                 // anew: kept for either branch the columns were in registers twice
-        blocks(std::true_type{}, products_tag);
-      }
-    };
-    if (NSUB == 2 || n_keys > 64) run(std::integral_constant<int, NSUB>{}); else run(std::integral_constant<int, 2>{});
+    // Columns in registers for several branches at once cost the third wavefront a SIMD at 64 values (prefill of 11 chunks of
+    // 2470 + 179 rows, 8 heads, all query rows voting: 186.7 -> 189.9 us).  So the short tiles' branch stands first, and pass 2
+    // loads a masked tile's columns anew, at 64 values a short one's too.  At 128 values LDS allows two wavefronts: there a
+    // short tile keeps the columns that are on their way (first call above: 65.4 us, anew 67.8).
+    if (NSUB > 2 && n_keys <= 64) {
+      if (PASS == 2 && D == 64) load_q(q_of(wave));
+      // (pass 1: such a tile ends the sequence, some row does not see all of it)
+      if (PASS == 2 && unmasked) blocks(std::false_type{}, std::integral_constant<int, 2>{});
+      else blocks(std::true_type{}, std::integral_constant<int, 2>{});
+    } else if (unmasked) {
+      blocks(std::false_type{}, std::integral_constant<int, NSUB>{});
+    } else {
+      if (PASS == 2) load_q(q_of(wave));
+      blocks(std::true_type{}, std::integral_constant<int, NSUB>{});
+    }
   } else if (PASS == 1) {
     for (int cb = wave; cb < a.n_cb; cb += PC_SC_WAVES) leave(cb);     // nobody looks at these keys
   }
