@@ -1029,6 +1029,8 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   }
 }
 
+#include "prefill_wide.h"
+
 template <int D, int MODE>
 __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_fwd_kernel(PcFlashArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -1055,6 +1057,25 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_both_kernel(PcFlashArg
   const int bid = blockIdx.x;
   if (bid >= front) flash_workgroup<D, PC_FA_LOCAL>(local, bid - front, smem);
   else if (bid < glob_blocks) flash_workgroup<D, PC_FA_ROWS>(global, bid, smem);
+}
+
+template <bool PAIR>
+__global__ __launch_bounds__(PC_FA_THREADS, 1) void flash_wide_kernel(PcFlashArgs a) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  int bid = blockIdx.x;
+  if (bid < a.sum_blocks) {
+    if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
+    return;
+  }
+  wide_workgroup<PAIR>(a, bid - a.sum_blocks, smem);
+}
+template <bool PAIR>
+__global__ __launch_bounds__(PC_FA_THREADS, 1) void flash_both_wide_kernel(PcFlashArgs local, PcFlashArgs global, int glob_blocks,
+                                                                           int front) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+  const int bid = blockIdx.x;
+  if (bid >= front) wide_workgroup<PAIR>(local, bid - front, smem);
+  else if (bid < glob_blocks) flash_workgroup<FW_D, PC_FA_ROWS>(global, bid, smem);
 }
 
 // The global part's reference follows the maximum at every tile there (window 0), as it starts anew in every part of
@@ -1087,6 +1108,47 @@ static long long flash_blocks(PcFlashArgs& a) {
   a.batch_div = pc_div_by(a.group_batch); a.last_div = pc_div_by(last);
   a.parts_div = pc_div_by(GLOBAL ? a.n_parts : 1);
   return (long long)a.n_seq * a.n_kv_heads * per_group;
+}
+
+// ---- 64 rows a wavefront (wide_workgroup)
+// Heads of a workgroup: the largest power of two up to 8 that divides the group; 1: rows of one head
+static int wide_heads(int G) { return G % 8 == 0 ? 8 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
+static long long wide_workgroups(int n_seq, int n_rows, int n_q_heads, int n_kv_heads) {
+  const int heads = wide_heads(n_q_heads / n_kv_heads), P = 256 / heads;
+  return (long long)n_seq * (n_q_heads / heads) * ((n_rows + P - 1) / P);
+}
+// Which local calls take it: a workgroup costs 12000 cycles around its loop that nothing else on its CU
+// hides, and 256 CUs hold one each, so it takes long rows and many of them.  Calls with the pre-pass (us, 32 rows a
+// wavefront / 64; sequences x rows): 32 / 8 heads, 1 x 1300 32.8 / 39.1, 2 x 1300 50.4 / 47.3, 36 x 1300 658 / 641,
+// 36 x 900 386 / 373, 36 x 600 206 / 215, 1 x 2000 50.6 / 55.1, 2 x 2000 85.1 / 78.4, 1 x 3000 88.5 / 84.2, 4 x 8192 1817 / 1672;
+// 16 / 4, 1 x 3000 68.7 / 68.7, 4 x 1300 51.0 / 46.9; 8 / 1, 4 x 2000 59.6 / 55.9; 4 / 2, 4 x 4096 90.2 / 99.6, 16 x 4096 287 / 265.
+// One head a workgroup, whose causal end is four tiles long: 32 / 32, 8 x 2000 371 / 403, 8 x 4096 1152 / 1155, 1 x
+// 4096 157 / 150, 1 x 8192 536 / 489, 8 x 8192 4004 / 3869.
+static bool wide_fits(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim) {
+  if (head_dim != FW_D) return false;
+  const int least = wide_heads(n_q_heads / n_kv_heads) > 1 ? 1280 : 6144;
+  return n_rows >= least && wide_workgroups(n_seq, n_rows, n_q_heads, n_kv_heads) >= 320;
+}
+static bool wide_fits(const PcFlashArgs& a) { return wide_fits(a.n_seq, a.n_rows, a.n_q_heads, a.n_kv_heads, a.head_dim); }
+// As flash_blocks.  Groups of fewer than two rounds of an XCD's 32 slots are interleaved up to two rounds: 16 x
+// 2000 rows, 32 / 8 heads, 573 -> 558 us.
+static long long wide_blocks(PcFlashArgs& a) {
+  const int G = a.n_q_heads / a.n_kv_heads;
+  a.wide_heads = wide_heads(G);
+  a.group = G / a.wide_heads;
+  const int P = 256 / a.wide_heads;
+  a.n_qt = (a.n_rows + P - 1) / P;
+  const long long per_group = (long long)a.n_qt * a.group, n_groups = (long long)a.n_seq * a.n_kv_heads, groups_xcd = n_groups / 8;
+  a.group_batch = 1;
+  if (per_group < 64 && groups_xcd > 1) {
+    const long long m = (64 + per_group - 1) / per_group, batches = (groups_xcd + m - 1) / m;
+    a.group_batch = (int)((groups_xcd + batches - 1) / batches);
+  }
+  a.group_div = pc_div_by(a.group); a.heads_div = pc_div_by(a.n_kv_heads);
+  a.per_batch_div = pc_div_by((int)(a.group_batch * per_group));
+  a.batch_div = pc_div_by(a.group_batch); a.last_div = pc_div_by((int)(groups_xcd % a.group_batch));
+  a.rest_div = pc_div_by((int)(n_groups % 8));
+  return n_groups * per_group;
 }
 
 // image loads address one (sequence, head) region with 32-bit byte offsets
@@ -1127,7 +1189,38 @@ static int launch_flash_both_t(const PcFlashArgs& local, const PcFlashArgs& glob
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
+template <bool PAIR>
+static int launch_wide_t(const PcFlashArgs& args, hipStream_t st) {
+  PcFlashArgs a = args;
+  static std::atomic<uint64_t> raised{0};
+  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_wide_kernel<PAIR>, FW_LDS_BYTES, raised);
+  if (lds_rc != PC_OK) return lds_rc;
+  a.sum_blocks = a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
+  const long long blocks = wide_blocks(a) + a.sum_blocks;
+  if (blocks > 0x7fffffffLL || images_too_long(a)) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_FLASH, st);
+  hipLaunchKernelGGL(flash_wide_kernel<PAIR>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, a);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
+template <bool PAIR>
+static int launch_both_wide_t(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
+  PcFlashArgs l = local, g = global;
+  static_assert(FlashSmem<FW_D>::BYTES <= FW_LDS_BYTES, "both fit");
+  static std::atomic<uint64_t> raised{0};
+  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_both_wide_kernel<PAIR>, FW_LDS_BYTES, raised);
+  if (lds_rc != PC_OK) return lds_rc;
+  const long long glob_blocks = flash_blocks<true>(g), front = (glob_blocks + 7) / 8 * 8, blocks = front + wide_blocks(l);
+  if (blocks > 0x7fffffffLL || images_too_long(l)) return PC_ERR_SHAPE;
+  PcProfScope prof(PC_KERNEL_FLASH, st);
+  hipLaunchKernelGGL(flash_both_wide_kernel<PAIR>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, l, g, (int)glob_blocks, (int)front);
+  PC_LAUNCH_CHECK();
+  return PC_OK;
+}
 int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
+  if (wide_fits(local))
+    return wide_heads(local.n_q_heads / local.n_kv_heads) > 1 ? launch_both_wide_t<true>(local, global, st)
+                                                              : launch_both_wide_t<false>(local, global, st);
   return local.head_dim == 128 ? launch_flash_both_t<128>(local, global, st) : launch_flash_both_t<64>(local, global, st);
 }
 
@@ -1138,12 +1231,16 @@ int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hi
 // 32 heads, 1 x 1792 kept: 1 part 227 / 2 parts 235, 4 244; 12 x 2011 + 203, 32 / 8, 5 x 701: 1 626 / 2 629, 4 634; 4 x 4096 +
 // 128, 32 / 8, 4 x 3000: 1 626 / 2 630, 16 639; 2 x 3000 + 64, 32 / 8, 2 x 2500: 2 212 / 1 227, 4 214, 16 226; 8 x 1500 + 512, 16 /
 // 4, 8 x 1400: 3 254 / 1 356, 2 257, 8 267; 1 x 1000 + 24, 24 / 8 of 64 values, 1 x 900: 2 49.7 / 1 54.9, 3 48.3, 16 51.9.
+// With 64 rows a wavefront 256 slots, 8 us + 1.45 a tile (local), and the global ones have their CU to themselves (1.27).
 int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most) {
-  const double loc_us = head_dim == 128 ? 1.54 : 1.0, glob_us = head_dim == 128 ? 2.1 : 1.4;
+  const bool wide = wide_fits(n_seq, n_rows, n_q_heads, n_kv_heads, head_dim);
+  const int heads = wide ? wide_heads(n_q_heads / n_kv_heads) : 1, rows = wide ? 256 / heads : PC_FA_BM;
+  const double loc_us = wide ? 1.45 : head_dim == 128 ? 1.54 : 1.0, glob_us = wide ? 1.27 : head_dim == 128 ? 2.1 : 1.4;
+  const double slots = wide ? 256.0 : 512.0, start_us = wide ? 8.0 : 10.0;
   double work = 0.0, longest = 0.0;
-  for (int r0 = 0; r0 < n_rows; r0 += PC_FA_BM) {
-    const double us = 10.0 + loc_us * ((std::min(n_rows, r0 + PC_FA_BM) + 63) / 64);
-    work += us * n_seq * n_q_heads;
+  for (int r0 = 0; r0 < n_rows; r0 += rows) {
+    const double us = start_us + loc_us * ((std::min(n_rows, r0 + rows) + 63) / 64);
+    work += us * n_seq * (n_q_heads / heads);
     longest = us;
   }
   const long long wgs = (long long)n_kv_heads * (((long long)n_q * (n_q_heads / n_kv_heads) + PC_FA_BM - 1) / PC_FA_BM);
@@ -1152,13 +1249,15 @@ int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_
   double best = 0.0;
   for (int p = 1; p <= most && p <= n_tiles; ++p) {
     const double each = 10.0 + glob_us * (double)((n_tiles + p - 1) / p);
-    const double us = std::max((work + each * (double)(wgs * p)) / 512.0, std::max(longest, each)) + (p > 1 ? 5.0 + merge_us * p : 0.0);
+    const double us = std::max((work + each * (double)(wgs * p)) / slots, std::max(longest, each)) + (p > 1 ? 5.0 + merge_us * p : 0.0);
     if (p == 1 || us < best) { best = us; best_p = p; }
   }
   return best_p;
 }
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
+  if (!a.global && wide_fits(a))
+    return wide_heads(a.n_q_heads / a.n_kv_heads) > 1 ? launch_wide_t<true>(a, st) : launch_wide_t<false>(a, st);
   if (a.head_dim == 128)
     return !a.global ? launch_flash_t<128, PC_FA_LOCAL>(a, st)
                      : (a.images ? launch_flash_t<128, PC_FA_IMAGES>(a, st) : launch_flash_t<128, PC_FA_ROWS>(a, st));
