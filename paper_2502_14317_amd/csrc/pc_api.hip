@@ -761,7 +761,8 @@ static bool widen_to_images(double groups, int D, double rows, double keys, int 
 
 // Eq. 9-11 for a block of query rows over the 8-bit cache: the segments are widened in the workspace (code * scale,
 // rounded to bf16), to rows or, with everything else, to tile images; then one launch of the tile kernel as
-// for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].  The same bits either way.
+// for a 16-bit cache: [segments ; 16-bit tail (all its rows visible) ; causal self segment].  The same bits either way,
+// except where images are long enough for 64 rows a wavefront (other sums of the same products, wide_workgroup).
 static int parallel_attn_fp8_tiles(const void* q, const void* k8, const void* v8, const float* k_scale,
                                    const float* v_scale, const int32_t* seg_len, int seg_len_per_head,
                                    const void* k_tail, const void* v_tail, const int32_t* tail_len,

@@ -1059,7 +1059,7 @@ __global__ __launch_bounds__(PC_FA_THREADS, 2) void flash_both_kernel(PcFlashArg
   else if (bid < glob_blocks) flash_workgroup<D, PC_FA_ROWS>(global, bid, smem);
 }
 
-template <bool PAIR>
+template <int MODE>
 __global__ __launch_bounds__(PC_FA_THREADS, 1) void flash_wide_kernel(PcFlashArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   int bid = blockIdx.x;
@@ -1067,14 +1067,14 @@ __global__ __launch_bounds__(PC_FA_THREADS, 1) void flash_wide_kernel(PcFlashArg
     if (bid < a.n_seq) pc_chunk_sum(a.sum.blk_sum, a.sum.chunk_score, a.sum.per_chunk, bid, (float*)smem);
     return;
   }
-  wide_workgroup<PAIR>(a, bid - a.sum_blocks, smem);
+  wide_workgroup<MODE>(a, bid - a.sum_blocks, smem);
 }
-template <bool PAIR>
+template <int MODE>
 __global__ __launch_bounds__(PC_FA_THREADS, 1) void flash_both_wide_kernel(PcFlashArgs local, PcFlashArgs global, int glob_blocks,
                                                                            int front) {
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   const int bid = blockIdx.x;
-  if (bid >= front) wide_workgroup<PAIR>(local, bid - front, smem);
+  if (bid >= front) wide_workgroup<MODE>(local, bid - front, smem);
   else if (bid < glob_blocks) flash_workgroup<FW_D, PC_FA_ROWS>(global, bid, smem);
 }
 
@@ -1129,15 +1129,34 @@ static bool wide_fits(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int 
   const int least = wide_heads(n_q_heads / n_kv_heads) > 1 ? 1280 : 6144;
   return n_rows >= least && wide_workgroups(n_seq, n_rows, n_q_heads, n_kv_heads) >= 320;
 }
+// ... and which block attentions over tile images (the 8-bit cache), in the same parts: where 32 rows a wavefront put
+// two workgroups on a CU (one alone has its LDS to itself: nothing to gain), over runs worth the start.  Whole cache
+// build and attention (us, 32 rows a wavefront / 64), sequences x segments x keys, rows: 32 / 8 heads, 4 x 8 x 2048, 512
+// 702 / 645; 2 x 8 x 2048, 512 378 / 354; 4 x 8 x 2048, 300 548 / 517; 4 x 8 x 600, 512 253 / 241; 16 / 4, 4 x 3 x 1500, 512 140 / 135;
+// 32 / 32, 4 x 8 x 520, 512 427 / 417; 3 x 5 x 1000, 170 305 / 307.
+static bool wide_images_fits(const PcFlashArgs& a) {
+  const long long G = a.n_q_heads / a.n_kv_heads;
+  const long long n = (long long)a.n_seq * a.n_kv_heads * ((a.n_rows * G + PC_FA_BM - 1) / PC_FA_BM) * a.n_parts;
+  long long tiles = 0;
+  for (const PcKvGroup& kg : a.grp) tiles += (long long)kg.n * ((kg.cap + 63) / 64);
+  return a.images && a.head_dim == FW_D && n > 256 && tiles >= 64;
+}
 static bool wide_fits(const PcFlashArgs& a) { return wide_fits(a.n_seq, a.n_rows, a.n_q_heads, a.n_kv_heads, a.head_dim); }
 // As flash_blocks.  Groups of fewer than two rounds of an XCD's 32 slots are interleaved up to two rounds: 16 x
 // 2000 rows, 32 / 8 heads, 573 -> 558 us.
 static long long wide_blocks(PcFlashArgs& a) {
   const int G = a.n_q_heads / a.n_kv_heads;
-  a.wide_heads = wide_heads(G);
+  a.wide_heads = a.global ? 1 : wide_heads(G);               // (global: packed rows)
   a.group = G / a.wide_heads;
   const int P = 256 / a.wide_heads;
-  a.n_qt = (a.n_rows + P - 1) / P;
+  a.n_qt = (int)(((a.global ? (long long)a.n_rows * G : a.n_rows) + P - 1) / P);
+  if (a.global) {
+    a.group_batch = 1;
+    a.group_div = pc_div_by(G); a.heads_div = pc_div_by(a.n_kv_heads); a.qt_div = pc_div_by(a.n_qt);
+    a.parts_div = pc_div_by(a.n_parts); a.per_batch_div = pc_div_by(a.n_qt * a.n_parts);
+    a.batch_div = a.last_div = pc_div_by(1); a.rest_div = pc_div_by((int)((long long)a.n_seq * a.n_kv_heads % 8));
+    return (long long)a.n_seq * a.n_kv_heads * a.n_qt * a.n_parts;
+  }
   const long long per_group = (long long)a.n_qt * a.group, n_groups = (long long)a.n_seq * a.n_kv_heads, groups_xcd = n_groups / 8;
   a.group_batch = 1;
   if (per_group < 64 && groups_xcd > 1) {
@@ -1189,38 +1208,38 @@ static int launch_flash_both_t(const PcFlashArgs& local, const PcFlashArgs& glob
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
-template <bool PAIR>
+template <int MODE>
 static int launch_wide_t(const PcFlashArgs& args, hipStream_t st) {
   PcFlashArgs a = args;
   static std::atomic<uint64_t> raised{0};
-  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_wide_kernel<PAIR>, FW_LDS_BYTES, raised);
+  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_wide_kernel<MODE>, FW_LDS_BYTES, raised);
   if (lds_rc != PC_OK) return lds_rc;
-  a.sum_blocks = a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
+  a.sum_blocks = !a.global && a.sum.chunk_score ? (a.n_seq + 7) / 8 * 8 : 0;
   const long long blocks = wide_blocks(a) + a.sum_blocks;
-  if (blocks > 0x7fffffffLL || images_too_long(a)) return PC_ERR_SHAPE;
+  if (blocks > 0x7fffffffLL || (!a.global && images_too_long(a))) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_FLASH, st);
-  hipLaunchKernelGGL(flash_wide_kernel<PAIR>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, a);
+  hipLaunchKernelGGL(flash_wide_kernel<MODE>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, a);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
-template <bool PAIR>
+template <int MODE>
 static int launch_both_wide_t(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
   PcFlashArgs l = local, g = global;
   static_assert(FlashSmem<FW_D>::BYTES <= FW_LDS_BYTES, "both fit");
   static std::atomic<uint64_t> raised{0};
-  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_both_wide_kernel<PAIR>, FW_LDS_BYTES, raised);
+  const int lds_rc = pc_raise_dynamic_lds((const void*)flash_both_wide_kernel<MODE>, FW_LDS_BYTES, raised);
   if (lds_rc != PC_OK) return lds_rc;
   const long long glob_blocks = flash_blocks<true>(g), front = (glob_blocks + 7) / 8 * 8, blocks = front + wide_blocks(l);
   if (blocks > 0x7fffffffLL || images_too_long(l)) return PC_ERR_SHAPE;
   PcProfScope prof(PC_KERNEL_FLASH, st);
-  hipLaunchKernelGGL(flash_both_wide_kernel<PAIR>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, l, g, (int)glob_blocks, (int)front);
+  hipLaunchKernelGGL(flash_both_wide_kernel<MODE>, dim3((unsigned)blocks), dim3(PC_FA_THREADS), FW_LDS_BYTES, st, l, g, (int)glob_blocks, (int)front);
   PC_LAUNCH_CHECK();
   return PC_OK;
 }
 int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
   if (wide_fits(local))
-    return wide_heads(local.n_q_heads / local.n_kv_heads) > 1 ? launch_both_wide_t<true>(local, global, st)
-                                                              : launch_both_wide_t<false>(local, global, st);
+    return wide_heads(local.n_q_heads / local.n_kv_heads) > 1 ? launch_both_wide_t<PC_FW_PAIR>(local, global, st)
+                                                              : launch_both_wide_t<PC_FW_HEAD>(local, global, st);
   return local.head_dim == 128 ? launch_flash_both_t<128>(local, global, st) : launch_flash_both_t<64>(local, global, st);
 }
 
@@ -1256,8 +1275,9 @@ int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_
 }
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
+  if (a.global && wide_images_fits(a)) return launch_wide_t<PC_FW_IMAGES>(a, st);
   if (!a.global && wide_fits(a))
-    return wide_heads(a.n_q_heads / a.n_kv_heads) > 1 ? launch_wide_t<true>(a, st) : launch_wide_t<false>(a, st);
+    return wide_heads(a.n_q_heads / a.n_kv_heads) > 1 ? launch_wide_t<PC_FW_PAIR>(a, st) : launch_wide_t<PC_FW_HEAD>(a, st);
   if (a.head_dim == 128)
     return !a.global ? launch_flash_t<128, PC_FA_LOCAL>(a, st)
                      : (a.images ? launch_flash_t<128, PC_FA_IMAGES>(a, st) : launch_flash_t<128, PC_FA_ROWS>(a, st));

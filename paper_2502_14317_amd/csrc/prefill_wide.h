@@ -20,22 +20,29 @@
 // products after its last one), one between an exponential and the use of its result (the group after it).
 // tests/test_wide_attn_host.py looks for all three in the compiled code.
 //
-// PAIR: the workgroup takes `wide_heads` query heads of a KV head (2, 4 or 8) at 256 / wide_heads positions,
+// PC_FW_PAIR: the workgroup takes `wide_heads` query heads of a KV head (2, 4 or 8) at 256 / wide_heads positions,
 // a wavefront two heads at 32 positions: one rotation table row, one mask and one causal end for both blocks.
-// Otherwise 256 positions of one head, 64 a wavefront.
+// PC_FW_HEAD: 256 positions of one head, 64 a wavefront.
+// PC_FW_IMAGES: flash_workgroup's mode of that name, rows of a KV group packed, parts and all: 4 x 512 rows of 32 / 8
+// heads over 8 x 2048 keys of the 8-bit cache 702 -> 645 us with everything else of the call, 3 sequences (two parts)
+// 567 -> 538, 2 x 512 of 32 / 32 714 -> 688.  Loads follow a walk over the segments' tiles that runs three ahead.
 #define PC_FW_RING 4                 // tiles of K and of V^T in LDS, 128 KiB
 constexpr int FW_D = 128, FW_TILE = 64 * FW_D;               // elements of a tile image
 constexpr int FW_LDS_BYTES = 2 * PC_FW_RING * FW_TILE * 2;
 
-template <bool PAIR>
+#define PC_FW_PAIR 0
+#define PC_FW_HEAD 1
+#define PC_FW_IMAGES 2
+template <int MODE>
 __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, uint16_t* smem) {
+  constexpr bool PAIR = MODE == PC_FW_PAIR, IMAGES = MODE == PC_FW_IMAGES;
   constexpr int D = FW_D, KS = D / 16, DB = D / 32, HALF = D / 2, NB = 2, NM = NB * KS;
   // ---- which (sequence, KV head), Q tile and heads: as flash_workgroup; a.group workgroups share a Q tile.  The
   //      groups that share an XCD change places from turn to turn: an XCD hands every fourth workgroup to the same
   //      shader engine, in order, and with a short sequence always in the same place two engines got all the
   //      padding (12 ragged chunks of 2214 rows 332 -> 309 us).  The groups beyond a multiple of 8 are dealt to
   //      all XCDs in the same way, long Q tiles of all of them first.
-  const int n_qt = a.n_qt, per_group = a.group * n_qt;
+  const int n_qt = a.n_qt, per_group = (IMAGES ? a.n_parts : a.group) * n_qt;
   const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
   int cg, within;
   if (bid < full_blocks) {
@@ -52,21 +59,89 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     cg = n_groups / 8 * 8 + pc_mod(rest - within * n_rest + within, n_rest, a.rest_div);
   }
   const int seq = pc_div(cg, a.heads_div), g = cg - seq * a.n_kv_heads;
-  const int turn = pc_div(within, a.group_div);
+  const int turn = pc_div(within, IMAGES ? a.qt_div : a.group_div);        // (IMAGES: the part)
   const int HW = PAIR ? a.wide_heads : 1, P_WG = 256 / HW;
   constexpr int POS_W = PAIR ? 32 : 64;                      // positions of a wavefront
   const int tid = threadIdx.x, lane = tid % PC_WAVE, wave = __builtin_amdgcn_readfirstlane(tid / PC_WAVE);
   const int hf = lane / 32, n = lane % 32;
-  const int pos0_wg = (n_qt - 1 - turn) * P_WG;
-  const int seq_rows = a.seq_ctx ? min(max(a.seq_ctx[seq], 0), a.n_rows - a.seq_add) + a.seq_add : a.n_rows;
+  const int pos0_wg = (IMAGES ? within - turn * n_qt : n_qt - 1 - turn) * P_WG;
+  const int seq_rows = IMAGES ? a.n_rows * a.group
+                              : (a.seq_ctx ? min(max(a.seq_ctx[seq], 0), a.n_rows - a.seq_add) + a.seq_add : a.n_rows);
   if (pos0_wg >= seq_rows) return;                           // padding rows (uniform over the workgroup)
-  const int pos0 = pos0_wg + 32 * (2 * wave / HW);           // the wavefront's first position and head
-  const int h = (g * a.group + within - turn * a.group) * HW + (PAIR ? 2 * wave % HW : 0);
-  const int T = (min(seq_rows, pos0_wg + P_WG) + 63) / 64;   // key tiles
+  const int pos0 = pos0_wg + 32 * (2 * wave / HW);           // the wavefront's first position (IMAGES: packed row) and head
+  const int h = IMAGES ? g * a.group : (g * a.group + within - turn * a.group) * HW + (PAIR ? 2 * wave % HW : 0);
+  int T = (min(seq_rows, pos0_wg + P_WG) + 63) / 64;         // key tiles
   const int J0 = (min(pos0_wg, seq_rows - 1) + 1) / 32;      // steps of 32 keys that every row sees whole
   int max_key[NB];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) max_key[nb] = min(pos0 + (PAIR ? 0 : 32 * nb) + n, seq_rows - 1);
+  for (int nb = 0; nb < NB; ++nb) {
+    max_key[nb] = min(pos0 + (PAIR ? 0 : 32 * nb) + n, seq_rows - 1);
+    if (IMAGES) max_key[nb] = pc_div(max_key[nb], a.group_div);        // the row's query
+  }
+  // IMAGES: a walk over the segments' tiles, those that every row sees whole first (as flash_workgroup's cursor).
+  // A tile's limits: valid keys from its first one, that key's position where the segment is causal.
+  struct Limit { int cut, c0; bool seg_start; };
+  struct Walk { const uint16_t* k; const uint16_t* v; Limit lim; int c0_step, in_seg, in_phase, left, grp, seg; bool masked; };
+  Walk cur = {};
+  int run_full = 0, masked_lo = 0;                           // unmasked tiles of the run; its first masked tile
+  const int wg_t0 = pc_div(pos0_wg, a.group_div), wg_t1 = pc_div(min(pos0_wg + 256, seq_rows) - 1, a.group_div);
+  auto walk_place = [&](int tile, int len) __attribute__((always_inline)) {  // tile: among the segment's of this kind
+    const PcKvGroup& kg = a.grp[cur.grp];
+    const int idx = tile + (cur.masked ? pc_full_tiles(kg, len, wg_t0) : 0);
+    const long long at = seq * kg.seq_stride + cur.seg * kg.seg_stride + g * kg.head_stride + (long long)FW_TILE * idx;
+    cur.k = (const uint16_t*)kg.k + at; cur.v = (const uint16_t*)kg.v + at;
+    cur.lim = {len - 64 * idx, kg.causal ? 64 * idx : -(1 << 28), idx == 0};
+    cur.c0_step = kg.causal ? 64 : 0;
+    cur.in_seg = pc_seg_tiles(kg, len, wg_t0, wg_t1, cur.masked) - tile;
+  };
+  auto walk_seek = [&](int rel) __attribute__((always_inline)) {             // to tile `rel` of this kind
+    int tile = 0, len = 0;
+    for (cur.grp = 0; cur.grp < PC_KV_GROUPS; ++cur.grp) {
+      const int nt = a.grp[cur.grp].n > 0 ? pc_kv_tiles(a.grp[cur.grp], seq, g, a.n_kv_heads, wg_t0, wg_t1, cur.masked, lane) : 0;
+      if (rel < nt) break;
+      rel -= nt;
+    }
+    pc_kv_find(a.grp[cur.grp], seq, g, a.n_kv_heads, wg_t0, wg_t1, cur.masked, lane, rel, cur.seg, tile, len);
+    walk_place(tile, len);
+  };
+  auto walk_next = [&]() __attribute__((always_inline)) {    // stays on the run's last tile
+    if (cur.left <= 1) return;
+    --cur.left; --cur.in_phase;
+    if (cur.in_phase > 0 && --cur.in_seg > 0) {
+      cur.k += FW_TILE; cur.v += FW_TILE;
+      cur.lim.cut -= 64; cur.lim.c0 += cur.c0_step; cur.lim.seg_start = false;
+    } else if (cur.in_phase > 0) {
+      int len;
+      do {                                                   // the next segment that has tiles of this kind
+        if (++cur.seg >= a.grp[cur.grp].n) { cur.seg = 0; ++cur.grp; }
+        len = a.grp[cur.grp].n > 0 ? __builtin_amdgcn_readfirstlane(pc_seg_len(a.grp[cur.grp], seq, g, a.n_kv_heads, cur.seg)) : 0;
+      } while (len == 0 || pc_seg_tiles(a.grp[cur.grp], len, wg_t0, wg_t1, cur.masked) == 0);
+      walk_place(0, len);
+    } else {
+      cur.masked = true;
+      cur.in_phase = cur.left;
+      walk_seek(masked_lo);
+    }
+  };
+  if (IMAGES) {
+    int n_full = 0, n_masked = 0;
+    for (int i = 0; i < PC_KV_GROUPS; ++i)
+      if (a.grp[i].n > 0) {
+        n_full += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, false, lane);
+        n_masked += pc_kv_tiles(a.grp[i], seq, g, a.n_kv_heads, wg_t0, wg_t1, true, lane);
+      }
+    // every part takes an equal run of all tiles, as in flash_workgroup
+    const int lo = pc_div((n_full + n_masked) * turn, a.parts_div), hi = pc_div((n_full + n_masked) * (turn + 1), a.parts_div);
+    T = cur.left = hi - lo;
+    run_full = max(0, min(hi, n_full) - lo);
+    masked_lo = max(0, lo - n_full);
+    if (T > 0) {
+      cur.masked = run_full == 0;
+      cur.in_phase = cur.masked ? T : run_full;
+      walk_seek(cur.masked ? masked_lo : lo);
+    }
+  }
+  Limit lim0 = cur.lim, lim1 = {}, lim2 = {};                // of tiles p, p + 1, p + 2
 
   // ---- tile loads: wavefront w copies bytes 4096 w .. of a tile image, 1 KiB an instruction (the immediate
   //      offset counts on both sides).  Tile t lives in slot t % 4; images behind the last one read as zeros.
@@ -78,8 +153,9 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint16_t*)a.v_img + img0), 0, n_img * IMG_BYTES, 0x00020000);
   const int ld_goff = 4096 * wave + 16 * lane;
   uint16_t* const v_area = smem + PC_FW_RING * FW_TILE;
-#define FW_LOAD_K(t, i) __builtin_amdgcn_raw_ptr_buffer_load_lds(k_rsrc, (lptr_t)(smem + ((t) & 3) * FW_TILE + 2048 * wave), 16, ld_goff, (t) * IMG_BYTES, 1024 * (i), 0)
-#define FW_LOAD_V(t, i) __builtin_amdgcn_raw_ptr_buffer_load_lds(v_rsrc, (lptr_t)(v_area + ((t) & 3) * FW_TILE + 2048 * wave), 16, ld_goff, (t) * IMG_BYTES, 1024 * (i), 0)
+  // (IMAGES: tile t is the one that the walk is on)
+#define FW_LOAD_K(t, i) __builtin_amdgcn_raw_ptr_buffer_load_lds(IMAGES ? __builtin_amdgcn_make_buffer_rsrc((void*)cur.k, 0, IMG_BYTES, 0x00020000) : k_rsrc, (lptr_t)(smem + ((t) & 3) * FW_TILE + 2048 * wave), 16, ld_goff, IMAGES ? 0 : (t) * IMG_BYTES, 1024 * (i), 0)
+#define FW_LOAD_V(t, i) __builtin_amdgcn_raw_ptr_buffer_load_lds(IMAGES ? __builtin_amdgcn_make_buffer_rsrc((void*)cur.v, 0, IMG_BYTES, 0x00020000) : v_rsrc, (lptr_t)(v_area + ((t) & 3) * FW_TILE + 2048 * wave), 16, ld_goff, IMAGES ? 0 : (t) * IMG_BYTES, 1024 * (i), 0)
 #define FW_LOAD4(M, t) do { M(t, 0); M(t, 1); M(t, 2); M(t, 3); } while (0)
 
   // ---- queries, as flash_workgroup fetches, stages (slots 2 and 3 of V) and rotates them, a block after the other.
@@ -90,28 +166,33 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   constexpr int PPR = D / 8, RPL = PC_WAVE / PPR, NLD = 32 / RPL;
   const int rows_left = min(seq_rows - pos0, POS_W);
   const int qo_stride = a.n_q_heads * (2 * D);
+  auto row_at = [&](int r) __attribute__((always_inline)) {  // (IMAGES) a packed row in [row, head] of q and output
+    return ((long long)seq * a.n_rows + pc_div(r, a.group_div)) * a.n_q_heads + h + pc_mod(r, a.group, a.group_div);
+  };
   const int qo_bytes = rows_left > 0 ? (rows_left - 1) * qo_stride + (PAIR ? 2 * D * NB : 2 * D) : 0;
   const int nb_step = PAIR ? 2 * D : 32 * qo_stride;         // bytes from a row of block 0 to block 1's
   const long long qo_at = (((long long)seq * a.n_rows + (rows_left > 0 ? pos0 : 0)) * a.n_q_heads + h) * D;
   const int l_row = lane / PPR, l_piece = lane % PPR, qo_off = l_row * qo_stride + 16 * l_piece;
   {
     uint16_t* st_q = v_area + 2 * FW_TILE + wave * (32 * D);
-    u32x4 rq[NB][NLD], cs[PAIR ? 1 : NB][KS / 2][4];
+    u32x4 rq[NB][NLD], cs[PAIR || IMAGES ? 1 : NB][IMAGES ? 1 : KS / 2][4];
     const __amdgpu_buffer_rsrc_t q_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((const uint16_t*)a.q + qo_at), 0, qo_bytes, 0x00020000);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) rq[nb][i] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, qo_off, RPL * i * qo_stride + nb * nb_step, PC_BUF_NT);
+      for (int i = 0; i < NLD; ++i)
+        rq[nb][i] = IMAGES ? pc_load_once((const u32x4*)((const uint16_t*)a.q + row_at(min(pos0 + 32 * nb + RPL * i + l_row, seq_rows - 1)) * D + 8 * l_piece))
+                           : __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, qo_off, RPL * i * qo_stride + nb * nb_step, PC_BUF_NT);
     const __amdgpu_buffer_rsrc_t t_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.table, 0, HALF * a.table_rows * 8, 0x00020000);
     const int t_off = 16 * (4 * hf * a.table_rows + pos0 + n);
 #pragma unroll
-    for (int nb = 0; nb < (PAIR ? 1 : NB); ++nb)
+    for (int nb = 0; nb < (IMAGES ? 0 : PAIR ? 1 : NB); ++nb)
 #pragma unroll
-      for (int ks = 0; ks < KS / 2; ++ks)
+      for (int ks = 0; ks < (IMAGES ? 0 : KS / 2); ++ks)
 #pragma unroll
         for (int e = 0; e < 4; ++e) cs[nb][ks][e] = __builtin_amdgcn_raw_buffer_load_b128(t_rsrc, t_off, 16 * (8 * ks + e) * a.table_rows + 512 * nb, 0);
     __builtin_amdgcn_sched_barrier(0);
-    FW_LOAD4(FW_LOAD_K, 0); FW_LOAD4(FW_LOAD_V, 0);
+    if (!IMAGES || T > 0) { FW_LOAD4(FW_LOAD_K, 0); FW_LOAD4(FW_LOAD_V, 0); }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)                          // (O is cleared while they are on their way)
@@ -132,12 +213,22 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       PC_FA_WAVE_LDS_SYNC();
       if (nb == 0) {
         __builtin_amdgcn_sched_barrier(0);
-        FW_LOAD4(FW_LOAD_K, 1); FW_LOAD4(FW_LOAD_V, 1); FW_LOAD4(FW_LOAD_K, 2);
+        if (!IMAGES || T > 0) {
+          if (IMAGES) { walk_next(); lim1 = cur.lim; }
+          FW_LOAD4(FW_LOAD_K, 1); FW_LOAD4(FW_LOAD_V, 1);
+          if (IMAGES) { walk_next(); lim2 = cur.lim; }
+          FW_LOAD4(FW_LOAD_K, 2);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
       auto piece = [&](int p) __attribute__((always_inline)) { return *(const u32x4*)(st_q + (n * PPR + (p ^ (n % PPR))) * 8); };
 #pragma unroll
-      for (int ks = 0; ks < KS / 2; ++ks) {
+      for (int ks = 0; ks < (IMAGES ? KS : 0); ++ks) {
+        const u32x4 x = piece(2 * ks + hf);
+        bq[nb][ks] = *(const bf16x8*)&x;
+      }
+#pragma unroll
+      for (int ks = 0; ks < (IMAGES ? 0 : KS / 2); ++ks) {
         const u32x4 x1 = piece(2 * ks + hf), x2 = piece(2 * ks + hf + PPR / 2);
         u32x4 ra, rbv;
 #pragma unroll
@@ -157,7 +248,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   floatx16 negm[NB], s_buf[2][NB];                           // -reference, the C operand of every S^T; [step parity] S^T
   u32x4 p_buf[2][NB][2];                                     // [step parity] P^T
   bf16x8 ka[KS], va[2][DB];
-  float m_run[NB], l_run[NB];
+  float m_run[NB] = {0.f, 0.f}, l_run[NB] = {0.f, 0.f};
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
@@ -202,13 +293,14 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       }
     }
   };
-  auto mask_step = [&](int k0, floatx16(&s)[NB]) __attribute__((always_inline)) {
+  // k0: the step's first key (IMAGES: counted from the tile's first)
+  auto mask_step = [&](int k0, const Limit& lim, floatx16(&s)[NB]) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = k0 + 16 * (r / 8) + 8 * hf + (r % 8);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
-        if (key > max_key[nb]) s[nb][r] = -INFINITY;
+        if (key > (IMAGES ? min(lim.cut - 1, max_key[nb] - lim.c0) : max_key[nb])) s[nb][r] = -INFINITY;
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -219,13 +311,12 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   // its first product.  LD: tile t_ld is asked for, 1 K, 2 V.
   // The window is 2^10 where flash_workgroup's is 2^8: a rescale holds up all four wavefronts (200 cycles a
   // tile on average at 2^8, logits of deviation 2), and O^T and the sums stay far inside the range of fp32.
-  auto step = [&](auto mask_tag, auto has_qk, auto bar_tag, auto ld_tag, int j, int t_ld, floatx16(&s_cur)[NB],
+  auto step = [&](auto mask_tag, auto has_qk, auto bar_tag, auto ld_tag, const Limit& lim, int j, int t_ld, floatx16(&s_cur)[NB],
                   floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2], const u32x4(&p_prev)[NB][2]) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value, QK = decltype(has_qk)::value, BAR = decltype(bar_tag)::value;
     constexpr int LD = decltype(ld_tag)::value;
-    float t[NB], pr[16 * NB];
-    unsigned long long grow = 0;
-    if (MASK) mask_step(32 * j, s_cur);
+    float t[NB], pr[16 * NB], most = 0.f;                    // t: the step's sums
+    if (MASK) mask_step(IMAGES ? 32 * (j & 1) : 32 * j, lim, s_cur);
 #pragma unroll
     for (int i = 0; i < 2 * NM; ++i) {
       if (i < NM) {
@@ -258,12 +349,13 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       for (int gr = 0; gr < NG; ++gr)
         if ((gr < 28 ? gr : gr < 30 ? 28 : gr < 31 ? 29 : 30) == i) prob_group(gr, s_cur, pr, t, p_cur);
       if (i == 2 * NM - 1) {
-        grow = __ballot(t[0] > 1024.f) | __ballot(t[1] > 1024.f);
-        asm volatile("" : "+s"(grow));
+        asm volatile("v_max_f32 %0, %1, %2" : "=v"(most) : "v"(t[0]), "v"(t[1]));
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (grow) {                                              // some row's maximum exceeds its reference by more than 6
+    // some row's maximum exceeds its reference by more than 6 (or a segment begins: see flash_workgroup)
+    if (__any(most > 1024.f) || (IMAGES && lim.seg_start)) {
+      const float least = IMAGES && lim.seg_start ? 0.0f : 6.0f;
       o_settle();
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -271,7 +363,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
 #pragma unroll
         for (int r = 1; r < 16; ++r) tm = fmaxf(tm, s_cur[nb][r]);
         tm = pc_xhalf_max(tm);
-        const float delta = tm > 6.0f ? tm : 0.f, alpha = __builtin_amdgcn_exp2f(-delta);
+        const float delta = tm > least ? tm : 0.f, alpha = __builtin_amdgcn_exp2f(-delta);
         m_run[nb] += delta;
         l_run[nb] *= alpha;
         t[nb] = 0.f;
@@ -297,6 +389,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  if (!IMAGES || T > 0) {                                    // (IMAGES: a part, or rows, without any key)
   // K 0 and V 0 have landed, and every wavefront has left its staging area: V 2 may move in
   PC_WAIT_VMCNT(3 * T_LD);
   __builtin_amdgcn_s_waitcnt(0xC07F);                        // (LDS)
@@ -313,7 +406,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) ka[ks] = read_k(0, 1, ks);
-  mask_step(0, s_buf[0]);
+  mask_step(0, lim0, s_buf[0]);
   {
     float t[NB], pr[16 * NB];
 #pragma unroll
@@ -345,12 +438,14 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   // there (one: 2560 cycles a tile instead of 2500, in an earlier build).
   auto period = [&](auto mask_tag, int p) __attribute__((always_inline)) {
     asm volatile("" : "+v"(k_base), "+v"(v_base));
-    step(mask_tag, yes{}, yes{}, std::integral_constant<int, 1>{}, 2 * p + 1, p + 3, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
-    step(mask_tag, yes{}, no{}, std::integral_constant<int, 2>{}, 2 * p + 2, p + 3, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+    if (IMAGES) { walk_next(); lim0.seg_start = false; }     // the walk is on tile p + 3
+    step(mask_tag, yes{}, yes{}, std::integral_constant<int, 1>{}, lim0, 2 * p + 1, p + 3, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+    step(mask_tag, yes{}, no{}, std::integral_constant<int, 2>{}, lim1, 2 * p + 2, p + 3, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+    lim0 = lim1; lim1 = lim2; lim2 = cur.lim;
   };
-  const int n_plain = min(T - 1, max(0, (J0 - 1) / 2));      // periods whose steps need no mask
+  const int n_plain = IMAGES ? run_full - 1 : min(T - 1, max(0, (J0 - 1) / 2));       // periods whose steps need no mask
   // Last step with a key visible to any row of this wavefront; periods behind it keep up loads and barriers only
-  const int j_need = min(pos0 + POS_W - 1, seq_rows - 1) >> 5;
+  const int j_need = IMAGES ? 2 * T - 1 : min(pos0 + POS_W - 1, seq_rows - 1) >> 5;
   const int n_periods = min(T - 1, (j_need + 1) / 2);
   int p = 0;
   for (; p < min(n_plain, n_periods); ++p) period(no{}, p);
@@ -363,8 +458,10 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   }
   PC_WAIT_VMCNT(0);
   __syncthreads();
-  if (j_need >= 2 * T - 1) {
-    step(yes{}, no{}, no{}, std::integral_constant<int, 0>{}, 2 * T - 1, 0, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+  // does the last tile's second half hold a key that some row of the wavefront sees?
+  lim0.seg_start = false;
+  if (IMAGES ? __builtin_amdgcn_readfirstlane(min(lim0.cut - 1, pc_div(min(pos0 + 63, seq_rows - 1), a.group_div) - lim0.c0)) >= 32 : j_need >= 2 * T - 1) {
+    step(yes{}, no{}, no{}, std::integral_constant<int, 0>{}, lim0, 2 * T - 1, 0, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
 #pragma unroll
     for (int i = 0; i < NB * 2; ++i) p_buf[0][i / 2][i % 2] = p_buf[1][i / 2][i % 2];
   }
@@ -373,6 +470,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   for (int i = 0; i < NM; ++i) pv(i, p_buf[0]);
   o_settle();
 
+  }
   // ---- epilogue, as flash_workgroup's: whole rows through the K slots (nobody reads K any more)
   static_assert(4 * 32 * D <= PC_FW_RING * FW_TILE, "staging area is the K slots");
   uint16_t* st_o = smem + wave * (32 * D);
@@ -382,6 +480,22 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     const float l = pc_xhalf_sum(l_run[nb]);
     const float inv_l = l > 0.f ? 1.f / l : 0.f;
     const float lse = l > 0.f ? m_run[nb] * PC_LN2 + logf(l) : -INFINITY;
+    if (IMAGES && a.n_parts > 1) {                           // a partial result for the merge
+      const int row = pos0 + 32 * nb + n;
+      if (row < seq_rows) {
+        const int query = pc_div(row, a.group_div);
+        const long long prow = (((long long)seq * a.n_parts + turn) * a.n_rows + query) * a.n_q_heads + h + row - query * a.group;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            floatx4 x = {o_acc[nb][db][4 * i] * inv_l, o_acc[nb][db][4 * i + 1] * inv_l, o_acc[nb][db][4 * i + 2] * inv_l, o_acc[nb][db][4 * i + 3] * inv_l};
+            *(floatx4*)(a.part_o + prow * D + 32 * db + 8 * i + 4 * hf) = x;
+          }
+        if (hf == 0) a.part_lse[prow] = lse;
+      }
+      continue;
+    }
     if (nb) PC_FA_WAVE_LDS_SYNC();
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -398,10 +512,18 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     for (int k = 0; k < NLD; ++k) {
       const int r = RPL * k + l_row;
       const u32x4 x = *(const u32x4*)(st_o + (r * PPR + (l_piece ^ (r % PPR))) * 8);
-      __builtin_amdgcn_raw_buffer_store_b128(x, o_rsrc, qo_off, RPL * k * qo_stride + nb * nb_step, PC_BUF_NT);
+      if (!IMAGES) {
+        __builtin_amdgcn_raw_buffer_store_b128(x, o_rsrc, qo_off, RPL * k * qo_stride + nb * nb_step, PC_BUF_NT);
+        continue;
+      }
+      const int row = pos0 + 32 * nb + r;
+      if (row < seq_rows) pc_store_once((u32x4*)((uint16_t*)a.o + row_at(row) * D + 8 * l_piece), x);
     }
     const int row = pos0 + (PAIR ? 0 : 32 * nb) + n;
-    if (row < seq_rows && hf == 0 && a.lse) a.lse[((long long)seq * a.n_q_heads + h + (PAIR ? nb : 0)) * a.n_rows + row] = lse;
+    if (row < seq_rows && hf == 0 && a.lse) {
+      if (IMAGES) a.lse[((long long)seq * a.n_q_heads + h + pc_mod(row, a.group, a.group_div)) * a.n_rows + pc_div(row, a.group_div)] = lse;
+      else a.lse[((long long)seq * a.n_q_heads + h + (PAIR ? nb : 0)) * a.n_rows + row] = lse;
+    }
   }
 #undef FW_LOAD_K
 #undef FW_LOAD_V

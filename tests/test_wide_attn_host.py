@@ -10,7 +10,8 @@ import pytest
 
 from paper_2502_14317_amd.build import CSRC, HIPCC_FLAGS, INCLUDE
 
-KERNELS = ["flash_wide_kernelILb1E", "flash_wide_kernelILb0E", "flash_both_wide_kernelILb1E", "flash_both_wide_kernelILb0E"]
+KERNELS = ["flash_wide_kernelILi0E", "flash_wide_kernelILi1E", "flash_wide_kernelILi2E", "flash_both_wide_kernelILi0E",
+           "flash_both_wide_kernelILi1E"]
 
 
 @pytest.fixture(scope="module")
