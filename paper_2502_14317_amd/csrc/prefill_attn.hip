@@ -1125,7 +1125,7 @@ static long long wide_workgroups(int n_seq, int n_rows, int n_q_heads, int n_kv_
 // One head a workgroup, whose causal end is four tiles long: 32 / 32, 8 x 2000 371 / 403, 8 x 4096 1152 / 1155, 1 x
 // 4096 157 / 150, 1 x 8192 536 / 489, 8 x 8192 4004 / 3869.
 static bool wide_fits(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim) {
-  if (head_dim != FW_D) return false;
+  if (head_dim != FW_D || n_q_heads > 65536) return false;   // (64 rows of q or o: 32-bit byte offsets)
   const int least = wide_heads(n_q_heads / n_kv_heads) > 1 ? 1280 : 6144;
   return n_rows >= least && wide_workgroups(n_seq, n_rows, n_q_heads, n_kv_heads) >= 320;
 }
