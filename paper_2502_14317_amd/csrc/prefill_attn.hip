@@ -32,6 +32,15 @@
 #define PC_FA_THREADS (PC_FA_WAVES * PC_WAVE)
 #define PC_FA_BM (PC_FA_WAVES * 32 * PC_FA_NB)   // query rows per workgroup
 #define PC_FA_BN 64                  // keys per tile
+// Largest sum of a lane's 16 probabilities of a step before the reference of its row moves (local attention behind a
+// row's first step, 64-row kernel).  A probability against a low reference is as exact as any, in fp32 and bf16, which share their
+// exponents: the sums stay below 2^68 (2^20 keys) and O^T in fp32 up to values of 2^59.  A step taken anew
+// costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window (2^8 and 2^10 were
+// tried) costs more than the maxima that it saves.  16 x 8192 rows, 32 / 8 heads, logits of deviation 4 / 8 / 16: row maxima and 2^8
+// 7.89 / 8.02 / 8.17 ms, 2^10 8.46 / 9.66 / 10.84, 2^48 6.90 / 6.94 / 7.56 (2^32: the first two alike); of deviation
+// 1: 7.57, 6.79, 6.79.  Only at 32 is it behind the maxima, 8.13 against 8.66.  The error against 64 bits is the same at 1, and 0.4 to
+// 1.3 % larger beyond (5.5e-3 -> 5.6e-3 at 4): a row's largest probability is no exact 1 in bf16 more often.
+#define PC_FA_WINDOW 281474976710656.f    // 2^48
 #define PC_LOG2E 1.4426950408889634f
 // orders a wavefront's own LDS writes before its own later LDS reads (no other wavefront involved)
 #define PC_FA_WAVE_LDS_SYNC()                                \
@@ -753,8 +762,8 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   };
   // Local attention, every step but the first: the same products and reads, no row maxima.  The
   // probabilities are taken against the reference as it stands; that none left its window shows in what is added
-  // up anyway, the sum over the lane's keys: above 2^8 some row's maximum exceeds its reference by more than
-  // 4 (16 keys a lane), and the step's probabilities are taken anew (rare).  The maxima were 9 of 53
+  // up anyway, the sum over the lane's keys: above PC_FA_WINDOW some row's maximum exceeds its reference by more
+  // than 44 (16 keys a lane), and the step's probabilities are taken anew (rare).  The maxima were 9 of 53
   // vector-ALU instructions a step, and the first probabilities had to wait for them; the groups now spread
   // over both regions, up to two slices in front of the end, so that the test's latency is behind products
   // too.  16 x 8192 rows, 32 / 8 heads, scores included 7.32 -> 7.20 ms (all-zero inputs 5.01 -> 4.91), 36 x
@@ -813,7 +822,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
       if (i == SLOTS) {
         bool left_window = false;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) left_window |= t[nb] > 256.f;
+        for (int nb = 0; nb < NB; ++nb) left_window |= t[nb] > PC_FA_WINDOW;
         grow = __ballot(left_window);
         asm volatile("" : "+s"(grow));
       }

@@ -309,8 +309,8 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   // the groups are light; the tile loads in even ones.  The last groups are doubled up so that the test of the sums
   // has its answer at the end.  BAR: the first step of a period waits for the tiles of the period behind
   // its first product.  LD: tile t_ld is asked for, 1 K, 2 V.
-  // The window is 2^10 where flash_workgroup's is 2^8: a rescale holds up all four wavefronts (200 cycles a
-  // tile on average at 2^8, logits of deviation 2), and O^T and the sums stay far inside the range of fp32.
+  // A rescale holds up all four wavefronts (200 cycles a tile on average with a window of 2^8 and logits of deviation
+  // 2): PC_FA_WINDOW is wide.
   auto step = [&](auto mask_tag, auto has_qk, auto bar_tag, auto ld_tag, const Limit& lim, int j, int t_ld, floatx16(&s_cur)[NB],
                   floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2], const u32x4(&p_prev)[NB][2]) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value, QK = decltype(has_qk)::value, BAR = decltype(bar_tag)::value;
@@ -353,8 +353,8 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // some row's maximum exceeds its reference by more than 6 (or a segment begins: see flash_workgroup)
-    if (__any(most > 1024.f) || (IMAGES && lim.seg_start)) {
+    // some row's maximum exceeds its reference by more than 44; every row beyond 6 moves (or a segment begins: see flash_workgroup)
+    if (__any(most > PC_FA_WINDOW) || (IMAGES && lim.seg_start)) {
       const float least = IMAGES && lim.seg_start ? 0.0f : 6.0f;
       o_settle();
 #pragma unroll
