@@ -32,8 +32,8 @@
 #define PC_FA_THREADS (PC_FA_WAVES * PC_WAVE)
 #define PC_FA_BM (PC_FA_WAVES * 32 * PC_FA_NB)   // query rows per workgroup
 #define PC_FA_BN 64                  // keys per tile
-// Largest sum of a lane's 16 probabilities of a step before the reference of its row moves (local attention behind a
-// row's first step, 64-row kernel).  A probability against a low reference is as exact as any, in fp32 and bf16, which share their
+// Largest sum of a lane's 16 probabilities of a step before the reference of its row moves (64 rows a wavefront, behind
+// a row's first step).  A probability against a low reference is as exact as any, in fp32 and bf16, which share their
 // exponents: the sums stay below 2^68 (2^20 keys) and O^T in fp32 up to values of 2^59.  A step taken anew
 // costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window (2^8 and 2^10 were
 // tried) costs more than the maxima that it saves.  16 x 8192 rows, 32 / 8 heads, logits of deviation 4 / 8 / 16: row maxima and 2^8
@@ -604,8 +604,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
 
-  // One step of the software pipeline (of the global modes, and the local one's first; its others are step_local's),
-  // j = the step whose softmax runs now.  A region is NM
+  // One step of the software pipeline, j = the step whose softmax runs now.  A region is NM
   // slices of [one MFMA, at most one LDS operand read, a few vector-ALU instructions], and the
   // compiler may not move instructions across a slice boundary, so the three pipes are fed
   // evenly by construction instead of by the scheduler's heuristics:
@@ -760,107 +759,6 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // Local attention, every step but the first: the same products and reads, no row maxima.  The
-  // probabilities are taken against the reference as it stands; that none left its window shows in what is added
-  // up anyway, the sum over the lane's keys: above PC_FA_WINDOW some row's maximum exceeds its reference by more
-  // than 44 (16 keys a lane), and the step's probabilities are taken anew (rare).  The maxima were 9 of 53
-  // vector-ALU instructions a step, and the first probabilities had to wait for them; the groups now spread
-  // over both regions, up to two slices in front of the end, so that the test's latency is behind products
-  // too.  16 x 8192 rows, 32 / 8 heads, scores included 7.32 -> 7.20 ms (all-zero inputs 5.01 -> 4.91), 36 x
-  // 4096, 32 / 32 5.80 -> 5.70, 12 x 1553, 32 / 8 343 -> 337 us, 1 x 4096, 32 / 32 178 -> 174.
-  auto step_local = [&](auto mask_tag, auto has_qk, auto has_ld, int j, int k0, int t_ld, const TileLoad& ld, floatx16(&s_cur)[NB],
-                        floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2], const u32x4(&p_prev)[NB][2]) __attribute__((always_inline)) {
-    constexpr bool MASK = decltype(mask_tag)::value, QK = decltype(has_qk)::value, LD = decltype(has_ld)::value;
-    constexpr int SLOTS = 2 * NM - 2;                // slices that take probability groups
-    const int kt = k_at((j + 1) >> 1);
-    const uint16_t* vt = v_lds(j >> 1);
-    float t[NB], pr[16 * NB];                        // the step's row sums
-    unsigned long long grow = 0;
-    auto prob_group = [&](int g) __attribute__((always_inline)) {      // two stages, as above
-      if (g >= 1 && g - 1 < 16 * NB) {
-        const int e = g - 1, nb = e / 16, r = e % 16;
-        t[nb] = r == 0 ? pr[e] : t[nb] + pr[e];
-        asm volatile("" : "+v"(t[nb]));
-        if (r % 2 == 1) {
-          uint32_t w = pack_bf16x2(pr[e - 1], pr[e]);
-          asm volatile("" : "+v"(w));
-          p_cur[nb][r / 8][(r % 8) / 2] = w;
-        }
-      }
-      if (g < 16 * NB) {
-        pr[g] = __builtin_amdgcn_exp2f(s_cur[g / 16][g % 16]);
-        asm volatile("" : "+v"(pr[g]));
-      }
-    };
-    if (MASK) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (k0 + 16 * (r / 8) + 8 * hf + (r % 8) > max_key[nb]) s_cur[nb][r] = -INFINITY;
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = 0; i < 2 * NM; ++i) {
-      if (i < NM) {                                  // region 1
-        const int ts = i / (NB * DB), db = (i / NB) % DB, nb = i % NB;
-        o_acc[nb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ts][db], *(const bf16x8*)&p_prev[nb][ts], o_acc[nb][db], 0, 0, 0);
-        if (QK && i < KS) ka[i] = read_k(kt, (j + 1) & 1, i);
-        if (LD && i >= NM - 2 * T_LD) {
-          const int li = i - (NM - 2 * T_LD);
-          if (li < T_LD) load_k_i(ld, t_ld, t_ld, li);
-          else load_v_i(ld, t_ld, t_ld, li - T_LD);
-        }
-      } else {                                       // region 2
-        const int ks = (i - NM) / NB, nb = i % NB;
-        if (QK) s_next[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], bq[nb][ks], ks == 0 ? negm[nb] : s_next[nb], 0, 0, 0);
-        if (i - NM < KS) va[(i - NM) / DB][(i - NM) % DB] = read_v(vt, j & 1, (i - NM) / DB, (i - NM) % DB);
-      }
-#pragma unroll
-      for (int g = 0; g < NG; ++g)
-        if (g * SLOTS / NG == i) prob_group(g);
-      if (i == SLOTS) {
-        bool left_window = false;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) left_window |= t[nb] > PC_FA_WINDOW;
-        grow = __ballot(left_window);
-        asm volatile("" : "+s"(grow));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (grow) {
-      // O holds the steps before this one, S^T(j + 1) was taken against the reference as it was
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        float tm = s_cur[nb][0];
-#pragma unroll
-        for (int r = 1; r < 16; ++r) tm = fmaxf(tm, s_cur[nb][r]);
-        tm = pc_xhalf_max(tm);                       // both lane halves hold keys of the same row
-        const float delta = tm > 4.0f ? tm : 0.f, alpha = __builtin_amdgcn_exp2f(-delta);
-        m_run[nb] += delta;
-        l_run[nb] *= alpha;
-        t[nb] = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          negm[nb][r] = -m_run[nb];
-          if (QK) s_next[nb][r] -= delta;
-          pr[16 * nb + r] = __builtin_amdgcn_exp2f(s_cur[nb][r] - delta);
-          t[nb] += pr[16 * nb + r];
-          if (r % 2 == 1) p_cur[nb][r / 8][(r % 8) / 2] = pack_bf16x2(pr[16 * nb + r - 1], pr[16 * nb + r]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {            // a block at a time: a handful of temporaries
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o_acc[nb][db][r] *= alpha;
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) l_run[nb] += t[nb];
-    __builtin_amdgcn_sched_barrier(0);
-  };
   // first S^T of a workgroup: operands of step 0, then the product
   auto first_qk = [&](floatx16(&s)[NB]) __attribute__((always_inline)) {
 #pragma unroll
@@ -915,8 +813,8 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
       PC_WAIT_VMCNT(0);
       __syncthreads();
       const int t_ld = min(p + 2, T - 1);
-      step_local(mask_tag, yes{}, yes{}, 2 * p + 1, 32 * (2 * p + 1), t_ld, ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
-      step_local(mask_tag, yes{}, no{}, 2 * p + 2, 32 * (2 * p + 2), 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
+      step(mask_tag, yes{}, yes{}, yes{}, no_lim, 8.0f, 2 * p + 1, 32 * (2 * p + 1), t_ld, ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      step(mask_tag, yes{}, yes{}, no{}, no_lim, 8.0f, 2 * p + 2, 32 * (2 * p + 2), 0, no_ld, s_buf[0], s_buf[1], p_buf[0], p_buf[1]);
     };
     const int n_plain = min(T - 1, max(0, (J0 - 1) / 2));   // periods whose steps need no mask
     // Last step with a key visible to any row of this wavefront.  On the diagonal the steps
@@ -936,7 +834,7 @@ __device__ __forceinline__ void flash_workgroup(const PcFlashArgs& a, int bid, u
     PC_WAIT_VMCNT(0);
     __syncthreads();
     if (j_need >= 2 * T - 1) {
-      step_local(with_mask{}, no{}, no{}, 2 * T - 1, 32 * (2 * T - 1), 0, no_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
+      step(with_mask{}, yes{}, no{}, no{}, no_lim, 8.0f, 2 * T - 1, 32 * (2 * T - 1), 0, no_ld, s_buf[1], s_buf[0], p_buf[1], p_buf[0]);
       last_pv(p_buf[1]);
     } else {
       last_pv(p_buf[0]);                                     // P V of the last step that ran (an even one)

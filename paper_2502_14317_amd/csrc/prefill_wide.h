@@ -304,7 +304,8 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // Step j: as flash_workgroup's step_local.  Slices 0 to 15 are the P V products of step j - 1 with the reads of
+  // Step j: the products and reads of flash_workgroup's step without its row maxima.  The probabilities are taken against
+  // the reference as it stands; whether one left its window shows in the step's sums.  Slices 0 to 15 are the P V products of step j - 1 with the reads of
   // the next keys, 16 to 31 the S^T products of step j + 1 with the reads of V^T(j), reads in the odd ones, where
   // the groups are light; the tile loads in even ones.  The last groups are doubled up so that the test of the sums
   // has its answer at the end.  BAR: the first step of a period waits for the tiles of the period behind

@@ -1,5 +1,5 @@
-"""Local attention where the softmax reference has to move behind a row's first 32 keys: the step that finds
-its probabilities' sum too large takes them anew, rescales what the row has so far and the next step's logits.
+"""Local attention where the softmax reference has to move behind a row's first 32 keys: the step whose maximum exceeds
+it by more than 8 (log2 units) moves it there and rescales what the row has so far.
 
 The logits are known exactly: only the slowest pair of every head is used, which a rotation by the largest angle
 here, 257 * 1e30^(-1 + 2 / D) < 1e-25, leaves as it is, and a query is one value times one key value.  What is left are

@@ -1,6 +1,6 @@
-"""Local attention with logits at the edges of the window of a row's softmax reference, a lane's step sum of 2^48: just
-inside it the probabilities are as large as they get and nothing moves, just outside the step is taken anew.  Both kernels:
-32 query rows a wavefront (short rows) and 64.
+"""Local attention with logits at the edges of the window of a row's softmax reference in the kernel of 64 query rows a
+wavefront, a lane's step sum of 2^48: just inside it the probabilities are as large as they get and nothing moves, just
+outside the step is taken anew.  The kernel of 32 rows (short rows), whose references move from 2^8 on, gets the same logits.
 
 Logits are known exactly, as in test_gpu_reference_moves.py: the slowest pair of a head, which the largest angle here,
 1553 * 1e30^(-1 + 2 / 128) < 2e-26, leaves as it is.  What is left are the bf16 roundings of a probability and of the output
