@@ -38,8 +38,7 @@
 // costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window (2^8 and 2^10 were
 // tried) costs more than the maxima that it saves.  16 x 8192 rows, 32 / 8 heads, logits of deviation 4 / 8 / 16: row maxima and 2^8
 // 7.89 / 8.02 / 8.17 ms, 2^10 8.46 / 9.66 / 10.84, 2^48 6.90 / 6.94 / 7.56 (2^32: the first two alike); of deviation
-// 1: 7.57, 6.79, 6.79.  Only at 32 is it behind the maxima, 8.13 against 8.66.  The error against 64 bits is the same at 1, and 0.4 to
-// 1.3 % larger beyond (5.5e-3 -> 5.6e-3 at 4): a row's largest probability is no exact 1 in bf16 more often.
+// 1: 7.57, 6.79, 6.79.  Only at 32 is it behind the maxima, 8.13 against 8.66.
 #define PC_FA_WINDOW 281474976710656.f    // 2^48
 #define PC_LOG2E 1.4426950408889634f
 // orders a wavefront's own LDS writes before its own later LDS reads (no other wavefront involved)

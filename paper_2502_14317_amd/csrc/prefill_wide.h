@@ -248,7 +248,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   floatx16 negm[NB], s_buf[2][NB];                           // -reference, the C operand of every S^T; [step parity] S^T
   u32x4 p_buf[2][NB][2];                                     // [step parity] P^T
   bf16x8 ka[KS], va[2][DB];
-  float m_run[NB] = {0.f, 0.f}, l_run[NB] = {0.f, 0.f};
+  float m_run[NB] = {0.f, 0.f}, l_run[NB] = {0.f, 0.f}, dl_run[NB] = {0.f, 0.f};
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
@@ -277,21 +277,41 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   using yes = std::integral_constant<bool, true>;
   using no = std::integral_constant<bool, false>;
 
-  // The probabilities of a step in NG groups: exp2 of element gr, sum and pack of the one before (element e:
+  // The probabilities of a step in NG groups: exp2 of element gr, sum, maximum and pack of the one before (element e:
   // register e % 16 of block e / 16)
   constexpr int NG = 16 * NB + 1;
-  auto prob_group = [&](int gr, const floatx16(&s)[NB], float(&pr)[16 * NB], float(&t)[NB], u32x4(&p)[NB][2]) __attribute__((always_inline)) {
+  auto prob_group = [&](int gr, const floatx16(&s)[NB], float(&pr)[16 * NB], float(&t)[NB], float(&mx)[NB], u32x4(&p)[NB][2]) __attribute__((always_inline)) {
     if (gr < 16 * NB) asm volatile("v_exp_f32 %0, %1" : "=v"(pr[gr]) : "v"(s[gr / 16][gr % 16]));
     if (gr >= 1) {
       const int e = gr - 1, nb = e / 16, r = e % 16;
       if (r == 1) asm volatile("v_add_f32 %0, %1, %2" : "=v"(t[nb]) : "v"(pr[e - 1]), "v"(pr[e]));
       if (r > 1) asm volatile("v_add_f32 %0, %0, %1" : "+v"(t[nb]) : "v"(pr[e]));
+      if (r == 2) asm volatile("v_max3_f32 %0, %1, %2, %3" : "=v"(mx[nb]) : "v"(pr[e - 2]), "v"(pr[e - 1]), "v"(pr[e]));
+      if (r > 2 && r % 2 == 0) asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(mx[nb]) : "v"(pr[e - 1]), "v"(pr[e]));
+      if (r == 15) asm volatile("v_max_f32 %0, %0, %1" : "+v"(mx[nb]) : "v"(pr[e]));
       if (r % 2 == 1) {
         uint32_t w;
         asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w) : "v"(pr[e - 1]), "v"(pr[e]));
         p[nb][r / 8][(r % 8) / 2] = w;
       }
     }
+  };
+  // What rounding to bf16 added to the heaviest probability of every lane's 16 goes into the output's row sum (dl_run), a
+  // step later, in seven parts.  The products take probabilities rounded, t sums them as they are (the
+  // logsumexp needs that), and a reference that stays behind leaves the heaviest one no power of two: its rounding would be an
+  // error of the weights' sum.  Error against 64 bits on the same operands, as a multiple of what the roundings of
+  // probabilities and outputs cost, deviation of the logits 1 / 4 / 8 / 16: flash_workgroup 1.00 / 1.10 / 1.11 / 1.00, without
+  // this 1.00 / 1.23 / 1.29 / 1.22, with it 0.99 / 0.99 / 0.98 / 0.88, with all rounded probabilities summed
+  // 1.00 / 1.00 / 0.98 / 0.88.  16 x 8192 rows, 32 / 8 heads, with the pre-pass 7000 -> 7180 us; all of them
+  // by v_dot2_f32_bf16 8030 (it waits for the matrix pipe), the parts in one slice of the step 7250.
+  float heavy[NB] = {0.f, 0.f}, was[NB];
+  uint32_t heavy_w;
+  auto round_part = [&](int i) __attribute__((always_inline)) {
+    if (i == 0) asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(heavy_w) : "v"(heavy[0]), "v"(heavy[1]));
+    if (i == 1) asm volatile("v_lshlrev_b32 %0, 16, %1" : "=v"(was[0]) : "v"(heavy_w));
+    if (i == 2) asm volatile("v_and_b32 %0, 0xffff0000, %1" : "=v"(was[1]) : "v"(heavy_w));
+    if (i == 3 || i == 4) asm volatile("v_sub_f32 %0, %0, %1" : "+v"(was[i - 3]) : "v"(heavy[i - 3]));
+    if (i == 5 || i == 6) asm volatile("v_add_f32 %0, %0, %1" : "+v"(dl_run[i - 5]) : "v"(was[i - 5]));
   };
   // k0: the step's first key (IMAGES: counted from the tile's first)
   auto mask_step = [&](int k0, const Limit& lim, floatx16(&s)[NB]) __attribute__((always_inline)) {
@@ -316,7 +336,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
                   floatx16(&s_next)[NB], u32x4(&p_cur)[NB][2], const u32x4(&p_prev)[NB][2]) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value, QK = decltype(has_qk)::value, BAR = decltype(bar_tag)::value;
     constexpr int LD = decltype(ld_tag)::value;
-    float t[NB], pr[16 * NB], most = 0.f;                    // t: the step's sums
+    float t[NB], mx[NB], pr[16 * NB], most = 0.f;            // the step's sums, maxima and probabilities
     if (MASK) mask_step(IMAGES ? 32 * (j & 1) : 32 * j, lim, s_cur);
 #pragma unroll
     for (int i = 0; i < 2 * NM; ++i) {
@@ -346,12 +366,12 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
         }
         if (i2 % 2 == 1) va[i2 / 2 / DB][i2 / 2 % DB] = read_v(j >> 1, j & 1, i2 / 2);
       }
-#pragma unroll
-      for (int gr = 0; gr < NG; ++gr)
-        if ((gr < 28 ? gr : gr < 30 ? 28 : gr < 31 ? 29 : 30) == i) prob_group(gr, s_cur, pr, t, p_cur);
+      if (i < 2 * NM - 1) prob_group(i <= 28 ? i : i == 29 ? 30 : 31, s_cur, pr, t, mx, p_cur);
+      if (i == 28 || i == 30) prob_group(i == 28 ? 29 : 32, s_cur, pr, t, mx, p_cur);
       if (i == 2 * NM - 1) {
         asm volatile("v_max_f32 %0, %1, %2" : "=v"(most) : "v"(t[0]), "v"(t[1]));
       }
+      if (i < 14 && i % 2 == 0) round_part(i / 2);           // of the step before
       __builtin_amdgcn_sched_barrier(0);
     }
     // some row's maximum exceeds its reference by more than 44; every row beyond 6 moves (or a segment begins: see flash_workgroup)
@@ -363,10 +383,13 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
         float tm = s_cur[nb][0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) tm = fmaxf(tm, s_cur[nb][r]);
+        mx[nb] = tm;
         tm = pc_xhalf_max(tm);
         const float delta = tm > least ? tm : 0.f, alpha = __builtin_amdgcn_exp2f(-delta);
         m_run[nb] += delta;
         l_run[nb] *= alpha;
+        dl_run[nb] *= alpha;
+        mx[nb] = __builtin_amdgcn_exp2f(mx[nb] - delta);
         t[nb] = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -386,7 +409,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       }
     }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) l_run[nb] += t[nb];
+    for (int nb = 0; nb < NB; ++nb) { l_run[nb] += t[nb]; heavy[nb] = mx[nb]; }
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -409,7 +432,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   for (int ks = 0; ks < KS; ++ks) ka[ks] = read_k(0, 1, ks);
   mask_step(0, lim0, s_buf[0]);
   {
-    float t[NB], pr[16 * NB];
+    float t[NB], mx[NB], pr[16 * NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       float tm = s_buf[0][nb][0];
@@ -427,12 +450,11 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       s_buf[1][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], bq[nb][ks], ks == 0 ? negm[nb] : s_buf[1][nb], 0, 0, 0);
       if (i < KS) va[i / DB][i % DB] = read_v(0, 0, i);
 #pragma unroll
-      for (int gr = 0; gr < NG; ++gr)
-        if (gr * NM / NG == i) prob_group(gr, s_buf[0], pr, t, p_buf[0]);
+      for (int gr = (i * NG + NM - 1) / NM; gr < ((i + 1) * NG + NM - 1) / NM; ++gr) prob_group(gr, s_buf[0], pr, t, mx, p_buf[0]);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) l_run[nb] = t[nb];
+    for (int nb = 0; nb < NB; ++nb) { l_run[nb] = t[nb]; heavy[nb] = mx[nb]; }
   }
   // Period p: steps 2p + 1 and 2p + 2 over K tile p + 1 and V^T tiles p and p + 1.  Tile p + 3 moves into the slots
   // of tile p - 1, last read in front of the period's barrier; two periods of loads (8 instructions) may be in flight
@@ -470,19 +492,24 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
 #pragma unroll
   for (int i = 0; i < NM; ++i) pv(i, p_buf[0]);
   o_settle();
+#pragma unroll
+  for (int i = 0; i < 7; ++i) round_part(i);
 
   }
   // ---- epilogue, as flash_workgroup's: whole rows through the K slots (nobody reads K any more)
   static_assert(4 * 32 * D <= PC_FW_RING * FW_TILE, "staging area is the K slots");
   uint16_t* st_o = smem + wave * (32 * D);
+  int l_out = lane;                                          // (IMAGES: no addresses kept across the loop)
+  if (IMAGES) asm volatile("" : "+v"(l_out));
+  const int n_out = l_out % 32, hf_out = l_out / 32, row_out = l_out / PPR, piece_out = l_out % PPR;
   const __amdgpu_buffer_rsrc_t o_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((uint16_t*)a.o + qo_at), 0, qo_bytes, 0x00020000);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const float l = pc_xhalf_sum(l_run[nb]);
-    const float inv_l = l > 0.f ? 1.f / l : 0.f;
+    const float inv_l = l > 0.f ? 1.f / (l + pc_xhalf_sum(dl_run[nb])) : 0.f;
     const float lse = l > 0.f ? m_run[nb] * PC_LN2 + logf(l) : -INFINITY;
     if (IMAGES && a.n_parts > 1) {                           // a partial result for the merge
-      const int row = pos0 + 32 * nb + n;
+      const int row = pos0 + 32 * nb + n_out;
       if (row < seq_rows) {
         const int query = pc_div(row, a.group_div);
         const long long prow = (((long long)seq * a.n_parts + turn) * a.n_rows + query) * a.n_q_heads + h + row - query * a.group;
@@ -491,9 +518,9 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             floatx4 x = {o_acc[nb][db][4 * i] * inv_l, o_acc[nb][db][4 * i + 1] * inv_l, o_acc[nb][db][4 * i + 2] * inv_l, o_acc[nb][db][4 * i + 3] * inv_l};
-            *(floatx4*)(a.part_o + prow * D + 32 * db + 8 * i + 4 * hf) = x;
+            *(floatx4*)(a.part_o + prow * D + 32 * db + 8 * i + 4 * hf_out) = x;
           }
-        if (hf == 0) a.part_lse[prow] = lse;
+        if (hf_out == 0) a.part_lse[prow] = lse;
       }
       continue;
     }
@@ -506,22 +533,22 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
         x.x = pack_bf16x2(o_acc[nb][db][4 * i] * inv_l, o_acc[nb][db][4 * i + 1] * inv_l);
         x.y = pack_bf16x2(o_acc[nb][db][4 * i + 2] * inv_l, o_acc[nb][db][4 * i + 3] * inv_l);
         const int q = 4 * db + i;
-        *(uint2*)(st_o + (n * PPR + (q ^ (n % PPR))) * 8 + 4 * hf) = x;
+        *(uint2*)(st_o + (n_out * PPR + (q ^ (n_out % PPR))) * 8 + 4 * hf_out) = x;
       }
     PC_FA_WAVE_LDS_SYNC();
 #pragma unroll
     for (int k = 0; k < NLD; ++k) {
-      const int r = RPL * k + l_row;
-      const u32x4 x = *(const u32x4*)(st_o + (r * PPR + (l_piece ^ (r % PPR))) * 8);
+      const int r = RPL * k + row_out;
+      const u32x4 x = *(const u32x4*)(st_o + (r * PPR + (piece_out ^ (r % PPR))) * 8);
       if (!IMAGES) {
         __builtin_amdgcn_raw_buffer_store_b128(x, o_rsrc, qo_off, RPL * k * qo_stride + nb * nb_step, PC_BUF_NT);
         continue;
       }
       const int row = pos0 + 32 * nb + r;
-      if (row < seq_rows) pc_store_once((u32x4*)((uint16_t*)a.o + row_at(row) * D + 8 * l_piece), x);
+      if (row < seq_rows) pc_store_once((u32x4*)((uint16_t*)a.o + row_at(row) * D + 8 * piece_out), x);
     }
-    const int row = pos0 + (PAIR ? 0 : 32 * nb) + n;
-    if (row < seq_rows && hf == 0 && a.lse) {
+    const int row = pos0 + (PAIR ? 0 : 32 * nb) + n_out;
+    if (row < seq_rows && hf_out == 0 && a.lse) {
       if (IMAGES) a.lse[((long long)seq * a.n_q_heads + h + pc_mod(row, a.group, a.group_div)) * a.n_rows + pc_div(row, a.group_div)] = lse;
       else a.lse[((long long)seq * a.n_q_heads + h + (PAIR ? nb : 0)) * a.n_rows + row] = lse;
     }
