@@ -34,7 +34,8 @@
 #define PC_FA_BN 64                  // keys per tile
 // Largest sum of a lane's 16 probabilities of a step before the reference of its row moves (64 rows a wavefront, behind
 // a row's first step).  A probability against a low reference is as exact as any, in fp32 and bf16, which share their
-// exponents: the sums stay below 2^68 (2^20 keys) and O^T in fp32 up to values of 2^59.  A step taken anew
+// exponents: the sums stay below 2^68 (2^20 keys) and O^T in fp32 up to values of 2^59, beyond
+// which a wavefront takes its rows a second time (end of wide_workgroup).  A step taken anew
 // costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window (2^8 and 2^10 were
 // tried) costs more than the maxima that it saves.  16 x 8192 rows, 32 / 8 heads, logits of deviation 4 / 8 / 16: row maxima and 2^8
 // 7.89 / 8.02 / 8.17 ms, 2^10 8.46 / 9.66 / 10.84, 2^48 6.90 / 6.94 / 7.56 (2^32: the first two alike); of deviation

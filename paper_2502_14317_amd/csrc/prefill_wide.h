@@ -26,6 +26,7 @@
 // PC_FW_IMAGES: flash_workgroup's mode of that name, rows of a KV group packed, parts and all: 4 x 512 rows of 32 / 8
 // heads over 8 x 2048 keys of the 8-bit cache 702 -> 645 us with everything else of the call, 3 sequences (two parts)
 // 567 -> 538, 2 x 512 of 32 / 32 714 -> 688.  Loads follow a walk over the segments' tiles that runs three ahead.
+#define PC_FW_FAR 262144.f           // a lane's row sum above it shows a reference behind the row's maximum (2^18: 2^10 keys, 2^8 behind)
 #define PC_FW_RING 4                 // tiles of K and of V^T in LDS, 128 KiB
 constexpr int FW_D = 128, FW_TILE = 64 * FW_D;               // elements of a tile image
 constexpr int FW_LDS_BYTES = 2 * PC_FW_RING * FW_TILE * 2;
@@ -123,7 +124,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       walk_seek(masked_lo);
     }
   };
-  if (IMAGES) {
+  auto walk_begin = [&]() __attribute__((always_inline)) {
     int n_full = 0, n_masked = 0;
     for (int i = 0; i < PC_KV_GROUPS; ++i)
       if (a.grp[i].n > 0) {
@@ -140,7 +141,8 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       cur.in_phase = cur.masked ? T : run_full;
       walk_seek(cur.masked ? masked_lo : lo);
     }
-  }
+  };
+  if (IMAGES) walk_begin();
   Limit lim0 = cur.lim, lim1 = {}, lim2 = {};                // of tiles p, p + 1, p + 2
 
   // ---- tile loads: wavefront w copies bytes 4096 w .. of a tile image, 1 KiB an instruction (the immediate
@@ -249,6 +251,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   u32x4 p_buf[2][NB][2];                                     // [step parity] P^T
   bf16x8 ka[KS], va[2][DB];
   float m_run[NB] = {0.f, 0.f}, l_run[NB] = {0.f, 0.f}, dl_run[NB] = {0.f, 0.f};
+  bool far = false;                                          // a sum beyond PC_FW_FAR was scaled down
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
@@ -377,6 +380,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     // some row's maximum exceeds its reference by more than 44; every row beyond 6 moves (or a segment begins: see flash_workgroup)
     if (__any(most > PC_FA_WINDOW) || (IMAGES && lim.seg_start)) {
       const float least = IMAGES && lim.seg_start ? 0.0f : 6.0f;
+      far |= !IMAGES || __any(fmaxf(most, fmaxf(l_run[0], l_run[1])) > PC_FW_FAR);
       o_settle();
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -495,6 +499,77 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
 #pragma unroll
   for (int i = 0; i < 7; ++i) round_part(i);
 
+  // ---- O^T beyond fp32, which a reference far behind a row's maximum allows for values from 2^59 on: the
+  //      wavefront takes its rows once more, straight from the tile images, with references that follow the maxima.  Then
+  //      probabilities are at most 1, and values up to 2^107 (2^20 keys) have finite sums.
+  if (far || __any(fmaxf(l_run[0], l_run[1]) > PC_FW_FAR)) {
+    float z = 0.f;                                           // NaN if some element is no number
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(o_acc[nb][db][r], 0.f, z);
+    if (__any(z != z)) {
+      if (IMAGES) walk_begin();
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        m_run[nb] = l_run[nb] = dl_run[nb] = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) negm[nb][r] = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o_acc[nb][db][r] = 0.f;
+          asm volatile("" : "+a"(o_acc[nb][db]));
+        }
+      }
+#pragma unroll 1
+      for (int j = 0; j < (IMAGES ? 2 * T : j_need + 1); ++j) {
+        if (IMAGES && j > 0 && j % 2 == 0) walk_next();
+        const long long at = img0 + (long long)(j >> 1) * FW_TILE;
+        const uint16_t* kt = (IMAGES ? cur.k : (const uint16_t*)a.k_img + at) + 32 * 8 * (j & 1) + k_base;
+        const uint16_t* vt = (IMAGES ? cur.v : (const uint16_t*)a.v_img + at) + 4 * (j & 1) * D * 8 + v_base;
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+          ka[i] = *(const bf16x8*)(kt + 2 * i * 64 * 8);
+          va[i / DB][i % DB] = *(const bf16x8*)(vt + 2 * (i / DB) * D * 8 + 32 * (i % DB) * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < NM; ++i)
+          s_buf[0][i % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i / NB], bq[i % NB][i / NB], i < NB ? negm[i % NB] : s_buf[0][i % NB], 0, 0, 0);
+        mask_step(IMAGES ? 32 * (j & 1) : 32 * j, cur.lim, s_buf[0]);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          float tm = s_buf[0][nb][0];
+#pragma unroll
+          for (int r = 1; r < 16; ++r) tm = fmaxf(tm, s_buf[0][nb][r]);
+          tm = pc_xhalf_max(tm);
+          const float delta = j > 0 ? fmaxf(tm, 0.f) : tm != -INFINITY ? tm : 0.f, alpha = j > 0 ? __builtin_amdgcn_exp2f(-delta) : 1.f;
+          m_run[nb] += delta;
+          l_run[nb] *= alpha;
+          dl_run[nb] *= alpha;
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            negm[nb][r] = negm[nb][r + 1] = -m_run[nb];
+            const float p0 = __builtin_amdgcn_exp2f(s_buf[0][nb][r] - delta), p1 = __builtin_amdgcn_exp2f(s_buf[0][nb][r + 1] - delta);
+            const uint32_t w = pack_bf16x2(p0, p1);
+            p_buf[0][nb][r / 8][r % 8 / 2] = w;
+            l_run[nb] += p0 + p1;
+            dl_run[nb] += (bf16_lo_to_f32(w) - p0) + (bf16_hi_to_f32(w) - p1);
+          }
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o_acc[nb][db][r] *= alpha;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) pv(i, p_buf[0]);
+        o_settle();
+      }
+    }
+  }
   }
   // ---- epilogue, as flash_workgroup's: whole rows through the K slots (nobody reads K any more)
   static_assert(4 * 32 * D <= PC_FW_RING * FW_TILE, "staging area is the K slots");
