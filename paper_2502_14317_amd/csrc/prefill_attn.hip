@@ -34,13 +34,14 @@
 #define PC_FA_BN 64                  // keys per tile
 // Largest sum of a lane's 16 probabilities of a step before the reference of its row moves (64 rows a wavefront, behind
 // a row's first step).  A probability against a low reference is as exact as any, in fp32 and bf16, which share their
-// exponents: the sums stay below 2^68 (2^20 keys) and O^T in fp32 up to values of 2^59, beyond
+// exponents: the sums stay below 2^110 (2^20 keys) and O^T in fp32 up to values of 2^17 (a few heavy keys: 2^35), beyond
 // which a wavefront takes its rows a second time (end of wide_workgroup).  A step taken anew
-// costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window (2^8 and 2^10 were
-// tried) costs more than the maxima that it saves.  16 x 8192 rows, 32 / 8 heads, logits of deviation 4 / 8 / 16: row maxima and 2^8
-// 7.89 / 8.02 / 8.17 ms, 2^10 8.46 / 9.66 / 10.84, 2^48 6.90 / 6.94 / 7.56 (2^32: the first two alike); of deviation
-// 1: 7.57, 6.79, 6.79.  Only at 32 is it behind the maxima, 8.13 against 8.66.
-#define PC_FA_WINDOW 281474976710656.f    // 2^48
+// costs some two, with 64 rows a wavefront more often than with 32, so on sharp logits a narrow window costs more than the
+// maxima that it saves.  16 x 8192 rows, 32 / 8 heads, ms, logits of deviation 1 / 4 / 8 / 16 / 32: 32 rows a wavefront (row
+// maxima, 2^8) 7.46 / 7.78 / 7.90 / 8.00 / 7.81, here with 2^48 6.80 / 6.84 / 6.87 / 7.81 / 9.19, 2^64 6.79 / 6.84 / 6.87 / 7.13 /
+// 8.47, 2^90 6.81 / 6.83 / 6.87 / 6.89 / 7.79; 12 x 2214 rows, us: 542 / 577 / 602 / 600 / 601, 2^48 487 / 493 / 502 / 562 / 715,
+// 2^90 497 / 493 / 501 / 503 / 580.  2^10: 9.7 ms at 8 already.
+#define PC_FA_WINDOW 1237940039285380274899124224.f    // 2^90
 #define PC_LOG2E 1.4426950408889634f
 // orders a wavefront's own LDS writes before its own later LDS reads (no other wavefront involved)
 #define PC_FA_WAVE_LDS_SYNC()                                \

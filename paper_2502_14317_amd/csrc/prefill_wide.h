@@ -377,7 +377,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       if (i < 14 && i % 2 == 0) round_part(i / 2);           // of the step before
       __builtin_amdgcn_sched_barrier(0);
     }
-    // some row's maximum exceeds its reference by more than 44; every row beyond 6 moves (or a segment begins: see flash_workgroup)
+    // some row's maximum exceeds its reference by more than 86; every row beyond 6 moves (or a segment begins: see flash_workgroup)
     if (__any(most > PC_FA_WINDOW) || (IMAGES && lim.seg_start)) {
       const float least = IMAGES && lim.seg_start ? 0.0f : 6.0f;
       far |= !IMAGES || __any(fmaxf(most, fmaxf(l_run[0], l_run[1])) > PC_FW_FAR);
@@ -499,7 +499,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
 #pragma unroll
   for (int i = 0; i < 7; ++i) round_part(i);
 
-  // ---- O^T beyond fp32, which a reference far behind a row's maximum allows for values from 2^59 on: the
+  // ---- O^T beyond fp32, which a reference far behind a row's maximum allows for large values: the
   //      wavefront takes its rows once more, straight from the tile images, with references that follow the maxima.  Then
   //      probabilities are at most 1, and values up to 2^107 (2^20 keys) have finite sums.
   if (far || __any(fmaxf(l_run[0], l_run[1]) > PC_FW_FAR)) {

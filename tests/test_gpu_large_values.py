@@ -1,5 +1,5 @@
 """Attention of many rows with values of 2^90: the sums of probabilities times values stay within fp32, also where logits rise
-far above a row's first ones, in the kernels of 32 and of 64 query rows a wavefront (whose references stay up to 2^48 behind).
+far above a row's first ones, in the kernels of 32 and of 64 query rows a wavefront (whose references stay up to 2^90 behind).
 
 Logits are known exactly: only the slowest pair of a head is used, which the largest angle here, 6157 * 1e30^(-1 + 2 / 128) <
 1e-25, leaves as it is.  Scaling values by a power of two changes no rounding, so the bounds are those of values of at most 6:
@@ -20,9 +20,9 @@ BIG = 2.0 ** 90
 SCALE_LOG2 = np.log2(np.e) / np.sqrt(D)
 LEVELS = {                                                  # logits of the quarters of the keys, log2 units
     "flat": [0.0, 0.0, 0.0, 0.0],
-    "behind": [0.0, 20.0, 40.0, 40.0],
-    "moves, then behind": [0.0, 56.0, 60.0, 96.0],
-    "behind, then moves": [0.0, 40.0, 96.0, 96.0],
+    "behind": [0.0, 40.0, 80.0, 80.0],
+    "moves, then behind": [0.0, 100.0, 104.0, 180.0],
+    "behind, then moves": [0.0, 80.0, 180.0, 180.0],
 }
 
 
@@ -79,24 +79,26 @@ def test_chunk_prefill(name, case):
 
 
 @pytest.mark.parametrize("B,G,S", [(4, 8, 9), (2, 8, 33), (2, 2, 12)])     # one part; several; groups of two
-@pytest.mark.parametrize("name", ["flat", "behind", "moves, then behind"])
+@pytest.mark.parametrize("name", ["flat", "behind", "moves", "every step"])
 def test_block_over_the_8_bit_cache(name, B, G, S):
-    """Tile images, 64 rows a wavefront: every segment rises from its first keys on, segments of odd length among them; then
-    the causal block itself, whose first keys' logits are 0."""
+    """Tile images, 64 rows a wavefront: every segment rises from its first keys on, the next one's keys higher, segments of
+    odd length among them; then the causal block itself, whose first keys' logits are 0."""
     n_q, kt, Hkv = 128, 500, 16
     Hq = G * Hkv
     print("large values over images", name, B, G, S, flush=True)
     r = np.random.default_rng([75, G, len(name)])
     gen = torch.Generator(device="cuda").manual_seed(G + len(name))
-    level = np.array([0.0, 0.0, 44.0, 88.0] if "moves" in name else LEVELS[name])
+    level = np.array([0.0, 112.0, 224.0, 448.0] if name == "moves" else LEVELS.get(name, LEVELS["flat"]))
     lens = r.integers(300, kt + 1, size=(B, S))
     j = np.arange(kt)
-    rise = level[4 * j // kt]                               # exact in E4M3
+    rise = 8.0 * (j // 32) if name == "every step" else level[4 * j // kt]      # exact in E4M3
+    grow = 1.0 + np.arange(S) if name == "moves" else 12.0 + np.arange(S) if name == "every step" else np.ones(S)
+    rise = bf16_bits_to_f64(f32_to_bf16_bits((grow[:, None] * rise[None]).astype(np.float32)))
     q = np.zeros((B, n_q, Hq, D), np.float32)
     q[..., D // 2 - 1] = r.choice([1.0, 0.5, 0.25], size=(B, n_q, Hq)) / SCALE_LOG2
     qb = f32_to_bf16_bits(q)
     k = torch.zeros((B, S, Hkv, kt, D), device="cuda")
-    k[..., D // 2 - 1] = torch.tensor(rise, device="cuda", dtype=torch.float32)
+    k[..., D // 2 - 1] = torch.tensor(rise[0] / grow[0], device="cuda", dtype=torch.float32)
     v = torch.randn((B, S, Hkv, kt, D), generator=gen, device="cuda").to(torch.float8_e4m3fn)
     dev = [fp8_from_rows("k", k.to(torch.float8_e4m3fn).view(torch.uint8)), fp8_from_rows("v", v.view(torch.uint8))]
     ones = torch.ones((B, S, Hkv), device="cuda")
@@ -106,14 +108,15 @@ def test_block_over_the_8_bit_cache(name, B, G, S):
     o = torch.full((B, n_q, Hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
     lse = torch.full((B, Hq, n_q), float("nan"), device="cuda")
     ws = pc.alloc_workspace(pc.pc_parallel_attn_fp8_workspace_bytes(B, n_q, S, kt, 0, Hq, Hkv, D, True))
-    pc.pc_parallel_attn_fp8(bits_to_dev(qb), *dev, ones, ones * BIG, torch.tensor(lens, dtype=torch.int32, device="cuda"), None, None, None,
+    k_scale = ones * torch.tensor(grow, device="cuda", dtype=torch.float32)[None, :, None]
+    pc.pc_parallel_attn_fp8(bits_to_dev(qb), *dev, k_scale.contiguous(), ones * BIG, torch.tensor(lens, dtype=torch.int32, device="cuda"), None, None, None,
                             0, B, n_q, S, kt, Hq, Hkv, D, 0, 1.0e30, 0.0, o, lse, ws, k_self=slf_k, v_self=(slf_v.float() * BIG).to(torch.bfloat16))
     torch.cuda.synchronize()
     assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
     qs, t = as_multiplied(bf16_bits_to_f64(qb)[..., D // 2 - 1]), np.arange(n_q)
     for b, h in [(0, 0), (0, Hq - 1), (B - 1, Hq // 2)]:
         g = h // G
-        key = np.concatenate([rise[:n] for n in lens[b]] + [level[4 * t // n_q]])
+        key = np.concatenate([rise[s, :n] for s, n in enumerate(lens[b])] + [level[4 * t // n_q]])
         val = np.concatenate([v[b, s, g, :n].float().cpu().numpy() for s, n in enumerate(lens[b])] + [slf_v[b, :, g].float().cpu().numpy()])
         s = qs[b, :, h, None] * key[None]
         s[:, -n_q:][t[None] > t[:, None]] = -np.inf

@@ -1,5 +1,5 @@
 """Local attention with logits at the edges of the window of a row's softmax reference in the kernel of 64 query rows a
-wavefront, a lane's step sum of 2^48: just inside it the probabilities are as large as they get and nothing moves, just
+wavefront, a lane's step sum of 2^90: just inside it the probabilities are as large as they get and nothing moves, just
 outside the step is taken anew.  The kernel of 32 rows (short rows), whose references move from 2^8 on, gets the same logits.
 
 Logits are known exactly, as in test_gpu_reference_moves.py: the slowest pair of a head, which the largest angle here,
@@ -18,10 +18,10 @@ pytestmark = pytest.mark.gpu
 
 D = 128
 STEPS = {                                                   # logits of the row's four quarters of keys, log2 units
-    "inside": [0.0, 20.0, 43.0, 43.5],                      # 16 keys a lane: 2^47.5
-    "at the edge": [0.0, 43.5, 44.0, 44.5],
-    "outside": [0.0, 46.0, 49.0, 97.0],
-    "inside, then outside": [0.0, 43.0, 90.0, 91.0],
+    "inside": [0.0, 40.0, 85.0, 85.5],                      # 16 keys a lane: 2^89.5
+    "at the edge": [0.0, 85.5, 86.0, 86.5],
+    "outside": [0.0, 88.0, 91.0, 180.0],
+    "inside, then outside": [0.0, 85.0, 174.0, 175.0],
 }
 
 

@@ -76,10 +76,13 @@ def test_wide_attention_edges(case):
 
 J = np.arange(1290)
 LEVELS = {                                                  # a key's logit for a query of 1, log2 units
-    "every step": 12.0 * (J // 32),
-    "just below and above the window": np.select([J < 40, J < 270, J < 611, J < 900], [0.0, 6.0, 10.0, 10.0625], 21.0),
+    "every step": 128.0 * (J // 32),
+    "every tile's second half": 128.0 * ((J + 32) // 64),
+    "two steps in turn": np.select([J < 160, J < 192, J < 544, J < 576], [0.0, 100.0, 200.0, 300.0], 400.0),
+    # a lane's 16 keys add up to more than 2^90 above 86
+    "just below and above the window": np.select([J < 40, J < 270, J < 611, J < 900], [0.0, 80.0, 86.0, 86.5], 180.0),
     "beyond the range of exp2": np.where(J < 77, 0.0, np.where(J < 700, 300.0, 900.0)),
-    "one key": np.where(J == 95, 40.0, np.where(J == 800, 90.0, 0.0)),
+    "one key": np.where(J == 95, 100.0, np.where(J == 800, 200.0, 0.0)),
     "last key": np.where(J == 1289, 200.0, 0.0),
 }
 
