@@ -377,9 +377,9 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
       if (i < 14 && i % 2 == 0) round_part(i / 2);           // of the step before
       __builtin_amdgcn_sched_barrier(0);
     }
-    // some row's maximum exceeds its reference by more than 86; every row beyond 6 moves (or a segment begins: see flash_workgroup)
+    // some row's maximum exceeds its reference by more than 86, or a segment begins (see flash_workgroup): every row whose
+    // maximum exceeds its reference moves (only those beyond 6: the same time at deviations from 1 to 32)
     if (__any(most > PC_FA_WINDOW) || (IMAGES && lim.seg_start)) {
-      const float least = IMAGES && lim.seg_start ? 0.0f : 6.0f;
       far |= !IMAGES || __any(fmaxf(most, fmaxf(l_run[0], l_run[1])) > PC_FW_FAR);
       o_settle();
 #pragma unroll
@@ -389,7 +389,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
         for (int r = 1; r < 16; ++r) tm = fmaxf(tm, s_cur[nb][r]);
         mx[nb] = tm;
         tm = pc_xhalf_max(tm);
-        const float delta = tm > least ? tm : 0.f, alpha = __builtin_amdgcn_exp2f(-delta);
+        const float delta = fmaxf(tm, 0.f), alpha = __builtin_amdgcn_exp2f(-delta);
         m_run[nb] += delta;
         l_run[nb] *= alpha;
         dl_run[nb] *= alpha;
