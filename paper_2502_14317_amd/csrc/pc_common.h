@@ -315,6 +315,9 @@ int pc_flash_parts(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int hea
 // this and of every smaller call, so it never falls where a size grows
 size_t pc_flash_part_rows(size_t rows, long long n_tiles, int has_self);
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st);
+// Which calls get 64 query rows a wavefront: local ones (heads of a workgroup, or 0), and blocks of rows over tile images
+int pc_flash_wide(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim);
+int pc_flash_wide_images(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int n_parts);
 // One launch of both (the chunk sums are not its business), and the parts of the global one in it
 int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st);
 int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most);

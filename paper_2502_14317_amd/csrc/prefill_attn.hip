@@ -1021,35 +1021,41 @@ static long long flash_blocks(PcFlashArgs& a) {
 // ---- 64 rows a wavefront (wide_workgroup)
 // Heads of a workgroup: the largest power of two up to 8 that divides the group; 1: rows of one head
 static int wide_heads(int G) { return G % 8 == 0 ? 8 : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
-static long long wide_workgroups(int n_seq, int n_rows, int n_q_heads, int n_kv_heads) {
+// Which local calls take it, and the heads of a workgroup (0: 32 rows a wavefront).  A workgroup costs 12000 cycles around
+// its loop that nothing else on its CU hides, and 256 CUs hold one each: long rows, more than 1.25 rounds of them.  Of
+// full Q tiles from 1984 rows on, with two heads, whose Q tile is 128 positions too, from 3072, with one head, whose causal
+// end is four tiles long, from 7680; where the 32 rows' last Q tile of 128 is half empty and the narrower one here is not,
+// from 1280 on.  Calls with the pre-pass (us, 32 rows a wavefront / 64; sequences x rows): 32 / 8 heads, 1 x 2500 68.6 / 71.9, 1 x
+// 3000 90.8 / 86.5, 2 x 1300 53.4 / 48.1, 36 x 1300 693 / 653, 4 x 1500 98.5 / 102.0, 36 x 1500 810 / 820, 16 x 1920 1.007 times as long,
+// 16 x 1984 0.975, 16 x 2048 0.975, 36 x 3000 2653 / 2501, 4 x 8192 1834 / 1710; 16 / 4, 2 x 2500 70.1 / 72.6, 12 x 1300 124 / 115, 8 x 1500
+// 97.5 / 100.4, 1 x 8192 282 / 228; 8 / 1, 8 x 1300 51.6 / 45.7, 24 x 1408 1.017 times as long, 4 x 4096 152 / 126; 4 / 2, 24 x 2000 129 /
+// 132, 12 x 2500 101 / 95, 16 x 2500 126 / 127, 36 x 3000 362 / 353, 8 x 4096 154 / 136.  One head: 32 / 32, 8 x 2000 384 / 402, 8 x
+// 4096 1199 / 1172, 4 x 6144 1200 / 1222, 8 x 8192 4054 / 3907; 7 / 7, 8 x 6144 1.053 times as long, 8 x 7680 0.986.
+int pc_flash_wide(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim) {
+  if (head_dim != FW_D || n_q_heads > 65536) return 0;       // (64 rows of q or o: 32-bit byte offsets)
   const int heads = wide_heads(n_q_heads / n_kv_heads), P = 256 / heads;
-  return (long long)n_seq * (n_q_heads / heads) * ((n_rows + P - 1) / P);
-}
-// Which local calls take it: a workgroup costs 12000 cycles around its loop that nothing else on its CU
-// hides, and 256 CUs hold one each, so it takes long rows and many of them.  Calls with the pre-pass (us, 32 rows a
-// wavefront / 64; sequences x rows): 32 / 8 heads, 1 x 1300 32.8 / 39.1, 2 x 1300 50.4 / 47.3, 36 x 1300 658 / 641,
-// 36 x 900 386 / 373, 36 x 600 206 / 215, 1 x 2000 50.6 / 55.1, 2 x 2000 85.1 / 78.4, 1 x 3000 88.5 / 84.2, 4 x 8192 1817 / 1672;
-// 16 / 4, 1 x 3000 68.7 / 68.7, 4 x 1300 51.0 / 46.9; 8 / 1, 4 x 2000 59.6 / 55.9; 4 / 2, 4 x 4096 90.2 / 99.6, 16 x 4096 287 / 265.
-// One head a workgroup, whose causal end is four tiles long: 32 / 32, 8 x 2000 371 / 403, 8 x 4096 1152 / 1155, 1 x
-// 4096 157 / 150, 1 x 8192 536 / 489, 8 x 8192 4004 / 3869.
-static bool wide_fits(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim) {
-  if (head_dim != FW_D || n_q_heads > 65536) return false;   // (64 rows of q or o: 32-bit byte offsets)
-  const int least = wide_heads(n_q_heads / n_kv_heads) > 1 ? 1280 : 6144;
-  return n_rows >= least && wide_workgroups(n_seq, n_rows, n_q_heads, n_kv_heads) >= 320;
+  const bool half_empty = (n_rows + PC_FA_BM - 1) / PC_FA_BM * PC_FA_BM > (n_rows + P - 1) / P * P;
+  const int least = heads == 1 ? 7680 : half_empty ? 1280 : heads == 2 ? 3072 : 1984;
+  const long long workgroups = (long long)n_seq * (n_q_heads / heads) * ((n_rows + P - 1) / P);
+  return n_rows >= least && workgroups > 320 ? heads : 0;
 }
 // ... and which block attentions over tile images (the 8-bit cache), in the same parts: where 32 rows a wavefront put
-// two workgroups on a CU (one alone has its LDS to itself: nothing to gain), over runs worth the start.  Whole cache
-// build and attention (us, 32 rows a wavefront / 64), sequences x segments x keys, rows: 32 / 8 heads, 4 x 8 x 2048, 512
-// 702 / 645; 2 x 8 x 2048, 512 378 / 354; 4 x 8 x 2048, 300 548 / 517; 4 x 8 x 600, 512 253 / 241; 16 / 4, 4 x 3 x 1500, 512 140 / 135;
-// 32 / 32, 4 x 8 x 520, 512 427 / 417; 3 x 5 x 1000, 170 305 / 307.
+// two workgroups on a CU (one alone has its LDS to itself: nothing to gain), no block of 256 packed rows has an empty
+// half, and a workgroup's run is 32 tiles or more, worth the start.  Whole cache build and attention (us, 32 rows a wavefront /
+// 64), sequences x segments x keys, rows (tiles a run): 32 / 8 heads, 4 x 8 x 2048, 512 (264) 691 / 648, 2 x 8 x 2048, 512 (132) 379 /
+// 359, 3 x 8 x 2048, 512 (66) 565 / 544, 3 x 8 x 2048, 128 (51) 285 / 277, 2 x 8 x 2048, 128 (32) 205 / 203, 3 x 4 x 1500, 512 (26) 265 /
+// 268, 2 x 8 x 700, 256 (23) 118 / 119, 1 x 8 x 2048, 128 (16) 127 / 130, 2 x 8 x 700, 128 (11) 102 / 105; half empty: 3 x 8 x 2048, 24
+// (12) 237 / 261, 32 / 32, 2 x 8 x 2048, 128 (32) 607 / 645.
+int pc_flash_wide_images(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int n_parts) {
+  const long long rows = (long long)n_rows * (n_q_heads / n_kv_heads), blocks = (rows + PC_FA_BM - 1) / PC_FA_BM;
+  return head_dim == FW_D && blocks % 2 == 0 && blocks * n_seq * n_kv_heads * n_parts > 256 && n_tiles >= 32LL * n_parts;
+}
 static bool wide_images_fits(const PcFlashArgs& a) {
-  const long long G = a.n_q_heads / a.n_kv_heads;
-  const long long n = (long long)a.n_seq * a.n_kv_heads * ((a.n_rows * G + PC_FA_BM - 1) / PC_FA_BM) * a.n_parts;
   long long tiles = 0;
   for (const PcKvGroup& kg : a.grp) tiles += (long long)kg.n * ((kg.cap + 63) / 64);
-  return a.images && a.head_dim == FW_D && n > 256 && tiles >= 64;
+  return a.images && pc_flash_wide_images(a.n_seq, a.n_rows, a.n_q_heads, a.n_kv_heads, a.head_dim, tiles, a.n_parts);
 }
-static bool wide_fits(const PcFlashArgs& a) { return wide_fits(a.n_seq, a.n_rows, a.n_q_heads, a.n_kv_heads, a.head_dim); }
+static int wide_fits(const PcFlashArgs& a) { return pc_flash_wide(a.n_seq, a.n_rows, a.n_q_heads, a.n_kv_heads, a.head_dim); }
 // As flash_blocks.  Groups of fewer than two rounds of an XCD's 32 slots are interleaved up to two rounds: 16 x
 // 2000 rows, 32 / 8 heads, 573 -> 558 us.
 static long long wide_blocks(PcFlashArgs& a) {
@@ -1145,9 +1151,8 @@ static int launch_both_wide_t(const PcFlashArgs& local, const PcFlashArgs& globa
   return PC_OK;
 }
 int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hipStream_t st) {
-  if (wide_fits(local))
-    return wide_heads(local.n_q_heads / local.n_kv_heads) > 1 ? launch_both_wide_t<PC_FW_PAIR>(local, global, st)
-                                                              : launch_both_wide_t<PC_FW_HEAD>(local, global, st);
+  if (const int heads = wide_fits(local))
+    return heads > 1 ? launch_both_wide_t<PC_FW_PAIR>(local, global, st) : launch_both_wide_t<PC_FW_HEAD>(local, global, st);
   return local.head_dim == 128 ? launch_flash_both_t<128>(local, global, st) : launch_flash_both_t<64>(local, global, st);
 }
 
@@ -1160,8 +1165,8 @@ int pc_launch_flash_both(const PcFlashArgs& local, const PcFlashArgs& global, hi
 // 4, 8 x 1400: 3 254 / 1 356, 2 257, 8 267; 1 x 1000 + 24, 24 / 8 of 64 values, 1 x 900: 2 49.7 / 1 54.9, 3 48.3, 16 51.9.
 // With 64 rows a wavefront 256 slots, 8 us + 1.45 a tile (local), and the global ones have their CU to themselves (1.27).
 int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int most) {
-  const bool wide = wide_fits(n_seq, n_rows, n_q_heads, n_kv_heads, head_dim);
-  const int heads = wide ? wide_heads(n_q_heads / n_kv_heads) : 1, rows = wide ? 256 / heads : PC_FA_BM;
+  const int wide = pc_flash_wide(n_seq, n_rows, n_q_heads, n_kv_heads, head_dim);
+  const int heads = wide ? wide : 1, rows = wide ? 256 / heads : PC_FA_BM;
   const double loc_us = wide ? 1.45 : head_dim == 128 ? 1.54 : 1.0, glob_us = wide ? 1.27 : head_dim == 128 ? 2.1 : 1.4;
   const double slots = wide ? 256.0 : 512.0, start_us = wide ? 8.0 : 10.0;
   double work = 0.0, longest = 0.0;
@@ -1184,8 +1189,7 @@ int pc_flash_both_parts(int n_seq, int n_rows, int n_q, int n_q_heads, int n_kv_
 
 int pc_launch_flash(const PcFlashArgs& a, hipStream_t st) {
   if (a.global && wide_images_fits(a)) return launch_wide_t<PC_FW_IMAGES>(a, st);
-  if (!a.global && wide_fits(a))
-    return wide_heads(a.n_q_heads / a.n_kv_heads) > 1 ? launch_wide_t<PC_FW_PAIR>(a, st) : launch_wide_t<PC_FW_HEAD>(a, st);
+  if (const int heads = a.global ? 0 : wide_fits(a)) return heads > 1 ? launch_wide_t<PC_FW_PAIR>(a, st) : launch_wide_t<PC_FW_HEAD>(a, st);
   if (a.head_dim == 128)
     return !a.global ? launch_flash_t<128, PC_FA_LOCAL>(a, st)
                      : (a.images ? launch_flash_t<128, PC_FA_IMAGES>(a, st) : launch_flash_t<128, PC_FA_ROWS>(a, st));

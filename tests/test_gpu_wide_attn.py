@@ -33,10 +33,10 @@ CASES = [
     (8, 1270, 74, 8, 1, [1270, 0, 1, 600, 1206, 1207, 64, 1238]),   # sequences that end at, before and behind tile edges
     (6, 1220, 61, 12, 3, None),                             # 4 heads x 64 positions; 18 groups: two dealt to all XCDs
     (12, 1283, 13, 8, 2, [1283, 2, 1200, 40, 900, 500, 51, 1139, 755, 1, 0, 321]),
-    (5, 1250, 58, 12, 2, None),                             # groups of 6: 2 heads x 128 positions, three workgroups a Q tile
-    (5, 1300, 108, 12, 2, [1300, 19, 20, 916, 1172]),
-    (2, 6100, 57, 7, 7, None),                              # one head x 256 positions
-    (2, 6100, 61, 9, 3, [6100, 3]),                         # groups of 3: one head too; a short sequence next to a long one
+    (5, 3030, 58, 12, 2, None),                             # groups of 6: 2 heads x 128 positions, three workgroups a Q tile
+    (5, 3000, 108, 12, 2, [3000, 19, 20, 916, 2872]),
+    (2, 7700, 57, 7, 7, None),                              # one head x 256 positions
+    (2, 7700, 61, 9, 3, [7700, 3]),                         # groups of 3: one head too; a short sequence next to a long one
 ]
 
 

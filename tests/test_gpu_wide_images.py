@@ -1,5 +1,5 @@
-"""A block of query rows over the 8-bit cache with 64 packed rows a wavefront (64 tiles and more of a KV head, rows that fill
-the CUs): edges of tiles, blocks and parts, lengths of zero, with NaN behind every length, against 64 bits."""
+"""A block of query rows over the 8-bit cache with 64 packed rows a wavefront (runs of 32 tiles and more, workgroups that fill
+the CUs; test_wide_routes_host.py checks that every case gets it): edges of tiles, blocks and parts, lengths of zero, with NaN behind every length, against 64 bits."""
 import pytest
 import torch
 
@@ -10,11 +10,11 @@ pytestmark = pytest.mark.gpu
 
 # B, n_q, S, k_t (tail capacity too), H_q, H_kv, tail, self, per-head lengths
 CASES = [
-    (4, 100, 33, 97, 128, 16, True, True, True),            # 800 packed rows: the last block of a workgroup is cut off; one part
-    (4, 17, 33, 97, 128, 16, True, True, False),            # 136 rows, several parts
-    (1, 130, 64, 64, 16, 16, False, False, False),          # one head a group, tiles full
-    (2, 33, 70, 63, 24, 8, True, False, True),              # groups of 3; more segments than lanes, every tile masked
-    (2, 512, 5, 900, 8, 8, False, True, False),             # the causal diagonal over 8 tiles, 4 of them a workgroup's own
+    (4, 125, 33, 97, 128, 16, True, True, True),            # 1000 packed rows: the last block of a workgroup is cut off; one part
+    (4, 17, 70, 97, 128, 16, True, True, False),            # 136 rows, several parts
+    (4, 130, 64, 64, 64, 64, False, False, False),          # one head a group, tiles full
+    (4, 65, 70, 63, 192, 64, True, False, True),            # groups of 3; more segments than lanes, every tile masked
+    (8, 512, 5, 900, 16, 16, False, True, False),           # the causal diagonal over 8 tiles, 4 of them a workgroup's own
 ]
 
 
