@@ -3,7 +3,7 @@ same bits everywhere but in the global attention, whose keys may be cut into oth
 probabilities round to bf16 against other references (2^-9 relative each; outputs within the outputs'
 tolerance).  Shapes on either side of the rules: more than 64 chunks or 2048 block sums a chunk (selection in
 launches of its own), segments of 64 KiB and more (gather in a launch of its own), few query columns (no tile path), global attention cut into parts, a global workgroup
-count that is no multiple of 8, ragged chunks, calibration."""
+count that is no multiple of 8, ragged chunks, calibration; and 64 query rows a wavefront next to the global attention."""
 import numpy as np
 import pytest
 import torch
@@ -28,9 +28,16 @@ CASES = [
     (3, 300, 20, 4, 2, 64, 20, 2, 257, True, None),          # above
     (3, 1300, 40, 4, 2, 128, 20, 3, 128, True, (0.0, 0, 1290)),   # heads without 128 candidates: zero rows
 ]
+# 64 query rows a wavefront: 4, 2, 8 heads and one a workgroup, (sequence, KV head) groups beyond a multiple of 8
+WIDE = [
+    (6, 1220, 61, 12, 3, 128, 61, 2, 300, True, None),
+    (5, 3030, 58, 12, 2, 128, 32, 3, 700, False, (0.05, 0, 20)),
+    (9, 1250, 31, 8, 1, 128, 31, 9, 620, True, None),
+    (2, 7700, 57, 7, 7, 128, 57, 2, 7000, False, None),      # global attention cut into parts, here and in the case above
+]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c[:9])))
+@pytest.mark.parametrize("case", CASES + WIDE, ids=lambda c: "x".join(map(str, c[:9])))
 def test_layer_call_is_the_separate_calls(case):
     C, w, wq, Hq, Hkv, D, obs, kc, kt, ragged, cal = case
     print("layer call", case, flush=True)

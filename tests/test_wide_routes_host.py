@@ -7,6 +7,7 @@ import pytest
 import paper_2502_14317_amd as pc
 import test_gpu_attention_error
 import test_gpu_large_values
+import test_gpu_layer_call
 import test_gpu_wide_attn
 import test_gpu_wide_images
 
@@ -20,6 +21,7 @@ def internal(name, types):
 local = internal("pc_flash_wide", "iiiii")                  # heads of a workgroup, or 0
 images = internal("pc_flash_wide_images", "iiiiixi")
 parts = internal("pc_flash_parts", "iiiiix")
+both_parts = internal("pc_flash_both_parts", "iiiiiixi")
 
 
 def over_images(B, n_q, S, k_t, H_q, H_kv, tail=False, own=False):
@@ -42,6 +44,16 @@ def test_other_local_cases():
         assert (local(C, w + wq, Hq, Hkv, 128) > 0) == (w > 200)
     for C, w, wq, Hq, Hkv, D, share in test_gpu_attention_error.CASES:
         assert (local(C, w + wq, Hq, Hkv, D) > 0) == (share < 1.1)
+
+
+def test_layer_cases():
+    cut = []
+    for C, w, wq, Hq, Hkv, D, _, kc, kt, _, _ in test_gpu_layer_call.WIDE:
+        assert local(C, w + wq, Hq, Hkv, D) == {4: 4, 6: 2, 8: 8, 1: 1}[Hq // Hkv]
+        tiles = kc * -(-kt // 64) + -(-wq // 64)
+        cut.append(both_parts(C, w + wq, wq, Hq, Hkv, D, tiles, parts(1, wq, Hq, Hkv, D, tiles)) > 1)
+    assert cut == [False, False, True, True]
+    assert not any(local(c[0], c[1] + c[2], c[3], c[4], c[5]) for c in test_gpu_layer_call.CASES)
 
 
 @pytest.mark.parametrize("case", test_gpu_wide_images.CASES, ids=str)
