@@ -1,4 +1,5 @@
 """Builds libparallelcomp.so (hand-written HIP for gfx950) in-tree with hipcc."""
+import importlib.util
 import os
 import subprocess
 import sys
@@ -17,6 +18,21 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-
                "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 
 
+# Its assembly text is checked before the library is linked; the compiler leaves what it assembled beside the object
+CHECKED = "prefill_attn.hip"
+
+
+def check_spacing(obj_dir: str) -> None:
+    spec = importlib.util.spec_from_file_location("spacing", os.path.join(PKG_DIR, "spacing.py"))
+    spacing = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(spacing)
+    with open(os.path.join(obj_dir, CHECKED.replace(".hip", "-hip-amdgcn-amd-amdhsa-gfx950.s"))) as f:
+        spacing.check(f.read())
+    for name in os.listdir(obj_dir):
+        if name.startswith((CHECKED + "-", CHECKED.replace(".hip", "-"))):
+            os.remove(os.path.join(obj_dir, name))
+
+
 def build_library(verbose: bool = True, jobs: int = 6) -> str:
     """Compile every translation unit and link the shared library.  Always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -27,6 +43,8 @@ def build_library(verbose: bool = True, jobs: int = 6) -> str:
         obj = os.path.join(obj_dir, src.replace(".hip", ".o"))
         objs.append(obj)
         cmd = [hipcc, *HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC, "-c", os.path.join(CSRC, src), "-o", obj]
+        if src == CHECKED:
+            cmd.append("-save-temps=obj")
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
@@ -43,6 +61,7 @@ def build_library(verbose: bool = True, jobs: int = 6) -> str:
             print(f"FAILED: {src}", file=sys.stderr)
     if failed:
         raise RuntimeError("hipcc failed")
+    check_spacing(obj_dir)
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -1,10 +1,10 @@
-// Causal local attention with 64 query rows a wavefront: flash_workgroup's local mode for head_dim 128 and
-// calls of many long rows (pc_flash_wide says which).  Included by prefill_attn.hip.
+// Attention with 64 query rows a wavefront for head_dim 128: flash_workgroup's local mode for calls of many long rows
+// (pc_flash_wide) and its mode of tile images for long runs (pc_flash_wide_images).  Included by prefill_attn.hip.
 //
 // What bounds flash_workgroup: at 32 rows a wavefront every MFMA has an LDS operand read of its own, so the
 // CU's LDS reads take as long as its MFMAs, and on real data the clock falls to 1.5 GHz under the power limit.
 // Two 32-row blocks share every K and V^T operand here: half the LDS reads, half the tile copies.  That takes
-// 470 registers, so one wavefront a SIMD and one workgroup of 256 rows a CU; what the second wavefront used to
+// 461 registers (over tile images, with the walk, 491 and 76 scalar ones spilled; next to the global attention 29), so one wavefront a SIMD and one workgroup of 256 rows a CU; what the second wavefront used to
 // hide has to fit between the MFMAs of the one.  It does: a step is 32 slices of one MFMA (32 cycles), a
 // softmax element for each lane (exp2 8, add 4, half a pack 8 cycles) and every other slice an LDS read.
 // Cycles a 64-key tile (2048 of MFMAs): 2350; without the loads 2320, without the barrier 2300, without
@@ -14,11 +14,11 @@
 // Registers: O^T and Q^T lie in accumulation registers, S^T, P^T and the operands in the others.  The compiler
 // would put O^T into the others too and move Q^T back and forth, so P V products are written as assembly text;
 // so are the exponentials, sums and packs, which it otherwise moves across the slices (2700 cycles a tile).
-// What the compiler then no longer sees to: two instructions between a write of a product's operand and the
+// What the compiler then no longer sees to: two issue states between a write of a product's operand and the
 // product (P^T is packed a region ahead, and each step's first product waits by itself, as a copy of O^T may
-// stand in front of it), eleven between a product and a use of its result (o_settle; S^T is used two
-// products after its last one), one between an exponential and the use of its result (the group after it).
-// tests/test_wide_attn_host.py looks for all three in the compiled code.
+// stand in front of it), twelve between a product and a use of its result (o_settle; S^T is used two
+// products after its last one), seven before its addend is written, one between an exponential and the use of its result
+// (the group after it).  spacing.py looks for all of them in the compiled code of every build.
 //
 // PC_FW_PAIR: the workgroup takes `wide_heads` query heads of a KV head (2, 4 or 8) at 256 / wide_heads positions,
 // a wavefront two heads at 32 positions: one rotation table row, one mask and one causal end for both blocks.
