@@ -39,9 +39,10 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
   constexpr bool PAIR = MODE == PC_FW_PAIR, IMAGES = MODE == PC_FW_IMAGES;
   constexpr int D = FW_D, KS = D / 16, DB = D / 32, HALF = D / 2, NB = 2, NM = NB * KS;
   // ---- which (sequence, KV head), Q tile and heads: as flash_workgroup; a.group workgroups share a Q tile.  The
-  //      groups that share an XCD change places from turn to turn: an XCD hands every fourth workgroup to the same
+  //      groups that share an XCD change places every other turn: an XCD hands every fourth workgroup to the same
   //      shader engine, in order, and with a short sequence always in the same place two engines got all the
-  //      padding (12 ragged chunks of 2214 rows 332 -> 309 us).  The groups beyond a multiple of 8 are dealt to
+  //      padding (12 ragged chunks of 2214 rows 332 -> 309 us; changed every turn, a group of a batch of 2, 6 or 10 would
+  //      keep to two engines too, changed every other one each engine gets a quarter to within 6 %).  The groups beyond a multiple of 8 are dealt to
   //      all XCDs in the same way, long Q tiles of all of them first.
   const int n_qt = a.n_qt, per_group = (IMAGES ? a.n_parts : a.group) * n_qt;
   const int n_groups = a.n_seq * a.n_kv_heads, full_blocks = n_groups / 8 * 8 * per_group;
@@ -52,7 +53,7 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     const int left = n_groups / 8 - batch * a.group_batch, n_batch = min(a.group_batch, left);
     const PcDiv by = left >= a.group_batch ? a.batch_div : a.last_div;
     within = pc_div(in_batch, by);
-    const int place = in_batch - within * n_batch + (within >> (n_batch % 4 == 2 ? 1 : 0));
+    const int place = in_batch - within * n_batch + (within >> 1);
     cg = (batch * a.group_batch + pc_mod(place, n_batch, by)) * 8 + xcd;
   } else {
     const int rest = bid - full_blocks, n_rest = n_groups % 8;
