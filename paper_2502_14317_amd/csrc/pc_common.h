@@ -283,15 +283,16 @@ struct PcFlashArgs {
                             //   rotated, multiplied by scale * log2(e) and rounded beforehand
   const float2* table;      // local: the queries' table [D / 4][table_rows][2 pairs], (cos, sin) x scale x log2(e)
   int table_rows;           //   (n_rows rounded up to 128)
+  int wide_heads;           // 64 rows a wavefront: heads of a workgroup (set by the launcher)
   void* o;                  // [n_seq, n_rows, H_q, D] bf16
   float* lse;               // [n_seq, H_q, n_rows] or nullptr
   int n_seq, n_rows, n_q_heads, n_kv_heads, head_dim;
   int group_batch;          // (sequence, KV head) groups an XCD interleaves, >= 1 (set by the launcher)
   // what a workgroup divides its number by (set by the launcher): H_q / H_kv = group, Q tiles, workgroups of a group, of
   // an XCD's batch of groups, groups of a batch and of the last one, KV heads, parts; with 64 rows a wavefront
-  // also groups beyond a multiple of 8, and group = the workgroups of wide_heads heads each that share a Q tile
-  int group, n_qt, wide_heads;
-  PcDiv group_div, qt_div, per_group_div, per_batch_div, batch_div, last_div, heads_div, parts_div, rest_div;
+  // per_group_div is by the groups beyond a multiple of 8, and group = the workgroups of wide_heads heads each that share a Q tile
+  int group, n_qt;
+  PcDiv group_div, qt_div, per_group_div, per_batch_div, batch_div, last_div, heads_div, parts_div;
   float scale;
   // local
   const void* k_img;        // K tile images (rotated keys), image index = seq * img_seq_stride +

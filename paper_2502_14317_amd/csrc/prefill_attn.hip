@@ -1068,7 +1068,7 @@ static long long wide_blocks(PcFlashArgs& a) {
     a.group_batch = 1;
     a.group_div = pc_div_by(G); a.heads_div = pc_div_by(a.n_kv_heads); a.qt_div = pc_div_by(a.n_qt);
     a.parts_div = pc_div_by(a.n_parts); a.per_batch_div = pc_div_by(a.n_qt * a.n_parts);
-    a.batch_div = a.last_div = pc_div_by(1); a.rest_div = pc_div_by((int)((long long)a.n_seq * a.n_kv_heads % 8));
+    a.batch_div = a.last_div = pc_div_by(1); a.per_group_div = pc_div_by((int)((long long)a.n_seq * a.n_kv_heads % 8));
     return (long long)a.n_seq * a.n_kv_heads * a.n_qt * a.n_parts;
   }
   const long long per_group = (long long)a.n_qt * a.group, n_groups = (long long)a.n_seq * a.n_kv_heads, groups_xcd = n_groups / 8;
@@ -1080,7 +1080,7 @@ static long long wide_blocks(PcFlashArgs& a) {
   a.group_div = pc_div_by(a.group); a.heads_div = pc_div_by(a.n_kv_heads);
   a.per_batch_div = pc_div_by((int)(a.group_batch * per_group));
   a.batch_div = pc_div_by(a.group_batch); a.last_div = pc_div_by((int)(groups_xcd % a.group_batch));
-  a.rest_div = pc_div_by((int)(n_groups % 8));
+  a.per_group_div = pc_div_by((int)(n_groups % 8));
   return n_groups * per_group;
 }
 

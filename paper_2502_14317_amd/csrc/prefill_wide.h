@@ -57,8 +57,8 @@ __device__ __forceinline__ void wide_workgroup(const PcFlashArgs& a, int bid, ui
     cg = (batch * a.group_batch + pc_mod(place, n_batch, by)) * 8 + xcd;
   } else {
     const int rest = bid - full_blocks, n_rest = n_groups % 8;
-    within = pc_div(rest, a.rest_div);
-    cg = n_groups / 8 * 8 + pc_mod(rest - within * n_rest + within, n_rest, a.rest_div);
+    within = pc_div(rest, a.per_group_div);
+    cg = n_groups / 8 * 8 + pc_mod(rest - within * n_rest + within, n_rest, a.per_group_div);
   }
   const int seq = pc_div(cg, a.heads_div), g = cg - seq * a.n_kv_heads;
   const int turn = pc_div(within, IMAGES ? a.qt_div : a.group_div);        // (IMAGES: the part)
