@@ -6,7 +6,8 @@ attention with chunk-local RoPE and the fused query-score reduction, chunk top-k
 token top-k, KV compaction gather, and the query's parallel attention over the kept KV.
 Inputs are resident in HBM before the timed region.  One JSON line is printed:
   value      context tokens per second per layer for the whole step
-  roofline   the dominant kernel (flash_fwd_kernel) against the bf16 MFMA peak, its duration
+  roofline   the dominant kernel (the attention launch, recorded as flash_fwd_kernel whatever its
+             variant: flash_both_wide_kernel<0> on cfg1) against the bf16 MFMA peak, its duration
              measured with HIP events recorded inside the library on the launch stream
   cpu_baseline  the fp64 CPU oracle timed on a bounded sample of the same workload
   secondary  the HBM-bound kernels (split-KV decode attention, KV gather) on the decode config
@@ -30,7 +31,7 @@ PEAK_HBM_BYTES = 8.0e12       # MI355X HBM3E
 # kernels taken with the commands in profiles/pmc_hbm_traffic.md (which lists the raw counts), not
 # values measured inside this process.  Keyed by (kernel, workload).
 MEASURED_TRAFFIC = {
-    ("flash_fwd_kernel", "cfg1_llama3_8b_128k"): 1.298e6 * 2048 + 1.069e6 * 1024,
+    ("flash_fwd_kernel", "cfg1_llama3_8b_128k"): 1.364e6 * 2048 + 1.069e6 * 1024,
     ("scores_kernel<1>+kv_prepass", "cfg1_llama3_8b_128k"): 2.734e5 * 2048 + 7.875e5 * 1024,
     ("scores_kernel<2>", "cfg1_llama3_8b_128k"): 1.281e5 * 2048 + 3.8e3 * 1024,
     ("decode_attn_kernel", "cfg4_decode_llama3_8b"): 2.10e6 * 2048 + 1.3e2 * 1024,

@@ -7,9 +7,9 @@
 // 461 registers (over tile images, with the walk, 491 and 76 scalar ones spilled; next to the global attention 29), so one wavefront a SIMD and one workgroup of 256 rows a CU; what the second wavefront used to
 // hide has to fit between the MFMAs of the one.  It does: a step is 32 slices of one MFMA (32 cycles), a
 // softmax element for each lane (exp2 8, add 4, half a pack 8 cycles) and every other slice an LDS read.
-// Cycles a 64-key tile (2048 of MFMAs): 2350; without the loads 2320, without the barrier 2300, without
-// either and without the LDS reads 2150.  16 x 8192 rows, 32 / 8 heads, with the pre-pass: 7500 us in
-// flash_workgroup, 6850 here (4950 and 5010 on all-zero inputs: what is saved is power); 64 x 8704 34.3 and 31.7 ms.
+// Cycles a 64-key tile (2048 of MFMAs), before the second row sum (round_part): 2350; without the loads 2320, without the
+// barrier 2300, without either and without the LDS reads 2150.  16 x 8192 rows, 32 / 8 heads, with the pre-pass: 7430 us in
+// flash_workgroup, 6800 here (4950 and 5010 on all-zero inputs: what is saved is power); 64 x 8704 33.6 and 30.8 ms.
 //
 // Registers: O^T and Q^T lie in accumulation registers, S^T, P^T and the operands in the others.  The compiler
 // would put O^T into the others too and move Q^T back and forth, so P V products are written as assembly text;
@@ -24,8 +24,8 @@
 // a wavefront two heads at 32 positions: one rotation table row, one mask and one causal end for both blocks.
 // PC_FW_HEAD: 256 positions of one head, 64 a wavefront.
 // PC_FW_IMAGES: flash_workgroup's mode of that name, rows of a KV group packed, parts and all: 4 x 512 rows of 32 / 8
-// heads over 8 x 2048 keys of the 8-bit cache 702 -> 645 us with everything else of the call, 3 sequences (two parts)
-// 567 -> 538, 2 x 512 of 32 / 32 714 -> 688.  Loads follow a walk over the segments' tiles that runs three ahead.
+// heads over 8 x 2048 keys of the 8-bit cache 691 -> 648 us with everything else of the call, 3 sequences (four parts)
+// 565 -> 544, 2 x 512 of 32 / 32 722 -> 702.  Loads follow a walk over the segments' tiles that runs three ahead.
 #define PC_FW_FAR 262144.f           // a lane's row sum above it shows a reference behind the row's maximum (2^18: 2^10 keys, 2^8 behind)
 #define PC_FW_RING 4                 // tiles of K and of V^T in LDS, 128 KiB
 constexpr int FW_D = 128, FW_TILE = 64 * FW_D;               // elements of a tile image
