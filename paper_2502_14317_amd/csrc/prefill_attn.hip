@@ -1041,14 +1041,16 @@ int pc_flash_wide(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head
 }
 // ... and which block attentions over tile images (the 8-bit cache), in the same parts: where 32 rows a wavefront put
 // two workgroups on a CU (one alone has its LDS to itself: nothing to gain), no block of 256 packed rows has an empty
-// half, and a workgroup's run is 32 tiles or more, worth the start.  Whole cache build and attention (us, 32 rows a wavefront /
+// half, and a workgroup's run is 32 tiles or more of 64 or more in all, worth the start.  Whole cache build and attention (us, 32 rows a wavefront /
 // 64), sequences x segments x keys, rows (tiles a run): 32 / 8 heads, 4 x 8 x 2048, 512 (264) 691 / 648, 2 x 8 x 2048, 512 (132) 379 /
 // 359, 3 x 8 x 2048, 512 (66) 565 / 544, 3 x 8 x 2048, 128 (51) 285 / 277, 2 x 8 x 2048, 128 (32) 205 / 203, 3 x 4 x 1500, 512 (26) 265 /
-// 268, 2 x 8 x 700, 256 (23) 118 / 119, 1 x 8 x 2048, 128 (16) 127 / 130, 2 x 8 x 700, 128 (11) 102 / 105; half empty: 3 x 8 x 2048, 24
+// 268, 2 x 8 x 700, 256 (23) 118 / 119, 1 x 8 x 2048, 128 (16) 127 / 130, 2 x 8 x 700, 128 (11) 102 / 105; of fewer in all: 4 x 4 x 400, 384 (34) 104 / 106,
+// 3 x 4 x 400, 512 (36) 103 / 105; half empty: 3 x 8 x 2048, 24
 // (12) 237 / 261, 32 / 32, 2 x 8 x 2048, 128 (32) 607 / 645.
 int pc_flash_wide_images(int n_seq, int n_rows, int n_q_heads, int n_kv_heads, int head_dim, long long n_tiles, int n_parts) {
   const long long rows = (long long)n_rows * (n_q_heads / n_kv_heads), blocks = (rows + PC_FA_BM - 1) / PC_FA_BM;
-  return head_dim == FW_D && blocks % 2 == 0 && blocks * n_seq * n_kv_heads * n_parts > 256 && n_tiles >= 32LL * n_parts;
+  return head_dim == FW_D && blocks % 2 == 0 && blocks * n_seq * n_kv_heads * n_parts > 256 &&
+         n_tiles >= 64 && n_tiles >= 32LL * n_parts;
 }
 static bool wide_images_fits(const PcFlashArgs& a) {
   long long tiles = 0;

@@ -75,6 +75,7 @@ def test_lines_of_the_rules():
     assert [local(36, n, 8, 1, 128) for n in (1280, 1281, 1376, 1377, 1408)] == [0, 8, 8, 0, 0]
     assert [local(36, n, 12, 6, 128) for n in (1300, 3071, 3072)] == [0, 0, 2]
     assert [local(36, n, 32, 32, 128) for n in (4096, 7679, 7680)] == [0, 0, 1]
-    # blocks of 256 packed rows, 257 workgroups of 128, 32 tiles a part
+    # blocks of 256 packed rows, 257 workgroups of 128, 64 tiles, 32 a part
+    assert images(4, 512, 32, 8, 128, 64, 1) and not images(4, 512, 32, 8, 128, 63, 1)
     assert images(4, 512, 32, 8, 128, 64, 2) and not images(4, 512, 32, 8, 128, 63, 2) and not images(4, 512, 32, 8, 64, 64, 2)
     assert not images(4, 544, 32, 8, 128, 64, 2) and not images(1, 512, 32, 8, 128, 64, 2)
